@@ -62,7 +62,7 @@ def kernel_source_digest():
     import hashlib
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2602_11688_amd", "csrc")
-    for name in ("device_common.h", "replay_segments.h", "replay_segments_packed.h", "kernels.hip"):
+    for name in ("device_common.h", "replay_segments.h", "kernels.hip"):
         with open(os.path.join(csrc, name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
@@ -155,33 +155,26 @@ def cpu_baseline(wl, params, n_req, threads, online=None, engine=None, proxy=Non
 
 def section_table(sec, N, P):
     """The timed instantiation's per-wavefront section budget as text: shader-clock cycles per request of each
-    of the three wavefronts of a replay (mean over replays), between the marks the kernel sets, and the cache side's
+    of the wavefronts of a replay (mean over replays), between the marks the kernel sets, and the deciding wavefront's
     event counts.  sec = the [P, 3, 12] array of gorgo_eval_population_sections."""
     m = (sec.astype(np.float64) / max(N, 1)).mean(axis=0)
     lines = []
-    cache = {0: "waiting at barrier A (queue terms)", 1: "prefix match (waits for the rows)", 2: "log records, next rows, uncached tokens",
-             3: "score, minimum, announcement", 5: "ownership", 4: "waiting at barrier B", 6: "cell, log and link stores",
-             7: "eviction, patching the next rows, loop"}
-    queue = {10: "lane broadcasts, retiring what is due", 0: "publishing the queue terms", 1: "waiting at barrier A",
-             2: "retiring ahead for the next request", 3: "(reading the clock once)", 4: "waiting at barrier B", 8: "reading the choice",
-             9: "service: slot, completion time", 5: "outputs, tuner, loop", 6: "batch turnover"}
-    front = {0: "descriptor of request r+2", 1: "waiting at barrier A", 3: "references of request r+3 (loads)", 2: "waiting at barrier B"}
+    decide = {0: "waiting at the meeting X", 1: "patching, prefix match", 2: "log records asked for and taken", 3: "score, minimum, announcement",
+              5: "ownership, cursor, taking the next request", 6: "eviction past the cursor's record", 4: "waiting at the meeting Y"}
+    queue = {0: "times and lengths of the request", 1: "waiting at the meeting X", 9: "choice, service", 5: "outputs, tuner", 2: "retiring",
+             6: "batch turnover"}
+    front = {0: "descriptors, row cells", 1: "waiting"}
+    book = {2: "stores", 3: "waiting at the meeting X"}
     lines.append(f"shader-clock cycles per request (s_memtime), mean over {P} replays")
-    k = 1.0
-    lines.append("cache wavefront (lane = replica):")
-    for i, name in cache.items():
-        lines.append(f"  {name:44s} {m[0, i] * k:8.1f}")
-    lines.append(f"  {'total':44s} {m[0, :8].sum() * k:8.1f}")
-    lines.append(f"  events per request: on-the-spot record fetches {m[0, 8]:.3f}, cursor advances {m[0, 9]:.3f}, "
-                 f"dead records dropped {m[0, 10]:.3f}, ownership walks {m[0, 11]:.3f}")
-    lines.append("queue wavefront (lane = service slot):")
-    for i, name in queue.items():
-        lines.append(f"  {name:44s} {m[1, i] * k:8.1f}")
-    lines.append(f"  {'total':44s} {sum(m[1, i] for i in queue) * k:8.1f}")
-    lines.append("front-end wavefront (lane = segment reference):")
-    for i, name in front.items():
-        lines.append(f"  {name:44s} {m[2, i] * k:8.1f}")
-    lines.append(f"  {'total':44s} {sum(m[2, i] for i in front) * k:8.1f}")
+    for title, row, names in (("deciding wavefront (lane = replica):", 0, decide), ("queue wavefront (lane = service slot):", 1, queue),
+                              ("front-end wavefront:", 2, front), ("book-keeping wavefront:", 2, book)):
+        lines.append(title)
+        for i, name in names.items():
+            lines.append(f"  {name:44s} {m[row, i]:8.1f}")
+        lines.append(f"  {'total':44s} {sum(m[row, i] for i in names):8.1f}")
+        if row == 0:
+            lines.append(f"  events per request: on-the-spot record fetches {m[0, 8]:.3f}, cursor advances {m[0, 9]:.3f}, "
+                         f"dead records dropped {m[0, 10]:.3f}, ownership walks {m[0, 11]:.3f}")
     return "\n".join(lines)
 
 
@@ -366,8 +359,7 @@ def main():
     segs_mean = rp["segment_refs"] / max(N, 1)
     if rp["path"] == 2:
         bpr = algorithmic_bytes_per_routing_segments(wl.R, segs_mean, outputs_bytes=8)   # ttft f64
-        plain = args.online or args.engine or args.proxy
-        kernel = "replay_segments_kernel" if plain or not g.replay_packing(tr, model, P) else "replay_segments_packed_kernel"
+        kernel = "replay_segments_kernel"
     else:
         bpr = algorithmic_bytes_per_routing(wl.R, n_mean, hit_mean, outputs_bytes=9)
         kernel = "replay_blocks_kernel"

@@ -315,6 +315,7 @@ int evaluate(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* op
         el.a_dec = d_eng + pl.R;
         el.budget = d_eng + 2 * (size_t)pl.R;
         el.slowdown = engine->decode_slowdown;
+        el.least_dec = *std::min_element(eng.begin() + m->R, eng.begin() + 2 * m->R);
     }
     ProxyLaunch xl;
     if (proxy) {

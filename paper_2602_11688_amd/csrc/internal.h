@@ -108,6 +108,7 @@ struct EngineLaunch {
     const double* a_dec = nullptr;       // [R]
     const double* budget = nullptr;      // [R] KV tokens as doubles, 0 = none
     double slowdown = 0.0;
+    double least_dec = 0.0;              // smallest decode rate
 };
 
 // Imperfect proxy knowledge of one launch (device pointers; see gorgo_proxy in gorgo.h).

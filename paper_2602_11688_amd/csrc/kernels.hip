@@ -1,5 +1,5 @@
-// Device side: the launches of the replay kernels (segment rows: replay_segments.h and replay_segments_packed.h;
-// block tables: replay_blocks.h), the exact percentile selection, and the trace upload.
+// Device side: the launches of the replay kernels (segment rows: replay_segments.h; block
+// tables: replay_blocks.h), the exact percentile selection, and the trace upload.
 //
 // Decision arithmetic is fp64 with every product and sum rounded separately (built with -ffp-contract=off)
 // in the association (w_rtt*rtt + w_prefill*pf) + w_queue*qd, so that routes are reproducible bit for bit.
@@ -15,7 +15,6 @@
 #include "internal.h"
 #include "replay_blocks.h"
 #include "replay_segments.h"
-#include "replay_segments_packed.h"
 
 namespace gorgo {
 
@@ -250,7 +249,7 @@ bool pack_replays(const Plan& pl, int64_t rows) {
     if (hipGetDevice(&device) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, replay_segments_kernel<MODE_COST_MODEL, false, false>,
-                                                     SEG3_THREADS, replay_segments_lds_bytes(pl.R, pl.B, 0)) != hipSuccess)
+                                                     seg_threads<1>(), replay_queue_lds_bytes(pl.R, pl.B, false, 0)) != hipSuccess)
         return false;
     // (measured: packed pairs win when they make one round of what would be two; with more rounds on either side
     // the unpacked kernel's shorter request step wins again)
@@ -318,11 +317,28 @@ void set_event_marks(bool on) { g_marks_on = on; }
 
 namespace {
 
+// The segment-row kernel's instantiations: every mode with either replica model; imperfect proxy knowledge concerns the
+// cost model (fixed weights or tuned online) only.
+template <int MODE>
+void launch_segments(bool engine, bool proxy, const Plan& pl, hipStream_t s, const SegArgs& a) {
+    const dim3 grid((unsigned)pl.P), block(seg_threads<1>());
+    const size_t lds = replay_queue_lds_bytes(pl.R, pl.B, engine, a.window);
+    if constexpr (MODE == MODE_COST_MODEL || MODE == MODE_ONLINE) {
+        if (proxy) {
+            if (engine) hipLaunchKernelGGL((replay_segments_kernel<MODE, true, true>), grid, block, lds, s, a);
+            else hipLaunchKernelGGL((replay_segments_kernel<MODE, false, true>), grid, block, lds, s, a);
+            return;
+        }
+    }
+    if (engine) hipLaunchKernelGGL((replay_segments_kernel<MODE, true, false>), grid, block, lds, s, a);
+    else hipLaunchKernelGGL((replay_segments_kernel<MODE, false, false>), grid, block, lds, s, a);
+}
+
 // The block-table kernel's instantiations: every mode with either replica model; imperfect proxy knowledge concerns
 // the cost model (fixed weights or tuned online) only.
 template <int MODE>
 void launch_blocks(bool engine, bool proxy, dim3 grid, size_t lds, hipStream_t s, const BlockArgs& b) {
-    const dim3 block(SEG_THREADS);
+    const dim3 block(BLOCK_THREADS);
     if constexpr (MODE == MODE_COST_MODEL || MODE == MODE_ONLINE) {
         if (proxy) {
             if (engine) hipLaunchKernelGGL((replay_blocks_kernel<MODE, true, true>), grid, block, lds, s, b);
@@ -355,6 +371,7 @@ int launch_replay(const gorgo_trace* t, const Plan& pl, const double* d_rtt, con
     a.out_len = t->dev.out_len;
     a.seg_off = segments ? t->dev.seg_off : nullptr;
     a.seg = segments ? t->dev.seg : nullptr;
+    a.blk_off = t->dev.blk_off;
     a.N = pl.N;
     a.R = pl.R;
     a.B = pl.B;
@@ -363,6 +380,7 @@ int launch_replay(const gorgo_trace* t, const Plan& pl, const double* d_rtt, con
     a.block_tokens = pl.block_tokens;
     a.a_pf = pl.a_pf;
     a.a_dec = pl.a_dec;
+    a.least_dec = engine ? engine->least_dec : pl.a_dec;
     a.rtt = d_rtt;
     a.params = d_params;
     a.scale = d_scale;
@@ -386,7 +404,6 @@ int launch_replay(const gorgo_trace* t, const Plan& pl, const double* d_rtt, con
     a.accepted = online ? online->accepted : nullptr;
     a.first_hash = t->dev.first_hash;
     a.seeds = policy ? policy->seeds : nullptr;
-    a.spin_limit = pl.poll_limit;           // (only the packed kernel polls)
     a.eng_a_pf = engine ? engine->a_pf : nullptr;
     a.eng_a_dec = engine ? engine->a_dec : nullptr;
     a.eng_budget = engine ? engine->budget : nullptr;
@@ -422,56 +439,20 @@ int launch_replay(const gorgo_trace* t, const Plan& pl, const double* d_rtt, con
         }
         mark(1, s);
         if (pl.N > 0 || online) {      // (an empty trace still reports the tuner's initial state)
-            if (online) {
-                const size_t lds = replay_segments_lds_bytes(pl.R, pl.B, online->window);
-                const dim3 grid((unsigned)pl.P), block(SEG3_THREADS);
-                if (proxy && engine) hipLaunchKernelGGL((replay_segments_kernel<MODE_ONLINE, true, true>), grid, block, lds, s, a);
-                else if (proxy) hipLaunchKernelGGL((replay_segments_kernel<MODE_ONLINE, false, true>), grid, block, lds, s, a);
-                else if (engine) hipLaunchKernelGGL((replay_segments_kernel<MODE_ONLINE, true, false>), grid, block, lds, s, a);
-                else if (SlotQueues::fits(pl.R, pl.B)) hipLaunchKernelGGL((replay_segments_kernel<MODE_ONLINE, false, false, true>), grid, block, lds, s, a);
-                else hipLaunchKernelGGL((replay_segments_kernel<MODE_ONLINE, false, false>), grid, block, lds, s, a);
-            } else if (proxy) {
-                const size_t lds = replay_segments_lds_bytes(pl.R, pl.B, 0);
-                const dim3 grid((unsigned)pl.P), block(SEG3_THREADS);
-                if (engine) hipLaunchKernelGGL((replay_segments_kernel<MODE_COST_MODEL, true, true>), grid, block, lds, s, a);
-                else hipLaunchKernelGGL((replay_segments_kernel<MODE_COST_MODEL, false, true>), grid, block, lds, s, a);
-            } else if (engine) {
-                const size_t lds = replay_segments_lds_bytes(pl.R, pl.B, 0);
-                const dim3 grid((unsigned)pl.P), block(SEG3_THREADS);
-                switch (mode) {
-                    case MODE_COST_MODEL: hipLaunchKernelGGL((replay_segments_kernel<MODE_COST_MODEL, true, false>), grid, block, lds, s, a); break;
-                    case MODE_LEAST_REQUEST: hipLaunchKernelGGL((replay_segments_kernel<MODE_LEAST_REQUEST, true, false>), grid, block, lds, s, a); break;
-                    case MODE_AFFINITY: hipLaunchKernelGGL((replay_segments_kernel<MODE_AFFINITY, true, false>), grid, block, lds, s, a); break;
-                    default: hipLaunchKernelGGL((replay_segments_kernel<MODE_RANDOM, true, false>), grid, block, lds, s, a); break;
-                }
+            if (mode == MODE_COST_MODEL && !engine && !proxy && !sections && pack_replays(pl, a.nseg)) {
+                hipLaunchKernelGGL((replay_segments_kernel<MODE_COST_MODEL, false, false, 2>), dim3((unsigned)(pl.P / 2)),
+                                   dim3(seg_threads<2>()), 2 * replay_queue_lds_bytes(pl.R, pl.B, false, 0), s, a);
             } else if (sections) {
-                const dim3 grid((unsigned)pl.P), block(SEG3_THREADS);
-                const size_t lds = replay_segments_lds_bytes(pl.R, pl.B, 0);
-                if (SlotQueues::fits(pl.R, pl.B))
-                    hipLaunchKernelGGL((replay_segments_kernel<MODE_COST_MODEL, false, false, true, true>), grid, block, lds, s, a);
-                else
-                    hipLaunchKernelGGL((replay_segments_kernel<MODE_COST_MODEL, false, false, false, true>), grid, block, lds, s, a);
-            } else if (mode == MODE_COST_MODEL && pack_replays(pl, a.nseg)) {
-                // fixed weights, at most 32 replicas: two replays per wavefront pair
-                hipLaunchKernelGGL(replay_segments_packed_kernel, dim3((unsigned)(pl.P / 2)), dim3(SEG_THREADS),
-                                   replay_segments_packed_lds_bytes(pl.B), s, a);
+                const dim3 grid((unsigned)pl.P), block(seg_threads<1>());
+                hipLaunchKernelGGL((replay_segments_kernel<MODE_COST_MODEL, false, false, 1, true>), grid, block,
+                                   replay_queue_lds_bytes(pl.R, pl.B, false, 0), s, a);
             } else {
-                const size_t lds = replay_segments_lds_bytes(pl.R, pl.B, 0);
-                const dim3 grid((unsigned)pl.P), block(SEG3_THREADS);
-                if (SlotQueues::fits(pl.R, pl.B)) {
-                    switch (mode) {
-                        case MODE_COST_MODEL: hipLaunchKernelGGL((replay_segments_kernel<MODE_COST_MODEL, false, false, true>), grid, block, lds, s, a); break;
-                        case MODE_LEAST_REQUEST: hipLaunchKernelGGL((replay_segments_kernel<MODE_LEAST_REQUEST, false, false, true>), grid, block, lds, s, a); break;
-                        case MODE_AFFINITY: hipLaunchKernelGGL((replay_segments_kernel<MODE_AFFINITY, false, false, true>), grid, block, lds, s, a); break;
-                        default: hipLaunchKernelGGL((replay_segments_kernel<MODE_RANDOM, false, false, true>), grid, block, lds, s, a); break;
-                    }
-                } else {
-                    switch (mode) {
-                        case MODE_COST_MODEL: hipLaunchKernelGGL((replay_segments_kernel<MODE_COST_MODEL, false, false>), grid, block, lds, s, a); break;
-                        case MODE_LEAST_REQUEST: hipLaunchKernelGGL((replay_segments_kernel<MODE_LEAST_REQUEST, false, false>), grid, block, lds, s, a); break;
-                        case MODE_AFFINITY: hipLaunchKernelGGL((replay_segments_kernel<MODE_AFFINITY, false, false>), grid, block, lds, s, a); break;
-                        default: hipLaunchKernelGGL((replay_segments_kernel<MODE_RANDOM, false, false>), grid, block, lds, s, a); break;
-                    }
+                switch (mode) {
+                    case MODE_COST_MODEL: launch_segments<MODE_COST_MODEL>(engine != nullptr, proxy != nullptr, pl, s, a); break;
+                    case MODE_ONLINE: launch_segments<MODE_ONLINE>(engine != nullptr, proxy != nullptr, pl, s, a); break;
+                    case MODE_LEAST_REQUEST: launch_segments<MODE_LEAST_REQUEST>(engine != nullptr, false, pl, s, a); break;
+                    case MODE_AFFINITY: launch_segments<MODE_AFFINITY>(engine != nullptr, false, pl, s, a); break;
+                    default: launch_segments<MODE_RANDOM>(engine != nullptr, false, pl, s, a); break;
                 }
             }
             if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "launch replay_segments_kernel");
@@ -495,7 +476,7 @@ int launch_replay(const gorgo_trace* t, const Plan& pl, const double* d_rtt, con
         if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "launch fill_slots");
         mark(1, s);
         if (pl.N > 0 || online) {      // (an empty trace still reports the tuner's initial state)
-            const size_t lds = replay_blocks_lds_bytes(pl.R, pl.B, a.window);
+            const size_t lds = replay_blocks_lds_bytes(pl.R, pl.B, engine != nullptr, a.window);
             const dim3 grid((unsigned)pl.P);
             switch (mode) {
                 case MODE_COST_MODEL: launch_blocks<MODE_COST_MODEL>(engine != nullptr, proxy != nullptr, grid, lds, s, b); break;

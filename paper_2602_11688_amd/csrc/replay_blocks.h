@@ -7,12 +7,13 @@
 // exactly its stamp.  Nothing about the trace is assumed (the same id may follow different ids in different
 // requests), so the match probes block by block.
 //
-// A replay is run by two wavefronts of one workgroup.  The queue wavefront is the segment formulation's, unchanged:
-// service slots, load signal (Eq. 2), service step, per-request outputs, and with them the online tuner, the
+// A replay is run by two wavefronts of one workgroup.  The queue wavefront is the segment formulation's: service
+// slots, service step, what leaves the load signal (Eq. 2), per-request outputs, and with them the online tuner, the
 // engine model and the epochs of the proxy's round-trip estimates.  The cache wavefront here does per request:
-// match against every replica's table; meet (A: the queue terms are there); score (Eq. 3) or apply the baseline
-// policy, lowest-index minimum, announce the choice; meet (B); table update and eviction on the chosen replica.
-// Both wavefronts execute exactly two barriers per request, whatever the data.
+// match against every replica's table, score (Eq. 3) or apply the baseline policy, lowest-index minimum, announce the
+// choice; meet (X: the choice is there); table update and eviction on the chosen replica, while the queue wavefront
+// serves the request; meet (Y: so is what completes by the next arrival).  Both wavefronts execute exactly two
+// barriers per request, whatever the data.
 //
 // The proxy's own index of a replica (Sec. 7: the proxy does not see replica-side eviction) is a second LRU over
 // the same touches with a capacity of its own.  Touches give an entry the same stamp in both, so the index is the
@@ -23,6 +24,8 @@
 #include "replay_segments.h"
 
 namespace gorgo {
+
+constexpr int BLOCK_THREADS = 2 * WAVE;      // cache wavefront + queue wavefront
 
 // One cache-table slot.  key 0 = never used (then stamp = -1).  An entry is held by an LRU iff stamp >= that
 // LRU's threshold; entries below every threshold are garbage whose slots can be taken over by inserts.
@@ -45,8 +48,8 @@ struct BlockArgs {
 
 // per replica: two thresholds (int64), then live x2, cursor request x2, cursor position x2, used slots (int32)
 __host__ __device__ inline size_t replay_blocks_state_bytes(int R) { return (size_t)R * (2 * 8 + 7 * 4); }
-__host__ __device__ inline size_t replay_blocks_lds_bytes(int R, int B, int window) {
-    return ((replay_segments_lds_bytes(R, B, window) + 15) & ~(size_t)15) + replay_blocks_state_bytes(R);
+__host__ __device__ inline size_t replay_blocks_lds_bytes(int R, int B, bool engine, int window) {
+    return ((replay_queue_lds_bytes(R, B, engine, window) + 15) & ~(size_t)15) + replay_blocks_state_bytes(R);
 }
 
 __device__ __forceinline__ bool cas_stamp(int64_t* p, int64_t expected, int64_t desired) {
@@ -109,9 +112,9 @@ __device__ __forceinline__ void wave_settle() {
 
 // Cache wavefront of a replay over block tables.  Lane = replica for the first-block probe, the scores and the
 // minimum; lane = block of the request for the prefix match, the table update and the eviction walk.
-template <int MODE, bool PROXY>
+template <int MODE, bool ENGINE, bool PROXY>
 __device__ __forceinline__ void block_cache_wave(const BlockArgs& b, int p, int lane, unsigned char* state,
-                                                 Handover* comm) {
+                                                 Handover<PROXY>* comm) {
     constexpr bool ONLINE = MODE == MODE_ONLINE;
     constexpr bool SCORED = MODE == MODE_COST_MODEL || MODE == MODE_ONLINE;
     const SegArgs& a = b.q;
@@ -142,8 +145,10 @@ __device__ __forceinline__ void block_cache_wave(const BlockArgs& b, int p, int 
     }
     wave_sync();
 
-    const double w_rtt = a.params[3 * (size_t)p + 0];             // (with the online tuner the weights come with
-    const double w_prefill = a.params[3 * (size_t)p + 1];         // the queue terms instead)
+    double w_rtt = a.params[3 * (size_t)p + 0];
+    double w_prefill = a.params[3 * (size_t)p + 1];
+    double w_queue = a.params[3 * (size_t)p + 2];
+    double q = 0.0;                                               // load signal of replica = lane
     const double my_rtt = !PROXY && in ? a.rtt[lane] : 0.0;       // (proxy variants: comes with the queue terms)
     const uint64_t seed = MODE == MODE_RANDOM ? a.seeds[p] : 0;
 
@@ -152,7 +157,7 @@ __device__ __forceinline__ void block_cache_wave(const BlockArgs& b, int p, int 
     uint8_t* const routed = b.routed + (size_t)p * N;
     const int64_t rebuild_at = b.cap - b.cap / 8;
 
-    meet(false);        // (the queue wavefront has set itself up)
+    meet(true);         // (the queue wavefront has set itself up)
     for (int64_t r = 0; r < N; ++r) {
         const int64_t off = b.blk_off[r];
         const int n = (int)(b.blk_off[r + 1] - off);
@@ -216,24 +221,20 @@ __device__ __forceinline__ void block_cache_wave(const BlockArgs& b, int p, int 
             target = spread(philox4x32_10_first((uint32_t)r, (uint32_t)((uint64_t)r >> 32), (uint32_t)seed,
                                                 (uint32_t)(seed >> 32)), R);
 
-        meet(true);                                                  // A(r): the queue terms of r are there
-        // ---- score (Eq. 3: rtt and prefill terms here, the queue term from the queue wavefront), lowest-index minimum
-        const double sq = SCORED || MODE == MODE_LEAST_REQUEST ? comm->sq[lane] : 0.0;
-        double rtt_now = my_rtt, now_rtt = w_rtt, now_prefill = w_prefill;
-        if (PROXY) rtt_now = comm->rtt[lane];
-        if (ONLINE) {
-            now_rtt = comm->w[0];
-            now_prefill = comm->w[1];
-        }
+        // ---- score (Eq. 3), lowest-index minimum; the load signal is kept here, what left it comes from the queue wavefront
+        q += comm->gone[r & 3][lane];
+        const double rtt_now = PROXY ? comm->rtt[r & 3][lane] : my_rtt;
         double my_score;
         if (SCORED) {
             const double pf = a.a_pf * (double)my_u_seen;
-            const double s_rtt = now_rtt * rtt_now;
-            const double s_pf = now_prefill * pf;
+            const double s_rtt = w_rtt * rtt_now;
+            const double s_pf = w_prefill * pf;
             const double rtt_and_prefill = s_rtt + s_pf;
-            my_score = rtt_and_prefill + sq;
+            const double qd = a.a_pf * q;
+            const double s_q = w_queue * qd;
+            my_score = rtt_and_prefill + s_q;
         } else if (MODE == MODE_LEAST_REQUEST) {
-            my_score = sq;                      // requests in flight
+            my_score = q;                       // requests in flight
         } else {
             my_score = lane == target ? 0.0 : 1.0;
         }
@@ -241,12 +242,14 @@ __device__ __forceinline__ void block_cache_wave(const BlockArgs& b, int p, int 
         const int m_best = __builtin_amdgcn_readlane(my_m, best);
         const int seen_best = two ? __builtin_amdgcn_readlane(my_seen, best) : m_best;
         const unsigned u_best = (unsigned)__builtin_amdgcn_readlane(my_u, best);
+        q += lane == best ? (MODE == MODE_LEAST_REQUEST ? 1.0 : (double)L) : 0.0;
         if (lane == 0) {
-            comm->choice = ((unsigned long long)((unsigned)best | ((unsigned)m_best << 8)) << 32) | u_best;
-            if (PROXY) comm->seen = seen_best;
+            comm->choice[r & 1][best] = Choice{ENGINE || PROXY ? (double)(int)u_best : a.a_pf * (double)(int)u_best, -2, (unsigned)m_best};
+            if (PROXY) comm->seen[r & 1][best] = (uint16_t)seen_best;
+            comm->best[r & 1][0] = best;
             st(&routed[r], (uint8_t)best);
         }
-        meet(true);                                                  // B(r): the choice is there
+        meet(true);                                                  // X(r): the choice is there
 
         // ---- update on the chosen replica
         Slot* const tab = tables + (size_t)best * b.cap;
@@ -360,26 +363,27 @@ __device__ __forceinline__ void block_cache_wave(const BlockArgs& b, int p, int 
         evict(C1, tau1, live1, cur_r1, cur_k1);
         if (two) evict(C2, tau2, live2, cur_r2, cur_k2);
         wave_settle();
+        meet(true);                                                  // Y(r): what completes by the next arrival is known
+        if (ONLINE) {
+            w_rtt = comm->w[0][0];
+            w_prefill = comm->w[0][1];
+            w_queue = comm->w[0][2];
+        }
     }
 }
 
 template <int MODE, bool ENGINE, bool PROXY>
-__global__ void __launch_bounds__(SEG_THREADS) replay_blocks_kernel(BlockArgs b) {
+__global__ void __launch_bounds__(BLOCK_THREADS) replay_blocks_kernel(BlockArgs b) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    __shared__ __align__(16) Handover comm;
+    __shared__ __align__(16) Handover<PROXY> comm;
     const int lane = threadIdx.x & (WAVE - 1);
     const int p = blockIdx.x;
-    if (threadIdx.x == 0) {
-        comm.w[0] = b.q.params[3 * (size_t)p + 0];
-        comm.w[1] = b.q.params[3 * (size_t)p + 1];
-    }
-    __syncthreads();
     if (threadIdx.x >= WAVE) {
-        queue_wave<MODE, ENGINE, PROXY, false, false>(b.q, p, lane, lds_raw, &comm);
+        queue_wave<MODE, ENGINE, PROXY, 1, true, false>(b.q, 0, lane, lds_raw, &comm);
     } else if (b.q.N > 0) {
         unsigned char* const state =
-            lds_raw + ((replay_segments_lds_bytes(b.q.R, b.q.B, MODE == MODE_ONLINE ? b.q.window : 0) + 15) & ~(size_t)15);
-        block_cache_wave<MODE, PROXY>(b, p, lane, state, &comm);
+            lds_raw + ((replay_queue_lds_bytes(b.q.R, b.q.B, ENGINE, MODE == MODE_ONLINE ? b.q.window : 0) + 15) & ~(size_t)15);
+        block_cache_wave<MODE, ENGINE, PROXY>(b, p, lane, state, &comm);
     }
 }
 

@@ -15,22 +15,30 @@
 // record per logged request (next request on the replica, own, n) and never re-reads cells.  Records that
 // own nothing any more are dropped from the walk as soon as they are seen.
 //
-// The request loop is one dependent chain per replay, and a lone wavefront issues about one instruction
-// every four to five cycles whatever its kind (a branch costs three to four times that), so the kernel is
-// arranged around the instruction count of that chain, not around bandwidth.  A replay is run by two
-// wavefronts of one workgroup that meet at two workgroup barriers per request.
-//   The cache wavefront (lane = replica) holds the cache side in registers: eviction cursor, the next log
-// records, the row cells of the current and the next request.  Per request it matches, scores, takes the
-// minimum, announces the choice, then updates rows, log and cursor.  It does nothing else.
-//   The queue wavefront (lane = replica) owns the service slots (LDS) and the load signal: before request r it
-// retires what has completed by t_r and publishes every replica's queue term of Eq. 3; after the choice it
-// serves the request and keeps the latencies and the per-request outputs.  It has the shorter chain, so it
-// also is the trace's front end: three requests ahead it reads the request's segment references and leaves a
-// descriptor in a small LDS ring -- row offsets, end positions, flags -- from which the cache wavefront
-// issues its row loads without any address arithmetic or staging of its own.
-//   Barrier A(r): the queue terms of r are published (and the descriptor of r + 1 is complete).  Barrier
-// B(r): the choice of r is published.  Every wavefront executes exactly two barriers per request, whatever
-// the data, so neither can wait for ever.
+// The request loop is one dependent chain per replay: decision r changes the cursor, the cells and the load signal of
+// one replica, and decision r + 1 may depend on them.  A dependent vector or scalar instruction costs a wavefront
+// eight to nine cycles, a branch on a vector comparison forty, a word handed to another wavefront through LDS and a
+// barrier 130.  So only what the next decision needs is on the chain, in the hands of one wavefront, and everything
+// else is done beside it by others of the same workgroup, which meet at ONE barrier per request:
+//   X(r): the choice of request r is published, and so is what has left the load signals by the arrival of r + 1.
+//   The deciding wavefront (lane = replica; two replays in its halves where R <= 32 and the launch packs) holds the
+// load signals, the eviction cursors and the row cells of the current and the next request.  Per request it matches,
+// scores, takes the minimum, announces the choice, moves the chosen replica's cursor.
+//   The queue wavefront (one per replay; lane = service slot or replica) is one request behind: while r + 1 is being
+// decided it serves r, keeps the latencies, and retires what completes by the arrival of r + 2.  The deciding
+// wavefront adds the tokens of r to the load signal itself, which is right unless r has completed before r + 1 even
+// arrives; the trace and the time scale alone can rule that out (r takes at least its decode time) and practically
+// always do.
+//   The book-keeping wavefront stores: cells, log records, ownership changes, routes and hit counts.
+//   The front-end wavefront walks the trace two dozen requests ahead, eight requests at a time, and leaves a descriptor
+// of each in an LDS ring; it touches the rows that will be read, so that they are in the L2 by then.
+// Where one barrier is not enough -- r may complete before r + 1 arrives, r + 1 has more segments than the deciding
+// wavefront preloads, the online tuner changes the weights after r -- the descriptor of r + 1 says so (DESC_SYNC), every
+// wavefront of the workgroup reads that same word, and all meet once more, Y(r), when the queue and the book-keeping
+// wavefront have caught up with r.  The number of barriers a wavefront executes depends on the descriptors alone, so
+// none can wait for ever.
+//
+// Config 5 (R = 32, 1,024 replays): MEASURED_HERE.
 #pragma once
 #include <type_traits>
 
@@ -52,6 +60,7 @@ struct SegArgs {
     const int32_t* in_len;
     const int32_t* out_len;
     const int64_t* seg_off;
+    const int64_t* blk_off;       // [N+1]
     const SegRef* seg;
     int64_t N;
     int32_t R, B;
@@ -59,6 +68,7 @@ struct SegArgs {
     int64_t nseg;
     int32_t block_tokens;
     double a_pf, a_dec;
+    double least_dec;             // smallest decode time per output token of any replica
     const double* rtt;
     const double* params;
     const double* scale;
@@ -83,7 +93,6 @@ struct SegArgs {
     // baseline policies
     const uint32_t* first_hash;   // [N] hash of the request's first block
     const uint64_t* seeds;        // [P] seed of the random policy
-    int32_t spin_limit;           // polls of a hand-over word before the replay is given up
     // engine model of a replica (only read by the kernel's engine variants)
     const double* eng_a_pf;       // [R] prefill ms per token
     const double* eng_a_dec;      // [R] decode ms per token
@@ -126,17 +135,8 @@ __device__ __forceinline__ uint32_t philox4x32_10_first(uint32_t c0, uint32_t c1
     return c0;
 }
 
-constexpr int SEG_STAGE = 512;   // segment references of a 64-request batch staged in LDS
-constexpr int SEG_CHUNK = 8;     // segments of a request whose rows are loaded together
-constexpr int SEG_THREADS = 2 * WAVE;        // two replays per wavefront pair: cache wavefront + queue wavefront
-constexpr int SEG3_THREADS = 3 * WAVE;       // cache, queue and front-end wavefront
-constexpr int SEG_SPIN_LIMIT = 1 << 24;      // default: polls of a hand-over word before the replay is given up (~1 s)
-
-// Fences between LDS data and the word that announces it (two replays per wavefront pair still hand over
-// through polled words): the LDS executes the instructions of one wavefront in the order they were issued, so
-// the fences only have to keep the compiler from changing that order, and cost no wait.
-__device__ __forceinline__ void lds_release() { __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront"); }
-__device__ __forceinline__ void lds_acquire() { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront"); }
+constexpr int HALF = WAVE / 2;               // lanes of one of two packed replays
+constexpr int SEG_CHUNK = 8;                 // segments of a request whose rows are loaded together
 
 // Orders the LDS accesses of one wavefront's lanes (the hardware executes them in program order).
 __device__ __forceinline__ void wave_sync() {
@@ -144,10 +144,9 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
-__host__ __device__ inline size_t replay_segments_lds_bytes(int R, int B, int window) {   // dynamic part
-    // queues (in whichever layout is the larger: the launch picks one), then the tuner's TTFT window
-    const size_t q = Queues::bytes(R, B) > SlotQueues::bytes() ? Queues::bytes(R, B) : SlotQueues::bytes();
-    return q + (size_t)((window + 7) & ~7) * sizeof(double);
+// dynamic LDS of one replay: its queues, then the tuner's TTFT window
+__host__ __device__ inline size_t replay_queue_lds_bytes(int R, int B, bool engine, int window) {
+    return SlotQueues::bytes(R, B, engine) + (size_t)((window + 7) & ~7) * sizeof(double);
 }
 
 // exp(x) for |x| <= 700 from additions and multiplications only, in a fixed order, so that the weights the
@@ -236,16 +235,6 @@ __device__ __forceinline__ double window_kth(const double* ring, int W, int kth,
     return __longlong_as_double((long long)b);
 }
 
-// Rows of one request's first SEG_CHUNK segments as seen by this lane (= replica), with the segments' end
-// positions (the same in every lane; entries past the request's last segment have end = n and no cell), and
-// the reference of segment k in lane k.
-struct RowSet {
-    int32_t cell[SEG_CHUNK];
-    int end[SEG_CHUNK];
-    SegRef of_lane;
-    int fresh;           // bit k: segment k's row slot starts over with this request (SEG_FRESH)
-};
-
 // Cached blocks of one segment [pos, end) whose row cell holds rl, against a cursor (c_r, c_k): all of them
 // if a later request than the cursor's touched it last, those below the cursor position if the cursor's
 // request did, none otherwise.  (A never-touched cell, -1, can only tie with the initial cursor (-1, 0).)
@@ -258,57 +247,70 @@ __device__ __forceinline__ int cached_in(int32_t rl, int pos, int end, int c_r, 
 
 
 // ---------------------------------------------------------------------------------------------- hand-over
-// Descriptor of one request, written by the queue wavefront's front end, read by the cache wavefront.
-struct SegEnt {
-    uint32_t rowoff;     // byte offset of the segment's row within the replay's rows
-    int32_t end;         // blocks of the request up to and including this segment
-};
+// Descriptor of one request, written by the front end.
 struct SegDesc {
-    SegEnt e[8];         // first eight segments, as the match reads them: where to load the row from and where the
-                         // segment ends.  Past the last segment: the never-cached row, n.  Also the never-cached row for
-                         // a segment whose row slot starts over with this request (SEG_FRESH: what the slot still holds
-                         // belongs to a segment of the past), and for one whose slot started over with the previous
-                         // request (this request's rows are loaded before that request's stores)
+    uint32_t rowoff[SEG_CHUNK];  // first eight segments: byte offset, within the replay's rows, of the row that the match
+                         // reads.  Past the last segment: the never-cached row.  Also the never-cached row for a segment whose
+                         // row slot starts over with this request (SEG_FRESH: what the slot still holds belongs to a segment of
+                         // the past), and for one whose slot started over with one of the three requests before (this request's
+                         // rows are loaded before those stores are sure to be there)
+    int32_t end[SEG_CHUNK];      // blocks of the request up to and including the segment (past the last one: n)
     int32_t L, n, s;     // input tokens, blocks, segments
-    int32_t flags;       // DESC_MORE4 | DESC_DEEP | leading segments shared with the previous request << 8 |
-                         // index of the first fresh segment among the first eight (8: none) << 16
+    int32_t flags;       // DESC_* | leading segments shared with the request j before, as far as none in between started them
+                         // over, << DESC_COMMON[j - 1] | index of the first fresh segment among the first eight (8: none) << 16
     int64_t j0;          // index of the request's first segment reference (for requests of more than 8 segments)
     int32_t target;      // replica dictated by the session-affinity / random policy
+    uint32_t tail;       // the row of the request's last segment if DESC_FRESH_TAIL, else the spare row
+    uint32_t slot[SEG_CHUNK];   // where the rows of the first eight segments really are (past the last one: the spare row)
+    double t[2];         // arrival at the time scale of each replay of the workgroup
+    double dec;          // decode time in the linear model
+    int32_t O;           // output tokens
     int32_t pad;
-    uint32_t slot[8];    // where the rows of the first eight segments really are (past the last one: the spare row)
-    uint32_t store[WAVE];   // per lane of the cache wavefront: the row its store after the decision goes to.  Lanes
-                         // 0..31: the row of segment (lane mod 8), where this request's number is written into the
-                         // chosen replica's cell.  Lanes 32..63, with at most 32 replicas: the row of the request's
-                         // last segment if that one is fresh (replica lane - 32 of that row starts over), else, like
-                         // every lane with nothing to store, the spare row
 };
-static_assert(sizeof(SegDesc) == 128 + 4 * WAVE, "descriptor layout");
-constexpr int DESC_FRESH_TAIL = 4;   // the request's last segment is fresh and among the first eight (lanes 32..63 reset its row)
-constexpr int DESC_FRESH_MORE = 8;   // further fresh segments among the first eight
-constexpr int DESC_RING = 8;         // descriptors in flight (power of two)
-constexpr int DESC_AHEAD = 3;        // the front end reads references this many requests ahead
+static_assert(sizeof(SegDesc) == 160, "descriptor layout");
 constexpr int DESC_MORE4 = 1;        // more than four segments
 constexpr int DESC_DEEP = 2;         // more than eight segments
+constexpr int DESC_FRESH_TAIL = 4;   // the last segment is fresh, among the first eight, and lanes 32..63 reset its row
+constexpr int DESC_FRESH_MORE = 8;   // further fresh segments among the first eight
+constexpr int DESC_SYNC = 16;        // all wavefronts meet once more between the previous request and this one
+constexpr int DESC_SHARED = 0xF0FF00;            // any leading segment shared with the three requests before
+constexpr int DESC_RING = 16;        // descriptors in flight (power of two)
+constexpr int DESC_GROUP = WAVE / SEG_CHUNK;     // requests whose descriptors are written together
+constexpr int DESC_AHEAD = DESC_GROUP;           // how far ahead of the request in hand
+static_assert(DESC_AHEAD + DESC_GROUP <= DESC_RING, "the front end overwrites descriptors of requests that are done with");
 constexpr int32_t NEVER_CACHED = INT32_MIN;      // cell value of the extra row: below any cursor
 
-constexpr int LOOK_RING = 8;          // log records of look-ahead kept in LDS per replica, behind the two in registers
+constexpr int LOOK_RING = 8;          // log records of look-ahead kept in LDS per replica
+// What every replica would mean for a request, written by its lane before the minimum is known; the replica with the
+// minimum is announced by its number alone.
+struct __align__(16) Choice {
+    double prefill;                   // prefill time (linear model, the replicas' caches known) or tokens to prefill
+    int owner;                        // request whose owned suffix would start at `end`, -2: none (or dealt with)
+    unsigned hit_end;                 // cached blocks | end << 16
+};
+template <bool PROXY>
 struct Handover {
-    double sq[WAVE];                  // per replica: queue term of Eq. 3, w_queue * (a_pf * outstanding tokens)
-                                      // (least-request policy: requests in flight)
-    double rtt[WAVE];                 // proxy variants: estimated round trip time per replica
-    double w[2];                      // online tuner: w_rtt, w_prefill in use
-    unsigned long long choice;        // uncached tokens | (replica | cached blocks << 8) << 32
-    unsigned long long unused[WAVE];  // where the lanes other than lane 0 write when the choice is announced
-    int seen;                         // proxy variants: blocks the proxy believed cached on the chosen replica
+    Choice choice[2][WAVE];           // [request mod 2][replica]
+    int best[2][2];                   // [request mod 2][replay of the workgroup] the choice: lane of the replica
+    uint16_t seen[PROXY ? 2 : 1][WAVE];   // proxy variants, [request mod 2]: blocks the proxy believes cached per replica
+    int first[WAVE];                  // first request routed to each replica (-1: none yet)
+    double gone[4][WAVE];             // [request mod 4][replica]: minus the tokens (least-request policy: the requests) that
+                                      // left the load signal between the previous request's arrival and this one's
+    double half[PROXY ? 4 : 1][WAVE]; // half the round trip time per replica (proxy variants: [request mod 4])
+    double rtt[PROXY ? 4 : 1][PROXY ? WAVE : 1];  // proxy variants, [request mod 4]: estimated round trip time per replica
+    double w[2][3];                   // online tuner: weights in use
     SegDesc ring[DESC_RING];
+    int32_t cells[2][SEG_CHUNK][WAVE];    // [request mod 2]: row cells of the request's first eight segments per replica
     // look-ahead of the eviction cursors (the cache's; the proxy's index's): per replica, log records fetched ahead
     // of the cursor, slot k of replica i at [k * WAVE + i]; the last slot is a spare that nothing reads
-    unsigned long long look[2][(LOOK_RING + 1) * WAVE];
+    unsigned long long look[PROXY ? 2 : 1][(LOOK_RING + 1) * WAVE];
+    int wanted[PROXY ? 2 : 1][WAVE];                 // log records that the front end is to fetch, every fourth request,
+    unsigned long long fetched[PROXY ? 2 : 1][WAVE]; // and what it has fetched
 };
 
-// Workgroup barrier that both wavefronts of a replay meet at; `after_lds`: this wavefront's LDS accesses have
-// been performed before it arrives (what it wrote is there for the partner, what it read has been read).
-// Global memory is not waited for: every global location is only ever touched by one of the two wavefronts.
+// Workgroup barrier; `after_lds`: this wavefront's LDS accesses have been performed before it arrives (what it wrote is
+// there for the others, what it read has been read).  Global memory is not waited for: the wavefronts of a workgroup
+// share one CU, whose vector memory accesses are performed in the order they were issued.
 __device__ __forceinline__ void meet(bool after_lds) {
     if (after_lds) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     else asm volatile("s_barrier" ::: "memory");
@@ -353,165 +355,435 @@ __device__ __forceinline__ int argmin_lanes(double v, bool in) {
     return __builtin_ctzll(ballot(tie && klo == mlo));
 }
 
+// Lowest-index minimum over the lanes with `in` set, of the wavefront or of either half of it (PACK = 2): a mask with
+// one bit per replay.  The values are compared as in wave_argmin.
+template <int PACK>
+__device__ __forceinline__ unsigned long long argmin_mask(double v, bool in, bool upper) {
+    const unsigned long long bits = (unsigned long long)__double_as_longlong(v + 0.0);
+    const unsigned hi = (unsigned)(bits >> 32), lo = (unsigned)bits;
+    const unsigned neg = (unsigned)((int)hi >> 31);
+    const unsigned khi = in ? hi ^ (neg | 0x80000000u) : 0xffffffffu;   // (lanes outside: a key that no score maps to)
+    auto least = [&](unsigned x) {
+        x = dpp_min_u32<0x111, 0xf>(x);   // row_shr:1
+        x = dpp_min_u32<0x112, 0xf>(x);   // row_shr:2
+        x = dpp_min_u32<0x114, 0xf>(x);   // row_shr:4
+        x = dpp_min_u32<0x118, 0xf>(x);   // row_shr:8
+        x = dpp_min_u32<0x142, 0xa>(x);   // row_bcast:15 into rows 1, 3
+        if (PACK == 2) {
+            const unsigned m0 = (unsigned)__builtin_amdgcn_readlane((int)x, HALF - 1);
+            const unsigned m1 = (unsigned)__builtin_amdgcn_readlane((int)x, WAVE - 1);
+            return upper ? m1 : m0;
+        }
+        x = dpp_min_u32<0x143, 0xc>(x);   // row_bcast:31 into rows 2, 3
+        return (unsigned)__builtin_amdgcn_readlane((int)x, WAVE - 1);
+    };
+    auto several = [](unsigned long long m) {
+        if (PACK == 1) return (m & (m - 1)) != 0;
+        const unsigned a = (unsigned)m, b = (unsigned)(m >> 32);
+        return ((a & (a - 1)) | (b & (b - 1))) != 0;
+    };
+    auto lowest = [](unsigned long long m) {
+        if (PACK == 1) return m & (0 - m);
+        const unsigned a = (unsigned)m, b = (unsigned)(m >> 32);
+        return (unsigned long long)(a & (0 - a)) | ((unsigned long long)(b & (0 - b)) << 32);
+    };
+    const bool tie = khi == least(khi);
+    const unsigned long long ties = ballot(tie);
+    if (!several(ties)) return ties;            // one lane holds the smallest high word: done
+    const unsigned klo = lo ^ neg;
+    const unsigned mlo = least(tie ? klo : 0xffffffffu);
+    return lowest(ballot(tie && klo == mlo));
+}
+__device__ __forceinline__ bool of_mask(unsigned long long m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
+// Eviction cursor of one LRU over a replica's log of routed requests, held by lane = replica.
+//   cursor: blocks last touched by a request before cur_r, or by cur_r at positions >= cur_k, are evicted;
+//   cur_own is where cur_r's owned suffix starts.
+//   The log is read ahead of the cursor, a record per visit: last_r is the last record read, fill_r the one after it if
+//   its link is known.  Where it is not (the log had not gone on), the next visit reads the link again, so that nothing
+//   has to be done for this when a request is added to the log.
+//   pend_*: a record being fetched by the front end; ownership changes made to it meanwhile are kept in pend_own and
+//   override the loaded field.
+//   Records that have arrived wait in a ring in LDS until the cursor reaches them: the log is
+//   read as far ahead of the cursor as the ring is long, so that a request which evicts several records' blocks at
+//   once rarely has to wait for a record to come from memory.
+//   The records in memory are written by the book-keeping wavefront, which is one request behind: the ownership change
+//   that the latest decided request makes (Fresh) may not have arrived, and is applied to what is loaded on the spot.
+// The same machinery serves the proxy's own index of the replica, an LRU of another capacity over the same log.
+struct Fresh {
+    int r = -1;               // the latest decided request (its own record cannot be loaded yet)
+    int owner = -2, end = 0;  // on the replica it went to: record whose owned suffix now starts at `end`
+};
+struct EvictCursor {
+    int cur_r = -1, cur_k = 0, cur_own = 0;
+    int last_r = -1, fill_r = -1;
+    int pend_r = -1, pend_own = -1;      // pend_r: record asked for (last_r: only its link), -1 none
+    const unsigned long long* fetched = nullptr;     // where it will be
+    // The look-ahead: a ring of records in LDS (slot k of this lane at ring[k * WAVE], packed r | own << 32 | n << 48),
+    // ring_cnt of them from slot ring_head on, the youngest being request ring_hi.
+    unsigned long long* ring = nullptr;
+    int ring_head = 0, ring_cnt = 0, ring_hi = -1;
+    int live = 0;             // blocks this LRU holds
+    int n_spot = 0, n_adv = 0, n_dead = 0;       // statistics (only the timed instantiation reads them): records fetched
+                                                 // on the spot, cursor advances, records dropped because they own nothing
+
+    // In the lanes with `who` set, what was asked for has arrived: the link of last_r, or a record, which is dropped if
+    // it owns nothing and else joins the ring.  Straight-line code: lanes with nothing pending go through it unchanged
+    // (every lane stores to LDS: those with nothing for the ring into its spare slot).
+    __device__ __forceinline__ void take_pending(unsigned long long raw, bool who = true) {
+        const bool have = who && pend_r >= 0;
+        const unsigned hi = (unsigned)(raw >> 32);
+        const int n = (int)(hi >> 16);
+        const int own_mem = (int)(hi & 0xFFFFu);
+        const int own = pend_own > own_mem ? pend_own : own_mem;
+        const bool record = have && pend_r != last_r;
+        const bool alive = record && own < n;
+        const int slot = alive ? (ring_head + ring_cnt) & (LOOK_RING - 1) : LOOK_RING;
+        ring[slot * WAVE] = (unsigned long long)(unsigned)pend_r | ((unsigned long long)((hi & 0xFFFF0000u) | (unsigned)own) << 32);
+        ring_cnt += alive ? 1 : 0;
+        ring_hi = alive ? pend_r : ring_hi;
+        n_dead += record && !alive ? 1 : 0;
+        fill_r = have ? (int)(unsigned)raw : fill_r;
+        last_r = have ? pend_r : last_r;
+        pend_r = have ? -1 : pend_r;
+    }
+    // What the next visit has to read: the record after the last one, or that one's link (-1: nothing, the log is empty).
+    // A replica's first request is announced in `first`.
+    __device__ __forceinline__ int wanted(const Fresh& f, int first) {
+        fill_r = last_r < 0 && fill_r < 0 ? first : fill_r;
+        return fill_r >= 0 && fill_r != f.r ? fill_r : last_r;
+    }
+    // Asks for the next record of the log where the ring has room for it (`spare`, the record behind the log, where
+    // there is nothing to fetch).  Called right after take_pending: nothing is pending.  The front end loads it after
+    // X(r), when everything that r - 1 changes is there; what r changes is kept in pend_own.
+    __device__ __forceinline__ int ask(int spare, const Fresh& f, int first) {
+        const int x = wanted(f, first);
+        const bool want = x >= 0 && ring_cnt < LOOK_RING;
+        pend_r = want ? x : -1;
+        pend_own = -1;
+        return want ? x : spare;
+    }
+    // whether request `owner` may be one of the records in the ring (then disowned_anywhere is the call to make)
+    __device__ __forceinline__ bool maybe_in_ring(int owner) const { return ring_cnt > 0 && owner <= ring_hi; }
+    // request `owner`'s owned suffix now starts at `end` (owner = -2: nobody's); the owner is not in the ring
+    __device__ __forceinline__ void disowned(int owner, int end) {
+        cur_own = owner == cur_r ? end : cur_own;
+        pend_own = owner == pend_r ? end : pend_own;
+    }
+    // the same where the owner may be a record in the ring (only called by the lanes it concerns)
+    __device__ __forceinline__ void disowned_anywhere(int owner, int end) {
+        disowned(owner, end);
+        if (maybe_in_ring(owner)) {
+#pragma nounroll
+            for (int k = 0; k < LOOK_RING; ++k) {
+                const unsigned long long e = ring[k * WAVE];
+                if ((int)(unsigned)e == owner)
+                    ring[k * WAVE] = (e & ~(0xFFFFull << 32)) | ((unsigned long long)(unsigned)end << 32);
+            }
+        }
+    }
+    // takes up to E blocks from the owned suffix of the cursor's record
+    __device__ __forceinline__ void take_from_cursor(int& E) {
+        int avail = cur_k - cur_own;
+        avail = avail > 0 ? avail : 0;
+        const int take = avail < E ? avail : E;
+        cur_k -= take;
+        E -= take;
+    }
+    // The cursor moves on to further records until E blocks have been given up (all lanes together, those with
+    // nothing to evict unchanged): records come from the ring, and from memory on the spot when the ring has run
+    // out.  Works on a copy of the state, written back at the end: the request loop's common path, which does not
+    // come here, then carries no register copies for this loop's sake.
+    __device__ __forceinline__ void advance(int E_in, const unsigned long long* log64, int spare, const Fresh& f, int first) {
+        EvictCursor w = *this;
+        int E = E_in;
+        w.advance_loop(E, log64, spare, f, first);
+        *this = w;
+    }
+    __device__ __forceinline__ void advance_loop(int& E, const unsigned long long* log64, int spare, const Fresh& f, int first) {
+        int asked = 0;
+        do {
+            const bool empty = E > 0 && ring_cnt == 0;
+            if (ballot(empty) != 0) {
+                // fetch a record, or the link to it, on the spot (what the front end has been asked for, if anything, may
+                // not be there yet)
+                const bool asked_for = pend_r >= 0;
+                const int x = asked_for ? pend_r : wanted(f, first);
+                // (no record, or a link that stays open: cannot happen while blocks are to be evicted; bounds the loop)
+                const bool stuck = empty && (x < 0 || (x == last_r && asked >= 2));
+                const bool fetch = empty && !stuck;
+                asked = fetch ? (x == last_r ? asked + 1 : 0) : asked;
+                live += stuck ? E : 0;
+                E = stuck ? 0 : E;
+                const unsigned long long got = ld(&log64[fetch ? x : spare]);
+                pend_own = fetch && !asked_for ? (x == f.owner ? f.end : -1) : pend_own;
+                pend_r = fetch ? x : pend_r;
+                n_spot += fetch ? 1 : 0;
+                take_pending(got, fetch);
+                continue;
+            }
+            const bool go = E > 0;
+            const unsigned long long e = ring[(ring_head & (LOOK_RING - 1)) * WAVE];
+            const unsigned hi = (unsigned)(e >> 32);
+            n_adv += go ? 1 : 0;
+            cur_r = go ? (int)(unsigned)e : cur_r;
+            cur_k = go ? (int)(hi >> 16) : cur_k;
+            cur_own = go ? (int)(hi & 0xFFFFu) : cur_own;
+            ring_head += go ? 1 : 0;
+            ring_cnt -= go ? 1 : 0;
+            take_from_cursor(E);         // (lanes with E = 0 take nothing)
+        } while (ballot(E > 0) != 0);
+    }
+    // `added` blocks have joined the LRU of the lane with `active` set.  First half: what the cursor's own record can
+    // give up, straight-line code; returns what is still to be evicted.  Second half, where some lane has any: steps
+    // to further records (all lanes together, those with nothing to evict unchanged), taking records from the ring,
+    // and from memory on the spot when the ring has run out.
+    __device__ __forceinline__ int evict_first(bool active, int added, int cap) {
+        live += active ? added : 0;
+        int E = active ? live - cap : 0;
+        E = E > 0 ? E : 0;
+        live -= E;
+        take_from_cursor(E);
+        return E;
+    }
+};
+
 // ---------------------------------------------------------------------------------------------- front end
-// Front-end wavefront of a replay: walks the trace DESC_AHEAD requests ahead of the other two and leaves every
-// request's descriptor in the ring.  Lane k < 8 holds segment reference k of the request in hand, lane 8 the last
-// one (whose end position is the request's number of blocks).  It takes part in both meetings of every request
-// (a workgroup barrier counts every wavefront) and is always early.
-template <int MODE, bool TIMED>
-__device__ __forceinline__ void front_wave(const SegArgs& a, int p, int lane, Handover* comm) {
-    const int R = a.R;
-    const int64_t N = a.N;
+// Front-end wavefront: lane = (request of a group of eight, segment reference).  A group's scalars, references and
+// descriptors are requested, requested and written in turn, eight requests apart, so that no load is waited for.
+template <int MODE, bool PROXY, int PACK, bool TIMED>
+__device__ __forceinline__ void front_wave(const SegArgs& a, int lane, Handover<PROXY>* comm) {
+    constexpr bool SIGNAL = MODE == MODE_COST_MODEL || MODE == MODE_ONLINE || MODE == MODE_LEAST_REQUEST;
+    const int R = a.R, N = (int)a.N;
+    const int q = lane / SEG_CHUNK, k = lane % SEG_CHUNK;
+    const size_t p = (size_t)blockIdx.x * PACK;
+    const double scale0 = a.scale[p], scale1 = PACK == 2 ? a.scale[p + 1] : 0.0;
     const uint64_t seed = MODE == MODE_RANDOM ? a.seeds[p] : 0;
-    const uint32_t seed_lo = (uint32_t)seed, seed_hi = (uint32_t)(seed >> 32);
-    // the trace, 64 requests per lane-held batch (lane = request), two batches deep
-    struct Batch {
-        int L, s;        // input tokens, segment references
-        int64_t j0;      // first segment reference
-        uint32_t hash;   // session-affinity policy: hash of the first block
-    };
-    auto load_batch = [&](int64_t b0, Batch& b) {
-        const int64_t x = b0 + lane;
-        const bool in = x < N;
-        const int64_t xx = in ? x : N - 1;
-        b.L = in ? a.in_len[xx] : 0;
-        const int64_t j0 = a.seg_off[xx], j1 = a.seg_off[xx + 1];
-        b.j0 = j0;
-        b.s = in ? (int)(j1 - j0) : 0;               // (requests past the end look empty)
-        b.hash = MODE == MODE_AFFINITY ? a.first_hash[xx] : 0u;
-    };
-    Batch cur, nxt;
-    int64_t b0 = 0;
-    load_batch(0, cur);
-    load_batch(WAVE, nxt);
     const uint32_t row_bytes = (uint32_t)R * 4u;
     const uint32_t never_off = (uint32_t)(a.nseg - 2) * row_bytes;      // the extra row that no request touches
     const uint32_t spare_off = (uint32_t)(a.nseg - 1) * row_bytes;      // the row that nothing reads
-    int pend_id = 0, pend_end = 0, pend_s = 0, pend_L = 0, pend_target = 0;
-    int64_t pend_j0 = 0;
-    int prev_id = 0, prev_end = 0, prev_s = 0;
-    bool prev_fresh = false;
-    // request j's references are requested ... (j in this batch or the next)
-    auto fe_issue = [&](int64_t j) {
-        const int jj = (int)(j - b0);
-        const bool here = jj < WAVE;
-        const int jl = here ? jj : jj - WAVE;
-        const int s = here ? __builtin_amdgcn_readlane(cur.s, jl) : __builtin_amdgcn_readlane(nxt.s, jl);
-        pend_L = here ? __builtin_amdgcn_readlane(cur.L, jl) : __builtin_amdgcn_readlane(nxt.L, jl);
-        pend_j0 = here ? readlane_i64(cur.j0, jl) : readlane_i64(nxt.j0, jl);
-        pend_s = s;
-        if (MODE == MODE_AFFINITY) {
-            const uint32_t h = (uint32_t)(here ? __builtin_amdgcn_readlane((int)cur.hash, jl) : __builtin_amdgcn_readlane((int)nxt.hash, jl));
-            pend_target = s > 0 ? spread(h, R) : 0;
-        } else if (MODE == MODE_RANDOM) {
-            pend_target = spread(philox4x32_10_first((uint32_t)j, (uint32_t)((uint64_t)j >> 32), seed_lo, seed_hi), R);
-        }
-        const int k = lane < 8 ? lane : s - 1;
-        const bool on = lane < 8 ? lane < s : (lane == 8 && s > 0);
-        SegRef ref{0, 0};
-        if (on) ref = a.seg[pend_j0 + k];
-        pend_id = ref.id;
-        pend_end = ref.end;       // (with the SEG_FRESH mark)
+    const char* const rows = reinterpret_cast<const char*>(a.last + p * (size_t)a.nseg * R);
+    // lane = replica, for the row cells and the log records that the deciding wavefront gets
+    const bool upper = PACK == 2 && lane >= HALF;
+    const int rl = PACK == 2 ? lane & (HALF - 1) : lane;
+    const uint32_t lane_off = (upper ? (uint32_t)a.nseg * row_bytes : 0u) + (uint32_t)(rl < R ? rl : 0) * 4u;
+    const unsigned long long* const log64 = reinterpret_cast<const unsigned long long*>(a.log + (p + (upper ? 1 : 0)) * ((size_t)N + 1));
+    const uint32_t other_replay = PACK == 2 ? (uint32_t)a.nseg * row_bytes : 0u;
+    struct Scalars {
+        int L, s, n;
+        int64_t j0;
+        uint32_t hash;
+        bool sync;
+        double t0, t1;       // arrival, at the time scale of each replay of the workgroup
+        int O;
     };
-    // ... and one request later its descriptor is written
-    auto fe_commit = [&](int64_t j) {
-        const int s = pend_s;
-        const bool fresh = (pend_end & SEG_FRESH) != 0;
-        const int my_end = pend_end & SEG_END_MASK;
-        const int n = s > 0 ? __builtin_amdgcn_readlane(my_end, 8) : 0;
-        SegDesc* const d = &comm->ring[j & (DESC_RING - 1)];
-        const bool real = lane < s;
-        // leading segments shared with the previous request (same tree, same path so far): the cache wavefront
-        // has requested this request's rows before the previous request's stores, and patches exactly these
-        // (a fresh segment may sit in the slot that the previous request's segment at this place just gave up)
-        const bool same = lane < 8 && lane < s && lane < prev_s && !fresh && pend_id == prev_id && my_end == prev_end;
-        const unsigned differ = ~(unsigned)ballot(same) | 0x100u;
-        const int common = __builtin_ctz(differ);
-        // what the match loads: the segment's row, unless the row starts over now or did with the previous request
-        const bool from_slot = real && !fresh && !(same && prev_fresh);
-        const uint32_t slot_off = (uint32_t)pend_id * row_bytes;
-        const int end = real ? my_end : n;
-        if (lane < 8) {
-            d->e[lane] = SegEnt{from_slot ? slot_off : never_off, end};
-            d->slot[lane] = real ? slot_off : spare_off;
+    auto load_scalars = [&](int g0, Scalars& c) {
+        const int r = g0 + q;
+        const bool on = r < N;                       // (requests past the end look empty)
+        const int x = on ? r : N - 1, before = x > 0 ? x - 1 : 0;
+        c.j0 = a.seg_off[x];
+        c.s = on ? (int)(a.seg_off[x + 1] - c.j0) : 0;
+        c.n = on ? (int)(a.blk_off[x + 1] - a.blk_off[x]) : 0;
+        c.L = on ? a.in_len[x] : 0;
+        c.hash = MODE == MODE_AFFINITY ? a.first_hash[x] : 0u;
+        // whether the request before may have completed by this one's arrival: it takes its decode time at least (every
+        // further term of its completion time is added to it and none is negative: rounding keeps the order)
+        bool sync = c.s > SEG_CHUNK;
+        const double at = (double)a.ts[x];
+        c.t0 = at * scale0;
+        c.t1 = at * scale1;
+        c.O = a.out_len[x];
+        if (SIGNAL) {
+            const double ahead = (double)a.ts[before], dec = a.least_dec * (double)a.out_len[before];
+            sync = sync || !(ahead * scale0 + dec > c.t0);
+            if (PACK == 2) sync = sync || !(ahead * scale1 + dec > c.t1);
         }
-        const unsigned fresh8 = (unsigned)ballot(lane < 8 && real && fresh);
-        const int first_fresh = __builtin_ctz(fresh8 | 0x100u);
-        // the store targets of the cache wavefront's lanes: lane 8 here holds the request's last segment
-        const bool tail_fresh = s > 0 && s <= 8 && ((fresh8 >> (s - 1)) & 1u) != 0;
-        const bool narrow = R <= 32;
-        const uint32_t of_seg = (uint32_t)__builtin_amdgcn_ds_bpermute((lane & 7) << 2, (int)(real ? slot_off : spare_off));
-        const uint32_t of_tail = (uint32_t)__builtin_amdgcn_readlane((int)slot_off, 8);
-        d->store[lane] = lane < 32 || !narrow ? of_seg : (tail_fresh && lane - 32 < R ? of_tail : spare_off);
-        const bool fresh_more = narrow ? (fresh8 & ~(tail_fresh ? 1u << (s - 1) : 0u)) != 0 : fresh8 != 0;
-        if (lane == 0) {
-            d->L = pend_L;
-            d->n = n;
-            d->s = s;
-            d->flags = (s > 4 ? DESC_MORE4 : 0) | (s > 8 ? DESC_DEEP : 0) | (tail_fresh && narrow ? DESC_FRESH_TAIL : 0) |
-                       (fresh_more ? DESC_FRESH_MORE : 0) | (common << 8) | (first_fresh << 16);
-            d->j0 = pend_j0;
-            d->target = pend_target;
-        }
-        prev_id = pend_id;
-        prev_end = my_end;
-        prev_s = s;
-        prev_fresh = fresh;
+        // whether the tuner changes the weights between the two
+        if (MODE == MODE_ONLINE) sync = sync || (r >= a.window && (unsigned)(r - a.window) % (unsigned)a.hop == 0u);
+        c.sync = on && r > 0 && sync;
     };
-    fe_issue(0);
-    fe_commit(0);
-    fe_issue(1);
-    fe_commit(1);
-    fe_issue(2);
-    meet(true);         // the first descriptors are there: the cache wavefront may start
+    int ref_id = -1, ref_end = 0;                    // (-1: no such segment)
+    auto load_ref = [&](const Scalars& c) {
+        SegRef ref{-1, 0};
+        if (k < c.s) ref = a.seg[c.j0 + k];
+        ref_id = ref.id;
+        ref_end = ref.end;                           // (with the SEG_FRESH mark)
+    };
+    int old_id = -1, old_end = 0;                    // the references of the group before
+    int touched = 0;
+    Scalars now, next;
+    // The descriptors of group g0 (scalars `now`, references in ref_*), in pieces of about equal length; done(k) is
+    // called after each.
+    auto commit = [&](int g0, auto done) {
+        // the references at the same place of the path in the three requests before: same tree, same path so far
+        const int from1 = ((lane - SEG_CHUNK) & (WAVE - 1)) << 2, from2 = ((lane - 2 * SEG_CHUNK) & (WAVE - 1)) << 2,
+                  from3 = ((lane - 3 * SEG_CHUNK) & (WAVE - 1)) << 2;
+        int p1_id = __builtin_amdgcn_ds_bpermute(from1, q < 7 ? ref_id : old_id);
+        int p1_end = __builtin_amdgcn_ds_bpermute(from1, q < 7 ? ref_end : old_end);
+        int p2_id = __builtin_amdgcn_ds_bpermute(from2, q < 6 ? ref_id : old_id);
+        int p2_end = __builtin_amdgcn_ds_bpermute(from2, q < 6 ? ref_end : old_end);
+        int p3_id = __builtin_amdgcn_ds_bpermute(from3, q < 5 ? ref_id : old_id);
+        int p3_end = __builtin_amdgcn_ds_bpermute(from3, q < 5 ? ref_end : old_end);
+        done(0);
+        const bool real = k < now.s, fresh = real && (ref_end & SEG_FRESH) != 0;
+        const int my_end = ref_end & SEG_END_MASK;
+        // (a fresh segment may sit in the slot that a request before just gave up)
+        const bool same1 = real && !fresh && ref_id == p1_id && my_end == (p1_end & SEG_END_MASK);
+        const bool new1 = same1 && (p1_end & SEG_FRESH) != 0;
+        const bool same2 = real && !fresh && !new1 && ref_id == p2_id && my_end == (p2_end & SEG_END_MASK);
+        const bool new2 = same2 && (p2_end & SEG_FRESH) != 0;
+        const uint32_t slot_off = (uint32_t)ref_id * row_bytes;
+        const bool same3 = real && !fresh && !new1 && !new2 && ref_id == p3_id && my_end == (p3_end & SEG_END_MASK);
+        const bool new3 = same3 && (p3_end & SEG_FRESH) != 0;
+        const uint32_t off = real && !fresh && !new1 && !new2 && !new3 ? slot_off : never_off;
+        const unsigned long long all1 = ballot(same1), all2 = ballot(same2), all3 = ballot(same3), allf = ballot(fresh);
+        done(1);
+        SegDesc* const d = &comm->ring[(g0 + q) & (DESC_RING - 1)];
+        d->rowoff[k] = off;
+        d->end[k] = real ? my_end : now.n;
+        d->slot[k] = real ? slot_off : spare_off;
+        // The rows that will be read a dozen requests from now are touched once, so that they come from the L2 then and
+        // not from memory: one load per 64 rows (both ends of rows that straddle a cache line, or
+        // are longer than one).  The values are only used to keep the loads.
+        asm volatile("" ::"v"(touched));
+        touched = ld(reinterpret_cast<const int32_t*>(rows + off));
+        if ((row_bytes & 127u) != 0 || row_bytes > 128u) touched ^= ld(reinterpret_cast<const int32_t*>(rows + (off + row_bytes - 4u)));
+        if (PACK == 2) {
+            touched ^= ld(reinterpret_cast<const int32_t*>(rows + (off + other_replay)));
+            if ((row_bytes & 127u) != 0) touched ^= ld(reinterpret_cast<const int32_t*>(rows + (off + other_replay + row_bytes - 4u)));
+        }
+        done(2);
+        const int byte = q * SEG_CHUNK;
+        const unsigned common1 = __builtin_ctz(~(unsigned)(all1 >> byte) | 0x100u);
+        const unsigned common2 = __builtin_ctz(~(unsigned)(all2 >> byte) | 0x100u);
+        const unsigned common3 = __builtin_ctz(~(unsigned)(all3 >> byte) | 0x100u);
+        const unsigned fresh8 = (unsigned)(allf >> byte) & 0xffu;
+        // the last segment's row, if it is fresh: with at most 32 replicas the book-keeping wavefront's upper lanes
+        // reset it in the same store
+        const bool tail_fresh = PACK == 1 && R <= 32 && now.s > 0 && now.s <= SEG_CHUNK && ((fresh8 >> ((now.s - 1) & 31)) & 1u) != 0;
+        const uint32_t tail = (uint32_t)__builtin_amdgcn_ds_bpermute((byte + ((now.s - 1) & (SEG_CHUNK - 1))) << 2, (int)slot_off);
+        const unsigned rest = fresh8 & ~(tail_fresh ? 1u << (now.s - 1) : 0u);
+        const int flags = (now.s > 4 ? DESC_MORE4 : 0) | (now.s > SEG_CHUNK ? DESC_DEEP : 0) | (tail_fresh ? DESC_FRESH_TAIL : 0) |
+                          (rest != 0 ? DESC_FRESH_MORE : 0) | (now.sync ? DESC_SYNC : 0) | (int)(common1 << 8) | (int)(common2 << 12) |
+                          (int)(common3 << 20) | (int)(__builtin_ctz(fresh8 | 0x100u) << 16);
+        done(3);
+        if (k == 0) *reinterpret_cast<int4*>(&d->L) = int4{now.L, now.n, now.s, flags};
+        if (k == 1) {
+            d->j0 = now.j0;
+            d->tail = tail_fresh ? tail : spare_off;
+            if (MODE == MODE_AFFINITY) d->target = now.s > 0 ? spread(now.hash, R) : 0;
+            else if (MODE == MODE_RANDOM)
+                d->target = spread(philox4x32_10_first((uint32_t)(g0 + q), 0u, (uint32_t)seed, (uint32_t)(seed >> 32)), R);
+        }
+        if (k == 2) {
+            d->t[0] = now.t0;
+            d->t[1] = now.t1;
+        }
+        if (k == 3) {
+            d->dec = a.a_dec * (double)now.O;
+            d->O = now.O;
+        }
+        old_id = ref_id;
+        old_end = ref_end;
+        done(4);
+    };
+    const auto at_once = [](int) {};
+    for (int g0 = 0; g0 < DESC_AHEAD; g0 += DESC_GROUP) {
+        load_scalars(g0, now);
+        load_ref(now);
+        commit(g0, at_once);
+    }
+    load_scalars(DESC_AHEAD, now);
+    load_ref(now);
+    load_scalars(DESC_AHEAD + DESC_GROUP, next);
+    // The row cells of request x, for the deciding wavefront, which reads them from LDS after the next meeting.
+    int32_t cell[SEG_CHUNK];
+    bool more4 = false;
+    auto load_cells = [&](int x) {
+        const SegDesc& d = comm->ring[x & (DESC_RING - 1)];
+        more4 = (__builtin_amdgcn_readfirstlane(d.flags) & DESC_MORE4) != 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) cell[j] = ld(reinterpret_cast<const int32_t*>(rows + (d.rowoff[j] + lane_off)));
+        if (more4) {
+#pragma unroll
+            for (int j = 4; j < 8; ++j) cell[j] = ld(reinterpret_cast<const int32_t*>(rows + (d.rowoff[j] + lane_off)));
+        }
+    };
+    auto store_cells = [&](int x) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) comm->cells[x & 1][j][lane] = cell[j];
+        if (more4) {
+#pragma unroll
+            for (int j = 4; j < 8; ++j) comm->cells[x & 1][j][lane] = cell[j];
+        }
+    };
+    load_cells(0);
+    store_cells(0);
+    load_cells(1);
+    store_cells(1);
+    meet(true);         // the first descriptors and cells are there
+    meet(false);
     SectionClock<TIMED> clk;
     clk.start();
-    for (int64_t r = 0; r < N; ++r) {
-        // in the long stretch between B(r - 1) and A(r), where the cache wavefront reads the descriptor of r + 1:
-        // the descriptor after that (first read by the cache wavefront after B(r))
-        fe_commit(r + 2);
-        clk.tick(0);                                                 // descriptors
-        meet(true);                                                  // A(r)
-        clk.tick(1);                                                 // waiting at A
-        // in the short stretch where the cache wavefront decides: the references of the request after that
-        fe_issue(r + 3);
-        if (r + 1 - b0 == WAVE) {
-            cur = nxt;
-            b0 += WAVE;
-            load_batch(b0 + WAVE, nxt);
-        }
-        clk.tick(3);                                                 // references
-        meet(false);                                                 // B(r)
-        clk.tick(2);                                                 // waiting at B
+    // what is done before the meeting X(r): the cells of r + 2 are loaded, and after a piece of the descriptors' work
+    // handed over; every fourth time the log records that were asked for as well
+    unsigned long long raw[PROXY ? 2 : 1] = {};
+    auto begin = [&](int r) {
+        if (r >= N) return;
+        load_cells(r + 2);
+        if ((r & 3) == 0 && r > 0)
+            for (int c = 0; c < (PROXY ? 2 : 1); ++c) raw[c] = ld(&log64[comm->wanted[c][lane]]);
+    };
+    auto pass = [&](int r) {
+        if (r >= N) return;
+        const bool sync = (__builtin_amdgcn_readfirstlane(comm->ring[(r + 1) & (DESC_RING - 1)].flags) & DESC_SYNC) != 0;
+        store_cells(r + 2);
+        if ((r & 3) == 0 && r > 0)
+            for (int c = 0; c < (PROXY ? 2 : 1); ++c) comm->fetched[c][lane] = raw[c];
+        clk.tick(0);                                                 // descriptors, cells
+        meet(true);                                                  // X(r)
+        if (sync) meet(false);                                       // Y(r)
+        clk.tick(1);                                                 // waiting
+    };
+    for (int r = 0; r < N; r += DESC_GROUP) {
+        // (a piece between any two meetings: all at once the work would make the meeting late)
+        begin(r);
+        commit(r + DESC_AHEAD, [&](int i) {
+            pass(r + i);
+            begin(r + i + 1);
+        });
+        now = next;
+        load_ref(now);
+        pass(r + 5);
+        begin(r + 6);
+        load_scalars(r + DESC_AHEAD + 2 * DESC_GROUP, next);
+        pass(r + 6);
+        begin(r + 7);
+        pass(r + 7);
     }
-    clk.write(a.sections ? a.sections + ((size_t)p * 3 + 2) * SECTIONS : nullptr, lane);
+    asm volatile("" ::"v"(touched));
+    if (TIMED && a.sections && lane == 0)            // (the book-keeping wavefront writes the next two)
+        for (int i = 0; i < 2; ++i) a.sections[(p * 3 + 2) * SECTIONS + i] = clk.acc[i];
 }
 
 // ---------------------------------------------------------------------------------------------- queue side
-// Queue wavefront of a replay.  Per request: retire what has completed by its arrival, publish the queue
-// terms, meet (A); retire ahead to the next arrival and run the front end; meet (B); serve the request on
-// the chosen replica.  Keeps and writes the latencies and the per-request outputs.
-template <int MODE, bool ENGINE, bool PROXY, bool SLOTS, bool TIMED>
-__device__ __forceinline__ void queue_wave(const SegArgs& a, int p, int lane, unsigned char* lds_raw, Handover* comm) {
+// Queue wavefront of a replay (`which` of the workgroup's).  One request behind the deciding wavefront: after
+// X(r) it serves r, then retires what completes by the arrival of r + 2, which the deciding wavefront reads after
+// X(r + 1).  BLOCKS: the partner is the block-table formulation's cache wavefront; the two meet twice at every request
+// and the route and hit outputs are written here.
+template <int MODE, bool ENGINE, bool PROXY, int PACK, bool BLOCKS, bool TIMED>
+__device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane, unsigned char* lds_raw, Handover<PROXY>* comm) {
     constexpr bool ONLINE = MODE == MODE_ONLINE;
-    static_assert(!SLOTS || (!ENGINE && !PROXY), "one lane per slot exists for the linear replica model with fixed round trip times");
-    const int R = a.R;
-    const int64_t N = a.N;
-    // the queue state: one lane per service slot where the model's shape allows it, else one lane per replica
-    // with the slots in LDS
-    // (the online tuner's instantiation does without the deferred fetch of deep lists: see SlotQueuesT)
-    typename std::conditional<SLOTS, SlotQueuesT<MODE != MODE_ONLINE>, Queues>::type Q;
-    if constexpr (SLOTS) {
-        Q.init(lds_raw, R, a.B, lane);
-    } else {
-        Q.carve(lds_raw, R, a.B, lane);
-        Q.init(lane);
-    }
+    constexpr bool COUNTS = MODE == MODE_LEAST_REQUEST;      // the load signal is the number of requests, not their tokens
+    const int R = a.R, N = (int)a.N;
+    const size_t p = (size_t)blockIdx.x * PACK + which;
+    SlotQueues Q;
+    Q.init(lds_raw, R, a.B, ENGINE, lane);
     // Online tuner (Sec. 2.3, Sec. 4), run here because this wavefront has the TTFTs: after every hop the p95
     // TTFT of the last `window` requests is the fitness of the weights in use; they replace the parent iff they
     // beat it; the step size follows the 1/5 rule; the next offspring is a log-space mutation of the parent.
     // The state is the same in every lane.
-    double* const ring = reinterpret_cast<double*>(lds_raw + (SLOTS ? SlotQueues::bytes() : Queues::bytes(R, a.B)));
+    double* const ring = reinterpret_cast<double*>(lds_raw + SlotQueues::bytes(R, a.B, ENGINE));
     const int W = ONLINE ? a.window : 0, H = ONLINE ? a.hop : 0;
     const int kth = (95 * W + 99) / 100;
     int ring_pos = 0, until_step = W;
@@ -521,15 +793,14 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int p, int lane, un
     double ln_par[3] = {0.0, 0.0, 0.0}, ln_cur[3] = {0.0, 0.0, 0.0};
     double f_par = 0.0, sigma = 0.0;
     if (ONLINE) {
-        for (int k = 0; k < 3; ++k) ln_par[k] = ln_cur[k] = a.ln_theta0[3 * (size_t)p + k];
+        for (int k = 0; k < 3; ++k) ln_par[k] = ln_cur[k] = a.ln_theta0[3 * p + k];
         sigma = a.tuner[12];
         if (W + lane < ((W + 7) & ~7)) ring[W + lane] = INFINITY;     // padding (entries below W are written before use)
     }
     auto tuner_results = [&]() {
         if (ONLINE && lane == 0) {
             if (a.theta_final)
-                for (int k = 0; k < 3; ++k)
-                    a.theta_final[3 * (size_t)p + k] = clip(tuner_exp(ln_par[k]), a.tuner[k], a.tuner[3 + k]);
+                for (int k = 0; k < 3; ++k) a.theta_final[3 * p + k] = clip(tuner_exp(ln_par[k]), a.tuner[k], a.tuner[3 + k]);
             if (a.sigma_final) a.sigma_final[p] = sigma;
             if (a.accepted) a.accepted[p] = accepted;
         }
@@ -538,130 +809,131 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int p, int lane, un
         tuner_results();
         return;
     }
-    double w_queue = a.params[3 * (size_t)p + 2];      // (the online tuner replaces it at every step)
+    if (ONLINE && lane < 3) comm->w[which][lane] = a.params[3 * p + lane];
     const double sc = a.scale[p];
-    double my_rtt = lane < R ? (PROXY ? a.rtt_true[lane] : a.rtt[lane]) : 0.0;
     // imperfect proxy knowledge (Sec. 2.2, Sec. 4 RTT figure): time is cut into probe epochs, the epoch of t being
     // the largest e with e * probe_ms <= t (capped at the last one given); a request experiences the true round
-    // trip time of its epoch, the cost model scores with the proxy's moving average, handed to the cache wavefront
-    // with the queue terms
+    // trip time of its epoch, the cost model scores with the proxy's moving average, handed to the deciding wavefront
+    // two requests ahead.  (The service step looks half the round trip time up in LDS.)
     int epoch = 0;
-    double next_probe = PROXY ? (double)a.probe_ms : 0.0;
-    if (PROXY) comm->rtt[lane] = lane < R ? a.rtt_est[lane] : 0.0;
+    double next_probe = PROXY ? (double)a.probe_ms : 0.0, rtt_now = 0.0, est_now = 0.0;
+    auto probe = [&](double t, int r) {          // request r arrives at t
+        bool moved = r == 0;
+        while (epoch + 1 < a.epochs && next_probe <= t) {       // (timestamps do not decrease)
+            ++epoch;
+            next_probe = (double)(epoch + 1) * (double)a.probe_ms;
+            moved = true;
+        }
+        if (moved) {
+            const size_t at = (size_t)epoch * R + (lane < R ? lane : 0);
+            rtt_now = a.rtt_true[at];
+            est_now = a.rtt_est[at];
+        }
+        comm->half[r & 3][lane] = 0.5 * rtt_now;
+        comm->rtt[r & 3][lane] = est_now;
+    };
+    if (!PROXY) comm->half[0][lane] = lane < R ? 0.5 * a.rtt[lane] : 0.0;
     // engine model: this lane's replica has its own rates and KV budget
     const double my_a_pf = ENGINE && lane < R ? a.eng_a_pf[lane] : 0.0;
     const double my_a_dec = ENGINE && lane < R ? a.eng_a_dec[lane] : 0.0;
     const double my_budget = ENGINE && lane < R ? a.eng_budget[lane] : 0.0;
-    Rec* const rec = a.rec + (size_t)p * N;
+    Rec* const rec = a.rec + p * (size_t)N;
 
-    // ---- the trace, 64 requests per lane-held batch (lane = request), two batches deep so that a batch's loads
-    // have a whole batch of time to arrive
+    // ---- times and lengths come with the descriptors; block tables have none: 64 requests per lane-held batch (lane =
+    // request), two batches deep so that a batch's loads have a whole batch of time to arrive
     struct Batch {
         double t;        // arrival time, scaled
         int L, O;        // input tokens, output tokens
     };
-    auto load_batch = [&](int64_t b0, Batch& b) {
-        const int64_t x = b0 + lane;
-        const int64_t xx = x < N ? x : N - 1;
+    auto load_batch = [&](int b0, Batch& b) {
+        const int x = b0 + lane;
+        const int xx = x < N ? x : N - 1;
         b.t = (double)a.ts[xx] * sc;                 // time scale: gaps scale linearly
         b.L = a.in_len[xx];
         b.O = a.out_len[xx];
     };
-    Batch cur, nxt;
-    load_batch(0, cur);
-    load_batch(WAVE, nxt);
-    meet(false);        // (the front end's first descriptors are there: the cache wavefront may start)
+    Batch cur{0.0, 0, 0}, nxt{0.0, 0, 0};
+    if (BLOCKS) {
+        load_batch(0, cur);
+        load_batch(WAVE, nxt);
+    } else {
+        meet(true);      // (the first descriptors are there)
+    }
+    auto desc = [&](int r) -> const SegDesc& { return comm->ring[r & (DESC_RING - 1)]; };
+    double* const gone0 = &comm->gone[0][which * HALF];
+    auto gone = [&](int r) { return gone0 + (r & 3) * WAVE; };
+    for (int b = 0; b < 4; ++b)
+        if (PACK == 1 || lane < HALF) gone(b)[lane] = 0.0;
+    // requests that complete by t leave the load signal between the arrivals of r - 1 and r
+    auto retire = [&](unsigned due, double t, int r) { Q.template retire<!PROXY>(due, t, rec, lane, gone(r)); };
+    // arrival times of the request in hand and the two after it
+    double t0, t1, t2 = 0.0;
+    if (BLOCKS) {
+        t0 = readlane_f64(cur.t, 0);
+        t1 = readlane_f64(cur.t, 1);
+    } else {
+        t0 = desc(0).t[which];
+        t1 = desc(1).t[which];
+    }
+    if (PROXY) {
+        probe(t0, 0);
+        if (N > 1) probe(t1, 1);
+    }
+    meet(true);        // (nothing has completed yet: the first request can be decided)
 
     double o_ttft = 0.0, o_e2e = 0.0;
     int o_route = 0, o_hit = 0, o_believed = 0;
-    double own_done = INFINITY;               // (one lane per slot) when the previous request's completion reaches the proxy
     SectionClock<TIMED> clk;
     clk.start();
-    // (a loop over the batches around a loop over a batch's requests: inside the inner one the batches do not change,
-    // so nothing there has to wait for the loads of the batch after next, or, with them, for the stores of the
-    // service step)
-    for (int64_t b0 = 0; b0 < N; b0 += WAVE) {
-        const int in_batch = N - b0 < WAVE ? (int)(N - b0) : WAVE;
+    for (int b0 = 0; b0 < N; b0 += WAVE) {
+        const int in_batch = N - b0 < WAVE ? N - b0 : WAVE;
         for (int i = 0; i < in_batch; ++i) {
-            const int64_t r = b0 + i;
-            const double t = readlane_f64(cur.t, i);
-            const int L = __builtin_amdgcn_readlane(cur.L, i);
-            const int O = __builtin_amdgcn_readlane(cur.O, i);
-            if (PROXY) {
-                bool moved = false;
-                while (epoch + 1 < a.epochs && next_probe <= t) {       // (timestamps do not decrease)
-                    ++epoch;
-                    next_probe = (double)(epoch + 1) * (double)a.probe_ms;
-                    moved = true;
-                }
-                if (moved) {
-                    const size_t at = (size_t)epoch * R + (lane < R ? lane : 0);
-                    my_rtt = a.rtt_true[at];
-                    comm->rtt[lane] = a.rtt_est[at];
-                }
-            }
-            // (one lane per slot: everything that completes by t was retired ahead, while the cache wavefront decided the
-            // previous request -- except that request itself, whose completion time is known since it was served)
-            if constexpr (SLOTS) {
-                if (own_done <= t) Q.retire(t, rec, lane);
+            const int r = b0 + i;
+            int L, O = 0;
+            double dec = 0.0;
+            bool sync = true;
+            if (BLOCKS) {
+                const int i2 = i + 2;
+                L = __builtin_amdgcn_readlane(cur.L, i);
+                O = __builtin_amdgcn_readlane(cur.O, i);
+                t2 = i2 < WAVE ? readlane_f64(cur.t, i2) : readlane_f64(nxt.t, i2 - WAVE);
+                dec = a.a_dec * (double)O;
             } else {
-                Q.retire(t, rec);
+                L = desc(r).L;
+                t2 = desc(r + 2).t[which];
+                if (ENGINE) O = desc(r).O;
+                else dec = desc(r).dec;
+                sync = (__builtin_amdgcn_readfirstlane(desc(r + 1).flags) & DESC_SYNC) != 0;
             }
-            clk.tick(10);                                                // (finer: readlanes and retiring)
-            // the queue term of Eq. 3, products rounded one by one (the least-request policy asks for the requests in
-            // flight instead; the dictated policies ignore it)
-            if (MODE == MODE_LEAST_REQUEST) comm->sq[lane] = Q.my_cnt;
-            else if (MODE == MODE_COST_MODEL || MODE == MODE_ONLINE) {
-                const double qd = a.a_pf * Q.my_q;
-                comm->sq[lane] = w_queue * qd;
-            }
-            clk.tick(0);                                                 // retire, publish
-            // The completions up to the next request's time do not depend on where this request goes (only this
-            // request's own completion does, which is left for the retire above, next time round): they are retired
-            // ahead, after the meeting, where this wavefront would otherwise wait while the cache wavefront decides.
-            // The service step still has to see the slots that were idle at this request's time, so their set is
-            // kept.
-            unsigned long long idle_now = 0;
-            SlotIdle idle_then{0, 0, 0, 0};
-            if constexpr (SLOTS) {
-                idle_then = Q.idle_slots();
-            } else {
-                idle_now = Q.idle;
-            }
-            clk.tick(2);                                                 // retire ahead
-            clk.tick(3);                                                 // (nothing: what reading the clock costs)
-            meet(true);                                                  // A(r)
-            clk.tick(1);                                                 // waiting at A
-            {
-                const double t_ahead = i + 1 < WAVE ? readlane_f64(cur.t, i + 1) : readlane_f64(nxt.t, 0);
-                if constexpr (SLOTS) {
-                    if (r + 1 < N) Q.retire(t_ahead, rec, lane);
-                } else {
-                    if (r + 1 < N) Q.retire(t_ahead, rec);
-                }
-            }
-            meet(false);                                                 // B(r)
-            clk.tick(4);                                                 // waiting at B
-            const unsigned long long w = comm->choice;
-            const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(w >> 32));
-            const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)w);
-            const int best = (int)(hi & 63u);
-            clk.tick(8);                                                 // (finer: the choice read)
+            clk.tick(0);
+            meet(true);                                                  // X(r)
+            clk.tick(1);                                                 // waiting at X
+            const int lane_best = comm->best[r & 1][which];
+            // (what completes by the arrival of the request after next, this request's own completion aside: read now, while
+            // the choice is on its way)
+            unsigned due = Q.due(t2, lane);
+            const Choice* const ch = &comm->choice[r & 1][lane_best];
+            const double prefill = ch->prefill;
+            const int best = PACK == 2 ? lane_best & (HALF - 1) : lane_best;
+            const double half = comm->half[PROXY ? r & 3 : 0][best];
+            const int weight = COUNTS ? 1 : L;
             double ttft, e2e;
-            if constexpr (SLOTS)
-                Q.serve(r, best, t, readlane_f64(my_rtt, best), (int)lo, L, O, a.a_pf, a.a_dec, rec, lane, idle_then, &ttft, &e2e, &own_done);
-            else if constexpr (ENGINE)
-                Q.template serve_engine<PROXY>(r, best, t, my_rtt, (int64_t)(int)lo, L, O, my_a_pf, my_a_dec, my_budget, a.eng_slowdown,
-                               rec, lane, &ttft, &e2e);
-            else
-                Q.template serve<PROXY>(r, best, t, my_rtt, (int64_t)(int)lo, L, O, a.a_pf, a.a_dec, rec, lane, idle_now,
-                                        &ttft, &e2e);
-            clk.tick(9);                                                 // (finer: service)
+            if constexpr (ENGINE) {
+                const int sb = __builtin_amdgcn_readfirstlane(best);
+                Q.template serve_engine<PROXY>(r, sb, t0, half, readlane_f64(my_a_pf, sb) * prefill,
+                                               readlane_f64(my_a_dec, sb) * (double)O, weight, (unsigned)L + (unsigned)O,
+                                               readlane_f64(my_budget, sb), a.eng_slowdown, rec, lane, &ttft, &e2e, t2, due);
+            } else {
+                Q.template serve<PROXY>(r, best, t0, half, PROXY ? a.a_pf * prefill : prefill, dec, weight, rec, lane, &ttft, &e2e, t2, due);
+            }
+            clk.tick(9);                                                 // service
             o_ttft = lane == i ? ttft : o_ttft;
             o_e2e = lane == i ? e2e : o_e2e;
-            o_route = lane == i ? best : o_route;
-            o_hit = lane == i ? (int)(hi >> 8) : o_hit;
-            if (PROXY && a.believed) o_believed = lane == i ? __builtin_amdgcn_readfirstlane(comm->seen) : o_believed;
+            if (BLOCKS) {
+                o_route = lane == i ? best : o_route;
+                o_hit = lane == i ? (int)(ch->hit_end & 0xFFFFu) : o_hit;
+                if (PROXY && a.believed) o_believed = lane == i ? (int)comm->seen[r & 1][lane_best] : o_believed;
+            }
             if (ONLINE) {
                 if (lane == 0) ring[ring_pos] = ttft;
                 ring_pos = ring_pos + 1 == W ? 0 : ring_pos + 1;
@@ -683,216 +955,186 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int p, int lane, un
                     }
                     double th[3];
                     for (int k = 0; k < 3; ++k) {
-                        const double zk = a.z[((size_t)p * a.steps + step) * 3 + k];
+                        const double zk = a.z[(p * a.steps + step) * 3 + k];
                         const double moved = ln_par[k] + sigma * zk;
                         ln_cur[k] = clip(moved, a.tuner[6 + k], a.tuner[9 + k]);
                         th[k] = clip(tuner_exp(ln_cur[k]), a.tuner[k], a.tuner[3 + k]);
                     }
-                    w_queue = th[2];                                     // in use from the next request on
-                    if (lane == 0) {
-                        comm->w[0] = th[0];
-                        comm->w[1] = th[1];
-                        if (a.fitness_step) a.fitness_step[(size_t)p * a.steps + step] = f;
+                    if (lane == 0) {                                     // in use from the next request on (Y(r) follows)
+                        for (int k = 0; k < 3; ++k) comm->w[which][k] = th[k];
+                        if (a.fitness_step) a.fitness_step[p * a.steps + step] = f;
                         if (a.theta_step)
-                            for (int k = 0; k < 3; ++k) a.theta_step[((size_t)p * a.steps + step) * 3 + k] = th[k];
+                            for (int k = 0; k < 3; ++k) a.theta_step[(p * a.steps + step) * 3 + k] = th[k];
                     }
                     ++step;
                     wave_sync();
                 }
             }
-            clk.tick(5);                                                 // serve, outputs, tuner
+            clk.tick(5);                                                 // outputs, tuner
+            if (sync) {
+                // the request may have completed before the next one arrives, or its latency matters to the next one
+                if (r + 1 < N) retire(Q.due(t1, lane), t1, r + 1);
+                meet(true);                                              // Y(r)
+                due = Q.due(t2, lane);
+            }
+            // The completions up to the arrival of the request after next (this request's among them) do not depend on
+            // where the next request goes, whose own completion the deciding wavefront has ruled out, or will wait for.
+            if (BLOCKS) gone(r + 3)[lane] = 0.0;             // (else the book-keeping wavefront does)
+            if (r + 2 < N) {
+                retire(due, t2, r + 2);
+                if (PROXY) probe(t2, r + 2);
+            }
+            t0 = t1;
+            t1 = t2;
+            clk.tick(2);                                                 // retiring
         }
-        // the batch is done: its outputs go out, the next batch moves up and the one after it is requested
+        // the batch is done: its outputs go out
         if (lane < in_batch) {
-            const size_t o = (size_t)p * N + b0 + lane;
+            const size_t o = p * N + b0 + lane;
             if (a.ttft) a.ttft[o] = o_ttft;
             if (a.e2e) a.e2e[o] = o_e2e;
-            if (a.route) a.route[o] = (uint8_t)o_route;
-            if (a.hit) a.hit[o] = (uint16_t)o_hit;
-            if (PROXY && a.believed) a.believed[o] = (uint16_t)o_believed;
+            if (BLOCKS) {
+                if (a.route) a.route[o] = (uint8_t)o_route;
+                if (a.hit) a.hit[o] = (uint16_t)o_hit;
+                if (PROXY && a.believed) a.believed[o] = (uint16_t)o_believed;
+            }
         }
-        cur = nxt;
-        load_batch(b0 + 2 * WAVE, nxt);
+        if (BLOCKS) {
+            cur = nxt;
+            load_batch(b0 + 2 * WAVE, nxt);
+        }
         clk.tick(6);                                                   // batch turnover
     }
-    clk.write(a.sections ? a.sections + ((size_t)p * 3 + 1) * SECTIONS : nullptr, lane);
+    clk.write(a.sections ? a.sections + (p * 3 + 1) * SECTIONS : nullptr, lane);
     tuner_results();
 }
 
-// ---------------------------------------------------------------------------------------------- cache side
-// Eviction cursor of one LRU over a replica's log of routed requests, held by lane = replica.
-//   cursor: blocks last touched by a request before cur_r, or by cur_r at positions >= cur_k, are evicted;
-//   cur_own is where cur_r's owned suffix starts.
-//   fill_r: the record after the last one held here, or -1 when that one is the youngest of the log.
-//   pend_*: a record being fetched (its load is only waited for one iteration later); changes made to it
-//   meanwhile are kept in pend_own / pend_next and override the loaded fields.
-//   Records that have arrived wait in a ring in LDS until the cursor reaches them: the log is
-//   read as far ahead of the cursor as the ring is long, so that a request which evicts several records' blocks at
-//   once rarely has to wait for a record to come from memory.
-// The same machinery serves the proxy's own index of the replica, an LRU of another capacity over the same log.
-struct EvictCursor {
-    int cur_r = -1, cur_k = 0, cur_own = 0;
-    int fill_r = -1;
-    int pend_r = -1, pend_own = -1, pend_next = -1;
-    unsigned long long pend_raw = 0;
-    // The look-ahead: a ring of records in LDS (slot k of this lane at ring[k * WAVE], packed r | own << 32 | n << 48),
-    // ring_cnt of them from slot ring_head on, the youngest being request ring_hi.
-    unsigned long long* ring = nullptr;
-    int ring_head = 0, ring_cnt = 0, ring_hi = -1;
-    int live = 0;             // blocks this LRU holds
-    int n_spot = 0, n_adv = 0, n_dead = 0;       // statistics (only the timed instantiation reads them): records fetched
-                                                 // on the spot, cursor advances, records dropped because they own nothing
-
-    // In the lanes with `who` set, the record requested by the previous issue_fill becomes usable: dropped if it owns
-    // nothing, else it joins the ring.  Straight-line code: lanes with nothing pending go through it unchanged
-    // (every lane stores to LDS: those with nothing for the ring into its spare slot).
-    __device__ __forceinline__ void take_pending(unsigned long long raw, bool who = true) {
-        const bool have = who && pend_r >= 0;
-        const unsigned hi = (unsigned)(raw >> 32);
-        const int n = (int)(hi >> 16);
-        const int own_mem = (int)(hi & 0xFFFFu);
-        const int own = pend_own > own_mem ? pend_own : own_mem;
-        const int next = pend_next >= 0 ? pend_next : (int)(unsigned)raw;
-        const bool alive = have && own < n;
-        const int slot = alive ? (ring_head + ring_cnt) & (LOOK_RING - 1) : LOOK_RING;
-        ring[slot * WAVE] = (unsigned long long)(unsigned)pend_r | ((unsigned long long)((hi & 0xFFFF0000u) | (unsigned)own) << 32);
-        ring_cnt += alive ? 1 : 0;
-        ring_hi = alive ? pend_r : ring_hi;
-        n_dead += have && !alive ? 1 : 0;
-        fill_r = have ? next : fill_r;
-        pend_r = have ? -1 : pend_r;
-    }
-    // Request the next record of the log where the ring has room for it.  Every lane loads (those with nothing to
-    // fetch read the spare record behind the log, `spare`, and ignore it), so that the load is a plain instruction
-    // of the request loop and not a branch around one.  Called right after take_pending: nothing is pending.
-    __device__ __forceinline__ void issue_fill(const unsigned long long* log64, int spare) {
-        const bool want = fill_r >= 0 && ring_cnt < LOOK_RING;
-        pend_r = want ? fill_r : -1;
-        pend_own = -1;
-        pend_next = -1;
-        pend_raw = ld(&log64[want ? fill_r : spare]);
-    }
-    // whether request `owner` may be one of the records in the ring (then disowned_anywhere is the call to make)
-    __device__ __forceinline__ bool maybe_in_ring(int owner) const { return ring_cnt > 0 && owner <= ring_hi; }
-    // request `owner`'s owned suffix now starts at `end` (owner = -2: nobody's); the owner is not in the ring
-    __device__ __forceinline__ void disowned(int owner, int end) {
-        cur_own = owner == cur_r ? end : cur_own;
-        pend_own = owner == pend_r ? end : pend_own;
-    }
-    // the same where the owner may be a record in the ring (only called by the lanes it concerns)
-    __device__ __forceinline__ void disowned_anywhere(int owner, int end) {
-        disowned(owner, end);
-        if (maybe_in_ring(owner)) {
-#pragma nounroll
-            for (int k = 0; k < LOOK_RING; ++k) {
-                const unsigned long long e = ring[k * WAVE];
-                if ((int)(unsigned)e == owner)
-                    ring[k * WAVE] = (e & ~(0xFFFFull << 32)) | ((unsigned long long)(unsigned)end << 32);
+// ---------------------------------------------------------------------------------------------- book-keeping
+// Book-keeping wavefront: after X(r) it stores what decision r changes in memory -- the cells of the request's segments
+// on the chosen replica, the rows that start over, the log record, its link, the previous owner's suffix -- and keeps
+// the routes and hit counts.  Stores that only some lanes have use for are issued by every lane, the others aimed at a
+// row and a log record that nothing reads: a plain instruction is cheaper than a branch around it.
+template <bool PROXY, int PACK, bool TIMED>
+__device__ __forceinline__ void book_wave(const SegArgs& a, int lane, Handover<PROXY>* comm) {
+    const int R = a.R, N = (int)a.N;
+    const bool upper = PACK == 2 && lane >= HALF;
+    const int rl = PACK == 2 ? lane & (HALF - 1) : lane;
+    const size_t p0 = (size_t)blockIdx.x * PACK, p = p0 + (upper ? 1 : 0);
+    const bool in = rl < R;
+    const unsigned row_bytes = (unsigned)R * 4u;
+    const unsigned spare_row = (unsigned)(a.nseg - 1) * row_bytes;
+    const unsigned replay_off = upper ? (unsigned)a.nseg * row_bytes : 0u;
+    char* const rows = reinterpret_cast<char*>(a.last + p0 * (size_t)a.nseg * R);
+    auto cell_of = [&](uint32_t rowoff, int replica) -> int32_t* {
+        return reinterpret_cast<int32_t*>(rows + (rowoff + replay_off + (unsigned)replica * 4u));
+    };
+    auto cell_at = [&](uint32_t rowoff) -> int32_t* { return cell_of(rowoff, in ? rl : 0); };
+    LogRec* const log = a.log + p * ((size_t)N + 1);
+    unsigned long long* const log64 = reinterpret_cast<unsigned long long*>(log);
+    // the lanes that reset the row of a fresh last segment, and the replica of each
+    const bool narrow = PACK == 1 && R <= 32;
+    const bool reset_lane = narrow && lane >= 32;
+    const int reset_rep = lane - 32 < R ? lane - 32 : R - 1;
+    int tail_r = -1;                          // youngest request routed to replica = lane
+    int o_route = 0, o_hit = 0, o_seen = 0;
+    constexpr int BATCH = WAVE / PACK;
+    comm->first[lane] = -1;
+    meet(true);                               // the first descriptors are there
+    meet(false);
+    SectionClock<TIMED> clk;
+    clk.start();
+    for (int r = 0; r < N; ++r) {
+        const SegDesc* const d = &comm->ring[r & (DESC_RING - 1)];
+        const bool sync = (__builtin_amdgcn_readfirstlane(comm->ring[(r + 1) & (DESC_RING - 1)].flags) & DESC_SYNC) != 0;
+        const uint32_t of_seg = d->slot[rl & (SEG_CHUNK - 1)], of_tail = d->tail;
+        const int n = d->n, s = __builtin_amdgcn_readfirstlane(d->s), flags = __builtin_amdgcn_readfirstlane(d->flags);
+        clk.tick(2);                                                 // stores
+        meet(true);                                                  // X(r)
+        clk.tick(3);                                                 // waiting at X
+        const int lane_best = comm->best[r & 1][upper ? 1 : 0];
+        const Choice c = comm->choice[r & 1][lane_best];
+        const int best = PACK == 2 ? lane_best & (HALF - 1) : lane_best;
+        const bool is_best = rl == best;
+        // every segment of the request is now last touched by r on the chosen replica (lanes k, k + 8, ...: segment k).
+        // A segment that this request is the first to reference has taken over a row slot from a segment of the past: its
+        // row starts over, never cached except on the chosen replica.  Fresh segments are the last ones of the path;
+        // mostly there is one, or none.  With at most 32 replicas the upper lanes do that in the same store; further
+        // fresh segments, and any with more replicas or two replays, take a loop of their own.
+        {
+            const int rep = reset_lane ? reset_rep : best;
+            const int32_t val = reset_lane && rep != best ? NEVER_CACHED : r;
+            const uint32_t off = reset_lane ? (lane - 32 < R ? of_tail : spare_row) : of_seg;
+            st(cell_of(off, rep), val);
+        }
+        if (flags & (DESC_FRESH_MORE | DESC_DEEP)) {      // (one test on the usual path for the two rare cases)
+            const int32_t fresh_cell = is_best ? r : NEVER_CACHED;
+            if (flags & DESC_FRESH_MORE) {
+                const int first_fresh = (flags >> 16) & 15;
+                const int stop = (s < SEG_CHUNK ? s : SEG_CHUNK) - ((flags & DESC_FRESH_TAIL) ? 1 : 0);
+                for (int k = first_fresh; k < stop; ++k) {
+                    const uint32_t off = d->slot[k];
+                    st(cell_at(in ? off : spare_row), fresh_cell);
+                }
+            }
+            if (flags & DESC_DEEP) {
+                const int64_t j0 = d->j0;
+                for (int j = SEG_CHUNK; j < s; ++j) {
+                    const SegRef sr = a.seg[j0 + j];
+                    const uint32_t off = (uint32_t)sr.id * row_bytes;
+                    if (sr.end & SEG_FRESH) st(cell_at(in ? off : spare_row), fresh_cell);
+                    else if (is_best) st(cell_at(off), r);
+                }
             }
         }
-    }
-    // request r (n blocks) has become the youngest record of the log of the replica whose lane has is_best set;
-    // tail_r is the youngest before it
-    // (The replica's first record is not made the cursor's at once: it is the next one to fetch, like any record
-    // appended after the look-ahead has caught up with the log, and the cursor, which starts before every request,
-    // moves to it when something has to be evicted.)
-    __device__ __forceinline__ void appended(bool is_best, int r, int n, int tail_r) {
-        const bool to_pend = is_best && pend_r >= 0 && pend_r == tail_r;
-        const bool to_fill = is_best && !to_pend && pend_r < 0 && fill_r < 0;
-        pend_next = to_pend ? r : pend_next;
-        fill_r = to_fill ? r : fill_r;
-    }
-    // takes up to E blocks from the owned suffix of the cursor's record
-    __device__ __forceinline__ void take_from_cursor(int& E) {
-        int avail = cur_k - cur_own;
-        avail = avail > 0 ? avail : 0;
-        const int take = avail < E ? avail : E;
-        cur_k -= take;
-        E -= take;
-    }
-    // The cursor moves on to further records until E blocks have been given up (all lanes together, those with
-    // nothing to evict unchanged): records come from the ring, and from memory on the spot when the ring has run
-    // out.  Works on a copy of the state, written back at the end: the request loop's common path, which does not
-    // come here, then carries no register copies for this loop's sake.
-    __device__ __forceinline__ void advance(int E_in, const unsigned long long* log64, int spare) {
-        EvictCursor w = *this;
-        int E = E_in;
-        w.advance_loop(E, log64, spare);
-        *this = w;
-    }
-    __device__ __forceinline__ void advance_loop(int& E, const unsigned long long* log64, int spare) {
-        do {
-            const bool empty = E > 0 && ring_cnt == 0;
-            if (ballot(empty) != 0) {
-                // fetch a record on the spot (the one being fetched, if any, is waited for instead)
-                const bool fetch = empty && pend_r < 0 && fill_r >= 0;
-                const bool stuck = empty && pend_r < 0 && fill_r < 0;      // cannot happen; bounds the loop
-                live += stuck ? E : 0;
-                E = stuck ? 0 : E;
-                const unsigned long long got = ld(&log64[fetch ? fill_r : spare]);
-                pend_r = fetch ? fill_r : pend_r;
-                pend_own = fetch ? -1 : pend_own;
-                pend_next = fetch ? -1 : pend_next;
-                n_spot += fetch ? 1 : 0;
-                take_pending(fetch ? got : pend_raw, empty && !stuck);
-                continue;
+        comm->gone[(r + 3) & 3][lane] = 0.0;
+        st(&log64[r], 0xFFFFFFFFull | ((unsigned long long)n << 48));      // next -1, own 0, n
+        st(&log[is_best && tail_r >= 0 ? tail_r : N].next, r);
+        st(&log[c.owner >= 0 ? c.owner : N].own, (uint16_t)(c.hit_end >> 16));
+        if (is_best && tail_r < 0) comm->first[lane] = r;
+        tail_r = is_best ? r : tail_r;
+        const int slot = r & (BATCH - 1);
+        const bool mine = rl == slot;
+        o_route = mine ? best : o_route;
+        o_hit = mine ? (int)(c.hit_end & 0xFFFFu) : o_hit;
+        if (PROXY) o_seen = mine ? (int)comm->seen[r & 1][lane_best] : o_seen;
+        if (slot == BATCH - 1 || r == N - 1) {
+            const int x = r - slot + rl;
+            if (rl <= slot) {
+                const size_t o = p * N + x;
+                if (a.route) a.route[o] = (uint8_t)o_route;
+                if (a.hit) a.hit[o] = (uint16_t)o_hit;
+                if (PROXY && a.believed) a.believed[o] = (uint16_t)o_seen;
             }
-            const bool go = E > 0;
-            const unsigned long long e = ring[(ring_head & (LOOK_RING - 1)) * WAVE];
-            const unsigned hi = (unsigned)(e >> 32);
-            n_adv += go ? 1 : 0;
-            cur_r = go ? (int)(unsigned)e : cur_r;
-            cur_k = go ? (int)(hi >> 16) : cur_k;
-            cur_own = go ? (int)(hi & 0xFFFFu) : cur_own;
-            ring_head += go ? 1 : 0;
-            ring_cnt -= go ? 1 : 0;
-            take_from_cursor(E);         // (lanes with E = 0 take nothing)
-        } while (ballot(E > 0) != 0);
+        }
+        if (sync) meet(false);                                       // Y(r)
     }
-    // `added` blocks have joined the LRU of the lane with `active` set; the cursor moves forward until the LRU
-    // fits `cap` blocks again.  The cursor's own record is straight-line code; steps to further records loop (all
-    // lanes together, those with nothing to evict unchanged), taking records from the ring, and from memory on the
-    // spot when the ring has run out.
-    __device__ __forceinline__ void evict(bool active, int added, int cap, const unsigned long long* log64, int spare) {
-        live += active ? added : 0;
-        int E = active ? live - cap : 0;
-        E = E > 0 ? E : 0;
-        live -= E;
-        take_from_cursor(E);
-        if (ballot(E > 0) != 0) advance(E, log64, spare);
+    if (TIMED && a.sections && lane == 0) {
+        a.sections[(p0 * 3 + 2) * SECTIONS + 2] = clk.acc[2];
+        a.sections[(p0 * 3 + 2) * SECTIONS + 3] = clk.acc[3];
     }
-};
+}
 
-// Row cells of one request's first eight segments as seen by this lane (= replica), with the request's scalars
-// (the same in every lane) and the row of segment (lane mod 8), whose cell that lane stores.
-struct RowsOf {
-    int32_t cell[8];
-    int32_t end[8];
-    int L, n, s, flags;
-    uint32_t my_off;
-};
-
-// Cache wavefront of a replay.  Per request: meet (A); match the rows requested one request earlier, request the
-// next request's rows, score, take the minimum, announce the choice; meet (B); update ownership, rows, log and
-// eviction cursor on the chosen replica.
-template <int MODE, bool ENGINE, bool PROXY, bool TIMED>
-__device__ __forceinline__ void cache_wave(const SegArgs& a, int p, int lane, Handover* comm) {
+// ---------------------------------------------------------------------------------------------- deciding
+template <int MODE, bool ENGINE, bool PROXY, int PACK, bool TIMED>
+__device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Handover<PROXY>* comm) {
     constexpr bool ONLINE = MODE == MODE_ONLINE;
     constexpr bool SCORED = MODE == MODE_COST_MODEL || MODE == MODE_ONLINE;
+    constexpr bool COUNTS = MODE == MODE_LEAST_REQUEST;
     constexpr bool DICTATED = MODE == MODE_AFFINITY || MODE == MODE_RANDOM;
-    const int R = a.R;
-    const int64_t N = a.N;
+    const int R = a.R, N = (int)a.N;
+    const bool upper = PACK == 2 && lane >= HALF;
+    const int rl = PACK == 2 ? lane & (HALF - 1) : lane;
+    const size_t p0 = (size_t)blockIdx.x * PACK, p = p0 + (upper ? 1 : 0);
     const bool bounded = a.C > 0;
     // (kept in a vector register: under scalar-register pressure the compiler would otherwise re-read it from the
     // kernel arguments inside the request loop, a scalar-memory wait on the chain)
     int cap = (int)a.C;
     asm volatile("" : "+v"(cap));
-    const bool in = lane < R;
-    // (with the online tuner the weights come with the queue terms instead)
-    const double w_rtt = a.params[3 * (size_t)p + 0];
-    const double w_prefill = a.params[3 * (size_t)p + 1];
-    const double my_rtt = !PROXY && in ? a.rtt[lane] : 0.0;     // (proxy variants: comes with the queue terms)
-    const double rtt_term = w_rtt * my_rtt;                      // first product of Eq. 3, the same for every request
+    const bool in = rl < R;
+    double w_rtt = a.params[3 * p + 0], w_prefill = a.params[3 * p + 1], w_queue = a.params[3 * p + 2];
+    const double my_rtt = !PROXY && in ? a.rtt[rl] : 0.0;        // (proxy variants: comes from the queue wavefront)
+    double rtt_term = w_rtt * my_rtt;                            // first product of Eq. 3
+    double q = 0.0;           // load signal of replica = lane (an integer below 2^53, exact in fp64)
     // Proxy variants (Sec. 7: the proxy does not see replica-side eviction): the proxy keeps an index of its own
     // of what it dispatched to each replica, an LRU like the replica's cache but at least as large (or unbounded).
     // It sees the same touches, so it is the same rows read against a second eviction cursor (c2), which lags
@@ -907,81 +1149,66 @@ __device__ __forceinline__ void cache_wave(const SegArgs& a, int p, int lane, Ha
     c2.ring = &comm->look[1][lane];
     for (int k = 0; k <= LOOK_RING; ++k) {
         c1.ring[k * WAVE] = ~0ull;
-        c2.ring[k * WAVE] = ~0ull;
+        if (PROXY) c2.ring[k * WAVE] = ~0ull;
     }
-    int tail_r = -1;                          // youngest request routed to this replica
+    Fresh latest;                             // what the latest decision changes in the log
+    unsigned long long went1 = 0, went2 = 0, went3 = 0;  // where the three requests before went (a lane of each replay)
 
-    char* const rows = reinterpret_cast<char*>(a.last + (size_t)p * a.nseg * R);
-    // this lane's cell of a row; the rows of one replay span less than 4 GiB (checked by the host)
-    const unsigned lane_off = (unsigned)(in ? lane : 0) * 4u;
+    const char* const rows = reinterpret_cast<const char*>(a.last + p0 * (size_t)a.nseg * R);
     const unsigned row_bytes = (unsigned)R * 4u;
-    auto cell_at = [&](uint32_t rowoff) -> int32_t* { return reinterpret_cast<int32_t*>(rows + (rowoff + lane_off)); };
-    auto cell_of = [&](uint32_t rowoff, int replica) -> int32_t* {
-        return reinterpret_cast<int32_t*>(rows + (rowoff + (unsigned)replica * 4u));
-    };
-    // Stores and loads that only some lanes have use for are issued by every lane all the same, the others aimed
-    // at a spare location (a row and a log record that nothing reads): a plain instruction of the request loop is
-    // cheaper than a branch around it, and the number of memory operations in flight stays the same on every path.
-    const unsigned spare_row = (unsigned)(a.nseg - 1) * row_bytes;
-    const int spare = (int)N;                                   // the log record behind the last request's
-    LogRec* const log = a.log + (size_t)p * (N + 1);
-    unsigned long long* const log64 = reinterpret_cast<unsigned long long*>(log);
-    unsigned long long* const choice_slot = lane == 0 ? &comm->choice : &comm->unused[lane];
-    // the lanes that reset the row of a fresh last segment (see the store after the decision), and the replica of each
-    const bool reset_lane = R <= 32 && lane >= 32;
-    const int reset_rep = lane - 32 < R ? lane - 32 : R - 1;
+    // this lane's cell of a row; the rows of a workgroup span less than 4 GiB (checked by the host)
+    const unsigned lane_off = (upper ? (unsigned)a.nseg * row_bytes : 0u) + (unsigned)(in ? rl : 0) * 4u;
+    auto cell_at = [&](uint32_t rowoff) { return reinterpret_cast<const int32_t*>(rows + (rowoff + lane_off)); };
+    const int spare = N;                      // the log record behind the last request's
+    LogRec* const log = a.log + p * ((size_t)N + 1);
+    const unsigned long long* const log64 = reinterpret_cast<const unsigned long long*>(log);
 
-    // the row loads of one request, from its descriptor: the descriptor is read (LDS) well before the loads go out
-    struct DescCopy {
-        int4 h, e01, e23, e45, e67;
-        uint32_t my_off;
-    };
-    auto read_desc = [&](const SegDesc* d) {
-        DescCopy c;
-        c.h = *reinterpret_cast<const int4*>(&d->L);
-        c.e01 = reinterpret_cast<const int4*>(d->e)[0];
-        c.e23 = reinterpret_cast<const int4*>(d->e)[1];
-        c.e45 = reinterpret_cast<const int4*>(d->e)[2];
-        c.e67 = reinterpret_cast<const int4*>(d->e)[3];
-        c.my_off = d->store[lane];
-        return c;
-    };
-    auto request_rows = [&](const DescCopy& c, RowsOf& w) {
-        w.my_off = c.my_off;
-        w.L = c.h.x;
-        w.n = c.h.y;
-        w.s = c.h.z;
-        w.flags = c.h.w;
-        w.cell[0] = ld(cell_at((uint32_t)c.e01.x));
-        w.cell[1] = ld(cell_at((uint32_t)c.e01.z));
-        w.cell[2] = ld(cell_at((uint32_t)c.e23.x));
-        w.cell[3] = ld(cell_at((uint32_t)c.e23.z));
-        w.end[0] = c.e01.y;
-        w.end[1] = c.e01.w;
-        w.end[2] = c.e23.y;
-        w.end[3] = c.e23.w;
-        if (c.h.w & DESC_MORE4) {
-            w.cell[4] = ld(cell_at((uint32_t)c.e45.x));
-            w.cell[5] = ld(cell_at((uint32_t)c.e45.z));
-            w.cell[6] = ld(cell_at((uint32_t)c.e67.x));
-            w.cell[7] = ld(cell_at((uint32_t)c.e67.z));
-            w.end[4] = c.e45.y;
-            w.end[5] = c.e45.w;
-            w.end[6] = c.e67.y;
-            w.end[7] = c.e67.w;
-        }
+    c1.fetched = &comm->fetched[0][lane];
+    c2.fetched = &comm->fetched[PROXY ? 1 : 0][lane];
+
+    // the request in hand: row cells of its first eight segments as seen by this lane (= replica), where they end, tokens,
+    // blocks, flags; read (LDS) before the meeting that decides the one before, when LDS is waited for anyway
+    int32_t cell[SEG_CHUNK];
+    int end[SEG_CHUNK];
+    int L = 0, n = 0, flags = 0;
+    auto take = [&](int r) {
+        const SegDesc& d = comm->ring[r & (DESC_RING - 1)];
+        const int4 h = *reinterpret_cast<const int4*>(&d.L);
+#pragma unroll
+        for (int k = 0; k < SEG_CHUNK; ++k) cell[k] = comm->cells[r & 1][k][lane];
+        const int4 lo = reinterpret_cast<const int4*>(d.end)[0], hi = reinterpret_cast<const int4*>(d.end)[1];
+        end[0] = lo.x, end[1] = lo.y, end[2] = lo.z, end[3] = lo.w;
+        end[4] = hi.x, end[5] = hi.y, end[6] = hi.z, end[7] = hi.w;
+        L = h.x;
+        n = h.y;
+        flags = __builtin_amdgcn_readfirstlane(h.w);
     };
 
-    // Request r: `mine` holds its rows, `other` receives those of request r + 1.
     SectionClock<TIMED> clk;
     int n_walks = 0;          // statistics: ownership walks
-    auto step = [&](int64_t r, RowsOf& mine, RowsOf& other, auto feeds) {
+    meet(true);                               // the first descriptors and cells are there
+    take(0);
+    meet(true);                               // the queue wavefronts have set themselves up
+    clk.start();
+    for (int r = 0; r < N; ++r) {
         const SegDesc* const dr = &comm->ring[r & (DESC_RING - 1)];
+        const int n_now = n;      // (the next request's numbers are taken before this one is done with)
         const int target = DICTATED ? dr->target : 0;
-        const DescCopy next = read_desc(&comm->ring[(r + 1) & (DESC_RING - 1)]);
-        const int L = mine.L, n = mine.n, s = mine.s;
-        int32_t rv = (int32_t)r;            // the request's number, once in a vector register for the stores below
-        asm volatile("" : "+v"(rv));
+        const double left = DICTATED ? 0.0 : comm->gone[r & 3][lane];
+        const double rtt_now = PROXY ? comm->rtt[r & 3][PROXY ? lane : 0] : my_rtt;
+
+        // ---- the rows were loaded before the stores of the three requests before were sure to be there: the leading
+        // segments that the paths share get the cells that those requests wrote on their replicas
+        if (flags & DESC_SHARED) {
+            const int common1 = (flags >> 8) & 15, common2 = (flags >> 12) & 15, common3 = (flags >> 20) & 15;
+            const bool is1 = of_mask(went1), is2 = of_mask(went2), is3 = of_mask(went3);
+#pragma unroll
+            for (int k = 0; k < SEG_CHUNK; ++k) {
+                cell[k] = is3 && k < common3 ? r - 3 : cell[k];
+                cell[k] = is2 && k < common2 ? r - 2 : cell[k];
+                cell[k] = is1 && k < common1 ? r - 1 : cell[k];
+            }
+        }
 
         // ---- prefix match: lane = replica.  A request that touches a segment touches all its ancestors,
         // so along the path the cells never increase: first the segments touched after the cursor's
@@ -994,24 +1221,24 @@ __device__ __forceinline__ void cache_wave(const SegArgs& a, int p, int lane, Ha
         int e_gt2 = 0, e_ge2 = 0;   // proxy variants: the same against the index's cursor
         int32_t own_gt2 = -1;
         auto compare = [&](int k) {
-            const bool gt = mine.cell[k] > c1.cur_r;
-            const bool ge = mine.cell[k] >= c1.cur_r;
-            e_gt = gt ? mine.end[k] : e_gt;
-            own_gt = gt ? mine.cell[k] : own_gt;
-            e_ge = ge ? mine.end[k] : e_ge;
+            const bool gt = cell[k] > c1.cur_r;
+            const bool ge = cell[k] >= c1.cur_r;
+            e_gt = gt ? end[k] : e_gt;
+            own_gt = gt ? cell[k] : own_gt;
+            e_ge = ge ? end[k] : e_ge;
             if (PROXY) {
-                const bool gt2 = mine.cell[k] > c2.cur_r;
-                const bool ge2 = mine.cell[k] >= c2.cur_r;
-                e_gt2 = gt2 ? mine.end[k] : e_gt2;
-                own_gt2 = gt2 ? mine.cell[k] : own_gt2;
-                e_ge2 = ge2 ? mine.end[k] : e_ge2;
+                const bool gt2 = cell[k] > c2.cur_r;
+                const bool ge2 = cell[k] >= c2.cur_r;
+                e_gt2 = gt2 ? end[k] : e_gt2;
+                own_gt2 = gt2 ? cell[k] : own_gt2;
+                e_ge2 = ge2 ? end[k] : e_ge2;
             }
         };
         compare(0);
         compare(1);
         compare(2);
         compare(3);
-        if (mine.flags & DESC_MORE4) {
+        if (flags & DESC_MORE4) {
             compare(4);
             compare(5);
             compare(6);
@@ -1028,41 +1255,44 @@ __device__ __forceinline__ void cache_wave(const SegArgs& a, int p, int lane, Ha
         // and whether all cached segments had the same previous owner.  (Proxy variants: the same for the
         // prefix in the index.)
         const int k_end = PROXY ? (some_eq2 ? e_ge2 : e_gt2) : (some_eq ? e_ge : e_gt);
-        const bool one_owner = PROXY ? (some_eq2 ? e_gt2 == 0 : own_gt2 == mine.cell[0])
-                                     : (some_eq ? e_gt == 0 : own_gt == mine.cell[0]);
+        // (masks over the lanes, put together with scalar instructions: nothing of it is on the chain)
+        const unsigned long long by_cursor = PROXY ? ballot(below_cursor2 > e_gt2) : ballot(below_cursor > e_gt);
+        const unsigned long long one_owner = (by_cursor & ballot((PROXY ? e_gt2 : e_gt) == 0)) |
+                                             (~by_cursor & ballot((PROXY ? own_gt2 : own_gt) == cell[0]));
         bool deep = false;          // the match went past the preloaded segments
-        if (mine.flags & DESC_DEEP) {
-            // more than eight segments (rare): the rest of the path is read from the trace, eight references at a
-            // time, as long as some replica's prefix is still open
+        if (flags & DESC_DEEP) {
+            // more than eight segments (rare; memory is up to date, Y(r - 1)): the rest of the path is read from the trace,
+            // eight references at a time, as long as some replica's prefix is still open
             const int64_t j0 = dr->j0;
-            int pos = mine.end[7];
+            const int s = __builtin_amdgcn_readfirstlane(dr->s);
+            int pos = end[7];
             bool open = my_m == pos;
             bool open_seen = PROXY && my_seen == pos;
             if (ballot((PROXY ? open_seen : open) && in) != 0) {
                 deep = true;
                 for (int c0 = 8; c0 < s; c0 += 8) {
-                    int32_t cell[8];
+                    int32_t more[8];
                     int send[8];
 #pragma unroll
                     for (int k = 0; k < 8; ++k) {
-                        cell[k] = NEVER_CACHED;
+                        more[k] = NEVER_CACHED;
                         send[k] = pos;
                         if (c0 + k < s) {
                             const SegRef sr = a.seg[j0 + c0 + k];
                             send[k] = sr.end & SEG_END_MASK;
                             // (a fresh segment's row still holds what a segment of the past left there)
                             if ((PROXY ? open_seen : open) && in && !(sr.end & SEG_FRESH))
-                                cell[k] = ld(cell_at((uint32_t)sr.id * row_bytes));
+                                more[k] = ld(cell_at((uint32_t)sr.id * row_bytes));
                         }
                     }
 #pragma unroll
                     for (int k = 0; k < 8; ++k) {
                         if (c0 + k < s) {
-                            const int cnt = cached_in(cell[k], pos, send[k], c1.cur_r, c1.cur_k);
+                            const int cnt = cached_in(more[k], pos, send[k], c1.cur_r, c1.cur_k);
                             my_m += open ? cnt : 0;
                             open = open && cnt == send[k] - pos;
                             if (PROXY) {
-                                const int cnt_seen = cached_in(cell[k], pos, send[k], c2.cur_r, c2.cur_k);
+                                const int cnt_seen = cached_in(more[k], pos, send[k], c2.cur_r, c2.cur_k);
                                 my_seen += open_seen ? cnt_seen : 0;
                                 open_seen = open_seen && cnt_seen == send[k] - pos;
                             }
@@ -1073,13 +1303,26 @@ __device__ __forceinline__ void cache_wave(const SegArgs& a, int p, int lane, Ha
                 }
             }
         }
+        clk.tick(1);                                                 // patch, match (and the wait for the rows)
 
-        clk.tick(1);                                                 // match (and the wait for the rows)
-        // ---- the rows of this request have arrived: the loads for the next request go out
-        request_rows(next, other);
+        // (every fourth request: the log record asked for four requests ago has arrived and becomes usable, and the next
+        // one is asked for.  A replica's look-ahead needs a record every thirty requests or so, and holds eight.)
+        if ((r & 3) == 3) {
+            const int first = comm->first[lane];
+            c1.take_pending(*c1.fetched);
+            comm->wanted[0][lane] = c1.ask(spare, latest, first);
+            if (PROXY) {
+                int also = spare;
+                if (index_cap > 0) {
+                    c2.take_pending(*c2.fetched);
+                    also = c2.ask(spare, latest, first);
+                }
+                comm->wanted[PROXY ? 1 : 0][lane] = also;
+            }
+        }
+        clk.tick(2);                                                 // log records
 
-        // ---- score (Eq. 3: rtt and prefill terms here, the queue term from the queue wavefront) and lowest-index
-        // minimum.  block_tokens * blocks fits: below 2^15 and 2^16.
+        // ---- score (Eq. 3) and lowest-index minimum.  block_tokens * blocks fits: below 2^15 and 2^16.
         int hit_tok = __mul24(a.block_tokens, my_m);
         hit_tok = hit_tok > L ? L : hit_tok;
         const int my_u = L - hit_tok;
@@ -1089,170 +1332,141 @@ __device__ __forceinline__ void cache_wave(const SegArgs& a, int p, int lane, Ha
             seen_tok = seen_tok > L ? L : seen_tok;
             my_u_seen = L - seen_tok;
         }
-        clk.tick(2);                                                 // log records, next rows, uncached tokens
-        meet(false);                                                 // A(r): the queue terms of r are there
-        clk.tick(0);                                                 // waiting at A
-        const double sq = SCORED || MODE == MODE_LEAST_REQUEST ? comm->sq[lane] : 0.0;
-        double rtt_now = my_rtt, now_rtt = w_rtt, now_prefill = w_prefill;
-        if (PROXY) rtt_now = comm->rtt[lane];
-        if (ONLINE) {
-            now_rtt = comm->w[0];
-            now_prefill = comm->w[1];
-        }
-        // (while those words come from LDS, every fourth request: the log record requested four requests ago has
-        // arrived and becomes usable, and the next one is requested.  A replica's look-ahead needs a record every
-        // thirty requests or so, and holds eight; feeding it in every fourth request costs a quarter.  Only the
-        // second copy of the step has the code at all, so the other requests do not even branch around it.)
-        if (decltype(feeds)::value && (r & 2)) {
-            c1.take_pending(c1.pend_raw);
-            if (PROXY && index_cap > 0) c2.take_pending(c2.pend_raw);
-            c1.issue_fill(log64, spare);
-            if (PROXY && index_cap > 0) c2.issue_fill(log64, spare);
-        }
-        double my_score;
+        q += left;
+        double my_score, my_prefill = (double)my_u;
+        if (!ENGINE && !PROXY) my_prefill = a.a_pf * my_prefill;
         if (SCORED) {
-            const double pf = a.a_pf * (double)my_u_seen;
-            const double s_rtt = ONLINE || PROXY ? now_rtt * rtt_now : rtt_term;
-            const double s_pf = now_prefill * pf;
+            const double pf = PROXY || ENGINE ? a.a_pf * (double)my_u_seen : my_prefill;
+            const double s_rtt = PROXY ? w_rtt * rtt_now : rtt_term;
+            const double s_pf = w_prefill * pf;
             const double rtt_and_prefill = s_rtt + s_pf;
-            my_score = rtt_and_prefill + sq;
-        } else if (MODE == MODE_LEAST_REQUEST) {
-            my_score = sq;                      // requests in flight
+            const double qd = a.a_pf * q;
+            const double s_q = w_queue * qd;
+            my_score = rtt_and_prefill + s_q;
+        } else if (COUNTS) {
+            my_score = q;                       // requests in flight
         } else {
-            my_score = lane == target ? 0.0 : 1.0;      // the replica is dictated
+            my_score = rl == target ? 0.0 : 1.0;        // the replica is dictated
         }
-        const int best = argmin_lanes(my_score, in);
-        const bool is_best = lane == best;
-        const int m_best = __builtin_amdgcn_readlane(my_m, best);
-        const int seen_best = PROXY ? __builtin_amdgcn_readlane(my_seen, best) : m_best;
-        const unsigned u_best = (unsigned)__builtin_amdgcn_readlane(my_u, best);
-        // (every lane writes: lane 0 the word that is read, the others a word of their own that is not)
-        *choice_slot = ((unsigned long long)((unsigned)best | ((unsigned)m_best << 8)) << 32) | u_best;
-        if (PROXY && lane == 0) comm->seen = own_index ? seen_best : m_best;
+        // ---- ownership, whatever the choice: the segments this request takes over on the chosen replica stop belonging
+        // to their previous requests.  Along the path the previous owners form runs; each run moves its owner's `own` to
+        // the end of the run.  Only cached segments matter (evicted ones belong to requests the cursor has passed, or to
+        // the cursor request beyond its position).  One previous owner (the usual case) needs no walk; one whose record
+        // waits in a cursor's look-ahead ring goes the long way too: rare, the ring holds the oldest records of the
+        // replica and previous owners are mostly young.
+        const int held = PROXY ? my_seen : my_m;
+        const unsigned long long holders = ballot(held > 0);
+        unsigned long long plain = deep ? 0 : one_owner & ~(ballot(c1.ring_cnt > 0) & ballot(cell[0] <= c1.ring_hi));
+        if (PROXY) plain &= ~(ballot(c2.ring_cnt > 0) & ballot(cell[0] <= c2.ring_hi));
+        const unsigned long long walkers = holders & ~plain;
+        const int owner = of_mask(holders & plain) ? cell[0] : -2;
+        comm->choice[r & 1][lane] = Choice{my_prefill, owner, (unsigned)my_m | ((unsigned)k_end << 16)};
+        if (PROXY) comm->seen[r & 1][lane] = (uint16_t)(own_index ? my_seen : my_m);
+
+        const unsigned long long bests = argmin_mask<PACK>(my_score, in, upper);
+        if (PACK == 1) comm->best[r & 1][0] = __builtin_ctzll(bests);
+        else comm->best[r & 1][upper ? 1 : 0] = upper ? HALF + __builtin_ctz((unsigned)(bests >> 32)) : __builtin_ctz((unsigned)bests);
+        const bool is_best = of_mask(bests);
         clk.tick(3);                                                 // score, minimum, announcement
-        // (the announcement is on its way through LDS; the second meeting comes after the ownership update below,
-        // which does not depend on the queue side and gives it the time to arrive)
-
-        // ---- ownership: the segments this request takes over on the chosen replica stop belonging to
-        // their previous requests.  Along the path the previous owners form runs; each run moves its
-        // owner's `own` to the end of the run.  Only cached segments matter (evicted ones belong to
-        // requests the cursor has passed, or to the cursor request beyond its position).  One previous owner
-        // (the usual case) is straight-line code: the chosen replica's lane names it, the others name nobody.
-        const bool cached_some = seen_best > 0;
-        // (a previous owner whose record waits in a cursor's look-ahead ring goes the long way too: rare, the ring
-        // holds the oldest records of the replica and previous owners are mostly young)
-        const bool plain_owner = one_owner && !c1.maybe_in_ring(mine.cell[0]) && !(PROXY && c2.maybe_in_ring(mine.cell[0]));
-        const bool simple = cached_some && !deep && ((ballot(plain_owner) >> best) & 1ull) != 0;
-        const int dis_owner = is_best && simple ? mine.cell[0] : -2;
-        if (cached_some && !simple) {
-            // several previous owners, or a prefix longer than the preloaded rows: walk it
-            ++n_walks;
-            auto disown = [&](int owner, int end) {       // lane `best`: owner's owned suffix now starts at end
-                st(&log[owner].own, (uint16_t)end);
-                c1.disowned_anywhere(owner, end);
-                if (PROXY) c2.disowned_anywhere(owner, end);
-            };
-            const int64_t j0 = dr->j0;
-            const int cb_r = __builtin_amdgcn_readlane(PROXY ? c2.cur_r : c1.cur_r, best);
-            const int cb_k = __builtin_amdgcn_readlane(PROXY ? c2.cur_k : c1.cur_k, best);
-            int run_owner = -1, run_end = 0, vpos = 0;
-            for (int j = 0; j < s; ++j) {
-                SegRef sr = a.seg[j0 + j];
-                const int32_t rl = sr.end & SEG_FRESH ? NEVER_CACHED : ld(cell_of((uint32_t)sr.id * row_bytes, best));
-                sr.end &= SEG_END_MASK;
-                const int cnt = cached_in(rl, vpos, sr.end, cb_r, cb_k);
+        // (the announcement is on its way through LDS; what follows needs nobody else and gives it the time to arrive)
+        if (COUNTS) q += is_best ? 1.0 : 0.0;
+        else if (!DICTATED) q += is_best ? (double)L : 0.0;
+        latest.r = r;
+        latest.owner = is_best ? owner : -2;
+        latest.end = k_end;
+        c1.disowned(latest.owner, k_end);
+        if (PROXY) c2.disowned(latest.owner, k_end);
+        const bool walks = (walkers & bests) != 0;
+        auto disown = [&](int of, int end) {           // chosen lane: `of`'s owned suffix now starts at end
+            st(&log[of].own, (uint16_t)end);
+            c1.disowned_anywhere(of, end);
+            if (PROXY) c2.disowned_anywhere(of, end);
+        };
+        // the ownership walk: segments [j0, j1) of the path, then what is left of it
+        bool walking = false;
+        int run_owner = -1, run_end = 0, vpos = 0;
+        auto walk = [&](int j0, int j1, auto segment) {
+            const int cb_r = PROXY ? c2.cur_r : c1.cur_r, cb_k = PROXY ? c2.cur_k : c1.cur_k;
+            for (int j = j0; j < j1 && ballot(walking) != 0; ++j) {
+                int32_t at;
+                int to;
+                segment(j, walking, at, to);
+                const int cnt = walking ? cached_in(at, vpos, to, cb_r, cb_k) : 0;
                 if (cnt > 0) {
-                    if (rl != run_owner) {
-                        if (run_owner >= 0 && is_best) disown(run_owner, run_end);
-                        run_owner = rl;
+                    if (at != run_owner) {
+                        if (run_owner >= 0) disown(run_owner, run_end);
+                        run_owner = at;
                     }
-                    run_end = sr.end;
+                    run_end = to;
                 }
-                if (cnt != sr.end - vpos) break;
-                vpos = sr.end;
+                walking = walking && cnt == to - vpos;
+                vpos = to;
             }
-            if (run_owner >= 0 && is_best) disown(run_owner, run_end);
-        }
-        c1.disowned(dis_owner, k_end);
-        if (PROXY) c2.disowned(dis_owner, k_end);
-        st(&log[dis_owner >= 0 ? dis_owner : spare].own, (uint16_t)k_end);
-
-        clk.tick(5);                                                 // ownership
-        meet(true);                                                  // B(r): the choice is there (the stores below follow it:
-                                                                     // the queue wavefront need not wait for them)
-        clk.tick(4);                                                 // waiting at B
-        // ---- cache update: every segment of the request is now last touched by r on the chosen replica
-        // (lane k, and k + 8, ..., store the cell of segment k)
-        // A segment that this request is the first to reference has taken over a row slot from a segment of the
-        // past (the loader hands slots on): the row starts over, every replica's cell, never cached except on the
-        // chosen one.  Fresh segments are the last ones of the path; mostly there is one, or none.  With at most 32
-        // replicas the upper lanes do that in the same store: lane 32 + i writes replica i's cell of the row that the
-        // front end names (the last segment's if it is fresh).  Further fresh segments, and any with more replicas,
-        // take a loop of their own.
-        {
-            const int rep = reset_lane ? reset_rep : best;
-            const int32_t val = reset_lane && rep != best ? NEVER_CACHED : rv;
-            st(cell_of(mine.my_off, rep), val);
-        }
-        if (mine.flags & (DESC_FRESH_MORE | DESC_DEEP)) {      // (one test on the usual path for the two rare cases)
-            if (mine.flags & DESC_FRESH_MORE) {
-                const int first_fresh = (mine.flags >> 16) & 15;
-                const int stop = (s < 8 ? s : 8) - ((mine.flags & DESC_FRESH_TAIL) ? 1 : 0);
-                const int32_t fresh_cell = is_best ? (int32_t)r : NEVER_CACHED;
-                for (int k = first_fresh; k < stop; ++k) {
-                    const uint32_t off = ld(&dr->slot[k]);
-                    st(cell_at(in ? off : spare_row), fresh_cell);
-                }
-            }
-            if (mine.flags & DESC_DEEP) {
+        };
+        int E = 0, E2 = 0;
+        auto evict_first = [&]() {
+            E = c1.evict_first(is_best && bounded, n_now - my_m, cap);
+            // the proxy's index evicts under its own capacity: its cursor walks the same log
+            if (PROXY && index_cap > 0) E2 = c2.evict_first(is_best, n_now - my_seen, index_cap);
+        };
+        if (walks) {
+            ++n_walks;
+            walking = of_mask(walkers & bests);
+            if (deep) {
+                // a prefix longer than the preloaded rows: from memory, which nobody writes before X(r) (Y(r - 1))
                 const int64_t j0 = dr->j0;
-                for (int j = 8; j < s; ++j) {
+                walk(0, __builtin_amdgcn_readfirstlane(dr->s), [&](int j, bool on, int32_t& at, int& to) {
                     const SegRef sr = a.seg[j0 + j];
-                    const uint32_t off = (uint32_t)sr.id * row_bytes;
-                    if (sr.end & SEG_FRESH) st(cell_at(in ? off : spare_row), is_best ? (int32_t)r : NEVER_CACHED);
-                    else if (is_best) st(cell_at(off), (int32_t)r);
+                    to = sr.end & SEG_END_MASK;
+                    at = on && !(sr.end & SEG_FRESH) ? ld(cell_at((uint32_t)sr.id * row_bytes)) : NEVER_CACHED;
+                });
+                if (run_owner >= 0) disown(run_owner, run_end);
+            }
+            int32_t old[SEG_CHUNK];
+#pragma unroll
+            for (int k = 0; k < SEG_CHUNK; ++k) old[k] = cell[k];
+            const bool more4 = (flags & DESC_MORE4) != 0;
+            take(r + 1);
+            meet(true);                                              // X(r)
+            if (!deep) {
+                // several previous owners: from the preloaded rows (after X(r): the book-keeping wavefront has then moved
+                // the previous request's owner, which may be one of these), through LDS (the announcement before the last
+                // is done with): a loop over registers would keep all of them in memory
+                int32_t* const by_lane = reinterpret_cast<int32_t*>(&comm->choice[(r + 1) & 1][0]) + lane;
+                for (int h = 0; h < (more4 ? 2 : 1); ++h) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) by_lane[k * WAVE] = h == 0 ? old[k] : old[4 + k];
+                    walk(4 * h, 4 * h + 4, [&](int j, bool, int32_t& at, int& to) {
+                        at = by_lane[(j & 3) * WAVE];
+                        to = dr->end[j];
+                    });
                 }
+                if (run_owner >= 0) disown(run_owner, run_end);
+            }
+            evict_first();
+        } else {
+            evict_first();
+            take(r + 1);
+            clk.tick(5);                                             // ownership, cursor, the next request
+            meet(true);                                              // X(r)
+        }
+        clk.tick(0);                                                 // waiting at X
+        if (ballot(E > 0) != 0) c1.advance(E, log64, spare, latest, comm->first[lane]);
+        if (PROXY && ballot(E2 > 0) != 0) c2.advance(E2, log64, spare, latest, comm->first[lane]);
+        went3 = went2;
+        went2 = went1;
+        went1 = bests;
+        clk.tick(6);                                                 // eviction past the cursor's record
+        if (flags & DESC_SYNC) {
+            meet(false);                                             // Y(r)
+            if (ONLINE) {
+                w_rtt = comm->w[upper ? 1 : 0][0];
+                w_prefill = comm->w[upper ? 1 : 0][1];
+                w_queue = comm->w[upper ? 1 : 0][2];
+                rtt_term = w_rtt * my_rtt;
             }
         }
-
-        // ---- log (every lane writes the same record; the chosen replica's lane links it) and eviction
-        st(&log64[r], 0xFFFFFFFFull | ((unsigned long long)n << 48));      // next -1, own 0, n
-        st(&log[is_best && tail_r >= 0 ? tail_r : spare].next, rv);
-        clk.tick(6);                                                 // stores, log
-        c1.appended(is_best, rv, n, tail_r);
-        if (PROXY) c2.appended(is_best, (int)r, n, tail_r);
-        tail_r = is_best ? rv : tail_r;
-        c1.evict(is_best && bounded, n - m_best, cap, log64, spare);
-        // the proxy's index evicts under its own capacity: its cursor walks the same log (whose memory is up to
-        // date: ownership changes and links are stored as they happen)
-        if (PROXY && index_cap > 0) c2.evict(is_best, n - seen_best, index_cap, log64, spare);
-
-        // ---- the rows of request r + 1 were requested before this request's stores: the leading segments the two
-        // paths share (none unless r + 1 continues the same tree) get the cells this request just wrote
-        const int common = (other.flags >> 8) & 0xFF;
-        if (common > 0) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) other.cell[k] = (k < common && is_best) ? rv : other.cell[k];
-            if (other.flags & DESC_MORE4) {
-#pragma unroll
-                for (int k = 4; k < 8; ++k) other.cell[k] = (k < common && is_best) ? rv : other.cell[k];
-            }
-        }
-        clk.tick(7);                                                 // eviction, patch, loop
-    };
-
-    RowsOf A, B;
-    meet(false);                              // the first descriptors are there
-    request_rows(read_desc(&comm->ring[0]), A);
-    // (Where the loop is entered, as many memory operations are in flight behind the first request's row loads as a
-    // pass through the loop leaves behind the next request's -- a log record load and five stores -- so that the
-    // wait for the rows at the top of the loop is the same wait on both ways in, and not one for everything.)
-    c1.issue_fill(log64, spare);
-    for (int k = 0; k < 5; ++k) st(&log64[spare], 0ull);
-    clk.start();
-    for (int64_t r = 0; r < N; r += 2) {
-        step(r, A, B, std::false_type{});
-        if (r + 1 < N) step(r + 1, B, A, std::true_type{});
+        clk.tick(4);                                                 // waiting at Y
     }
     if (TIMED) {
         // statistics of the eviction walk, summed over the replicas
@@ -1261,34 +1475,37 @@ __device__ __forceinline__ void cache_wave(const SegArgs& a, int p, int lane, Ha
         clk.acc[10] = wave_sum_u32((unsigned)c1.n_dead);
         clk.acc[11] = (unsigned)__builtin_amdgcn_readfirstlane(n_walks);
     }
-    clk.write(a.sections ? a.sections + (size_t)p * 3 * SECTIONS : nullptr, lane);
+    clk.write(a.sections ? a.sections + p0 * 3 * SECTIONS : nullptr, lane);
 }
 
-// (At most 128 vector registers: four wavefronts per SIMD.  The 1,024 replays of a population are 3,072 wavefronts,
-// three per SIMD on 256 CUs; with registers for exactly three per SIMD a workgroup only fits where the wavefronts
-// happen to be spread evenly, and part of the population waits for a second round.)
-template <int MODE, bool ENGINE, bool PROXY, bool SLOTS = false, bool TIMED = false>
-__global__ void __launch_bounds__(SEG3_THREADS, 4) replay_segments_kernel(SegArgs a) {
+// One workgroup = one replay, or two neighbouring ones (PACK = 2: at most 32 replicas, one lane per service slot).
+// (At most 128 vector registers: four wavefronts per SIMD, so that the 1,024 workgroups of four wavefronts are all
+// resident.)
+template <int PACK>
+constexpr int seg_threads() { return (3 + PACK) * WAVE; }
+
+template <int MODE, bool ENGINE, bool PROXY, int PACK = 1, bool TIMED = false>
+__global__ void __launch_bounds__(seg_threads<PACK>(), PACK == 2 ? 5 : 4) replay_segments_kernel(SegArgs a) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    __shared__ __align__(16) Handover comm;
+    __shared__ __align__(16) Handover<PROXY> comm;
     const int lane = threadIdx.x & (WAVE - 1);
-    const int p = blockIdx.x;
-    if (threadIdx.x == 0) {
-        comm.w[0] = a.params[3 * (size_t)p + 0];
-        comm.w[1] = a.params[3 * (size_t)p + 1];
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+    unsigned char* const mine = lds_raw + (wave - 1) * replay_queue_lds_bytes(a.R, a.B, ENGINE, MODE == MODE_ONLINE ? a.window : 0);
+    if (a.N == 0) {
+        if (wave >= 1 && wave <= PACK) queue_wave<MODE, ENGINE, PROXY, PACK, false, TIMED>(a, wave - 1, lane, mine, &comm);
+        return;
     }
-    __syncthreads();
-    if (threadIdx.x >= 2 * WAVE) {
-        if (a.N > 0) {
-            __builtin_amdgcn_s_setprio(1);
-            front_wave<MODE, TIMED>(a, p, lane, &comm);
-        }
-    } else if (threadIdx.x >= WAVE) {
-        __builtin_amdgcn_s_setprio(3);
-        queue_wave<MODE, ENGINE, PROXY, SLOTS, TIMED>(a, p, lane, lds_raw, &comm);
-    } else if (a.N > 0) {
-        __builtin_amdgcn_s_setprio(3);      // the two wavefronts on the chain go first at issue
-        cache_wave<MODE, ENGINE, PROXY, TIMED>(a, p, lane, &comm);
+    if (wave == 0) {
+        __builtin_amdgcn_s_setprio(3);      // the wavefront on the chain goes first at issue
+        decide_wave<MODE, ENGINE, PROXY, PACK, TIMED>(a, lane, &comm);
+    } else if (wave <= PACK) {
+        __builtin_amdgcn_s_setprio(2);
+        queue_wave<MODE, ENGINE, PROXY, PACK, false, TIMED>(a, wave - 1, lane, mine, &comm);
+    } else if (wave == PACK + 1) {
+        __builtin_amdgcn_s_setprio(1);
+        book_wave<PROXY, PACK, TIMED>(a, lane, &comm);
+    } else {
+        front_wave<MODE, PROXY, PACK, TIMED>(a, lane, &comm);
     }
 }
 
