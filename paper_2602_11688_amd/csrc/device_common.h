@@ -351,7 +351,8 @@ struct SlotQueues {
         *ttft_out = (first_tok + half) - t;
         *e2e_out = done - t;
         const int at = best * B + k;
-        due |= lane == (at & (WAVE - 1)) && done <= until ? 1u << (at / WAVE) : 0u;
+        const unsigned bit = done <= until ? 1u << (at / WAVE) : 0u;
+        due |= lane == (at & (WAVE - 1)) ? bit : 0u;
         take_slot<REORDER>(s, k, d, r, end, done, weight, rec);
     }
 
@@ -407,7 +408,8 @@ struct SlotQueues {
         *ttft_out = (first_tok + half) - t;
         *e2e_out = done - t;
         const int at = best * B + k;
-        due |= lane == (at & (WAVE - 1)) && done <= until ? 1u << (at / WAVE) : 0u;
+        const unsigned bit = done <= until ? 1u << (at / WAVE) : 0u;
+        due |= lane == (at & (WAVE - 1)) ? bit : 0u;
         if (lane == k) kv[s] = tokens;           // two counts below 2^31 each
         take_slot<REORDER>(s, k, d, r, end, done, weight, rec);
     }

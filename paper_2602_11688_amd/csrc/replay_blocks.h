@@ -222,8 +222,9 @@ __device__ __forceinline__ void block_cache_wave(const BlockArgs& b, int p, int 
                                                 (uint32_t)(seed >> 32)), R);
 
         // ---- score (Eq. 3), lowest-index minimum; the load signal is kept here, what left it comes from the queue wavefront
-        q += comm->gone[r & 3][lane];
-        const double rtt_now = PROXY ? comm->rtt[r & 3][lane] : my_rtt;
+        q += comm->gone[r & 1][lane];
+        comm->gone[r & 1][lane] = 0.0;
+        const double rtt_now = PROXY ? comm->rtt[r & 3][PROXY ? lane : 0] : my_rtt;
         double my_score;
         if (SCORED) {
             const double pf = a.a_pf * (double)my_u_seen;
@@ -245,7 +246,7 @@ __device__ __forceinline__ void block_cache_wave(const BlockArgs& b, int p, int 
         q += lane == best ? (MODE == MODE_LEAST_REQUEST ? 1.0 : (double)L) : 0.0;
         if (lane == 0) {
             comm->choice[r & 1][best] = Choice{ENGINE || PROXY ? (double)(int)u_best : a.a_pf * (double)(int)u_best, -2, (unsigned)m_best};
-            if (PROXY) comm->seen[r & 1][best] = (uint16_t)seen_best;
+            if constexpr (PROXY) comm->seen[r & 1][best] = (uint16_t)seen_best;
             comm->best[r & 1][0] = best;
             st(&routed[r], (uint8_t)best);
         }

@@ -33,7 +33,7 @@
 //   The front-end wavefront walks the trace two dozen requests ahead, eight requests at a time, and leaves a descriptor
 // of each in an LDS ring; it touches the rows that will be read, so that they are in the L2 by then.
 // Where one barrier is not enough -- r may complete before r + 1 arrives, r + 1 has more segments than the deciding
-// wavefront preloads, the online tuner changes the weights after r -- the descriptor of r + 1 says so (DESC_SYNC), every
+// wavefront preloads, the online tuner changes the weights after r -- the descriptor of r says so (DESC_SYNC), every
 // wavefront of the workgroup reads that same word, and all meet once more, Y(r), when the queue and the book-keeping
 // wavefront have caught up with r.  The number of barriers a wavefront executes depends on the descriptors alone, so
 // none can wait for ever.
@@ -248,7 +248,7 @@ __device__ __forceinline__ int cached_in(int32_t rl, int pos, int end, int c_r, 
 
 // ---------------------------------------------------------------------------------------------- hand-over
 // Descriptor of one request, written by the front end.
-struct SegDesc {
+struct __align__(16) SegDesc {
     uint32_t rowoff[SEG_CHUNK];  // first eight segments: byte offset, within the replay's rows, of the row that the match
                          // reads.  Past the last segment: the never-cached row.  Also the never-cached row for a segment whose
                          // row slot starts over with this request (SEG_FRESH: what the slot still holds belongs to a segment of
@@ -262,7 +262,7 @@ struct SegDesc {
     int32_t target;      // replica dictated by the session-affinity / random policy
     uint32_t tail;       // the row of the request's last segment if DESC_FRESH_TAIL, else the spare row
     uint32_t slot[SEG_CHUNK];   // where the rows of the first eight segments really are (past the last one: the spare row)
-    double t[2];         // arrival at the time scale of each replay of the workgroup
+    double t2[2];        // arrival of the request after next at the time scale of each replay of the workgroup
     double dec;          // decode time in the linear model
     int32_t O;           // output tokens
     int32_t pad;
@@ -272,7 +272,7 @@ constexpr int DESC_MORE4 = 1;        // more than four segments
 constexpr int DESC_DEEP = 2;         // more than eight segments
 constexpr int DESC_FRESH_TAIL = 4;   // the last segment is fresh, among the first eight, and lanes 32..63 reset its row
 constexpr int DESC_FRESH_MORE = 8;   // further fresh segments among the first eight
-constexpr int DESC_SYNC = 16;        // all wavefronts meet once more between the previous request and this one
+constexpr int DESC_SYNC = 16;        // all wavefronts meet once more between this request and the next
 constexpr int DESC_SHARED = 0xF0FF00;            // any leading segment shared with the three requests before
 constexpr int DESC_RING = 16;        // descriptors in flight (power of two)
 constexpr int DESC_GROUP = WAVE / SEG_CHUNK;     // requests whose descriptors are written together
@@ -280,6 +280,7 @@ constexpr int DESC_AHEAD = DESC_GROUP;           // how far ahead of the request
 static_assert(DESC_AHEAD + DESC_GROUP <= DESC_RING, "the front end overwrites descriptors of requests that are done with");
 constexpr int32_t NEVER_CACHED = INT32_MIN;      // cell value of the extra row: below any cursor
 
+constexpr int CELL_SETS = 3;          // requests whose row cells are in LDS: two ahead are loaded while one is at hand
 constexpr int LOOK_RING = 8;          // log records of look-ahead kept in LDS per replica
 // What every replica would mean for a request, written by its lane before the minimum is known; the replica with the
 // minimum is announced by its number alone.
@@ -288,24 +289,30 @@ struct __align__(16) Choice {
     int owner;                        // request whose owned suffix would start at `end`, -2: none (or dealt with)
     unsigned hit_end;                 // cached blocks | end << 16
 };
+// An ownership change: `owner`'s owned suffix now starts at `end`.
+struct OwnChange {
+    int owner, end;
+};
+constexpr int OWN_LIST = -3;              // in Choice::owner: the changes are in Handover::changes, as many as its `end` says
 template <bool PROXY>
-struct Handover {
-    Choice choice[2][WAVE];           // [request mod 2][replica]
-    int best[2][2];                   // [request mod 2][replay of the workgroup] the choice: lane of the replica
-    uint16_t seen[PROXY ? 2 : 1][WAVE];   // proxy variants, [request mod 2]: blocks the proxy believes cached per replica
-    int first[WAVE];                  // first request routed to each replica (-1: none yet)
-    double gone[4][WAVE];             // [request mod 4][replica]: minus the tokens (least-request policy: the requests) that
-                                      // left the load signal between the previous request's arrival and this one's
-    double half[PROXY ? 4 : 1][WAVE]; // half the round trip time per replica (proxy variants: [request mod 4])
-    double rtt[PROXY ? 4 : 1][PROXY ? WAVE : 1];  // proxy variants, [request mod 4]: estimated round trip time per replica
-    double w[2][3];                   // online tuner: weights in use
-    SegDesc ring[DESC_RING];
-    int32_t cells[2][SEG_CHUNK][WAVE];    // [request mod 2]: row cells of the request's first eight segments per replica
+struct __align__(256) Handover {
+    int32_t cells[CELL_SETS][SEG_CHUNK][WAVE];    // [request mod 3]: row cells of the request's first eight segments per replica
+    Choice choice[2][WAVE];               // [request mod 2][replica]
+    double gone[2][WAVE];                 // [request mod 2][replica]: minus the tokens (least-request policy: the requests) that
+                                          // left the load signal between the previous request's arrival and this one's
     // look-ahead of the eviction cursors (the cache's; the proxy's index's): per replica, log records fetched ahead
-    // of the cursor, slot k of replica i at [k * WAVE + i]; the last slot is a spare that nothing reads
-    unsigned long long look[PROXY ? 2 : 1][(LOOK_RING + 1) * WAVE];
-    int wanted[PROXY ? 2 : 1][WAVE];                 // log records that the front end is to fetch, every fourth request,
-    unsigned long long fetched[PROXY ? 2 : 1][WAVE]; // and what it has fetched
+    // of the cursor, slot k of replica i at [k * WAVE + i] (one slot is always free)
+    unsigned long long look[PROXY ? 2 : 1][LOOK_RING * WAVE];
+    unsigned long long fetched[PROXY ? 2 : 1][WAVE]; // log records that the front end has fetched ...
+    int wanted[PROXY ? 2 : 1][WAVE];      // ... and is to fetch, every fourth request
+    SegDesc ring[DESC_RING];
+    double half[PROXY ? 4 : 1][WAVE];     // half the round trip time per replica (proxy variants: [request mod 4])
+    double rtt[PROXY ? 4 : 1][PROXY ? WAVE : 1];  // proxy variants, [request mod 4]: estimated round trip time per replica
+    double w[2][3];                       // online tuner: weights in use
+    int first[WAVE];                      // first request routed to each replica (-1: none yet)
+    int best[2][2];                       // [request mod 2][replay of the workgroup] the choice: lane of the replica
+    OwnChange changes[2][2][SEG_CHUNK];   // [request mod 2][replay]
+    uint16_t seen[PROXY ? 2 : 1][PROXY ? WAVE : 1];   // proxy variants, [request mod 2]: blocks the proxy believes cached
 };
 
 // Workgroup barrier; `after_lds`: this wavefront's LDS accesses have been performed before it arrives (what it wrote is
@@ -355,14 +362,14 @@ __device__ __forceinline__ int argmin_lanes(double v, bool in) {
     return __builtin_ctzll(ballot(tie && klo == mlo));
 }
 
-// Lowest-index minimum over the lanes with `in` set, of the wavefront or of either half of it (PACK = 2): a mask with
-// one bit per replay.  The values are compared as in wave_argmin.
+// Lowest-index minimum over the wavefront or over either half of it (PACK = 2): a mask with one bit per replay.  The
+// values are compared as in wave_argmin; none is NaN or -0.0, lanes without a replica hold +inf.
 template <int PACK>
-__device__ __forceinline__ unsigned long long argmin_mask(double v, bool in, bool upper) {
-    const unsigned long long bits = (unsigned long long)__double_as_longlong(v + 0.0);
+__device__ __forceinline__ unsigned long long argmin_mask(double v, bool upper) {
+    const unsigned long long bits = (unsigned long long)__double_as_longlong(v);
     const unsigned hi = (unsigned)(bits >> 32), lo = (unsigned)bits;
     const unsigned neg = (unsigned)((int)hi >> 31);
-    const unsigned khi = in ? hi ^ (neg | 0x80000000u) : 0xffffffffu;   // (lanes outside: a key that no score maps to)
+    const unsigned khi = hi ^ (neg | 0x80000000u);
     auto least = [&](unsigned x) {
         x = dpp_min_u32<0x111, 0xf>(x);   // row_shr:1
         x = dpp_min_u32<0x112, 0xf>(x);   // row_shr:2
@@ -377,11 +384,6 @@ __device__ __forceinline__ unsigned long long argmin_mask(double v, bool in, boo
         x = dpp_min_u32<0x143, 0xc>(x);   // row_bcast:31 into rows 2, 3
         return (unsigned)__builtin_amdgcn_readlane((int)x, WAVE - 1);
     };
-    auto several = [](unsigned long long m) {
-        if (PACK == 1) return (m & (m - 1)) != 0;
-        const unsigned a = (unsigned)m, b = (unsigned)(m >> 32);
-        return ((a & (a - 1)) | (b & (b - 1))) != 0;
-    };
     auto lowest = [](unsigned long long m) {
         if (PACK == 1) return m & (0 - m);
         const unsigned a = (unsigned)m, b = (unsigned)(m >> 32);
@@ -389,7 +391,7 @@ __device__ __forceinline__ unsigned long long argmin_mask(double v, bool in, boo
     };
     const bool tie = khi == least(khi);
     const unsigned long long ties = ballot(tie);
-    if (!several(ties)) return ties;            // one lane holds the smallest high word: done
+    if (__builtin_popcountll(ties) == PACK) return ties;      // one lane (of each half) holds the smallest high word: done
     const unsigned klo = lo ^ neg;
     const unsigned mlo = least(tie ? klo : 0xffffffffu);
     return lowest(ballot(tie && klo == mlo));
@@ -413,6 +415,16 @@ __device__ __forceinline__ bool of_mask(unsigned long long m) { return __builtin
 struct Fresh {
     int r = -1;               // the latest decided request (its own record cannot be loaded yet)
     int owner = -2, end = 0;  // on the replica it went to: record whose owned suffix now starts at `end`
+    int count = 0;            // ... or several such records
+    const OwnChange* list = nullptr;
+    __device__ __forceinline__ int of(int x) const {
+        int own = x == owner ? end : -1;
+        for (int i = 0; ballot(i < count) != 0; ++i) {
+            const OwnChange c = list[i & (SEG_CHUNK - 1)];
+            own = i < count && c.owner == x ? c.end : own;
+        }
+        return own;
+    }
 };
 struct EvictCursor {
     int cur_r = -1, cur_k = 0, cur_own = 0;
@@ -423,13 +435,13 @@ struct EvictCursor {
     // ring_cnt of them from slot ring_head on, the youngest being request ring_hi.
     unsigned long long* ring = nullptr;
     int ring_head = 0, ring_cnt = 0, ring_hi = -1;
-    int live = 0;             // blocks this LRU holds
+    int over = 0;             // blocks this LRU holds beyond its capacity (below 0: room)
     int n_spot = 0, n_adv = 0, n_dead = 0;       // statistics (only the timed instantiation reads them): records fetched
                                                  // on the spot, cursor advances, records dropped because they own nothing
 
     // In the lanes with `who` set, what was asked for has arrived: the link of last_r, or a record, which is dropped if
     // it owns nothing and else joins the ring.  Straight-line code: lanes with nothing pending go through it unchanged
-    // (every lane stores to LDS: those with nothing for the ring into its spare slot).
+    // (every lane stores to LDS: those with nothing for the ring into its free slot).
     __device__ __forceinline__ void take_pending(unsigned long long raw, bool who = true) {
         const bool have = who && pend_r >= 0;
         const unsigned hi = (unsigned)(raw >> 32);
@@ -438,8 +450,7 @@ struct EvictCursor {
         const int own = pend_own > own_mem ? pend_own : own_mem;
         const bool record = have && pend_r != last_r;
         const bool alive = record && own < n;
-        const int slot = alive ? (ring_head + ring_cnt) & (LOOK_RING - 1) : LOOK_RING;
-        ring[slot * WAVE] = (unsigned long long)(unsigned)pend_r | ((unsigned long long)((hi & 0xFFFF0000u) | (unsigned)own) << 32);
+        ring[((ring_head + ring_cnt) & (LOOK_RING - 1)) * WAVE] = (unsigned long long)(unsigned)pend_r | ((unsigned long long)((hi & 0xFFFF0000u) | (unsigned)own) << 32);
         ring_cnt += alive ? 1 : 0;
         ring_hi = alive ? pend_r : ring_hi;
         n_dead += record && !alive ? 1 : 0;
@@ -458,7 +469,7 @@ struct EvictCursor {
     // X(r), when everything that r - 1 changes is there; what r changes is kept in pend_own.
     __device__ __forceinline__ int ask(int spare, const Fresh& f, int first) {
         const int x = wanted(f, first);
-        const bool want = x >= 0 && ring_cnt < LOOK_RING;
+        const bool want = x >= 0 && ring_cnt < LOOK_RING - 1;
         pend_r = want ? x : -1;
         pend_own = -1;
         return want ? x : spare;
@@ -513,10 +524,9 @@ struct EvictCursor {
                 const bool stuck = empty && (x < 0 || (x == last_r && asked >= 2));
                 const bool fetch = empty && !stuck;
                 asked = fetch ? (x == last_r ? asked + 1 : 0) : asked;
-                live += stuck ? E : 0;
                 E = stuck ? 0 : E;
                 const unsigned long long got = ld(&log64[fetch ? x : spare]);
-                pend_own = fetch && !asked_for ? (x == f.owner ? f.end : -1) : pend_own;
+                pend_own = fetch && !asked_for ? f.of(x) : pend_own;
                 pend_r = fetch ? x : pend_r;
                 n_spot += fetch ? 1 : 0;
                 take_pending(got, fetch);
@@ -534,15 +544,14 @@ struct EvictCursor {
             take_from_cursor(E);         // (lanes with E = 0 take nothing)
         } while (ballot(E > 0) != 0);
     }
-    // `added` blocks have joined the LRU of the lane with `active` set.  First half: what the cursor's own record can
-    // give up, straight-line code; returns what is still to be evicted.  Second half, where some lane has any: steps
-    // to further records (all lanes together, those with nothing to evict unchanged), taking records from the ring,
-    // and from memory on the spot when the ring has run out.
-    __device__ __forceinline__ int evict_first(bool active, int added, int cap) {
-        live += active ? added : 0;
-        int E = active ? live - cap : 0;
-        E = E > 0 ? E : 0;
-        live -= E;
+    // `added` blocks have joined the LRU.  First half: what the cursor's own record can give up, straight-line code;
+    // returns what is still to be evicted.  Second half (advance), where some lane has any: steps to further records
+    // (all lanes together, those with nothing to evict unchanged), taking records from the ring, and from memory on the
+    // spot when the ring has run out.
+    __device__ __forceinline__ int evict_first(int added) {
+        over += added;
+        int E = over > 0 ? over : 0;
+        over -= E;
         take_from_cursor(E);
         return E;
     }
@@ -574,33 +583,35 @@ __device__ __forceinline__ void front_wave(const SegArgs& a, int lane, Handover<
         int64_t j0;
         uint32_t hash;
         bool sync;
-        double t0, t1;       // arrival, at the time scale of each replay of the workgroup
+        double t0, t1;       // arrival of the request after next, at the time scale of each replay of the workgroup
         int O;
     };
     auto load_scalars = [&](int g0, Scalars& c) {
         const int r = g0 + q;
         const bool on = r < N;                       // (requests past the end look empty)
-        const int x = on ? r : N - 1, before = x > 0 ? x - 1 : 0;
+        const int x = on ? r : N - 1;
         c.j0 = a.seg_off[x];
         c.s = on ? (int)(a.seg_off[x + 1] - c.j0) : 0;
         c.n = on ? (int)(a.blk_off[x + 1] - a.blk_off[x]) : 0;
         c.L = on ? a.in_len[x] : 0;
         c.hash = MODE == MODE_AFFINITY ? a.first_hash[x] : 0u;
-        // whether the request before may have completed by this one's arrival: it takes its decode time at least (every
-        // further term of its completion time is added to it and none is negative: rounding keeps the order)
-        bool sync = c.s > SEG_CHUNK;
-        const double at = (double)a.ts[x];
-        c.t0 = at * scale0;
-        c.t1 = at * scale1;
         c.O = a.out_len[x];
+        const bool has1 = r + 1 < N, has2 = r + 2 < N;
+        const double t2 = (double)a.ts[has2 ? r + 2 : N - 1];
+        c.t0 = t2 * scale0;
+        c.t1 = t2 * scale1;
+        // whether all wavefronts meet once more before the next request: if it has more segments than are preloaded ...
+        bool sync = a.seg_off[has1 ? r + 2 : N] - a.seg_off[has1 ? r + 1 : N] > SEG_CHUNK;
+        // ... if this one may have completed by its arrival -- it takes its decode time at least: every further term of its
+        // completion time is added to it and none is negative, and rounding keeps the order ...
         if (SIGNAL) {
-            const double ahead = (double)a.ts[before], dec = a.least_dec * (double)a.out_len[before];
-            sync = sync || !(ahead * scale0 + dec > c.t0);
-            if (PACK == 2) sync = sync || !(ahead * scale1 + dec > c.t1);
+            const double t = (double)a.ts[x], t1 = (double)a.ts[has1 ? r + 1 : N - 1], dec = a.least_dec * (double)c.O;
+            sync = sync || !(t * scale0 + dec > t1 * scale0);
+            if (PACK == 2) sync = sync || !(t * scale1 + dec > t1 * scale1);
         }
-        // whether the tuner changes the weights between the two
-        if (MODE == MODE_ONLINE) sync = sync || (r >= a.window && (unsigned)(r - a.window) % (unsigned)a.hop == 0u);
-        c.sync = on && r > 0 && sync;
+        // ... and if the tuner changes the weights after this one
+        if (MODE == MODE_ONLINE) sync = sync || (r + 1 >= a.window && (unsigned)(r + 1 - a.window) % (unsigned)a.hop == 0u);
+        c.sync = has1 && sync;
     };
     int ref_id = -1, ref_end = 0;                    // (-1: no such segment)
     auto load_ref = [&](const Scalars& c) {
@@ -676,8 +687,8 @@ __device__ __forceinline__ void front_wave(const SegArgs& a, int lane, Handover<
                 d->target = spread(philox4x32_10_first((uint32_t)(g0 + q), 0u, (uint32_t)seed, (uint32_t)(seed >> 32)), R);
         }
         if (k == 2) {
-            d->t[0] = now.t0;
-            d->t[1] = now.t1;
+            d->t2[0] = now.t0;
+            d->t2[1] = now.t1;
         }
         if (k == 3) {
             d->dec = a.a_dec * (double)now.O;
@@ -709,18 +720,20 @@ __device__ __forceinline__ void front_wave(const SegArgs& a, int lane, Handover<
             for (int j = 4; j < 8; ++j) cell[j] = ld(reinterpret_cast<const int32_t*>(rows + (d.rowoff[j] + lane_off)));
         }
     };
-    auto store_cells = [&](int x) {
+    int set = 0;                                     // the set of cells that the next request gets
+    auto store_cells = [&]() {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) comm->cells[x & 1][j][lane] = cell[j];
+        for (int j = 0; j < 4; ++j) comm->cells[set][j][lane] = cell[j];
         if (more4) {
 #pragma unroll
-            for (int j = 4; j < 8; ++j) comm->cells[x & 1][j][lane] = cell[j];
+            for (int j = 4; j < 8; ++j) comm->cells[set][j][lane] = cell[j];
         }
+        set = set == CELL_SETS - 1 ? 0 : set + 1;
     };
     load_cells(0);
-    store_cells(0);
+    store_cells();
     load_cells(1);
-    store_cells(1);
+    store_cells();
     meet(true);         // the first descriptors and cells are there
     meet(false);
     SectionClock<TIMED> clk;
@@ -736,8 +749,8 @@ __device__ __forceinline__ void front_wave(const SegArgs& a, int lane, Handover<
     };
     auto pass = [&](int r) {
         if (r >= N) return;
-        const bool sync = (__builtin_amdgcn_readfirstlane(comm->ring[(r + 1) & (DESC_RING - 1)].flags) & DESC_SYNC) != 0;
-        store_cells(r + 2);
+        const bool sync = (__builtin_amdgcn_readfirstlane(comm->ring[r & (DESC_RING - 1)].flags) & DESC_SYNC) != 0;
+        store_cells();
         if ((r & 3) == 0 && r > 0)
             for (int c = 0; c < (PROXY ? 2 : 1); ++c) comm->fetched[c][lane] = raw[c];
         clk.tick(0);                                                 // descriptors, cells
@@ -830,7 +843,7 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
             est_now = a.rtt_est[at];
         }
         comm->half[r & 3][lane] = 0.5 * rtt_now;
-        comm->rtt[r & 3][lane] = est_now;
+        if constexpr (PROXY) comm->rtt[r & 3][lane] = est_now;
     };
     if (!PROXY) comm->half[0][lane] = lane < R ? 0.5 * a.rtt[lane] : 0.0;
     // engine model: this lane's replica has its own rates and KV budget
@@ -859,10 +872,9 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
     } else {
         meet(true);      // (the first descriptors are there)
     }
-    auto desc = [&](int r) -> const SegDesc& { return comm->ring[r & (DESC_RING - 1)]; };
     double* const gone0 = &comm->gone[0][which * HALF];
-    auto gone = [&](int r) { return gone0 + (r & 3) * WAVE; };
-    for (int b = 0; b < 4; ++b)
+    auto gone = [&](int r) { return gone0 + (r & 1) * WAVE; };
+    for (int b = 0; b < 2; ++b)
         if (PACK == 1 || lane < HALF) gone(b)[lane] = 0.0;
     // requests that complete by t leave the load signal between the arrivals of r - 1 and r
     auto retire = [&](unsigned due, double t, int r) { Q.template retire<!PROXY>(due, t, rec, lane, gone(r)); };
@@ -872,8 +884,8 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
         t0 = readlane_f64(cur.t, 0);
         t1 = readlane_f64(cur.t, 1);
     } else {
-        t0 = desc(0).t[which];
-        t1 = desc(1).t[which];
+        t0 = (double)a.ts[0] * sc;
+        t1 = (double)a.ts[N > 1 ? 1 : 0] * sc;
     }
     if (PROXY) {
         probe(t0, 0);
@@ -899,16 +911,18 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
                 t2 = i2 < WAVE ? readlane_f64(cur.t, i2) : readlane_f64(nxt.t, i2 - WAVE);
                 dec = a.a_dec * (double)O;
             } else {
-                L = desc(r).L;
-                t2 = desc(r + 2).t[which];
-                if (ENGINE) O = desc(r).O;
-                else dec = desc(r).dec;
-                sync = (__builtin_amdgcn_readfirstlane(desc(r + 1).flags) & DESC_SYNC) != 0;
+                const SegDesc& d = comm->ring[r & (DESC_RING - 1)];
+                const int4 h = *reinterpret_cast<const int4*>(&d.L);
+                L = h.x;
+                t2 = d.t2[which];
+                if (ENGINE) O = d.O;
+                else dec = d.dec;
+                sync = (__builtin_amdgcn_readfirstlane(h.w) & DESC_SYNC) != 0;
             }
             clk.tick(0);
             meet(true);                                                  // X(r)
             clk.tick(1);                                                 // waiting at X
-            const int lane_best = comm->best[r & 1][which];
+            const int lane_best = __builtin_amdgcn_readfirstlane(comm->best[r & 1][which]);
             // (what completes by the arrival of the request after next, this request's own completion aside: read now, while
             // the choice is on its way)
             unsigned due = Q.due(t2, lane);
@@ -919,10 +933,9 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
             const int weight = COUNTS ? 1 : L;
             double ttft, e2e;
             if constexpr (ENGINE) {
-                const int sb = __builtin_amdgcn_readfirstlane(best);
-                Q.template serve_engine<PROXY>(r, sb, t0, half, readlane_f64(my_a_pf, sb) * prefill,
-                                               readlane_f64(my_a_dec, sb) * (double)O, weight, (unsigned)L + (unsigned)O,
-                                               readlane_f64(my_budget, sb), a.eng_slowdown, rec, lane, &ttft, &e2e, t2, due);
+                Q.template serve_engine<PROXY>(r, best, t0, half, readlane_f64(my_a_pf, best) * prefill,
+                                               readlane_f64(my_a_dec, best) * (double)O, weight, (unsigned)L + (unsigned)O,
+                                               readlane_f64(my_budget, best), a.eng_slowdown, rec, lane, &ttft, &e2e, t2, due);
             } else {
                 Q.template serve<PROXY>(r, best, t0, half, PROXY ? a.a_pf * prefill : prefill, dec, weight, rec, lane, &ttft, &e2e, t2, due);
             }
@@ -932,7 +945,7 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
             if (BLOCKS) {
                 o_route = lane == i ? best : o_route;
                 o_hit = lane == i ? (int)(ch->hit_end & 0xFFFFu) : o_hit;
-                if (PROXY && a.believed) o_believed = lane == i ? (int)comm->seen[r & 1][lane_best] : o_believed;
+                if constexpr (PROXY) o_believed = lane == i ? (int)comm->seen[r & 1][lane_best] : o_believed;
             }
             if (ONLINE) {
                 if (lane == 0) ring[ring_pos] = ttft;
@@ -979,7 +992,6 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
             }
             // The completions up to the arrival of the request after next (this request's among them) do not depend on
             // where the next request goes, whose own completion the deciding wavefront has ruled out, or will wait for.
-            if (BLOCKS) gone(r + 3)[lane] = 0.0;             // (else the book-keeping wavefront does)
             if (r + 2 < N) {
                 retire(due, t2, r + 2);
                 if (PROXY) probe(t2, r + 2);
@@ -1045,7 +1057,6 @@ __device__ __forceinline__ void book_wave(const SegArgs& a, int lane, Handover<P
     clk.start();
     for (int r = 0; r < N; ++r) {
         const SegDesc* const d = &comm->ring[r & (DESC_RING - 1)];
-        const bool sync = (__builtin_amdgcn_readfirstlane(comm->ring[(r + 1) & (DESC_RING - 1)].flags) & DESC_SYNC) != 0;
         const uint32_t of_seg = d->slot[rl & (SEG_CHUNK - 1)], of_tail = d->tail;
         const int n = d->n, s = __builtin_amdgcn_readfirstlane(d->s), flags = __builtin_amdgcn_readfirstlane(d->flags);
         clk.tick(2);                                                 // stores
@@ -1086,17 +1097,25 @@ __device__ __forceinline__ void book_wave(const SegArgs& a, int lane, Handover<P
                 }
             }
         }
-        comm->gone[(r + 3) & 3][lane] = 0.0;
         st(&log64[r], 0xFFFFFFFFull | ((unsigned long long)n << 48));      // next -1, own 0, n
         st(&log[is_best && tail_r >= 0 ? tail_r : N].next, r);
         st(&log[c.owner >= 0 ? c.owner : N].own, (uint16_t)(c.hit_end >> 16));
+        if (ballot(c.owner == OWN_LIST) != 0) {
+            // (several previous owners: rare)
+            const int count = c.owner == OWN_LIST ? (int)(c.hit_end >> 16) : 0;
+            for (int i = 0; ballot(i < count) != 0; ++i)
+                if (i < count) {
+                    const OwnChange x = comm->changes[r & 1][upper ? 1 : 0][i];
+                    st(&log[x.owner].own, (uint16_t)x.end);
+                }
+        }
         if (is_best && tail_r < 0) comm->first[lane] = r;
         tail_r = is_best ? r : tail_r;
         const int slot = r & (BATCH - 1);
         const bool mine = rl == slot;
         o_route = mine ? best : o_route;
         o_hit = mine ? (int)(c.hit_end & 0xFFFFu) : o_hit;
-        if (PROXY) o_seen = mine ? (int)comm->seen[r & 1][lane_best] : o_seen;
+        if constexpr (PROXY) o_seen = mine ? (int)comm->seen[r & 1][lane_best] : o_seen;
         if (slot == BATCH - 1 || r == N - 1) {
             const int x = r - slot + rl;
             if (rl <= slot) {
@@ -1106,7 +1125,7 @@ __device__ __forceinline__ void book_wave(const SegArgs& a, int lane, Handover<P
                 if (PROXY && a.believed) a.believed[o] = (uint16_t)o_seen;
             }
         }
-        if (sync) meet(false);                                       // Y(r)
+        if (flags & DESC_SYNC) meet(false);                          // Y(r)
     }
     if (TIMED && a.sections && lane == 0) {
         a.sections[(p0 * 3 + 2) * SECTIONS + 2] = clk.acc[2];
@@ -1125,16 +1144,12 @@ __device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Handover
     const bool upper = PACK == 2 && lane >= HALF;
     const int rl = PACK == 2 ? lane & (HALF - 1) : lane;
     const size_t p0 = (size_t)blockIdx.x * PACK, p = p0 + (upper ? 1 : 0);
-    const bool bounded = a.C > 0;
-    // (kept in a vector register: under scalar-register pressure the compiler would otherwise re-read it from the
-    // kernel arguments inside the request loop, a scalar-memory wait on the chain)
-    int cap = (int)a.C;
-    asm volatile("" : "+v"(cap));
     const bool in = rl < R;
     double w_rtt = a.params[3 * p + 0], w_prefill = a.params[3 * p + 1], w_queue = a.params[3 * p + 2];
     const double my_rtt = !PROXY && in ? a.rtt[rl] : 0.0;        // (proxy variants: comes from the queue wavefront)
-    double rtt_term = w_rtt * my_rtt;                            // first product of Eq. 3
-    double q = 0.0;           // load signal of replica = lane (an integer below 2^53, exact in fp64)
+    // first product of Eq. 3 (lanes without a replica: a score above any)
+    double rtt_term = in ? w_rtt * my_rtt : INFINITY;
+    double q = COUNTS && !in ? INFINITY : 0.0;       // load signal of replica = lane (an integer below 2^53, exact in fp64)
     // Proxy variants (Sec. 7: the proxy does not see replica-side eviction): the proxy keeps an index of its own
     // of what it dispatched to each replica, an LRU like the replica's cache but at least as large (or unbounded).
     // It sees the same touches, so it is the same rows read against a second eviction cursor (c2), which lags
@@ -1147,7 +1162,9 @@ __device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Handover
     EvictCursor c1, c2;                       // the cache's cursor, the index's cursor
     c1.ring = &comm->look[0][lane];
     c2.ring = &comm->look[1][lane];
-    for (int k = 0; k <= LOOK_RING; ++k) {
+    c1.over = a.C > 0 ? -(int)a.C : INT32_MIN;         // (unbounded)
+    c2.over = -index_cap;
+    for (int k = 0; k < LOOK_RING; ++k) {
         c1.ring[k * WAVE] = ~0ull;
         if (PROXY) c2.ring[k * WAVE] = ~0ull;
     }
@@ -1167,47 +1184,47 @@ __device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Handover
     c2.fetched = &comm->fetched[PROXY ? 1 : 0][lane];
 
     // the request in hand: row cells of its first eight segments as seen by this lane (= replica), where they end, tokens,
-    // blocks, flags; read (LDS) before the meeting that decides the one before, when LDS is waited for anyway
+    // blocks, flags; read (LDS) while the minimum of the one before is being found
     int32_t cell[SEG_CHUNK];
     int end[SEG_CHUNK];
-    int L = 0, n = 0, flags = 0;
-    auto take = [&](int r) {
+    int L = 0, n = 0, word = 0, set = 0;
+    auto take = [&](int r, int set) {
         const SegDesc& d = comm->ring[r & (DESC_RING - 1)];
         const int4 h = *reinterpret_cast<const int4*>(&d.L);
 #pragma unroll
-        for (int k = 0; k < SEG_CHUNK; ++k) cell[k] = comm->cells[r & 1][k][lane];
+        for (int k = 0; k < SEG_CHUNK; ++k) cell[k] = comm->cells[set][k][lane];
         const int4 lo = reinterpret_cast<const int4*>(d.end)[0], hi = reinterpret_cast<const int4*>(d.end)[1];
         end[0] = lo.x, end[1] = lo.y, end[2] = lo.z, end[3] = lo.w;
         end[4] = hi.x, end[5] = hi.y, end[6] = hi.z, end[7] = hi.w;
         L = h.x;
         n = h.y;
-        flags = __builtin_amdgcn_readfirstlane(h.w);
+        word = h.w;       // (the same in every lane; made scalar behind the meeting, where it has arrived)
     };
 
     SectionClock<TIMED> clk;
     int n_walks = 0;          // statistics: ownership walks
     meet(true);                               // the first descriptors and cells are there
-    take(0);
+    take(0, 0);
     meet(true);                               // the queue wavefronts have set themselves up
     clk.start();
     for (int r = 0; r < N; ++r) {
         const SegDesc* const dr = &comm->ring[r & (DESC_RING - 1)];
-        const int n_now = n;      // (the next request's numbers are taken before this one is done with)
         const int target = DICTATED ? dr->target : 0;
-        const double left = DICTATED ? 0.0 : comm->gone[r & 3][lane];
+        const int flags = __builtin_amdgcn_readfirstlane(word);
+        const double left = DICTATED ? 0.0 : comm->gone[r & 1][lane];
+        if (!DICTATED) comm->gone[r & 1][lane] = 0.0;
         const double rtt_now = PROXY ? comm->rtt[r & 3][PROXY ? lane : 0] : my_rtt;
 
         // ---- the rows were loaded before the stores of the three requests before were sure to be there: the leading
         // segments that the paths share get the cells that those requests wrote on their replicas
+        auto patch = [&](int32_t& c, int k, int f) {
+            c = of_mask(went3) && k < ((f >> 20) & 15) ? r - 3 : c;
+            c = of_mask(went2) && k < ((f >> 12) & 15) ? r - 2 : c;
+            c = of_mask(went1) && k < ((f >> 8) & 15) ? r - 1 : c;
+        };
         if (flags & DESC_SHARED) {
-            const int common1 = (flags >> 8) & 15, common2 = (flags >> 12) & 15, common3 = (flags >> 20) & 15;
-            const bool is1 = of_mask(went1), is2 = of_mask(went2), is3 = of_mask(went3);
 #pragma unroll
-            for (int k = 0; k < SEG_CHUNK; ++k) {
-                cell[k] = is3 && k < common3 ? r - 3 : cell[k];
-                cell[k] = is2 && k < common2 ? r - 2 : cell[k];
-                cell[k] = is1 && k < common1 ? r - 1 : cell[k];
-            }
+            for (int k = 0; k < SEG_CHUNK; ++k) patch(cell[k], k, flags);
         }
 
         // ---- prefix match: lane = replica.  A request that touches a segment touches all its ancestors,
@@ -1259,7 +1276,7 @@ __device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Handover
         const unsigned long long by_cursor = PROXY ? ballot(below_cursor2 > e_gt2) : ballot(below_cursor > e_gt);
         const unsigned long long one_owner = (by_cursor & ballot((PROXY ? e_gt2 : e_gt) == 0)) |
                                              (~by_cursor & ballot((PROXY ? own_gt2 : own_gt) == cell[0]));
-        bool deep = false;          // the match went past the preloaded segments
+        unsigned long long in_reach = ~0ull;     // 0: the match went past the preloaded segments
         if (flags & DESC_DEEP) {
             // more than eight segments (rare; memory is up to date, Y(r - 1)): the rest of the path is read from the trace,
             // eight references at a time, as long as some replica's prefix is still open
@@ -1269,7 +1286,7 @@ __device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Handover
             bool open = my_m == pos;
             bool open_seen = PROXY && my_seen == pos;
             if (ballot((PROXY ? open_seen : open) && in) != 0) {
-                deep = true;
+                in_reach = 0;
                 for (int c0 = 8; c0 < s; c0 += 8) {
                     int32_t more[8];
                     int send[8];
@@ -1337,11 +1354,11 @@ __device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Handover
         if (!ENGINE && !PROXY) my_prefill = a.a_pf * my_prefill;
         if (SCORED) {
             const double pf = PROXY || ENGINE ? a.a_pf * (double)my_u_seen : my_prefill;
-            const double s_rtt = PROXY ? w_rtt * rtt_now : rtt_term;
+            const double s_rtt = PROXY ? (in ? w_rtt * rtt_now : INFINITY) : rtt_term;
             const double s_pf = w_prefill * pf;
             const double rtt_and_prefill = s_rtt + s_pf;
             const double qd = a.a_pf * q;
-            const double s_q = w_queue * qd;
+            const double s_q = w_queue * qd + 0.0;       // (not -0.0: nor is the score then)
             my_score = rtt_and_prefill + s_q;
         } else if (COUNTS) {
             my_score = q;                       // requests in flight
@@ -1356,106 +1373,106 @@ __device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Handover
         // replica and previous owners are mostly young.
         const int held = PROXY ? my_seen : my_m;
         const unsigned long long holders = ballot(held > 0);
-        unsigned long long plain = deep ? 0 : one_owner & ~(ballot(c1.ring_cnt > 0) & ballot(cell[0] <= c1.ring_hi));
+        unsigned long long plain = one_owner & in_reach & ~(ballot(c1.ring_cnt > 0) & ballot(cell[0] <= c1.ring_hi));
         if (PROXY) plain &= ~(ballot(c2.ring_cnt > 0) & ballot(cell[0] <= c2.ring_hi));
         const unsigned long long walkers = holders & ~plain;
         const int owner = of_mask(holders & plain) ? cell[0] : -2;
         comm->choice[r & 1][lane] = Choice{my_prefill, owner, (unsigned)my_m | ((unsigned)k_end << 16)};
-        if (PROXY) comm->seen[r & 1][lane] = (uint16_t)(own_index ? my_seen : my_m);
+        if constexpr (PROXY) comm->seen[r & 1][lane] = (uint16_t)(own_index ? my_seen : my_m);
 
-        const unsigned long long bests = argmin_mask<PACK>(my_score, in, upper);
+        // (what is still needed of this request's numbers, and the next one's: its reads are under way during the minimum)
+        const int added = n - my_m, also_added = n - my_seen, set_now = set;
+        const double tokens = (double)L;
+        set = set == CELL_SETS - 1 ? 0 : set + 1;
+        take(r + 1, set);
+
+        const unsigned long long bests = argmin_mask<PACK>(my_score, upper);
         if (PACK == 1) comm->best[r & 1][0] = __builtin_ctzll(bests);
         else comm->best[r & 1][upper ? 1 : 0] = upper ? HALF + __builtin_ctz((unsigned)(bests >> 32)) : __builtin_ctz((unsigned)bests);
         const bool is_best = of_mask(bests);
         clk.tick(3);                                                 // score, minimum, announcement
         // (the announcement is on its way through LDS; what follows needs nobody else and gives it the time to arrive)
-        if (COUNTS) q += is_best ? 1.0 : 0.0;
-        else if (!DICTATED) q += is_best ? (double)L : 0.0;
         latest.r = r;
         latest.owner = is_best ? owner : -2;
         latest.end = k_end;
+        latest.count = 0;
         c1.disowned(latest.owner, k_end);
         if (PROXY) c2.disowned(latest.owner, k_end);
-        const bool walks = (walkers & bests) != 0;
-        auto disown = [&](int of, int end) {           // chosen lane: `of`'s owned suffix now starts at end
-            st(&log[of].own, (uint16_t)end);
-            c1.disowned_anywhere(of, end);
-            if (PROXY) c2.disowned_anywhere(of, end);
-        };
-        // the ownership walk: segments [j0, j1) of the path, then what is left of it
-        bool walking = false;
-        int run_owner = -1, run_end = 0, vpos = 0;
-        auto walk = [&](int j0, int j1, auto segment) {
+        if (__builtin_expect((walkers & bests) != 0, 0)) {
+            // several previous owners, or a prefix longer than the preloaded rows, or an owner in a look-ahead ring
+            ++n_walks;
+            bool walking = of_mask(walkers & bests);
             const int cb_r = PROXY ? c2.cur_r : c1.cur_r, cb_k = PROXY ? c2.cur_k : c1.cur_k;
-            for (int j = j0; j < j1 && ballot(walking) != 0; ++j) {
-                int32_t at;
-                int to;
-                segment(j, walking, at, to);
+            int run_owner = -1, run_end = 0, vpos = 0;
+            // takes one more segment of the path; changed(owner, end) is told of every run that is complete
+            auto walk = [&](int32_t at, int to, auto changed) {
                 const int cnt = walking ? cached_in(at, vpos, to, cb_r, cb_k) : 0;
                 if (cnt > 0) {
-                    if (at != run_owner) {
-                        if (run_owner >= 0) disown(run_owner, run_end);
-                        run_owner = at;
-                    }
+                    if (at != run_owner && run_owner >= 0) changed(run_owner, run_end);
+                    run_owner = at;
                     run_end = to;
                 }
                 walking = walking && cnt == to - vpos;
                 vpos = to;
-            }
-        };
-        int E = 0, E2 = 0;
-        auto evict_first = [&]() {
-            E = c1.evict_first(is_best && bounded, n_now - my_m, cap);
-            // the proxy's index evicts under its own capacity: its cursor walks the same log
-            if (PROXY && index_cap > 0) E2 = c2.evict_first(is_best, n_now - my_seen, index_cap);
-        };
-        if (walks) {
-            ++n_walks;
-            walking = of_mask(walkers & bests);
-            if (deep) {
-                // a prefix longer than the preloaded rows: from memory, which nobody writes before X(r) (Y(r - 1))
+            };
+            if (in_reach == 0) {
+                // from memory, which nobody else writes before X(r) (Y(r - 1))
+                auto changed = [&](int of, int to) {
+                    st(&log[of].own, (uint16_t)to);
+                    c1.disowned_anywhere(of, to);
+                    if (PROXY) c2.disowned_anywhere(of, to);
+                };
                 const int64_t j0 = dr->j0;
-                walk(0, __builtin_amdgcn_readfirstlane(dr->s), [&](int j, bool on, int32_t& at, int& to) {
+                const int s = __builtin_amdgcn_readfirstlane(dr->s);
+                for (int j = 0; j < s && ballot(walking) != 0; ++j) {
                     const SegRef sr = a.seg[j0 + j];
-                    to = sr.end & SEG_END_MASK;
-                    at = on && !(sr.end & SEG_FRESH) ? ld(cell_at((uint32_t)sr.id * row_bytes)) : NEVER_CACHED;
-                });
-                if (run_owner >= 0) disown(run_owner, run_end);
-            }
-            int32_t old[SEG_CHUNK];
-#pragma unroll
-            for (int k = 0; k < SEG_CHUNK; ++k) old[k] = cell[k];
-            const bool more4 = (flags & DESC_MORE4) != 0;
-            take(r + 1);
-            meet(true);                                              // X(r)
-            if (!deep) {
-                // several previous owners: from the preloaded rows (after X(r): the book-keeping wavefront has then moved
-                // the previous request's owner, which may be one of these), through LDS (the announcement before the last
-                // is done with): a loop over registers would keep all of them in memory
-                int32_t* const by_lane = reinterpret_cast<int32_t*>(&comm->choice[(r + 1) & 1][0]) + lane;
-                for (int h = 0; h < (more4 ? 2 : 1); ++h) {
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) by_lane[k * WAVE] = h == 0 ? old[k] : old[4 + k];
-                    walk(4 * h, 4 * h + 4, [&](int j, bool, int32_t& at, int& to) {
-                        at = by_lane[(j & 3) * WAVE];
-                        to = dr->end[j];
-                    });
+                    const int32_t at = walking && !(sr.end & SEG_FRESH) ? ld(cell_at((uint32_t)sr.id * row_bytes)) : NEVER_CACHED;
+                    walk(at, sr.end & SEG_END_MASK, changed);
                 }
-                if (run_owner >= 0) disown(run_owner, run_end);
+                if (run_owner >= 0) changed(run_owner, run_end);
+            } else {
+                // from the preloaded rows.  The book-keeping wavefront stores the changes: it may still be at work on the
+                // previous request's, which may concern one of these owners.
+                OwnChange* const list = comm->changes[r & 1][upper ? 1 : 0];
+                int count = 0;
+                auto changed = [&](int of, int to) { list[count++] = OwnChange{of, to}; };
+                const int most = flags & DESC_MORE4 ? SEG_CHUNK : 4;
+                for (int k = 0; k < most && ballot(walking) != 0; ++k) {
+                    int32_t at = comm->cells[set_now][k][lane];
+                    patch(at, k, flags);
+                    walk(at, dr->end[k], changed);
+                }
+                if (run_owner >= 0) changed(run_owner, run_end);
+                latest.count = count;
+                latest.list = list;
+                if (count > 0) {
+                    Choice* const mine = &comm->choice[r & 1][lane];
+                    mine->owner = OWN_LIST;
+                    mine->hit_end = (unsigned)my_m | ((unsigned)count << 16);
+                }
+                for (int i = 0; ballot(i < count) != 0; ++i)
+                    if (i < count) {
+                        const OwnChange x = list[i];
+                        c1.disowned_anywhere(x.owner, x.end);
+                        if (PROXY) c2.disowned_anywhere(x.owner, x.end);
+                    }
             }
-            evict_first();
-        } else {
-            evict_first();
-            take(r + 1);
-            clk.tick(5);                                             // ownership, cursor, the next request
-            meet(true);                                              // X(r)
         }
-        clk.tick(0);                                                 // waiting at X
-        if (ballot(E > 0) != 0) c1.advance(E, log64, spare, latest, comm->first[lane]);
-        if (PROXY && ballot(E2 > 0) != 0) c2.advance(E2, log64, spare, latest, comm->first[lane]);
+        const int E = c1.evict_first(is_best ? added : 0);
+        // the proxy's index evicts under its own capacity: its cursor walks the same log
+        const int E2 = PROXY && index_cap > 0 ? c2.evict_first(is_best ? also_added : 0) : 0;
+        unsigned long long more = ballot(E > 0), more2 = PROXY ? ballot(E2 > 0) : 0;
+        if (COUNTS) q += is_best ? 1.0 : 0.0;
+        else if (!DICTATED) q += is_best ? tokens : 0.0;
+        asm volatile("" : "+s"(more), "+v"(q));       // (before the meeting, not after it)
         went3 = went2;
         went2 = went1;
         went1 = bests;
+        clk.tick(5);                                                 // ownership, cursor, the next request
+        meet(true);                                                  // X(r)
+        clk.tick(0);                                                 // waiting at X
+        if (more != 0) c1.advance(E, log64, spare, latest, comm->first[lane]);
+        if (PROXY && more2 != 0) c2.advance(E2, log64, spare, latest, comm->first[lane]);
         clk.tick(6);                                                 // eviction past the cursor's record
         if (flags & DESC_SYNC) {
             meet(false);                                             // Y(r)
@@ -1463,7 +1480,7 @@ __device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Handover
                 w_rtt = comm->w[upper ? 1 : 0][0];
                 w_prefill = comm->w[upper ? 1 : 0][1];
                 w_queue = comm->w[upper ? 1 : 0][2];
-                rtt_term = w_rtt * my_rtt;
+                rtt_term = in ? w_rtt * my_rtt : INFINITY;
             }
         }
         clk.tick(4);                                                 // waiting at Y
@@ -1485,7 +1502,7 @@ template <int PACK>
 constexpr int seg_threads() { return (3 + PACK) * WAVE; }
 
 template <int MODE, bool ENGINE, bool PROXY, int PACK = 1, bool TIMED = false>
-__global__ void __launch_bounds__(seg_threads<PACK>(), PACK == 2 ? 5 : 4) replay_segments_kernel(SegArgs a) {
+__global__ void __launch_bounds__(seg_threads<PACK>(), PACK == 2 ? 6 : 4) replay_segments_kernel(SegArgs a) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     __shared__ __align__(16) Handover<PROXY> comm;
     const int lane = threadIdx.x & (WAVE - 1);
