@@ -364,13 +364,11 @@ int evaluate(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* op
     if (!ttft && outputs->p95_ttft_ms) ttft = reinterpret_cast<double*>(ws + pl.off_ttft);
     double* e2e = outputs->e2e_ms;
     if (!e2e && outputs->p95_e2e_ms) e2e = reinterpret_cast<double*>(ws + pl.off_e2e);
-    rc = launch_replay(t, pl, d_rtt, d_params, d_scale, route, outputs->hit_blocks, ttft, e2e, workspace, hip_stream,
-                       online ? &ol : nullptr, policy != 0 ? &pol : nullptr, engine ? &el : nullptr, proxy ? &xl : nullptr,
-                       sections);
-    if (rc) return rc;
-    if (outputs->p95_ttft_ms && (rc = launch_p95(ttft, pl.N, P, outputs->p95_ttft_ms, hip_stream))) return rc;
-    if (outputs->p95_e2e_ms && (rc = launch_p95(e2e, pl.N, P, outputs->p95_e2e_ms, hip_stream))) return rc;
-    return GORGO_OK;
+    pl.p95_ttft = outputs->p95_ttft_ms;
+    pl.p95_e2e = outputs->p95_e2e_ms;
+    return launch_replay(t, pl, d_rtt, d_params, d_scale, route, outputs->hit_blocks, ttft, e2e, workspace, hip_stream,
+                         online ? &ol : nullptr, policy != 0 ? &pol : nullptr, engine ? &el : nullptr, proxy ? &xl : nullptr,
+                         sections);
 }
 
 }  // namespace

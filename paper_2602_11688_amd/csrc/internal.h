@@ -79,6 +79,8 @@ struct Plan {
     // workspace carve-up (byte offsets from the workspace base)
     size_t off_tables = 0, off_spare = 0, off_rec = 0, off_route = 0, off_ttft = 0, off_e2e = 0, off_small = 0;
     size_t total = 0;
+    // [P] nearest-rank percentiles to be computed (device pointers), or null
+    double *p95_ttft = nullptr, *p95_e2e = nullptr;
 };
 
 // Online tuner of one launch (device pointers; see gorgo_online in gorgo.h).
@@ -128,7 +130,6 @@ int launch_replay(const gorgo_trace* t, const Plan& pl, const double* d_rtt, con
                   void* workspace, void* stream, const OnlineLaunch* online = nullptr,
                   const PolicyLaunch* policy = nullptr, const EngineLaunch* engine = nullptr,
                   const ProxyLaunch* proxy = nullptr, unsigned long long* sections = nullptr);
-int launch_p95(const double* x, int64_t N, int32_t P, double* out, void* stream);
 int last_eval_kernel_ms(double* fill_ms, double* replay_ms, double* select_ms);
 int upload_trace(const gorgo_trace* t);
 bool trace_is_resident(const gorgo_trace* t);          // on the current device

@@ -27,118 +27,183 @@ __global__ void __launch_bounds__(256) fill_last_rows(int32_t* x, int32_t P, int
     if (i < (size_t)P * R) x[((i / R) * (size_t)rows + (size_t)(rows - 2)) * R + i % R] = v;
 }
 
-// ---- exact nearest-rank percentile: k-th smallest of x[p][0..N) by most-significant-digit radix selection
-// on the order-preserving integer image of the doubles.  One 256-thread workgroup per row.  Every digit is a pass
-// over the row; as soon as the bin that holds the k-th element has few enough elements they are gathered into LDS
-// in one more pass and the element is picked there by counting (latencies of a replay differ in the first two or
-// three digits: three passes instead of six).
-constexpr int SEL_THREADS = 256;
-constexpr int SEL_BITS = 11;
-constexpr int SEL_BINS = 1 << SEL_BITS;
-constexpr int SEL_GATHER = 2048;      // candidates that are finished in LDS
+// ---- exact nearest-rank percentile: the k-th smallest of x[p][0..N) on the order-preserving integer image (key) of the
+// doubles.  One workgroup per row, and per array where both percentiles are wanted (blockIdx.y).
+// A pass counts the keys of the current interval [lo, hi], which holds the k-th, in 2,046 equal bins above a point a, one
+// for what is below a and one for what is above the last; the bin with the k-th is the next interval.  The first pass
+// over a long row takes a and the bins' width from a sample of 1,024 elements: the latencies of a replay spread over a few
+// powers of two, so bins of fixed digits would send nearly all of them to a handful of LDS words, and the atomics on one
+// word run one after the other.  Intervals with few enough keys are gathered into LDS and narrowed there, the last 64 by
+// counting.  A row is so read twice and sampled once.
+constexpr int SEL_THREADS = 1024;
+constexpr int SEL_BINS = 2 * SEL_THREADS;
+constexpr int SEL_GATHER = 4096;      // keys that are narrowed further in LDS
+constexpr int SEL_FEW = WAVE;         // keys that are finished by counting
+constexpr int SEL_LOADS = 8;          // loads in flight per thread
 
 __device__ __forceinline__ uint64_t ordered_bits(double x) {
     uint64_t b = (uint64_t)__double_as_longlong(x);
     return (b >> 63) ? ~b : (b | 0x8000000000000000ull);
 }
 
-__global__ void __launch_bounds__(SEL_THREADS) select_kth(const double* x, int64_t N, int64_t kth /*1-based*/,
-                                                          double* out) {
+__global__ void __launch_bounds__(SEL_THREADS) select_kth(const double* x0, const double* x1, int64_t N, int64_t kth /*1-based*/,
+                                                          double* out0, double* out1) {
     __shared__ uint32_t hist[SEL_BINS];
-    __shared__ uint32_t part[SEL_THREADS];
     __shared__ uint64_t cand[SEL_GATHER];
-    __shared__ uint64_t s_prefix;
-    __shared__ int64_t s_k;
-    __shared__ uint32_t s_in_bin, n_cand;
-    const int tid = threadIdx.x;
-    const double* row = x + (size_t)blockIdx.x * N;
+    __shared__ uint64_t few[SEL_FEW];
+    __shared__ unsigned long long s_lo, s_hi;
+    __shared__ uint32_t part[SEL_THREADS / WAVE];
+    __shared__ uint32_t s_k, s_m, s_n;
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
+    const double* const row = (blockIdx.y ? x1 : x0) + (size_t)blockIdx.x * N;
+    double* const out = (blockIdx.y ? out1 : out0) + blockIdx.x;
     if (N <= 0) {
-        if (tid == 0) out[blockIdx.x] = 0.0;
+        if (tid == 0) *out = 0.0;
         return;
     }
+    // f(key) for every element of the row
+    auto each = [&](auto f) {
+        for (int64_t i0 = tid; i0 < N; i0 += (int64_t)SEL_LOADS * SEL_THREADS) {
+            uint64_t v[SEL_LOADS];
+#pragma unroll
+            for (int u = 0; u < SEL_LOADS; ++u) {
+                const int64_t i = i0 + (int64_t)u * SEL_THREADS;
+                v[u] = ordered_bits(row[i < N ? i : N - 1]);
+            }
+#pragma unroll
+            for (int u = 0; u < SEL_LOADS; ++u)
+                if (i0 + (int64_t)u * SEL_THREADS < N) f(v[u]);
+        }
+    };
     if (tid == 0) {
-        s_prefix = 0;
-        s_k = kth;
+        s_lo = ~0ull;
+        s_hi = 0;
+        s_n = 0;
     }
-    int shift = 64;
-    uint64_t prefix_mask = 0;
-    while (shift > 0) {
-        const int bits = shift >= SEL_BITS ? SEL_BITS : shift;
-        shift -= bits;
-        for (int b = tid; b < SEL_BINS; b += SEL_THREADS) hist[b] = 0;
-        __syncthreads();
-        const uint64_t prefix = s_prefix;
-        const int64_t k = s_k;
-        // (four loads in flight per thread)
-        int64_t i = tid;
-        for (; i + 3 * SEL_THREADS < N; i += 4 * SEL_THREADS) {
-            uint64_t v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = ordered_bits(row[i + u * SEL_THREADS]);
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if ((v[u] & prefix_mask) == prefix) atomicAdd(&hist[(v[u] >> shift) & ((1u << bits) - 1)], 1u);
-        }
-        for (; i < N; i += SEL_THREADS) {
+    hist[2 * tid] = hist[2 * tid + 1] = 0;
+    __syncthreads();
+    // the whole of a short row in LDS, a sample of a long one; either's smallest and largest key
+    bool in_lds = N <= SEL_GATHER;
+    uint32_t n = in_lds ? (uint32_t)N : 0;           // keys in LDS
+    unsigned long long least = ~0ull, most = 0;
+    if (in_lds) {
+        for (int i = tid; i < (int)N; i += SEL_THREADS) {
             const uint64_t v = ordered_bits(row[i]);
-            if ((v & prefix_mask) == prefix) atomicAdd(&hist[(v >> shift) & ((1u << bits) - 1)], 1u);
+            cand[i] = v;
+            least = v < least ? v : least;
+            most = v > most ? v : most;
         }
-        __syncthreads();
-        // locate the bin that holds the k-th element: per-thread partial sums, then a short serial scan
-        constexpr int PER = SEL_BINS / SEL_THREADS;
-        uint32_t sum = 0;
-        for (int j = 0; j < PER; ++j) sum += hist[tid * PER + j];
-        part[tid] = sum;
-        __syncthreads();
-        if (tid == 0) {
-            int64_t acc = 0;
-            int g = 0;
-            while (g < SEL_THREADS - 1 && acc + part[g] < k) acc += part[g++];
-            int b = g * PER;
-            while (b < SEL_BINS - 1 && acc + hist[b] < k) acc += hist[b++];
-            s_prefix = prefix | ((uint64_t)b << shift);
-            s_k = k - acc;
-            s_in_bin = hist[b];
-            n_cand = 0;
-        }
-        prefix_mask |= ((bits == 64 ? ~0ull : ((1ull << bits) - 1)) << shift);
-        __syncthreads();
-        if (shift > 0 && s_in_bin <= (uint32_t)SEL_GATHER) {
-            // few enough left: gather them, and take the one with fewer than k below it and at least k not above it
-            const uint64_t want = s_prefix;
-            int64_t i = tid;
-            for (; i + 3 * SEL_THREADS < N; i += 4 * SEL_THREADS) {
-                uint64_t v[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) v[u] = ordered_bits(row[i + u * SEL_THREADS]);
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if ((v[u] & prefix_mask) == want) cand[atomicAdd(&n_cand, 1u)] = v[u];
-            }
-            for (; i < N; i += SEL_THREADS) {
-                const uint64_t v = ordered_bits(row[i]);
-                if ((v & prefix_mask) == want) cand[atomicAdd(&n_cand, 1u)] = v;
-            }
-            __syncthreads();
-            const int n = (int)n_cand;
-            const int64_t kk = s_k;
-            for (int c = tid; c < n; c += SEL_THREADS) {
-                const uint64_t mine = cand[c];
-                int64_t less = 0, leq = 0;
-                for (int j = 0; j < n; ++j) {
-                    less += cand[j] < mine ? 1 : 0;
-                    leq += cand[j] <= mine ? 1 : 0;
-                }
-                if (less < kk && kk <= leq) s_prefix = mine;      // (every such element has the same value)
-            }
-            __syncthreads();
+    } else {
+        least = most = ordered_bits(row[(int64_t)tid * N / SEL_THREADS]);
+    }
+    for (int d = 1; d < WAVE; d *= 2) {
+        const unsigned long long a = __shfl_xor(least, d), b = __shfl_xor(most, d);
+        least = a < least ? a : least;
+        most = b > most ? b : most;
+    }
+    if (lane == 0) {
+        atomicMin(&s_lo, least);
+        atomicMax(&s_hi, most);
+    }
+    __syncthreads();
+    unsigned long long lo = s_lo, hi = s_hi;         // the interval; where the bins start and their width (log2)
+    unsigned long long a = lo;
+    auto width = [](unsigned long long range) {      // the least with range >> width <= SEL_BINS - 2
+        int s = range < SEL_BINS - 1 ? 0 : 64 - __clzll(range) - 11;
+        return (range >> s) > SEL_BINS - 2 ? s + 1 : s;
+    };
+    int shift = width(hi - lo);
+    if (!in_lds) {
+        lo = 0;
+        hi = ~0ull;
+    }
+    uint32_t m = (uint32_t)N;                        // keys in the interval
+    int64_t k = kth;
+    unsigned long long answer = lo;
+    for (;;) {
+        if (lo == hi) {
+            answer = lo;
             break;
         }
+        if (in_lds && m <= (uint32_t)SEL_FEW) {
+            // the one with fewer than k below it and at least k not above it
+            for (uint32_t c = tid; c < n; c += SEL_THREADS) {
+                const uint64_t v = cand[c];
+                if (v >= lo && v <= hi) few[atomicAdd(&s_n, 1u)] = v;
+            }
+            __syncthreads();
+            if (tid < (int)m) {
+                const uint64_t mine = few[tid];
+                int64_t less = 0, leq = 0;
+                for (uint32_t j = 0; j < m; ++j) {
+                    less += few[j] < mine ? 1 : 0;
+                    leq += few[j] <= mine ? 1 : 0;
+                }
+                if (less < k && k <= leq) s_lo = mine;               // (every such key has the same value)
+            }
+            __syncthreads();
+            answer = s_lo;
+            break;
+        }
+        if (!in_lds && m <= (uint32_t)SEL_GATHER) {
+            each([&](uint64_t v) {
+                if (v >= lo && v <= hi) cand[atomicAdd(&s_n, 1u)] = v;
+            });
+            __syncthreads();
+            n = m;
+            in_lds = true;
+            if (tid == 0) s_n = 0;
+            __syncthreads();
+            continue;
+        }
+        auto count = [&](uint64_t v) {
+            if (v < lo || v > hi) return;
+            const unsigned long long b = v < a ? 0 : 1 + ((v - a) >> shift);
+            atomicAdd(&hist[b < SEL_BINS - 1 ? b : SEL_BINS - 1], 1u);
+        };
+        if (in_lds) {
+            for (uint32_t c = tid; c < n; c += SEL_THREADS) count(cand[c]);
+        } else {
+            each(count);
+        }
+        __syncthreads();
+        // the bin that holds the k-th: sums up to each bin (two per thread), within the wavefront and over wavefronts
+        const uint32_t h0 = hist[2 * tid], h1 = hist[2 * tid + 1];
+        hist[2 * tid] = hist[2 * tid + 1] = 0;
+        uint32_t incl = h0 + h1;
+        for (int d = 1; d < WAVE; d *= 2) {
+            const uint32_t below = __shfl_up(incl, d);
+            incl += lane >= d ? below : 0;
+        }
+        if (lane == WAVE - 1) part[wave] = incl;
+        __syncthreads();
+        for (int w = 0; w < wave; ++w) incl += part[w];
+        const int64_t before = (int64_t)incl - h0 - h1;
+        if (before < k && k <= (int64_t)incl) {
+            const bool first = k <= before + h0;
+            const unsigned long long b = 2 * tid + (first ? 0 : 1);
+            s_k = (uint32_t)(k - before - (first ? 0 : h0));
+            s_m = first ? h0 : h1;
+            if (b == 0) {
+                s_lo = lo;
+                s_hi = a - 1;
+            } else {
+                const unsigned long long from = a + ((b - 1) << shift), span = (1ull << shift) - 1;
+                s_lo = from;
+                s_hi = b == SEL_BINS - 1 || hi - from < span ? hi : from + span;
+            }
+        }
+        __syncthreads();
+        lo = a = s_lo;
+        hi = s_hi;
+        k = s_k;
+        m = s_m;
+        shift = width(hi - lo);
+        __syncthreads();
     }
     if (tid == 0) {
-        uint64_t v = s_prefix;
-        uint64_t b = (v >> 63) ? (v & 0x7FFFFFFFFFFFFFFFull) : ~v;
-        out[blockIdx.x] = __longlong_as_double((long long)b);
+        const uint64_t b = (answer >> 63) ? (answer & 0x7FFFFFFFFFFFFFFFull) : ~answer;
+        *out = __longlong_as_double((long long)b);
     }
 }
 
@@ -489,6 +554,13 @@ int launch_replay(const gorgo_trace* t, const Plan& pl, const double* d_rtt, con
         }
     }
     mark(2, s);
+    if (pl.p95_ttft || pl.p95_e2e) {
+        // (one launch for both percentiles)
+        const bool both = pl.p95_ttft && pl.p95_e2e;
+        hipLaunchKernelGGL(select_kth, dim3((unsigned)pl.P, both ? 2 : 1), dim3(SEL_THREADS), 0, s, pl.p95_ttft ? ttft : e2e,
+                           e2e, pl.N, (95 * pl.N + 99) / 100, pl.p95_ttft ? pl.p95_ttft : pl.p95_e2e, pl.p95_e2e);
+        if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "launch select_kth");
+    }
     mark(3, s);
     g_marks.valid = g_marks_on && g_marks.device >= 0;
     return GORGO_OK;
@@ -507,15 +579,6 @@ int last_eval_kernel_ms(double* fill_ms, double* replay_ms, double* select_ms) {
     if (replay_ms) *replay_ms = b;
     if (select_ms) *select_ms = c;
     return GORGO_OK;
-}
-
-int launch_p95(const double* x, int64_t N, int32_t P, double* out, void* stream) {
-    const int64_t kth = (95 * N + 99) / 100;
-    hipLaunchKernelGGL(select_kth, dim3((unsigned)P), dim3(SEL_THREADS), 0, static_cast<hipStream_t>(stream), x, N,
-                       kth, out);
-    hipError_t e = hipGetLastError();
-    mark(3, static_cast<hipStream_t>(stream));
-    return e == hipSuccess ? GORGO_OK : hip_fail(e, "launch select_kth");
 }
 
 }  // namespace gorgo
