@@ -61,29 +61,61 @@ __device__ __forceinline__ uint64_t home_slot(uint64_t key, int cap_log2) {
     return (key * 0x9E3779B97F4A7C15ull) >> (64 - cap_log2);
 }
 
-// Physical lookup: slot index of `key`, or -1 when the probe sequence reaches a never-used slot.
-__device__ __forceinline__ int64_t find_slot(const Slot* tab, uint64_t key, uint64_t mask, int cap_log2) {
-    uint64_t h = home_slot(key, cap_log2);
-    for (;;) {
-        uint64_t k = ld(&tab[h].key);
-        if (k == key) return (int64_t)h;
-        if (k == 0) return -1;
-        h = (h + 1) & mask;
+// Physical lookup of G keys per lane, in a table each, all lanes of the wavefront together: slot index and stamp of the
+// key, or -1 (a stamp below every threshold) where the probe sequence reaches a never-used slot.  A probe is a serial
+// chain of memory round trips of 600 cycles and more, so every step reads U whole slots of all G sequences before it
+// looks at any of them.  (One slot of one sequence at a time, key before stamp: 65 replays of 3,001 requests on 7
+// replicas 37.1 ms, 1,024 of 4,000 on 32 replicas 33.3 ms; so 26.6 and 24.5.  Only what `active` has a bit for is looked up; the other loads stay where the sequence ended.)
+// FREE: also the first slot on the way that an insert may take over (stamp below `tau`), with that stamp.
+template <int G>
+struct Found {
+    int64_t slot[G], stamp[G];
+    int64_t free_slot[G], free_stamp[G];
+};
+template <int G, int U, bool FREE = false>
+__device__ __forceinline__ Found<G> find_slots(const Slot* const (&tab)[G], const uint64_t (&key)[G], unsigned active, uint64_t mask,
+                                               int cap_log2, int64_t tau = 0) {
+    Found<G> f;
+    uint64_t h[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        h[g] = home_slot(key[g], cap_log2);
+        f.slot[g] = f.stamp[g] = f.free_slot[g] = f.free_stamp[g] = -1;
     }
+    unsigned open = active;
+    while (ballot(open != 0) != 0) {
+        Slot e[G][U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int g = 0; g < G; ++g) e[g][u] = tab[g][(h[g] + u) & mask];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            bool on = (open >> g & 1u) != 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t at = (int64_t)((h[g] + u) & mask);
+                if (FREE) {
+                    const bool take = on && f.free_slot[g] < 0 && e[g][u].stamp < tau;
+                    f.free_slot[g] = take ? at : f.free_slot[g];
+                    f.free_stamp[g] = take ? e[g][u].stamp : f.free_stamp[g];
+                }
+                const bool hit = on && e[g][u].key == key[g];
+                f.slot[g] = hit ? at : f.slot[g];
+                f.stamp[g] = hit ? e[g][u].stamp : f.stamp[g];
+                on = on && !hit && e[g][u].key != 0;
+            }
+            h[g] = on ? (h[g] + U) & mask : h[g];
+            open &= on ? ~0u : ~(1u << g);
+        }
+    }
+    return f;
 }
 
-// Stamp of `key` in the table, -1 (below every threshold) when it is not there.
-__device__ __forceinline__ int64_t stamp_of(const Slot* tab, uint64_t key, uint64_t mask, int cap_log2) {
-    const int64_t s = find_slot(tab, key, mask, cap_log2);
-    return s >= 0 ? ld(&tab[s].stamp) : -1;
-}
-
-// Takes over the first never-used or garbage slot of the probe sequence (stamp below `tau`, the lowest threshold).
-// Returns true when a never-used slot was consumed.  Only called for keys known to be physically absent, by lanes
-// with distinct keys.
-__device__ __forceinline__ bool insert_new(Slot* tab, uint64_t key, int64_t stamp, int64_t tau, uint64_t mask,
-                                           int cap_log2) {
-    uint64_t h = home_slot(key, cap_log2);
+// Takes over the first never-used or garbage slot of the probe sequence (stamp below `tau`, the lowest threshold) from
+// slot h on.  Returns true when a never-used slot was consumed.  Only called for keys known to be physically absent, by
+// lanes with distinct keys.
+__device__ __forceinline__ bool insert_new(Slot* tab, uint64_t h, uint64_t key, int64_t stamp, int64_t tau, uint64_t mask) {
     for (;;) {
         int64_t s = ld(&tab[h].stamp);
         if (s < tau && cas_stamp(&tab[h].stamp, s, stamp)) {
@@ -157,54 +189,115 @@ __device__ __forceinline__ void block_cache_wave(const BlockArgs& b, int p, int 
     uint8_t* const routed = b.routed + (size_t)p * N;
     const int64_t rebuild_at = b.cap - b.cap / 8;
 
+    // Of the request in hand and the next one: where its blocks are, how many, input tokens, and its first 128 keys with
+    // their first-occurrence marks (lane = block), read a request ahead.
+    struct Blocks {
+        int64_t off;
+        int n, L;
+        uint32_t key[2];
+        int first[2];
+    };
+    auto read_scalars = [&](int64_t r, Blocks& q) {
+        const int64_t x = r < N ? r : N - 1;
+        q.off = b.blk_off[x];
+        q.n = (int)(b.blk_off[x + 1] - q.off);
+        q.L = a.in_len[x];
+    };
+    auto key_at = [&](const Blocks& q, int k) { return k < q.n ? b.key[q.off + k] : 0u; };
+    auto read_keys = [&](Blocks& q) {
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            const int k = g * WAVE + lane;
+            q.key[g] = key_at(q, k);
+            q.first[g] = k < q.n ? b.first[q.off + k] : 0;
+        }
+    };
+    Blocks now, next;
+    read_scalars(0, now);
+    read_keys(now);
+    read_scalars(1, next);
+
     meet(true);         // (the queue wavefront has set itself up)
     for (int64_t r = 0; r < N; ++r) {
-        const int64_t off = b.blk_off[r];
-        const int n = (int)(b.blk_off[r + 1] - off);
-        const int L = a.in_len[r];
+        const int64_t off = now.off;
+        const int n = now.n, L = now.L;
+        read_keys(next);
+        Blocks after;
+        read_scalars(r + 2, after);
 
-        // ---- prefix match: first block on every replica, then the whole list on the replicas that hold it; against
-        // the cache's threshold and, with an index, against the index's as well
+        // ---- prefix match: first block on every replica, then the whole list on the replicas that hold it, four at a
+        // time (their probes do not depend on each other); against the cache's threshold and, with an index, against the
+        // index's as well
         int my_m = 0, my_seen = 0;
         {
             bool has0 = false;
-            if (n > 0 && in) {
-                const int64_t t1 = tau1[lane], t2 = two ? tau2[lane] : t1;
-                has0 = stamp_of(tables + (size_t)lane * b.cap, b.key[off], mask, cap_log2) >= (t2 < t1 ? t2 : t1);
+            if (n > 0) {
+                const Slot* const tab[1] = {tables + (size_t)(in ? lane : 0) * b.cap};
+                const uint64_t key[1] = {(uint32_t)__builtin_amdgcn_readlane((int)now.key[0], 0)};
+                const int64_t stamp = find_slots<1, 4>(tab, key, in ? 1u : 0u, mask, cap_log2).stamp[0];
+                const int64_t t1 = in ? tau1[lane] : 0, t2 = two && in ? tau2[lane] : t1;
+                has0 = in && stamp >= (t2 < t1 ? t2 : t1);
             }
             unsigned long long holders = ballot(has0);
-            while (holders) {
-                const int i = __builtin_ctzll(holders);
-                holders &= holders - 1;
-                const Slot* tab = tables + (size_t)i * b.cap;
-                const int64_t t1 = tau1[i], t2 = two ? tau2[i] : t1;
-                int m1 = 0, m2 = 0;
-                bool open1 = true, open2 = two;
-                for (int base = 0; base < n && (open1 || open2); base += WAVE) {
+            auto match = [&](auto count) {          // the next `count` holders
+                constexpr int G = decltype(count)::value;
+                int id[G], m1[G], m2[G];
+                int64_t t1[G], t2[G];
+                const Slot* tab[G];
+                bool open1[G], open2[G];
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    const bool there = holders != 0;
+                    id[g] = there ? __builtin_ctzll(holders) : id[0];
+                    holders &= holders - (there ? 1 : 0);
+                    tab[g] = tables + (size_t)id[g] * b.cap;
+                    t1[g] = tau1[id[g]];
+                    t2[g] = two ? tau2[id[g]] : t1[g];
+                    m1[g] = m2[g] = 0;
+                    open1[g] = there;
+                    open2[g] = there && two;
+                }
+                for (int base = 0; base < n; base += WAVE) {
                     const int k = base + lane;
-                    const int64_t s = k < n ? stamp_of(tab, b.key[off + k], mask, cap_log2) : -1;
+                    const uint64_t mine = base == 0 ? now.key[0] : (base == WAVE ? now.key[1] : key_at(now, k));
+                    uint64_t key[G];
+                    unsigned active = 0;
+#pragma unroll
+                    for (int g = 0; g < G; ++g) {
+                        key[g] = mine;
+                        active |= k < n && (open1[g] || open2[g]) ? 1u << g : 0u;
+                    }
+                    const Found<G> f = find_slots<G, 2>(tab, key, active, mask, cap_log2);
                     const int width = n - base < WAVE ? n - base : WAVE;
                     const unsigned long long want = width == WAVE ? ~0ull : ((1ull << width) - 1);
-                    const unsigned long long got1 = ballot(k < n && s >= t1), got2 = ballot(k < n && s >= t2);
-                    if (open1) {
-                        if (got1 == want) m1 += width;
-                        else {
-                            m1 += __builtin_ctzll(~got1);
-                            open1 = false;
+                    bool more = false;
+#pragma unroll
+                    for (int g = 0; g < G; ++g) {
+                        const unsigned long long got1 = ballot(k < n && f.stamp[g] >= t1[g]);
+                        const unsigned long long got2 = ballot(k < n && f.stamp[g] >= t2[g]);
+                        if (open1[g]) {
+                            m1[g] += got1 == want ? width : __builtin_ctzll(~got1);
+                            open1[g] = got1 == want;
                         }
-                    }
-                    if (open2) {
-                        if (got2 == want) m2 += width;
-                        else {
-                            m2 += __builtin_ctzll(~got2);
-                            open2 = false;
+                        if (open2[g]) {
+                            m2[g] += got2 == want ? width : __builtin_ctzll(~got2);
+                            open2[g] = got2 == want;
                         }
+                        more = more || open1[g] || open2[g];
                     }
+                    if (!more) break;
                 }
-                if (lane == i) {
-                    my_m = m1;
-                    my_seen = m2;
+#pragma unroll
+                for (int g = G - 1; g >= 0; --g) {      // (a repeated first holder is written last)
+                    my_m = lane == id[g] ? m1[g] : my_m;
+                    my_seen = lane == id[g] ? m2[g] : my_seen;
                 }
+            };
+            while (holders != 0) {
+                const int count = __builtin_popcountll(holders);
+                if (count == 1) match(std::integral_constant<int, 1>());
+                else if (count == 2) match(std::integral_constant<int, 2>());
+                else match(std::integral_constant<int, 4>());
             }
         }
         // uncached tokens, really and as Eq. 3 sees them (block_tokens * blocks fits: below 2^15 and 2^16)
@@ -278,8 +371,10 @@ __device__ __forceinline__ void block_cache_wave(const BlockArgs& b, int p, int 
             }
             wave_settle();
             for (int64_t base = 0; base < kept; base += WAVE) {
-                if (base + lane < kept)
-                    insert_new(tab, ld(&spare[base + lane].key), ld(&spare[base + lane].stamp), 0, mask, cap_log2);
+                if (base + lane < kept) {
+                    const uint64_t k = ld(&spare[base + lane].key);
+                    insert_new(tab, home_slot(k, cap_log2), k, ld(&spare[base + lane].stamp), 0, mask);
+                }
                 wave_settle();
             }
             if (lane == 0) used[best] = (int32_t)kept;
@@ -290,26 +385,39 @@ __device__ __forceinline__ void block_cache_wave(const BlockArgs& b, int p, int 
             const int64_t t1 = tau1[best], t2 = two ? tau2[best] : t1;
             const int64_t garbage_below = t2 < t1 ? t2 : t1;
             int add1 = 0, add2 = 0, add_used = 0;
-            for (int base = 0; base < n; base += WAVE) {
-                const int k = base + lane;
-                const bool mine = k < n && b.first[off + k] != 0;
-                const uint64_t key = mine ? b.key[off + k] : 0;
-                const int64_t stamp = r * STAMP_STRIDE + (STAMP_STRIDE - 1 - k);
-                int64_t slot = -1, before = -1;
-                if (mine) {
-                    slot = find_slot(tab, key, mask, cap_log2);
-                    if (slot >= 0) {
-                        before = ld(&tab[slot].stamp);
-                        st(&tab[slot].stamp, stamp);          // touch, or revive an evicted entry in place
+            for (int base = 0; base < n; base += 2 * WAVE) {
+                bool mine[2];
+                uint64_t key[2];
+                const Slot* const tabs[2] = {tab, tab};
+#pragma unroll
+                for (int g = 0; g < 2; ++g) {
+                    const int k = base + g * WAVE + lane;
+                    key[g] = base == 0 ? now.key[g] : key_at(now, k);
+                    mine[g] = base == 0 ? now.first[g] != 0 : k < n && b.first[off + k] != 0;
+                }
+                const Found<2> f = find_slots<2, 2, true>(tabs, key, (mine[0] ? 1u : 0u) | (mine[1] ? 2u : 0u), mask, cap_log2, garbage_below);
+                auto stamp_at = [&](int g) { return r * STAMP_STRIDE + (STAMP_STRIDE - 1 - (base + g * WAVE + lane)); };
+#pragma unroll
+                for (int g = 0; g < 2; ++g)
+                    if (mine[g] && f.slot[g] >= 0) st(&tab[f.slot[g]].stamp, stamp_at(g));     // touch, or revive an evicted entry in place
+                wave_settle();
+#pragma unroll
+                for (int g = 0; g < 2; ++g) {
+                    // (the slot seen on the way is taken unless it has been revived or taken meanwhile)
+                    bool took_fresh = false;
+                    if (mine[g] && f.slot[g] < 0) {
+                        if (cas_stamp(&tab[f.free_slot[g]].stamp, f.free_stamp[g], stamp_at(g))) {
+                            st(&tab[f.free_slot[g]].key, key[g]);
+                            took_fresh = f.free_stamp[g] == -1;
+                        } else {
+                            took_fresh = insert_new(tab, (uint64_t)f.free_slot[g], key[g], stamp_at(g), garbage_below, mask);
+                        }
                     }
+                    add1 += __builtin_popcountll(ballot(mine[g] && f.stamp[g] < t1));
+                    add2 += __builtin_popcountll(ballot(mine[g] && f.stamp[g] < t2));
+                    add_used += __builtin_popcountll(ballot(took_fresh));
                 }
                 wave_settle();
-                bool took_fresh = false;
-                if (mine && slot < 0) took_fresh = insert_new(tab, key, stamp, garbage_below, mask, cap_log2);
-                wave_settle();
-                add1 += __builtin_popcountll(ballot(mine && before < t1));
-                add2 += __builtin_popcountll(ballot(mine && before < t2));
-                add_used += __builtin_popcountll(ballot(took_fresh));
             }
             if (lane == 0) {
                 live1[best] += add1;
@@ -325,32 +433,45 @@ __device__ __forceinline__ void block_cache_wave(const BlockArgs& b, int p, int 
         auto evict = [&](int64_t C, int64_t* tau, int32_t* live, int32_t* cur_r, int32_t* cur_k) {
             if (C <= 0 || live[best] <= C) return;
             int E = (int)(live[best] - C);
-            int cr = cur_r[best], ck = cur_k[best];
+            int cr = __builtin_amdgcn_readfirstlane(cur_r[best]), ck = __builtin_amdgcn_readfirstlane(cur_k[best]);
             while (E > 0) {
                 if (ck == 0) {
                     const int64_t x = next_routed(routed, cr, r, best, lane);
                     if (x >= r) break;          // cannot happen while E > 0; bounds the loop regardless
-                    cr = (int)x;
-                    ck = (int)(b.blk_off[x + 1] - b.blk_off[x]);
+                    cr = __builtin_amdgcn_readfirstlane((int)x);
+                    ck = (int)(b.blk_off[cr + 1] - b.blk_off[cr]);
                     continue;
                 }
+                // 128 positions of the request, lane order = eviction order (deepest first)
                 const int64_t ooff = b.blk_off[cr];
-                const int k = ck - 1 - lane;               // lane order = eviction order (deepest first)
-                bool alive = false;
-                if (k >= 0 && b.first[ooff + k] != 0)
-                    alive = stamp_of(tab, b.key[ooff + k], mask, cap_log2) ==
-                            (int64_t)cr * STAMP_STRIDE + (STAMP_STRIDE - 1 - k);
-                const unsigned long long mk = ballot(alive);
-                const int cnt = __builtin_popcountll(mk);
-                if (cnt <= E) {
-                    E -= cnt;
-                    ck = ck > WAVE ? ck - WAVE : 0;
-                } else {
-                    const int rank = __builtin_popcountll(mk & ((1ull << lane) - 1));
-                    const unsigned long long last = ballot(alive && rank == E - 1);
-                    const int j = __builtin_ctzll(last);
-                    ck = ck - 1 - j;
-                    E = 0;
+                bool mine[2];
+                uint64_t key[2];
+                const Slot* const tabs[2] = {tab, tab};
+#pragma unroll
+                for (int g = 0; g < 2; ++g) {
+                    const int k = ck - 1 - g * WAVE - lane;
+                    const int64_t at = ooff + (k > 0 ? k : 0);
+                    key[g] = b.key[at];
+                    mine[g] = b.first[at] != 0 && k >= 0;
+                }
+                const Found<2> f = find_slots<2, 2>(tabs, key, (mine[0] ? 1u : 0u) | (mine[1] ? 2u : 0u), mask, cap_log2);
+                const int from = ck;
+#pragma unroll
+                for (int g = 0; g < 2; ++g) {
+                    const int k = from - 1 - g * WAVE - lane;
+                    const bool alive = mine[g] && f.stamp[g] == (int64_t)cr * STAMP_STRIDE + (STAMP_STRIDE - 1 - k);
+                    const unsigned long long mk = ballot(alive);
+                    const int cnt = __builtin_popcountll(mk);
+                    if (E == 0) continue;
+                    if (cnt <= E) {
+                        E -= cnt;
+                        ck = ck > WAVE ? ck - WAVE : 0;
+                    } else {
+                        const int rank = __builtin_popcountll(mk & ((1ull << lane) - 1));
+                        const unsigned long long last = ballot(alive && rank == E - 1);
+                        ck = ck - 1 - __builtin_ctzll(last);
+                        E = 0;
+                    }
                 }
             }
             if (lane == 0) {
@@ -370,11 +491,13 @@ __device__ __forceinline__ void block_cache_wave(const BlockArgs& b, int p, int 
             w_prefill = comm->w[0][1];
             w_queue = comm->w[0][2];
         }
+        now = next;
+        next = after;
     }
 }
 
 template <int MODE, bool ENGINE, bool PROXY>
-__global__ void __launch_bounds__(BLOCK_THREADS) replay_blocks_kernel(BlockArgs b) {
+__global__ void __launch_bounds__(BLOCK_THREADS, PROXY ? 3 : 4) replay_blocks_kernel(BlockArgs b) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     __shared__ __align__(16) Handover<PROXY> comm;
     const int lane = threadIdx.x & (WAVE - 1);

@@ -121,6 +121,26 @@ def test_long_requests_many_compactions():
         check_proxy(tr, model, px, PAR[:2], 1.0)
 
 
+@pytest.mark.parametrize("blocks", [1, 63, 64, 65, 127, 128, 129, 257])
+@pytest.mark.parametrize("R", [1, 2, 3, 5, 9])
+def test_lengths_and_holders_at_the_edges_of_a_step(blocks, R):
+    """Requests of a length around one and two times the wavefront, all with the same first block, so that every replica
+    that has served one holds it: one, two, four and more lists are matched together, prefixes of every length."""
+    rng = np.random.default_rng(100 * blocks + R)
+    N = 150
+    lengths = np.maximum(1, blocks - rng.integers(0, 2, N))
+    ids = []
+    for r in range(N):
+        same = int(rng.integers(0, lengths[r] + 1))           # a common beginning, then blocks in an order of its own
+        tail = 1000 + rng.permutation(2 * blocks + 4)[:lengths[r]]
+        ids.append(np.where(np.arange(lengths[r]) < max(1, same), 1 + np.arange(lengths[r]), tail))
+    off = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    tr = tg.Trace(ts_ms=np.cumsum(rng.integers(0, 400, N)).astype(np.int64), in_len=(512 * lengths - 7).astype(np.int32),
+                  out_len=rng.integers(1, 50, N).astype(np.int32), blk_off=off, hash_ids=np.concatenate(ids).astype(np.int64))
+    model = g.Model(R, 2, 2 * blocks + 3, 0.05, 20.0)
+    check_population(tr, model, np.linspace(5.0, 90.0, R), PAR, 1.0, paths=[1])
+
+
 @pytest.mark.parametrize("config,n", [(1, 2000), (2, 4000)])
 def test_block_tables_give_what_segment_rows_give(config, n):
     """Chain-consistent workloads, forced onto block tables: every variant against the oracle (the segment rows'
