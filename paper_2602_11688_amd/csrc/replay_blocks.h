@@ -7,12 +7,15 @@
 // exactly its stamp.  Nothing about the trace is assumed (the same id may follow different ids in different
 // requests), so the match probes block by block.
 //
-// A replay is run by two wavefronts of one workgroup.  The queue wavefront is the segment formulation's: service
+// A replay is run by three wavefronts of one workgroup.  The queue wavefront is the segment formulation's: service
 // slots, service step, what leaves the load signal (Eq. 2), per-request outputs, and with them the online tuner, the
-// engine model and the epochs of the proxy's round-trip estimates.  The cache wavefront here does per request:
-// match against every replica's table, score (Eq. 3) or apply the baseline policy, lowest-index minimum, announce the
-// choice; meet (X: the choice is there); table update and eviction on the chosen replica, while the queue wavefront
-// serves the request; meet (Y: so is what completes by the next arrival).  Both wavefronts execute exactly two
+// engine model and the epochs of the proxy's round-trip estimates.  The deciding wavefront scores a request (Eq. 3) or
+// applies the baseline policy, takes the lowest-index minimum and announces the choice; meeting X.  Then the updating
+// wavefront updates the chosen replica's table and evicts, the queue wavefront serves the request, and the deciding
+// wavefront matches the next request against the tables of all other replicas, which the choice does not change;
+// meeting Y; the chosen replica is matched then.  A request is a chain of memory round trips and nothing else: with the
+// match and the update one after the other in one wavefront 65 replays of 3,001 requests on 7 replicas took 26.6 ms, so
+// 23.8; 1,024 replays of 4,000 requests on 32 replicas take 24.5 either way.  Every wavefront executes exactly two
 // barriers per request, whatever the data.
 //
 // The proxy's own index of a replica (Sec. 7: the proxy does not see replica-side eviction) is a second LRU over
@@ -25,7 +28,7 @@
 
 namespace gorgo {
 
-constexpr int BLOCK_THREADS = 2 * WAVE;      // cache wavefront + queue wavefront
+constexpr int BLOCK_THREADS = 3 * WAVE;      // deciding, updating and queue wavefront
 
 // One cache-table slot.  key 0 = never used (then stamp = -1).  An entry is held by an LRU iff stamp >= that
 // LRU's threshold; entries below every threshold are garbage whose slots can be taken over by inserts.
@@ -135,18 +138,68 @@ __global__ void __launch_bounds__(256) fill_slots(Slot* s, size_t n) {
     }
 }
 
-// What the lanes of this wavefront have written to global memory is there for its other lanes to read (the cache
-// wavefront is the only one that touches the tables and the log of choices).
+// What the lanes of this wavefront have written to global memory is there for its other lanes to read (the updating
+// wavefront is the only one that writes the tables and the log of choices; a table is read by the deciding wavefront only
+// while it is not being written: meetings X and Y).
 __device__ __forceinline__ void wave_settle() {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
     __builtin_amdgcn_wave_barrier();
 }
 
-// Cache wavefront of a replay over block tables.  Lane = replica for the first-block probe, the scores and the
-// minimum; lane = block of the request for the prefix match, the table update and the eviction walk.
+// The replicas' LRU state, shared by the two wavefronts (LDS).
+struct LruState {
+    int64_t *tau1, *tau2;      // [R] eviction thresholds: the cache's, the index's
+    int32_t *live1, *live2;    // [R] blocks held
+    int32_t *cur_r1, *cur_r2;  // [R] eviction cursors: request ...
+    int32_t *cur_k1, *cur_k2;  // [R] ... and position (blocks >= cur_k are gone)
+    int32_t *used;             // [R] slots ever used since the last compaction
+    __device__ __forceinline__ LruState(unsigned char* state, int R) {
+        tau1 = reinterpret_cast<int64_t*>(state);
+        tau2 = tau1 + R;
+        live1 = reinterpret_cast<int32_t*>(tau2 + R);
+        live2 = live1 + R;
+        cur_r1 = live2 + R;
+        cur_r2 = cur_r1 + R;
+        cur_k1 = cur_r2 + R;
+        cur_k2 = cur_k1 + R;
+        used = cur_k2 + R;
+    }
+};
+
+// Where a request's blocks are, how many, input tokens, and its first 128 keys with their first-occurrence marks (lane =
+// block).  Read ahead of the request.
+struct Blocks {
+    int64_t off;
+    int n, L;
+    uint32_t key[2];
+    int first[2];
+    __device__ __forceinline__ void read_scalars(const BlockArgs& b, int64_t r) {
+        const int64_t x = r < b.q.N ? r : b.q.N - 1;
+        off = b.blk_off[x];
+        n = (int)(b.blk_off[x + 1] - off);
+        L = b.q.in_len[x];
+    }
+    __device__ __forceinline__ uint64_t key_at(const BlockArgs& b, int k) const { return k < n ? b.key[off + k] : 0u; }
+    __device__ __forceinline__ void read_keys(const BlockArgs& b, int lane) {
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            const int k = g * WAVE + lane;
+            key[g] = k < n ? b.key[off + k] : 0u;
+        }
+    }
+    __device__ __forceinline__ void read_marks(const BlockArgs& b, int lane) {
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            const int k = g * WAVE + lane;
+            first[g] = k < n ? b.first[off + k] : 0;
+        }
+    }
+};
+
+// Deciding wavefront of a replay over block tables.  Lane = replica for the first-block probe, the scores and the
+// minimum; lane = block of the request for the prefix match.
 template <int MODE, bool ENGINE, bool PROXY>
-__device__ __forceinline__ void block_cache_wave(const BlockArgs& b, int p, int lane, unsigned char* state,
-                                                 Handover<PROXY>* comm) {
+__device__ __forceinline__ void block_decide_wave(const BlockArgs& b, int p, int lane, const LruState& lru, Handover<PROXY>* comm) {
     constexpr bool ONLINE = MODE == MODE_ONLINE;
     constexpr bool SCORED = MODE == MODE_COST_MODEL || MODE == MODE_ONLINE;
     const SegArgs& a = b.q;
@@ -155,27 +208,15 @@ __device__ __forceinline__ void block_cache_wave(const BlockArgs& b, int p, int 
     const bool in = lane < R;
     const uint64_t mask = (uint64_t)b.cap - 1;
     const int cap_log2 = b.cap_log2;
-    // the proxy's own index: a second LRU (capacity index_blocks, 0 = it never forgets) over the same touches
-    const bool two = PROXY && a.index_blocks >= 0;
-    const int64_t C1 = a.C, C2 = two ? a.index_blocks : 0;
-
-    int64_t* const tau1 = reinterpret_cast<int64_t*>(state);      // [R] the cache's eviction threshold
-    int64_t* const tau2 = tau1 + R;                               // [R] the index's
-    int32_t* const live1 = reinterpret_cast<int32_t*>(tau2 + R);  // [R] blocks the cache holds
-    int32_t* const live2 = live1 + R;                             // [R] blocks the index holds
-    int32_t* const cur_r1 = live2 + R;                            // [R] eviction cursors: request ...
-    int32_t* const cur_r2 = cur_r1 + R;
-    int32_t* const cur_k1 = cur_r2 + R;                           // [R] ... and position (blocks >= cur_k are gone)
-    int32_t* const cur_k2 = cur_k1 + R;
-    int32_t* const used = cur_k2 + R;                             // [R] slots ever used since the last compaction
+    const bool two = PROXY && a.index_blocks >= 0;      // the proxy has an index of its own
+    int64_t *const tau1 = lru.tau1, *const tau2 = lru.tau2;
     for (int i = lane; i < R; i += WAVE) {
         tau1[i] = tau2[i] = 0;
-        live1[i] = live2[i] = 0;
-        cur_r1[i] = cur_r2[i] = -1;
-        cur_k1[i] = cur_k2[i] = 0;
-        used[i] = 0;
+        lru.live1[i] = lru.live2[i] = 0;
+        lru.cur_r1[i] = lru.cur_r2[i] = -1;
+        lru.cur_k1[i] = lru.cur_k2[i] = 0;
+        lru.used[i] = 0;
     }
-    wave_sync();
 
     double w_rtt = a.params[3 * (size_t)p + 0];
     double w_prefill = a.params[3 * (size_t)p + 1];
@@ -183,123 +224,100 @@ __device__ __forceinline__ void block_cache_wave(const BlockArgs& b, int p, int 
     double q = 0.0;                                               // load signal of replica = lane
     const double my_rtt = !PROXY && in ? a.rtt[lane] : 0.0;       // (proxy variants: comes with the queue terms)
     const uint64_t seed = MODE == MODE_RANDOM ? a.seeds[p] : 0;
+    const Slot* const tables = b.tables + (size_t)p * R * b.cap;
 
-    Slot* const tables = b.tables + (size_t)p * R * b.cap;
-    Slot* const spare = b.spare + (size_t)p * b.cap;
-    uint8_t* const routed = b.routed + (size_t)p * N;
-    const int64_t rebuild_at = b.cap - b.cap / 8;
+    Blocks now, next, after;
+    now.read_scalars(b, 0);
+    now.read_keys(b, lane);
+    next.read_scalars(b, 1);
+    next.read_keys(b, lane);
+    after.read_scalars(b, 2);
 
-    // Of the request in hand and the next one: where its blocks are, how many, input tokens, and its first 128 keys with
-    // their first-occurrence marks (lane = block), read a request ahead.
-    struct Blocks {
-        int64_t off;
-        int n, L;
-        uint32_t key[2];
-        int first[2];
-    };
-    auto read_scalars = [&](int64_t r, Blocks& q) {
-        const int64_t x = r < N ? r : N - 1;
-        q.off = b.blk_off[x];
-        q.n = (int)(b.blk_off[x + 1] - q.off);
-        q.L = a.in_len[x];
-    };
-    auto key_at = [&](const Blocks& q, int k) { return k < q.n ? b.key[q.off + k] : 0u; };
-    auto read_keys = [&](Blocks& q) {
+    // ---- prefix match of a request against the cache's threshold and, with an index, against the index's as well: the
+    // whole list on the replicas in `holders`, four at a time (their probes do not depend on each other)
+    int my_m = 0, my_seen = 0;
+    auto match_on = [&](const Blocks& of, unsigned long long holders) {
+        const int n = of.n;
+        auto match = [&](auto count) {          // the next `count` holders
+            constexpr int G = decltype(count)::value;
+            int id[G], m1[G], m2[G];
+            int64_t t1[G], t2[G];
+            const Slot* tab[G];
+            bool open1[G], open2[G];
 #pragma unroll
-        for (int g = 0; g < 2; ++g) {
-            const int k = g * WAVE + lane;
-            q.key[g] = key_at(q, k);
-            q.first[g] = k < q.n ? b.first[q.off + k] : 0;
-        }
-    };
-    Blocks now, next;
-    read_scalars(0, now);
-    read_keys(now);
-    read_scalars(1, next);
-
-    meet(true);         // (the queue wavefront has set itself up)
-    for (int64_t r = 0; r < N; ++r) {
-        const int64_t off = now.off;
-        const int n = now.n, L = now.L;
-        read_keys(next);
-        Blocks after;
-        read_scalars(r + 2, after);
-
-        // ---- prefix match: first block on every replica, then the whole list on the replicas that hold it, four at a
-        // time (their probes do not depend on each other); against the cache's threshold and, with an index, against the
-        // index's as well
-        int my_m = 0, my_seen = 0;
-        {
-            bool has0 = false;
-            if (n > 0) {
-                const Slot* const tab[1] = {tables + (size_t)(in ? lane : 0) * b.cap};
-                const uint64_t key[1] = {(uint32_t)__builtin_amdgcn_readlane((int)now.key[0], 0)};
-                const int64_t stamp = find_slots<1, 4>(tab, key, in ? 1u : 0u, mask, cap_log2).stamp[0];
-                const int64_t t1 = in ? tau1[lane] : 0, t2 = two && in ? tau2[lane] : t1;
-                has0 = in && stamp >= (t2 < t1 ? t2 : t1);
+            for (int g = 0; g < G; ++g) {
+                const bool there = holders != 0;
+                id[g] = there ? __builtin_ctzll(holders) : id[0];
+                holders &= holders - (there ? 1 : 0);
+                tab[g] = tables + (size_t)id[g] * b.cap;
+                t1[g] = tau1[id[g]];
+                t2[g] = two ? tau2[id[g]] : t1[g];
+                m1[g] = m2[g] = 0;
+                open1[g] = there;
+                open2[g] = there && two;
             }
-            unsigned long long holders = ballot(has0);
-            auto match = [&](auto count) {          // the next `count` holders
-                constexpr int G = decltype(count)::value;
-                int id[G], m1[G], m2[G];
-                int64_t t1[G], t2[G];
-                const Slot* tab[G];
-                bool open1[G], open2[G];
+            for (int base = 0; base < n; base += WAVE) {
+                const int k = base + lane;
+                const uint64_t mine = base == 0 ? of.key[0] : (base == WAVE ? of.key[1] : of.key_at(b, k));
+                uint64_t key[G];
+                unsigned active = 0;
 #pragma unroll
                 for (int g = 0; g < G; ++g) {
-                    const bool there = holders != 0;
-                    id[g] = there ? __builtin_ctzll(holders) : id[0];
-                    holders &= holders - (there ? 1 : 0);
-                    tab[g] = tables + (size_t)id[g] * b.cap;
-                    t1[g] = tau1[id[g]];
-                    t2[g] = two ? tau2[id[g]] : t1[g];
-                    m1[g] = m2[g] = 0;
-                    open1[g] = there;
-                    open2[g] = there && two;
+                    key[g] = mine;
+                    active |= k < n && (open1[g] || open2[g]) ? 1u << g : 0u;
                 }
-                for (int base = 0; base < n; base += WAVE) {
-                    const int k = base + lane;
-                    const uint64_t mine = base == 0 ? now.key[0] : (base == WAVE ? now.key[1] : key_at(now, k));
-                    uint64_t key[G];
-                    unsigned active = 0;
+                const Found<G> f = find_slots<G, 2>(tab, key, active, mask, cap_log2);
+                const int width = n - base < WAVE ? n - base : WAVE;
+                const unsigned long long want = width == WAVE ? ~0ull : ((1ull << width) - 1);
+                bool more = false;
 #pragma unroll
-                    for (int g = 0; g < G; ++g) {
-                        key[g] = mine;
-                        active |= k < n && (open1[g] || open2[g]) ? 1u << g : 0u;
+                for (int g = 0; g < G; ++g) {
+                    const unsigned long long got1 = ballot(k < n && f.stamp[g] >= t1[g]);
+                    const unsigned long long got2 = ballot(k < n && f.stamp[g] >= t2[g]);
+                    if (open1[g]) {
+                        m1[g] += got1 == want ? width : __builtin_ctzll(~got1);
+                        open1[g] = got1 == want;
                     }
-                    const Found<G> f = find_slots<G, 2>(tab, key, active, mask, cap_log2);
-                    const int width = n - base < WAVE ? n - base : WAVE;
-                    const unsigned long long want = width == WAVE ? ~0ull : ((1ull << width) - 1);
-                    bool more = false;
-#pragma unroll
-                    for (int g = 0; g < G; ++g) {
-                        const unsigned long long got1 = ballot(k < n && f.stamp[g] >= t1[g]);
-                        const unsigned long long got2 = ballot(k < n && f.stamp[g] >= t2[g]);
-                        if (open1[g]) {
-                            m1[g] += got1 == want ? width : __builtin_ctzll(~got1);
-                            open1[g] = got1 == want;
-                        }
-                        if (open2[g]) {
-                            m2[g] += got2 == want ? width : __builtin_ctzll(~got2);
-                            open2[g] = got2 == want;
-                        }
-                        more = more || open1[g] || open2[g];
+                    if (open2[g]) {
+                        m2[g] += got2 == want ? width : __builtin_ctzll(~got2);
+                        open2[g] = got2 == want;
                     }
-                    if (!more) break;
+                    more = more || open1[g] || open2[g];
                 }
-#pragma unroll
-                for (int g = G - 1; g >= 0; --g) {      // (a repeated first holder is written last)
-                    my_m = lane == id[g] ? m1[g] : my_m;
-                    my_seen = lane == id[g] ? m2[g] : my_seen;
-                }
-            };
-            while (holders != 0) {
-                const int count = __builtin_popcountll(holders);
-                if (count == 1) match(std::integral_constant<int, 1>());
-                else if (count == 2) match(std::integral_constant<int, 2>());
-                else match(std::integral_constant<int, 4>());
+                if (!more) break;
             }
+#pragma unroll
+            for (int g = G - 1; g >= 0; --g) {      // (a repeated first holder is written last)
+                my_m = lane == id[g] ? m1[g] : my_m;
+                my_seen = lane == id[g] ? m2[g] : my_seen;
+            }
+        };
+        while (holders != 0) {
+            const int count = __builtin_popcountll(holders);
+            if (count == 1) match(std::integral_constant<int, 1>());
+            else if (count == 2) match(std::integral_constant<int, 2>());
+            else match(std::integral_constant<int, 4>());
         }
+    };
+    // ---- the same on the replicas in `among` that hold the first block
+    auto match_among = [&](const Blocks& of, unsigned long long among) {
+        if (of.n == 0) return;
+        const bool mine = (among >> lane & 1) != 0;
+        const Slot* const tab[1] = {tables + (size_t)(mine ? lane : 0) * b.cap};
+        const uint64_t key[1] = {(uint32_t)__builtin_amdgcn_readlane((int)of.key[0], 0)};
+        const int64_t stamp = find_slots<1, 4>(tab, key, mine ? 1u : 0u, mask, cap_log2).stamp[0];
+        const int64_t t1 = mine ? tau1[lane] : 0, t2 = two && mine ? tau2[lane] : t1;
+        match_on(of, ballot(mine && stamp >= (t2 < t1 ? t2 : t1)));
+    };
+    const unsigned long long all = R >= WAVE ? ~0ull : (1ull << R) - 1;
+
+    meet(true);         // (the queue wavefront has set itself up)
+    // (nothing is cached yet: the first request matches nowhere)
+    int previous = -1;
+    for (int64_t r = 0; r < N; ++r) {
+        const int n = now.n, L = now.L;
+        // the replica that the previous request went to was still being updated: its turn now
+        if (previous >= 0 && n > 0) match_on(now, 1ull << previous);
         // uncached tokens, really and as Eq. 3 sees them (block_tokens * blocks fits: below 2^15 and 2^16)
         int hit_tok = a.block_tokens * my_m;
         hit_tok = hit_tok > L ? L : hit_tok;
@@ -341,9 +359,60 @@ __device__ __forceinline__ void block_cache_wave(const BlockArgs& b, int p, int 
             comm->choice[r & 1][best] = Choice{ENGINE || PROXY ? (double)(int)u_best : a.a_pf * (double)(int)u_best, -2, (unsigned)m_best};
             if constexpr (PROXY) comm->seen[r & 1][best] = (uint16_t)seen_best;
             comm->best[r & 1][0] = best;
-            st(&routed[r], (uint8_t)best);
         }
         meet(true);                                                  // X(r): the choice is there
+
+        // ---- the next request, on the replicas that this one does not change
+        after.read_keys(b, lane);
+        my_m = my_seen = 0;
+        if (r + 1 < N) match_among(next, all & ~(1ull << best));
+        now = next;
+        next = after;
+        after.read_scalars(b, r + 3);
+        previous = best;
+        meet(true);                                                  // Y(r): what completes by the next arrival is known
+        if (ONLINE) {
+            w_rtt = comm->w[0][0];
+            w_prefill = comm->w[0][1];
+            w_queue = comm->w[0][2];
+        }
+    }
+}
+
+// Updating wavefront: between X(r) and Y(r) it brings the chosen replica up to date.  Lane = block.
+template <bool PROXY>
+__device__ __forceinline__ void block_update_wave(const BlockArgs& b, int p, int lane, const LruState& lru, Handover<PROXY>* comm) {
+    const SegArgs& a = b.q;
+    const int64_t N = a.N;
+    const uint64_t mask = (uint64_t)b.cap - 1;
+    const int cap_log2 = b.cap_log2;
+    // the proxy's own index: a second LRU (capacity index_blocks, 0 = it never forgets) over the same touches
+    const bool two = PROXY && a.index_blocks >= 0;
+    const int64_t C1 = a.C, C2 = two ? a.index_blocks : 0;
+    int64_t *const tau1 = lru.tau1, *const tau2 = lru.tau2;
+    int32_t *const live1 = lru.live1, *const live2 = lru.live2, *const cur_r1 = lru.cur_r1, *const cur_r2 = lru.cur_r2,
+            *const cur_k1 = lru.cur_k1, *const cur_k2 = lru.cur_k2, *const used = lru.used;
+    Slot* const tables = b.tables + (size_t)p * a.R * b.cap;
+    Slot* const spare = b.spare + (size_t)p * b.cap;
+    uint8_t* const routed = b.routed + (size_t)p * N;
+    const int64_t rebuild_at = b.cap - b.cap / 8;
+
+    Blocks now, next;
+    now.read_scalars(b, 0);
+    now.read_keys(b, lane);
+    now.read_marks(b, lane);
+    next.read_scalars(b, 1);
+    meet(true);
+    for (int64_t r = 0; r < N; ++r) {
+        const int64_t off = now.off;
+        const int n = now.n;
+        next.read_keys(b, lane);
+        next.read_marks(b, lane);
+        Blocks after;
+        after.read_scalars(b, r + 2);
+        meet(true);                                                  // X(r): the choice is there
+        const int best = __builtin_amdgcn_readfirstlane(comm->best[r & 1][0]);
+        if (lane == 0) st(&routed[r], (uint8_t)best);
 
         // ---- update on the chosen replica
         Slot* const tab = tables + (size_t)best * b.cap;
@@ -392,7 +461,7 @@ __device__ __forceinline__ void block_cache_wave(const BlockArgs& b, int p, int 
 #pragma unroll
                 for (int g = 0; g < 2; ++g) {
                     const int k = base + g * WAVE + lane;
-                    key[g] = base == 0 ? now.key[g] : key_at(now, k);
+                    key[g] = base == 0 ? now.key[g] : now.key_at(b, k);
                     mine[g] = base == 0 ? now.first[g] != 0 : k < n && b.first[off + k] != 0;
                 }
                 const Found<2> f = find_slots<2, 2, true>(tabs, key, (mine[0] ? 1u : 0u) | (mine[1] ? 2u : 0u), mask, cap_log2, garbage_below);
@@ -485,14 +554,10 @@ __device__ __forceinline__ void block_cache_wave(const BlockArgs& b, int p, int 
         evict(C1, tau1, live1, cur_r1, cur_k1);
         if (two) evict(C2, tau2, live2, cur_r2, cur_k2);
         wave_settle();
-        meet(true);                                                  // Y(r): what completes by the next arrival is known
-        if (ONLINE) {
-            w_rtt = comm->w[0][0];
-            w_prefill = comm->w[0][1];
-            w_queue = comm->w[0][2];
-        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");              // (the deciding wavefront reads this replica next)
         now = next;
         next = after;
+        meet(true);                                                  // Y(r)
     }
 }
 
@@ -502,12 +567,13 @@ __global__ void __launch_bounds__(BLOCK_THREADS, PROXY ? 3 : 4) replay_blocks_ke
     __shared__ __align__(16) Handover<PROXY> comm;
     const int lane = threadIdx.x & (WAVE - 1);
     const int p = blockIdx.x;
-    if (threadIdx.x >= WAVE) {
+    if (threadIdx.x >= 2 * WAVE) {
         queue_wave<MODE, ENGINE, PROXY, 1, true, false>(b.q, 0, lane, lds_raw, &comm);
     } else if (b.q.N > 0) {
-        unsigned char* const state =
-            lds_raw + ((replay_queue_lds_bytes(b.q.R, b.q.B, ENGINE, MODE == MODE_ONLINE ? b.q.window : 0) + 15) & ~(size_t)15);
-        block_cache_wave<MODE, ENGINE, PROXY>(b, p, lane, state, &comm);
+        const LruState lru(lds_raw + ((replay_queue_lds_bytes(b.q.R, b.q.B, ENGINE, MODE == MODE_ONLINE ? b.q.window : 0) + 15) & ~(size_t)15),
+                           b.q.R);
+        if (threadIdx.x < WAVE) block_decide_wave<MODE, ENGINE, PROXY>(b, p, lane, lru, &comm);
+        else block_update_wave<PROXY>(b, p, lane, lru, &comm);
     }
 }
 
