@@ -893,6 +893,25 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
     }
     meet(true);        // (nothing has completed yet: the first request can be decided)
 
+    // What the descriptor of the next request says, read (LDS) while this one's completions are retired: a round trip less
+    // before the meeting (64 replays of 50,000 requests 35.4 -> 34.9 ms, 1,024 online tuners of 40,000 32.9 -> 32.0; the
+    // proxy variants, whose deciding wavefront has the longer chain, lose 1 % and read it when they need it).
+    constexpr bool AHEAD = !BLOCKS && !PROXY;
+    struct {
+        int L, O, flags;
+        double t2, dec;
+    } coming{0, 0, 0, 0.0, 0.0};
+    auto read_desc = [&](int r) {
+        const SegDesc& d = comm->ring[r & (DESC_RING - 1)];
+        const int4 h = *reinterpret_cast<const int4*>(&d.L);
+        coming.L = h.x;
+        coming.flags = h.w;
+        coming.t2 = d.t2[which];
+        if (ENGINE) coming.O = d.O;
+        else coming.dec = d.dec;
+    };
+    if (AHEAD) read_desc(0);
+
     double o_ttft = 0.0, o_e2e = 0.0;
     int o_route = 0, o_hit = 0, o_believed = 0;
     SectionClock<TIMED> clk;
@@ -911,13 +930,12 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
                 t2 = i2 < WAVE ? readlane_f64(cur.t, i2) : readlane_f64(nxt.t, i2 - WAVE);
                 dec = a.a_dec * (double)O;
             } else {
-                const SegDesc& d = comm->ring[r & (DESC_RING - 1)];
-                const int4 h = *reinterpret_cast<const int4*>(&d.L);
-                L = h.x;
-                t2 = d.t2[which];
-                if (ENGINE) O = d.O;
-                else dec = d.dec;
-                sync = (__builtin_amdgcn_readfirstlane(h.w) & DESC_SYNC) != 0;
+                if (!AHEAD) read_desc(r);
+                L = coming.L;
+                O = coming.O;
+                t2 = coming.t2;
+                dec = coming.dec;
+                sync = (__builtin_amdgcn_readfirstlane(coming.flags) & DESC_SYNC) != 0;
             }
             clk.tick(0);
             meet(true);                                                  // X(r)
@@ -940,6 +958,7 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
                 Q.template serve<PROXY>(r, best, t0, half, PROXY ? a.a_pf * prefill : prefill, dec, weight, rec, lane, &ttft, &e2e, t2, due);
             }
             clk.tick(9);                                                 // service
+            if (AHEAD) read_desc(r + 1);
             o_ttft = lane == i ? ttft : o_ttft;
             o_e2e = lane == i ? e2e : o_e2e;
             if (BLOCKS) {
