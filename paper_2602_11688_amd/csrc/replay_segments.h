@@ -282,6 +282,12 @@ constexpr int32_t NEVER_CACHED = INT32_MIN;      // cell value of the extra row:
 
 constexpr int CELL_SETS = 3;          // requests whose row cells are in LDS: two ahead are loaded while one is at hand
 constexpr int LOOK_RING = 8;          // log records of look-ahead kept in LDS per replica
+// How often the look-ahead is fed, as a mask: a record per replica every fourth request, or every eighth with 24 replicas
+// or more.  The cursors of all replicas together pass about 0.9 log records per request, so the more replicas there are
+// the less often each needs one, and taking one costs the deciding wavefront some 500 cycles.  (1,024 replays of 40,000
+// requests, 32 replicas: proxy variant 33.4 -> 32.6 ms, the others equal within 1 %; 16 replicas, bursts, every eighth:
+// 47.6 -> 48.2 ms, records are then waited for.)
+__host__ __device__ constexpr int look_every(int R) { return R >= 24 ? 7 : 3; }
 // What every replica would mean for a request, written by its lane before the minimum is known; the replica with the
 // minimum is announced by its number alone.
 struct __align__(16) Choice {
@@ -304,7 +310,7 @@ struct __align__(256) Handover {
     // of the cursor, slot k of replica i at [k * WAVE + i] (one slot is always free)
     unsigned long long look[PROXY ? 2 : 1][LOOK_RING * WAVE];
     unsigned long long fetched[PROXY ? 2 : 1][WAVE]; // log records that the front end has fetched ...
-    int wanted[PROXY ? 2 : 1][WAVE];      // ... and is to fetch, every fourth request
+    int wanted[PROXY ? 2 : 1][WAVE];      // ... and is to fetch, every fourth or eighth request
     SegDesc ring[DESC_RING];
     double half[PROXY ? 4 : 1][WAVE];     // half the round trip time per replica (proxy variants: [request mod 4])
     double rtt[PROXY ? 4 : 1][PROXY ? WAVE : 1];  // proxy variants, [request mod 4]: estimated round trip time per replica
@@ -738,20 +744,21 @@ __device__ __forceinline__ void front_wave(const SegArgs& a, int lane, Handover<
     meet(false);
     SectionClock<TIMED> clk;
     clk.start();
+    const int every = look_every(R);
     // what is done before the meeting X(r): the cells of r + 2 are loaded, and after a piece of the descriptors' work
-    // handed over; every fourth time the log records that were asked for as well
+    // handed over; every fourth or eighth time the log records that were asked for as well
     unsigned long long raw[PROXY ? 2 : 1] = {};
     auto begin = [&](int r) {
         if (r >= N) return;
         load_cells(r + 2);
-        if ((r & 3) == 0 && r > 0)
+        if ((r & every) == 0 && r > 0)
             for (int c = 0; c < (PROXY ? 2 : 1); ++c) raw[c] = ld(&log64[comm->wanted[c][lane]]);
     };
     auto pass = [&](int r) {
         if (r >= N) return;
         const bool sync = (__builtin_amdgcn_readfirstlane(comm->ring[r & (DESC_RING - 1)].flags) & DESC_SYNC) != 0;
         store_cells();
-        if ((r & 3) == 0 && r > 0)
+        if ((r & every) == 0 && r > 0)
             for (int c = 0; c < (PROXY ? 2 : 1); ++c) comm->fetched[c][lane] = raw[c];
         clk.tick(0);                                                 // descriptors, cells
         meet(true);                                                  // X(r)
@@ -1199,6 +1206,7 @@ __device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Handover
     LogRec* const log = a.log + p * ((size_t)N + 1);
     const unsigned long long* const log64 = reinterpret_cast<const unsigned long long*>(log);
 
+    const int every = look_every(R);
     c1.fetched = &comm->fetched[0][lane];
     c2.fetched = &comm->fetched[PROXY ? 1 : 0][lane];
 
@@ -1341,9 +1349,9 @@ __device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Handover
         }
         clk.tick(1);                                                 // patch, match (and the wait for the rows)
 
-        // (every fourth request: the log record asked for four requests ago has arrived and becomes usable, and the next
-        // one is asked for.  A replica's look-ahead needs a record every thirty requests or so, and holds eight.)
-        if ((r & 3) == 3) {
+        // (every fourth or eighth request: the log record asked for the time before has arrived and becomes usable, and the
+        // next one is asked for)
+        if ((r & every) == every) {
             const int first = comm->first[lane];
             c1.take_pending(*c1.fetched);
             comm->wanted[0][lane] = c1.ask(spare, latest, first);
