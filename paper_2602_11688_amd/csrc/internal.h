@@ -81,6 +81,10 @@ struct Plan {
     size_t total = 0;
     // [P] nearest-rank percentiles to be computed (device pointers), or null
     double *p95_ttft = nullptr, *p95_e2e = nullptr;
+    // the small inputs on the host, which the launch brings to d_rtt, d_params and d_scale (adjacent, in this order);
+    // keep_copies: they are the library's own and go away when the call returns
+    const double *h_rtt = nullptr, *h_params = nullptr, *h_scale = nullptr;
+    bool keep_copies = false;
 };
 
 // Online tuner of one launch (device pointers; see gorgo_online in gorgo.h).

@@ -7,8 +7,10 @@
 #include <hip/hip_runtime.h>
 #include <mutex>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <cstring>
 #include <string>
 
 #include "device_common.h"
@@ -20,11 +22,20 @@ namespace gorgo {
 
 namespace {
 
-// The last row but one of every replay's rows (the one no request touches) gets the cell value that is below any
-// cursor.
-__global__ void __launch_bounds__(256) fill_last_rows(int32_t* x, int32_t P, int64_t rows, int32_t R, int32_t v) {
+// What a launch needs before its replays start: the small inputs (round trip times, weights, time scales), which travel as
+// arguments of the kernel where they fit, and the cell value that is below any cursor in the last row but one of every
+// replay's rows (the one no request touches; rows: null for block tables).  (With three copies
+// from pageable host memory and a launch a ten-request replay takes 57.5 us, so 47.3; arguments also are taken when the
+// launch is enqueued, so nothing has to be waited for before the library's own arrays go away.)
+constexpr int SMALL_INPUTS = 448;      // doubles: the arguments of a launch are limited to 4 KiB
+struct SmallInputs {
+    double v[SMALL_INPUTS];
+};
+__global__ void __launch_bounds__(256) prepare_replays(SmallInputs in, int count, double* dst, int32_t* last, int32_t P, int64_t rows,
+                                                       int32_t R, int32_t v) {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < (size_t)P * R) x[((i / R) * (size_t)rows + (size_t)(rows - 2)) * R + i % R] = v;
+    if (i < (size_t)count) dst[i] = in.v[i];
+    if (last && i < (size_t)P * R) last[((i / R) * (size_t)rows + (size_t)(rows - 2)) * R + i % R] = v;
 }
 
 // ---- exact nearest-rank percentile: the k-th smallest of x[p][0..N) on the order-preserving integer image (key) of the
@@ -382,6 +393,36 @@ void set_event_marks(bool on) { g_marks_on = on; }
 
 namespace {
 
+// The small inputs on their way to the device, and the never-cached rows filled.  A stream under capture keeps the copies:
+// a graph reads the caller's arrays again at every replay.
+int prepare(const Plan& pl, double* d_small, int32_t* last, int64_t rows, hipStream_t s) {
+    const size_t R = (size_t)pl.R, P = (size_t)pl.P, count = R + 4 * P;
+    SmallInputs in;
+    bool as_arguments = count <= (size_t)SMALL_INPUTS;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (as_arguments && (hipStreamIsCapturing(s, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)) {
+        (void)hipGetLastError();
+        as_arguments = false;
+    }
+    int rc;
+    if (as_arguments) {
+        std::memcpy(in.v, pl.h_rtt, R * sizeof(double));
+        std::memcpy(in.v + R, pl.h_params, 3 * P * sizeof(double));
+        std::memcpy(in.v + R + 3 * P, pl.h_scale, P * sizeof(double));
+    } else {
+        if ((rc = copy_small_to_device(d_small, pl.h_rtt, R * sizeof(double), s))) return rc;
+        if ((rc = copy_small_to_device(d_small + R, pl.h_params, 3 * P * sizeof(double), s))) return rc;
+        if ((rc = copy_small_to_device(d_small + R + 3 * P, pl.h_scale, P * sizeof(double), s))) return rc;
+        if (pl.keep_copies && (rc = wait_for_copies(s))) return rc;
+    }
+    const size_t threads = std::max(as_arguments ? count : 0, last ? P * R : 0);
+    if (threads == 0) return GORGO_OK;
+    hipLaunchKernelGGL(prepare_replays, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, in, as_arguments ? (int)count : 0,
+                       d_small, last, pl.P, rows, pl.R, NEVER_CACHED);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? GORGO_OK : hip_fail(e, "launch prepare_replays");
+}
+
 // The segment-row kernel's instantiations: every mode with either replica model; imperfect proxy knowledge concerns the
 // cost model (fixed weights or tuned online) only.
 template <int MODE>
@@ -423,6 +464,7 @@ int launch_replay(const gorgo_trace* t, const Plan& pl, const double* d_rtt, con
                   const EngineLaunch* engine, const ProxyLaunch* proxy, unsigned long long* sections) {
     hipStream_t s = static_cast<hipStream_t>(stream);
     char* ws = static_cast<char*>(workspace);
+    int rc;
     g_marks.valid = false;
     if (g_marks_on) marks_ready();
     mark(0, s);
@@ -494,14 +536,10 @@ int launch_replay(const gorgo_trace* t, const Plan& pl, const double* d_rtt, con
                             : !policy || policy->policy == 0 ? MODE_COST_MODEL
                             : policy->policy == 1 ? MODE_LEAST_REQUEST
                             : policy->policy == 2 ? MODE_AFFINITY : MODE_RANDOM;
+    // (a row is written through before it is first read -- the request that brings a segment into a row slot resets the
+    // row -- so only the never-cached row needs a value beforehand)
+    if ((rc = prepare(pl, const_cast<double*>(d_rtt), segments ? a.last : nullptr, a.nseg, s))) return rc;
     if (segments) {
-        // (a row is written through before it is first read -- the request that brings a segment into a row slot
-        // resets the row -- so only the never-cached row needs a value beforehand)
-        if (pl.P > 0) {
-            hipLaunchKernelGGL(fill_last_rows, dim3((unsigned)(((size_t)pl.P * pl.R + 255) / 256)), dim3(256), 0, s, a.last,
-                               pl.P, a.nseg, pl.R, NEVER_CACHED);
-            if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "launch fill_last_rows");
-        }
         mark(1, s);
         if (pl.N > 0 || online) {      // (an empty trace still reports the tuner's initial state)
             if (mode == MODE_COST_MODEL && !engine && !proxy && !sections && pack_replays(pl, a.nseg)) {
