@@ -4,6 +4,7 @@
 // block hash ids).  Everything that does not depend on the candidate weights is done here once: hash ids
 // are renumbered densely (1 + order of first appearance), repeated ids inside one request are flagged, and
 // the trace is classified as chain-consistent or not.
+#include <algorithm>
 #include <cerrno>
 #include <cstdio>
 #include <cstring>
@@ -26,24 +27,34 @@ void clear_error() { g_err.clear(); }
 
 namespace {
 
-// Open-addressed int64 -> uint32 map (linear probing, grows by doubling); value 0 means empty.
+// What preprocessing knows of a key (a distinct block id; keys are numbered from 1 in order of first appearance).
+struct KeyInfo {
+    int64_t id = 0;
+    uint32_t parent = 0, pos = 0;    // predecessor and position it was first seen with
+    uint32_t next = 0;               // key that followed it last
+    uint32_t nchild = 0;             // distinct successors
+    int32_t seen_in = -1;            // last request that it was seen in
+    uint8_t ends = 0;                // some request ends here
+};
+
+// Open-addressed map from ids to keys: linear probing over the keys' numbers alone (0: empty), grows by doubling.
 class IdMap {
   public:
-    IdMap() { resize(1 << 12); }
-    // returns the dense key of id, assigning the next one on first sight
+    explicit IdMap(std::vector<KeyInfo>& keys) : keys_(keys), slot_((size_t)1 << 12, 0) {}
+    // the key of an id, the next one on first sight
     uint32_t get_or_add(int64_t id, bool* added) {
-        if ((count_ + 1) * 2 > cap_) resize(cap_ * 2);
-        size_t h = mix((uint64_t)id) & (cap_ - 1);
-        while (val_[h] != 0) {
-            if (key_[h] == id) { *added = false; return val_[h]; }
-            h = (h + 1) & (cap_ - 1);
+        if (keys_.size() * 2 > slot_.size()) grow();
+        size_t h = mix((uint64_t)id) & (slot_.size() - 1);
+        while (slot_[h] != 0) {
+            if (keys_[slot_[h]].id == id) { *added = false; return slot_[h]; }
+            h = (h + 1) & (slot_.size() - 1);
         }
-        key_[h] = id;
-        val_[h] = (uint32_t)(++count_);
+        slot_[h] = (uint32_t)keys_.size();
+        keys_.emplace_back();
+        keys_.back().id = id;
         *added = true;
-        return val_[h];
+        return slot_[h];
     }
-    size_t size() const { return count_; }
 
   private:
     static uint64_t mix(uint64_t x) {
@@ -51,26 +62,16 @@ class IdMap {
         x ^= x >> 27; x *= 0x94d049bb133111ebULL;
         return x ^ (x >> 31);
     }
-    void resize(size_t ncap) {
-        std::vector<int64_t> ok;
-        std::vector<uint32_t> ov;
-        ok.swap(key_);
-        ov.swap(val_);
-        key_.assign(ncap, 0);
-        val_.assign(ncap, 0);
-        size_t ocap = cap_;
-        cap_ = ncap;
-        for (size_t i = 0; i < ocap; ++i) {
-            if (!ov[i]) continue;
-            size_t h = mix((uint64_t)ok[i]) & (cap_ - 1);
-            while (val_[h] != 0) h = (h + 1) & (cap_ - 1);
-            key_[h] = ok[i];
-            val_[h] = ov[i];
+    void grow() {
+        slot_.assign(slot_.size() * 2, 0);
+        for (size_t k = 1; k < keys_.size(); ++k) {
+            size_t h = mix((uint64_t)keys_[k].id) & (slot_.size() - 1);
+            while (slot_[h] != 0) h = (h + 1) & (slot_.size() - 1);
+            slot_[h] = (uint32_t)k;
         }
     }
-    std::vector<int64_t> key_;
-    std::vector<uint32_t> val_;
-    size_t cap_ = 0, count_ = 0;
+    std::vector<KeyInfo>& keys_;
+    std::vector<uint32_t> slot_;
 };
 
 // Fills key/first/statistics from the raw ids.  Returns 0 or an error code.
@@ -80,19 +81,10 @@ int preprocess(gorgo_trace* t, const int64_t* hash_ids) {
     t->total_blocks = total;
     t->key.resize((size_t)total);
     t->first.resize((size_t)total);
-    IdMap map;
-    // for chain consistency: the (predecessor key, position) each key was first seen with
-    std::vector<uint32_t> parent;
-    std::vector<uint32_t> pos;
-    parent.push_back(0);
-    pos.push_back(0);
-    // per-request duplicate detection: last request index in which a key was seen
-    std::vector<int64_t> seen_in;
-    seen_in.push_back(-1);
-    std::vector<uint32_t> nchild;    // distinct successors of a key
-    std::vector<uint8_t> ends;       // some request ends at this key
-    nchild.push_back(0);
-    ends.push_back(0);
+    std::vector<KeyInfo> keys;
+    keys.reserve((size_t)std::min<int64_t>(total, 1 << 20) + 1);
+    keys.emplace_back();             // (key 0 stands before a request's first block)
+    IdMap map(keys);
     bool consistent = true;
     int32_t max_blocks = 0, max_distinct = 0;
     for (int64_t r = 0; r < N; ++r) {
@@ -102,33 +94,38 @@ int preprocess(gorgo_trace* t, const int64_t* hash_ids) {
         int32_t distinct = 0;
         uint32_t prev = 0;
         for (int64_t k = 0; k < n; ++k) {
+            // Prompts repeat each other's beginnings: an id is mostly the one that followed its predecessor the last time,
+            // whose entry is the next one in memory, and needs no look-up.
+            const int64_t id = hash_ids[b + k];
             bool added = false;
-            uint32_t key = map.get_or_add(hash_ids[b + k], &added);
-            if (map.size() >= 0xFFFFFFF0ull) return fail(GORGO_ERR_INVALID_ARG, "too many distinct hash ids");
+            uint32_t key = prev ? keys[prev].next : 0;
+            if (key == 0 || keys[key].id != id) {
+                key = map.get_or_add(id, &added);
+                if (keys.size() > 0xFFFFFFF0ull) return fail(GORGO_ERR_INVALID_ARG, "too many distinct hash ids");
+                if (prev) keys[prev].next = key;
+            }
+            KeyInfo& of = keys[key];
             if (added) {
-                parent.push_back(prev);
-                pos.push_back((uint32_t)k);
-                seen_in.push_back(-1);
-                nchild.push_back(0);
-                ends.push_back(0);
-                if (prev) ++nchild[prev];
-            } else if (parent[key] != prev || pos[key] != (uint32_t)k) {
+                of.parent = prev;
+                of.pos = (uint32_t)k;
+                if (prev) ++keys[prev].nchild;
+            } else if (of.parent != prev || of.pos != (uint32_t)k) {
                 consistent = false;
             }
-            const bool dup = seen_in[key] == r;
+            const bool dup = of.seen_in == (int32_t)r;
             if (dup) consistent = false;
             else ++distinct;
-            seen_in[key] = r;
+            of.seen_in = (int32_t)r;
             t->key[(size_t)(b + k)] = key;
             t->first[(size_t)(b + k)] = dup ? 0 : 1;
             prev = key;
         }
-        if (prev) ends[prev] = 1;
+        if (prev) keys[prev].ends = 1;
         if (distinct > max_distinct) max_distinct = distinct;
     }
     t->max_blocks = max_blocks;
     t->max_distinct = max_distinct;
-    t->unique_ids = (int64_t)map.size();
+    t->unique_ids = (int64_t)keys.size() - 1;
     t->chain_consistent = consistent;
     t->seg_off.clear();
     t->seg.clear();
@@ -140,12 +137,12 @@ int preprocess(gorgo_trace* t, const int64_t* hash_ids) {
     // forest into segments -- maximal runs of keys with a single successor and no request ending inside --
     // so that every request is a whole number of segments and all blocks of a segment are always touched
     // together.  Keys are numbered in order of first appearance, so a predecessor precedes its successors.
-    const size_t U = map.size();
+    const size_t U = keys.size() - 1;
     std::vector<int32_t> seg_of(U + 1, 0);
     int64_t nseg = 0;
     for (size_t k = 1; k <= U; ++k) {
-        const uint32_t par = parent[k];
-        if (par == 0 || nchild[par] > 1 || ends[par]) seg_of[k] = (int32_t)(nseg++);
+        const uint32_t par = keys[k].parent;
+        if (par == 0 || keys[par].nchild > 1 || keys[par].ends) seg_of[k] = (int32_t)(nseg++);
         else seg_of[k] = seg_of[par];
         if (nseg >= 0x7FFFFFF0) return fail(GORGO_ERR_INVALID_ARG, "too many segments");
     }
