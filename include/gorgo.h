@@ -99,16 +99,13 @@ typedef struct gorgo_model {
  *     chain-consistent and its requests average at most 16 segments.  Size the workspace with the same options
  *     as the evaluation.
  *   replay_packing: with at most 32 replicas, at most 16 slots per replica and an even number of replays,
- *     gorgo_eval_population and gorgo_es_step can run two replays per pair of wavefronts of the segment-row kernel
+ *     gorgo_eval_population and gorgo_es_step can run two replays per workgroup of the segment-row kernel
  *     (a replay keeps one lane per replica, so half of a 64-lane wavefront idles otherwise).  A replay is a serial
  *     chain, so this only pays when the replays would not all be resident on the GPU at once (more than about
- *     1,024 of them) but the pairs would: 2 (default) packs exactly then, 1 whenever the shape allows, 0 never.
- *   handover_poll_limit: how many times a wavefront of the packed segment-row replay polls for its partner's
- *     word before the replay is given up (default 2^24, about a second; a replay that is given up ends at once,
- *     every latency of it becomes NaN, so does its p95, and gorgo_es_step fails with GORGO_ERR_NONFINITE).  It
- *     never happens unless the library is wrong; the setting exists so that this path can be exercised: with 0
- *     every replay whose partner is not ready at the first poll is given up.  (The unpacked kernel's wavefronts
- *     meet at workgroup barriers and do not poll.)
+ *     1,280 of them) but the pairs would: 2 (default) packs exactly then, 1 whenever the shape allows, 0 never.
+ *   handover_poll_limit: how many times wavefronts that hand over through polled words poll before a replay is
+ *     given up (default 2^24; must be >= 0).  No kernel polls: the wavefronts of a replay meet at workgroup barriers,
+ *     packed or not, so the value has no effect and no replay is given up.
  *   table_factor_percent: the open-addressed cache tables of the block-table formulation get at least
  *     ceil(factor/100 * (cache_blocks + max blocks of a request)) slots, rounded up to a power of two
  *     (default 200, 110..1600). */
@@ -374,14 +371,14 @@ int gorgo_last_eval_kernel_ms(double* fill_ms, double* replay_ms, double* select
 /* Measurement aid: gorgo_eval_population run by an instantiation of the segment-row kernel that reads the GPU's
  * cycle counter between the sections of its request loop and adds up, per replay and wavefront, the cycles each
  * section took (same results; slower by the clock reads, each of which also waits for the wavefront's
- * outstanding LDS accesses).  sections: DEVICE [P][3][GORGO_SECTIONS] uint64, [p][0] the cache wavefront
- * (0 waiting for the queue terms, 1 match incl. the wait for its rows, 2 log records and the next rows, 3 score,
- * minimum and announcement, 4 waiting at the second meeting point, 5 ownership, 6 stores, log and eviction,
- * 7 patch and loop; then counts, not cycles: 8 log records fetched on the spot by the eviction walk, 9 cursor
- * advances, 10 log records dropped because they own nothing, 11 ownership walks), [p][1] the queue wavefront (0 retire and publish, 1 waiting at the first meeting point,
- * 2 retiring ahead, 3 nothing, 4 waiting for the choice, 5 service and outputs, 6 batch turnover), [p][2] the
- * front-end wavefront (0 the descriptor of the request after next, 1 and 2 waiting at the two meeting points, 3 the
- * references of the request after that, loaded between the meeting points).  Needs the
+ * outstanding LDS accesses).  sections: DEVICE [P][3][GORGO_SECTIONS] uint64, [p][0] the deciding wavefront
+ * (0 waiting at the meeting X, 1 patching and match, 2 log records taken and asked for, 3 score, minimum and
+ * announcement, 4 waiting at the meeting Y, 5 ownership, cursor, taking the next request, 6 eviction past the
+ * cursor's record; then counts, not cycles: 8 log records fetched on the spot by the eviction walk, 9 cursor
+ * advances, 10 log records dropped because they own nothing, 11 ownership walks), [p][1] the queue wavefront (0 times
+ * and lengths, 1 waiting at X, 2 retiring, 5 outputs and tuner, 6 batch turnover, 9 choice and service), [p][2] the
+ * front-end wavefront (0 descriptors and row cells, 1 waiting) and the book-keeping wavefront (2 stores, 3 waiting at
+ * X).  Needs the
  * segment formulation without packing; everything else as gorgo_eval_population. */
 #define GORGO_SECTIONS 12
 int gorgo_eval_population_sections(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* options, const double* rtt_ms,

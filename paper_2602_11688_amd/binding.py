@@ -51,7 +51,7 @@ class _Proxy(C.Structure):
 class Options(C.Structure):
     """gorgo_options: how an evaluation is carried out (no result depends on it), passed to the library with every
     call.  replay_path 0 automatic / 1 hashed block tables / 2 dense segment rows; replay_packing 0 never / 1 whenever
-    the shape allows / 2 automatic; handover_poll_limit polls before a packed replay is given up;
+    the shape allows / 2 automatic; handover_poll_limit has no effect (no kernel polls);
     table_factor_percent 110..1600."""
     _fields_ = [("replay_path", C.c_int32), ("replay_packing", C.c_int32), ("handover_poll_limit", C.c_int32),
                 ("table_factor_percent", C.c_int32)]
@@ -253,7 +253,7 @@ def replay_packing(trace: "Trace", model: "Model", P: int, options: Optional[Opt
 
 
 def set_handover_poll_limit(polls: int):
-    """Polls of a hand-over word before a packed replay is given up (default 2^24); for tests of that path."""
+    """Sets options.handover_poll_limit (default 2^24), which has no effect: no kernel polls."""
     _set_default("handover_poll_limit", polls, 0, 2**31 - 1, "handover_poll_limit")
 
 
@@ -310,7 +310,7 @@ def eval_population(trace: Trace, model: Model, rtt_ms, params, scale, *, per_re
                     p95: bool = True, workspace=None, stream=None, device="cuda:0", sections: bool = False, options: Optional[Options] = None) -> EvalResult:
     """gorgo_eval_population with torch-allocated outputs.  Returns device tensors; asynchronous on `stream`
     (default: torch's current stream).  sections=True runs gorgo_eval_population_sections instead and adds
-    `sections` [P, 3, 12] (cycles per section of the request loop: cache, queue and front-end wavefront) to the result."""
+    `sections` [P, 3, 12] (cycles per section of the request loop: deciding, queue, front-end and book-keeping wavefront) to the result."""
     import torch
     rtt = _np(rtt_ms, np.float64)
     par = _np(params, np.float64)
