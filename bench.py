@@ -228,7 +228,7 @@ def main():
     ap.add_argument("--path", type=int, default=0, help="0 auto, 1 hashed block tables, 2 segment rows (experiments only)")
     ap.add_argument("--sections", action="store_true",
                     help="after the timed region, launch the kernel's timed instantiation once (it reads the clock at marks "
-                         "in each of its three wavefronts) and print the per-section cycle budget to stderr")
+                         "in each of its four wavefronts) and print the per-section cycle budget to stderr")
     ap.add_argument("--policies", action="store_true",
                     help="also replay the trace once under each routing policy of the paper's comparison (cost model with "
                          "the tuner's weights, its special cases, least-request, session affinity, random) and report "

@@ -44,7 +44,7 @@ struct BlockArgs {
     const uint8_t* first;    // [T] 1 where the key occurs for the first time within its request
     Slot* tables;            // [P][R][cap]
     Slot* spare;             // [P][cap] scratch of the compaction
-    uint8_t* routed;         // [P][N] the cache wavefront's log of choices (what its eviction cursors walk)
+    uint8_t* routed;         // [P][N] the updating wavefront's log of choices (what its eviction cursors walk)
     int64_t cap;             // slots per table, a power of two
     int32_t cap_log2;
 };
