@@ -71,7 +71,6 @@ int make_plan(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* o
     int orc = take_options(options, &opt);
     if (orc) return orc;
     pl->packing = opt.replay_packing;
-    pl->poll_limit = opt.handover_poll_limit;
     pl->P = P;
     pl->R = m->R;
     pl->B = m->batch;

@@ -75,7 +75,6 @@ struct Plan {
     int32_t block_tokens = 0;
     double a_pf = 0, a_dec = 0;
     int32_t packing = 2;             // gorgo_options::replay_packing of the call
-    int32_t poll_limit = 1 << 24;    // gorgo_options::handover_poll_limit of the call
     // workspace carve-up (byte offsets from the workspace base)
     size_t off_tables = 0, off_spare = 0, off_rec = 0, off_route = 0, off_ttft = 0, off_e2e = 0, off_small = 0;
     size_t total = 0;
