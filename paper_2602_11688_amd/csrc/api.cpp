@@ -333,6 +333,7 @@ int evaluate(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* op
     pol.policy = policy;
     if (policy == GORGO_POLICY_RANDOM) {
         if ((rc = copy_small_to_device(d_seeds, seeds, sizeof(uint64_t) * (size_t)P, hip_stream))) return rc;
+        if ((rc = wait_for_copies(hip_stream))) return rc;       // (the caller's array may go away when this returns)
         pol.seeds = d_seeds;
     }
     pl.h_rtt = rtt_ms;

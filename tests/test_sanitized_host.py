@@ -1,8 +1,9 @@
 """The host side of the library (trace loading, evolution-strategy arithmetic, argument and option checks, workspace
 planning) and the CPU oracle, each built for the CPU with AddressSanitizer and UndefinedBehaviorSanitizer and run on
-seeded inputs: a mutation fuzz of the JSON-lines loader followed by a walk over the host-side entry points, and the
-oracle's replays on small traces in awkward shapes.  The GPU kernels are not part of these builds (GPU sanitizers are
-not available to this project): the library's device operations are replaced by stubs that fail."""
+seeded inputs: a mutation fuzz of the JSON-lines loader followed by a walk over the host-side entry points, the copies
+of what the caller's arrays hold, and the oracle's replays on small traces in awkward shapes.  The GPU kernels are not
+part of these builds (GPU sanitizers are not available to this project): the library's device operations are replaced by
+stubs that fail, or that put a copy off for as long as an asynchronous one may take."""
 import os
 import shutil
 import subprocess
@@ -46,6 +47,13 @@ def host_fuzz(tmp_path_factory):
 def test_host_side_survives_a_mutation_fuzz_under_asan_and_ubsan(host_fuzz, tmp_path, seed):
     out = _run([host_fuzz, str(seed), "700", str(tmp_path / "fuzz.jsonl")])
     assert "700 iterations" in out
+
+
+def test_copies_are_taken_before_the_callers_arrays_go_away(tmp_path):
+    exe = str(tmp_path / "host_copies")
+    _build(exe, [os.path.join(CSRC, f) for f in ("trace.cpp", "es.cpp", "api.cpp")] + [os.path.join(SAN, "host_copies.cpp")],
+           [os.path.join(ROOT, "include"), CSRC])
+    assert "10 calls" in _run([exe])
 
 
 def test_oracle_replays_run_clean_under_asan_and_ubsan(tmp_path):
