@@ -110,20 +110,21 @@ __device__ __forceinline__ unsigned long long ballot(bool c) { return __builtin_
 // one 1,150 of 0.65 us, all of it one request behind the decisions.)
 // The load signal itself lives with the cache side, which adds what it dispatches; what completes is subtracted here
 // with LDS atomics (integers below 2^53 in doubles: exact in any order).
+// These words decide how many replays a CU holds.  A slot's state is therefore told from the completion times and the
+// youngest request alone -- none in flight, one, two, a longer list -- and there is no count of requests.
 struct SlotQueues {
     struct Slot {
         double free_at;  // time the service slot becomes free
         double h_done;   // completion time of the oldest in-flight request (+inf: none)
-        double s_done;   // ... of the second oldest
+        double s_done;   // ... of the second oldest (+inf: none; finite, not yet valid, while its record is on its way)
         int32_t h_tok;   // what the oldest takes from the load signal when it completes
-        int32_t depth;   // requests in flight on the slot
         int32_t s_tok;   // what the second oldest takes from the load signal
         int32_t s_next;  // request after the second oldest (-1: none)
+        int32_t tail;    // youngest request of a list of three or more (-1: at most two)
     };
     Slot* slot;          // (40 bytes apart: 16 neighbouring slots lie in different LDS banks)
-    int32_t* tail;       // [slots] youngest request of a list of three or more
     uint32_t* kv;        // [slots] engine model: KV tokens held by the request that frees the slot at free_at
-    int B, passes;       // passes: sets of 64 slots, a multiple of four
+    int B, passes;       // passes: sets of 64 slots, at least four
     unsigned inv_b;      // replica of slot g = g * inv_b >> 16 (exact for g < 1,024 + 256, B <= 64)
     unsigned long long lanes;  // lanes that hold a slot of the replica in hand
     double last_start;   // engine model: admission time of the latest request of replica = lane
@@ -135,9 +136,12 @@ struct SlotQueues {
     int f_slot, f_tok, f_next;
     double f_done;
 
-    static __host__ __device__ int slots(int R, int B) { return (R * B + 4 * WAVE - 1) / (4 * WAVE) * (4 * WAVE); }
-    static __host__ __device__ size_t bytes(int R, int B, bool engine) {
-        return (size_t)slots(R, B) * (sizeof(Slot) + 4 + (engine ? 4 : 0));
+    // (Four sets at least: with only as many as there are, the look at them in a loop, 8 replicas of 8 slots took 3 % longer.)
+    static __host__ __device__ constexpr int slots(int R, int B) {
+        return R * B <= 4 * WAVE ? 4 * WAVE : (R * B + WAVE - 1) / WAVE * WAVE;
+    }
+    static __host__ __device__ constexpr size_t bytes(int R, int B, bool engine) {
+        return (size_t)slots(R, B) * (sizeof(Slot) + (engine ? 4 : 0));
     }
 
     __device__ __forceinline__ void init(unsigned char* lds, int R, int B_, bool engine, int lane) {
@@ -147,11 +151,9 @@ struct SlotQueues {
         inv_b = (65536u + (unsigned)B - 1u) / (unsigned)B;
         lanes = B >= WAVE ? ~0ull : (1ull << B) - 1;
         slot = reinterpret_cast<Slot*>(lds);
-        tail = reinterpret_cast<int32_t*>(slot + n);
-        kv = reinterpret_cast<uint32_t*>(tail + n);
+        kv = reinterpret_cast<uint32_t*>(slot + n);
         for (int g = lane; g < n; g += WAVE) {
-            slot[g] = Slot{0.0, INFINITY, INFINITY, 0, 0, 0, -1};
-            tail[g] = -1;
+            slot[g] = Slot{0.0, INFINITY, INFINITY, 0, 0, -1, -1};
             if (engine) kv[g] = 0;
         }
         last_start = 0.0;
@@ -171,16 +173,21 @@ struct SlotQueues {
         f_slot = -1;
     }
 
-    // Bit p: the oldest request of slot p * 64 + lane has completed by t.
+    // Bit p: the oldest request of slot p * 64 + lane has completed by t.  Four sets are looked at together; where there are
+    // fewer left the last one stands in for them, and counts once.
     __device__ __forceinline__ unsigned due(double t, int lane) const {
-        auto four = [&](int p) {
-            const Slot* const h = &slot[p * WAVE + lane];
-            const double d0 = h[0].h_done, d1 = h[WAVE].h_done, d2 = h[2 * WAVE].h_done, d3 = h[3 * WAVE].h_done;
+        const Slot* const h = &slot[lane];
+        auto four = [&](int p0, int p1, int p2, int p3) {
+            const double d0 = h[p0 * WAVE].h_done, d1 = h[p1 * WAVE].h_done, d2 = h[p2 * WAVE].h_done, d3 = h[p3 * WAVE].h_done;
             return (d0 <= t ? 1u : 0u) | (d1 <= t ? 2u : 0u) | (d2 <= t ? 4u : 0u) | (d3 <= t ? 8u : 0u);
         };
-        unsigned bits = four(0);
-        if (passes > 4)                   // (more than 256 slots: rare)
-            for (int p = 4; p < passes; p += 4) bits |= four(p) << p;
+        if (passes == 4) return four(0, 1, 2, 3);
+        unsigned bits = four(0, 1, 2, 3);         // (more than 256 slots: rare)
+        int p = 4;
+        for (; p + 4 <= passes; p += 4) bits |= four(p, p + 1, p + 2, p + 3) << p;
+        const int last = passes - 1;
+        auto upto = [&](int k) { return k < last ? k : last; };
+        if (p < passes) bits |= (four(p, upto(p + 1), upto(p + 2), last) & ((1u << (passes - p)) - 1)) << p;
         return bits;
     }
     // Drop requests whose completion event has reached the proxy (done <= t): the oldest of the slots in `due` and
@@ -194,15 +201,16 @@ struct SlotQueues {
             if (due != 0) {
                 const int g = __builtin_ctz(due) * WAVE + lane;
                 Slot* const l = &slot[g];
-                const int h_tok = l->h_tok, d = l->depth, up_tok = l->s_tok, x = l->s_next;
+                const int h_tok = l->h_tok, up_tok = l->s_tok, x = l->s_next, tail = l->tail;
                 const double up = l->s_done;
+                const bool deep = tail >= 0;
                 __hip_atomic_fetch_add(&gone[(unsigned)g * inv_b >> 16], -(double)h_tok, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                const bool more = d > 1;
-                l->h_done = more ? up : INFINITY;
+                l->h_done = up;
                 l->h_tok = up_tok;
-                l->depth = d - 1;
-                const bool again = more && up <= t;             // the new head has completed too
-                if (d >= 3) {
+                l->s_done = deep ? up : INFINITY;
+                l->tail = x == tail ? -1 : tail;
+                const bool again = up <= t;                     // the new head has completed too
+                if (deep) {
                     // the request that moves into second position (x) comes from memory
                     if (DEFER && !again && f_slot < 0) {
                         f_slot = g;
@@ -226,18 +234,19 @@ struct SlotQueues {
     // The completion times along a slot's in-flight list increase as long as a replica's round trip time is
     // constant.  When it changes between dispatches (probe epochs), a request can complete at the proxy before one
     // dispatched earlier on the same slot; the list is then kept sorted by completion time instead: this inserts
-    // request r (completion `done`, `tok` tokens) into the list of slot s, which holds d >= 1 requests the last of which
+    // request r (completion `done`, `tok` tokens) into the list of slot s, which holds at least one, the last of which
     // completes after `done`.  An element that has to leave the two LDS positions moves into the record of request r,
-    // which r itself does not need then.  tail[s] stays the record of the last element (of three or more).
-    __device__ __forceinline__ void insert_sorted(int s, int d, int r, double done, int32_t tok, Rec* rec) {
-        if (done < slot[s].h_done || (d >= 2 && done < slot[s].s_done)) {
+    // which r itself does not need then.  `tail` stays the record of the last element (of three or more).
+    __device__ __forceinline__ void insert_sorted(int s, int r, double done, int32_t tok, Rec* rec) {
+        const bool two = slot[s].s_done < INFINITY, deep = slot[s].tail >= 0;
+        if (done < slot[s].h_done || (two && done < slot[s].s_done)) {
             // r goes into LDS; the element in second position, if any, moves to global memory behind it
-            if (d >= 2) {
+            if (two) {
                 st(&rec[r].done, slot[s].s_done);
                 st(&rec[r].tokens, slot[s].s_tok);
-                st(&rec[r].next, d >= 3 ? slot[s].s_next : (int32_t)-1);
+                st(&rec[r].next, deep ? slot[s].s_next : (int32_t)-1);
                 slot[s].s_next = r;
-                if (d == 2) tail[s] = r;
+                if (!deep) slot[s].tail = r;
             } else {
                 slot[s].s_next = -1;
             }
@@ -251,10 +260,10 @@ struct SlotQueues {
                 slot[s].s_tok = tok;
             }
         } else {
-            // r goes between two elements further down (d >= 3): walk to the last one that completes no later
+            // r goes between two elements further down: walk to the last one that completes no later
             int32_t prev = -1;               // -1: the second position
             int32_t x = slot[s].s_next;
-            for (int steps = 0; steps < d && x >= 0 && !(done < ld(&rec[x].done)); ++steps) {
+            for (int steps = 0; steps < r && x >= 0 && !(done < ld(&rec[x].done)); ++steps) {
                 prev = x;
                 x = ld(&rec[x].next);
             }
@@ -264,18 +273,19 @@ struct SlotQueues {
             if (prev < 0) slot[s].s_next = r;
             else st(&rec[prev].next, (int32_t)r);
         }
-        slot[s].depth = d + 1;
     }
 
-    // Request r joins the list of slot s, which holds d >= 1 requests (called by one lane).  REORDER: round trip times
+    // Request r joins the list of slot s, which holds at least one (called by one lane).  REORDER: round trip times
     // change.
     template <bool REORDER>
-    __device__ __forceinline__ void queue_behind(int s, int d, int r, double done, int weight, Rec* rec) {
-        if (REORDER && done < (d == 1 ? slot[s].h_done : (d == 2 ? slot[s].s_done : ld(&rec[tail[s]].done)))) {
-            insert_sorted(s, d, r, done, weight, rec);
+    __device__ __forceinline__ void queue_behind(int s, int r, double done, int weight, Rec* rec) {
+        const bool two = slot[s].s_done < INFINITY;
+        const int32_t tail = slot[s].tail;
+        if (REORDER && done < (!two ? slot[s].h_done : (tail < 0 ? slot[s].s_done : ld(&rec[tail].done)))) {
+            insert_sorted(s, r, done, weight, rec);
             return;
         }
-        if (d == 1) {
+        if (!two) {
             slot[s].s_done = done;
             slot[s].s_tok = weight;
             slot[s].s_next = -1;
@@ -284,27 +294,26 @@ struct SlotQueues {
             st(&rec[r].done, done);
             st(&rec[r].next, (int32_t)-1);
             st(&rec[r].tokens, (int32_t)weight);
-            if (d == 2) slot[s].s_next = r;      // (behind the second oldest, whose record may still be on its way)
-            else st(&rec[tail[s]].next, (int32_t)r);
-            tail[s] = r;
+            if (tail < 0) slot[s].s_next = r;    // (behind the second oldest, whose record may still be on its way)
+            else st(&rec[tail].next, (int32_t)r);
+            slot[s].tail = r;
         }
-        slot[s].depth = d + 1;
     }
-    // Request r takes slot s, the k-th of its replica, which holds d requests in the lane concerned; it ends at `end`.
+    // Request r takes slot s, the k-th of its replica, in the lane concerned; it ends at `end`.  none: the lanes whose slot
+    // has nothing in flight.
     template <bool REORDER>
-    __device__ __forceinline__ void take_slot(int s, int k, int d, int r, double end, double done, int weight, Rec* rec) {
+    __device__ __forceinline__ void take_slot(int s, int k, unsigned long long none, int r, double end, double done, int weight, Rec* rec) {
         const unsigned long long it = 1ull << k;
-        const unsigned long long empty = it & ballot(d == 0);
+        const unsigned long long empty = it & none;
         if (__builtin_amdgcn_inverse_ballot_w64(empty)) {
             slot[s].free_at = end;
             slot[s].h_done = done;
             slot[s].h_tok = weight;
-            slot[s].depth = 1;
         }
         if (empty == 0) {
             if (__builtin_amdgcn_inverse_ballot_w64(it)) {
                 slot[s].free_at = end;
-                queue_behind<REORDER>(s, d, r, done, weight, rec);
+                queue_behind<REORDER>(s, r, done, weight, rec);
             }
         }
     }
@@ -322,13 +331,13 @@ struct SlotQueues {
                                           int lane, double* ttft_out, double* e2e_out, double until, unsigned& due) {
         const int s = best * B + (lane < B ? lane : B - 1);
         const double f = slot[s].free_at;
-        const int d = slot[s].depth;
+        const unsigned long long none = ballot(slot[s].h_done == INFINITY);
         const double arrive = t + half;
         double start = arrive;
         int k;
         const unsigned long long ready = ballot(f <= (REORDER ? t : arrive)) & lanes;
         if (ready != 0) {
-            const unsigned long long idle = ready & ballot(d == 0);
+            const unsigned long long idle = ready & none;
             k = __builtin_ctzll(idle != 0 ? idle : ready);
         } else {
             // (times are >= 0: the order of the bits is the order of the values; mostly one slot alone holds the smallest
@@ -354,7 +363,7 @@ struct SlotQueues {
         const int at = best * B + k;
         const unsigned bit = done <= until ? 1u << (at / WAVE) : 0u;
         due |= lane == (at & (WAVE - 1)) ? bit : 0u;
-        take_slot<REORDER>(s, k, d, r, end, done, weight, rec);
+        take_slot<REORDER>(s, k, none, r, end, done, weight, rec);
     }
 
     // Service of request r on replica `best` under the engine model of a replica (continuous batching, Sec. 2.2;
@@ -377,7 +386,7 @@ struct SlotQueues {
         const int s = best * B + (lane < B ? lane : B - 1);
         const double f = slot[s].free_at;
         const unsigned h = kv[s];
-        const int d = slot[s].depth;
+        const unsigned long long none = ballot(slot[s].h_done == INFINITY);
         int n, k;
         for (int scans = 0;; ++scans) {
             const bool late = f > start;
@@ -412,7 +421,7 @@ struct SlotQueues {
         const unsigned bit = done <= until ? 1u << (at / WAVE) : 0u;
         due |= lane == (at & (WAVE - 1)) ? bit : 0u;
         if (lane == k) kv[s] = tokens;           // two counts below 2^31 each
-        take_slot<REORDER>(s, k, d, r, end, done, weight, rec);
+        take_slot<REORDER>(s, k, none, r, end, done, weight, rec);
     }
 };
 

@@ -199,7 +199,7 @@ struct Blocks {
 // Deciding wavefront of a replay over block tables.  Lane = replica for the first-block probe, the scores and the
 // minimum; lane = block of the request for the prefix match.
 template <int MODE, bool ENGINE, bool PROXY>
-__device__ __forceinline__ void block_decide_wave(const BlockArgs& b, int p, int lane, const LruState& lru, Handover<PROXY>* comm) {
+__device__ __forceinline__ void block_decide_wave(const BlockArgs& b, int p, int lane, const LruState& lru, QueueHandover<PROXY>* comm) {
     constexpr bool ONLINE = MODE == MODE_ONLINE;
     constexpr bool SCORED = MODE == MODE_COST_MODEL || MODE == MODE_ONLINE;
     const SegArgs& a = b.q;
@@ -222,7 +222,7 @@ __device__ __forceinline__ void block_decide_wave(const BlockArgs& b, int p, int
     double w_prefill = a.params[3 * (size_t)p + 1];
     double w_queue = a.params[3 * (size_t)p + 2];
     double q = 0.0;                                               // load signal of replica = lane
-    const double my_rtt = !PROXY && in ? a.rtt[lane] : 0.0;       // (proxy variants: comes with the queue terms)
+    double my_rtt = !PROXY && in ? a.rtt[lane] : 0.0;             // (proxy variants: comes from the queue wavefront)
     const uint64_t seed = MODE == MODE_RANDOM ? a.seeds[p] : 0;
     const Slot* const tables = b.tables + (size_t)p * R * b.cap;
 
@@ -335,11 +335,11 @@ __device__ __forceinline__ void block_decide_wave(const BlockArgs& b, int p, int
         // ---- score (Eq. 3), lowest-index minimum; the load signal is kept here, what left it comes from the queue wavefront
         q += comm->gone[r & 1][lane];
         comm->gone[r & 1][lane] = 0.0;
-        const double rtt_now = PROXY ? comm->rtt[r & 3][PROXY ? lane : 0] : my_rtt;
+        if constexpr (PROXY) my_rtt = comm->rtt[r & 1][lane];
         double my_score;
         if (SCORED) {
             const double pf = a.a_pf * (double)my_u_seen;
-            const double s_rtt = w_rtt * rtt_now;
+            const double s_rtt = w_rtt * my_rtt;
             const double s_pf = w_prefill * pf;
             const double rtt_and_prefill = s_rtt + s_pf;
             const double qd = a.a_pf * q;
@@ -356,8 +356,8 @@ __device__ __forceinline__ void block_decide_wave(const BlockArgs& b, int p, int
         const unsigned u_best = (unsigned)__builtin_amdgcn_readlane(my_u, best);
         q += lane == best ? (MODE == MODE_LEAST_REQUEST ? 1.0 : (double)L) : 0.0;
         if (lane == 0) {
-            comm->choice[r & 1][best] = Choice{ENGINE || PROXY ? (double)(int)u_best : a.a_pf * (double)(int)u_best, -2, (unsigned)m_best};
-            if constexpr (PROXY) comm->seen[r & 1][best] = (uint16_t)seen_best;
+            if constexpr (PROXY) comm->choice[r & 1][best] = Choice<true>{(int)u_best, seen_best, -2, (unsigned)m_best};
+            else comm->choice[r & 1][best] = Choice<false>{ENGINE ? (double)(int)u_best : a.a_pf * (double)(int)u_best, -2, (unsigned)m_best};
             comm->best[r & 1][0] = best;
         }
         meet(true);                                                  // X(r): the choice is there
@@ -381,7 +381,7 @@ __device__ __forceinline__ void block_decide_wave(const BlockArgs& b, int p, int
 
 // Updating wavefront: between X(r) and Y(r) it brings the chosen replica up to date.  Lane = block.
 template <bool PROXY>
-__device__ __forceinline__ void block_update_wave(const BlockArgs& b, int p, int lane, const LruState& lru, Handover<PROXY>* comm) {
+__device__ __forceinline__ void block_update_wave(const BlockArgs& b, int p, int lane, const LruState& lru, QueueHandover<PROXY>* comm) {
     const SegArgs& a = b.q;
     const int64_t N = a.N;
     const uint64_t mask = (uint64_t)b.cap - 1;
@@ -562,9 +562,9 @@ __device__ __forceinline__ void block_update_wave(const BlockArgs& b, int p, int
 }
 
 template <int MODE, bool ENGINE, bool PROXY>
-__global__ void __launch_bounds__(BLOCK_THREADS, PROXY ? 3 : 4) replay_blocks_kernel(BlockArgs b) {
+__global__ void __launch_bounds__(BLOCK_THREADS, 4) replay_blocks_kernel(BlockArgs b) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    __shared__ __align__(16) Handover<PROXY> comm;
+    __shared__ QueueHandover<PROXY> comm;
     const int lane = threadIdx.x & (WAVE - 1);
     const int p = blockIdx.x;
     if (threadIdx.x >= 2 * WAVE) {

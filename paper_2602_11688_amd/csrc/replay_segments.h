@@ -44,8 +44,6 @@
 // them, 165.6 ms so (0.65 us, some 1,400 cycles a request).  The deciding and the queue wavefront now have chains of
 // the same length, each is the last to arrive about half of the time; 2 replays take 0.56 us.
 #pragma once
-#include <type_traits>
-
 #include "device_common.h"
 #include "internal.h"
 
@@ -285,7 +283,12 @@ static_assert(DESC_AHEAD + DESC_GROUP <= DESC_RING, "the front end overwrites de
 constexpr int32_t NEVER_CACHED = INT32_MIN;      // cell value of the extra row: below any cursor
 
 constexpr int CELL_SETS = 3;          // requests whose row cells are in LDS: two ahead are loaded while one is at hand
-constexpr int LOOK_RING = 8;          // log records of look-ahead kept in LDS per replica
+// Log records of look-ahead kept in LDS, of each cursor: eight per replica.  The proxy variants have two cursors and keep
+// eight for 32 replicas or fewer, four for more (a cursor among 33 needs one half as often as one among 16); with the
+// engine model and the tuner as well, half of that.  Their workgroups then fit a CU as often as the others' do.
+__host__ __device__ constexpr int look_words(bool engine, bool online, bool proxy) {
+    return proxy ? (engine && online ? 2 * WAVE : 4 * WAVE) : 8 * WAVE;
+}
 // How often the look-ahead is fed, as a mask: a record per replica every fourth request, or every eighth with 24 replicas
 // or more.  The cursors of all replicas together pass about 0.9 log records per request, so the more replicas there are
 // the less often each needs one, and taking one costs the deciding wavefront some 500 cycles.  (1,024 replays of 40,000
@@ -294,35 +297,47 @@ constexpr int LOOK_RING = 8;          // log records of look-ahead kept in LDS p
 __host__ __device__ constexpr int look_every(int R) { return R >= 24 ? 7 : 3; }
 // What every replica would mean for a request, written by its lane before the minimum is known; the replica with the
 // minimum is announced by its number alone.
+template <bool PROXY>
 struct __align__(16) Choice {
-    double prefill;                   // prefill time (linear model, the replicas' caches known) or tokens to prefill
+    double prefill;                   // prefill time (linear model) or tokens to prefill
     int owner;                        // request whose owned suffix would start at `end`, -2: none (or dealt with)
     unsigned hit_end;                 // cached blocks | end << 16
+};
+template <>
+struct __align__(16) Choice<true> {
+    int prefill;                      // tokens to prefill
+    int seen;                         // blocks the proxy believes cached
+    int owner;
+    unsigned hit_end;
 };
 // An ownership change: `owner`'s owned suffix now starts at `end`.
 struct OwnChange {
     int owner, end;
 };
 constexpr int OWN_LIST = -3;              // in Choice::owner: the changes are in Handover::changes, as many as its `end` says
+// What the deciding and the queue wavefront tell each other, in both formulations.
 template <bool PROXY>
-struct __align__(256) Handover {
-    int32_t cells[CELL_SETS][SEG_CHUNK][WAVE];    // [request mod 3]: row cells of the request's first eight segments per replica
-    Choice choice[2][WAVE];               // [request mod 2][replica]
+struct __align__(16) QueueHandover {
+    Choice<PROXY> choice[2][WAVE];        // [request mod 2][replica]
     double gone[2][WAVE];                 // [request mod 2][replica]: minus the tokens (least-request policy: the requests) that
                                           // left the load signal between the previous request's arrival and this one's
-    // look-ahead of the eviction cursors (the cache's; the proxy's index's): per replica, log records fetched ahead
-    // of the cursor, slot k of replica i at [k * WAVE + i] (one slot is always free)
-    unsigned long long look[PROXY ? 2 : 1][LOOK_RING * WAVE];
-    unsigned long long fetched[PROXY ? 2 : 1][WAVE]; // log records that the front end has fetched ...
-    int wanted[PROXY ? 2 : 1][WAVE];      // ... and is to fetch, every fourth or eighth request
-    SegDesc ring[DESC_RING];
-    double half[PROXY ? 4 : 1][WAVE];     // half the round trip time per replica (proxy variants: [request mod 4])
-    double rtt[PROXY ? 4 : 1][PROXY ? WAVE : 1];  // proxy variants, [request mod 4]: estimated round trip time per replica
     double w[2][3];                       // online tuner: weights in use
-    int first[WAVE];                      // first request routed to each replica (-1: none yet)
     int best[2][2];                       // [request mod 2][replay of the workgroup] the choice: lane of the replica
-    OwnChange changes[2][2][SEG_CHUNK];   // [request mod 2][replay]
-    uint16_t seen[PROXY ? 2 : 1][PROXY ? WAVE : 1];   // proxy variants, [request mod 2]: blocks the proxy believes cached
+    double half[PROXY ? 1 : WAVE];        // half the round trip time per replica (proxy variants: kept by the queue wavefront)
+    double rtt[PROXY ? 2 : 1][PROXY ? WAVE : 1];   // proxy variants, [request mod 2]: estimated round trip time per replica
+};
+template <bool PROXY, int PACK, int LOOK>
+struct Handover : QueueHandover<PROXY> {
+    static constexpr int LOOK_WORDS = LOOK;
+    int32_t cells[CELL_SETS][SEG_CHUNK][WAVE];    // [request mod 3]: row cells of the request's first eight segments per replica
+    // look-ahead of the eviction cursors (the cache's; the proxy's index's): per replica, log records fetched ahead
+    // of the cursor (one slot is always free)
+    unsigned long long look[PROXY ? 2 : 1][LOOK];
+    // the log record that the front end is to fetch, every fourth or eighth request, then what it has fetched
+    unsigned long long record[PROXY ? 2 : 1][WAVE];
+    SegDesc ring[DESC_RING];
+    int first[WAVE];                      // first request routed to each replica (-1: none yet)
+    OwnChange changes[2][PACK][SEG_CHUNK];   // [request mod 2][replay]
 };
 
 // Workgroup barrier; `after_lds`: this wavefront's LDS accesses have been performed before it arrives (what it wrote is
@@ -436,18 +451,34 @@ struct Fresh {
         return own;
     }
 };
+template <int WORDS>
 struct EvictCursor {
     int cur_r = -1, cur_k = 0, cur_own = 0;
     int last_r = -1, fill_r = -1;
     int pend_r = -1, pend_own = -1;      // pend_r: record asked for (last_r: only its link), -1 none
-    const unsigned long long* fetched = nullptr;     // where it will be
-    // The look-ahead: a ring of records in LDS (slot k of this lane at ring[k * WAVE], packed r | own << 32 | n << 48),
-    // ring_cnt of them from slot ring_head on, the youngest being request ring_hi.
+    unsigned long long* record = nullptr;            // where it will be
+    // The look-ahead: a ring of records in LDS (packed r | own << 32 | n << 48), ring_cnt of them from slot ring_head on,
+    // the youngest being request ring_hi.
     unsigned long long* ring = nullptr;
+    int apart = 0;            // log2 of the distance between a lane's slots
     int ring_head = 0, ring_cnt = 0, ring_hi = -1;
     int over = 0;             // blocks this LRU holds beyond its capacity (below 0: room)
     int n_spot = 0, n_adv = 0, n_dead = 0;       // statistics (only the timed instantiation reads them): records fetched
                                                  // on the spot, cursor advances, records dropped because they own nothing
+
+    // `look`, `record`: the handed-over words of this cursor.  Lanes that no replica can have where the slots are 32 apart use
+    // their own word of `record` instead, which nothing else is done with.
+    __device__ __forceinline__ void init(unsigned long long* look, unsigned long long* record_, int R, int lane) {
+        apart = WORDS < 8 * WAVE && R <= HALF ? 5 : 6;
+        const bool there = lane < 1 << apart;
+        ring = there ? look + lane : record_ + lane;
+        record = record_ + lane;
+        *record = ~0ull;
+        if (there)
+            for (int k = 0; k < slots(); ++k) *at(k) = ~0ull;
+    }
+    __device__ __forceinline__ int slots() const { return WORDS < 8 * WAVE ? WORDS >> apart : 8; }
+    __device__ __forceinline__ unsigned long long* at(int k) const { return ring + ((k & (slots() - 1)) << (WORDS < 8 * WAVE ? apart : 6)); }
 
     // In the lanes with `who` set, what was asked for has arrived: the link of last_r, or a record, which is dropped if
     // it owns nothing and else joins the ring.  Straight-line code: lanes with nothing pending go through it unchanged
@@ -460,7 +491,7 @@ struct EvictCursor {
         const int own = pend_own > own_mem ? pend_own : own_mem;
         const bool record = have && pend_r != last_r;
         const bool alive = record && own < n;
-        ring[((ring_head + ring_cnt) & (LOOK_RING - 1)) * WAVE] = (unsigned long long)(unsigned)pend_r | ((unsigned long long)((hi & 0xFFFF0000u) | (unsigned)own) << 32);
+        *at(ring_head + ring_cnt) = (unsigned long long)(unsigned)pend_r | ((unsigned long long)((hi & 0xFFFF0000u) | (unsigned)own) << 32);
         ring_cnt += alive ? 1 : 0;
         ring_hi = alive ? pend_r : ring_hi;
         n_dead += record && !alive ? 1 : 0;
@@ -479,7 +510,7 @@ struct EvictCursor {
     // X(r), when everything that r - 1 changes is there; what r changes is kept in pend_own.
     __device__ __forceinline__ int ask(int spare, const Fresh& f, int first) {
         const int x = wanted(f, first);
-        const bool want = x >= 0 && ring_cnt < LOOK_RING - 1;
+        const bool want = x >= 0 && ring_cnt < slots() - 1;
         pend_r = want ? x : -1;
         pend_own = -1;
         return want ? x : spare;
@@ -496,10 +527,10 @@ struct EvictCursor {
         disowned(owner, end);
         if (maybe_in_ring(owner)) {
 #pragma nounroll
-            for (int k = 0; k < LOOK_RING; ++k) {
-                const unsigned long long e = ring[k * WAVE];
+            for (int k = 0; k < slots(); ++k) {
+                const unsigned long long e = *at(k);
                 if ((int)(unsigned)e == owner)
-                    ring[k * WAVE] = (e & ~(0xFFFFull << 32)) | ((unsigned long long)(unsigned)end << 32);
+                    *at(k) = (e & ~(0xFFFFull << 32)) | ((unsigned long long)(unsigned)end << 32);
             }
         }
     }
@@ -543,7 +574,7 @@ struct EvictCursor {
                 continue;
             }
             const bool go = E > 0;
-            const unsigned long long e = ring[(ring_head & (LOOK_RING - 1)) * WAVE];
+            const unsigned long long e = *at(ring_head);
             const unsigned hi = (unsigned)(e >> 32);
             n_adv += go ? 1 : 0;
             cur_r = go ? (int)(unsigned)e : cur_r;
@@ -570,8 +601,8 @@ struct EvictCursor {
 // ---------------------------------------------------------------------------------------------- front end
 // Front-end wavefront: lane = (request of a group of eight, segment reference).  A group's scalars, references and
 // descriptors are requested, requested and written in turn, eight requests apart, so that no load is waited for.
-template <int MODE, bool PROXY, int PACK, bool TIMED>
-__device__ __forceinline__ void front_wave(const SegArgs& a, int lane, Handover<PROXY>* comm) {
+template <int MODE, bool PROXY, int PACK, bool TIMED, class Comm>
+__device__ __forceinline__ void front_wave(const SegArgs& a, int lane, Comm* comm) {
     constexpr bool SIGNAL = MODE == MODE_COST_MODEL || MODE == MODE_ONLINE || MODE == MODE_LEAST_REQUEST;
     const int R = a.R, N = (int)a.N;
     const int q = lane / SEG_CHUNK, k = lane % SEG_CHUNK;
@@ -756,14 +787,14 @@ __device__ __forceinline__ void front_wave(const SegArgs& a, int lane, Handover<
         if (r >= N) return;
         load_cells(r + 2);
         if ((r & every) == 0 && r > 0)
-            for (int c = 0; c < (PROXY ? 2 : 1); ++c) raw[c] = ld(&log64[comm->wanted[c][lane]]);
+            for (int c = 0; c < (PROXY ? 2 : 1); ++c) raw[c] = ld(&log64[(int)(unsigned)comm->record[c][lane]]);
     };
     auto pass = [&](int r) {
         if (r >= N) return;
         const bool sync = (__builtin_amdgcn_readfirstlane(comm->ring[r & (DESC_RING - 1)].flags) & DESC_SYNC) != 0;
         store_cells();
         if ((r & every) == 0 && r > 0)
-            for (int c = 0; c < (PROXY ? 2 : 1); ++c) comm->fetched[c][lane] = raw[c];
+            for (int c = 0; c < (PROXY ? 2 : 1); ++c) comm->record[c][lane] = raw[c];
         clk.tick(0);                                                 // descriptors, cells
         meet(true);                                                  // X(r)
         if (sync) meet(false);                                       // Y(r)
@@ -795,8 +826,8 @@ __device__ __forceinline__ void front_wave(const SegArgs& a, int lane, Handover<
 // X(r) it serves r, then retires what completes by the arrival of r + 2, which the deciding wavefront reads after
 // X(r + 1).  BLOCKS: the partner is the block-table formulation's cache wavefront; the two meet twice at every request
 // and the route and hit outputs are written here.
-template <int MODE, bool ENGINE, bool PROXY, int PACK, bool BLOCKS, bool TIMED>
-__device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane, unsigned char* lds_raw, Handover<PROXY>* comm) {
+template <int MODE, bool ENGINE, bool PROXY, int PACK, bool BLOCKS, bool TIMED, class Comm>
+__device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane, unsigned char* lds_raw, Comm* comm) {
     constexpr bool ONLINE = MODE == MODE_ONLINE;
     constexpr bool COUNTS = MODE == MODE_LEAST_REQUEST;      // the load signal is the number of requests, not their tokens
     const int R = a.R, N = (int)a.N;
@@ -806,7 +837,7 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
     // Online tuner (Sec. 2.3, Sec. 4), run here because this wavefront has the TTFTs: after every hop the p95
     // TTFT of the last `window` requests is the fitness of the weights in use; they replace the parent iff they
     // beat it; the step size follows the 1/5 rule; the next offspring is a log-space mutation of the parent.
-    // The state is the same in every lane.
+    // The three weights are held by lanes 0 to 2 (the other lanes repeat the third), the rest of the state by every lane.
     double* const ring = reinterpret_cast<double*>(lds_raw + SlotQueues::bytes(R, a.B, ENGINE));
     const int W = ONLINE ? a.window : 0, H = ONLINE ? a.hop : 0;
     const int kth = (95 * W + 99) / 100;
@@ -814,19 +845,20 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
     int64_t step = 0;
     int accepted = 0;
     bool have_parent = false;
-    double ln_par[3] = {0.0, 0.0, 0.0}, ln_cur[3] = {0.0, 0.0, 0.0};
+    const int wk = lane < 3 ? lane : 2;                 // the weight of this lane
+    double ln_par = 0.0, ln_cur = 0.0;
     double f_par = 0.0, sigma = 0.0;
     if (ONLINE) {
-        for (int k = 0; k < 3; ++k) ln_par[k] = ln_cur[k] = a.ln_theta0[3 * p + k];
+        ln_par = ln_cur = a.ln_theta0[3 * p + wk];
         sigma = a.tuner[12];
         if (W + lane < ((W + 7) & ~7)) ring[W + lane] = INFINITY;     // padding (entries below W are written before use)
     }
     auto tuner_results = [&]() {
-        if (ONLINE && lane == 0) {
-            if (a.theta_final)
-                for (int k = 0; k < 3; ++k) a.theta_final[3 * p + k] = clip(tuner_exp(ln_par[k]), a.tuner[k], a.tuner[3 + k]);
-            if (a.sigma_final) a.sigma_final[p] = sigma;
-            if (a.accepted) a.accepted[p] = accepted;
+        if (ONLINE) {
+            const double best = clip(tuner_exp(ln_par), a.tuner[wk], a.tuner[3 + wk]);
+            if (a.theta_final && lane < 3) a.theta_final[3 * p + lane] = best;
+            if (a.sigma_final && lane == 0) a.sigma_final[p] = sigma;
+            if (a.accepted && lane == 0) a.accepted[p] = accepted;
         }
     };
     if (N == 0) {           // (an empty trace still reports the tuner's initial state)
@@ -838,10 +870,10 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
     // imperfect proxy knowledge (Sec. 2.2, Sec. 4 RTT figure): time is cut into probe epochs, the epoch of t being
     // the largest e with e * probe_ms <= t (capped at the last one given); a request experiences the true round
     // trip time of its epoch, the cost model scores with the proxy's moving average, handed to the deciding wavefront
-    // two requests ahead.  (The service step looks half the round trip time up in LDS.)
+    // two requests ahead.
     int epoch = 0;
     double next_probe = PROXY ? (double)a.probe_ms : 0.0, rtt_now = 0.0, est_now = 0.0;
-    auto probe = [&](double t, int r) {          // request r arrives at t
+    auto probe = [&](double t, int r) -> double {          // request r arrives at t: half the round trip time of replica = lane
         bool moved = r == 0;
         while (epoch + 1 < a.epochs && next_probe <= t) {       // (timestamps do not decrease)
             ++epoch;
@@ -853,10 +885,12 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
             rtt_now = a.rtt_true[at];
             est_now = a.rtt_est[at];
         }
-        comm->half[r & 3][lane] = 0.5 * rtt_now;
-        if constexpr (PROXY) comm->rtt[r & 3][lane] = est_now;
+        if constexpr (PROXY) comm->rtt[r & 1][lane] = est_now;
+        return 0.5 * rtt_now;
     };
-    if (!PROXY) comm->half[0][lane] = lane < R ? 0.5 * a.rtt[lane] : 0.0;
+    // proxy variants: half the round trip time of replica = lane, the request in hand's and the next two's
+    double half0 = 0.0, half1 = 0.0, half2 = 0.0;
+    if constexpr (!PROXY) comm->half[lane] = lane < R ? 0.5 * a.rtt[lane] : 0.0;
     // engine model: this lane's replica has its own rates and KV budget
     const double my_a_pf = ENGINE && lane < R ? a.eng_a_pf[lane] : 0.0;
     const double my_a_dec = ENGINE && lane < R ? a.eng_a_dec[lane] : 0.0;
@@ -899,8 +933,8 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
         t1 = (double)a.ts[N > 1 ? 1 : 0] * sc;
     }
     if (PROXY) {
-        probe(t0, 0);
-        if (N > 1) probe(t1, 1);
+        half0 = probe(t0, 0);
+        if (N > 1) half1 = probe(t1, 1);
     }
     meet(true);        // (nothing has completed yet: the first request can be decided)
 
@@ -913,13 +947,15 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
         double t2, dec;
     } coming{0, 0, 0, 0.0, 0.0};
     auto read_desc = [&](int r) {
-        const SegDesc& d = comm->ring[r & (DESC_RING - 1)];
-        const int4 h = *reinterpret_cast<const int4*>(&d.L);
-        coming.L = h.x;
-        coming.flags = h.w;
-        coming.t2 = d.t2[which];
-        if (ENGINE) coming.O = d.O;
-        else coming.dec = d.dec;
+        if constexpr (!BLOCKS) {
+            const SegDesc& d = comm->ring[r & (DESC_RING - 1)];
+            const int4 h = *reinterpret_cast<const int4*>(&d.L);
+            coming.L = h.x;
+            coming.flags = h.w;
+            coming.t2 = d.t2[which];
+            if (ENGINE) coming.O = d.O;
+            else coming.dec = d.dec;
+        }
     };
     if (AHEAD) read_desc(0);
 
@@ -955,10 +991,12 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
             // (what completes by the arrival of the request after next, this request's own completion aside: read now, while
             // the choice is on its way)
             unsigned due = Q.due(t2, lane);
-            const Choice* const ch = &comm->choice[r & 1][lane_best];
-            const double prefill = ch->prefill;
+            const Choice<PROXY>* const ch = &comm->choice[r & 1][lane_best];
+            const double prefill = (double)ch->prefill;
             const int best = PACK == 2 ? lane_best & (HALF - 1) : lane_best;
-            const double half = comm->half[PROXY ? r & 3 : 0][best];
+            double half;
+            if constexpr (PROXY) half = readlane_f64(half0, best);
+            else half = comm->half[best];
             const int weight = COUNTS ? 1 : L;
             double ttft, e2e;
             if constexpr (ENGINE) {
@@ -975,7 +1013,7 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
             if (BLOCKS) {
                 o_route = lane == i ? best : o_route;
                 o_hit = lane == i ? (int)(ch->hit_end & 0xFFFFu) : o_hit;
-                if constexpr (PROXY) o_believed = lane == i ? (int)comm->seen[r & 1][lane_best] : o_believed;
+                if constexpr (PROXY) o_believed = lane == i ? ch->seen : o_believed;
             }
             if (ONLINE) {
                 if (lane == 0) ring[ring_pos] = ttft;
@@ -990,25 +1028,20 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
                     } else {
                         const bool success = f < f_par;
                         if (success) {
-                            for (int k = 0; k < 3; ++k) ln_par[k] = ln_cur[k];
+                            ln_par = ln_cur;
                             f_par = f;
                             ++accepted;
                         }
                         sigma = sigma * (success ? a.tuner[13] : a.tuner[14]);
                     }
-                    double th[3];
-                    for (int k = 0; k < 3; ++k) {
-                        const double zk = a.z[(p * a.steps + step) * 3 + k];
-                        const double moved = ln_par[k] + sigma * zk;
-                        ln_cur[k] = clip(moved, a.tuner[6 + k], a.tuner[9 + k]);
-                        th[k] = clip(tuner_exp(ln_cur[k]), a.tuner[k], a.tuner[3 + k]);
+                    const double moved = ln_par + sigma * a.z[(p * a.steps + step) * 3 + wk];
+                    ln_cur = clip(moved, a.tuner[6 + wk], a.tuner[9 + wk]);
+                    const double th = clip(tuner_exp(ln_cur), a.tuner[wk], a.tuner[3 + wk]);
+                    if (lane < 3) {                                      // in use from the next request on (Y(r) follows)
+                        comm->w[which][lane] = th;
+                        if (a.theta_step) a.theta_step[(p * a.steps + step) * 3 + lane] = th;
                     }
-                    if (lane == 0) {                                     // in use from the next request on (Y(r) follows)
-                        for (int k = 0; k < 3; ++k) comm->w[which][k] = th[k];
-                        if (a.fitness_step) a.fitness_step[p * a.steps + step] = f;
-                        if (a.theta_step)
-                            for (int k = 0; k < 3; ++k) a.theta_step[(p * a.steps + step) * 3 + k] = th[k];
-                    }
+                    if (lane == 0 && a.fitness_step) a.fitness_step[p * a.steps + step] = f;
                     ++step;
                     wave_sync();
                 }
@@ -1024,7 +1057,11 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
             // where the next request goes, whose own completion the deciding wavefront has ruled out, or will wait for.
             if (r + 2 < N) {
                 retire(due, t2, r + 2);
-                if (PROXY) probe(t2, r + 2);
+                if (PROXY) half2 = probe(t2, r + 2);
+            }
+            if (PROXY) {
+                half0 = half1;
+                half1 = half2;
             }
             t0 = t1;
             t1 = t2;
@@ -1056,8 +1093,8 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
 // on the chosen replica, the rows that start over, the log record, its link, the previous owner's suffix -- and keeps
 // the routes and hit counts.  Stores that only some lanes have use for are issued by every lane, the others aimed at a
 // row and a log record that nothing reads: a plain instruction is cheaper than a branch around it.
-template <bool PROXY, int PACK, bool TIMED>
-__device__ __forceinline__ void book_wave(const SegArgs& a, int lane, Handover<PROXY>* comm) {
+template <bool PROXY, int PACK, bool TIMED, class Comm>
+__device__ __forceinline__ void book_wave(const SegArgs& a, int lane, Comm* comm) {
     const int R = a.R, N = (int)a.N;
     const bool upper = PACK == 2 && lane >= HALF;
     const int rl = PACK == 2 ? lane & (HALF - 1) : lane;
@@ -1093,7 +1130,7 @@ __device__ __forceinline__ void book_wave(const SegArgs& a, int lane, Handover<P
         meet(true);                                                  // X(r)
         clk.tick(3);                                                 // waiting at X
         const int lane_best = comm->best[r & 1][upper ? 1 : 0];
-        const Choice c = comm->choice[r & 1][lane_best];
+        const Choice<PROXY> c = comm->choice[r & 1][lane_best];
         const int best = PACK == 2 ? lane_best & (HALF - 1) : lane_best;
         const bool is_best = rl == best;
         // every segment of the request is now last touched by r on the chosen replica (lanes k, k + 8, ...: segment k).
@@ -1135,7 +1172,7 @@ __device__ __forceinline__ void book_wave(const SegArgs& a, int lane, Handover<P
             const int count = c.owner == OWN_LIST ? (int)(c.hit_end >> 16) : 0;
             for (int i = 0; ballot(i < count) != 0; ++i)
                 if (i < count) {
-                    const OwnChange x = comm->changes[r & 1][upper ? 1 : 0][i];
+                    const OwnChange x = comm->changes[r & 1][PACK == 2 && upper ? 1 : 0][i];
                     st(&log[x.owner].own, (uint16_t)x.end);
                 }
         }
@@ -1145,7 +1182,7 @@ __device__ __forceinline__ void book_wave(const SegArgs& a, int lane, Handover<P
         const bool mine = rl == slot;
         o_route = mine ? best : o_route;
         o_hit = mine ? (int)(c.hit_end & 0xFFFFu) : o_hit;
-        if constexpr (PROXY) o_seen = mine ? (int)comm->seen[r & 1][lane_best] : o_seen;
+        if constexpr (PROXY) o_seen = mine ? c.seen : o_seen;
         if (slot == BATCH - 1 || r == N - 1) {
             const int x = r - slot + rl;
             if (rl <= slot) {
@@ -1164,8 +1201,8 @@ __device__ __forceinline__ void book_wave(const SegArgs& a, int lane, Handover<P
 }
 
 // ---------------------------------------------------------------------------------------------- deciding
-template <int MODE, bool ENGINE, bool PROXY, int PACK, bool TIMED>
-__device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Handover<PROXY>* comm) {
+template <int MODE, bool ENGINE, bool PROXY, int PACK, bool TIMED, class Comm>
+__device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Comm* comm) {
     constexpr bool ONLINE = MODE == MODE_ONLINE;
     constexpr bool SCORED = MODE == MODE_COST_MODEL || MODE == MODE_ONLINE;
     constexpr bool COUNTS = MODE == MODE_LEAST_REQUEST;
@@ -1176,7 +1213,7 @@ __device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Handover
     const size_t p0 = (size_t)blockIdx.x * PACK, p = p0 + (upper ? 1 : 0);
     const bool in = rl < R;
     double w_rtt = a.params[3 * p + 0], w_prefill = a.params[3 * p + 1], w_queue = a.params[3 * p + 2];
-    const double my_rtt = !PROXY && in ? a.rtt[rl] : 0.0;        // (proxy variants: comes from the queue wavefront)
+    double my_rtt = !PROXY && in ? a.rtt[rl] : 0.0;              // (proxy variants: comes from the queue wavefront)
     // first product of Eq. 3 (lanes without a replica: a score above any)
     double rtt_term = in ? w_rtt * my_rtt : INFINITY;
     double q = COUNTS && !in ? INFINITY : 0.0;       // load signal of replica = lane (an integer below 2^53, exact in fp64)
@@ -1189,15 +1226,11 @@ __device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Handover
     // cursor stays at the replica's first record and "in the index" means "ever dispatched here".
     const bool own_index = PROXY && a.index_blocks >= 0;
     const int index_cap = PROXY && a.index_blocks > 0 ? (int)a.index_blocks : 0;
-    EvictCursor c1, c2;                       // the cache's cursor, the index's cursor
-    c1.ring = &comm->look[0][lane];
-    c2.ring = &comm->look[1][lane];
+    EvictCursor<Comm::LOOK_WORDS> c1, c2;                 // the cache's cursor, the index's cursor
+    c1.init(comm->look[0], comm->record[0], R, lane);
+    if (PROXY) c2.init(comm->look[PROXY ? 1 : 0], comm->record[PROXY ? 1 : 0], R, lane);
     c1.over = a.C > 0 ? -(int)a.C : INT32_MIN;         // (unbounded)
     c2.over = -index_cap;
-    for (int k = 0; k < LOOK_RING; ++k) {
-        c1.ring[k * WAVE] = ~0ull;
-        if (PROXY) c2.ring[k * WAVE] = ~0ull;
-    }
     Fresh latest;                             // what the latest decision changes in the log
     unsigned long long went1 = 0, went2 = 0, went3 = 0;  // where the three requests before went (a lane of each replay)
 
@@ -1211,9 +1244,6 @@ __device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Handover
     const unsigned long long* const log64 = reinterpret_cast<const unsigned long long*>(log);
 
     const int every = look_every(R);
-    c1.fetched = &comm->fetched[0][lane];
-    c2.fetched = &comm->fetched[PROXY ? 1 : 0][lane];
-
     // the request in hand: row cells of its first eight segments as seen by this lane (= replica), where they end, tokens,
     // blocks, flags; read (LDS) while the minimum of the one before is being found
     int32_t cell[SEG_CHUNK];
@@ -1244,7 +1274,7 @@ __device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Handover
         const int flags = __builtin_amdgcn_readfirstlane(word);
         const double left = DICTATED ? 0.0 : comm->gone[r & 1][lane];
         if (!DICTATED) comm->gone[r & 1][lane] = 0.0;
-        const double rtt_now = PROXY ? comm->rtt[r & 3][PROXY ? lane : 0] : my_rtt;
+        if constexpr (PROXY) my_rtt = comm->rtt[r & 1][lane];
 
         // ---- the rows were loaded before the stores of the three requests before were sure to be there: the leading
         // segments that the paths share get the cells that those requests wrote on their replicas
@@ -1357,15 +1387,15 @@ __device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Handover
         // next one is asked for)
         if ((r & every) == every) {
             const int first = comm->first[lane];
-            c1.take_pending(*c1.fetched);
-            comm->wanted[0][lane] = c1.ask(spare, latest, first);
+            c1.take_pending(*c1.record);
+            *c1.record = (unsigned)c1.ask(spare, latest, first);
             if (PROXY) {
                 int also = spare;
                 if (index_cap > 0) {
-                    c2.take_pending(*c2.fetched);
+                    c2.take_pending(*c2.record);
                     also = c2.ask(spare, latest, first);
                 }
-                comm->wanted[PROXY ? 1 : 0][lane] = also;
+                *c2.record = (unsigned)also;
             }
         }
         clk.tick(2);                                                 // log records
@@ -1385,7 +1415,7 @@ __device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Handover
         if (!ENGINE && !PROXY) my_prefill = a.a_pf * my_prefill;
         if (SCORED) {
             const double pf = PROXY || ENGINE ? a.a_pf * (double)my_u_seen : my_prefill;
-            const double s_rtt = PROXY ? (in ? w_rtt * rtt_now : INFINITY) : rtt_term;
+            const double s_rtt = PROXY ? (in ? w_rtt * my_rtt : INFINITY) : rtt_term;
             const double s_pf = w_prefill * pf;
             const double rtt_and_prefill = s_rtt + s_pf;
             const double qd = a.a_pf * q;
@@ -1408,8 +1438,9 @@ __device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Handover
         if (PROXY) plain &= ~(ballot(c2.ring_cnt > 0) & ballot(cell[0] <= c2.ring_hi));
         const unsigned long long walkers = holders & ~plain;
         const int owner = of_mask(holders & plain) ? cell[0] : -2;
-        comm->choice[r & 1][lane] = Choice{my_prefill, owner, (unsigned)my_m | ((unsigned)k_end << 16)};
-        if constexpr (PROXY) comm->seen[r & 1][lane] = (uint16_t)(own_index ? my_seen : my_m);
+        const unsigned hit_end = (unsigned)my_m | ((unsigned)k_end << 16);
+        if constexpr (PROXY) comm->choice[r & 1][lane] = Choice<true>{my_u, own_index ? my_seen : my_m, owner, hit_end};
+        else comm->choice[r & 1][lane] = Choice<false>{my_prefill, owner, hit_end};
 
         // (what is still needed of this request's numbers, and the next one's: its reads are under way during the minimum)
         const int added = n - my_m, also_added = n - my_seen, set_now = set;
@@ -1464,7 +1495,7 @@ __device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Handover
             } else {
                 // from the preloaded rows.  The book-keeping wavefront stores the changes: it may still be at work on the
                 // previous request's, which may concern one of these owners.
-                OwnChange* const list = comm->changes[r & 1][upper ? 1 : 0];
+                OwnChange* const list = comm->changes[r & 1][PACK == 2 && upper ? 1 : 0];
                 int count = 0;
                 auto changed = [&](int of, int to) { list[count++] = OwnChange{of, to}; };
                 const int most = flags & DESC_MORE4 ? SEG_CHUNK : 4;
@@ -1477,7 +1508,7 @@ __device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Handover
                 latest.count = count;
                 latest.list = list;
                 if (count > 0) {
-                    Choice* const mine = &comm->choice[r & 1][lane];
+                    Choice<PROXY>* const mine = &comm->choice[r & 1][lane];
                     mine->owner = OWN_LIST;
                     mine->hit_end = (unsigned)my_m | ((unsigned)count << 16);
                 }
@@ -1527,15 +1558,17 @@ __device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Handover
 }
 
 // One workgroup = one replay, or two neighbouring ones (PACK = 2: at most 32 replicas, one lane per service slot).
-// (At most 128 vector registers: four wavefronts per SIMD, so that the 1,024 workgroups of four wavefronts are all
-// resident.)
+// A replay takes its time however few run beside it, so a population that needs a second round takes twice as long.  At most
+// 96 vector registers (five wavefronts per SIMD) and what is in LDS hold five workgroups on a CU with 256 slots, 1,280
+// replays, and four with 512: every variant, with a tuner window of 128.  (10,000 requests, 1,024 replays of 32 replicas with
+// 16 slots, three workgroups on a CU before: engine 15.1 -> 8.0 ms, tuner 15.0 -> 8.1, proxy 14.1 -> 7.8.)
 template <int PACK>
 constexpr int seg_threads() { return (3 + PACK) * WAVE; }
 
 template <int MODE, bool ENGINE, bool PROXY, int PACK = 1, bool TIMED = false>
-__global__ void __launch_bounds__(seg_threads<PACK>(), PACK == 2 ? 6 : 4) replay_segments_kernel(SegArgs a) {
+__global__ void __launch_bounds__(seg_threads<PACK>(), PACK == 2 ? 6 : 5) replay_segments_kernel(SegArgs a) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    __shared__ __align__(16) Handover<PROXY> comm;
+    __shared__ Handover<PROXY, PACK, look_words(ENGINE, MODE == MODE_ONLINE, PROXY)> comm;
     const int lane = threadIdx.x & (WAVE - 1);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
     unsigned char* const mine = lds_raw + (wave - 1) * replay_queue_lds_bytes(a.R, a.B, ENGINE, MODE == MODE_ONLINE ? a.window : 0);

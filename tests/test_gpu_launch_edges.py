@@ -1,11 +1,14 @@
-"""Where a launch changes its way: small inputs as kernel arguments or as copies (R + 4 P against 448), and how often the
-eviction cursors' look-ahead is fed (24 replicas), against the CPU oracle."""
+"""Where a launch changes its way: small inputs as kernel arguments or as copies (R + 4 P against 448), how often the
+eviction cursors' look-ahead is fed (24 replicas), and how many sets of 64 service slots there are, against the CPU
+oracle."""
 import numpy as np
 import pytest
 
 import paper_2602_11688_amd as g
 from synth import tracegen as tg
 from tests.gpu_helpers import check_population
+from tests.test_gpu_engine import check_engine
+from tests.test_gpu_proxy import check_proxy
 
 pytestmark = pytest.mark.gpu
 
@@ -27,3 +30,22 @@ def test_look_ahead_either_way(R, cache):
     rtt = np.linspace(5.0, 120.0, R)
     # (the second weights send nearly everything to the nearest replica: one cursor passes a record at every request)
     check_population(wl.trace, model, rtt, [[0.5, 1.0, 0.1], [50.0, 0.05, 0.0]], 1.0, paths=[2], label=f"R={R}")
+
+
+@pytest.mark.parametrize("R,B", [(1, 1), (9, 7), (8, 8), (13, 5), (24, 8), (27, 9), (33, 8), (32, 10), (39, 10), (64, 8), (64, 16)])
+def test_sets_of_service_slots(R, B):
+    """63, 64, 65 slots, 192, 243, and sets beyond the fourth, one to four at a time; fleets with the look-ahead's records 32
+    and 64 apart; all at once, dense and sparse arrivals, so that lists are empty, deep, and taken down one by one."""
+    tr = tg.random_forest(100 * R + B, 1500, roots=4, max_blocks=12, grow=4, gap_ms=40)
+    nmax = int(np.diff(tr.blk_off).max())
+    rng = np.random.default_rng(R * B)
+    model = g.Model(R, B, 4 * nmax, 0.05, 4.0)
+    rtt = np.linspace(5.0, 300.0, R)
+    params, scale = [[0.5, 1.0, 0.1], [0.0, 0.1, 1.0], [1.0, 0.0, 0.01]], [1.0, 0.02, 50.0]
+    check_population(tr, model, rtt, params, scale, label=f"{R}x{B}")
+    most = int((tr.in_len.astype(np.int64) + tr.out_len).max())
+    engine = g.Engine(rng.uniform(0.02, 0.1, R), rng.uniform(1.0, 8.0, R), [3 * most] * R, 0.1)
+    check_engine(tr, model, engine, rtt, params, scale, label=f"{R}x{B} engine")
+    px = g.Proxy(np.round(rng.uniform(1.0, 900.0, (40, R)), 1), 1700, 0.3, 7 * nmax)
+    check_proxy(tr, model, px, params, scale, label=f"{R}x{B} proxy")
+    check_proxy(tr, model, px, params, scale, engine=engine, label=f"{R}x{B} proxy, engine")
