@@ -38,7 +38,10 @@
 // wavefront preloads, the online tuner changes the weights after r -- the descriptor of r says so (DESC_SYNC), every
 // wavefront of the workgroup reads that same word, and all meet once more, Y(r), when the queue and the book-keeping
 // wavefront have caught up with r.  The number of barriers a wavefront executes depends on the descriptors alone, so
-// none can wait for ever.
+// none can wait for ever.  The deciding wavefront comes to Y(r) when it has matched r + 1 against the rows in hand, which
+// the service of r does not concern; only the load signals, the weights and a longer path's rows wait for it.  (10,000
+// requests, 32 replicas, 2 and 1,024 replays, every request with two meetings: a request a minute 11.2 and 12.3 ms with the
+// match behind Y(r), so 9.8 and 11.2; without decode time 8.6 and 9.6, so 6.8 and 8.2.)
 //
 // 1,024 replays of 250,000 requests on 32 replicas: 241 ms with two barriers per request and half of its work between
 // them, 165.6 ms so (0.65 us, some 1,400 cycles a request).  The deciding and the queue wavefront now have chains of
@@ -988,9 +991,10 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
             meet(true);                                                  // X(r)
             clk.tick(1);                                                 // waiting at X
             const int lane_best = __builtin_amdgcn_readfirstlane(comm->best[r & 1][which]);
-            // (what completes by the arrival of the request after next, this request's own completion aside: read now, while
-            // the choice is on its way)
-            unsigned due = Q.due(t2, lane);
+            // (what completes by the arrival of the request after next, or of the next one where it is waited for, this request's
+            // own completion aside: read now, while the choice is on its way)
+            const double until = sync ? t1 : t2;
+            unsigned due = Q.due(until, lane);
             const Choice<PROXY>* const ch = &comm->choice[r & 1][lane_best];
             const double prefill = (double)ch->prefill;
             const int best = PACK == 2 ? lane_best & (HALF - 1) : lane_best;
@@ -1002,9 +1006,9 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
             if constexpr (ENGINE) {
                 Q.template serve_engine<PROXY>(r, best, t0, half, readlane_f64(my_a_pf, best) * prefill,
                                                readlane_f64(my_a_dec, best) * (double)O, weight, (unsigned)L + (unsigned)O,
-                                               readlane_f64(my_budget, best), a.eng_slowdown, rec, lane, &ttft, &e2e, t2, due);
+                                               readlane_f64(my_budget, best), a.eng_slowdown, rec, lane, &ttft, &e2e, until, due);
             } else {
-                Q.template serve<PROXY>(r, best, t0, half, PROXY ? a.a_pf * prefill : prefill, dec, weight, rec, lane, &ttft, &e2e, t2, due);
+                Q.template serve<PROXY>(r, best, t0, half, PROXY ? a.a_pf * prefill : prefill, dec, weight, rec, lane, &ttft, &e2e, until, due);
             }
             clk.tick(9);                                                 // service
             if (AHEAD) read_desc(r + 1);
@@ -1049,7 +1053,7 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
             clk.tick(5);                                                 // outputs, tuner
             if (sync) {
                 // the request may have completed before the next one arrives, or its latency matters to the next one
-                if (r + 1 < N) retire(Q.due(t1, lane), t1, r + 1);
+                if (r + 1 < N) retire(due, t1, r + 1);
                 meet(true);                                              // Y(r)
                 due = Q.due(t2, lane);
             }
@@ -1264,6 +1268,7 @@ __device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Comm* co
 
     SectionClock<TIMED> clk;
     int n_walks = 0;          // statistics: ownership walks
+    int before = 0;           // flags of the request before
     meet(true);                               // the first descriptors and cells are there
     take(0, 0);
     meet(true);                               // the queue wavefronts have set themselves up
@@ -1272,9 +1277,22 @@ __device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Comm* co
         const SegDesc* const dr = &comm->ring[r & (DESC_RING - 1)];
         const int target = DICTATED ? dr->target : 0;
         const int flags = __builtin_amdgcn_readfirstlane(word);
-        const double left = DICTATED ? 0.0 : comm->gone[r & 1][lane];
-        if (!DICTATED) comm->gone[r & 1][lane] = 0.0;
+        double left = DICTATED ? 0.0 : comm->gone[r & 1][lane];      // (read again behind Y(r - 1))
         if constexpr (PROXY) my_rtt = comm->rtt[r & 1][lane];
+
+        // Y(r - 1), as late as this request allows: the match needs only rows that are in hand
+        bool behind = (before & DESC_SYNC) != 0;
+        auto caught_up = [&]() {
+            meet(false);
+            behind = false;
+            if (!DICTATED) left = comm->gone[r & 1][lane];
+            if (ONLINE) {
+                w_rtt = comm->w[upper ? 1 : 0][0];
+                w_prefill = comm->w[upper ? 1 : 0][1];
+                w_queue = comm->w[upper ? 1 : 0][2];
+                rtt_term = in ? w_rtt * my_rtt : INFINITY;
+            }
+        };
 
         // ---- the rows were loaded before the stores of the three requests before were sure to be there: the leading
         // segments that the paths share get the cells that those requests wrote on their replicas
@@ -1337,10 +1355,13 @@ __device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Comm* co
         const unsigned long long by_cursor = PROXY ? ballot(below_cursor2 > e_gt2) : ballot(below_cursor > e_gt);
         const unsigned long long one_owner = (by_cursor & ballot((PROXY ? e_gt2 : e_gt) == 0)) |
                                              (~by_cursor & ballot((PROXY ? own_gt2 : own_gt) == cell[0]));
+        if (__builtin_expect(behind, 0)) caught_up();
+        if (!DICTATED) comm->gone[r & 1][lane] = 0.0;
+        clk.tick(4);                                                 // waiting at Y
         unsigned long long in_reach = ~0ull;     // 0: the match went past the preloaded segments
         if (flags & DESC_DEEP) {
-            // more than eight segments (rare; memory is up to date, Y(r - 1)): the rest of the path is read from the trace,
-            // eight references at a time, as long as some replica's prefix is still open
+            // more than eight segments (rare; memory is up to date behind Y(r - 1)): the rest of the path is read from the
+            // trace, eight references at a time, as long as some replica's prefix is still open
             const int64_t j0 = dr->j0;
             const int s = __builtin_amdgcn_readfirstlane(dr->s);
             int pos = end[7];
@@ -1536,16 +1557,7 @@ __device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Comm* co
         if (more != 0) c1.advance(E, log64, spare, latest, comm->first[lane]);
         if (PROXY && more2 != 0) c2.advance(E2, log64, spare, latest, comm->first[lane]);
         clk.tick(6);                                                 // eviction past the cursor's record
-        if (flags & DESC_SYNC) {
-            meet(false);                                             // Y(r)
-            if (ONLINE) {
-                w_rtt = comm->w[upper ? 1 : 0][0];
-                w_prefill = comm->w[upper ? 1 : 0][1];
-                w_queue = comm->w[upper ? 1 : 0][2];
-                rtt_term = in ? w_rtt * my_rtt : INFINITY;
-            }
-        }
-        clk.tick(4);                                                 // waiting at Y
+        before = flags;
     }
     if (TIMED) {
         // statistics of the eviction walk, summed over the replicas

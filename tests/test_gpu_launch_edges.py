@@ -1,6 +1,6 @@
 """Where a launch changes its way: small inputs as kernel arguments or as copies (R + 4 P against 448), how often the
-eviction cursors' look-ahead is fed (24 replicas), and how many sets of 64 service slots there are, against the CPU
-oracle."""
+eviction cursors' look-ahead is fed (24 replicas), how many sets of 64 service slots there are, and which requests the
+wavefronts meet twice at, against the CPU oracle."""
 import numpy as np
 import pytest
 
@@ -8,6 +8,8 @@ import paper_2602_11688_amd as g
 from synth import tracegen as tg
 from tests.gpu_helpers import check_population
 from tests.test_gpu_engine import check_engine
+from tests.test_gpu_online import _check as check_online
+from tests.test_gpu_policies import _check as check_policy
 from tests.test_gpu_proxy import check_proxy
 
 pytestmark = pytest.mark.gpu
@@ -49,3 +51,24 @@ def test_sets_of_service_slots(R, B):
     px = g.Proxy(np.round(rng.uniform(1.0, 900.0, (40, R)), 1), 1700, 0.3, 7 * nmax)
     check_proxy(tr, model, px, params, scale, label=f"{R}x{B} proxy")
     check_proxy(tr, model, px, params, scale, engine=engine, label=f"{R}x{B} proxy, engine")
+
+
+@pytest.mark.parametrize("gap_ms,decode", [(0, 0.0), (3, 0.0), (40, 0.02), (40, 0.3), (4000, 4.0)])
+def test_requests_that_are_waited_for(gap_ms, decode):
+    """No request, some or every one may have completed when the next arrives, or the next has more than eight segments: the
+    wavefronts meet twice, the deciding one in the middle of the next request."""
+    tr = tg.random_forest(7 + gap_ms, 1200, roots=3, max_blocks=60, grow=3, gap_ms=gap_ms, keep=0.85)
+    nmax = int(np.diff(tr.blk_off).max())
+    rng = np.random.default_rng(gap_ms)
+    R = 5
+    model = g.Model(R, 3, 3 * nmax, 0.05, decode)
+    rtt = np.array([0.0, 3.0, 10.0, 40.0, 500.0])
+    params, scale = [[0.5, 1.0, 0.1], [0.0, 0.1, 1.0], [1.0, 0.0, 0.01], [0.0, 0.0, 1.0]], [1.0, 0.1, 1.0, 3.0]
+    check_population(tr, model, rtt, params, scale, label="fixed weights")
+    check_policy(tr, model, rtt, "least-request", [1.0, 0.1])
+    most = int((tr.in_len.astype(np.int64) + tr.out_len).max())
+    engine = g.Engine(rng.uniform(0.02, 0.1, R), decode * rng.uniform(0.0, 2.0, R), [3 * most] * R, 0.1)
+    check_engine(tr, model, engine, rtt, params, scale)
+    check_proxy(tr, model, g.Proxy(np.round(rng.uniform(0.0, 300.0, (30, R)), 1), 700, 0.3, 5 * nmax), params, scale)
+    z = rng.standard_normal((2, g.online_steps(tr.N, 8, 1), 3))
+    check_online(tr, model, rtt, [[1.0, 0.5, 0.1]] * 2, z, [1.0, 0.1], 8, 1, [0.05] * 3, [2.0] * 3, 0.5)
