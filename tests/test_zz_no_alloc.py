@@ -63,3 +63,52 @@ def test_static_scratch_entry_point_refuses_what_does_not_fit_and_a_trace_that_i
     rc = L.gorgo_eval_population_static(tr._h, C.byref(m), None, binding._ptr(rtt), binding._ptr(parb), binding._ptr(scb), big,
                                         C.byref(ob), None)
     assert rc == -7 and b"static scratch" in L.gorgo_last_error()
+
+
+@pytest.mark.parametrize("P", [4, 200])
+def test_captured_in_a_graph_and_replayed(P):
+    """Under capture the small inputs stay copies (few of them would otherwise travel as kernel arguments): a graph reads the
+    caller's arrays at every replay.  Four replays with other weights each time and eager work on the same scratch array
+    between them, every one against an eager evaluation."""
+    import ctypes as C
+
+    import torch
+    wl = tg.config(1, 900)
+    tr = g.Trace.from_arrays(wl.trace.ts_ms, wl.trace.in_len, wl.trace.out_len, wl.trace.blk_off, wl.trace.hash_ids)
+    model = g.Model(wl.R, wl.batch, 300, wl.prefill_ms_per_token, wl.decode_ms_per_token)
+    rng = np.random.default_rng(P)
+    rtt, par, sc = np.ascontiguousarray(wl.rtt_ms, np.float64), rng.uniform(0.05, 2.0, (P, 3)), np.ones(P)
+    assert g.workspace_bytes(tr, model, P) <= binding.STATIC_SCRATCH_BYTES
+    dev = "cuda:0"
+    out = dict(route=torch.empty((P, tr.N), dtype=torch.uint8, device=dev), hit=torch.empty((P, tr.N), dtype=torch.int16, device=dev),
+               ttft_ms=torch.empty((P, tr.N), dtype=torch.float64, device=dev), e2e_ms=torch.empty((P, tr.N), dtype=torch.float64, device=dev),
+               p95_ttft_ms=torch.empty((P,), dtype=torch.float64, device=dev), p95_e2e_ms=torch.empty((P,), dtype=torch.float64, device=dev))
+    o = binding._outputs_struct(*out.values())
+    m = model.c()
+    L = g.lib()
+    assert L.gorgo_trace_to_device(tr._h) == 0
+
+    def enqueue(stream):
+        rc = L.gorgo_eval_population_static(tr._h, C.byref(m), None, binding._ptr(rtt), binding._ptr(par), binding._ptr(sc), P,
+                                            C.byref(o), C.c_void_p(stream.cuda_stream))
+        assert rc == 0, L.gorgo_last_error()
+
+    enqueue(torch.cuda.current_stream())                  # (everything is loaded before the capture begins)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        enqueue(torch.cuda.current_stream())
+    for k in range(4):
+        par[:] = rng.uniform(0.05, 2.0, (P, 3))
+        sc[:] = 1.0 + 0.5 * k
+        for x in out.values():
+            x.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        got = {n: x.clone() for n, x in out.items()}
+        ref = g.eval_population(tr, model, rtt, par, sc)
+        g.eval_population_static(tr, model, rtt, rng.uniform(0.05, 2.0, (P, 3)), 2.0)
+        torch.cuda.synchronize()
+        assert torch.equal(got["route"], ref.route) and torch.equal(got["hit"], ref.hit_blocks.view(torch.int16)), f"replay {k}"
+        for n in ("ttft_ms", "e2e_ms", "p95_ttft_ms", "p95_e2e_ms"):
+            assert torch.equal(got[n], getattr(ref, n)), f"replay {k}: {n}"
