@@ -101,8 +101,9 @@ typedef struct gorgo_model {
  *   replay_packing: with at most 32 replicas, at most 16 slots per replica and an even number of replays,
  *     gorgo_eval_population and gorgo_es_step can run two replays per workgroup of the segment-row kernel
  *     (a replay keeps one lane per replica, so half of a 64-lane wavefront idles otherwise).  A replay is a serial
- *     chain, so this only pays when the replays would not all be resident on the GPU at once (more than about
- *     1,280 of them) but the pairs would: 2 (default) packs exactly then, 1 whenever the shape allows, 0 never.
+ *     chain, so this pays when the replays would not all be resident on the GPU at once (with up to 256 service
+ *     slots more than 1,280 of them): 2 (default) packs then, up to twice as many, 1 whenever the shape allows,
+ *     0 never.
  *   handover_poll_limit: how many times wavefronts that hand over through polled words poll before a replay is
  *     given up (default 2^24; must be >= 0).  No kernel polls: the wavefronts of a replay meet at workgroup barriers,
  *     packed or not, so the value has no effect and no replay is given up.
@@ -145,13 +146,13 @@ int gorgo_workspace_bytes(const gorgo_trace* t, const gorgo_model* m, const gorg
  *   hip_stream           hipStream_t (NULL = default stream)
  * The call copies the small host arrays, enqueues its kernels on the stream and returns without waiting
  * for them; outputs are valid once the stream has reached that point.  The first evaluation of a trace on
- * a device uploads the trace (one allocation and one synchronous copy).  Calls that share a workspace must
+ * a device uploads the trace (one allocation, a synchronous copy of each of its arrays).  Calls that share a workspace must
  * be ordered on one stream. */
 int gorgo_eval_population(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* options, const double* rtt_ms,
                           const double* params, const double* scale, int32_t P, const gorgo_outputs* outputs,
                           void* workspace, size_t workspace_bytes, void* hip_stream);
 
-/* Uploads the trace to the current device now (one allocation, one synchronous copy) instead of at its first
+/* Uploads the trace to the current device now (one allocation, synchronous copies) instead of at its first
  * evaluation there.  Does nothing if it is already resident on this device. */
 int gorgo_trace_to_device(const gorgo_trace* t);
 
@@ -279,8 +280,8 @@ typedef enum gorgo_policy {
 } gorgo_policy;
 
 /* Evaluate P replays routed by `policy`, replay p at time scale scale[p] (and, for the random policy, with
- * seed seeds[p]; seeds is a host array [P], may be NULL for the other policies).  Everything else as
- * gorgo_eval_population, same workspace size. */
+ * seed seeds[p]; seeds is a host array [P], may be NULL for the other policies; the call returns when they have
+ * been copied).  Everything else as gorgo_eval_population, same workspace size. */
 int gorgo_eval_policy(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* options, const double* rtt_ms, int32_t policy,
                       const uint64_t* seeds, const double* scale, int32_t P, const gorgo_outputs* outputs,
                       void* workspace, size_t workspace_bytes, void* hip_stream);

@@ -312,9 +312,9 @@ int copy_small_to_device(void* dst, const void* src, size_t bytes, void* stream)
 }
 
 // Whether a launch of fixed-weight replays runs two replays per workgroup.  A replay is a serial chain whose duration
-// does not depend on how many others run beside it, and a packed pair takes about a quarter longer per request than a
-// lone replay (0.82 against 0.65 us with 32 replicas): packing pays when the replays would not all be resident at once
-// otherwise.
+// hardly depends on how many others run beside it, and a packed pair takes about a quarter longer per request than a
+// lone replay (0.82 us against 0.64 with 32 replicas and the chip full of either): packing pays when the replays would not
+// all be resident at once otherwise.
 bool pack_replays(const Plan& pl, int64_t rows) {
     const int32_t mode = pl.packing;       // 0 never, 1 whenever the shape allows, 2 when the replays would not all be resident
     if (mode == 0 || pl.R > HALF || pl.B > 16 || pl.P % 2 != 0 ||
@@ -327,9 +327,11 @@ bool pack_replays(const Plan& pl, int64_t rows) {
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, replay_segments_kernel<MODE_COST_MODEL, false, false>,
                                                      seg_threads<1>(), replay_queue_lds_bytes(pl.R, pl.B, false, 0)) != hipSuccess)
         return false;
-    // (10,000 requests, 32 replicas of 8 slots, unpacked against packed: 1,280 replays 7.1 / 6.8 ms, 1,536 12.1 / 6.9,
-    // 2,048 13.2 / 7.9, and 2,304 14.1 / 13.4, 2,560 14.7 / 13.6, where both take two rounds; with more rounds on either
-    // side the unpacked kernel's shorter request step wins again)
+    // (10,000 requests, 32 replicas of 8 slots, unpacked against packed: 1,280 replays 7.2 / 7.2 ms, 1,282 12.5 / 7.2, 1,536
+    // 12.3 / 7.2, 2,048 13.6 / 8.2; where the pairs take two rounds as well: 2,050 13.6 / 14.0, 2,304 14.7 / 13.8, 2,560
+    // 14.9 / 14.0.  16 slots, where 1,024 replays are resident either way: 1,026 13.0 / 13.6, 1,536 14.1 / 14.1, 2,048
+    // 15.0 / 14.2.  The upper end is what the option says, not where packing stops being the faster: 3,072 20.0 / 15.7,
+    // 4,096 26.3 / 21.8, 8,192 47.9 / 37.7.)
     const int64_t resident = (int64_t)cus * per_cu;
     return (int64_t)pl.P > resident && (int64_t)pl.P <= 2 * resident;
 }

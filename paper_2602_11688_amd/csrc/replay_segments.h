@@ -17,8 +17,8 @@
 //
 // The request loop is one dependent chain per replay: decision r changes the cursor, the cells and the load signal of
 // one replica, and decision r + 1 may depend on them.  A dependent vector or scalar instruction costs a wavefront
-// eight to nine cycles, a branch on a vector comparison forty, a word handed to another wavefront through LDS and a
-// barrier 130.  So only what the next decision needs is on the chain, in the hands of one wavefront, and everything
+// eight cycles (an independent one five), a branch on a vector comparison forty, a word handed to another wavefront through
+// LDS and a barrier 180.  So only what the next decision needs is on the chain, in the hands of one wavefront, and everything
 // else is done beside it by others of the same workgroup, which meet at ONE barrier per request:
 //   X(r): the choice of request r is published, and so is what has left the load signals by the arrival of r + 1.
 //   The deciding wavefront (lane = replica; two replays in its halves where R <= 32 and the launch packs) holds the
@@ -44,8 +44,8 @@
 // match behind Y(r), so 9.8 and 11.2; without decode time 8.6 and 9.6, so 6.8 and 8.2.)
 //
 // 1,024 replays of 250,000 requests on 32 replicas: 241 ms with two barriers per request and half of its work between
-// them, 165.6 ms so (0.65 us, some 1,400 cycles a request).  The deciding and the queue wavefront now have chains of
-// the same length, each is the last to arrive about half of the time; 2 replays take 0.56 us.
+// them, 164 ms so (0.65 us, some 1,400 cycles a request).  The deciding and the queue wavefront now have chains of
+// the same length, each is the last to arrive about half of the time; 2 replays take 0.55 us.
 #pragma once
 #include "device_common.h"
 #include "internal.h"
@@ -110,7 +110,7 @@ struct SegArgs {
     int64_t index_blocks;         // >= 0: Eq. 3 takes its cached prefix from the proxy's own index (an LRU of this
                                   // many blocks per replica, 0 = it never forgets); < 0: from the replica's cache
     uint16_t* believed;           // [P][N] blocks the proxy believed cached on the chosen replica, nullable
-    unsigned long long* sections; // timed instantiation only: [P][3][SECTIONS] cycles per section (cache, queue, front-end wavefront)
+    unsigned long long* sections; // timed instantiation only: [P][3][SECTIONS] cycles per section (deciding; queue; front-end and book-keeping wavefront)
 };
 
 // What picks the replica: the cost model of Eq. 3 with fixed weights, the same with the online tuner, or one
@@ -294,9 +294,11 @@ __host__ __device__ constexpr int look_words(bool engine, bool online, bool prox
 }
 // How often the look-ahead is fed, as a mask: a record per replica every fourth request, or every eighth with 24 replicas
 // or more.  The cursors of all replicas together pass about 0.9 log records per request, so the more replicas there are
-// the less often each needs one, and taking one costs the deciding wavefront some 500 cycles.  (1,024 replays of 40,000
-// requests, 32 replicas: proxy variant 33.4 -> 32.6 ms, the others equal within 1 %; 16 replicas, bursts, every eighth:
-// 47.6 -> 48.2 ms, records are then waited for.)
+// the less often each needs one, and taking one costs the deciding wavefront some 500 cycles.  (1,024 replays of 10,000
+// requests, every fourth against every eighth: 16 replicas 7.34 / 7.29 ms, with bursts 7.52 / 7.59, proxy variant 9.50 /
+// 9.54; 20 replicas 6.93 / 6.84, 7.14 / 7.07, 8.57 / 8.47; 24 replicas 6.69 / 6.57, 6.89 / 6.74, 8.17 / 8.03; 32 replicas
+// 6.54 / 6.37, 6.58 / 6.40, 7.92 / 7.74.  All requests sent to one replica, 256 replays: 8.68 / 8.74 whatever their number:
+// its cursor then runs past what either brings, and takes most records from memory.)
 __host__ __device__ constexpr int look_every(int R) { return R >= 24 ? 7 : 3; }
 // What every replica would mean for a request, written by its lane before the minimum is known; the replica with the
 // minimum is announced by its number alone.
