@@ -1357,6 +1357,7 @@ __device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Comm* co
         const unsigned long long by_cursor = PROXY ? ballot(below_cursor2 > e_gt2) : ballot(below_cursor > e_gt);
         const unsigned long long one_owner = (by_cursor & ballot((PROXY ? e_gt2 : e_gt) == 0)) |
                                              (~by_cursor & ballot((PROXY ? own_gt2 : own_gt) == cell[0]));
+        clk.tick(1);                                                 // patch, match (and the wait for the rows)
         if (__builtin_expect(behind, 0)) caught_up();
         if (!DICTATED) comm->gone[r & 1][lane] = 0.0;
         clk.tick(4);                                                 // waiting at Y
@@ -1404,7 +1405,7 @@ __device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Comm* co
                 }
             }
         }
-        clk.tick(1);                                                 // patch, match (and the wait for the rows)
+        clk.tick(1);                                                 // a longer path's rows
 
         // (every fourth or eighth request: the log record asked for the time before has arrived and becomes usable, and the
         // next one is asked for)
