@@ -173,21 +173,20 @@ struct SlotQueues {
         f_slot = -1;
     }
 
-    // Bit p: the oldest request of slot p * 64 + lane has completed by t.  Four sets are looked at together; where there are
-    // fewer left the last one stands in for them, and counts once.
+    // Bit p: the oldest request of slot p * 64 + lane has completed by t.  Four sets are looked at together, the last four
+    // once more where they are not a multiple.
     __device__ __forceinline__ unsigned due(double t, int lane) const {
-        const Slot* const h = &slot[lane];
-        auto four = [&](int p0, int p1, int p2, int p3) {
-            const double d0 = h[p0 * WAVE].h_done, d1 = h[p1 * WAVE].h_done, d2 = h[p2 * WAVE].h_done, d3 = h[p3 * WAVE].h_done;
+        auto four = [&](int p) {
+            const Slot* const h = &slot[p * WAVE + lane];
+            const double d0 = h[0].h_done, d1 = h[WAVE].h_done, d2 = h[2 * WAVE].h_done, d3 = h[3 * WAVE].h_done;
             return (d0 <= t ? 1u : 0u) | (d1 <= t ? 2u : 0u) | (d2 <= t ? 4u : 0u) | (d3 <= t ? 8u : 0u);
         };
-        if (passes == 4) return four(0, 1, 2, 3);
-        unsigned bits = four(0, 1, 2, 3);         // (more than 256 slots: rare)
-        int p = 4;
-        for (; p + 4 <= passes; p += 4) bits |= four(p, p + 1, p + 2, p + 3) << p;
-        const int last = passes - 1;
-        auto upto = [&](int k) { return k < last ? k : last; };
-        if (p < passes) bits |= (four(p, upto(p + 1), upto(p + 2), last) & ((1u << (passes - p)) - 1)) << p;
+        unsigned bits = four(0);
+        if (__builtin_expect(passes > 4, 0))                           // (more than 256 slots: rare)
+            for (int p = 4; p < passes; p += 4) {
+                const int q = p < passes - 4 ? p : passes - 4;
+                bits |= four(q) << q;
+            }
         return bits;
     }
     // Drop requests whose completion event has reached the proxy (done <= t): the oldest of the slots in `due` and
