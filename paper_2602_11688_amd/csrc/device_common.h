@@ -359,10 +359,17 @@ struct SlotQueues {
         const double done = end + half;
         *ttft_out = (first_tok + half) - t;
         *e2e_out = done - t;
-        const int at = best * B + k;
-        const unsigned bit = done <= until ? 1u << (at / WAVE) : 0u;
-        due |= lane == (at & (WAVE - 1)) ? bit : 0u;
+        due |= due_bit(best, k, lane, done, until);
         take_slot<REORDER>(s, k, none, r, end, done, weight, rec);
+    }
+
+    // The bit of `due` of the k-th slot of replica `best`, in its lane, if its request has completed by `until`.  (Told by the
+    // lane: as a test of the request first it became a branch on a vector comparison.  1,024 replays of 20,000 requests on 32
+    // replicas 12.63 -> 12.47 ms, tuners 14.90 -> 14.68, 777 of the engine model 17.51 -> 17.18.)
+    __device__ __forceinline__ unsigned due_bit(int best, int k, int lane, double done, double until) const {
+        const unsigned at = (unsigned)(best * B + k);
+        const unsigned bit = (unsigned)lane == (at & (WAVE - 1)) ? 1u << (at / WAVE) : 0u;
+        return done <= until ? bit : 0u;
     }
 
     // Service of request r on replica `best` under the engine model of a replica (continuous batching, Sec. 2.2;
@@ -416,9 +423,7 @@ struct SlotQueues {
         const double done = end + half;
         *ttft_out = (first_tok + half) - t;
         *e2e_out = done - t;
-        const int at = best * B + k;
-        const unsigned bit = done <= until ? 1u << (at / WAVE) : 0u;
-        due |= lane == (at & (WAVE - 1)) ? bit : 0u;
+        due |= due_bit(best, k, lane, done, until);
         if (lane == k) kv[s] = tokens;           // two counts below 2^31 each
         take_slot<REORDER>(s, k, none, r, end, done, weight, rec);
     }

@@ -644,7 +644,9 @@ __device__ __forceinline__ void front_wave(const SegArgs& a, int lane, Comm* com
         c.O = a.out_len[x];
         const bool has1 = r + 1 < N, has2 = r + 2 < N;
         const double t2 = (double)a.ts[has2 ? r + 2 : N - 1];
-        c.t0 = t2 * scale0;
+        // (nothing completes by the arrival of a request that there is not: the queue wavefront need not ask whether there is
+        // one; with two replays the test is the cheaper: 2,048 of 20,000 requests 16.0 / 16.25 ms)
+        c.t0 = PACK == 2 || has2 ? t2 * scale0 : -INFINITY;
         c.t1 = t2 * scale1;
         // whether all wavefronts meet once more before the next request: if it has more segments than are preloaded ...
         bool sync = a.seg_off[has1 ? r + 2 : N] - a.seg_off[has1 ? r + 1 : N] > SEG_CHUNK;
@@ -927,6 +929,7 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
     for (int b = 0; b < 2; ++b)
         if (PACK == 1 || lane < HALF) gone(b)[lane] = 0.0;
     // requests that complete by t leave the load signal between the arrivals of r - 1 and r
+    constexpr bool ASK = BLOCKS || PACK == 2;      // whether there is a next request is asked here
     auto retire = [&](unsigned due, double t, int r) { Q.template retire<!PROXY>(due, t, rec, lane, gone(r)); };
     // arrival times of the request in hand and the two after it
     double t0, t1, t2 = 0.0;
@@ -1055,13 +1058,13 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
             clk.tick(5);                                                 // outputs, tuner
             if (sync) {
                 // the request may have completed before the next one arrives, or its latency matters to the next one
-                if (r + 1 < N) retire(due, t1, r + 1);
+                if (!ASK || r + 1 < N) retire(due, t1, r + 1);
                 meet(true);                                              // Y(r)
                 due = Q.due(t2, lane);
             }
             // The completions up to the arrival of the request after next (this request's among them) do not depend on
             // where the next request goes, whose own completion the deciding wavefront has ruled out, or will wait for.
-            if (r + 2 < N) {
+            if (!ASK || r + 2 < N) {
                 retire(due, t2, r + 2);
                 if (PROXY) half2 = probe(t2, r + 2);
             }
