@@ -165,9 +165,15 @@ def section_table(sec, N, P):
              6: "batch turnover"}
     front = {0: "descriptors, row cells", 1: "waiting"}
     book = {2: "stores", 3: "waiting at the meeting X"}
+    wavefronts = [("deciding wavefront (lane = replica):", 0, decide), ("queue wavefront (lane = service slot):", 1, queue),
+                  ("front-end wavefront:", 2, front), ("book-keeping wavefront:", 2, book)]
+    if P <= 512:                       # (six wavefronts per replay)
+        wavefronts = [("deciding wavefront (lane = replica):", 0, {k: decide[k] for k in (0, 1, 3)}),
+                      ("serving wavefront (lane = service slot):", 1, {k: queue[k] for k in (0, 1, 9, 5)}),
+                      ("retiring wavefront:", 1, {2: "requests in flight", 3: "waiting at the meeting X"}),
+                      ("evicting wavefront:", 2, {4: "eviction cursors, log records", 5: "waiting at the meeting X"})] + wavefronts[2:]
     lines.append(f"shader-clock cycles per request (s_memtime), mean over {P} replays")
-    for title, row, names in (("deciding wavefront (lane = replica):", 0, decide), ("queue wavefront (lane = service slot):", 1, queue),
-                              ("front-end wavefront:", 2, front), ("book-keeping wavefront:", 2, book)):
+    for title, row, names in wavefronts:
         lines.append(title)
         for i, name in names.items():
             lines.append(f"  {name:44s} {m[row, i]:8.1f}")

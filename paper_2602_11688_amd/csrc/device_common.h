@@ -144,7 +144,8 @@ struct SlotQueues {
         return (size_t)slots(R, B) * (sizeof(Slot) + (engine ? 4 : 0));
     }
 
-    __device__ __forceinline__ void init(unsigned char* lds, int R, int B_, bool engine, int lane) {
+    // (attach: the words are there already)
+    __device__ __forceinline__ void attach(unsigned char* lds, int R, int B_) {
         const int n = slots(R, B_);
         B = B_;
         passes = n / WAVE;
@@ -152,14 +153,17 @@ struct SlotQueues {
         lanes = B >= WAVE ? ~0ull : (1ull << B) - 1;
         slot = reinterpret_cast<Slot*>(lds);
         kv = reinterpret_cast<uint32_t*>(slot + n);
-        for (int g = lane; g < n; g += WAVE) {
-            slot[g] = Slot{0.0, INFINITY, INFINITY, 0, 0, -1, -1};
-            if (engine) kv[g] = 0;
-        }
         last_start = 0.0;
         f_slot = f_next = -1;
         f_tok = 0;
         f_done = INFINITY;
+    }
+    __device__ __forceinline__ void init(unsigned char* lds, int R, int B_, bool engine, int lane) {
+        attach(lds, R, B_);
+        for (int g = lane; g < passes * WAVE; g += WAVE) {
+            slot[g] = Slot{0.0, INFINITY, INFINITY, 0, 0, -1, -1};
+            if (engine) kv[g] = 0;
+        }
     }
 
     // The record that was requested by an earlier retirement has arrived: it becomes the slot's second oldest.
@@ -317,6 +321,20 @@ struct SlotQueues {
         }
     }
 
+    // The slot with the smallest free time, lowest index on ties.  (Times are >= 0: the order of the bits is the order of the
+    // values; mostly one slot alone holds the smallest high word and the low words need not be looked at.)
+    __device__ __forceinline__ int earliest(double f, int lane) const {
+        const unsigned long long bits = (unsigned long long)__double_as_longlong(f);
+        const unsigned hi = lane < B ? (unsigned)(bits >> 32) : 0xffffffffu, lo = (unsigned)bits;
+        const unsigned mhi = wave_min_u32(hi);
+        unsigned long long ties = ballot(hi == mhi);
+        if ((ties & (ties - 1)) != 0) {
+            const unsigned mlo = wave_min_u32(hi == mhi ? lo : 0xffffffffu);
+            ties &= ballot(lo == mlo);
+        }
+        return __builtin_ctzll(ties);
+    }
+
     // Service of request r on replica `best` (the stated linear model; reproduces Eq. 1: ttft = rtt + wait +
     // prefill).  Which of the slots that are free takes the request changes no latency and no load signal as long as no
     // later request can arrive at the replica before they are free: with fixed round trip times those free by this
@@ -339,18 +357,7 @@ struct SlotQueues {
             const unsigned long long idle = ready & none;
             k = __builtin_ctzll(idle != 0 ? idle : ready);
         } else {
-            // (times are >= 0: the order of the bits is the order of the values; mostly one slot alone holds the smallest
-            // high word and the low words need not be looked at)
-            const bool in = lane < B;
-            const unsigned long long bits = (unsigned long long)__double_as_longlong(f);
-            const unsigned hi = in ? (unsigned)(bits >> 32) : 0xffffffffu, lo = (unsigned)bits;
-            const unsigned mhi = wave_min_u32(hi);
-            unsigned long long ties = ballot(hi == mhi);
-            if ((ties & (ties - 1)) != 0) {
-                const unsigned mlo = wave_min_u32(hi == mhi ? lo : 0xffffffffu);
-                ties &= ballot(lo == mlo);
-            }
-            k = __builtin_ctzll(ties);
+            k = earliest(f, lane);
             const double fv = readlane_f64(f, k);
             start = arrive > fv ? arrive : fv;
         }
@@ -370,6 +377,114 @@ struct SlotQueues {
         const unsigned at = (unsigned)(best * B + k);
         const unsigned bit = (unsigned)lane == (at & (WAVE - 1)) ? 1u << (at / WAVE) : 0u;
         return done <= until ? bit : 0u;
+    }
+
+    // Engine model: from `start` on, the time at which a request holding `tokens` is admitted, the number of requests running
+    // then and a slot that is free.  f, h: when this lane's slot becomes free and the tokens held by what runs in it.
+    __device__ __forceinline__ int admission(double f, unsigned h, unsigned tokens, double budget, int lane, double& start, int& n) const {
+        int k;
+        for (int scans = 0;; ++scans) {
+            const bool late = f > start;
+            const unsigned long long run_mask = ballot(late) & lanes;
+            n = __builtin_popcountll(run_mask);
+            k = __ffsll(~run_mask & lanes) - 1;
+            if (n == 0) break;
+            const bool running = late && lane < B;
+            bool fits = n < B;
+            if (fits && budget != 0.0) {
+                // tokens held by the running requests: two 16-bit halves summed apart (each sum below 2^22)
+                const unsigned lo = wave_sum_u32(running ? h & 0xffffu : 0u);
+                const unsigned hi = wave_sum_u32(running ? h >> 16 : 0u);
+                const double held = (double)hi * 65536.0 + (double)lo;
+                fits = held + (double)tokens <= budget;
+            }
+            if (fits || scans >= B) break;       // (the second test is not reached: every repeat has fewer running)
+            // the next time a running request ends (running ones end after `start`: positive, finite)
+            const double ends = running ? f : INFINITY;
+            start = readlane_f64(ends, wave_argmin(ends, lane, WAVE));
+        }
+        return k < 0 ? 0 : k;                    // (a free slot exists whenever fewer than B are running)
+    }
+
+    // ---- the two halves of a service where they are in the hands of two wavefronts: this one keeps the times the slots become
+    // free (and the tokens held, and the latest admissions), the other one the requests in flight.  Any slot that is ready
+    // will do, see serve().  They return the slot taken; done: when the completion event reaches the proxy.
+    template <bool REORDER>
+    __device__ __forceinline__ int start_linear(int best, double t, double half, double pf, double dec, int lane, double* ttft_out,
+                                                double* e2e_out, double* done_out) {
+        Slot* const l = &slot[best * B + (lane < B ? lane : B - 1)];
+        const double f = l->free_at;
+        const double arrive = t + half;
+        double start = arrive;
+        const unsigned long long ready = ballot(f <= (REORDER ? t : arrive)) & lanes;
+        int k = __builtin_ctzll(ready | 1ull << 63);
+        if (ready == 0) {
+            k = earliest(f, lane);
+            const double fv = readlane_f64(f, k);
+            start = arrive > fv ? arrive : fv;
+        }
+        const double first_tok = start + pf;
+        const double end = first_tok + dec;
+        const double done = end + half;
+        *ttft_out = (first_tok + half) - t;
+        *e2e_out = done - t;
+        *done_out = done;
+        if (lane == k) l->free_at = end;
+        return k;
+    }
+    __device__ __forceinline__ int start_engine(int best, double t, double half, double pf, double dec_alone, unsigned tokens, double budget,
+                                                double slowdown, int lane, double* ttft_out, double* e2e_out, double* done_out) {
+        const double arrive = t + half;
+        const double before = readlane_f64(last_start, best);
+        double start = arrive > before ? arrive : before;
+        const int s = best * B + (lane < B ? lane : B - 1);
+        int n;
+        const int k = admission(slot[s].free_at, kv[s], tokens, budget, lane, start, n);
+        last_start = lane == best ? start : last_start;
+        const double first_tok = start + pf;
+        const double factor = 1.0 + slowdown * (double)n;
+        const double dec = dec_alone * factor;
+        const double end = first_tok + dec;
+        const double done = end + half;
+        *ttft_out = (first_tok + half) - t;
+        *e2e_out = done - t;
+        *done_out = done;
+        if (lane == k) {
+            slot[s].free_at = end;
+            kv[s] = tokens;
+        }
+        return k;
+    }
+    // Request r joins the requests in flight on slot s.
+    template <bool REORDER>
+    __device__ __forceinline__ void enter(int s, int r, double done, int weight, Rec* rec, int lane) {
+        Slot* const l = &slot[s];
+        const double h_done = l->h_done, s_done = l->s_done;
+        const int tail = l->tail;
+        if (ballot(h_done == INFINITY) != 0) {
+            if (lane == 0) {
+                l->h_done = done;
+                l->h_tok = weight;
+            }
+        } else if (REORDER) {
+            if (lane == 0) queue_behind<true>(s, r, done, weight, rec);
+        } else if (ballot(s_done == INFINITY) != 0) {
+            if (lane == 0) {
+                l->s_done = done;
+                l->s_tok = weight;
+                l->s_next = -1;
+            }
+        } else {
+            // the third or deeper; the record that is on its way first, whose wait would be one for these stores as well
+            settle();
+            if (lane == 0) {
+                const long long bits = __double_as_longlong(done);
+                *reinterpret_cast<int4*>(&rec[r]) = int4{(int)bits, (int)(bits >> 32), -1, weight};
+                if (tail < 0) l->s_next = r;
+                else st(&rec[tail].next, (int32_t)r);
+                l->tail = r;
+            }
+        }
     }
 
     // Service of request r on replica `best` under the engine model of a replica (continuous batching, Sec. 2.2;
@@ -393,28 +508,8 @@ struct SlotQueues {
         const double f = slot[s].free_at;
         const unsigned h = kv[s];
         const unsigned long long none = ballot(slot[s].h_done == INFINITY);
-        int n, k;
-        for (int scans = 0;; ++scans) {
-            const bool late = f > start;
-            const unsigned long long run_mask = ballot(late) & lanes;
-            n = __builtin_popcountll(run_mask);
-            k = __ffsll(~run_mask & lanes) - 1;
-            if (n == 0) break;
-            const bool running = late && lane < B;
-            bool fits = n < B;
-            if (fits && budget != 0.0) {
-                // tokens held by the running requests: two 16-bit halves summed apart (each sum below 2^22)
-                const unsigned lo = wave_sum_u32(running ? h & 0xffffu : 0u);
-                const unsigned hi = wave_sum_u32(running ? h >> 16 : 0u);
-                const double held = (double)hi * 65536.0 + (double)lo;
-                fits = held + (double)tokens <= budget;
-            }
-            if (fits || scans >= B) break;       // (the second test is not reached: every repeat has fewer running)
-            // the next time a running request ends (running ones end after `start`: positive, finite)
-            const double ends = running ? f : INFINITY;
-            start = readlane_f64(ends, wave_argmin(ends, lane, WAVE));
-        }
-        k = k < 0 ? 0 : k;                       // (a free slot exists whenever fewer than B are running)
+        int n;
+        const int k = admission(f, h, tokens, budget, lane, start, n);
         last_start = lane == best ? start : last_start;
         const double first_tok = start + pf;
         const double factor = 1.0 + slowdown * (double)n;

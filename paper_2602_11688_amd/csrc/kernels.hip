@@ -15,6 +15,7 @@
 
 #include "device_common.h"
 #include "internal.h"
+#include "replay_apart.h"
 #include "replay_blocks.h"
 #include "replay_segments.h"
 
@@ -426,12 +427,35 @@ int prepare(const Plan& pl, double* d_small, int32_t* last, int64_t rows, hipStr
     return e == hipSuccess ? GORGO_OK : hip_fail(e, "launch prepare_replays");
 }
 
-// The segment-row kernel's instantiations: every mode with either replica model; imperfect proxy knowledge concerns the
+// Whether a launch of segment rows spreads each replay over six wavefronts instead of four: up to two replays for each of
+// the 256 CUs.  A replay's chain is then a tenth to a third shorter; with more replays per CU the quarter more vector
+// instructions a request takes is what counts.  (10,000 requests, four / six wavefronts.  512 replays: 32 replicas 6.11 / 5.67
+// ms, sweep on 16 7.69 / 5.96, engine model 8.34 / 6.72, proxy 7.50 / 7.26, tuner 7.18 / 6.33; 640 replays: 6.04 / 6.87, 7.60 /
+// 6.68, 8.06 / 7.16, 7.49 / 7.91, 7.14 / 8.08; 1,024: 6.18 / 7.50, 7.65 / 7.26, 8.44 / 8.64, 7.77 / 8.60, 7.49 / 8.00.  Two
+// replays: 5.56 / 5.01; 3 replicas 7.52 / 5.34; all requests sent to one of 13 replicas 8.36 / 5.86.)
+constexpr int SPREAD_UP_TO = 512;
+bool spread_replays(const Plan& pl) { return pl.P <= SPREAD_UP_TO; }
+
+// The segment-row kernels' instantiations: every mode with either replica model; imperfect proxy knowledge concerns the
 // cost model (fixed weights or tuned online) only.
 template <int MODE>
 void launch_segments(bool engine, bool proxy, const Plan& pl, hipStream_t s, const SegArgs& a) {
-    const dim3 grid((unsigned)pl.P), block(seg_threads<1>());
     const size_t lds = replay_queue_lds_bytes(pl.R, pl.B, engine, a.window);
+    const dim3 grid((unsigned)pl.P);
+    if (spread_replays(pl)) {
+        const dim3 block(APART_WAVES * WAVE);
+        if constexpr (MODE == MODE_COST_MODEL || MODE == MODE_ONLINE) {
+            if (proxy) {
+                if (engine) hipLaunchKernelGGL((replay_apart_kernel<MODE, true, true>), grid, block, lds, s, a);
+                else hipLaunchKernelGGL((replay_apart_kernel<MODE, false, true>), grid, block, lds, s, a);
+                return;
+            }
+        }
+        if (engine) hipLaunchKernelGGL((replay_apart_kernel<MODE, true, false>), grid, block, lds, s, a);
+        else hipLaunchKernelGGL((replay_apart_kernel<MODE, false, false>), grid, block, lds, s, a);
+        return;
+    }
+    const dim3 block(seg_threads<1>());
     if constexpr (MODE == MODE_COST_MODEL || MODE == MODE_ONLINE) {
         if (proxy) {
             if (engine) hipLaunchKernelGGL((replay_segments_kernel<MODE, true, true>), grid, block, lds, s, a);
@@ -548,6 +572,9 @@ int launch_replay(const gorgo_trace* t, const Plan& pl, const double* d_rtt, con
             if (mode == MODE_COST_MODEL && !engine && !proxy && !sections && pack_replays(pl, a.nseg)) {
                 hipLaunchKernelGGL((replay_segments_kernel<MODE_COST_MODEL, false, false, 2>), dim3((unsigned)(pl.P / 2)),
                                    dim3(seg_threads<2>()), 2 * replay_queue_lds_bytes(pl.R, pl.B, false, 0), s, a);
+            } else if (sections && spread_replays(pl)) {
+                hipLaunchKernelGGL((replay_apart_kernel<MODE_COST_MODEL, false, false, true>), dim3((unsigned)pl.P),
+                                   dim3(APART_WAVES * WAVE), replay_queue_lds_bytes(pl.R, pl.B, false, 0), s, a);
             } else if (sections) {
                 const dim3 grid((unsigned)pl.P), block(seg_threads<1>());
                 hipLaunchKernelGGL((replay_segments_kernel<MODE_COST_MODEL, false, false, 1, true>), grid, block,

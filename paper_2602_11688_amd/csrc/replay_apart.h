@@ -1,0 +1,921 @@
+// Replay kernel, segment formulation, for launches that leave most of the chip idle: six wavefronts per replay.
+//
+// A replay is one dependent chain of requests, so a launch of few replays takes as long as one of them.  What
+// replay_segments.h does in four wavefronts is here spread over six, which costs a quarter more vector instructions per
+// request (the wavefronts read the announcement and the descriptors each for themselves) and shortens the longest of
+// the chains: with a replay per SIMD the instructions are what counts, with two per CU or fewer the chain is.  The state, the
+// descriptors and the results are the same.
+//   The deciding wavefront only matches, scores, takes the minimum and announces.  Meeting X(r).
+//   The evicting wavefront holds the eviction cursors.  After X(r) it moves the one of the replica that r went to, while r + 1
+// is being decided against the cursors as they stand in LDS.  That makes no difference to r + 1 unless it matches blocks on
+// that replica whose last request is among the oldest the cursor has in hand; then the deciding wavefront waits for it.
+//   The serving wavefront serves r (which slot, from when, until when) and has the latencies, hence the tuner.
+//   The retiring wavefront keeps the requests in flight: it enters r - 1, and takes from the load signals what completes by
+// the arrival of r + 2.  That r itself completes by then is the serving wavefront's business.
+//   The book-keeping wavefront stores, and touches what the front end is about to read, so that it comes from the L2: vector
+// memory accesses of a wavefront complete in order, and in the front end a row's way from memory would hold up the cells.
+//   The front end is the one of replay_segments.h.
+// (A fifth wavefront for the cursors alone left the queue wavefront as the longest chain: 64 replays of 20,000 requests on 8
+// replicas 14.2 -> 12.7 ms, with its two halves apart 12.0.)
+// Meetings as there: X(r) at every request, Y(r) where the descriptor of r says so.
+#pragma once
+#include "device_common.h"
+#include "internal.h"
+#include "replay_segments.h"
+
+namespace gorgo {
+
+constexpr int APART_WAVES = 6;
+constexpr int APART_LOOK = 16;       // log records of look-ahead kept in LDS per replica and cursor
+constexpr int OWN_WALK = -4;         // in Choice::owner: several previous owners, or a path that goes past the preloaded rows
+
+// A request on its way from the serving to the retiring wavefront.
+struct Served {
+    double done;         // time its completion event reaches the proxy
+    int32_t at;          // service slot, -1: it has completed already
+    int32_t weight;      // what it takes from the load signal
+};
+template <bool PROXY>
+struct ApartHandover : QueueHandover<PROXY> {
+    static constexpr bool APART = true;
+    int32_t cells[CELL_SETS][SEG_CHUNK][WAVE];    // [request mod 3]: row cells of the request's first eight segments per replica
+    unsigned long long look[PROXY ? 2 : 1][APART_LOOK * WAVE];       // rings of the cursors (one slot is always free)
+    SegDesc ring[DESC_RING];
+    Served served[2];                     // [request mod 2]
+    // Where the eviction cursors are, per replica.
+    int32_t cur_r[PROXY ? 2 : 1][WAVE];   // request
+    uint32_t k_room[WAVE];                // the cache's cursor's position | room << 16
+    int32_t cur_k2[PROXY ? WAVE : 1];     // the index's cursor's position
+    int32_t hi[WAVE];                     // youngest record in the ring (of either cursor): a request that adds no more than `room`
+                                          // blocks, none of them taken from records up to this one, moves no cursor past it
+    int32_t evicted;                      // the cursors are up to date with the requests up to this one
+    int32_t walked;                       // a request whose previous owners have been looked up
+};
+
+// ---------------------------------------------------------------------------------------------- evicting
+// What the latest request changes in the log, which the book-keeping wavefront is writing at the same time.
+struct LogChange {
+    int r;               // the request (its own record cannot be loaded yet)
+    int tail;            // on the replica it went to: the request it is linked behind (elsewhere no record's number)
+    int owner, end;      // ... and the one whose owned suffix now starts at `end`
+};
+// Eviction cursor of one LRU over a replica's log of routed requests, held by lane = replica: as EvictCursor, but with the
+// log's links followed as requests are added.
+struct ApartCursor {
+    int cur_r = -1, cur_k = 0, cur_own = 0;
+    int fill_r = -1;                     // the record to be read next (-1: the log has been read to its end)
+    int pend_r = -1, pend_own = -1, pend_link = -1;      // record being fetched, and what has changed in it meanwhile
+    unsigned long long raw = 0;          // the record asked for
+    unsigned long long* ring = nullptr;  // records packed as r | own << 32 | n << 48, ring_cnt of them from slot ring_head on
+    int ring_head = 0, ring_cnt = 0, ring_hi = -1, stock = 0;        // the youngest; blocks they own
+    unsigned long long next = ~0ull;     // the record at ring_head, read at the end of the request before
+    int over = 0;                        // blocks this LRU holds beyond its capacity (below 0: room)
+    int n_spot = 0, n_adv = 0, n_dead = 0;       // statistics of the timed instantiation
+
+    __device__ __forceinline__ void init(unsigned long long* look, int lane) {
+        ring = look + lane;
+        for (int k = 0; k < APART_LOOK; ++k) *at(k) = ~0ull;
+    }
+    __device__ __forceinline__ unsigned long long* at(int k) const { return ring + ((k & (APART_LOOK - 1)) * WAVE); }
+
+    // In the lanes with `who` set, what was asked for has arrived: a record, which is dropped if it owns nothing and else
+    // joins the ring.  Straight-line code: lanes with nothing pending go through it unchanged (every lane stores to LDS:
+    // those with nothing for the ring into its free slot).
+    __device__ __forceinline__ void take_pending(unsigned long long got, bool who = true) {
+        const bool have = who && pend_r >= 0;
+        const unsigned hi = (unsigned)(got >> 32);
+        const int n = (int)(hi >> 16);
+        const int own_mem = (int)(hi & 0xFFFFu);
+        const int own = pend_own > own_mem ? pend_own : own_mem;
+        const bool alive = have && own < n;
+        *at(ring_head + ring_cnt) = (unsigned long long)(unsigned)pend_r | ((unsigned long long)((hi & 0xFFFF0000u) | (unsigned)own) << 32);
+        ring_cnt += alive ? 1 : 0;
+        ring_hi = alive ? pend_r : ring_hi;
+        stock += alive ? n - own : 0;
+        n_dead += have && !alive ? 1 : 0;
+        const int link = (int)(unsigned)got;
+        fill_r = have ? (pend_link > link ? pend_link : link) : fill_r;
+        pend_r = have ? -1 : pend_r;
+    }
+    __device__ __forceinline__ void expect(bool want, const LogChange& f) {
+        pend_r = want ? fill_r : -1;
+        pend_own = fill_r == f.owner ? f.end : -1;
+        pend_link = fill_r == f.tail ? f.r : -1;
+    }
+    // Asks for the next record of the log where the ring has room for it (`spare`, the record behind the log, where
+    // there is nothing to fetch).  Called when nothing is pending.
+    __device__ __forceinline__ void ask(const unsigned long long* log64, int spare, const LogChange& f) {
+        const bool want = fill_r >= 0 && fill_r != f.r && ring_cnt < APART_LOOK - 1;
+        expect(want, f);
+        raw = ld(&log64[want ? fill_r : spare]);
+    }
+    // request f.r is added to the log behind request f.tail, in the lanes with `here` set
+    __device__ __forceinline__ void append(bool here, const LogChange& f) {
+        fill_r = here && fill_r < 0 ? f.r : fill_r;
+        pend_link = here && pend_r == f.tail ? f.r : pend_link;
+    }
+    // Request `owner`'s owned suffix now starts at `end`, in the lanes concerned (elsewhere a request that is no record's).
+    // Returns whether it may be one of the records in the ring: then disowned_in_ring is the call to make as well.
+    __device__ __forceinline__ bool disowned(int owner, int end) {
+        cur_own = owner == cur_r ? end : cur_own;
+        pend_own = owner == pend_r ? end : pend_own;
+        return ring_cnt > 0 && owner <= ring_hi;
+    }
+    __device__ __forceinline__ void disowned_in_ring(int owner, int end) {
+#pragma nounroll
+        for (int k = 0; k < APART_LOOK; ++k) {
+            const unsigned long long e = *at(k);
+            const bool it = ((k - ring_head) & (APART_LOOK - 1)) < ring_cnt && (int)(unsigned)e == owner;
+            if (it) *at(k) = (e & ~(0xFFFFull << 32)) | ((unsigned long long)(unsigned)end << 32);
+            stock -= it ? end - (int)((e >> 32) & 0xFFFFu) : 0;
+        }
+    }
+    // takes up to E blocks from the owned suffix of the cursor's record
+    __device__ __forceinline__ void take_from_cursor(int& E) {
+        int avail = cur_k - cur_own;
+        avail = avail > 0 ? avail : 0;
+        const int take = avail < E ? avail : E;
+        cur_k -= take;
+        E -= take;
+    }
+    // the cursor moves on to record e, the one at ring_head, in the lanes with `go` set
+    __device__ __forceinline__ void step_to(unsigned long long e, bool go) {
+        const unsigned hi = (unsigned)(e >> 32);
+        n_adv += go ? 1 : 0;
+        cur_r = go ? (int)(unsigned)e : cur_r;
+        cur_k = go ? (int)(hi >> 16) : cur_k;
+        cur_own = go ? (int)(hi & 0xFFFFu) : cur_own;
+        stock -= go ? (int)(hi >> 16) - (int)(hi & 0xFFFFu) : 0;
+        ring_head += go ? 1 : 0;
+        ring_cnt -= go ? 1 : 0;
+    }
+    // `added` blocks have joined the LRU: what the cursor's own record can give up, then the next one (read ahead), then
+    // further ones.
+    __device__ __forceinline__ void evict(int added, const unsigned long long* log64, int spare, const LogChange& f) {
+        over += added;
+        int E = over > 0 ? over : 0;
+        over -= E;
+        take_from_cursor(E);
+        if (ballot(E > 0) != 0) {
+            step_to(next, E > 0 && ring_cnt > 0);
+            take_from_cursor(E);             // (lanes with E = 0 take nothing)
+            if (__builtin_expect(ballot(E > 0) != 0, 0)) advance(E, log64, spare, f);
+        }
+    }
+    __device__ __forceinline__ void look_ahead() { next = *at(ring_head); }
+    // The cursor moves on to further records until E blocks have been given up (all lanes together, those with
+    // nothing to evict unchanged): records come from the ring, and from memory on the spot when the ring has run
+    // out.  Works on a copy of the state, written back at the end: the request loop's common path, which does not
+    // come here, then carries no register copies for this loop's sake.
+    __device__ __forceinline__ void advance(int E_in, const unsigned long long* log64, int spare, const LogChange& f) {
+        ApartCursor w = *this;
+        int E = E_in;
+        w.advance_loop(E, log64, spare, f);
+        *this = w;
+    }
+    __device__ __forceinline__ void advance_loop(int& E, const unsigned long long* log64, int spare, const LogChange& f) {
+        do {
+            const bool empty = E > 0 && ring_cnt == 0;
+            if (ballot(empty) != 0) {
+                if (ballot(empty && pend_r >= 0) != 0) {             // what has been asked for is on its way
+                    take_pending(raw, empty);
+                    continue;
+                }
+                // (no record, or the latest request's own, whose blocks are the last to go: cannot happen while blocks are
+                // to be evicted; bounds the loop)
+                const bool stuck = empty && (fill_r < 0 || fill_r == f.r);
+                const bool fetch = empty && !stuck;
+                E = stuck ? 0 : E;
+                const unsigned long long got = ld(&log64[fetch ? fill_r : spare]);
+                if (fetch) expect(true, f);
+                n_spot += fetch ? 1 : 0;
+                take_pending(got, fetch);
+                continue;
+            }
+            step_to(*at(ring_head), E > 0);
+            take_from_cursor(E);
+        } while (ballot(E > 0) != 0);
+    }
+    // blocks that may join before the cursor passes the last record of the ring (saturated: a request has fewer than 2^16)
+    __device__ __forceinline__ unsigned room() const {
+        const int avail = cur_k - cur_own;
+        const unsigned x = (unsigned)(stock + (avail > 0 ? avail : 0)) + (unsigned)(0 - over);
+        return x < 0xFFFFu ? x : 0xFFFFu;
+    }
+};
+
+template <bool PROXY, bool TIMED, class Comm>
+__device__ __forceinline__ void apart_evict_wave(const SegArgs& a, int lane, Comm* comm) {
+    const int R = a.R, N = (int)a.N;
+    const size_t p = blockIdx.x;
+    const unsigned row_bytes = (unsigned)R * 4u;
+    const unsigned spare_row = (unsigned)(a.nseg - 1) * row_bytes;
+    const unsigned lane_off = (unsigned)(lane < R ? lane : 0) * 4u;
+    const char* const rows = reinterpret_cast<const char*>(a.last + p * (size_t)a.nseg * R);
+    auto cell_at = [&](uint32_t rowoff) { return reinterpret_cast<const int32_t*>(rows + (rowoff + lane_off)); };
+    LogRec* const log = a.log + p * ((size_t)N + 1);
+    const unsigned long long* const log64 = reinterpret_cast<const unsigned long long*>(log);
+    const int spare = N;                      // the log record behind the last request's
+    int tail_r = -1;                          // youngest request routed to replica = lane
+    const int index_cap = PROXY && a.index_blocks > 0 ? (int)a.index_blocks : 0;
+    const bool bounded = a.C > 0, forgets = PROXY && index_cap > 0;
+    ApartCursor c1, c2;                       // the cache's, the index's
+    c1.init(comm->look[0], lane);
+    c1.over = bounded ? -(int)a.C : -INT32_MAX;
+    if (PROXY) {
+        c2.init(comm->look[PROXY ? 1 : 0], lane);
+        c2.over = forgets ? -index_cap : -INT32_MAX;
+    }
+    const int every = look_every(R);
+    int n_walks = 0;
+    // (`hi` is written first and read last: the deciding wavefront may look in between)
+    auto publish = [&]() {
+        const unsigned room1 = c1.room(), room2 = PROXY ? c2.room() : room1;
+        comm->hi[lane] = PROXY && c2.ring_hi > c1.ring_hi ? c2.ring_hi : c1.ring_hi;
+        asm volatile("" ::: "memory");
+        comm->cur_r[0][lane] = c1.cur_r;
+        comm->k_room[lane] = (unsigned)c1.cur_k | (room2 < room1 ? room2 : room1) << 16;
+        if constexpr (PROXY) {
+            comm->cur_r[1][lane] = c2.cur_r;
+            comm->cur_k2[lane] = c2.cur_k;
+        }
+    };
+    publish();
+    comm->evicted = comm->walked = -1;
+    meet(true);                               // the first descriptors are there
+    meet(true);
+    SectionClock<TIMED> clk;
+    clk.start();
+    for (int r = 0; r < N; ++r) {
+        const SegDesc* const d = &comm->ring[r & (DESC_RING - 1)];
+        const int n = d->n, s = __builtin_amdgcn_readfirstlane(d->s), flags = __builtin_amdgcn_readfirstlane(d->flags);
+        clk.tick(4);                                                 // cursors
+        meet(true);                                                  // X(r)
+        clk.tick(5);                                                 // waiting at X
+        const int best = comm->best[r & 1][0];
+        const Choice<PROXY> c = comm->choice[r & 1][lane];           // (of this lane's replica: no second trip to LDS)
+        const bool is_best = lane == best;
+        int owner = is_best ? c.owner : spare;
+        const int end = (int)(c.hit_end >> 16);
+        if (__builtin_expect(ballot(owner == OWN_WALK) != 0, 0)) {
+            // The segments that this request takes over on the chosen replica have several previous owners: along the path
+            // these form runs; each run moves its owner's `own` to the end of the run.  Only what is held matters (what is
+            // evicted belongs to requests the cursor has passed, or to the cursor's request beyond its position).  The rows are
+            // read as they still are: the book-keeping wavefront waits.
+            ++n_walks;
+            bool walking = owner == OWN_WALK;
+            const int cb_r = PROXY ? c2.cur_r : c1.cur_r, cb_k = PROXY ? c2.cur_k : c1.cur_k;
+            int run_owner = -1, run_end = 0, vpos = 0;
+            auto changed = [&](int of, int to) {
+                st(&log[of].own, (uint16_t)to);
+                if (c1.disowned(of, to)) c1.disowned_in_ring(of, to);
+                if (PROXY && c2.disowned(of, to)) c2.disowned_in_ring(of, to);
+            };
+            const int64_t j0 = d->j0;
+            for (int j = 0; j < s && ballot(walking) != 0; j += SEG_CHUNK) {
+                int32_t at[SEG_CHUNK];
+                int to[SEG_CHUNK];
+#pragma unroll
+                for (int k = 0; k < SEG_CHUNK; ++k) {
+                    // (past the last segment: nothing)
+                    const SegRef sr = a.seg[j0 + (j + k < s ? j + k : s - 1)];
+                    const bool fresh = (sr.end & SEG_FRESH) != 0 || j + k >= s;
+                    to[k] = sr.end & SEG_END_MASK;
+                    at[k] = ld(cell_at(fresh ? spare_row : (uint32_t)sr.id * row_bytes));
+                    at[k] = fresh ? NEVER_CACHED : at[k];
+                }
+#pragma unroll
+                for (int k = 0; k < SEG_CHUNK; ++k) {
+                    const int cnt = walking ? cached_in(at[k], vpos, to[k], cb_r, cb_k) : 0;
+                    if (cnt > 0) {
+                        if (at[k] != run_owner && run_owner >= 0) changed(run_owner, run_end);
+                        run_owner = at[k];
+                        run_end = to[k];
+                    }
+                    walking = walking && cnt == to[k] - vpos;
+                    vpos = to[k];
+                }
+            }
+            if (run_owner >= 0) changed(run_owner, run_end);
+            owner = owner == OWN_WALK ? spare : owner;
+            c1.look_ahead();
+            if (PROXY) c2.look_ahead();
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            comm->walked = r;
+        }
+        if (bounded) {
+            const LogChange f{r, is_best ? tail_r : N, owner, end};
+            c1.append(is_best, f);
+            const bool in_ring = c1.disowned(owner, end);
+            bool in_ring2 = false;
+            if (PROXY) {
+                c2.append(is_best, f);
+                in_ring2 = c2.disowned(owner, end);
+            }
+            if (__builtin_expect(ballot(in_ring || in_ring2) != 0, 0)) {
+                if (in_ring) c1.disowned_in_ring(owner, end);
+                if (PROXY && in_ring2) c2.disowned_in_ring(owner, end);
+                c1.look_ahead();
+                if (PROXY) c2.look_ahead();
+            }
+            c1.evict(is_best ? n - (int)(c.hit_end & 0xFFFFu) : 0, log64, spare, f);
+            if constexpr (PROXY) {
+                if (forgets) c2.evict(is_best ? n - c.seen : 0, log64, spare, f);
+            }
+            publish();
+            asm volatile("" ::: "memory");
+            comm->evicted = r;
+            // (records arrive every so often for all replicas, and whenever a request goes to one whose ring has run low)
+            if ((r & every) == every || ballot(is_best && c1.ring_cnt < APART_LOOK / 4) != 0) {
+                c1.take_pending(c1.raw);
+                c1.ask(log64, spare, f);
+                if (PROXY && forgets) {
+                    c2.take_pending(c2.raw);
+                    c2.ask(log64, spare, f);
+                }
+            }
+            c1.look_ahead();
+            if (PROXY) c2.look_ahead();
+            tail_r = is_best ? r : tail_r;
+        } else {
+            comm->evicted = r;
+        }
+        if (flags & DESC_SYNC) meet(true);                           // Y(r)
+    }
+    if (TIMED && a.sections) {
+        // (with statistics of the eviction walk, summed over the replicas)
+        const unsigned spot = wave_sum_u32((unsigned)c1.n_spot), adv = wave_sum_u32((unsigned)c1.n_adv),
+                       dead = wave_sum_u32((unsigned)c1.n_dead);
+        if (lane == 0) {
+            unsigned long long* const out = a.sections + p * 3 * SECTIONS;
+            out[2 * SECTIONS + 4] = clk.acc[4];
+            out[2 * SECTIONS + 5] = clk.acc[5];
+            out[8] = spot;
+            out[9] = adv;
+            out[10] = dead;
+            out[11] = (unsigned)n_walks;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------- book-keeping
+// As book_wave of replay_segments.h; also touches, eight requests at a time, the rows and the lines of the trace that the front
+// end is going to read.  (Loads whose values only keep them: this wavefront waits for none.)
+template <bool PROXY, bool TIMED, class Comm>
+__device__ __forceinline__ void apart_book_wave(const SegArgs& a, int lane, Comm* comm) {
+    const int R = a.R, N = (int)a.N;
+    const size_t p = blockIdx.x;
+    const bool in = lane < R;
+    const unsigned row_bytes = (unsigned)R * 4u;
+    const unsigned spare_row = (unsigned)(a.nseg - 1) * row_bytes;
+    char* const rows = reinterpret_cast<char*>(a.last + p * (size_t)a.nseg * R);
+    auto cell_of = [&](uint32_t rowoff, int replica) -> int32_t* {
+        return reinterpret_cast<int32_t*>(rows + (rowoff + (unsigned)replica * 4u));
+    };
+    auto cell_at = [&](uint32_t rowoff) -> int32_t* { return cell_of(rowoff, in ? lane : 0); };
+    LogRec* const log = a.log + p * ((size_t)N + 1);
+    unsigned long long* const log64 = reinterpret_cast<unsigned long long*>(log);
+    // the lanes that reset the row of a fresh last segment, and the replica of each
+    const bool reset_lane = R <= 32 && lane >= 32;
+    const int reset_rep = lane - 32 < R ? lane - 32 : R - 1;
+    int tail_r = -1;                          // youngest request routed to replica = lane
+    int o_route = 0, o_hit = 0, o_seen = 0;
+    int touched = 0;
+    const bool wide = (row_bytes & 127u) != 0 || row_bytes > 128u;      // (rows that straddle a cache line, or are longer)
+    const int64_t refs = a.seg_off[N];
+    // (a lane per array; a group of eight requests is 32 or 64 bytes of each; one reference behind the last is there to be read)
+    auto touch_trace = [&](int x, int64_t j0) {
+        const int64_t r = x < N ? x : N - 1;
+        const void* at = &a.ts[r];
+        at = lane == 1 ? (const void*)&a.seg_off[r] : at;
+        at = lane == 2 ? (const void*)&a.blk_off[r] : at;
+        at = lane == 3 ? (const void*)&a.in_len[r] : at;
+        at = lane == 4 ? (const void*)&a.out_len[r] : at;
+        const int64_t j = j0 + (lane - 4) * 16;
+        at = lane >= 5 && lane < 21 ? (const void*)&a.seg[j < refs ? j : refs] : at;
+        return ld(reinterpret_cast<const int32_t*>(at));
+    };
+    meet(true);                               // the first descriptors are there
+    meet(true);
+    SectionClock<TIMED> clk;
+    clk.start();
+    for (int r = 0; r < N; ++r) {
+        const SegDesc* const d = &comm->ring[r & (DESC_RING - 1)];
+        const uint32_t of_seg = d->slot[lane & (SEG_CHUNK - 1)], of_tail = d->tail;
+        const int n = d->n, s = __builtin_amdgcn_readfirstlane(d->s), flags = __builtin_amdgcn_readfirstlane(d->flags);
+        clk.tick(2);                                                 // stores
+        meet(true);                                                  // X(r)
+        clk.tick(3);                                                 // waiting at X
+        const int best = comm->best[r & 1][0];
+        const Choice<PROXY> c = comm->choice[r & 1][lane];           // (of this lane's replica: no second trip to LDS)
+        const bool is_best = lane == best;
+        // (several previous owners: the evicting wavefront looks them up in the rows as they still are, and stores the changes)
+        if (__builtin_expect(ballot(is_best && c.owner == OWN_WALK) != 0, 0))
+            while (ld(&comm->walked) < r) __builtin_amdgcn_s_sleep(1);
+        // every segment of the request is now last touched by r on the chosen replica (lanes k, k + 8, ...: segment k); fresh ones
+        // start over (see book_wave)
+        {
+            const int rep = reset_lane ? reset_rep : best;
+            const int32_t val = reset_lane && rep != best ? NEVER_CACHED : r;
+            const uint32_t off = reset_lane ? (lane - 32 < R ? of_tail : spare_row) : of_seg;
+            st(cell_of(off, rep), val);
+        }
+        if (flags & (DESC_FRESH_MORE | DESC_DEEP)) {      // (one test on the usual path for the two rare cases)
+            const int32_t fresh_cell = is_best ? r : NEVER_CACHED;
+            if (flags & DESC_FRESH_MORE) {
+                const int first_fresh = (flags >> 16) & 15;
+                const int stop = (s < SEG_CHUNK ? s : SEG_CHUNK) - ((flags & DESC_FRESH_TAIL) ? 1 : 0);
+                for (int k = first_fresh; k < stop; ++k) {
+                    const uint32_t off = d->slot[k];
+                    st(cell_at(in ? off : spare_row), fresh_cell);
+                }
+            }
+            if (flags & DESC_DEEP) {
+                const int64_t j0 = d->j0;
+                for (int j = SEG_CHUNK; j < s; ++j) {
+                    const SegRef sr = a.seg[j0 + j];
+                    const uint32_t off = (uint32_t)sr.id * row_bytes;
+                    if (sr.end & SEG_FRESH) st(cell_at(in ? off : spare_row), fresh_cell);
+                    else if (is_best) st(cell_at(off), r);
+                }
+            }
+        }
+        st(&log64[r], 0xFFFFFFFFull | ((unsigned long long)n << 48));      // next -1, own 0, n
+        st(&log[is_best && tail_r >= 0 ? tail_r : N].next, r);
+        st(&log[is_best && c.owner >= 0 ? c.owner : N].own, (uint16_t)(c.hit_end >> 16));
+        tail_r = is_best ? r : tail_r;
+        if ((r & (DESC_GROUP - 1)) == 3) {
+            // (the rows of the eight requests from the next multiple of eight on: their descriptors are there but for the last words)
+            asm volatile("" ::"v"(touched));
+            const SegDesc& x = comm->ring[((r & ~(DESC_GROUP - 1)) + DESC_AHEAD + lane / SEG_CHUNK) & (DESC_RING - 1)];
+            const uint32_t off = x.rowoff[lane % SEG_CHUNK];
+            touched = ld(reinterpret_cast<const int32_t*>(rows + off));
+            if (wide) touched ^= ld(reinterpret_cast<const int32_t*>(rows + (off + row_bytes - 4u)));
+            touched ^= touch_trace(r + 5 * DESC_GROUP, d->j0);
+        }
+        const int slot = r & (WAVE - 1);
+        const bool mine = lane == slot;
+        auto of_best = [&](int x) { return __builtin_amdgcn_readlane(x, __builtin_amdgcn_readfirstlane(best)); };
+        const int hit = of_best((int)(c.hit_end & 0xFFFFu));          // (by all lanes together)
+        o_route = mine ? best : o_route;
+        o_hit = mine ? hit : o_hit;
+        if constexpr (PROXY) {
+            const int seen = of_best(c.seen);
+            o_seen = mine ? seen : o_seen;
+        }
+        if (slot == WAVE - 1 || r == N - 1) {
+            const int x = r - slot + lane;
+            if (lane <= slot) {
+                const size_t o = p * N + x;
+                if (a.route) a.route[o] = (uint8_t)o_route;
+                if (a.hit) a.hit[o] = (uint16_t)o_hit;
+                if (PROXY && a.believed) a.believed[o] = (uint16_t)o_seen;
+            }
+        }
+        if (flags & DESC_SYNC) meet(false);                          // Y(r)
+    }
+    asm volatile("" ::"v"(touched));
+    if (TIMED && a.sections && lane == 0) {
+        a.sections[(p * 3 + 2) * SECTIONS + 2] = clk.acc[2];
+        a.sections[(p * 3 + 2) * SECTIONS + 3] = clk.acc[3];
+    }
+}
+
+// ---------------------------------------------------------------------------------------------- retiring
+// Retiring wavefront: the lists of requests in flight (all of SlotQueues but the times the slots become free).  After X(r)
+// it enters r - 1, which has not completed by the arrival of r + 1 (else the serving wavefront has dealt with it), and retires
+// what completes by the arrival of r + 2, r itself aside.
+template <bool PROXY, bool TIMED, class Comm>
+__device__ __forceinline__ void apart_retire_wave(const SegArgs& a, int lane, SlotQueues& Q, Comm* comm) {
+    const int N = (int)a.N;
+    Rec* const rec = a.rec + (size_t)blockIdx.x * N;
+    const double sc = a.scale[blockIdx.x];
+    if (lane == 0) comm->served[1].at = -1;   // (there is nothing before the first request)
+    meet(true);                               // the first descriptors are there
+    double t1 = (double)a.ts[N > 1 ? 1 : 0] * sc;
+    meet(true);
+    auto retire = [&](unsigned due, double t, int r) { Q.template retire<!PROXY>(due, t, rec, lane, comm->gone[r & 1]); };
+    SectionClock<TIMED> clk;
+    clk.start();
+    for (int r = 0; r < N; ++r) {
+        const SegDesc& d = comm->ring[r & (DESC_RING - 1)];
+        const bool sync = (__builtin_amdgcn_readfirstlane(d.flags) & DESC_SYNC) != 0;
+        const double t2 = d.t2[0];
+        clk.tick(2);                                                 // retiring
+        meet(true);                                                  // X(r)
+        clk.tick(3);                                                 // waiting at X
+        const Served x = comm->served[(r - 1) & 1];
+        const int at = __builtin_amdgcn_readfirstlane(x.at);
+        if (at >= 0) Q.template enter<PROXY>(at, r - 1, x.done, x.weight, rec, lane);
+        if (sync) {
+            retire(Q.due(t1, lane), t1, r + 1);
+            meet(true);                                              // Y(r)
+        }
+        retire(Q.due(t2, lane), t2, r + 2);
+        t1 = t2;
+    }
+    if (TIMED && a.sections && lane == 0) {
+        for (int k = 2; k < 4; ++k) a.sections[((size_t)blockIdx.x * 3 + 1) * SECTIONS + k] = clk.acc[k];
+    }
+}
+
+// ---------------------------------------------------------------------------------------------- serving
+// Serving wavefront: after X(r) it serves r and hands it to the retiring wavefront, unless r completes by the arrival of
+// r + 2: then it takes r from the load signal itself.  The times at which the slots become free are its own.
+template <int MODE, bool ENGINE, bool PROXY, bool TIMED, class Comm>
+__device__ __forceinline__ void apart_serve_wave(const SegArgs& a, int lane, SlotQueues& Q, double* window, Comm* comm) {
+    constexpr bool COUNTS = MODE == MODE_LEAST_REQUEST;      // the load signal is the number of requests, not their tokens
+    const int N = (int)a.N;
+    const size_t p = blockIdx.x;
+    const double sc = a.scale[p];
+    Tuner<MODE == MODE_ONLINE> tuner(a, p, window, lane);
+    if (MODE == MODE_ONLINE && lane < 3) comm->w[0][lane] = a.params[3 * p + lane];
+    ProbeEpochs<PROXY> probes(a, lane);
+    // proxy variants: half the round trip time of replica = lane, the request in hand's and the next two's
+    double half0 = 0.0, half1 = 0.0, half2 = 0.0;
+    if constexpr (!PROXY) comm->half[lane] = lane < a.R ? 0.5 * a.rtt[lane] : 0.0;
+    // engine model: this lane's replica has its own rates and KV budget
+    const double my_a_pf = ENGINE && lane < a.R ? a.eng_a_pf[lane] : 0.0;
+    const double my_a_dec = ENGINE && lane < a.R ? a.eng_a_dec[lane] : 0.0;
+    const double my_budget = ENGINE && lane < a.R ? a.eng_budget[lane] : 0.0;
+    meet(true);                               // the first descriptors are there
+    for (int b = 0; b < 2; ++b) comm->gone[b][lane] = 0.0;
+    // arrival times of the request in hand and the two after it
+    double t0 = (double)a.ts[0] * sc, t1 = (double)a.ts[N > 1 ? 1 : 0] * sc;
+    if (PROXY) {
+        half0 = probes.at(t0, 0, comm);
+        if (N > 1) half1 = probes.at(t1, 1, comm);
+    }
+    meet(true);                               // (nothing has completed yet: the first request can be decided)
+    double o_ttft = 0.0, o_e2e = 0.0;
+    SectionClock<TIMED> clk;
+    clk.start();
+    for (int b0 = 0; b0 < N; b0 += WAVE) {
+        const int in_batch = N - b0 < WAVE ? N - b0 : WAVE;
+        for (int i = 0; i < in_batch; ++i) {
+            const int r = b0 + i;
+            const SegDesc& d = comm->ring[r & (DESC_RING - 1)];
+            const int4 h = *reinterpret_cast<const int4*>(&d.L);
+            const int L = h.x, O = ENGINE ? d.O : 0;
+            const double t2 = d.t2[0], dec = ENGINE ? 0.0 : d.dec;
+            const bool sync = (__builtin_amdgcn_readfirstlane(h.w) & DESC_SYNC) != 0;
+            clk.tick(0);
+            meet(true);                                                  // X(r)
+            clk.tick(1);                                                 // waiting at X
+            const int best = __builtin_amdgcn_readfirstlane(comm->best[r & 1][0]);
+            const double prefill = (double)comm->choice[r & 1][best].prefill;
+            double half;
+            if constexpr (PROXY) half = readlane_f64(half0, best);
+            else half = comm->half[best];
+            double ttft, e2e, done;
+            int k;
+            if constexpr (ENGINE)
+                k = Q.start_engine(best, t0, half, readlane_f64(my_a_pf, best) * prefill, readlane_f64(my_a_dec, best) * (double)O,
+                            (unsigned)L + (unsigned)O, readlane_f64(my_budget, best), a.eng_slowdown, lane, &ttft, &e2e, &done);
+            else
+                k = Q.template start_linear<PROXY>(best, t0, half, PROXY ? a.a_pf * prefill : prefill, dec, lane, &ttft, &e2e, &done);
+            clk.tick(9);                                                 // service
+            const int weight = COUNTS ? 1 : L;
+            bool left = done <= (sync ? t1 : t2);
+            // (the same in every lane)
+            auto leave = [&](int to) {
+                if (lane == 0)
+                    __hip_atomic_fetch_add(&comm->gone[to & 1][best], -(double)weight, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            };
+            if (__builtin_expect(ballot(left) != 0, 0)) leave(sync ? r + 1 : r + 2);
+            o_ttft = lane == i ? ttft : o_ttft;
+            o_e2e = lane == i ? e2e : o_e2e;
+            if constexpr (MODE == MODE_ONLINE) tuner.sample(ttft, comm->w[0]);
+            clk.tick(5);                                                 // outputs, tuner
+            if (sync) {
+                meet(true);                                              // Y(r)
+                const bool now = !left && done <= t2;
+                if (ballot(now) != 0) leave(r + 2);
+                left = left || now;
+            }
+            comm->served[r & 1] = Served{done, left ? -1 : best * Q.B + k, weight};
+            if (PROXY) {
+                half2 = probes.at(t2, r + 2, comm);
+                half0 = half1;
+                half1 = half2;
+            }
+            t0 = t1;
+            t1 = t2;
+        }
+        // the batch is done: its outputs go out
+        if (lane < in_batch) {
+            const size_t o = p * N + b0 + lane;
+            if (a.ttft) a.ttft[o] = o_ttft;
+            if (a.e2e) a.e2e[o] = o_e2e;
+        }
+    }
+    if (TIMED && a.sections && lane == 0)
+        for (int k = 0; k < SECTIONS; ++k)
+            if (k != 2 && k != 3) a.sections[(p * 3 + 1) * SECTIONS + k] = clk.acc[k];
+    tuner.results();
+}
+
+// ---------------------------------------------------------------------------------------------- deciding
+template <int MODE, bool ENGINE, bool PROXY, bool TIMED, class Comm>
+__device__ __forceinline__ void apart_decide_wave(const SegArgs& a, int lane, Comm* comm) {
+    constexpr bool ONLINE = MODE == MODE_ONLINE;
+    constexpr bool SCORED = MODE == MODE_COST_MODEL || MODE == MODE_ONLINE;
+    constexpr bool COUNTS = MODE == MODE_LEAST_REQUEST;
+    constexpr bool DICTATED = MODE == MODE_AFFINITY || MODE == MODE_RANDOM;
+    const int R = a.R, N = (int)a.N;
+    const size_t p = blockIdx.x;
+    const bool in = lane < R;
+    double w_rtt = a.params[3 * p + 0], w_prefill = a.params[3 * p + 1], w_queue = a.params[3 * p + 2];
+    double my_rtt = !PROXY && in ? a.rtt[lane] : 0.0;            // (proxy variants: comes from the serving wavefront)
+    // first product of Eq. 3 (lanes without a replica: a score above any)
+    double rtt_term = in ? w_rtt * my_rtt : INFINITY;
+    double q = COUNTS && !in ? INFINITY : 0.0;       // load signal of replica = lane (an integer below 2^53, exact in fp64)
+    double tokens = 0.0;                             // what the request before adds to it where it went
+    const bool own_index = PROXY && a.index_blocks >= 0;
+    unsigned long long went1 = 0, went2 = 0, went3 = 0;  // where the three requests before went
+    const char* const rows = reinterpret_cast<const char*>(a.last + p * (size_t)a.nseg * R);
+    const unsigned row_bytes = (unsigned)R * 4u;
+    const unsigned lane_off = (unsigned)(in ? lane : 0) * 4u;
+    auto cell_at = [&](uint32_t rowoff) { return reinterpret_cast<const int32_t*>(rows + (rowoff + lane_off)); };
+    const int spare = N;                      // the log record behind the last request's
+    // the request before, on this lane's replica: blocks it would have added, oldest request it matched blocks of
+    int added1 = 0, oldest1 = INT32_MAX;
+    // where this replica's eviction cursors are (`hi` is read last)
+    struct {
+        int32_t cur_r, cur_r2, hi;
+        uint32_t k_room;
+        int32_t cur_k2;
+    } at{-1, -1, -1, 0, 0};
+    auto look = [&]() {
+        at.cur_r = comm->cur_r[0][lane];
+        at.k_room = comm->k_room[lane];
+        if constexpr (PROXY) {
+            at.cur_r2 = comm->cur_r[1][lane];
+            at.cur_k2 = comm->cur_k2[lane];
+        }
+        asm volatile("" ::: "memory");
+        at.hi = comm->hi[lane];
+    };
+    // the request in hand: row cells of its first eight segments as seen by this lane (= replica), where they end, tokens,
+    // blocks, flags; read (LDS) while the minimum of the one before is being found
+    int32_t cell[SEG_CHUNK];
+    int end[SEG_CHUNK];
+    int L = 0, n = 0, word = 0, set = 0;
+    auto take = [&](int r, int set) {
+        const SegDesc& d = comm->ring[r & (DESC_RING - 1)];
+        const int4 h = *reinterpret_cast<const int4*>(&d.L);
+#pragma unroll
+        for (int k = 0; k < SEG_CHUNK; ++k) cell[k] = comm->cells[set][k][lane];
+        const int4 lo = reinterpret_cast<const int4*>(d.end)[0], hi = reinterpret_cast<const int4*>(d.end)[1];
+        end[0] = lo.x, end[1] = lo.y, end[2] = lo.z, end[3] = lo.w;
+        end[4] = hi.x, end[5] = hi.y, end[6] = hi.z, end[7] = hi.w;
+        L = h.x;
+        n = h.y;
+        word = h.w;       // (the same in every lane; made scalar behind the meeting, where it has arrived)
+    };
+    SectionClock<TIMED> clk;
+    int before = 0;           // flags of the request before
+    meet(true);                               // the first descriptors and cells are there
+    take(0, 0);
+    meet(true);                               // the other wavefronts have set themselves up
+    clk.start();
+    for (int next = 0; next < N; ++next) {
+        const int r = __builtin_amdgcn_readfirstlane(next);
+        const SegDesc* const dr = &comm->ring[r & (DESC_RING - 1)];
+        const int target = DICTATED ? dr->target : 0;
+        look();
+        double left = DICTATED ? 0.0 : comm->gone[r & 1][lane];      // (read again behind Y(r - 1))
+        // (what the choice before adds to the load signal, while LDS is read)
+        if (COUNTS) q += of_mask(went1) ? 1.0 : 0.0;
+        else if (!DICTATED) q += of_mask(went1) ? tokens : 0.0;
+        if constexpr (PROXY) my_rtt = comm->rtt[r & 1][lane];
+        const int flags = __builtin_amdgcn_readfirstlane(word);
+        const int was = __builtin_amdgcn_readfirstlane(before);
+        bool behind = (was & DESC_SYNC) != 0;
+        auto caught_up = [&]() {
+            meet(false);
+            behind = false;
+            if (!DICTATED) left = comm->gone[r & 1][lane];
+            if (ONLINE) {
+                w_rtt = comm->w[0][0];
+                w_prefill = comm->w[0][1];
+                w_queue = comm->w[0][2];
+                rtt_term = in ? w_rtt * my_rtt : INFINITY;
+            }
+        };
+        // ---- the rows were loaded before the stores of the three requests before were sure to be there: the leading
+        // segments that the paths share get the cells that those requests wrote on their replicas
+        if (flags & DESC_SHARED) {
+#pragma unroll
+            for (int k = 0; k < SEG_CHUNK; ++k) {
+                cell[k] = of_mask(went3) && k < ((flags >> 20) & 15) ? r - 3 : cell[k];
+                cell[k] = of_mask(went2) && k < ((flags >> 12) & 15) ? r - 2 : cell[k];
+                cell[k] = of_mask(went1) && k < ((flags >> 8) & 15) ? r - 1 : cell[k];
+            }
+        }
+        // ---- prefix match as in decide_wave: max(e_gt, min(cur_k, e_ge)) with e_gt, e_ge the ends of the last segment whose
+        // cell is above, respectively not below, the cursor's request
+        int my_m, my_seen = 0, k_end, oldest;
+        unsigned long long holders, single;      // lanes that match, and whose match has one previous owner
+        const unsigned long long tight = (ballot(added1 > (int)(at.k_room >> 16)) | ballot(oldest1 <= at.hi)) & went1;
+        const unsigned long long late = (unsigned)((was & DESC_SYNC) | (flags & DESC_DEEP));
+        auto match = [&]() {
+            int e_gt = 0, e_ge = 0;
+            int32_t own_ge = INT32_MAX;      // previous owner of the last segment counted in e_ge
+            int e_gt2 = 0, e_ge2 = 0;        // proxy variants: the same against the index's cursor
+            int32_t own_ge2 = INT32_MAX;
+            auto compare = [&](int k) {
+                const bool gt = cell[k] > at.cur_r;
+                const bool ge = cell[k] >= at.cur_r;
+                e_gt = gt ? end[k] : e_gt;
+                e_ge = ge ? end[k] : e_ge;
+                own_ge = ge ? cell[k] : own_ge;
+                if (PROXY) {
+                    const bool gt2 = cell[k] > at.cur_r2;
+                    const bool ge2 = cell[k] >= at.cur_r2;
+                    e_gt2 = gt2 ? end[k] : e_gt2;
+                    e_ge2 = ge2 ? end[k] : e_ge2;
+                    own_ge2 = ge2 ? cell[k] : own_ge2;
+                }
+            };
+            compare(0);
+            compare(1);
+            compare(2);
+            compare(3);
+            if (flags & DESC_MORE4) {
+                compare(4);
+                compare(5);
+                compare(6);
+                compare(7);
+            }
+            const int cur_k = (int)(at.k_room & 0xFFFFu);
+            const int below_cursor = cur_k < e_ge ? cur_k : e_ge;
+            const bool some_eq = below_cursor > e_gt;       // blocks of the cursor's own request are matched
+            my_m = some_eq ? below_cursor : e_gt;
+            const int below_cursor2 = at.cur_k2 < e_ge2 ? at.cur_k2 : e_ge2;
+            const bool some_eq2 = below_cursor2 > e_gt2;
+            my_seen = PROXY ? (some_eq2 ? below_cursor2 : e_gt2) : 0;       // blocks in the proxy's index (>= my_m)
+            // For the ownership update: where the cached prefix ends on this replica (rounded up to the end of a segment
+            // that the cursor's request owns: what lies beyond the cursor is evicted anyway) and whether all cached segments
+            // had the same previous owner: the evicting wavefront is told that one, and finds several by itself.  (A segment of
+            // the cursor's request beyond the cursor is taken for one more owner: rare, and the walk knows better.)
+            k_end = PROXY ? (some_eq2 ? e_ge2 : e_gt2) : (some_eq ? e_ge : e_gt);
+            holders = ballot((PROXY ? my_seen : my_m) > 0);
+            single = ballot((PROXY ? own_ge2 : own_ge) == cell[0]);
+            oldest = PROXY ? own_ge2 : own_ge;
+        };
+        match();
+        int owner = of_mask(holders & single) ? cell[0] : spare;
+        owner = of_mask(holders & ~single) ? OWN_WALK : owner;
+        // The evicting wavefront may still be moving the cursor of the replica that the request before went to.  Where it is,
+        // read before, while or after it moves, makes no difference if it cannot pass the youngest record of the look-ahead ring
+        // and everything matched is younger -- by this request, and for `room` to be what it says by the one before.  One
+        // request in a hundred waits with 32 replicas, one in twelve with three.  The other rare cases share the branch:
+        // Y(r - 1), as late as this, and a path longer than is preloaded.
+        const unsigned long long unsure = (ballot(oldest <= at.hi) & went1) | tight;
+        if (__builtin_expect((unsure | late) != 0, 0)) {
+            if (behind) caught_up();
+            if (unsure != 0 || (flags & DESC_DEEP)) {
+                while (ld(&comm->evicted) < r - 1) __builtin_amdgcn_s_sleep(1);
+                asm volatile("" ::: "memory");
+                look();
+                match();
+                owner = of_mask(holders & single) ? cell[0] : spare;
+                owner = of_mask(holders & ~single) ? OWN_WALK : owner;
+            }
+            if (flags & DESC_DEEP) {
+                // more than eight segments (memory is up to date behind Y(r - 1)): the rest of the path is read from the
+                // trace, eight references at a time, as long as some replica's prefix is still open
+                const int64_t j0 = dr->j0;
+                const int s = __builtin_amdgcn_readfirstlane(dr->s);
+                const int cur_k = (int)(at.k_room & 0xFFFFu);
+                int pos = end[7];
+                bool open = my_m == pos;
+                bool open_seen = PROXY && my_seen == pos;
+                if (ballot((PROXY ? open_seen : open) && in) != 0) {
+                    owner = of_mask(holders) ? OWN_WALK : spare;
+                    oldest = -1;                     // (older than the preloaded ones)
+                    for (int c0 = 8; c0 < s; c0 += 8) {
+                        int32_t more[8];
+                        int send[8];
+#pragma unroll
+                        for (int k = 0; k < 8; ++k) {
+                            more[k] = NEVER_CACHED;
+                            send[k] = pos;
+                            if (c0 + k < s) {
+                                const SegRef sr = a.seg[j0 + c0 + k];
+                                send[k] = sr.end & SEG_END_MASK;
+                                // (a fresh segment's row still holds what a segment of the past left there)
+                                if ((PROXY ? open_seen : open) && in && !(sr.end & SEG_FRESH))
+                                    more[k] = ld(cell_at((uint32_t)sr.id * row_bytes));
+                            }
+                        }
+#pragma unroll
+                        for (int k = 0; k < 8; ++k) {
+                            if (c0 + k < s) {
+                                const int cnt = cached_in(more[k], pos, send[k], at.cur_r, cur_k);
+                                my_m += open ? cnt : 0;
+                                open = open && cnt == send[k] - pos;
+                                if (PROXY) {
+                                    const int cnt_seen = cached_in(more[k], pos, send[k], at.cur_r2, at.cur_k2);
+                                    my_seen += open_seen ? cnt_seen : 0;
+                                    open_seen = open_seen && cnt_seen == send[k] - pos;
+                                }
+                                pos = send[k];
+                            }
+                        }
+                        if (ballot((PROXY ? open_seen : open) && in) == 0) break;
+                    }
+                }
+            }
+        }
+        if (!DICTATED) comm->gone[r & 1][lane] = 0.0;
+        clk.tick(1);                                                 // patch, match
+
+        // ---- score (Eq. 3) and lowest-index minimum.  block_tokens * blocks fits: below 2^15 and 2^16.
+        int hit_tok = __mul24(a.block_tokens, my_m);
+        hit_tok = hit_tok > L ? L : hit_tok;
+        const int my_u = L - hit_tok;
+        int my_u_seen = my_u;       // uncached tokens as Eq. 3 sees them
+        if (PROXY) {
+            int seen_tok = __mul24(a.block_tokens, own_index ? my_seen : my_m);
+            seen_tok = seen_tok > L ? L : seen_tok;
+            my_u_seen = L - seen_tok;
+        }
+        q += left;
+        double my_score, my_prefill = (double)my_u;
+        if (!ENGINE && !PROXY) my_prefill = a.a_pf * my_prefill;
+        if (SCORED) {
+            const double pf = PROXY || ENGINE ? a.a_pf * (double)my_u_seen : my_prefill;
+            const double s_rtt = PROXY ? (in ? w_rtt * my_rtt : INFINITY) : rtt_term;
+            const double s_pf = w_prefill * pf;
+            const double rtt_and_prefill = s_rtt + s_pf;
+            const double qd = a.a_pf * q;
+            const double s_q = w_queue * qd + 0.0;       // (not -0.0: nor is the score then)
+            my_score = rtt_and_prefill + s_q;
+        } else if (COUNTS) {
+            my_score = q;                       // requests in flight
+        } else {
+            my_score = lane == target ? 0.0 : 1.0;      // the replica is dictated
+        }
+        // ---- what every replica would mean for the request, whatever the choice
+        const unsigned hit_end = (unsigned)my_m | ((unsigned)k_end << 16);
+        if constexpr (PROXY) comm->choice[r & 1][lane] = Choice<true>{my_u, own_index ? my_seen : my_m, owner, hit_end};
+        else comm->choice[r & 1][lane] = Choice<false>{my_prefill, owner, hit_end};
+        // (what is still needed of this request's numbers, and the next one's: its reads are under way during the minimum)
+        added1 = n - my_m;                      // (not below what the index would add)
+        oldest1 = oldest;
+        tokens = (double)L;
+        set = set == CELL_SETS - 1 ? 0 : set + 1;
+        take(r + 1, set);
+        const unsigned long long bests = argmin_mask<1>(my_score, false);
+        comm->best[r & 1][0] = __builtin_ctzll(bests);
+        clk.tick(3);                                                 // score, minimum, announcement
+        went3 = went2;
+        went2 = went1;
+        went1 = bests;
+        meet(true);                                                  // X(r)
+        clk.tick(0);                                                 // waiting at X
+        before = flags;
+    }
+    if (TIMED && a.sections && lane == 0)            // (the evicting wavefront writes the counts)
+        for (int k = 0; k < 8; ++k) a.sections[p * 3 * SECTIONS + k] = clk.acc[k];
+}
+
+// One workgroup = one replay; two fit a CU whatever the shape (at most 128 vector registers, 84 KiB of LDS).
+template <int MODE, bool ENGINE, bool PROXY, bool TIMED = false>
+__global__ void __launch_bounds__(APART_WAVES * WAVE, 4) replay_apart_kernel(SegArgs a) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    __shared__ ApartHandover<PROXY> comm;
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+    double* const window = reinterpret_cast<double*>(lds_raw + SlotQueues::bytes(a.R, a.B, ENGINE));
+    if (a.N == 0) {           // (an empty trace still reports the tuner's initial state)
+        if (wave == 1) Tuner<MODE == MODE_ONLINE>(a, blockIdx.x, window, lane).results();
+        return;
+    }
+    if (wave == 0) {
+        __builtin_amdgcn_s_setprio(3);      // the wavefront on the chain goes first at issue
+        apart_decide_wave<MODE, ENGINE, PROXY, TIMED>(a, lane, &comm);
+    } else if (wave == 1) {
+        __builtin_amdgcn_s_setprio(2);
+        SlotQueues Q;
+        Q.init(lds_raw, a.R, a.B, ENGINE, lane);
+        apart_serve_wave<MODE, ENGINE, PROXY, TIMED>(a, lane, Q, window, &comm);
+    } else if (wave == 2) {
+        __builtin_amdgcn_s_setprio(2);
+        SlotQueues Q;
+        Q.attach(lds_raw, a.R, a.B);
+        apart_retire_wave<PROXY, TIMED>(a, lane, Q, &comm);
+    } else if (wave == 3) {
+        __builtin_amdgcn_s_setprio(1);
+        apart_book_wave<PROXY, TIMED>(a, lane, &comm);
+    } else if (wave == 4) {
+        __builtin_amdgcn_s_setprio(2);
+        apart_evict_wave<PROXY, TIMED>(a, lane, &comm);
+    } else {
+        front_wave<MODE, PROXY, 1, TIMED>(a, lane, &comm);
+    }
+}
+
+}  // namespace gorgo

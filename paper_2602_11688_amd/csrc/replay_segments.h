@@ -334,6 +334,7 @@ struct __align__(16) QueueHandover {
 template <bool PROXY, int PACK, int LOOK>
 struct Handover : QueueHandover<PROXY> {
     static constexpr int LOOK_WORDS = LOOK;
+    static constexpr bool APART = false;
     int32_t cells[CELL_SETS][SEG_CHUNK][WAVE];    // [request mod 3]: row cells of the request's first eight segments per replica
     // look-ahead of the eviction cursors (the cache's; the proxy's index's): per replica, log records fetched ahead
     // of the cursor (one slot is always free)
@@ -608,6 +609,7 @@ struct EvictCursor {
 // descriptors are requested, requested and written in turn, eight requests apart, so that no load is waited for.
 template <int MODE, bool PROXY, int PACK, bool TIMED, class Comm>
 __device__ __forceinline__ void front_wave(const SegArgs& a, int lane, Comm* comm) {
+    constexpr bool APART = Comm::APART;      // the book-keeping wavefront touches the rows, the evicting one reads the log
     constexpr bool SIGNAL = MODE == MODE_COST_MODEL || MODE == MODE_ONLINE || MODE == MODE_LEAST_REQUEST;
     const int R = a.R, N = (int)a.N;
     const int q = lane / SEG_CHUNK, k = lane % SEG_CHUNK;
@@ -624,7 +626,32 @@ __device__ __forceinline__ void front_wave(const SegArgs& a, int lane, Comm* com
     const uint32_t lane_off = (upper ? (uint32_t)a.nseg * row_bytes : 0u) + (uint32_t)(rl < R ? rl : 0) * 4u;
     const unsigned long long* const log64 = reinterpret_cast<const unsigned long long*>(a.log + (p + (upper ? 1 : 0)) * ((size_t)N + 1));
     const uint32_t other_replay = PACK == 2 ? (uint32_t)a.nseg * row_bytes : 0u;
+    // A request's numbers as they are in memory: nothing is done with them before the group is next, so that no load is
+    // waited for where it is issued (low words where only differences count).
     struct Scalars {
+        int64_t j0;
+        uint32_t j1, j2, b0, b1;
+        int64_t ts0, ts1, ts2;
+        int L, O;
+        uint32_t hash;
+    };
+    auto load_scalars = [&](int g0, Scalars& c) {
+        const int r = g0 + q;
+        const int x = r < N ? r : N - 1, x1 = r + 1 < N ? r + 1 : N - 1, x2 = r + 2 < N ? r + 2 : N - 1;
+        auto low = [](const int64_t* at) { return *reinterpret_cast<const uint32_t*>(at); };
+        c.j0 = a.seg_off[x];
+        c.j1 = low(&a.seg_off[x + 1]);
+        c.j2 = low(&a.seg_off[x1 + 1]);
+        c.b0 = low(&a.blk_off[x]);
+        c.b1 = low(&a.blk_off[x + 1]);
+        c.ts0 = a.ts[x];
+        c.ts1 = a.ts[x1];
+        c.ts2 = a.ts[x2];
+        c.L = a.in_len[x];
+        c.O = a.out_len[x];
+        c.hash = MODE == MODE_AFFINITY ? a.first_hash[x] : 0u;
+    };
+    struct Request {
         int L, s, n;
         int64_t j0;
         uint32_t hash;
@@ -632,48 +659,50 @@ __device__ __forceinline__ void front_wave(const SegArgs& a, int lane, Comm* com
         double t0, t1;       // arrival of the request after next, at the time scale of each replay of the workgroup
         int O;
     };
-    auto load_scalars = [&](int g0, Scalars& c) {
+    auto settle = [&](int g0, const Scalars& c) {
+        Request x;
         const int r = g0 + q;
-        const bool on = r < N;                       // (requests past the end look empty)
-        const int x = on ? r : N - 1;
-        c.j0 = a.seg_off[x];
-        c.s = on ? (int)(a.seg_off[x + 1] - c.j0) : 0;
-        c.n = on ? (int)(a.blk_off[x + 1] - a.blk_off[x]) : 0;
-        c.L = on ? a.in_len[x] : 0;
-        c.hash = MODE == MODE_AFFINITY ? a.first_hash[x] : 0u;
-        c.O = a.out_len[x];
-        const bool has1 = r + 1 < N, has2 = r + 2 < N;
-        const double t2 = (double)a.ts[has2 ? r + 2 : N - 1];
+        const bool on = r < N, has1 = r + 1 < N, has2 = r + 2 < N;       // (requests past the end look empty)
+        x.j0 = c.j0;
+        x.s = on ? (int)(c.j1 - (uint32_t)c.j0) : 0;
+        x.n = on ? (int)(c.b1 - c.b0) : 0;
+        x.L = on ? c.L : 0;
+        x.hash = c.hash;
+        x.O = c.O;
+        const double t2 = (double)c.ts2;
         // (nothing completes by the arrival of a request that there is not: the queue wavefront need not ask whether there is
         // one; with two replays the test is the cheaper: 2,048 of 20,000 requests 16.0 / 16.25 ms)
-        c.t0 = PACK == 2 || has2 ? t2 * scale0 : -INFINITY;
-        c.t1 = t2 * scale1;
+        x.t0 = PACK == 2 || has2 ? t2 * scale0 : -INFINITY;
+        x.t1 = t2 * scale1;
         // whether all wavefronts meet once more before the next request: if it has more segments than are preloaded ...
-        bool sync = a.seg_off[has1 ? r + 2 : N] - a.seg_off[has1 ? r + 1 : N] > SEG_CHUNK;
+        bool sync = has1 && c.j2 - c.j1 > (uint32_t)SEG_CHUNK;
         // ... if this one may have completed by its arrival -- it takes its decode time at least: every further term of its
         // completion time is added to it and none is negative, and rounding keeps the order ...
         if (SIGNAL) {
-            const double t = (double)a.ts[x], t1 = (double)a.ts[has1 ? r + 1 : N - 1], dec = a.least_dec * (double)c.O;
+            const double t = (double)c.ts0, t1 = (double)c.ts1, dec = a.least_dec * (double)c.O;
             sync = sync || !(t * scale0 + dec > t1 * scale0);
             if (PACK == 2) sync = sync || !(t * scale1 + dec > t1 * scale1);
         }
         // ... and if the tuner changes the weights after this one
         if (MODE == MODE_ONLINE) sync = sync || (r + 1 >= a.window && (unsigned)(r + 1 - a.window) % (unsigned)a.hop == 0u);
-        c.sync = has1 && sync;
+        x.sync = has1 && sync;
+        return x;
     };
     int ref_id = -1, ref_end = 0;                    // (-1: no such segment)
-    auto load_ref = [&](const Scalars& c) {
-        SegRef ref{-1, 0};
-        if (k < c.s) ref = a.seg[c.j0 + k];
-        ref_id = ref.id;
-        ref_end = ref.end;                           // (with the SEG_FRESH mark)
+    SegRef raw_ref{-1, 0};
+    auto load_ref = [&](const Request& c) { raw_ref = a.seg[c.j0 + (k < c.s ? k : 0)]; };   // (one behind the last is there to be read)
+    auto settle_ref = [&](const Request& c) {
+        ref_id = k < c.s ? raw_ref.id : -1;
+        ref_end = k < c.s ? raw_ref.end : 0;         // (with the SEG_FRESH mark)
     };
     int old_id = -1, old_end = 0;                    // the references of the group before
     int touched = 0;
-    Scalars now, next;
+    Request now;
+    Scalars next;
     // The descriptors of group g0 (scalars `now`, references in ref_*), in pieces of about equal length; done(k) is
     // called after each.
     auto commit = [&](int g0, auto done) {
+        settle_ref(now);
         // the references at the same place of the path in the three requests before: same tree, same path so far
         const int from1 = ((lane - SEG_CHUNK) & (WAVE - 1)) << 2, from2 = ((lane - 2 * SEG_CHUNK) & (WAVE - 1)) << 2,
                   from3 = ((lane - 3 * SEG_CHUNK) & (WAVE - 1)) << 2;
@@ -701,15 +730,17 @@ __device__ __forceinline__ void front_wave(const SegArgs& a, int lane, Comm* com
         d->rowoff[k] = off;
         d->end[k] = real ? my_end : now.n;
         d->slot[k] = real ? slot_off : spare_off;
-        // The rows that will be read a dozen requests from now are touched once, so that they come from the L2 then and
-        // not from memory: one load per 64 rows (both ends of rows that straddle a cache line, or
-        // are longer than one).  The values are only used to keep the loads.
-        asm volatile("" ::"v"(touched));
-        touched = ld(reinterpret_cast<const int32_t*>(rows + off));
-        if ((row_bytes & 127u) != 0 || row_bytes > 128u) touched ^= ld(reinterpret_cast<const int32_t*>(rows + (off + row_bytes - 4u)));
-        if (PACK == 2) {
-            touched ^= ld(reinterpret_cast<const int32_t*>(rows + (off + other_replay)));
-            if ((row_bytes & 127u) != 0) touched ^= ld(reinterpret_cast<const int32_t*>(rows + (off + other_replay + row_bytes - 4u)));
+        if constexpr (!APART) {
+            // The rows that will be read a dozen requests from now are touched once, so that they come from the L2 then and
+            // not from memory: one load per 64 rows (both ends of rows that straddle a cache line, or
+            // are longer than one).  The values are only used to keep the loads.
+            asm volatile("" ::"v"(touched));
+            touched = ld(reinterpret_cast<const int32_t*>(rows + off));
+            if ((row_bytes & 127u) != 0 || row_bytes > 128u) touched ^= ld(reinterpret_cast<const int32_t*>(rows + (off + row_bytes - 4u)));
+            if (PACK == 2) {
+                touched ^= ld(reinterpret_cast<const int32_t*>(rows + (off + other_replay)));
+                if ((row_bytes & 127u) != 0) touched ^= ld(reinterpret_cast<const int32_t*>(rows + (off + other_replay + row_bytes - 4u)));
+            }
         }
         done(2);
         const int byte = q * SEG_CHUNK;
@@ -748,11 +779,13 @@ __device__ __forceinline__ void front_wave(const SegArgs& a, int lane, Comm* com
     };
     const auto at_once = [](int) {};
     for (int g0 = 0; g0 < DESC_AHEAD; g0 += DESC_GROUP) {
-        load_scalars(g0, now);
+        load_scalars(g0, next);
+        now = settle(g0, next);
         load_ref(now);
         commit(g0, at_once);
     }
-    load_scalars(DESC_AHEAD, now);
+    load_scalars(DESC_AHEAD, next);
+    now = settle(DESC_AHEAD, next);
     load_ref(now);
     load_scalars(DESC_AHEAD + DESC_GROUP, next);
     // The row cells of request x, for the deciding wavefront, which reads them from LDS after the next meeting.
@@ -793,15 +826,19 @@ __device__ __forceinline__ void front_wave(const SegArgs& a, int lane, Comm* com
     auto begin = [&](int r) {
         if (r >= N) return;
         load_cells(r + 2);
-        if ((r & every) == 0 && r > 0)
-            for (int c = 0; c < (PROXY ? 2 : 1); ++c) raw[c] = ld(&log64[(int)(unsigned)comm->record[c][lane]]);
+        if constexpr (!APART) {
+            if ((r & every) == 0 && r > 0)
+                for (int c = 0; c < (PROXY ? 2 : 1); ++c) raw[c] = ld(&log64[(int)(unsigned)comm->record[c][lane]]);
+        }
     };
     auto pass = [&](int r) {
         if (r >= N) return;
         const bool sync = (__builtin_amdgcn_readfirstlane(comm->ring[r & (DESC_RING - 1)].flags) & DESC_SYNC) != 0;
         store_cells();
-        if ((r & every) == 0 && r > 0)
-            for (int c = 0; c < (PROXY ? 2 : 1); ++c) comm->record[c][lane] = raw[c];
+        if constexpr (!APART) {
+            if ((r & every) == 0 && r > 0)
+                for (int c = 0; c < (PROXY ? 2 : 1); ++c) comm->record[c][lane] = raw[c];
+        }
         clk.tick(0);                                                 // descriptors, cells
         meet(true);                                                  // X(r)
         if (sync) meet(false);                                       // Y(r)
@@ -814,7 +851,7 @@ __device__ __forceinline__ void front_wave(const SegArgs& a, int lane, Comm* com
             pass(r + i);
             begin(r + i + 1);
         });
-        now = next;
+        now = settle(r + DESC_AHEAD + DESC_GROUP, next);
         load_ref(now);
         pass(r + 5);
         begin(r + 6);
@@ -827,6 +864,103 @@ __device__ __forceinline__ void front_wave(const SegArgs& a, int lane, Comm* com
     if (TIMED && a.sections && lane == 0)            // (the book-keeping wavefront writes the next two)
         for (int i = 0; i < 2; ++i) a.sections[(p * 3 + 2) * SECTIONS + i] = clk.acc[i];
 }
+
+// ---------------------------------------------------------------------------------------------- tuner, probe epochs
+// Online tuner (Sec. 2.3, Sec. 4), run by the wavefront that has the TTFTs: after every hop the p95
+// TTFT of the last `window` requests is the fitness of the weights in use; they replace the parent iff they
+// beat it; the step size follows the 1/5 rule; the next offspring is a log-space mutation of the parent.
+// The three weights are held by lanes 0 to 2 (the other lanes repeat the third), the rest of the state by every lane.
+template <bool ONLINE>
+struct Tuner {
+    const SegArgs& a;
+    const size_t p;
+    double* const ring;                 // the window (LDS)
+    const int lane, W, H, kth;
+    const int wk;                       // the weight of this lane
+    int ring_pos = 0, until_step, accepted = 0;
+    int64_t step = 0;
+    bool have_parent = false;
+    double ln_par = 0.0, ln_cur = 0.0, f_par = 0.0, sigma = 0.0;
+    __device__ __forceinline__ Tuner(const SegArgs& a_, size_t p_, double* ring_, int lane_)
+        : a(a_), p(p_), ring(ring_), lane(lane_), W(ONLINE ? a_.window : 0), H(ONLINE ? a_.hop : 0), kth((95 * W + 99) / 100),
+          wk(lane_ < 3 ? lane_ : 2), until_step(W) {
+        if (ONLINE) {
+            ln_par = ln_cur = a.ln_theta0[3 * p + wk];
+            sigma = a.tuner[12];
+            if (W + lane < ((W + 7) & ~7)) ring[W + lane] = INFINITY;     // padding (entries below W are written before use)
+        }
+    }
+    __device__ __forceinline__ void results() const {
+        if (ONLINE) {
+            const double best = clip(tuner_exp(ln_par), a.tuner[wk], a.tuner[3 + wk]);
+            if (a.theta_final && lane < 3) a.theta_final[3 * p + lane] = best;
+            if (a.sigma_final && lane == 0) a.sigma_final[p] = sigma;
+            if (a.accepted && lane == 0) a.accepted[p] = accepted;
+        }
+    }
+    // the next request's TTFT; weights: where the weights in use are handed over
+    __device__ __forceinline__ void sample(double ttft, double* weights) {
+        if (lane == 0) ring[ring_pos] = ttft;
+        ring_pos = ring_pos + 1 == W ? 0 : ring_pos + 1;
+        if (--until_step == 0) {
+            until_step = H;
+            wave_sync();
+            const double f = window_kth(ring, W, kth, lane);
+            if (!have_parent) {
+                f_par = f;                 // the first window measures the initial weights: the parent
+                have_parent = true;
+            } else {
+                const bool success = f < f_par;
+                if (success) {
+                    ln_par = ln_cur;
+                    f_par = f;
+                    ++accepted;
+                }
+                sigma = sigma * (success ? a.tuner[13] : a.tuner[14]);
+            }
+            const double moved = ln_par + sigma * a.z[(p * a.steps + step) * 3 + wk];
+            ln_cur = clip(moved, a.tuner[6 + wk], a.tuner[9 + wk]);
+            const double th = clip(tuner_exp(ln_cur), a.tuner[wk], a.tuner[3 + wk]);
+            if (lane < 3) {
+                weights[lane] = th;
+                if (a.theta_step) a.theta_step[(p * a.steps + step) * 3 + lane] = th;
+            }
+            if (lane == 0 && a.fitness_step) a.fitness_step[p * a.steps + step] = f;
+            ++step;
+            wave_sync();
+        }
+    }
+};
+
+// Imperfect proxy knowledge (Sec. 2.2, Sec. 4 RTT figure): time is cut into probe epochs, the epoch of t being
+// the largest e with e * probe_ms <= t (capped at the last one given); a request experiences the true round
+// trip time of its epoch, the cost model scores with the proxy's moving average, handed to the deciding wavefront
+// two requests ahead.
+template <bool PROXY>
+struct ProbeEpochs {
+    const SegArgs& a;
+    const int lane;
+    int epoch = 0;
+    double next_probe, rtt_now = 0.0, est_now = 0.0;
+    __device__ __forceinline__ ProbeEpochs(const SegArgs& a_, int lane_) : a(a_), lane(lane_), next_probe(PROXY ? (double)a_.probe_ms : 0.0) {}
+    // request r arrives at t: half the round trip time of replica = lane
+    template <class Comm>
+    __device__ __forceinline__ double at(double t, int r, Comm* comm) {
+        bool moved = r == 0;
+        while (epoch + 1 < a.epochs && next_probe <= t) {       // (timestamps do not decrease)
+            ++epoch;
+            next_probe = (double)(epoch + 1) * (double)a.probe_ms;
+            moved = true;
+        }
+        if (moved) {
+            const size_t x = (size_t)epoch * a.R + (lane < a.R ? lane : 0);
+            rtt_now = a.rtt_true[x];
+            est_now = a.rtt_est[x];
+        }
+        if constexpr (PROXY) comm->rtt[r & 1][lane] = est_now;
+        return 0.5 * rtt_now;
+    }
+};
 
 // ---------------------------------------------------------------------------------------------- queue side
 // Queue wavefront of a replay (`which` of the workgroup's).  One request behind the deciding wavefront: after
@@ -841,60 +975,14 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
     const size_t p = (size_t)blockIdx.x * PACK + which;
     SlotQueues Q;
     Q.init(lds_raw, R, a.B, ENGINE, lane);
-    // Online tuner (Sec. 2.3, Sec. 4), run here because this wavefront has the TTFTs: after every hop the p95
-    // TTFT of the last `window` requests is the fitness of the weights in use; they replace the parent iff they
-    // beat it; the step size follows the 1/5 rule; the next offspring is a log-space mutation of the parent.
-    // The three weights are held by lanes 0 to 2 (the other lanes repeat the third), the rest of the state by every lane.
-    double* const ring = reinterpret_cast<double*>(lds_raw + SlotQueues::bytes(R, a.B, ENGINE));
-    const int W = ONLINE ? a.window : 0, H = ONLINE ? a.hop : 0;
-    const int kth = (95 * W + 99) / 100;
-    int ring_pos = 0, until_step = W;
-    int64_t step = 0;
-    int accepted = 0;
-    bool have_parent = false;
-    const int wk = lane < 3 ? lane : 2;                 // the weight of this lane
-    double ln_par = 0.0, ln_cur = 0.0;
-    double f_par = 0.0, sigma = 0.0;
-    if (ONLINE) {
-        ln_par = ln_cur = a.ln_theta0[3 * p + wk];
-        sigma = a.tuner[12];
-        if (W + lane < ((W + 7) & ~7)) ring[W + lane] = INFINITY;     // padding (entries below W are written before use)
-    }
-    auto tuner_results = [&]() {
-        if (ONLINE) {
-            const double best = clip(tuner_exp(ln_par), a.tuner[wk], a.tuner[3 + wk]);
-            if (a.theta_final && lane < 3) a.theta_final[3 * p + lane] = best;
-            if (a.sigma_final && lane == 0) a.sigma_final[p] = sigma;
-            if (a.accepted && lane == 0) a.accepted[p] = accepted;
-        }
-    };
+    Tuner<ONLINE> tuner(a, p, reinterpret_cast<double*>(lds_raw + SlotQueues::bytes(R, a.B, ENGINE)), lane);
     if (N == 0) {           // (an empty trace still reports the tuner's initial state)
-        tuner_results();
+        tuner.results();
         return;
     }
     if (ONLINE && lane < 3) comm->w[which][lane] = a.params[3 * p + lane];
     const double sc = a.scale[p];
-    // imperfect proxy knowledge (Sec. 2.2, Sec. 4 RTT figure): time is cut into probe epochs, the epoch of t being
-    // the largest e with e * probe_ms <= t (capped at the last one given); a request experiences the true round
-    // trip time of its epoch, the cost model scores with the proxy's moving average, handed to the deciding wavefront
-    // two requests ahead.
-    int epoch = 0;
-    double next_probe = PROXY ? (double)a.probe_ms : 0.0, rtt_now = 0.0, est_now = 0.0;
-    auto probe = [&](double t, int r) -> double {          // request r arrives at t: half the round trip time of replica = lane
-        bool moved = r == 0;
-        while (epoch + 1 < a.epochs && next_probe <= t) {       // (timestamps do not decrease)
-            ++epoch;
-            next_probe = (double)(epoch + 1) * (double)a.probe_ms;
-            moved = true;
-        }
-        if (moved) {
-            const size_t at = (size_t)epoch * R + (lane < R ? lane : 0);
-            rtt_now = a.rtt_true[at];
-            est_now = a.rtt_est[at];
-        }
-        if constexpr (PROXY) comm->rtt[r & 1][lane] = est_now;
-        return 0.5 * rtt_now;
-    };
+    ProbeEpochs<PROXY> probes(a, lane);
     // proxy variants: half the round trip time of replica = lane, the request in hand's and the next two's
     double half0 = 0.0, half1 = 0.0, half2 = 0.0;
     if constexpr (!PROXY) comm->half[lane] = lane < R ? 0.5 * a.rtt[lane] : 0.0;
@@ -941,8 +1029,8 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
         t1 = (double)a.ts[N > 1 ? 1 : 0] * sc;
     }
     if (PROXY) {
-        half0 = probe(t0, 0);
-        if (N > 1) half1 = probe(t1, 1);
+        half0 = probes.at(t0, 0, comm);
+        if (N > 1) half1 = probes.at(t1, 1, comm);
     }
     meet(true);        // (nothing has completed yet: the first request can be decided)
 
@@ -1024,37 +1112,7 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
                 o_hit = lane == i ? (int)(ch->hit_end & 0xFFFFu) : o_hit;
                 if constexpr (PROXY) o_believed = lane == i ? ch->seen : o_believed;
             }
-            if (ONLINE) {
-                if (lane == 0) ring[ring_pos] = ttft;
-                ring_pos = ring_pos + 1 == W ? 0 : ring_pos + 1;
-                if (--until_step == 0) {
-                    until_step = H;
-                    wave_sync();
-                    const double f = window_kth(ring, W, kth, lane);
-                    if (!have_parent) {
-                        f_par = f;                 // the first window measures the initial weights: the parent
-                        have_parent = true;
-                    } else {
-                        const bool success = f < f_par;
-                        if (success) {
-                            ln_par = ln_cur;
-                            f_par = f;
-                            ++accepted;
-                        }
-                        sigma = sigma * (success ? a.tuner[13] : a.tuner[14]);
-                    }
-                    const double moved = ln_par + sigma * a.z[(p * a.steps + step) * 3 + wk];
-                    ln_cur = clip(moved, a.tuner[6 + wk], a.tuner[9 + wk]);
-                    const double th = clip(tuner_exp(ln_cur), a.tuner[wk], a.tuner[3 + wk]);
-                    if (lane < 3) {                                      // in use from the next request on (Y(r) follows)
-                        comm->w[which][lane] = th;
-                        if (a.theta_step) a.theta_step[(p * a.steps + step) * 3 + lane] = th;
-                    }
-                    if (lane == 0 && a.fitness_step) a.fitness_step[p * a.steps + step] = f;
-                    ++step;
-                    wave_sync();
-                }
-            }
+            if constexpr (ONLINE) tuner.sample(ttft, comm->w[which]);        // (in use from the next request on: Y(r) follows)
             clk.tick(5);                                                 // outputs, tuner
             if (sync) {
                 // the request may have completed before the next one arrives, or its latency matters to the next one
@@ -1066,7 +1124,7 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
             // where the next request goes, whose own completion the deciding wavefront has ruled out, or will wait for.
             if (!ASK || r + 2 < N) {
                 retire(due, t2, r + 2);
-                if (PROXY) half2 = probe(t2, r + 2);
+                if (PROXY) half2 = probes.at(t2, r + 2, comm);
             }
             if (PROXY) {
                 half0 = half1;
@@ -1094,7 +1152,7 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
         clk.tick(6);                                                   // batch turnover
     }
     clk.write(a.sections ? a.sections + (p * 3 + 1) * SECTIONS : nullptr, lane);
-    tuner_results();
+    tuner.results();
 }
 
 // ---------------------------------------------------------------------------------------------- book-keeping

@@ -1,12 +1,14 @@
 """Where a launch changes its way: small inputs as kernel arguments or as copies (R + 4 P against 448), how often the
 eviction cursors' look-ahead is fed (24 replicas), how many sets of 64 service slots there are, and which requests the
-wavefronts meet twice at, against the CPU oracle."""
+wavefronts meet twice at, against the CPU oracle; six wavefronts per replay (up to 512 replays) against four."""
 import numpy as np
 import pytest
 
+import torch
+
 import paper_2602_11688_amd as g
 from synth import tracegen as tg
-from tests.gpu_helpers import check_population
+from tests.gpu_helpers import check_population, formulation, load
 from tests.test_gpu_engine import check_engine
 from tests.test_gpu_online import _check as check_online
 from tests.test_gpu_policies import _check as check_policy
@@ -72,3 +74,52 @@ def test_requests_that_are_waited_for(gap_ms, decode):
     check_proxy(tr, model, g.Proxy(np.round(rng.uniform(0.0, 300.0, (30, R)), 1), 700, 0.3, 5 * nmax), params, scale)
     z = rng.standard_normal((2, g.online_steps(tr.N, 8, 1), 3))
     check_online(tr, model, rtt, [[1.0, 0.5, 0.1]] * 2, z, [1.0, 0.1], 8, 1, [0.05] * 3, [2.0] * 3, 0.5)
+
+
+@pytest.mark.parametrize("R,B,cache", [(3, 8, 1), (5, 3, 3), (16, 2, 2), (33, 8, 1), (64, 16, 4), (7, 9, 0)])
+def test_six_wavefronts_or_four(R, B, cache):
+    """The same replays in a launch of 12 and repeated in one of 516: paths of many segments and owners, caches that hold one to
+    four of the longest requests (cursors that run into their look-ahead's end) or everything, requests that complete at
+    once, every entry point; bit for bit."""
+    tr = tg.random_forest(31 * R + B, 1100, roots=3, max_blocks=60, grow=4, gap_ms=60, keep=0.85)
+    nmax = int(np.diff(tr.blk_off).max())
+    rng = np.random.default_rng(R * B)
+    model = g.Model(R, B, cache * nmax, 0.05, 2.0)
+    rtt = rng.uniform(0.0, 400.0, R)
+    few, times = 12, 43
+    params = np.concatenate([rng.uniform(0.05, 2.0, (few - 2, 3)), [[1.0, 0.0, 0.0], [0.0, 1.0, 0.0]]])
+    scale = rng.choice([0.02, 0.5, 1.0, 4.0, 100.0], few)
+    most = int((tr.in_len.astype(np.int64) + tr.out_len).max())
+    engine = g.Engine(rng.uniform(0.02, 0.1, R), rng.uniform(0.0, 8.0, R), [3 * most] * R, 0.1)
+    table = np.round(rng.uniform(0.0, 900.0, (40, R)), 1)
+    online = dict(lo=[0.05] * 3, hi=[2.0] * 3, sigma0=0.5, window=16, hop=3)
+    z = torch.from_numpy(rng.standard_normal((few, g.online_steps(tr.N, 16, 3), 3))).to("cuda:0")
+    seeds = rng.integers(0, 1 << 62, few).astype(np.uint64)
+    handle = load(tr)
+    indexes = [-1, 0] + ([2 * cache * nmax] if cache else [])
+
+    def everything(n):
+        par, sc, zz, sd = np.tile(params, (n, 1)), np.tile(scale, n), z.repeat(n, 1, 1), np.tile(seeds, n)
+        start = np.tile([0.5, 1.0, 0.1], (few * n, 1))
+        yield "eval", g.eval_population(handle, model, rtt, par, sc)
+        for policy in ("least-request", "session-affinity", "random"):
+            yield policy, g.eval_policy(handle, model, rtt, policy, sc, seeds=sd)
+        yield "online", g.eval_online(handle, model, rtt, start, zz, sc, **online)
+        yield "engine", g.eval_engine(handle, model, engine, rtt, sc, params=par)
+        for index in indexes:
+            proxy = g.Proxy(table, 1700, 0.3, index)
+            yield f"proxy, index {index}", g.eval_proxy(handle, model, proxy, par, sc)
+            yield f"proxy, index {index}, engine, tuner", g.eval_proxy(handle, model, proxy, start, sc, engine=engine, online=dict(z=zz, **online))
+
+    names = ("route", "hit_blocks", "believed_hit_blocks", "ttft_ms", "e2e_ms", "p95_ttft_ms", "p95_e2e_ms", "theta_final", "accepted")
+    with formulation(2):
+        few_of, many_of = list(everything(1)), list(everything(times))
+    for (label, one), (_, other) in zip(few_of, many_of):
+        for name in names:
+            a, b = getattr(one, name, None), getattr(other, name, None)
+            assert (a is None) == (b is None), (label, name)
+            if a is not None:
+                a, b = a.cpu().numpy(), b.cpu().numpy()
+                for at in (0, times // 2, times - 1):
+                    np.testing.assert_array_equal(a, b[at * few:(at + 1) * few], err_msg=f"{label}: {name}")
+    handle.close()
