@@ -93,7 +93,7 @@ typedef struct gorgo_model {
  * evaluates, sizes a workspace or answers a question about an evaluation takes a `const gorgo_options*`, and NULL
  * stands for the defaults (the library keeps no settings between calls).  gorgo_options_default fills in the
  * defaults; out-of-range values make the call fail with GORGO_ERR_INVALID_ARG.
- *   replay_path: formulation of the cache state.  0 = automatic (default), 1 = hashed block tables (any trace),
+ *   replay_path: formulation of the cache state.  0 = automatic (default), 1 = block by block (any trace; stamps in rows or hashed tables),
  *     2 = dense segment rows (chain-consistent traces only; the call fails otherwise).  Both compute identical
  *     results; they differ in workspace size and speed.  Automatic picks segment rows when the trace is
  *     chain-consistent and its requests average at most 16 segments.  Size the workspace with the same options

@@ -32,8 +32,7 @@ int take_options(const gorgo_options* given, gorgo_options* out) {
 
 // which formulation a trace gets under a replay_path setting
 int32_t path_for(const gorgo_trace* t, int32_t mode) {
-    const bool few = (int64_t)t->seg.size() <= 16 * (t->N > 0 ? t->N : 1);
-    return mode == PATH_SEGMENTS || (mode == PATH_AUTO && t->chain_consistent && few) ? PATH_SEGMENTS : PATH_BLOCKS;
+    return mode == PATH_SEGMENTS || (mode == PATH_AUTO && t->chain_consistent && segments_suit(t)) ? PATH_SEGMENTS : PATH_BLOCKS;
 }
 
 int check_model(const gorgo_trace* t, const gorgo_model* m) {
@@ -63,9 +62,45 @@ int check_model(const gorgo_trace* t, const gorgo_model* m) {
 // inserted, given that the replay compacts a table once 7/8 of its slots have been used.
 int64_t least_table_slots(int64_t resident, int64_t d) { return ((resident + d) * 8 + 6) / 7 + 64; }
 
-// Table geometry and workspace carve-up.
+// Rows of stamps may be larger than hashed tables up to this many bytes.
+constexpr size_t ROWS_BYTES = (size_t)4 << 30;
+
+// Workspace carve-up of a plan whose geometry is set.
+void lay_out(const gorgo_trace* t, const gorgo_outputs* o, Plan* pl) {
+    const size_t P = (size_t)pl->P, N = (size_t)t->N;
+    size_t off = 0;
+    pl->off_tables = off;
+    if (pl->path == PATH_SEGMENTS) {
+        off += up256(P * (size_t)(pl->nseg + 2) * pl->R * 4);   // a row per segment, one that no request touches, a spare
+        pl->off_spare = off;                              // per-request log records of the segment kernel
+        off += up256(P * (N + 1) * 8);                    // (and a spare record per replay)
+    } else if (pl->row_slots > 0) {
+        off += up256(P * (size_t)pl->row_slots * pl->R * 8);
+        pl->off_spare = off;                              // per-request log records
+        off += up256(P * N * (size_t)pl->row_words * 4);
+    } else {
+        off += up256(P * pl->R * (size_t)pl->cap * 16);
+        pl->off_spare = off;
+        off += up256(P * (size_t)pl->cap * 16);
+    }
+    pl->off_rec = off;
+    off += up256(P * N * 16);
+    const bool want_p95_t = !o || o->p95_ttft_ms, want_p95_e = !o || o->p95_e2e_ms;
+    pl->off_route = off;
+    if (pl->path == PATH_BLOCKS && pl->row_slots == 0) off += up256(P * N);   // the block tables' log of choices (their eviction walks it)
+    pl->off_ttft = off;
+    if (!o || (!o->ttft_ms && want_p95_t)) off += up256(P * N * 8);
+    pl->off_e2e = off;
+    if (!o || (!o->e2e_ms && want_p95_e)) off += up256(P * N * 8);
+    pl->off_small = off;
+    // rtt, params, scale; tuner constants, ln theta0; seeds of the random policy; rates and budgets of the engine model
+    off += up256((4 * (size_t)pl->R + 8 * P + TUNER_CONSTS) * 8);
+    pl->total = off;
+}
+
+// Table geometry and workspace carve-up.  `room`: bytes of workspace there are, where that is known.
 int make_plan(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* options, int32_t P, const gorgo_outputs* o,
-              Plan* pl) {
+              Plan* pl, size_t room = SIZE_MAX) {
     if (P < 1 || P > (1 << 20)) return fail(GORGO_ERR_INVALID_ARG, "P must be in 1..2^20");
     gorgo_options opt;
     int orc = take_options(options, &opt);
@@ -98,31 +133,23 @@ int make_plan(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* o
     int64_t cap = 128;
     while (cap < need) cap <<= 1;
     pl->cap = cap;
-    const size_t N = (size_t)t->N;
-    size_t off = 0;
-    pl->off_tables = off;
-    if (pl->path == PATH_SEGMENTS) {
-        off += up256((size_t)P * (size_t)(pl->nseg + 2) * pl->R * 4);   // a row per segment, one that no request touches, a spare
-        pl->off_spare = off;                              // per-request log records of the segment kernel
-        off += up256((size_t)P * ((size_t)t->N + 1) * 8);            // (and a spare record per replay)
-    } else {
-        off += up256((size_t)P * pl->R * (size_t)cap * 16);
-        pl->off_spare = off;
-        off += up256((size_t)P * (size_t)cap * 16);
+    pl->row_slots = 0;
+    // Rows of stamps instead of tables, where the trace has row slots and a record's words fit a wavefront: where they take no
+    // more memory (nobody's workspace is then too small, and what fitted the static scratch still does), or no more than
+    // ROWS_BYTES and there is room.  Tables / rows, ms: 65 replays of 3,001 requests on 7 replicas 23.6 / 6.7, with caches of 600
+    // blocks (rows the larger) 26.6 / 7.6; 1,024 of 2,000 on 64 with caches of 600 blocks (3.5 GiB of rows) 46.5 / 15.9.
+    if (pl->path == PATH_BLOCKS && !t->row_ref.empty()) {
+        const size_t slots = (size_t)t->n_row_slots, words = 2 + ((size_t)t->max_blocks + 31) / 32;
+        lay_out(t, o, pl);
+        const size_t tables = pl->total;
+        if (words <= 64 && slots * pl->R * 8 < ((size_t)1 << 32)) {
+            pl->row_slots = t->n_row_slots;
+            pl->row_words = (int32_t)words;
+            lay_out(t, o, pl);
+            if (pl->total > tables && (pl->total > room || pl->off_rec > ROWS_BYTES)) pl->row_slots = 0;
+        }
     }
-    pl->off_rec = off;
-    off += up256((size_t)P * N * 16);
-    const bool want_p95_t = !o || o->p95_ttft_ms, want_p95_e = !o || o->p95_e2e_ms;
-    pl->off_route = off;
-    if (pl->path == PATH_BLOCKS) off += up256((size_t)P * N);   // the block kernel's log of choices (its eviction walks it)
-    pl->off_ttft = off;
-    if (!o || (!o->ttft_ms && want_p95_t)) off += up256((size_t)P * N * 8);
-    pl->off_e2e = off;
-    if (!o || (!o->e2e_ms && want_p95_e)) off += up256((size_t)P * N * 8);
-    pl->off_small = off;
-    // rtt, params, scale; tuner constants, ln theta0; seeds of the random policy; rates and budgets of the engine model
-    off += up256((4 * (size_t)pl->R + 8 * (size_t)P + TUNER_CONSTS) * 8);
-    pl->total = off;
+    lay_out(t, o, pl);
     return GORGO_OK;
 }
 
@@ -189,6 +216,21 @@ int gorgo_workspace_bytes(const gorgo_trace* t, const gorgo_model* m, const gorg
 
 namespace {
 
+// Workspace of one generation of the evolution strategy: its evaluation's, then the fitness.
+int es_bytes(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* options, int32_t P, size_t room, size_t* bytes) {
+    int rc = check_model(t, m);
+    if (rc) return rc;
+    gorgo_outputs o;
+    std::memset(&o, 0, sizeof o);
+    o.p95_ttft_ms = reinterpret_cast<double*>(256);   // only which outputs are wanted matters for sizing
+    const size_t fitness = up256(sizeof(double) * (size_t)(P > 0 ? P : 0));
+    Plan pl;
+    rc = make_plan(t, m, options, P, &o, &pl, room > fitness ? room - fitness : 0);
+    if (rc) return rc;
+    *bytes = pl.total + fitness;
+    return GORGO_OK;
+}
+
 // Validation, small copies and launches common to the fixed-weight and the online evaluation.
 int evaluate(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* options, const double* rtt_ms,
              const double* params,
@@ -237,7 +279,7 @@ int evaluate(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* op
     }
     if (!rtt_ms || !params || !scale || !outputs) return fail(GORGO_ERR_INVALID_ARG, "a required pointer is NULL");
     Plan pl;
-    rc = make_plan(t, m, options, P, outputs, &pl);
+    rc = make_plan(t, m, options, P, outputs, &pl, workspace_bytes);
     if (rc) return rc;
     for (int i = 0; i < m->R; ++i)
         if (!std::isfinite(rtt_ms[i]) || rtt_ms[i] < 0 || rtt_ms[i] > 1e9)
@@ -412,6 +454,7 @@ int gorgo_eval_population_static(const gorgo_trace* t, const gorgo_model* m, con
     void* scratch = nullptr;
     size_t have = 0;
     if ((rc = static_scratch(&scratch, &have))) return rc;
+    if (pl.total > have && (rc = make_plan(t, m, options, P, outputs, &pl, have))) return rc;
     if (pl.total > have)
         return fail(GORGO_ERR_WORKSPACE, "this evaluation needs " + std::to_string(pl.total) + " bytes of workspace, the "
                                          "library's static scratch holds " + std::to_string(have) +
@@ -492,16 +535,7 @@ int gorgo_es_workspace_bytes(const gorgo_trace* t, const gorgo_model* m, const g
                              size_t* bytes) {
     clear_error();
     if (!bytes) return fail(GORGO_ERR_INVALID_ARG, "bytes is NULL");
-    int rc = check_model(t, m);
-    if (rc) return rc;
-    gorgo_outputs o;
-    std::memset(&o, 0, sizeof o);
-    o.p95_ttft_ms = reinterpret_cast<double*>(256);   // only which outputs are wanted matters for sizing
-    Plan pl;
-    rc = make_plan(t, m, options, P, &o, &pl);
-    if (rc) return rc;
-    *bytes = pl.total + up256(sizeof(double) * (size_t)P);
-    return GORGO_OK;
+    return es_bytes(t, m, options, P, SIZE_MAX, bytes);
 }
 
 int gorgo_es_step(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* options,
@@ -511,7 +545,7 @@ int gorgo_es_step(const gorgo_trace* t, const gorgo_model* m, const gorgo_option
     clear_error();
     if (!inout) return fail(GORGO_ERR_INVALID_ARG, "state is NULL");
     size_t need = 0;
-    int rc = gorgo_es_workspace_bytes(t, m, options, P, &need);
+    int rc = es_bytes(t, m, options, P, workspace_bytes, &need);
     if (rc) return rc;
     if (!workspace) return fail(GORGO_ERR_WORKSPACE, "workspace is NULL");
     if (workspace_bytes < need)

@@ -22,6 +22,13 @@ struct SegRef {
 constexpr int32_t SEG_FRESH = 1 << 30;
 constexpr int32_t SEG_END_MASK = 0xFFFF;     // (a request has fewer than 2^16 blocks)
 
+// One block of a request, for the block formulation over rows: the row slot of its id, and marks.
+constexpr uint32_t ROW_SLOT = (1u << 27) - 1;
+constexpr uint32_t ROW_FIRST = 1u << 27;         // first occurrence within the request
+constexpr uint32_t ROW_FRESH = 1u << 28;         // the id's first request in the trace: its row starts over there
+constexpr uint32_t ROW_NEW_BEFORE = 1u << 29;    // ... was the request before this one
+constexpr uint32_t ROW_IN_BEFORE = 1u << 30;     // the request before this one has the id as well
+
 // Device-resident copy of a trace (filled lazily by the first evaluation).
 struct DeviceTrace {
     int device = -1;
@@ -35,6 +42,7 @@ struct DeviceTrace {
     const int64_t* seg_off = nullptr;   // [N+1] (chain-consistent traces only)
     const SegRef* seg = nullptr;        // [seg_off[N]]
     const uint32_t* first_hash = nullptr;   // [N] hash of the request's first block (session-affinity policy)
+    const uint32_t* row_ref = nullptr;      // [total] (traces that do not go by segments only)
 };
 
 }  // namespace gorgo
@@ -58,10 +66,15 @@ struct gorgo_trace {
     std::vector<gorgo::SegRef> seg;
     int64_t n_segments = 0;
     int64_t n_slots = 0;             // rows a replay needs: the most segments in use at one time
+    std::vector<uint32_t> row_ref;   // traces that do not go by segments: row slot and marks of every block
+    int64_t n_row_slots = 0;         // the most ids in use at one time
     gorgo::DeviceTrace dev;
 };
 
 namespace gorgo {
+
+// whether a chain-consistent trace's requests are few segments long (each then costs a handful of row reads)
+inline bool segments_suit(const gorgo_trace* t) { return (int64_t)t->seg.size() <= 16 * (t->N > 0 ? t->N : 1); }
 
 // Geometry of one evaluation, computed on the host and handed to the launchers.
 enum ReplayPath { PATH_AUTO = 0, PATH_BLOCKS = 1, PATH_SEGMENTS = 2 };
@@ -72,6 +85,8 @@ struct Plan {
     int32_t P = 0, R = 0, B = 0;
     int64_t N = 0, C = 0;
     int64_t cap = 0;                 // slots per (replay, replica) table, power of two
+    int64_t row_slots = 0;           // block formulation: rows of stamps instead of tables where not 0
+    int32_t row_words = 0;           // ... and words of a log record
     int32_t block_tokens = 0;
     double a_pf = 0, a_dec = 0;
     int32_t packing = 2;             // gorgo_options::replay_packing of the call

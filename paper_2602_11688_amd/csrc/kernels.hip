@@ -17,6 +17,7 @@
 #include "internal.h"
 #include "replay_apart.h"
 #include "replay_blocks.h"
+#include "replay_rows.h"
 #include "replay_segments.h"
 
 namespace gorgo {
@@ -272,7 +273,8 @@ int upload_trace(const gorgo_trace* tc) {
     const size_t o_soff = o_first + up(T);
     const size_t o_seg = o_soff + up(t->seg_off.size() * 8);
     const size_t o_fh = o_seg + up(n_sr * sizeof(SegRef));
-    const size_t total = o_fh + up(N * 4) + 256;
+    const size_t o_row = o_fh + up(N * 4);
+    const size_t total = o_row + up(t->row_ref.size() * 4) + 256;
     char* base = nullptr;
     e = hipMalloc(reinterpret_cast<void**>(&base), total);
     if (e != hipSuccess) return fail(GORGO_ERR_OOM, std::string("hipMalloc(trace): ") + hipGetErrorString(e));
@@ -284,7 +286,8 @@ int upload_trace(const gorgo_trace* tc) {
         (e = put(o_key, t->key.data(), T * 4)) != hipSuccess || (e = put(o_first, t->first.data(), T)) != hipSuccess ||
         (e = put(o_soff, t->seg_off.data(), t->seg_off.size() * 8)) != hipSuccess ||
         (e = put(o_seg, t->seg.data(), n_sr * sizeof(SegRef))) != hipSuccess ||
-        (e = put(o_fh, t->first_hash.data(), N * 4)) != hipSuccess) {
+        (e = put(o_fh, t->first_hash.data(), N * 4)) != hipSuccess ||
+        (e = put(o_row, t->row_ref.data(), t->row_ref.size() * 4)) != hipSuccess) {
         (void)hipFree(base);
         return hip_fail(e, "hipMemcpy(trace)");
     }
@@ -299,6 +302,7 @@ int upload_trace(const gorgo_trace* tc) {
     t->dev.seg_off = reinterpret_cast<const int64_t*>(base + o_soff);
     t->dev.seg = reinterpret_cast<const SegRef*>(base + o_seg);
     t->dev.first_hash = reinterpret_cast<const uint32_t*>(base + o_fh);
+    t->dev.row_ref = reinterpret_cast<const uint32_t*>(base + o_row);
     return GORGO_OK;
 }
 
@@ -467,6 +471,21 @@ void launch_segments(bool engine, bool proxy, const Plan& pl, hipStream_t s, con
     else hipLaunchKernelGGL((replay_segments_kernel<MODE, false, false>), grid, block, lds, s, a);
 }
 
+// The block formulation over rows of stamps: the same instantiations as the block tables'.
+template <int MODE>
+void launch_rows(bool engine, bool proxy, dim3 grid, size_t lds, hipStream_t s, const RowArgs& b) {
+    const dim3 block(ROW_WAVES * WAVE);
+    if constexpr (MODE == MODE_COST_MODEL || MODE == MODE_ONLINE) {
+        if (proxy) {
+            if (engine) hipLaunchKernelGGL((replay_rows_kernel<MODE, true, true>), grid, block, lds, s, b);
+            else hipLaunchKernelGGL((replay_rows_kernel<MODE, false, true>), grid, block, lds, s, b);
+            return;
+        }
+    }
+    if (engine) hipLaunchKernelGGL((replay_rows_kernel<MODE, true, false>), grid, block, lds, s, b);
+    else hipLaunchKernelGGL((replay_rows_kernel<MODE, false, false>), grid, block, lds, s, b);
+}
+
 // The block-table kernel's instantiations: every mode with either replica model; imperfect proxy knowledge concerns
 // the cost model (fixed weights or tuned online) only.
 template <int MODE>
@@ -589,6 +608,28 @@ int launch_replay(const gorgo_trace* t, const Plan& pl, const double* d_rtt, con
                 }
             }
             if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "launch replay_segments_kernel");
+        }
+    } else if (pl.row_slots > 0) {
+        RowArgs b;
+        b.q = a;
+        b.blk_off = t->dev.blk_off;
+        b.ref = t->dev.row_ref;
+        b.cells = reinterpret_cast<int64_t*>(ws + pl.off_tables);
+        b.log = reinterpret_cast<uint32_t*>(ws + pl.off_spare);
+        b.slots = pl.row_slots;
+        b.words = pl.row_words;
+        mark(1, s);                    // (nothing to be cleared: a row starts over before it is first read)
+        if (pl.N > 0 || online) {      // (an empty trace still reports the tuner's initial state)
+            const size_t lds = replay_rows_lds_bytes(pl.R, pl.B, engine != nullptr, a.window);
+            const dim3 grid((unsigned)pl.P);
+            switch (mode) {
+                case MODE_COST_MODEL: launch_rows<MODE_COST_MODEL>(engine != nullptr, proxy != nullptr, grid, lds, s, b); break;
+                case MODE_ONLINE: launch_rows<MODE_ONLINE>(engine != nullptr, proxy != nullptr, grid, lds, s, b); break;
+                case MODE_LEAST_REQUEST: launch_rows<MODE_LEAST_REQUEST>(engine != nullptr, false, grid, lds, s, b); break;
+                case MODE_AFFINITY: launch_rows<MODE_AFFINITY>(engine != nullptr, false, grid, lds, s, b); break;
+                default: launch_rows<MODE_RANDOM>(engine != nullptr, false, grid, lds, s, b); break;
+            }
+            if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "launch replay_rows_kernel");
         }
     } else {
         BlockArgs b;

@@ -74,6 +74,44 @@ class IdMap {
     std::vector<uint32_t> slot_;
 };
 
+// Row slots of single blocks, for traces that do not go by segments: an id has a slot from its first to its last request (see
+// the segments' below; reused oldest-first, not before the next request).
+int block_rows(gorgo_trace* t, const std::vector<KeyInfo>& keys) {
+    const int64_t N = t->N, total = t->total_blocks;
+    struct Use { int32_t last = -1, slot = -1, born = -1, seen = -2, before = -2; };      // `seen`: latest request so far
+    std::vector<Use> use(keys.size());
+    for (size_t k = 1; k < keys.size(); ++k) use[k].last = keys[k].seen_in;
+    std::vector<int32_t> free_slots, gone;
+    size_t head = 0;
+    int32_t n_slots = 0;
+    t->row_ref.resize((size_t)total);
+    for (int64_t r = 0; r < N; ++r) {
+        for (int64_t j = t->blk_off[r]; j < t->blk_off[r + 1]; ++j) {
+            Use& of = use[t->key[(size_t)j]];
+            if (of.slot < 0) {
+                if (head >= free_slots.size() && (uint32_t)n_slots >= ROW_SLOT) {        // (too many: tables only)
+                    t->row_ref.clear();
+                    return GORGO_OK;
+                }
+                of.slot = head < free_slots.size() ? free_slots[head++] : n_slots++;
+                of.born = (int32_t)r;
+            }
+            if (of.seen != r) {
+                of.before = of.seen;
+                of.seen = (int32_t)r;
+            }
+            const bool first = t->first[(size_t)j] != 0;
+            t->row_ref[(size_t)j] = (uint32_t)of.slot | (first ? ROW_FIRST : 0u) | (of.before == r - 1 ? ROW_IN_BEFORE : 0u) |
+                                    (of.born == r ? ROW_FRESH : of.born == r - 1 ? ROW_NEW_BEFORE : 0u);
+            if (first && of.last == r) gone.push_back(of.slot);
+        }
+        free_slots.insert(free_slots.end(), gone.begin(), gone.end());
+        gone.clear();
+    }
+    t->n_row_slots = n_slots;
+    return GORGO_OK;
+}
+
 // Fills key/first/statistics from the raw ids.  Returns 0 or an error code.
 int preprocess(gorgo_trace* t, const int64_t* hash_ids) {
     const int64_t N = t->N;
@@ -131,7 +169,9 @@ int preprocess(gorgo_trace* t, const int64_t* hash_ids) {
     t->seg.clear();
     t->n_segments = 0;
     t->n_slots = 0;
-    if (!consistent) return GORGO_OK;
+    t->row_ref.clear();
+    t->n_row_slots = 0;
+    if (!consistent) return block_rows(t, keys);
 
     // Chain-consistent traces: the keys form a forest and every request is a root-to-node path.  Cut the
     // forest into segments -- maximal runs of keys with a single successor and no request ending inside --
@@ -191,7 +231,7 @@ int preprocess(gorgo_trace* t, const int64_t* hash_ids) {
         }
     }
     t->n_slots = n_slots;
-    return GORGO_OK;
+    return segments_suit(t) ? GORGO_OK : block_rows(t, keys);
 }
 
 int check_and_finish(gorgo_trace* t, const int64_t* hash_ids, int32_t block_tokens) {

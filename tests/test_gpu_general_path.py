@@ -3,10 +3,13 @@ on hashed block tables -- the formulation of the cache state that assumes nothin
 oracle, through the C ABI: on traces that are not chain-consistent (the same id under several predecessors, at
 several positions, twice in one request), where it is the only formulation, and on chain-consistent ones, where it
 has to give what the segment rows give."""
+import re
+
 import numpy as np
 import pytest
 
 import paper_2602_11688_amd as g
+from paper_2602_11688_amd import binding
 from synth import tracegen as tg
 from tests.gpu_helpers import check_population, formulation, load
 from tests.test_gpu_engine import check_engine, check_engine_online, check_engine_policy
@@ -139,6 +142,49 @@ def test_lengths_and_holders_at_the_edges_of_a_step(blocks, R):
                   out_len=rng.integers(1, 50, N).astype(np.int32), blk_off=off, hash_ids=np.concatenate(ids).astype(np.int64))
     model = g.Model(R, 2, 2 * blocks + 3, 0.05, 20.0)
     check_population(tr, model, np.linspace(5.0, 90.0, R), PAR, 1.0, paths=[1])
+
+
+@pytest.mark.parametrize("spare", [0, 7, "all"])
+@pytest.mark.parametrize("blocks", [1, 30, 33, 65, 448, 449, 961, 1984, 1985])
+@pytest.mark.parametrize("R", [1, 7, 64])
+def test_rows_of_stamps_and_tables(monkeypatch, R, blocks, spare):
+    """Block counts around a record's 16, 32 and 64 words and beyond what rows take, caches that hold one request, little
+    more and everything: with the workspace asked for (rows), and with one that is enough for the smaller of both."""
+    rng = np.random.default_rng(1000 * R + blocks)
+    N, told, ids, fresh = 60, [], [], 1
+    for r in range(N):
+        n = int(rng.integers(max(1, blocks // 2), blocks + 1)) if r else blocks
+        base = told[int(rng.integers(0, len(told)))] if told and rng.random() < 0.7 else np.zeros(0, np.int64)
+        keep = base[:int(rng.integers(0, min(n, base.size) + 1))]           # a turn goes on, or branches off
+        new = np.arange(fresh, fresh + n - keep.size)
+        fresh += new.size
+        if fresh > 10 and rng.random() < 0.3:                                # ids of other places, other prompts, or twice
+            at = rng.integers(0, new.size + 1, size=min(3, new.size))
+            new[at[at < new.size]] = rng.integers(1, fresh, size=(at < new.size).sum())
+        told.append(np.concatenate([keep, new]).astype(np.int64))
+    lengths = np.array([x.size for x in told], np.int64)
+    # (nothing of this is chain-consistent: the last request has the second id of the first in front)
+    told[-1] = told[-1].copy()
+    told[-1][0] = told[0][-1] if blocks > 1 else told[0][0]
+    if blocks == 1:
+        told[-2] = np.array([5, 5], np.int64)
+        lengths[-2] = 2
+    tr = tg.Trace(ts_ms=np.cumsum(rng.integers(0, 9000, N)).astype(np.int64), in_len=(512 * lengths - 7).astype(np.int32),
+                  out_len=rng.integers(1, 50, N).astype(np.int32), blk_off=np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64),
+                  hash_ids=np.concatenate(told))
+    most = max(len(set(x.tolist())) for x in told)
+    model = g.Model(R, 2, 0 if spare == "all" else most + spare, 0.05, 20.0)
+    rtt = np.linspace(5.0, 90.0, R)
+    assert not load(tr).info()["chain_consistent"]
+    check_population(tr, model, rtt, PAR, 1.0)
+    enough = binding.workspace_bytes
+    monkeypatch.setattr(binding, "workspace_bytes", lambda *a: 1)
+    with pytest.raises(g.GorgoError, match="needs") as refused:
+        g.eval_population(load(tr), model, rtt, PAR, 1.0)
+    least = int(re.search(r"needs (\d+)", str(refused.value)).group(1))
+    assert least <= enough(load(tr), model, len(PAR))
+    monkeypatch.setattr(binding, "workspace_bytes", lambda *a: least)
+    check_population(tr, model, rtt, PAR, 1.0)
 
 
 @pytest.mark.parametrize("config,n", [(1, 2000), (2, 4000)])
