@@ -65,6 +65,14 @@ int64_t least_table_slots(int64_t resident, int64_t d) { return ((resident + d) 
 // Rows of stamps may be larger than hashed tables up to this many bytes.
 constexpr size_t ROWS_BYTES = (size_t)4 << 30;
 
+// Replays whose policy dictates the routes go replica by replica: up to so many replays, from so many requests on, and with
+// at most this much more workspace.  (Request by request / replica by replica, ms.  One replay: 256 requests on 2 replicas 0.17 /
+// 0.16, on 13 0.18 / 0.10; 10,000 on 2 5.4 / 3.2, on 32 5.2 / 0.35.  10,000 requests, 128 replays on 2 replicas 5.6 / 3.4, on
+// 32 5.4 / 1.7; 256 replays 5.7 / 3.7 and 5.5 / 3.3.  From 512 replays on the shares of either take as long as the replays.)
+constexpr int32_t EACH_REPLAYS = 256;
+constexpr int64_t EACH_REQUESTS = 256;
+constexpr size_t EACH_BYTES = (size_t)1 << 30;
+
 // Workspace carve-up of a plan whose geometry is set.
 void lay_out(const gorgo_trace* t, const gorgo_outputs* o, Plan* pl) {
     const size_t P = (size_t)pl->P, N = (size_t)t->N;
@@ -73,7 +81,7 @@ void lay_out(const gorgo_trace* t, const gorgo_outputs* o, Plan* pl) {
     if (pl->path == PATH_SEGMENTS) {
         off += up256(P * (size_t)(pl->nseg + 2) * pl->R * 4);   // a row per segment, one that no request touches, a spare
         pl->off_spare = off;                              // per-request log records of the segment kernel
-        off += up256(P * (N + 1) * 8);                    // (and a spare record per replay)
+        off += up256(P * (N + (pl->each ? (size_t)pl->R : 1)) * 8);   // (and a spare record per replay, or per share of one)
     } else if (pl->row_slots > 0) {
         off += up256(P * (size_t)pl->row_slots * pl->R * 8);
         pl->off_spare = off;                              // per-request log records
@@ -92,15 +100,18 @@ void lay_out(const gorgo_trace* t, const gorgo_outputs* o, Plan* pl) {
     if (!o || (!o->ttft_ms && want_p95_t)) off += up256(P * N * 8);
     pl->off_e2e = off;
     if (!o || (!o->e2e_ms && want_p95_e)) off += up256(P * N * 8);
+    pl->off_each = off;
+    if (pl->each) off += EachSpace(P, N, t->seg.size(), (size_t)pl->R).total;
     pl->off_small = off;
     // rtt, params, scale; tuner constants, ln theta0; seeds of the random policy; rates and budgets of the engine model
     off += up256((4 * (size_t)pl->R + 8 * P + TUNER_CONSTS) * 8);
     pl->total = off;
 }
 
-// Table geometry and workspace carve-up.  `room`: bytes of workspace there are, where that is known.
+// Table geometry and workspace carve-up.  `room`: bytes of workspace there are, where that is known.  `dictated`: whether the
+// evaluation's policy dictates the routes (or may, where only the size is asked for).
 int make_plan(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* options, int32_t P, const gorgo_outputs* o,
-              Plan* pl, size_t room = SIZE_MAX) {
+              Plan* pl, size_t room = SIZE_MAX, bool dictated = false) {
     if (P < 1 || P > (1 << 20)) return fail(GORGO_ERR_INVALID_ARG, "P must be in 1..2^20");
     gorgo_options opt;
     int orc = take_options(options, &opt);
@@ -134,6 +145,7 @@ int make_plan(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* o
     while (cap < need) cap <<= 1;
     pl->cap = cap;
     pl->row_slots = 0;
+    pl->each = false;
     // Rows of stamps instead of tables, where the trace has row slots and a record's words fit a wavefront: where they take no
     // more memory (nobody's workspace is then too small, and what fitted the static scratch still does), or no more than
     // ROWS_BYTES and there is room.  Tables / rows, ms: 65 replays of 3,001 requests on 7 replicas 23.6 / 6.7, with caches of 600
@@ -150,6 +162,15 @@ int make_plan(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* o
         }
     }
     lay_out(t, o, pl);
+    if (dictated && pl->path == PATH_SEGMENTS && pl->R > 1 && P <= EACH_REPLAYS && t->N >= EACH_REQUESTS) {
+        const size_t without = pl->total;
+        pl->each = true;
+        lay_out(t, o, pl);
+        if (pl->total > room || pl->total - without > EACH_BYTES) {
+            pl->each = false;
+            lay_out(t, o, pl);
+        }
+    }
     return GORGO_OK;
 }
 
@@ -206,7 +227,7 @@ int gorgo_workspace_bytes(const gorgo_trace* t, const gorgo_model* m, const gorg
     int rc = check_model(t, m);
     if (rc) return rc;
     Plan pl;
-    rc = make_plan(t, m, options, P, outputs, &pl);
+    rc = make_plan(t, m, options, P, outputs, &pl, SIZE_MAX, true);
     if (rc) return rc;
     *bytes = pl.total;
     return GORGO_OK;
@@ -279,7 +300,7 @@ int evaluate(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* op
     }
     if (!rtt_ms || !params || !scale || !outputs) return fail(GORGO_ERR_INVALID_ARG, "a required pointer is NULL");
     Plan pl;
-    rc = make_plan(t, m, options, P, outputs, &pl, workspace_bytes);
+    rc = make_plan(t, m, options, P, outputs, &pl, workspace_bytes, policy == GORGO_POLICY_SESSION_AFFINITY || policy == GORGO_POLICY_RANDOM);
     if (rc) return rc;
     for (int i = 0; i < m->R; ++i)
         if (!std::isfinite(rtt_ms[i]) || rtt_ms[i] < 0 || rtt_ms[i] > 1e9)

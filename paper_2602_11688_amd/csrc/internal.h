@@ -42,6 +42,7 @@ struct DeviceTrace {
     const int64_t* seg_off = nullptr;   // [N+1] (chain-consistent traces only)
     const SegRef* seg = nullptr;        // [seg_off[N]]
     const uint32_t* first_hash = nullptr;   // [N] hash of the request's first block (session-affinity policy)
+    const int32_t* seg_prev = nullptr;      // [seg_off[N]] latest request before with the same segment, -1: none
     const uint32_t* row_ref = nullptr;      // [total] (traces that do not go by segments only)
 };
 
@@ -64,6 +65,7 @@ struct gorgo_trace {
     bool chain_consistent = true;
     std::vector<int64_t> seg_off;    // chain-consistent traces: request -> its segments
     std::vector<gorgo::SegRef> seg;
+    std::vector<int32_t> seg_prev;
     int64_t n_segments = 0;
     int64_t n_slots = 0;             // rows a replay needs: the most segments in use at one time
     std::vector<uint32_t> row_ref;   // traces that do not go by segments: row slot and marks of every block
@@ -79,6 +81,37 @@ inline bool segments_suit(const gorgo_trace* t) { return (int64_t)t->seg.size() 
 // Geometry of one evaluation, computed on the host and handed to the launchers.
 enum ReplayPath { PATH_AUTO = 0, PATH_BLOCKS = 1, PATH_SEGMENTS = 2 };
 
+// A share of a chunk's requests (replay_each.h): segment references, blocks, requests.
+struct EachCount {
+    int64_t segs, blocks, count;
+};
+
+// Workspace of replay_each.h (byte offsets): P replays of N requests with T segment references on R replicas.
+struct EachSpace {
+    size_t where, count, from, list, ts, seg_off, blk_off, in_len, out_len, seg, hit, ttft, e2e, total;
+    EachSpace(size_t P, size_t N, size_t T, size_t R) {
+        total = 0;
+        auto take = [&](size_t bytes) {
+            const size_t at = total;
+            total += (bytes + 255) & ~(size_t)255;
+            return at;
+        };
+        where = take(P * N);
+        count = take(P * ((N + 1023) / 1024) * R * sizeof(EachCount));
+        from = take(P * (R + 1) * 4);
+        list = take(P * N * 4);
+        ts = take(P * N * 8);
+        seg_off = take(P * (N + R) * 8);
+        blk_off = take(P * (N + R) * 8);
+        in_len = take(P * N * 4);
+        out_len = take(P * N * 4);
+        seg = take(P * (T + 1) * sizeof(SegRef));
+        hit = take(P * N * 2);
+        ttft = take(P * N * 8);
+        e2e = take(P * N * 8);
+    }
+};
+
 struct Plan {
     int32_t path = PATH_BLOCKS;      // PATH_BLOCKS: hashed block tables; PATH_SEGMENTS: dense segment rows
     int64_t nseg = 0;
@@ -86,12 +119,13 @@ struct Plan {
     int64_t N = 0, C = 0;
     int64_t cap = 0;                 // slots per (replay, replica) table, power of two
     int64_t row_slots = 0;           // block formulation: rows of stamps instead of tables where not 0
+    bool each = false;               // segment formulation: a workgroup per replay and replica (routes that a policy dictates)
     int32_t row_words = 0;           // ... and words of a log record
     int32_t block_tokens = 0;
     double a_pf = 0, a_dec = 0;
     int32_t packing = 2;             // gorgo_options::replay_packing of the call
     // workspace carve-up (byte offsets from the workspace base)
-    size_t off_tables = 0, off_spare = 0, off_rec = 0, off_route = 0, off_ttft = 0, off_e2e = 0, off_small = 0;
+    size_t off_tables = 0, off_spare = 0, off_rec = 0, off_route = 0, off_ttft = 0, off_e2e = 0, off_small = 0, off_each = 0;
     size_t total = 0;
     // [P] nearest-rank percentiles to be computed (device pointers), or null
     double *p95_ttft = nullptr, *p95_e2e = nullptr;

@@ -17,6 +17,7 @@
 #include "internal.h"
 #include "replay_apart.h"
 #include "replay_blocks.h"
+#include "replay_each.h"
 #include "replay_rows.h"
 #include "replay_segments.h"
 
@@ -274,7 +275,8 @@ int upload_trace(const gorgo_trace* tc) {
     const size_t o_seg = o_soff + up(t->seg_off.size() * 8);
     const size_t o_fh = o_seg + up(n_sr * sizeof(SegRef));
     const size_t o_row = o_fh + up(N * 4);
-    const size_t total = o_row + up(t->row_ref.size() * 4) + 256;
+    const size_t o_prev = o_row + up(t->row_ref.size() * 4);
+    const size_t total = o_prev + up(t->seg_prev.size() * 4) + 256;
     char* base = nullptr;
     e = hipMalloc(reinterpret_cast<void**>(&base), total);
     if (e != hipSuccess) return fail(GORGO_ERR_OOM, std::string("hipMalloc(trace): ") + hipGetErrorString(e));
@@ -287,7 +289,8 @@ int upload_trace(const gorgo_trace* tc) {
         (e = put(o_soff, t->seg_off.data(), t->seg_off.size() * 8)) != hipSuccess ||
         (e = put(o_seg, t->seg.data(), n_sr * sizeof(SegRef))) != hipSuccess ||
         (e = put(o_fh, t->first_hash.data(), N * 4)) != hipSuccess ||
-        (e = put(o_row, t->row_ref.data(), t->row_ref.size() * 4)) != hipSuccess) {
+        (e = put(o_row, t->row_ref.data(), t->row_ref.size() * 4)) != hipSuccess ||
+        (e = put(o_prev, t->seg_prev.data(), t->seg_prev.size() * 4)) != hipSuccess) {
         (void)hipFree(base);
         return hip_fail(e, "hipMemcpy(trace)");
     }
@@ -303,6 +306,7 @@ int upload_trace(const gorgo_trace* tc) {
     t->dev.seg = reinterpret_cast<const SegRef*>(base + o_seg);
     t->dev.first_hash = reinterpret_cast<const uint32_t*>(base + o_fh);
     t->dev.row_ref = reinterpret_cast<const uint32_t*>(base + o_row);
+    t->dev.seg_prev = reinterpret_cast<const int32_t*>(base + o_prev);
     return GORGO_OK;
 }
 
@@ -403,6 +407,7 @@ namespace {
 
 // The small inputs on their way to the device, and the never-cached rows filled.  A stream under capture keeps the copies:
 // a graph reads the caller's arrays again at every replay.
+// (a replay laid out by replica has its rows replica by replica)
 int prepare(const Plan& pl, double* d_small, int32_t* last, int64_t rows, hipStream_t s) {
     const size_t R = (size_t)pl.R, P = (size_t)pl.P, count = R + 4 * P;
     SmallInputs in;
@@ -426,7 +431,7 @@ int prepare(const Plan& pl, double* d_small, int32_t* last, int64_t rows, hipStr
     const size_t threads = std::max(as_arguments ? count : 0, last ? P * R : 0);
     if (threads == 0) return GORGO_OK;
     hipLaunchKernelGGL(prepare_replays, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, in, as_arguments ? (int)count : 0,
-                       d_small, last, pl.P, rows, pl.R, NEVER_CACHED);
+                       d_small, last, pl.each ? pl.P * pl.R : pl.P, rows, pl.each ? 1 : pl.R, NEVER_CACHED);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? GORGO_OK : hip_fail(e, "launch prepare_replays");
 }
@@ -469,6 +474,52 @@ void launch_segments(bool engine, bool proxy, const Plan& pl, hipStream_t s, con
     }
     if (engine) hipLaunchKernelGGL((replay_segments_kernel<MODE, true, false>), grid, block, lds, s, a);
     else hipLaunchKernelGGL((replay_segments_kernel<MODE, false, false>), grid, block, lds, s, a);
+}
+
+// Dictated routes: the shares laid out, a replay per share, the outputs back in their order.
+int launch_each(const gorgo_trace* t, const Plan& pl, int mode, bool engine, const SegArgs& a, char* ws, hipStream_t s) {
+    const size_t P = (size_t)pl.P, N = (size_t)pl.N, R = (size_t)pl.R;
+    const EachSpace at(P, N, t->seg.size(), R);
+    char* const base = ws + pl.off_each;
+    EachArgs e;
+    e.ts = a.ts;
+    e.seg_off = a.seg_off;
+    e.blk_off = a.blk_off;
+    e.in_len = a.in_len;
+    e.out_len = a.out_len;
+    e.seg = a.seg;
+    e.seg_prev = t->dev.seg_prev;
+    e.first_hash = a.first_hash;
+    e.seeds = a.seeds;
+    e.N = pl.N;
+    e.T = (int64_t)t->seg.size();
+    e.R = pl.R;
+    e.chunks = (int32_t)((N + EACH_CHUNK - 1) / EACH_CHUNK);
+    e.where = reinterpret_cast<uint8_t*>(base + at.where);
+    e.count = reinterpret_cast<EachCount*>(base + at.count);
+    e.from = reinterpret_cast<int32_t*>(base + at.from);
+    e.list = reinterpret_cast<int32_t*>(base + at.list);
+    e.s_ts = reinterpret_cast<int64_t*>(base + at.ts);
+    e.s_seg_off = reinterpret_cast<int64_t*>(base + at.seg_off);
+    e.s_blk_off = reinterpret_cast<int64_t*>(base + at.blk_off);
+    e.s_in = reinterpret_cast<int32_t*>(base + at.in_len);
+    e.s_out = reinterpret_cast<int32_t*>(base + at.out_len);
+    e.s_seg = reinterpret_cast<SegRef*>(base + at.seg);
+    e.hit = a.hit ? reinterpret_cast<uint16_t*>(base + at.hit) : nullptr;
+    e.ttft = a.ttft ? reinterpret_cast<double*>(base + at.ttft) : nullptr;
+    e.e2e = a.e2e ? reinterpret_cast<double*>(base + at.e2e) : nullptr;
+    const dim3 chunks((unsigned)e.chunks, (unsigned)P), threads(EACH_CHUNK);
+    if (mode == MODE_AFFINITY) hipLaunchKernelGGL((each_route<MODE_AFFINITY>), chunks, threads, 0, s, e);
+    else hipLaunchKernelGGL((each_route<MODE_RANDOM>), chunks, threads, 0, s, e);
+    hipLaunchKernelGGL(each_begin, dim3((unsigned)P), dim3(WAVE), 0, s, e);
+    hipLaunchKernelGGL(each_place, chunks, threads, 0, s, e);
+    const dim3 shares((unsigned)(P * R)), block(APART_WAVES * WAVE);
+    const size_t lds = replay_queue_lds_bytes(1, pl.B, engine, 0);
+    if (engine) hipLaunchKernelGGL((replay_each_kernel<true>), shares, block, lds, s, a, e);
+    else hipLaunchKernelGGL((replay_each_kernel<false>), shares, block, lds, s, a, e);
+    hipLaunchKernelGGL(each_return, chunks, threads, 0, s, e, a.route, a.hit, a.ttft, a.e2e);
+    const hipError_t rc = hipGetLastError();
+    return rc == hipSuccess ? GORGO_OK : hip_fail(rc, "launch replay_each_kernel");
 }
 
 // The block formulation over rows of stamps: the same instantiations as the block tables'.
@@ -588,7 +639,9 @@ int launch_replay(const gorgo_trace* t, const Plan& pl, const double* d_rtt, con
     if (segments) {
         mark(1, s);
         if (pl.N > 0 || online) {      // (an empty trace still reports the tuner's initial state)
-            if (mode == MODE_COST_MODEL && !engine && !proxy && !sections && pack_replays(pl, a.nseg)) {
+            if (pl.each) {
+                if ((rc = launch_each(t, pl, mode, engine != nullptr, a, ws, s))) return rc;
+            } else if (mode == MODE_COST_MODEL && !engine && !proxy && !sections && pack_replays(pl, a.nseg)) {
                 hipLaunchKernelGGL((replay_segments_kernel<MODE_COST_MODEL, false, false, 2>), dim3((unsigned)(pl.P / 2)),
                                    dim3(seg_threads<2>()), 2 * replay_queue_lds_bytes(pl.R, pl.B, false, 0), s, a);
             } else if (sections && spread_replays(pl)) {

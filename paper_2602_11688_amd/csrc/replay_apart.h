@@ -205,9 +205,8 @@ struct ApartCursor {
 };
 
 template <bool PROXY, bool TIMED, class Comm>
-__device__ __forceinline__ void apart_evict_wave(const SegArgs& a, int lane, Comm* comm) {
+__device__ __forceinline__ void apart_evict_wave(const SegArgs& a, size_t p, int lane, Comm* comm) {
     const int R = a.R, N = (int)a.N;
-    const size_t p = blockIdx.x;
     const unsigned row_bytes = (unsigned)R * 4u;
     const unsigned spare_row = (unsigned)(a.nseg - 1) * row_bytes;
     const unsigned lane_off = (unsigned)(lane < R ? lane : 0) * 4u;
@@ -362,9 +361,8 @@ __device__ __forceinline__ void apart_evict_wave(const SegArgs& a, int lane, Com
 // As book_wave of replay_segments.h; also touches, eight requests at a time, the rows and the lines of the trace that the front
 // end is going to read.  (Loads whose values only keep them: this wavefront waits for none.)
 template <bool PROXY, bool TIMED, class Comm>
-__device__ __forceinline__ void apart_book_wave(const SegArgs& a, int lane, Comm* comm) {
+__device__ __forceinline__ void apart_book_wave(const SegArgs& a, size_t p, int lane, Comm* comm) {
     const int R = a.R, N = (int)a.N;
-    const size_t p = blockIdx.x;
     const bool in = lane < R;
     const unsigned row_bytes = (unsigned)R * 4u;
     const unsigned spare_row = (unsigned)(a.nseg - 1) * row_bytes;
@@ -384,16 +382,21 @@ __device__ __forceinline__ void apart_book_wave(const SegArgs& a, int lane, Comm
     const bool wide = (row_bytes & 127u) != 0 || row_bytes > 128u;      // (rows that straddle a cache line, or are longer)
     const int64_t refs = a.seg_off[N];
     // (a lane per array; a group of eight requests is 32 or 64 bytes of each; one reference behind the last is there to be read)
+    // (the arrays' addresses by value: a lane would otherwise pick the argument that it loads its address from, and arguments
+    // that a workgroup has worked out would have to lie in memory)
+    auto value = [](const void* of) {
+        uint64_t x = reinterpret_cast<uint64_t>(of);
+        asm("" : "+s"(x));
+        return x;
+    };
+    const uint64_t at0 = value(a.ts), at1 = value(a.seg_off), at2 = value(a.blk_off), at3 = value(a.in_len), at4 = value(a.out_len),
+                   at5 = value(a.seg);
+    const uint64_t my_array = lane >= 5 && lane < 21 ? at5 : lane == 4 ? at4 : lane == 3 ? at3 : lane == 2 ? at2 : lane == 1 ? at1 : at0;
+    const int log_size = lane == 3 || lane == 4 ? 2 : 3;
+    static_assert(sizeof(SegRef) == 8);
     auto touch_trace = [&](int x, int64_t j0) {
-        const int64_t r = x < N ? x : N - 1;
-        const void* at = &a.ts[r];
-        at = lane == 1 ? (const void*)&a.seg_off[r] : at;
-        at = lane == 2 ? (const void*)&a.blk_off[r] : at;
-        at = lane == 3 ? (const void*)&a.in_len[r] : at;
-        at = lane == 4 ? (const void*)&a.out_len[r] : at;
-        const int64_t j = j0 + (lane - 4) * 16;
-        at = lane >= 5 && lane < 21 ? (const void*)&a.seg[j < refs ? j : refs] : at;
-        return ld(reinterpret_cast<const int32_t*>(at));
+        const int64_t j = j0 + (lane - 4) * 16, k = lane >= 5 && lane < 21 ? (j < refs ? j : refs) : x < N ? x : N - 1;
+        return ld(reinterpret_cast<const int32_t*>(my_array + ((uint64_t)k << log_size)));
     };
     meet(true);                               // the first descriptors are there
     meet(true);
@@ -486,10 +489,10 @@ __device__ __forceinline__ void apart_book_wave(const SegArgs& a, int lane, Comm
 // it enters r - 1, which has not completed by the arrival of r + 1 (else the serving wavefront has dealt with it), and retires
 // what completes by the arrival of r + 2, r itself aside.
 template <bool PROXY, bool TIMED, class Comm>
-__device__ __forceinline__ void apart_retire_wave(const SegArgs& a, int lane, SlotQueues& Q, Comm* comm) {
+__device__ __forceinline__ void apart_retire_wave(const SegArgs& a, size_t p, int lane, SlotQueues& Q, Comm* comm) {
     const int N = (int)a.N;
-    Rec* const rec = a.rec + (size_t)blockIdx.x * N;
-    const double sc = a.scale[blockIdx.x];
+    Rec* const rec = a.rec + p * N;
+    const double sc = a.scale[p];
     if (lane == 0) comm->served[1].at = -1;   // (there is nothing before the first request)
     meet(true);                               // the first descriptors are there
     double t1 = (double)a.ts[N > 1 ? 1 : 0] * sc;
@@ -515,7 +518,7 @@ __device__ __forceinline__ void apart_retire_wave(const SegArgs& a, int lane, Sl
         t1 = t2;
     }
     if (TIMED && a.sections && lane == 0) {
-        for (int k = 2; k < 4; ++k) a.sections[((size_t)blockIdx.x * 3 + 1) * SECTIONS + k] = clk.acc[k];
+        for (int k = 2; k < 4; ++k) a.sections[(p * 3 + 1) * SECTIONS + k] = clk.acc[k];
     }
 }
 
@@ -523,10 +526,9 @@ __device__ __forceinline__ void apart_retire_wave(const SegArgs& a, int lane, Sl
 // Serving wavefront: after X(r) it serves r and hands it to the retiring wavefront, unless r completes by the arrival of
 // r + 2: then it takes r from the load signal itself.  The times at which the slots become free are its own.
 template <int MODE, bool ENGINE, bool PROXY, bool TIMED, class Comm>
-__device__ __forceinline__ void apart_serve_wave(const SegArgs& a, int lane, SlotQueues& Q, double* window, Comm* comm) {
+__device__ __forceinline__ void apart_serve_wave(const SegArgs& a, size_t p, int lane, SlotQueues& Q, double* window, Comm* comm) {
     constexpr bool COUNTS = MODE == MODE_LEAST_REQUEST;      // the load signal is the number of requests, not their tokens
     const int N = (int)a.N;
-    const size_t p = blockIdx.x;
     const double sc = a.scale[p];
     Tuner<MODE == MODE_ONLINE> tuner(a, p, window, lane);
     if (MODE == MODE_ONLINE && lane < 3) comm->w[0][lane] = a.params[3 * p + lane];
@@ -617,13 +619,12 @@ __device__ __forceinline__ void apart_serve_wave(const SegArgs& a, int lane, Slo
 
 // ---------------------------------------------------------------------------------------------- deciding
 template <int MODE, bool ENGINE, bool PROXY, bool TIMED, class Comm>
-__device__ __forceinline__ void apart_decide_wave(const SegArgs& a, int lane, Comm* comm) {
+__device__ __forceinline__ void apart_decide_wave(const SegArgs& a, size_t p, int lane, Comm* comm) {
     constexpr bool ONLINE = MODE == MODE_ONLINE;
     constexpr bool SCORED = MODE == MODE_COST_MODEL || MODE == MODE_ONLINE;
     constexpr bool COUNTS = MODE == MODE_LEAST_REQUEST;
-    constexpr bool DICTATED = MODE == MODE_AFFINITY || MODE == MODE_RANDOM;
+    constexpr bool DICTATED = MODE == MODE_AFFINITY || MODE == MODE_RANDOM || MODE == MODE_GIVEN;
     const int R = a.R, N = (int)a.N;
-    const size_t p = blockIdx.x;
     const bool in = lane < R;
     double w_rtt = a.params[3 * p + 0], w_prefill = a.params[3 * p + 1], w_queue = a.params[3 * p + 2];
     double my_rtt = !PROXY && in ? a.rtt[lane] : 0.0;            // (proxy variants: comes from the serving wavefront)
@@ -682,7 +683,7 @@ __device__ __forceinline__ void apart_decide_wave(const SegArgs& a, int lane, Co
     for (int next = 0; next < N; ++next) {
         const int r = __builtin_amdgcn_readfirstlane(next);
         const SegDesc* const dr = &comm->ring[r & (DESC_RING - 1)];
-        const int target = DICTATED ? dr->target : 0;
+        const int target = DICTATED && MODE != MODE_GIVEN ? dr->target : 0;
         look();
         double left = DICTATED ? 0.0 : comm->gone[r & 1][lane];      // (read again behind Y(r - 1))
         // (what the choice before adds to the load signal, while LDS is read)
@@ -882,40 +883,45 @@ __device__ __forceinline__ void apart_decide_wave(const SegArgs& a, int lane, Co
         for (int k = 0; k < 8; ++k) a.sections[p * 3 * SECTIONS + k] = clk.acc[k];
 }
 
-// One workgroup = one replay; two fit a CU whatever the shape (at most 128 vector registers, 84 KiB of LDS).
-template <int MODE, bool ENGINE, bool PROXY, bool TIMED = false>
-__global__ void __launch_bounds__(APART_WAVES * WAVE, 4) replay_apart_kernel(SegArgs a) {
-    extern __shared__ __align__(16) unsigned char lds_raw[];
+// Replay p by one workgroup; two fit a CU whatever the shape (at most 128 vector registers, 84 KiB of LDS).
+template <int MODE, bool ENGINE, bool PROXY, bool TIMED>
+__device__ __forceinline__ void apart_replay(const SegArgs& a, size_t p, unsigned char* lds_raw) {
     __shared__ ApartHandover<PROXY> comm;
     const int lane = threadIdx.x & (WAVE - 1);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
     double* const window = reinterpret_cast<double*>(lds_raw + SlotQueues::bytes(a.R, a.B, ENGINE));
     if (a.N == 0) {           // (an empty trace still reports the tuner's initial state)
-        if (wave == 1) Tuner<MODE == MODE_ONLINE>(a, blockIdx.x, window, lane).results();
+        if (wave == 1) Tuner<MODE == MODE_ONLINE>(a, p, window, lane).results();
         return;
     }
     if (wave == 0) {
         __builtin_amdgcn_s_setprio(3);      // the wavefront on the chain goes first at issue
-        apart_decide_wave<MODE, ENGINE, PROXY, TIMED>(a, lane, &comm);
+        apart_decide_wave<MODE, ENGINE, PROXY, TIMED>(a, p, lane, &comm);
     } else if (wave == 1) {
         __builtin_amdgcn_s_setprio(2);
         SlotQueues Q;
         Q.init(lds_raw, a.R, a.B, ENGINE, lane);
-        apart_serve_wave<MODE, ENGINE, PROXY, TIMED>(a, lane, Q, window, &comm);
+        apart_serve_wave<MODE, ENGINE, PROXY, TIMED>(a, p, lane, Q, window, &comm);
     } else if (wave == 2) {
         __builtin_amdgcn_s_setprio(2);
         SlotQueues Q;
         Q.attach(lds_raw, a.R, a.B);
-        apart_retire_wave<PROXY, TIMED>(a, lane, Q, &comm);
+        apart_retire_wave<PROXY, TIMED>(a, p, lane, Q, &comm);
     } else if (wave == 3) {
         __builtin_amdgcn_s_setprio(1);
-        apart_book_wave<PROXY, TIMED>(a, lane, &comm);
+        apart_book_wave<PROXY, TIMED>(a, p, lane, &comm);
     } else if (wave == 4) {
         __builtin_amdgcn_s_setprio(2);
-        apart_evict_wave<PROXY, TIMED>(a, lane, &comm);
+        apart_evict_wave<PROXY, TIMED>(a, p, lane, &comm);
     } else {
         front_wave<MODE, PROXY, 1, TIMED>(a, lane, &comm);
     }
+}
+
+template <int MODE, bool ENGINE, bool PROXY, bool TIMED = false>
+__global__ void __launch_bounds__(APART_WAVES * WAVE, 4) replay_apart_kernel(SegArgs a) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    apart_replay<MODE, ENGINE, PROXY, TIMED>(a, blockIdx.x, lds_raw);
 }
 
 }  // namespace gorgo

@@ -115,8 +115,8 @@ struct SegArgs {
 
 // What picks the replica: the cost model of Eq. 3 with fixed weights, the same with the online tuner, or one
 // of the baseline policies of Sec. 4 (prefix-cache and proxy-only least-load are the cost model with weights
-// (0, 1, 0) and (0, 0, 1)).
-enum SegMode { MODE_COST_MODEL = 0, MODE_ONLINE = 1, MODE_LEAST_REQUEST = 2, MODE_AFFINITY = 3, MODE_RANDOM = 4 };
+// (0, 1, 0) and (0, 0, 1)); MODE_GIVEN: there is one replica (a workgroup of replay_each.h).
+enum SegMode { MODE_COST_MODEL = 0, MODE_ONLINE = 1, MODE_LEAST_REQUEST = 2, MODE_AFFINITY = 3, MODE_RANDOM = 4, MODE_GIVEN = 5 };
 
 // A 32-bit value spread over R replicas: floor(h * R / 2^32).
 __device__ __forceinline__ int spread(uint32_t h, int R) { return (int)(((uint64_t)h * (uint64_t)R) >> 32); }
@@ -613,7 +613,7 @@ __device__ __forceinline__ void front_wave(const SegArgs& a, int lane, Comm* com
     constexpr bool SIGNAL = MODE == MODE_COST_MODEL || MODE == MODE_ONLINE || MODE == MODE_LEAST_REQUEST;
     const int R = a.R, N = (int)a.N;
     const int q = lane / SEG_CHUNK, k = lane % SEG_CHUNK;
-    const size_t p = (size_t)blockIdx.x * PACK;
+    const size_t p = MODE == MODE_GIVEN ? 0 : (size_t)blockIdx.x * PACK;
     const double scale0 = a.scale[p], scale1 = PACK == 2 ? a.scale[p + 1] : 0.0;
     const uint64_t seed = MODE == MODE_RANDOM ? a.seeds[p] : 0;
     const uint32_t row_bytes = (uint32_t)R * 4u;

@@ -169,6 +169,7 @@ int preprocess(gorgo_trace* t, const int64_t* hash_ids) {
     t->seg.clear();
     t->n_segments = 0;
     t->n_slots = 0;
+    t->seg_prev.clear();
     t->row_ref.clear();
     t->n_row_slots = 0;
     if (!consistent) return block_rows(t, keys);
@@ -203,9 +204,14 @@ int preprocess(gorgo_trace* t, const int64_t* hash_ids) {
     // time only the segments of conversations still going on are between the two.  So segments share rows: a
     // segment takes a slot at its first reference -- marked SEG_FRESH in that reference, where the replay resets
     // the row before anything reads it -- and gives it back after its last one.  Slots are reused oldest-first.
-    std::vector<int64_t> last_ref((size_t)nseg, -1);
+    std::vector<int32_t> last_ref((size_t)nseg, -1);
+    t->seg_prev.resize(t->seg.size());
     for (int64_t r = 0; r < N; ++r)
-        for (int64_t j = t->seg_off[(size_t)r]; j < t->seg_off[(size_t)r + 1]; ++j) last_ref[(size_t)t->seg[(size_t)j].id] = r;
+        for (int64_t j = t->seg_off[(size_t)r]; j < t->seg_off[(size_t)r + 1]; ++j) {
+            int32_t& of = last_ref[(size_t)t->seg[(size_t)j].id];
+            t->seg_prev[(size_t)j] = of;
+            of = (int32_t)r;
+        }
     std::vector<int32_t> slot_of((size_t)nseg, -1);
     std::vector<int32_t> free_slots;       // a queue: taken from `head`, given back at the end
     size_t head = 0;

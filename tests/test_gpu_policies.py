@@ -1,11 +1,15 @@
 """GPU parity of the baseline policies (Sec. 4 "Baseline policies") against the CPU oracle, through the C ABI."""
+import re
+
 import numpy as np
 import pytest
 
 import paper_2602_11688_amd as g
+from paper_2602_11688_amd import binding
 from oracle import binding as ob
 from synth import tracegen as tg
-from tests.gpu_helpers import assert_replay_equal, gpu_eval, load
+from tests.gpu_helpers import assert_replay_equal, formulation, gpu_eval, load
+from tests.test_gpu_engine import check_engine_policy
 
 pytestmark = pytest.mark.gpu
 
@@ -53,6 +57,39 @@ def test_policies_at_the_replica_and_slot_limits():
     for policy in ("least-request", "session-affinity", "random"):
         _check(tr, g.Model(64, 16, 40, 0.05, 20.0), rtt, policy, [1.0], np.array([3], np.uint64))
     _check(tr, g.Model(1, 64, 12, 0.05, 20.0), [9.0], "least-request", [1.0])
+
+
+@pytest.mark.parametrize("N", [255, 256, 1023, 1024, 1025, 2500])
+@pytest.mark.parametrize("R", [1, 2, 7, 64])
+def test_dictated_routes_replica_by_replica(monkeypatch, R, N):
+    """Replays laid out by replica (a share each, from 256 requests on) at the edges of a chunk of 1,024 requests, with requests
+    without blocks, replicas that get next to nothing and caches that hold little or everything; and the same calls with a
+    workspace that is too small for it, which go request by request."""
+    tr = tg.random_forest(100 * R + N, N, roots=2 * R, max_blocks=24, gap_ms=300)
+    keep = np.repeat(np.arange(N) % 41 != 7, np.diff(tr.blk_off))
+    size = np.where(np.arange(N) % 41 != 7, np.diff(tr.blk_off), 0)
+    tr = tg.Trace(tr.ts_ms, tr.in_len, tr.out_len, np.concatenate([[0], np.cumsum(size)]).astype(np.int64), tr.hash_ids[keep])
+    model, rtt = g.Model(R, 3, 0 if N % 2 else 40, 0.05, 20.0), np.linspace(5.0, 90.0, R)
+    eng = g.Engine(np.linspace(0.03, 0.08, R), np.linspace(15.0, 25.0, R), np.full(R, 40000, np.int64), 0.05)
+
+    def go():
+        for policy in ("session-affinity", "random"):
+            _check(tr, model, rtt, policy, [1.0, 0.25, 3.0], np.array([11, 2**50 + 3, 7], np.uint64))
+            check_engine_policy(tr, model, eng, rtt, policy, [1.0, 0.5], np.array([4, 5], np.uint64))
+
+    size_of = binding.workspace_bytes
+    with formulation(2):
+        go()
+        least = {}
+        for P in (2, 3):
+            asked = []
+            monkeypatch.setattr(binding, "workspace_bytes", lambda *a: asked.append(size_of(*a)) or 1)
+            with pytest.raises(g.GorgoError, match="needs") as refused:
+                g.eval_policy(load(tr), model, rtt, "random", [1.0] * P, seeds=np.arange(P, dtype=np.uint64))
+            least[P] = int(re.search(r"needs (\d+)", str(refused.value)).group(1))
+            assert (least[P] < asked[0]) == (N >= 256 and R > 1)
+        monkeypatch.setattr(binding, "workspace_bytes", lambda trace, model, P, *rest: least[P])
+        go()
 
 
 def test_special_case_weights_are_the_other_two_baselines():
