@@ -74,6 +74,50 @@ def test_jsonl_loader_errors(tmp_path, text, code):
     assert e.value.code == code and len(str(e.value)) > 15
 
 
+def _record(r):
+    return '{"timestamp": %d, "input_length": 700, "output_length": 3, "hash_ids": [%d, %d]}' % (r, 2 * r, 2 * r + 1)
+
+
+@pytest.mark.parametrize("N", [1, 1900, 2000, 20000])          # (a thread from 128 KiB on: about 1,850 of these lines)
+@pytest.mark.parametrize("end", ["\n", "\r\n", "\n \t\n"])
+@pytest.mark.parametrize("last", [True, False])
+def test_jsonl_loader_in_pieces(tmp_path, N, end, last):
+    """Files of one piece and of several: nothing is lost, doubled or out of order at their edges (the times are the numbers of
+    the requests and have to rise), with and without the last line's end; and an error is told with its line."""
+    p = tmp_path / "t.jsonl"
+    lines = [_record(r) for r in range(N)]
+    p.write_bytes((end.join(lines) + (end if last else "")).encode())
+    info = g.Trace.from_jsonl(str(p)).info()
+    assert (info["N"], info["total_blocks"], info["unique_ids"]) == (N, 2 * N, 2 * N)
+    per = end.count("\n")
+    for bad in sorted({0, N // 3, N // 2, N - 1}):
+        wrong = list(lines)
+        wrong[bad] = wrong[bad].replace("output", "input")
+        wrong[-1] = wrong[-1] if bad == N - 1 else "{"           # (the first one counts)
+        p.write_bytes((end.join(wrong) + (end if last else "")).encode())
+        with pytest.raises(g.GorgoError, match=f"line {bad * per + 1}: needs"):
+            g.Trace.from_jsonl(str(p))
+    p.write_bytes((end.join(lines[:-1] + ["{"])).encode())
+    with pytest.raises(g.GorgoError, match=f"malformed record on line {(N - 1) * per + 1}$"):
+        g.Trace.from_jsonl(str(p))
+
+
+def test_jsonl_loader_with_long_lines_and_nuls(tmp_path):
+    p = tmp_path / "t.jsonl"
+    # a line that is longer than what is read at a time, in the middle
+    lines = [_record(r).encode() for r in range(5)]
+    lines[2] = lines[2][:-1] + b', "note": "' + b"x" * (34 << 20) + b'"}'
+    p.write_bytes(b"\n".join(lines))
+    assert g.Trace.from_jsonl(str(p)).info()["N"] == 5
+    # a NUL ends what is read of a line, not the line: the next one goes on with it
+    lines = [_record(r).encode() for r in range(4000)]
+    p.write_bytes(b"\n".join(lines[:1000] + [b"\0skipped"] + lines[1000:]))
+    assert g.Trace.from_jsonl(str(p)).info()["N"] == 4000
+    p.write_bytes(b"\n".join(lines[:3000] + [lines[3000] + b"\0"] + lines[3001:]))
+    with pytest.raises(g.GorgoError, match="malformed record on line 3001$"):
+        g.Trace.from_jsonl(str(p))
+
+
 def test_loader_io_and_argument_errors(tmp_path):
     with pytest.raises(g.GorgoError) as e:
         g.Trace.from_jsonl(str(tmp_path / "missing.jsonl"))
