@@ -121,14 +121,19 @@ struct ApartCursor {
         pend_own = owner == pend_r ? end : pend_own;
         return ring_cnt > 0 && owner <= ring_hi;
     }
-    __device__ __forceinline__ void disowned_in_ring(int owner, int end) {
-#pragma nounroll
-        for (int k = 0; k < APART_LOOK; ++k) {
-            const unsigned long long e = *at(k);
-            const bool it = ((k - ring_head) & (APART_LOOK - 1)) < ring_cnt && (int)(unsigned)e == owner;
-            if (it) *at(k) = (e & ~(0xFFFFull << 32)) | ((unsigned long long)(unsigned)end << 32);
-            stock -= it ? end - (int)((e >> 32) & 0xFFFFu) : 0;
-        }
+    // The same for the records in the ring of replica `best`, a lane per slot (all lanes together).  With few requests in a
+    // replica's log this is looked for at nearly every request: slot after slot, a trip to LDS each, it was the longest of the
+    // chains.  (19 replays on 29 replicas: 292 requests 305 us, so 184; 4,672 4.40 ms, 2.92.)
+    __device__ __forceinline__ void disowned_in_ring(int best, int owner, int end, int lane) {
+        const int head = __builtin_amdgcn_readlane(ring_head, best), cnt = __builtin_amdgcn_readlane(ring_cnt, best);
+        unsigned long long* const slot = ring - lane + best + (lane & (APART_LOOK - 1)) * WAVE;
+        const unsigned long long e = *slot;
+        const bool it = lane < APART_LOOK && ((lane - head) & (APART_LOOK - 1)) < cnt && (int)(unsigned)e == owner;
+        if (it) *slot = (e & ~(0xFFFFull << 32)) | ((unsigned long long)(unsigned)end << 32);
+        asm volatile("" ::: "memory");       // (another lane's slot: nothing read before is to be taken for it)
+        const unsigned long long found = ballot(it);
+        const int own = __builtin_amdgcn_readlane((int)(e >> 32), found != 0 ? __builtin_ctzll(found) : 0) & 0xFFFF;
+        stock -= found != 0 && lane == best ? end - own : 0;
     }
     // takes up to E blocks from the owned suffix of the cursor's record
     __device__ __forceinline__ void take_from_cursor(int& E) {
@@ -209,9 +214,7 @@ __device__ __forceinline__ void apart_evict_wave(const SegArgs& a, size_t p, int
     const int R = a.R, N = (int)a.N;
     const unsigned row_bytes = (unsigned)R * 4u;
     const unsigned spare_row = (unsigned)(a.nseg - 1) * row_bytes;
-    const unsigned lane_off = (unsigned)(lane < R ? lane : 0) * 4u;
     const char* const rows = reinterpret_cast<const char*>(a.last + p * (size_t)a.nseg * R);
-    auto cell_at = [&](uint32_t rowoff) { return reinterpret_cast<const int32_t*>(rows + (rowoff + lane_off)); };
     LogRec* const log = a.log + p * ((size_t)N + 1);
     const unsigned long long* const log64 = reinterpret_cast<const unsigned long long*>(log);
     const int spare = N;                      // the log record behind the last request's
@@ -251,7 +254,7 @@ __device__ __forceinline__ void apart_evict_wave(const SegArgs& a, size_t p, int
         clk.tick(4);                                                 // cursors
         meet(true);                                                  // X(r)
         clk.tick(5);                                                 // waiting at X
-        const int best = comm->best[r & 1][0];
+        const int best = __builtin_amdgcn_readfirstlane(comm->best[r & 1][0]);
         const Choice<PROXY> c = comm->choice[r & 1][lane];           // (of this lane's replica: no second trip to LDS)
         const bool is_best = lane == best;
         int owner = is_best ? c.owner : spare;
@@ -262,37 +265,36 @@ __device__ __forceinline__ void apart_evict_wave(const SegArgs& a, size_t p, int
             // evicted belongs to requests the cursor has passed, or to the cursor's request beyond its position).  The rows are
             // read as they still are: the book-keeping wavefront waits.
             ++n_walks;
-            bool walking = owner == OWN_WALK;
-            const int cb_r = PROXY ? c2.cur_r : c1.cur_r, cb_k = PROXY ? c2.cur_k : c1.cur_k;
+            const int cb_r = __builtin_amdgcn_readlane(PROXY ? c2.cur_r : c1.cur_r, best);
+            const int cb_k = __builtin_amdgcn_readlane(PROXY ? c2.cur_k : c1.cur_k, best);
             int run_owner = -1, run_end = 0, vpos = 0;
+            bool walking = true;
             auto changed = [&](int of, int to) {
                 st(&log[of].own, (uint16_t)to);
-                if (c1.disowned(of, to)) c1.disowned_in_ring(of, to);
-                if (PROXY && c2.disowned(of, to)) c2.disowned_in_ring(of, to);
-            };
-            const int64_t j0 = d->j0;
-            for (int j = 0; j < s && ballot(walking) != 0; j += SEG_CHUNK) {
-                int32_t at[SEG_CHUNK];
-                int to[SEG_CHUNK];
-#pragma unroll
-                for (int k = 0; k < SEG_CHUNK; ++k) {
-                    // (past the last segment: nothing)
-                    const SegRef sr = a.seg[j0 + (j + k < s ? j + k : s - 1)];
-                    const bool fresh = (sr.end & SEG_FRESH) != 0 || j + k >= s;
-                    to[k] = sr.end & SEG_END_MASK;
-                    at[k] = ld(cell_at(fresh ? spare_row : (uint32_t)sr.id * row_bytes));
-                    at[k] = fresh ? NEVER_CACHED : at[k];
+                const int its = is_best ? of : spare;
+                if (ballot(c1.disowned(its, to)) != 0) c1.disowned_in_ring(best, of, to, lane);
+                if (PROXY) {
+                    if (ballot(c2.disowned(its, to)) != 0) c2.disowned_in_ring(best, of, to, lane);
                 }
-#pragma unroll
-                for (int k = 0; k < SEG_CHUNK; ++k) {
-                    const int cnt = walking ? cached_in(at[k], vpos, to[k], cb_r, cb_k) : 0;
+            };
+            // (lane = segment: one load for the references, one for the cells)
+            const int64_t j0 = d->j0;
+            for (int j = 0; j < s && walking; j += WAVE) {
+                const SegRef sr = a.seg[j0 + (j + lane < s ? j + lane : s - 1)];
+                const bool fresh = (sr.end & SEG_FRESH) != 0;
+                const int32_t cell = ld(reinterpret_cast<const int32_t*>(rows + (fresh ? spare_row : (uint32_t)sr.id * row_bytes) +
+                                                                         (unsigned)best * 4u));
+                const int my_at = fresh ? NEVER_CACHED : cell, my_to = sr.end & SEG_END_MASK;
+                for (int k = 0; k < WAVE && j + k < s && walking; ++k) {
+                    const int at = __builtin_amdgcn_readlane(my_at, k), to = __builtin_amdgcn_readlane(my_to, k);
+                    const int cnt = cached_in(at, vpos, to, cb_r, cb_k);
                     if (cnt > 0) {
-                        if (at[k] != run_owner && run_owner >= 0) changed(run_owner, run_end);
-                        run_owner = at[k];
-                        run_end = to[k];
+                        if (at != run_owner && run_owner >= 0) changed(run_owner, run_end);
+                        run_owner = at;
+                        run_end = to;
                     }
-                    walking = walking && cnt == to[k] - vpos;
-                    vpos = to[k];
+                    walking = cnt == to - vpos;
+                    vpos = to;
                 }
             }
             if (run_owner >= 0) changed(run_owner, run_end);
@@ -312,8 +314,11 @@ __device__ __forceinline__ void apart_evict_wave(const SegArgs& a, size_t p, int
                 in_ring2 = c2.disowned(owner, end);
             }
             if (__builtin_expect(ballot(in_ring || in_ring2) != 0, 0)) {
-                if (in_ring) c1.disowned_in_ring(owner, end);
-                if (PROXY && in_ring2) c2.disowned_in_ring(owner, end);
+                const int of = __builtin_amdgcn_readlane(owner, best), to = __builtin_amdgcn_readlane(end, best);
+                if (ballot(in_ring) != 0) c1.disowned_in_ring(best, of, to, lane);
+                if (PROXY) {
+                    if (ballot(in_ring2) != 0) c2.disowned_in_ring(best, of, to, lane);
+                }
                 c1.look_ahead();
                 if (PROXY) c2.look_ahead();
             }
