@@ -153,7 +153,7 @@ def cpu_baseline(wl, params, n_req, threads, online=None, engine=None, proxy=Non
     return threads * tr.N / dt, dt, tr.N
 
 
-def section_table(sec, N, P):
+def section_table(sec, N, P, R):
     """The timed instantiation's per-wavefront section budget as text: shader-clock cycles per request of each
     of the wavefronts of a replay (mean over replays), between the marks the kernel sets, and the deciding wavefront's
     event counts.  sec = the [P, 3, 12] array of gorgo_eval_population_sections."""
@@ -167,7 +167,7 @@ def section_table(sec, N, P):
     book = {2: "stores", 3: "waiting at the meeting X"}
     wavefronts = [("deciding wavefront (lane = replica):", 0, decide), ("queue wavefront (lane = service slot):", 1, queue),
                   ("front-end wavefront:", 2, front), ("book-keeping wavefront:", 2, book)]
-    if P <= 512:                       # (six wavefronts per replay)
+    if P <= (768 if R <= 12 else 512):                       # (six wavefronts per replay)
         wavefronts = [("deciding wavefront (lane = replica):", 0, {k: decide[k] for k in (0, 1, 3)}),
                       ("serving wavefront (lane = service slot):", 1, {k: queue[k] for k in (0, 1, 9, 5)}),
                       ("retiring wavefront:", 1, {2: "requests in flight", 3: "waiting at the meeting X"}),
@@ -404,7 +404,7 @@ def main():
         t_ms = g.last_eval_kernel_ms()["replay_ms"]
         print(f"[bench] timed instantiation: replay kernel {t_ms:.1f} ms = {t_ms * 1e3 / max(N, 1):.3f} us per request step "
               f"(plain kernel: {k_ms * 1e3 / max(N, 1):.3f})", file=sys.stderr)
-        print(section_table(res.sections.cpu().numpy(), N, P), file=sys.stderr, flush=True)
+        print(section_table(res.sections.cpu().numpy(), N, P, wl.R), file=sys.stderr, flush=True)
         del res
 
     mode = "P online tuners (window 128, hop 32) over the trace per step" if args.online else \

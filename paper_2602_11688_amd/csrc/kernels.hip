@@ -437,13 +437,20 @@ int prepare(const Plan& pl, double* d_small, int32_t* last, int64_t rows, hipStr
 }
 
 // Whether a launch of segment rows spreads each replay over six wavefronts instead of four: up to two replays for each of
-// the 256 CUs.  A replay's chain is then a tenth to a third shorter; with more replays per CU the quarter more vector
-// instructions a request takes is what counts.  (10,000 requests, four / six wavefronts.  512 replays: 32 replicas 6.11 / 5.67
-// ms, sweep on 16 7.69 / 5.96, engine model 8.34 / 6.72, proxy 7.50 / 7.26, tuner 7.18 / 6.33; 640 replays: 6.04 / 6.87, 7.60 /
-// 6.68, 8.06 / 7.16, 7.49 / 7.91, 7.14 / 8.08; 1,024: 6.18 / 7.50, 7.65 / 7.26, 8.44 / 8.64, 7.77 / 8.60, 7.49 / 8.00.  Two
-// replays: 5.56 / 5.01; 3 replicas 7.52 / 5.34; all requests sent to one of 13 replicas 8.36 / 5.86.)
-constexpr int SPREAD_UP_TO = 512;
-bool spread_replays(const Plan& pl) { return pl.P <= SPREAD_UP_TO; }
+// the 256 CUs, with few replicas up to three.  A replay's chain is then a tenth to a third shorter; with more replays per CU the
+// quarter more vector instructions a request takes is what counts.  (10,000 requests, four / six wavefronts, ms.  Two replays:
+// 5.56 / 5.01.  19, caches of 8,000 blocks: 3 replicas 7.2 / 5.3, 16 6.0 / 4.9, 32 5.3 / 4.6, 48 5.6 / 5.2; of 700 blocks 7.6 / 5.4,
+// 6.5 / 5.9, 6.0 / 6.2, 6.3 / 6.8.  512: 7.9 / 5.8, 6.8 / 5.6, 5.7 / 5.3, 6.2 / 6.2.  768: 2 replicas 8.5 / 6.6, 8 7.6 / 6.8, 12 7.3 /
+// 6.7, proxy 10.8 / 10.2, engine model 10.2 / 8.1, tuner 8.7 / 7.4; 16 6.7 / 6.6, proxy 8.6 / 9.9, caches of 700 blocks 7.2 / 7.8; 20
+// 6.4 / 6.6, 32 6.0 / 6.4.  1,024: 2 replicas 8.6 / 11.9, 32 6.1 / 11.3, for not all are resident.)  And only where all of them are
+// resident by their LDS, `lds` bytes of it for the service slots (with 1,024 slots or long tuner windows fewer fit a CU).
+constexpr int SPREAD_UP_TO = 512, SPREAD_FEW_REPLICAS = 12, SPREAD_FEW_UP_TO = 768;
+bool spread_replays(const Plan& pl, bool proxy, size_t lds) {
+    if (pl.P > (pl.R <= SPREAD_FEW_REPLICAS ? SPREAD_FEW_UP_TO : SPREAD_UP_TO)) return false;
+    const size_t fixed = proxy ? sizeof(ApartHandover<true>) : sizeof(ApartHandover<false>);
+    const size_t per_cu = (size_t)160 * 1024 / ((fixed + lds + 1279) / 1280 * 1280);        // (given out in pieces of 1,280 bytes)
+    return pl.P <= 256 * (int)per_cu;
+}
 
 // The segment-row kernels' instantiations: every mode with either replica model; imperfect proxy knowledge concerns the
 // cost model (fixed weights or tuned online) only.
@@ -451,7 +458,7 @@ template <int MODE>
 void launch_segments(bool engine, bool proxy, const Plan& pl, hipStream_t s, const SegArgs& a) {
     const size_t lds = replay_queue_lds_bytes(pl.R, pl.B, engine, a.window);
     const dim3 grid((unsigned)pl.P);
-    if (spread_replays(pl)) {
+    if (spread_replays(pl, proxy, lds)) {
         const dim3 block(APART_WAVES * WAVE);
         if constexpr (MODE == MODE_COST_MODEL || MODE == MODE_ONLINE) {
             if (proxy) {
@@ -644,7 +651,7 @@ int launch_replay(const gorgo_trace* t, const Plan& pl, const double* d_rtt, con
             } else if (mode == MODE_COST_MODEL && !engine && !proxy && !sections && pack_replays(pl, a.nseg)) {
                 hipLaunchKernelGGL((replay_segments_kernel<MODE_COST_MODEL, false, false, 2>), dim3((unsigned)(pl.P / 2)),
                                    dim3(seg_threads<2>()), 2 * replay_queue_lds_bytes(pl.R, pl.B, false, 0), s, a);
-            } else if (sections && spread_replays(pl)) {
+            } else if (sections && spread_replays(pl, false, replay_queue_lds_bytes(pl.R, pl.B, false, 0))) {
                 hipLaunchKernelGGL((replay_apart_kernel<MODE_COST_MODEL, false, false, true>), dim3((unsigned)pl.P),
                                    dim3(APART_WAVES * WAVE), replay_queue_lds_bytes(pl.R, pl.B, false, 0), s, a);
             } else if (sections) {

@@ -1,6 +1,6 @@
 """Where a launch changes its way: small inputs as kernel arguments or as copies (R + 4 P against 448), how often the
 eviction cursors' look-ahead is fed (24 replicas), how many sets of 64 service slots there are, and which requests the
-wavefronts meet twice at, against the CPU oracle; six wavefronts per replay (up to 512 replays) against four."""
+wavefronts meet twice at, against the CPU oracle; six wavefronts per replay (up to 512 replays, 768 with up to 12 replicas) against four."""
 import numpy as np
 import pytest
 
@@ -78,7 +78,7 @@ def test_requests_that_are_waited_for(gap_ms, decode):
 
 @pytest.mark.parametrize("R,B,cache", [(3, 8, 1), (5, 3, 3), (16, 2, 2), (33, 8, 1), (64, 16, 4), (7, 9, 0)])
 def test_six_wavefronts_or_four(R, B, cache):
-    """The same replays in a launch of 12 and repeated in one of 516: paths of many segments and owners, caches that hold one to
+    """The same replays in a launch of 12 and repeated in one of 780: paths of many segments and owners, caches that hold one to
     four of the longest requests (cursors that run into their look-ahead's end) or everything, requests that complete at
     once, every entry point; bit for bit."""
     tr = tg.random_forest(31 * R + B, 1100, roots=3, max_blocks=60, grow=4, gap_ms=60, keep=0.85)
@@ -86,7 +86,7 @@ def test_six_wavefronts_or_four(R, B, cache):
     rng = np.random.default_rng(R * B)
     model = g.Model(R, B, cache * nmax, 0.05, 2.0)
     rtt = rng.uniform(0.0, 400.0, R)
-    few, times = 12, 43
+    few, times = 12, 65
     params = np.concatenate([rng.uniform(0.05, 2.0, (few - 2, 3)), [[1.0, 0.0, 0.0], [0.0, 1.0, 0.0]]])
     scale = rng.choice([0.02, 0.5, 1.0, 4.0, 100.0], few)
     most = int((tr.in_len.astype(np.int64) + tr.out_len).max())
