@@ -76,10 +76,11 @@ def test_requests_that_are_waited_for(gap_ms, decode):
     check_online(tr, model, rtt, [[1.0, 0.5, 0.1]] * 2, z, [1.0, 0.1], 8, 1, [0.05] * 3, [2.0] * 3, 0.5)
 
 
-@pytest.mark.parametrize("R,B,cache", [(3, 8, 1), (5, 3, 3), (16, 2, 2), (33, 8, 1), (64, 16, 4), (7, 9, 0)])
+@pytest.mark.parametrize("R,B,cache", [(3, 8, 1), (5, 3, 3), (16, 2, 2), (33, 8, 1), (64, 16, 4), (7, 9, 0), (32, 4, 9), (12, 8, 14)])
 def test_six_wavefronts_or_four(R, B, cache):
     """The same replays in a launch of 12 and repeated in one of 780: paths of many segments and owners, caches that hold one to
-    four of the longest requests (cursors that run into their look-ahead's end) or everything, requests that complete at
+    four of the longest requests (cursors that run into their look-ahead's end), about as many as the look-ahead has records
+    (owners are found in it), or everything, requests that complete at
     once, every entry point; bit for bit."""
     tr = tg.random_forest(31 * R + B, 1100, roots=3, max_blocks=60, grow=4, gap_ms=60, keep=0.85)
     nmax = int(np.diff(tr.blk_off).max())
