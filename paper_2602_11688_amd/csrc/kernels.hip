@@ -449,18 +449,22 @@ int prepare(const Plan& pl, double* d_small, int32_t* last, int64_t rows, hipStr
 
 // Whether a launch of segment rows spreads each replay over six wavefronts instead of four: up to two replays for each of
 // the 256 CUs, with few replicas up to three.  A replay's chain is then a tenth to a third shorter; with more replays per CU the
-// quarter more vector instructions a request takes is what counts.  (10,000 requests, four / six wavefronts, ms.  Two replays:
-// 5.56 / 5.01.  19, caches of 8,000 blocks: 3 replicas 7.2 / 5.3, 16 6.0 / 4.9, 32 5.3 / 4.6, 48 5.6 / 5.2; of 700 blocks 7.6 / 5.4,
-// 6.5 / 5.9, 6.0 / 6.2, 6.3 / 6.8.  512: 7.9 / 5.8, 6.8 / 5.6, 5.7 / 5.3, 6.2 / 6.2.  768: 2 replicas 8.5 / 6.6, 8 7.6 / 6.8, 12 7.3 /
-// 6.7, proxy 10.8 / 10.2, engine model 10.2 / 8.1, tuner 8.7 / 7.4; 16 6.7 / 6.6, proxy 8.6 / 9.9, caches of 700 blocks 7.2 / 7.8; 20
-// 6.4 / 6.6, 32 6.0 / 6.4.  1,024: 2 replicas 8.6 / 11.9, 32 6.1 / 11.3, for not all are resident.)  And only where all of them are
-// resident by their LDS, `lds` bytes of it for the service slots (with 1,024 slots or long tuner windows fewer fit a CU).
+// quarter more vector instructions a request takes is what counts.  (10,000 requests, four / six wavefronts, ms.  Two replays on 2
+// replicas: 7.8 / 5.3.  19, caches of 8,000 blocks: 3 replicas 7.3 / 5.3, 16 5.9 / 5.0, 32 5.6 / 4.8, 48 5.9 / 5.3, 64 5.4 / 5.0; of
+// 700 blocks 7.5 / 5.8, 6.2 / 5.9, 6.0 / 5.7, 6.2 / 6.1, 5.9 / 6.0.  512, of 8,000: 7.9 / 5.8, 6.6 / 5.6, 6.0 / 5.4, 6.4 / 6.2, 6.0 /
+// 5.7; of 700 8.2 / 6.4, 6.8 / 6.5, 6.3 / 6.2, 6.7 / 6.9, 6.3 / 6.6.  768: 2 replicas 8.4 / 6.5, 8 7.5 / 6.7, 12 7.6 / 6.9, proxy 10.9 /
+// 10.6, engine model 10.3 / 8.2, tuner 8.6 / 7.4; 16 6.5 / 6.4, proxy 8.6 / 9.8, caches of 700 blocks 6.8 / 7.9; 20 6.3 / 6.7, 32 6.0 /
+// 6.4.)  And only where all of them are resident: by their LDS, `lds` bytes of it for the service slots (with 1,024 slots or long
+// tuner windows fewer fit a CU), and by their registers, `held` workgroups.  That is half of the wavefronts that fit a SIMD,
+// for a workgroup of six takes the room of two on each: three up to 80 registers, two up to 128.  (The time doubles from 768
+// replays to 769, 2 replicas 6.5 / 11.6 ms, 32 6.0 / 10.6, and not where the kernel is kept to 64 registers; proxy, engine model
+// and tuner together take 85, 3,000 requests on 8 replicas: 512 replays 3.0 ms, 640 5.9, with four wavefronts 4.8.)
 constexpr int SPREAD_UP_TO = 512, SPREAD_FEW_REPLICAS = 12, SPREAD_FEW_UP_TO = 768;
-bool spread_replays(const Plan& pl, bool proxy, size_t lds) {
+bool spread_replays(const Plan& pl, bool proxy, size_t lds, int held) {
     if (pl.P > (pl.R <= SPREAD_FEW_REPLICAS ? SPREAD_FEW_UP_TO : SPREAD_UP_TO)) return false;
     const size_t fixed = proxy ? sizeof(ApartHandover<true>) : sizeof(ApartHandover<false>);
     const size_t per_cu = (size_t)160 * 1024 / ((fixed + lds + 1279) / 1280 * 1280);        // (given out in pieces of 1,280 bytes)
-    return pl.P <= 256 * (int)per_cu;
+    return pl.P <= 256 * std::min((int)per_cu, held);
 }
 
 // The segment-row kernels' instantiations: every mode with either replica model; imperfect proxy knowledge concerns the
@@ -469,7 +473,7 @@ template <int MODE>
 void launch_segments(bool engine, bool proxy, const Plan& pl, hipStream_t s, const SegArgs& a) {
     const size_t lds = replay_queue_lds_bytes(pl.R, pl.B, engine, a.window);
     const dim3 grid((unsigned)pl.P);
-    if (spread_replays(pl, proxy, lds)) {
+    if (spread_replays(pl, proxy, lds, MODE == MODE_ONLINE && engine && proxy ? 2 : 3)) {
         const dim3 block(APART_WAVES * WAVE);
         if constexpr (MODE == MODE_COST_MODEL || MODE == MODE_ONLINE) {
             if (proxy) {
@@ -662,7 +666,7 @@ int launch_replay(const gorgo_trace* t, const Plan& pl, const double* d_rtt, con
             } else if (mode == MODE_COST_MODEL && !engine && !proxy && !sections && pack_replays(pl, a.nseg)) {
                 hipLaunchKernelGGL((replay_segments_kernel<MODE_COST_MODEL, false, false, 2>), dim3((unsigned)(pl.P / 2)),
                                    dim3(seg_threads<2>()), 2 * replay_queue_lds_bytes(pl.R, pl.B, false, 0), s, a);
-            } else if (sections && spread_replays(pl, false, replay_queue_lds_bytes(pl.R, pl.B, false, 0))) {
+            } else if (sections && spread_replays(pl, false, replay_queue_lds_bytes(pl.R, pl.B, false, 0), 3)) {
                 hipLaunchKernelGGL((replay_apart_kernel<MODE_COST_MODEL, false, false, true>), dim3((unsigned)pl.P),
                                    dim3(APART_WAVES * WAVE), replay_queue_lds_bytes(pl.R, pl.B, false, 0), s, a);
             } else if (sections) {

@@ -888,7 +888,9 @@ __device__ __forceinline__ void apart_decide_wave(const SegArgs& a, size_t p, in
         for (int k = 0; k < 8; ++k) a.sections[p * 3 * SECTIONS + k] = clk.acc[k];
 }
 
-// Replay p by one workgroup; two fit a CU whatever the shape (at most 128 vector registers, 84 KiB of LDS).
+// Replay p by one workgroup.  Three fit a CU by their registers, two in the proxy variant with engine model and tuner; LDS may
+// allow fewer (30,592 bytes of hand-over words in the proxy variants and 53,248 of slots and window make 84 KB: one).  The launch
+// rule counts both.
 template <int MODE, bool ENGINE, bool PROXY, bool TIMED>
 __device__ __forceinline__ void apart_replay(const SegArgs& a, size_t p, unsigned char* lds_raw) {
     __shared__ ApartHandover<PROXY> comm;

@@ -53,6 +53,15 @@ def _resident(kernel, dynamic):
     return min(waves // (threads // 64), LDS // lds)
 
 
+def _resident_of_six(kernel, dynamic):
+    """Workgroups of six wavefronts: each takes the room of two on every SIMD (seven wavefronts of 72 registers fit a SIMD, and
+    three such workgroups a compute unit)."""
+    registers, fixed, threads = kernel
+    assert threads == 384
+    lds = -(-(fixed + dynamic) // PIECE) * PIECE
+    return min(min(WAVES, LANE_REGISTERS // ((registers + 7) // 8 * 8)) // 2, LDS // lds)
+
+
 def _queues(R, B, engine, window):
     """Dynamic LDS of a segment-row replay: its service slots, four sets of 64 or more, and the tuner's window."""
     return max(4, -(-R * B // 64)) * 64 * (44 if engine else 40) + (window + 7) // 8 * 64
@@ -73,3 +82,37 @@ def test_replays_of_a_compute_unit(kernels, R, B, window, least):
         assert _resident(kernel, dynamic) >= least, (name, kernel, dynamic)
         seen += 1
     assert seen >= 24
+
+
+@pytest.mark.parametrize("R,B,window,few", [(12, 8, 128, True), (2, 64, 1024, True), (32, 8, 128, False), (64, 4, 128, False),
+                                            (16, 16, 1024, False)])
+def test_replays_of_six_wavefronts(kernels, R, B, window, few):
+    """What the launch rule takes for granted: up to 768 replays (three per compute unit) with up to 12 replicas, but 512 with
+    proxy, engine model and tuner together; 512 (two) with more."""
+    seen = 0
+    for name, kernel in kernels.items():
+        apart = re.search(r"replay_apart_kernel<(\d), (true|false), (true|false), false>", name)
+        if not apart:
+            continue
+        mode, engine, proxy = apart.groups()
+        dynamic = _queues(R, B, engine == "true", window if mode == "1" else 0)
+        all_three = (mode, engine, proxy) == ("1", "true", "true")
+        assert _resident_of_six(kernel, dynamic) >= (3 if few and not all_three else 2), (name, kernel, dynamic)
+        seen += 1
+    assert seen == 14
+
+
+@pytest.mark.parametrize("R,B,window,least", [(32, 8, 128, 4), (64, 4, 128, 4), (16, 8, 1024, 4), (32, 16, 128, 4)])
+def test_replays_over_rows_of_stamps(kernels, R, B, window, least):
+    """As many as with hashed tables: four per compute unit, five in the variants of up to 96 registers."""
+    seen = 0
+    for name, kernel in kernels.items():
+        rows = re.search(r"replay_rows_kernel<(\d), (true|false), (true|false)>", name)
+        if not rows:
+            continue
+        mode, engine, proxy = rows.groups()
+        dynamic = _queues(R, B, engine == "true", window if mode == "1" else 0) + R * (16 + 25 * 4) + 4
+        all_three = (mode, engine, proxy) == ("1", "true", "true")
+        assert _resident(kernel, dynamic) >= least + (0 if all_three or R * B > 256 else 1), (name, kernel, dynamic)
+        seen += 1
+    assert seen == 14
