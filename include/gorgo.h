@@ -129,10 +129,11 @@ typedef struct gorgo_outputs {
     double* p95_e2e_ms;    /* [P]    nearest-rank 95th percentile of e2e_ms[p][.]             */
 } gorgo_outputs;
 
-/* Device workspace needed by gorgo_eval_population for P replays with this set of outputs (`outputs` may
- * be NULL: the size then covers any combination).  The workspace holds the per-replay cache tables, the
+/* Device workspace for gorgo_eval_population, or any other evaluation, of P replays with this set of outputs (`outputs`
+ * may be NULL: the size then covers any combination).  The workspace holds the per-replay cache state, the
  * in-flight request records and stand-ins for per-request outputs that were not requested but are needed
- * by the percentile reduction. */
+ * by the percentile reduction.  It is what the fastest layout of the cache state takes; block by block (options.replay_path)
+ * an evaluation also runs in less where hashed tables are smaller than rows of stamps. */
 int gorgo_workspace_bytes(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* options, int32_t P, const gorgo_outputs* outputs,
                           size_t* bytes);
 
@@ -146,8 +147,8 @@ int gorgo_workspace_bytes(const gorgo_trace* t, const gorgo_model* m, const gorg
  *   hip_stream           hipStream_t (NULL = default stream)
  * The call copies the small host arrays, enqueues its kernels on the stream and returns without waiting
  * for them; outputs are valid once the stream has reached that point.  The first evaluation of a trace on
- * a device uploads the trace (one allocation, a synchronous copy of each of its arrays).  Calls that share a workspace must
- * be ordered on one stream. */
+ * a device uploads the trace (one allocation; a synchronous copy of each of its arrays, or one of a trace of up to 256 KiB).
+ * Calls that share a workspace must be ordered on one stream. */
 int gorgo_eval_population(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* options, const double* rtt_ms,
                           const double* params, const double* scale, int32_t P, const gorgo_outputs* outputs,
                           void* workspace, size_t workspace_bytes, void* hip_stream);
@@ -162,9 +163,9 @@ int gorgo_trace_to_device(const gorgo_trace* t);
  * GORGO_STATIC_SCRATCH_BYTES that is part of the library's device code (each GPU the library runs on holds it
  * until the process ends).  The call allocates nothing on the device and creates no event or stream
  * (gorgo_last_eval_kernel_ms does not cover it); the trace must already be resident on the current device
- * (gorgo_trace_to_device, or any earlier evaluation there), else GORGO_ERR_INVALID_ARG.  An evaluation whose
- * gorgo_workspace_bytes exceeds GORGO_STATIC_SCRATCH_BYTES is refused with GORGO_ERR_WORKSPACE before anything
- * is enqueued.  Every call on a GPU uses that GPU's one array: what must start clean is cleared by the call's
+ * (gorgo_trace_to_device, or any earlier evaluation there), else GORGO_ERR_INVALID_ARG.  An evaluation that does not fit
+ * into GORGO_STATIC_SCRATCH_BYTES is refused with GORGO_ERR_WORKSPACE before anything is enqueued; one whose
+ * gorgo_workspace_bytes is not above that fits, and so may one whose cache state takes less as hashed tables.  Every call on a GPU uses that GPU's one array: what must start clean is cleared by the call's
  * own kernels, and two such calls that overlap in time on one GPU (different streams or threads) race. */
 #define GORGO_STATIC_SCRATCH_BYTES ((size_t)64 << 20)
 int gorgo_eval_population_static(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* options, const double* rtt_ms,
@@ -279,9 +280,16 @@ typedef enum gorgo_policy {
     GORGO_POLICY_RANDOM = 3
 } gorgo_policy;
 
+/* Device workspace in which gorgo_eval_policy and gorgo_eval_engine run `policy` fastest.  The session-affinity and the random
+ * policy dictate the routes; with room to lay the requests out replica by replica their replays are several times as fast
+ * (up to 256 replays, from 256 requests on), and that room is asked for here.  With gorgo_workspace_bytes, which is enough, they
+ * go request by request.  The other policies: the same as gorgo_workspace_bytes. */
+int gorgo_policy_workspace_bytes(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* options, int32_t policy, int32_t P,
+                                 const gorgo_outputs* outputs, size_t* bytes);
+
 /* Evaluate P replays routed by `policy`, replay p at time scale scale[p] (and, for the random policy, with
  * seed seeds[p]; seeds is a host array [P], may be NULL for the other policies; the call returns when they have
- * been copied).  Everything else as gorgo_eval_population, same workspace size. */
+ * been copied).  Everything else as gorgo_eval_population; see gorgo_policy_workspace_bytes for the workspace. */
 int gorgo_eval_policy(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* options, const double* rtt_ms, int32_t policy,
                       const uint64_t* seeds, const double* scale, int32_t P, const gorgo_outputs* outputs,
                       void* workspace, size_t workspace_bytes, void* hip_stream);

@@ -83,6 +83,8 @@ def lib():
         L.gorgo_free_trace.argtypes = [vp]
         L.gorgo_free_trace.restype = None
         L.gorgo_workspace_bytes.argtypes = [vp, C.POINTER(_Model), C.POINTER(Options), i32, C.POINTER(_Outputs), C.POINTER(C.c_size_t)]
+        L.gorgo_policy_workspace_bytes.argtypes = [vp, C.POINTER(_Model), C.POINTER(Options), i32, i32, C.POINTER(_Outputs),
+                                                   C.POINTER(C.c_size_t)]
         L.gorgo_eval_population.argtypes = [vp, C.POINTER(_Model), C.POINTER(Options), vp, vp, vp, i32, C.POINTER(_Outputs), vp,
                                             C.c_size_t, vp]
         L.gorgo_eval_population_sections.argtypes = [vp, C.POINTER(_Model), C.POINTER(Options), vp, vp, vp, i32, C.POINTER(_Outputs), vp,
@@ -113,7 +115,7 @@ def lib():
         L.gorgo_options_default.argtypes = [C.POINTER(Options)]
         L.gorgo_options_default.restype = None
         L.gorgo_last_eval_kernel_ms.argtypes = [C.POINTER(dbl)] * 3
-        for name in ("gorgo_load_trace", "gorgo_load_trace_arrays", "gorgo_trace_info", "gorgo_workspace_bytes",
+        for name in ("gorgo_load_trace", "gorgo_load_trace_arrays", "gorgo_trace_info", "gorgo_workspace_bytes", "gorgo_policy_workspace_bytes",
                      "gorgo_eval_population", "gorgo_eval_population_sections", "gorgo_trace_to_device", "gorgo_eval_population_static", "gorgo_eval_online", "gorgo_eval_policy", "gorgo_eval_engine", "gorgo_eval_proxy", "gorgo_es_init", "gorgo_es_sample", "gorgo_es_propose",
                      "gorgo_es_update", "gorgo_es_workspace_bytes", "gorgo_es_step",
                      "gorgo_last_eval_kernel_ms", "gorgo_query_replay_packing", "gorgo_query_replay_path"):
@@ -275,12 +277,35 @@ def _outputs_struct(route=None, hit_blocks=None, ttft_ms=None, e2e_ms=None, p95_
     return _Outputs(dp(route), dp(hit_blocks), dp(ttft_ms), dp(e2e_ms), dp(p95_ttft_ms), dp(p95_e2e_ms))
 
 
-def workspace_bytes(trace: Trace, model: Model, P: int, outputs: Optional[_Outputs] = None, options: Optional[Options] = None) -> int:
+def workspace_bytes(trace: Trace, model: Model, P: int, outputs: Optional[_Outputs] = None, options: Optional[Options] = None,
+                    policy: Optional[str] = None) -> int:
+    """Bytes of workspace for an evaluation; with a policy ("session-affinity", "random", ...) those in which
+    eval_policy and eval_engine run it fastest (gorgo_policy_workspace_bytes)."""
     n = C.c_size_t()
     m = model.c()
-    _check(lib().gorgo_workspace_bytes(trace._h, C.byref(m), _opt(options), P, None if outputs is None else C.byref(outputs),
-                                       C.byref(n)))
+    o = None if outputs is None else C.byref(outputs)
+    if policy is None:
+        _check(lib().gorgo_workspace_bytes(trace._h, C.byref(m), _opt(options), P, o, C.byref(n)))
+    else:
+        _check(lib().gorgo_policy_workspace_bytes(trace._h, C.byref(m), _opt(options), _policy_code(policy), P, o, C.byref(n)))
     return n.value
+
+
+_ERR_WORKSPACE = -7
+
+
+def _in_workspace(given, need: int, dev, call):
+    """call(workspace), which returns a status: in the caller's workspace where the call gets along with it, though it may hold
+    fewer than the `need` bytes asked for, else in one allocated here.  (What is refused has enqueued nothing.)"""
+    import torch
+    if given is not None:
+        rc = call(given)
+        if rc != _ERR_WORKSPACE or given.numel() >= need:
+            _check(rc)
+            return given
+    fresh = torch.empty((need,), dtype=torch.uint8, device=dev)
+    _check(call(fresh))
+    return fresh
 
 
 @dataclass
@@ -331,21 +356,19 @@ def eval_population(trace: Trace, model: Model, rtt_ms, params, scale, *, per_re
         res.p95_e2e_ms = torch.empty((P,), dtype=torch.float64, device=dev)
     o = _outputs_struct(res.route, res.hit_blocks, res.ttft_ms, res.e2e_ms, res.p95_ttft_ms, res.p95_e2e_ms)
     need = workspace_bytes(trace, model, P, o, options)
-    if workspace is None or workspace.numel() < need:
-        workspace = torch.empty((need,), dtype=torch.uint8, device=dev)
-    res.workspace = workspace
     s = stream if stream is not None else torch.cuda.current_stream(dev)
     m = model.c()
-    with torch.cuda.device(dev):
+    if sections:
+        res.sections = torch.zeros((P, 3, 12), dtype=torch.int64, device=dev)
+
+    def call(ws):
+        args = (trace._h, C.byref(m), _opt(options), _ptr(rtt), _ptr(par), _ptr(sc), P, C.byref(o), C.c_void_p(ws.data_ptr()),
+                ws.numel(), C.c_void_p(s.cuda_stream))
         if sections:
-            res.sections = torch.zeros((P, 3, 12), dtype=torch.int64, device=dev)
-            _check(lib().gorgo_eval_population_sections(trace._h, C.byref(m), _opt(options), _ptr(rtt), _ptr(par), _ptr(sc), P, C.byref(o),
-                                                        C.c_void_p(workspace.data_ptr()), workspace.numel(),
-                                                        C.c_void_p(s.cuda_stream), C.c_void_p(res.sections.data_ptr())))
-        else:
-            _check(lib().gorgo_eval_population(trace._h, C.byref(m), _opt(options), _ptr(rtt), _ptr(par), _ptr(sc), P, C.byref(o),
-                                               C.c_void_p(workspace.data_ptr()), workspace.numel(),
-                                               C.c_void_p(s.cuda_stream)))
+            return lib().gorgo_eval_population_sections(*args, C.c_void_p(res.sections.data_ptr()))
+        return lib().gorgo_eval_population(*args)
+    with torch.cuda.device(dev):
+        res.workspace = _in_workspace(workspace, need, dev, call)
     return res
 
 
@@ -387,6 +410,10 @@ def eval_population_static(trace: Trace, model: Model, rtt_ms, params, scale, *,
 POLICIES = {"least-request": 1, "session-affinity": 2, "random": 3}
 
 
+def _policy_code(policy: str) -> int:
+    return 0 if policy == "cost-model" else POLICIES[policy]
+
+
 def eval_policy(trace: Trace, model: Model, rtt_ms, policy: str, scale, *, seeds=None, per_request: bool = True,
                 p95: bool = True, workspace=None, stream=None, device="cuda:0", options: Optional[Options] = None) -> EvalResult:
     """gorgo_eval_policy with torch-allocated outputs: one replay per entry of `scale`, routed by a baseline policy
@@ -411,15 +438,16 @@ def eval_policy(trace: Trace, model: Model, rtt_ms, policy: str, scale, *, seeds
         res.p95_ttft_ms = torch.empty((P,), dtype=torch.float64, device=dev)
         res.p95_e2e_ms = torch.empty((P,), dtype=torch.float64, device=dev)
     o = _outputs_struct(res.route, res.hit_blocks, res.ttft_ms, res.e2e_ms, res.p95_ttft_ms, res.p95_e2e_ms)
-    need = workspace_bytes(trace, model, P, o, options)
-    if workspace is None or workspace.numel() < need:
-        workspace = torch.empty((need,), dtype=torch.uint8, device=dev)
-    res.workspace = workspace
+    code = POLICIES[policy]
+    need = workspace_bytes(trace, model, P, o, options, policy)
     s = stream if stream is not None else torch.cuda.current_stream(dev)
     m = model.c()
+
+    def call(ws):
+        return lib().gorgo_eval_policy(trace._h, C.byref(m), _opt(options), _ptr(rtt), code, _ptr(sd), _ptr(sc), P, C.byref(o),
+                                       C.c_void_p(ws.data_ptr()), ws.numel(), C.c_void_p(s.cuda_stream))
     with torch.cuda.device(dev):
-        _check(lib().gorgo_eval_policy(trace._h, C.byref(m), _opt(options), _ptr(rtt), POLICIES[policy], _ptr(sd), _ptr(sc), P, C.byref(o),
-                                       C.c_void_p(workspace.data_ptr()), workspace.numel(), C.c_void_p(s.cuda_stream)))
+        res.workspace = _in_workspace(workspace, need, dev, call)
     return res
 
 
@@ -472,14 +500,14 @@ def eval_online(trace: Trace, model: Model, rtt_ms, theta0, z, scale, *, lo, hi,
                  float(sigma0), dp(zt), dp(res.theta_step), dp(res.fitness_step), dp(res.theta_final),
                  dp(res.sigma_final), dp(res.accepted))
     need = workspace_bytes(trace, model, P, o, options)
-    if workspace is None or workspace.numel() < need:
-        workspace = torch.empty((need,), dtype=torch.uint8, device=dev)
-    res.workspace = workspace
     s = stream if stream is not None else torch.cuda.current_stream(dev)
     m = model.c()
+
+    def call(ws):
+        return lib().gorgo_eval_online(trace._h, C.byref(m), _opt(options), _ptr(rtt), _ptr(th0), _ptr(sc), P, C.byref(on), C.byref(o),
+                                       C.c_void_p(ws.data_ptr()), ws.numel(), C.c_void_p(s.cuda_stream))
     with torch.cuda.device(dev):
-        _check(lib().gorgo_eval_online(trace._h, C.byref(m), _opt(options), _ptr(rtt), _ptr(th0), _ptr(sc), P, C.byref(on), C.byref(o),
-                                       C.c_void_p(workspace.data_ptr()), workspace.numel(), C.c_void_p(s.cuda_stream)))
+        res.workspace = _in_workspace(workspace, need, dev, call)
     res._z = zt          # keep the draws alive until the stream has consumed them
     return res
 
@@ -553,17 +581,17 @@ def eval_engine(trace: Trace, model: Model, engine: Engine, rtt_ms, scale, *, pa
                      C.c_void_p(res.fitness_step.data_ptr()), C.c_void_p(res.theta_final.data_ptr()),
                      C.c_void_p(res.sigma_final.data_ptr()), C.c_void_p(res.accepted.data_ptr()))
     o = _outputs_struct(res.route, res.hit_blocks, res.ttft_ms, res.e2e_ms, res.p95_ttft_ms, res.p95_e2e_ms)
-    need = workspace_bytes(trace, model, P, o, options)
-    if workspace is None or workspace.numel() < need:
-        workspace = torch.empty((need,), dtype=torch.uint8, device=dev)
-    res.workspace = workspace
+    code = _policy_code(policy)
+    need = workspace_bytes(trace, model, P, o, options, policy)
     s = stream if stream is not None else torch.cuda.current_stream(dev)
     m = model.c()
-    code = 0 if cost_model else POLICIES[policy]
+
+    def call(ws):
+        return lib().gorgo_eval_engine(trace._h, C.byref(m), _opt(options), C.byref(eng), _ptr(rtt), code, _ptr(par), _ptr(sd),
+                                       None if on is None else C.byref(on), _ptr(sc), P, C.byref(o), C.c_void_p(ws.data_ptr()),
+                                       ws.numel(), C.c_void_p(s.cuda_stream))
     with torch.cuda.device(dev):
-        _check(lib().gorgo_eval_engine(trace._h, C.byref(m), _opt(options), C.byref(eng), _ptr(rtt), code, _ptr(par), _ptr(sd),
-                                       None if on is None else C.byref(on), _ptr(sc), P, C.byref(o),
-                                       C.c_void_p(workspace.data_ptr()), workspace.numel(), C.c_void_p(s.cuda_stream)))
+        res.workspace = _in_workspace(workspace, need, dev, call)
     return res
 
 
@@ -641,15 +669,15 @@ def eval_proxy(trace: Trace, model: Model, proxy: Proxy, params, scale, *, engin
                      C.c_void_p(res.sigma_final.data_ptr()), C.c_void_p(res.accepted.data_ptr()))
     o = _outputs_struct(res.route, res.hit_blocks, res.ttft_ms, res.e2e_ms, res.p95_ttft_ms, res.p95_e2e_ms)
     need = workspace_bytes(trace, model, P, o, options)
-    if workspace is None or workspace.numel() < need:
-        workspace = torch.empty((need,), dtype=torch.uint8, device=dev)
-    res.workspace = workspace
     s = stream if stream is not None else torch.cuda.current_stream(dev)
     m = model.c()
+
+    def call(ws):
+        return lib().gorgo_eval_proxy(trace._h, C.byref(m), _opt(options), C.byref(px), None if eng is None else C.byref(eng), _ptr(par),
+                                      None if on is None else C.byref(on), _ptr(sc), P, C.byref(o), C.c_void_p(ws.data_ptr()),
+                                      ws.numel(), C.c_void_p(s.cuda_stream))
     with torch.cuda.device(dev):
-        _check(lib().gorgo_eval_proxy(trace._h, C.byref(m), _opt(options), C.byref(px), None if eng is None else C.byref(eng), _ptr(par),
-                                      None if on is None else C.byref(on), _ptr(sc), P, C.byref(o),
-                                      C.c_void_p(workspace.data_ptr()), workspace.numel(), C.c_void_p(s.cuda_stream)))
+        res.workspace = _in_workspace(workspace, need, dev, call)
     res._tables = tables
     return res
 
@@ -702,14 +730,14 @@ def es_step(trace: Trace, model: Model, rtt_ms, scale: float, P: int, state: EsS
     rtt = _np(rtt_ms, np.float64)
     dev = torch.device(device)
     need = es_workspace_bytes(trace, model, P, options)
-    if workspace is None or workspace.numel() < need:
-        workspace = torch.empty((need,), dtype=torch.uint8, device=dev)
     par = np.zeros((P, 3), np.float64)
     fit = np.zeros(P, np.float64)
     s = stream if stream is not None else torch.cuda.current_stream(dev)
     m = model.c()
+
+    def call(ws):
+        return lib().gorgo_es_step(trace._h, C.byref(m), _opt(options), _ptr(rtt), float(scale), P, C.byref(state), _ptr(par), _ptr(fit),
+                                   C.c_void_p(ws.data_ptr()), ws.numel(), C.c_void_p(s.cuda_stream))
     with torch.cuda.device(dev):
-        _check(lib().gorgo_es_step(trace._h, C.byref(m), _opt(options), _ptr(rtt), float(scale), P, C.byref(state), _ptr(par),
-                                   _ptr(fit), C.c_void_p(workspace.data_ptr()), workspace.numel(),
-                                   C.c_void_p(s.cuda_stream)))
+        workspace = _in_workspace(workspace, need, dev, call)
     return par, fit, workspace

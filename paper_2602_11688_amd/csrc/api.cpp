@@ -108,8 +108,10 @@ void lay_out(const gorgo_trace* t, const gorgo_outputs* o, Plan* pl) {
     pl->total = off;
 }
 
+bool dictates(int32_t policy) { return policy == GORGO_POLICY_SESSION_AFFINITY || policy == GORGO_POLICY_RANDOM; }
+
 // Table geometry and workspace carve-up.  `room`: bytes of workspace there are, where that is known.  `dictated`: whether the
-// evaluation's policy dictates the routes (or may, where only the size is asked for).
+// evaluation's policy dictates the routes.
 int make_plan(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* options, int32_t P, const gorgo_outputs* o,
               Plan* pl, size_t room = SIZE_MAX, bool dictated = false) {
     if (P < 1 || P > (1 << 20)) return fail(GORGO_ERR_INVALID_ARG, "P must be in 1..2^20");
@@ -227,7 +229,22 @@ int gorgo_workspace_bytes(const gorgo_trace* t, const gorgo_model* m, const gorg
     int rc = check_model(t, m);
     if (rc) return rc;
     Plan pl;
-    rc = make_plan(t, m, options, P, outputs, &pl, SIZE_MAX, true);
+    rc = make_plan(t, m, options, P, outputs, &pl);
+    if (rc) return rc;
+    *bytes = pl.total;
+    return GORGO_OK;
+}
+
+int gorgo_policy_workspace_bytes(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* options, int32_t policy, int32_t P,
+                                 const gorgo_outputs* outputs, size_t* bytes) {
+    clear_error();
+    if (!bytes) return fail(GORGO_ERR_INVALID_ARG, "bytes is NULL");
+    if (policy < GORGO_POLICY_COST_MODEL || policy > GORGO_POLICY_RANDOM)
+        return fail(GORGO_ERR_INVALID_ARG, "policy must be 0 (cost model) .. 3 (random)");
+    int rc = check_model(t, m);
+    if (rc) return rc;
+    Plan pl;
+    rc = make_plan(t, m, options, P, outputs, &pl, SIZE_MAX, dictates(policy));
     if (rc) return rc;
     *bytes = pl.total;
     return GORGO_OK;
@@ -300,7 +317,7 @@ int evaluate(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* op
     }
     if (!rtt_ms || !params || !scale || !outputs) return fail(GORGO_ERR_INVALID_ARG, "a required pointer is NULL");
     Plan pl;
-    rc = make_plan(t, m, options, P, outputs, &pl, workspace_bytes, policy == GORGO_POLICY_SESSION_AFFINITY || policy == GORGO_POLICY_RANDOM);
+    rc = make_plan(t, m, options, P, outputs, &pl, workspace_bytes, dictates(policy));
     if (rc) return rc;
     for (int i = 0; i < m->R; ++i)
         if (!std::isfinite(rtt_ms[i]) || rtt_ms[i] < 0 || rtt_ms[i] > 1e9)

@@ -224,6 +224,35 @@ def test_options_are_per_call_and_validated():
     assert t.replay_path()["path"] == 2
 
 
+@pytest.mark.parametrize("R,N", [(1, 300), (2, 255), (2, 256), (16, 300), (64, 2000)])
+def test_room_for_dictated_routes_is_asked_for_by_their_policies_alone(R, N):
+    """What the other evaluations cannot use is not in gorgo_workspace_bytes (whose size per replay is the same for few replays,
+    which a policy's replays may be laid out by replica for, and many), and it is not needed: any evaluation is content with
+    that size."""
+    t = _trace(tg.random_forest(R + N, N, roots=3))
+    model, L = g.Model(R, 4, 0, 0.05, 20.0), g.lib()
+    m, n, o = model.c(), C.c_size_t(), gb._Outputs()
+    few = 64
+    plain = g.workspace_bytes(t, model, few)
+    assert g.workspace_bytes(t, model, 16 * few) > 15 * plain
+    laid_out = N >= 256 and R > 1
+    for policy, more in (("cost-model", False), ("least-request", False), ("session-affinity", laid_out), ("random", laid_out)):
+        size = g.workspace_bytes(t, model, few, policy=policy)
+        assert size > plain if more else size == plain, policy
+    assert L.gorgo_policy_workspace_bytes(t._h, C.byref(m), None, 4, few, None, C.byref(n)) == -1
+    assert L.gorgo_policy_workspace_bytes(t._h, C.byref(m), None, 2, few, None, None) == -1
+    rtt, sc, seeds = np.ones(R), np.ones(few), np.arange(few, dtype=np.uint64)
+    exact = g.workspace_bytes(t, model, few, o)
+
+    def policy_call(policy, nbytes, ws):
+        return L.gorgo_eval_policy(t._h, C.byref(m), None, gb._ptr(rtt), policy, gb._ptr(seeds), gb._ptr(sc), few, C.byref(o), ws, nbytes,
+                                   None)
+    for policy in (1, 2, 3):
+        # one byte less is refused, naming this size; nothing else is wrong with the call but its address
+        assert policy_call(policy, exact - 1, C.c_void_p(256)) == -7 and str(exact).encode() in L.gorgo_last_error()
+        assert policy_call(policy, exact, C.c_void_p(264)) == -7 and b"aligned" in L.gorgo_last_error()
+
+
 def test_online_and_policy_entry_points_reject_bad_arguments_before_touching_a_device():
     t = _trace(tg.config(1, 300).trace)
     m = g.Model(4, 8, 0, 0.05, 20.0).c()
