@@ -528,16 +528,22 @@ struct EvictCursor {
         cur_own = owner == cur_r ? end : cur_own;
         pend_own = owner == pend_r ? end : pend_own;
     }
-    // The owner may be a record in the ring: its copy there (every slot is looked at before any is written; a number may stand in
-    // the free slot as well).
+    // The owner may be a record in the ring: its copy there (every slot of a trip is looked at before any is written; a number may
+    // stand in the free slot as well).  Eight slots a trip to LDS; where there is the index's ring as well four, for with eight
+    // the proxy variants took 96 registers and spilled six, 85 so.  (10,000 requests, 1,024 replays, 32 replicas of 700 blocks: one
+    // slot a trip 9.0 ms, proxy 14.8; four 6.5 and 8.5; eight 6.4 and 8.5.  All lanes together, a slot each: proxy 8.5.)
     __device__ __forceinline__ void disowned_in_ring(int owner, int end) {
         constexpr int SLOTS = WORDS < 8 * WAVE ? WORDS >> 5 : 8;      // (at most; with fewer some are looked at twice)
-        unsigned found = 0;
+        constexpr int TRIP = WORDS < 8 * WAVE ? 4 : 8;
+#pragma nounroll
+        for (int k0 = 0; k0 < SLOTS; k0 += TRIP) {
+            unsigned found = 0;
 #pragma unroll
-        for (int k = 0; k < SLOTS; ++k) found |= (int)(unsigned)*at(k) == owner ? 1u << k : 0u;
-        for (; found != 0; found &= found - 1) {
-            unsigned long long* const e = at(__builtin_ctz(found));
-            *e = (*e & ~(0xFFFFull << 32)) | ((unsigned long long)(unsigned)end << 32);
+            for (int k = 0; k < TRIP; ++k) found |= (int)(unsigned)*at(k0 + k) == owner ? 1u << k : 0u;
+            for (; found != 0; found &= found - 1) {
+                unsigned long long* const e = at(k0 + __builtin_ctz(found));
+                *e = (*e & ~(0xFFFFull << 32)) | ((unsigned long long)(unsigned)end << 32);
+            }
         }
     }
     // the same where that is not known (only called by the lanes it concerns)

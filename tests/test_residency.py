@@ -1,5 +1,5 @@
-"""How many replays a compute unit holds at once, from what the compiler wrote into the built library: registers and
-fixed LDS of every replay kernel, and the dynamic LDS of a launch.  A replay takes its time however few run beside it, so
+"""How many replays a compute unit holds at once, from what the compiler wrote into the built library: registers (and how many
+of them it keeps in memory) and fixed LDS of every replay kernel, and the dynamic LDS of a launch.  A replay takes its time however few run beside it, so
 a population that does not fit at once takes a second round."""
 import os
 import re
@@ -19,8 +19,8 @@ pytestmark = pytest.mark.skipif(not os.path.exists(LIB) or not all(map(os.path.e
 
 
 @pytest.fixture(scope="module")
-def kernels(tmp_path_factory):
-    """name -> (registers of a lane, fixed LDS, threads of a workgroup)."""
+def notes(tmp_path_factory):
+    """name -> (registers of a lane, fixed LDS, threads of a workgroup, registers of a lane kept in memory)."""
     tmp = tmp_path_factory.mktemp("code")
     fat, code = str(tmp / "fat"), str(tmp / "code")
     subprocess.run([TOOLS[0], f"--dump-section=.hip_fatbin={fat}", LIB, os.devnull], check=True)
@@ -40,10 +40,28 @@ def kernels(tmp_path_factory):
                 return m.group(1) if m else None
             name = field("name")
             if name and field("vgpr_count"):
-                found[name] = (int(field("vgpr_count")), int(field("group_segment_fixed_size")), int(field("max_flat_workgroup_size")))
+                found[name] = tuple(int(field(k)) for k in ("vgpr_count", "group_segment_fixed_size", "max_flat_workgroup_size",
+                                                            "vgpr_spill_count"))
     names = list(found)
     plain = subprocess.run(["c++filt"], input="\n".join(names), check=True, capture_output=True, text=True).stdout.split("\n")
     return {p: found[n] for p, n in zip(plain, names)}
+
+
+@pytest.fixture(scope="module")
+def kernels(notes):
+    """name -> (registers of a lane, fixed LDS, threads of a workgroup)."""
+    return {name: kernel[:3] for name, kernel in notes.items()}
+
+
+def test_registers_stay_registers(notes):
+    """No replay kernel keeps a lane's registers in memory, and the four-wavefront kernel of imperfect proxy knowledge is away from the
+    96 where it would begin to (engine model and tuner together need them all)."""
+    replays = {name: kernel for name, kernel in notes.items() if re.search(r"replay_\w+_kernel<", name)}
+    assert len(replays) >= 50
+    assert not [(name, kernel) for name, kernel in replays.items() if kernel[3] != 0]
+    proxy = {name: kernel[0] for name, kernel in replays.items()
+             if re.search(r"replay_segments_kernel<(0, false|0, true|1, false), true, 1, false>", name)}
+    assert len(proxy) == 3 and max(proxy.values()) <= 88, proxy
 
 
 def _resident(kernel, dynamic):
