@@ -105,8 +105,9 @@ typedef struct gorgo_model {
  *     slots more than 1,280 of them): 2 (default) packs then, up to twice as many, 1 whenever the shape allows,
  *     0 never.
  *   handover_poll_limit: how many times wavefronts that hand over through polled words poll before a replay is
- *     given up (default 2^24; must be >= 0).  No kernel polls: the wavefronts of a replay meet at workgroup barriers,
- *     packed or not, so the value has no effect and no replay is given up.
+ *     given up (default 2^24; must be >= 0).  The value has no effect and no replay is given up: the wavefronts of a replay
+ *     meet at workgroup barriers, and where one looks at a word until another has written it (replays of six wavefronts), the
+ *     writer waits for nothing but barriers that it has passed.
  *   table_factor_percent: the open-addressed cache tables of the block-table formulation get at least
  *     ceil(factor/100 * (cache_blocks + max blocks of a request)) slots, rounded up to a power of two
  *     (default 200, 110..1600). */

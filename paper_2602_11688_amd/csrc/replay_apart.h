@@ -48,9 +48,17 @@ struct ApartHandover : QueueHandover<PROXY> {
     int32_t cur_k2[PROXY ? WAVE : 1];     // the index's cursor's position
     int32_t hi[WAVE];                     // youngest record in the ring (of either cursor): a request that adds no more than `room`
                                           // blocks, none of them taken from records up to this one, moves no cursor past it
+    // Two words that are polled; their waits end.  Both are written by the evicting wavefront between meetings that it comes to by
+    // itself: it waits for nobody but at the meetings, and between X(r) and the next one (Y(r), X(r + 1)) it writes `walked` = r, if r
+    // has several previous owners, and `evicted` = r at every request.  Who polls for r has passed X(r), which the evicting
+    // wavefront has passed then too, and the next meeting cannot be over before the poller has come to it: so the writer is on
+    // its way between the two or done.  All wavefronts of a workgroup are resident, and a poller sleeps between two looks.
     int32_t evicted;                      // the cursors are up to date with the requests up to this one
     int32_t walked;                       // a request whose previous owners have been looked up
 };
+
+// The compiler moves no access to memory across this.
+__device__ __forceinline__ void in_order() { __atomic_signal_fence(__ATOMIC_SEQ_CST); }
 
 // ---------------------------------------------------------------------------------------------- evicting
 // What the latest request changes in the log, which the book-keeping wavefront is writing at the same time.
@@ -230,20 +238,23 @@ __device__ __forceinline__ void apart_evict_wave(const SegArgs& a, size_t p, int
     }
     const int every = look_every(R);
     int n_walks = 0;
-    // (`hi` is written first and read last: the deciding wavefront may look in between)
+    // (the deciding wavefront may look in between: `hi` is written first and read last.  LDS performs a wavefront's accesses in their
+    // order, so relaxed ones that the compiler keeps in order will do)
     auto publish = [&]() {
         const unsigned room1 = c1.room(), room2 = PROXY ? c2.room() : room1;
-        comm->hi[lane] = PROXY && c2.ring_hi > c1.ring_hi ? c2.ring_hi : c1.ring_hi;
-        asm volatile("" ::: "memory");
-        comm->cur_r[0][lane] = c1.cur_r;
-        comm->k_room[lane] = (unsigned)c1.cur_k | (room2 < room1 ? room2 : room1) << 16;
+        st(&comm->hi[lane], PROXY && c2.ring_hi > c1.ring_hi ? c2.ring_hi : c1.ring_hi);
+        in_order();
+        st(&comm->cur_r[0][lane], c1.cur_r);
+        st(&comm->k_room[lane], (uint32_t)c1.cur_k | (room2 < room1 ? room2 : room1) << 16);
         if constexpr (PROXY) {
-            comm->cur_r[1][lane] = c2.cur_r;
-            comm->cur_k2[lane] = c2.cur_k;
+            st(&comm->cur_r[1][lane], c2.cur_r);
+            st(&comm->cur_k2[lane], c2.cur_k);
         }
+        in_order();
     };
     publish();
-    comm->evicted = comm->walked = -1;
+    st(&comm->evicted, -1);
+    st(&comm->walked, -1);
     meet(true);                               // the first descriptors are there
     meet(true);
     SectionClock<TIMED> clk;
@@ -302,7 +313,7 @@ __device__ __forceinline__ void apart_evict_wave(const SegArgs& a, size_t p, int
             c1.look_ahead();
             if (PROXY) c2.look_ahead();
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            comm->walked = r;
+            st(&comm->walked, (int32_t)r);
         }
         if (bounded) {
             const LogChange f{r, is_best ? tail_r : N, owner, end};
@@ -327,8 +338,7 @@ __device__ __forceinline__ void apart_evict_wave(const SegArgs& a, size_t p, int
                 if (forgets) c2.evict(is_best ? n - c.seen : 0, log64, spare, f);
             }
             publish();
-            asm volatile("" ::: "memory");
-            comm->evicted = r;
+            st(&comm->evicted, (int32_t)r);
             // (records arrive every so often for all replicas, and whenever a request goes to one whose ring has run low)
             if ((r & every) == every || ballot(is_best && c1.ring_cnt < APART_LOOK / 4) != 0) {
                 c1.take_pending(c1.raw);
@@ -342,7 +352,7 @@ __device__ __forceinline__ void apart_evict_wave(const SegArgs& a, size_t p, int
             if (PROXY) c2.look_ahead();
             tail_r = is_best ? r : tail_r;
         } else {
-            comm->evicted = r;
+            st(&comm->evicted, (int32_t)r);
         }
         if (flags & DESC_SYNC) meet(true);                           // Y(r)
     }
@@ -653,14 +663,14 @@ __device__ __forceinline__ void apart_decide_wave(const SegArgs& a, size_t p, in
         int32_t cur_k2;
     } at{-1, -1, -1, 0, 0};
     auto look = [&]() {
-        at.cur_r = comm->cur_r[0][lane];
-        at.k_room = comm->k_room[lane];
+        at.cur_r = ld(&comm->cur_r[0][lane]);
+        at.k_room = ld(&comm->k_room[lane]);
         if constexpr (PROXY) {
-            at.cur_r2 = comm->cur_r[1][lane];
-            at.cur_k2 = comm->cur_k2[lane];
+            at.cur_r2 = ld(&comm->cur_r[1][lane]);
+            at.cur_k2 = ld(&comm->cur_k2[lane]);
         }
-        asm volatile("" ::: "memory");
-        at.hi = comm->hi[lane];
+        in_order();
+        at.hi = ld(&comm->hi[lane]);
     };
     // the request in hand: row cells of its first eight segments as seen by this lane (= replica), where they end, tokens,
     // blocks, flags; read (LDS) while the minimum of the one before is being found
@@ -783,7 +793,7 @@ __device__ __forceinline__ void apart_decide_wave(const SegArgs& a, size_t p, in
             if (behind) caught_up();
             if (unsure != 0 || (flags & DESC_DEEP)) {
                 while (ld(&comm->evicted) < r - 1) __builtin_amdgcn_s_sleep(1);
-                asm volatile("" ::: "memory");
+                in_order();
                 look();
                 match();
                 owner = of_mask(holders & single) ? cell[0] : spare;
