@@ -1,9 +1,10 @@
 // Seeded mutation fuzz of libgorgo's host side, built with AddressSanitizer and UndefinedBehaviorSanitizer
-// (tests/test_sanitized_host.py compiles and runs it).  usage: host_fuzz SEED ITERATIONS SCRATCH_FILE
+// (tests/test_sanitized_host.py compiles and runs it).  usage: host_fuzz SEED ITERATIONS SCRATCH_FILE [tell]
 // Each iteration writes a small valid JSON-lines trace (Sec. 3 layout: timestamp, input_length, output_length,
 // hash_ids), damages it in one of several ways (or not at all), loads it, and on success walks the host-side entry
 // points with ordinary and hostile arguments.  Nothing here has an expected value beyond "returns a documented
 // status and the sanitizers stay silent"; valid files must load, and what they report must match what was written.
+// With `tell` it only loads, and prints what came of each file, for builds that read them in different pieces to be compared.
 #include <cinttypes>
 #include <cmath>
 #include <cstdio>
@@ -14,6 +15,7 @@
 #include <vector>
 
 #include "gorgo.h"
+#include "internal.h"
 
 static uint64_t rng_state;
 static uint64_t rnd() {       // SplitMix64
@@ -175,11 +177,33 @@ static void es_walk() {
     CHECK(gorgo_online_steps(-1, 128, 32) < 0 && gorgo_online_steps(1000, 128, 32) == 28);
 }
 
+// a number that stands for everything a file's trace holds
+template <class T>
+static void mix(uint64_t* sum, const std::vector<T>& v) {
+    const unsigned char* const at = reinterpret_cast<const unsigned char*>(v.data());
+    for (size_t k = 0; k < v.size() * sizeof(T); ++k) *sum = (*sum ^ at[k]) * 0x100000001B3ull;
+    *sum = (*sum ^ v.size()) * 0x100000001B3ull;
+}
+static uint64_t digest(const gorgo_trace* t) {
+    uint64_t sum = 0xCBF29CE484222325ull;
+    mix(&sum, t->ts);
+    mix(&sum, t->in_len);
+    mix(&sum, t->out_len);
+    mix(&sum, t->blk_off);
+    mix(&sum, t->key);
+    mix(&sum, t->first);
+    mix(&sum, t->seg_off);
+    mix(&sum, t->seg_prev);
+    mix(&sum, t->row_ref);
+    return sum;
+}
+
 int main(int argc, char** argv) {
-    if (argc != 4) {
-        std::fprintf(stderr, "usage: host_fuzz SEED ITERATIONS SCRATCH_FILE\n");
+    if (argc != 4 && !(argc == 5 && std::strcmp(argv[4], "tell") == 0)) {
+        std::fprintf(stderr, "usage: host_fuzz SEED ITERATIONS SCRATCH_FILE [tell]\n");
         return 2;
     }
+    const bool tell = argc == 5;
     rng_state = std::strtoull(argv[1], nullptr, 10);
     const long iterations = std::strtol(argv[2], nullptr, 10);
     const char* path = argv[3];
@@ -198,6 +222,11 @@ int main(int argc, char** argv) {
         const int rc = gorgo_load_trace(path, bt, &t);
         CHECK(documented(rc));
         if (hits == 0 && bt == 512) CHECK(rc == 0);
+        if (tell) {
+            std::printf("%ld %d %s %016" PRIx64 "\n", it, rc, rc ? gorgo_last_error() : "", rc ? 0 : digest(t));
+            gorgo_free_trace(t);
+            continue;
+        }
         if (rc == 0) {
             CHECK(t != nullptr);
             ++loaded;
@@ -214,6 +243,8 @@ int main(int argc, char** argv) {
     CHECK(gorgo_load_trace(nullptr, 512, &t) == GORGO_ERR_INVALID_ARG);
     CHECK(gorgo_load_trace(path, 512, nullptr) == GORGO_ERR_INVALID_ARG);
     gorgo_free_trace(nullptr);
+    CHECK(gorgo_load_trace("/", 512, &t) == GORGO_ERR_IO);      // (a folder can be opened but not read)
+    if (tell) return 0;
     std::printf("host_fuzz: %ld iterations, %ld files loaded, %ld refused\n", iterations, loaded, refused);
     return loaded > 0 && refused > 0 ? 0 : 4;
 }

@@ -21,8 +21,8 @@ ENV.pop("LD_PRELOAD", None)
 pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="no host C++ compiler")
 
 
-def _build(out, sources, includes):
-    cmd = ["g++", *FLAGS, *[f"-I{i}" for i in includes], *sources, "-o", out]
+def _build(out, sources, includes, flags=FLAGS):
+    cmd = ["g++", *flags, *[f"-I{i}" for i in includes], *sources, "-o", out]
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-4000:]
 
@@ -30,17 +30,35 @@ def _build(out, sources, includes):
 def _run(cmd):
     r = subprocess.run(cmd, capture_output=True, text=True, env=ENV, timeout=600)
     assert r.returncode == 0, (r.stdout[-2000:], r.stderr[-6000:])
-    assert "runtime error" not in r.stderr and "AddressSanitizer" not in r.stderr, r.stderr[-6000:]
+    assert not any(x in r.stderr for x in ("runtime error", "AddressSanitizer", "ThreadSanitizer")), r.stderr[-6000:]
     return r.stdout
+
+
+def _build_fuzz(folder, flags=FLAGS):
+    out = str(folder / "host_fuzz")
+    _build(out, [os.path.join(CSRC, f) for f in ("trace.cpp", "es.cpp", "api.cpp")] +
+           [os.path.join(SAN, "host_stubs.cpp"), os.path.join(SAN, "host_fuzz.cpp")],
+           [os.path.join(ROOT, "include"), CSRC], flags)
+    return out
 
 
 @pytest.fixture(scope="module")
 def host_fuzz(tmp_path_factory):
-    out = str(tmp_path_factory.mktemp("san") / "host_fuzz")
-    _build(out, [os.path.join(CSRC, f) for f in ("trace.cpp", "es.cpp", "api.cpp")] +
-           [os.path.join(SAN, "host_stubs.cpp"), os.path.join(SAN, "host_fuzz.cpp")],
-           [os.path.join(ROOT, "include"), CSRC])
-    return out
+    return _build_fuzz(tmp_path_factory.mktemp("san"))
+
+
+@pytest.mark.parametrize("read,piece", [(300, 64), (4096, 200)])
+@pytest.mark.parametrize("sanitizer", ["address,undefined", "thread"])
+def test_files_read_in_small_pieces_give_what_one_piece_gives(host_fuzz, tmp_path, sanitizer, read, piece):
+    """Blocks and pieces of a few lines, so that these files take the way of long ones: several threads, lines on two blocks,
+    lines longer than a block, NULs; the same traces and the same words about bad lines as read at once."""
+    flags = ["-std=c++17", "-O1", "-g", f"-fsanitize={sanitizer}", "-fno-sanitize-recover=all", "-pthread",
+             f"-DGORGO_READ_BYTES={read}", f"-DGORGO_PIECE_BYTES={piece}"]
+    small = _build_fuzz(tmp_path, flags)
+    args = [str(read + piece), "400", str(tmp_path / "fuzz.jsonl"), "tell"]
+    told = _run([small, *args])
+    assert told.count("\n") == 400
+    assert told == _run([host_fuzz, *args])
 
 
 @pytest.mark.parametrize("seed", [1, 20260211, 11688])
