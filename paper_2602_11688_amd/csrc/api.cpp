@@ -124,6 +124,7 @@ int make_plan(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* o
     pl->B = m->batch;
     pl->N = t->N;
     pl->C = m->cache_blocks;
+    pl->requests_held = pl->C > 0 && t->total_blocks > 0 ? (double)pl->C * (double)pl->N / (double)t->total_blocks : INFINITY;
     pl->block_tokens = m->block_tokens;
     pl->a_pf = m->prefill_ms_per_token;
     pl->a_dec = m->decode_ms_per_token;

@@ -117,6 +117,7 @@ struct Plan {
     int64_t nseg = 0;
     int32_t P = 0, R = 0, B = 0;
     int64_t N = 0, C = 0;
+    double requests_held = 0;        // by a replica's cache, requests of the trace's mean length
     int64_t cap = 0;                 // slots per (replay, replica) table, power of two
     int64_t row_slots = 0;           // block formulation: rows of stamps instead of tables where not 0
     bool each = false;               // segment formulation: a workgroup per replay and replica (routes that a policy dictates)

@@ -76,6 +76,37 @@ def test_requests_that_are_waited_for(gap_ms, decode):
     check_online(tr, model, rtt, [[1.0, 0.5, 0.1]] * 2, z, [1.0, 0.1], 8, 1, [0.05] * 3, [2.0] * 3, 0.5)
 
 
+def wavefronts(handle, model, rtt, P):
+    """Of each replay in a launch of P with fixed weights, by the sections of its time: the evicting wavefront's is one of six."""
+    res = g.eval_population(handle, model, rtt, np.tile([[0.5, 1.0, 0.1]], (P, 1)), np.ones(P), per_request=False, sections=True)
+    kinds = {(bool(x[0][2] > 0), bool(x[2][4] > 0)) for x in res.sections.cpu().numpy()}
+    return {frozenset([(True, False)]): 4, frozenset([(False, True)]): 6}[frozenset(kinds)]
+
+
+@pytest.mark.parametrize("R,B,P,held,want", [(12, 2, 768, 0, 6), (12, 2, 769, 0, 4), (13, 2, 512, 0, 6), (13, 2, 513, 0, 4),
+                                             (32, 2, 300, 5, 6), (33, 2, 300, 14.9, 4), (33, 2, 300, 15.1, 6), (64, 2, 2, 5, 4),
+                                             (64, 16, 512, 0, 6), (12, 64, 768, 0, 6)])
+def test_which_launches_have_six_wavefronts(R, B, P, held, want):
+    """The number of replays, of replicas, and of requests that a cache holds; many slots (fixed weights fit all the same)."""
+    wl = tg.config(2, 400)
+    blocks = int(np.diff(wl.trace.blk_off).max())
+    mean = wl.trace.blk_off[-1] / wl.trace.N
+    cache = int(held * mean)
+    assert cache == 0 or cache >= blocks
+    assert wavefronts(load(wl.trace), g.Model(R, B, cache, 0.05, 20.0), np.linspace(5.0, 90.0, R), P) == want
+
+
+@pytest.mark.parametrize("R,held", [(32, 12), (33, 12), (64, 14), (64, 24), (40, 26)])
+def test_caches_of_few_requests(R, held):
+    """On both sides of the rule for caches that hold few requests, the policies it concerns and one that it does not."""
+    tr = tg.random_forest(R + held, 1500, roots=5, max_blocks=30, grow=3, gap_ms=30, keep=0.8)
+    model = g.Model(R, 4, max(int(held * tr.blk_off[-1] / tr.N), int(np.diff(tr.blk_off).max())), 0.05, 4.0)
+    rtt = np.linspace(5.0, 120.0, R)
+    check_population(tr, model, rtt, [[0.5, 1.0, 0.1], [0.0, 0.1, 1.0], [50.0, 0.05, 0.0]], 1.0, paths=[2])
+    for policy, P in (("session-affinity", 257), ("least-request", 2)):
+        check_policy(tr, model, rtt, policy, np.linspace(0.5, 2.0, P).tolist())
+
+
 @pytest.mark.parametrize("R,B,cache", [(3, 8, 1), (5, 3, 3), (16, 2, 2), (33, 8, 1), (64, 16, 4), (7, 9, 0), (32, 4, 9), (12, 8, 14)])
 def test_six_wavefronts_or_four(R, B, cache):
     """The same replays in a launch of 12 and repeated in one of 780: paths of many segments and owners, caches that hold one to
