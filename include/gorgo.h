@@ -130,11 +130,12 @@ typedef struct gorgo_outputs {
     double* p95_e2e_ms;    /* [P]    nearest-rank 95th percentile of e2e_ms[p][.]             */
 } gorgo_outputs;
 
-/* Device workspace for gorgo_eval_population, or any other evaluation, of P replays with this set of outputs (`outputs`
- * may be NULL: the size then covers any combination).  The workspace holds the per-replay cache state, the
+/* Device workspace in which gorgo_eval_population, or any other evaluation, of P replays with this set of outputs runs fastest
+ * (`outputs` may be NULL: the size then covers any combination).  The workspace holds the per-replay cache state, the
  * in-flight request records and stand-ins for per-request outputs that were not requested but are needed
- * by the percentile reduction.  It is what the fastest layout of the cache state takes; block by block (options.replay_path)
- * an evaluation also runs in less where hashed tables are smaller than rows of stamps. */
+ * by the percentile reduction.  It includes the room in which the policies that dictate the routes lay the requests out, which
+ * the other evaluations do without: gorgo_policy_workspace_bytes says what one policy takes.  Block by block
+ * (options.replay_path) an evaluation also runs in less where hashed tables are smaller than rows of stamps. */
 int gorgo_workspace_bytes(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* options, int32_t P, const gorgo_outputs* outputs,
                           size_t* bytes);
 
@@ -166,7 +167,8 @@ int gorgo_trace_to_device(const gorgo_trace* t);
  * (gorgo_last_eval_kernel_ms does not cover it); the trace must already be resident on the current device
  * (gorgo_trace_to_device, or any earlier evaluation there), else GORGO_ERR_INVALID_ARG.  An evaluation that does not fit
  * into GORGO_STATIC_SCRATCH_BYTES is refused with GORGO_ERR_WORKSPACE before anything is enqueued; one whose
- * gorgo_workspace_bytes is not above that fits, and so may one whose cache state takes less as hashed tables.  Every call on a GPU uses that GPU's one array: what must start clean is cleared by the call's
+ * gorgo_policy_workspace_bytes for the cost model is not above that fits, and so may one whose cache state takes less as
+ * hashed tables.  Every call on a GPU uses that GPU's one array: what must start clean is cleared by the call's
  * own kernels, and two such calls that overlap in time on one GPU (different streams or threads) race. */
 #define GORGO_STATIC_SCRATCH_BYTES ((size_t)64 << 20)
 int gorgo_eval_population_static(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* options, const double* rtt_ms,
@@ -281,10 +283,10 @@ typedef enum gorgo_policy {
     GORGO_POLICY_RANDOM = 3
 } gorgo_policy;
 
-/* Device workspace in which gorgo_eval_policy and gorgo_eval_engine run `policy` fastest.  The session-affinity and the random
- * policy dictate the routes; with room to lay the requests out replica by replica their replays are several times as fast
- * (up to 256 replays, from 256 requests on), and that room is asked for here.  With gorgo_workspace_bytes, which is enough, they
- * go request by request.  The other policies: the same as gorgo_workspace_bytes. */
+/* Device workspace in which an evaluation with `policy` runs fastest (0: the cost model, with gorgo_eval_online and
+ * gorgo_eval_proxy too).  The session-affinity and the random policy dictate the routes; with room to lay the requests out replica by
+ * replica their replays are several times as fast (up to 256 replays, from 256 requests on): their size is gorgo_workspace_bytes, and
+ * in that of the other policies, which has no such room and is enough, they go request by request. */
 int gorgo_policy_workspace_bytes(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* options, int32_t policy, int32_t P,
                                  const gorgo_outputs* outputs, size_t* bytes);
 

@@ -279,8 +279,8 @@ def _outputs_struct(route=None, hit_blocks=None, ttft_ms=None, e2e_ms=None, p95_
 
 def workspace_bytes(trace: Trace, model: Model, P: int, outputs: Optional[_Outputs] = None, options: Optional[Options] = None,
                     policy: Optional[str] = None) -> int:
-    """Bytes of workspace for an evaluation; with a policy ("session-affinity", "random", ...) those in which
-    eval_policy and eval_engine run it fastest (gorgo_policy_workspace_bytes)."""
+    """Bytes of workspace for any evaluation; with a policy ("cost-model", "session-affinity", ...) for one with that policy
+    (gorgo_policy_workspace_bytes)."""
     n = C.c_size_t()
     m = model.c()
     o = None if outputs is None else C.byref(outputs)
@@ -289,23 +289,6 @@ def workspace_bytes(trace: Trace, model: Model, P: int, outputs: Optional[_Outpu
     else:
         _check(lib().gorgo_policy_workspace_bytes(trace._h, C.byref(m), _opt(options), _policy_code(policy), P, o, C.byref(n)))
     return n.value
-
-
-_ERR_WORKSPACE = -7
-
-
-def _in_workspace(given, need: int, dev, call):
-    """call(workspace), which returns a status: in the caller's workspace where the call gets along with it, though it may hold
-    fewer than the `need` bytes asked for, else in one allocated here.  (What is refused has enqueued nothing.)"""
-    import torch
-    if given is not None:
-        rc = call(given)
-        if rc != _ERR_WORKSPACE or given.numel() >= need:
-            _check(rc)
-            return given
-    fresh = torch.empty((need,), dtype=torch.uint8, device=dev)
-    _check(call(fresh))
-    return fresh
 
 
 @dataclass
@@ -355,20 +338,22 @@ def eval_population(trace: Trace, model: Model, rtt_ms, params, scale, *, per_re
         res.p95_ttft_ms = torch.empty((P,), dtype=torch.float64, device=dev)
         res.p95_e2e_ms = torch.empty((P,), dtype=torch.float64, device=dev)
     o = _outputs_struct(res.route, res.hit_blocks, res.ttft_ms, res.e2e_ms, res.p95_ttft_ms, res.p95_e2e_ms)
-    need = workspace_bytes(trace, model, P, o, options)
+    need = workspace_bytes(trace, model, P, o, options, "cost-model")
+    if workspace is None or workspace.numel() < need:
+        workspace = torch.empty((need,), dtype=torch.uint8, device=dev)
+    res.workspace = workspace
     s = stream if stream is not None else torch.cuda.current_stream(dev)
     m = model.c()
-    if sections:
-        res.sections = torch.zeros((P, 3, 12), dtype=torch.int64, device=dev)
-
-    def call(ws):
-        args = (trace._h, C.byref(m), _opt(options), _ptr(rtt), _ptr(par), _ptr(sc), P, C.byref(o), C.c_void_p(ws.data_ptr()),
-                ws.numel(), C.c_void_p(s.cuda_stream))
-        if sections:
-            return lib().gorgo_eval_population_sections(*args, C.c_void_p(res.sections.data_ptr()))
-        return lib().gorgo_eval_population(*args)
     with torch.cuda.device(dev):
-        res.workspace = _in_workspace(workspace, need, dev, call)
+        if sections:
+            res.sections = torch.zeros((P, 3, 12), dtype=torch.int64, device=dev)
+            _check(lib().gorgo_eval_population_sections(trace._h, C.byref(m), _opt(options), _ptr(rtt), _ptr(par), _ptr(sc), P, C.byref(o),
+                                                        C.c_void_p(workspace.data_ptr()), workspace.numel(),
+                                                        C.c_void_p(s.cuda_stream), C.c_void_p(res.sections.data_ptr())))
+        else:
+            _check(lib().gorgo_eval_population(trace._h, C.byref(m), _opt(options), _ptr(rtt), _ptr(par), _ptr(sc), P, C.byref(o),
+                                               C.c_void_p(workspace.data_ptr()), workspace.numel(),
+                                               C.c_void_p(s.cuda_stream)))
     return res
 
 
@@ -438,16 +423,15 @@ def eval_policy(trace: Trace, model: Model, rtt_ms, policy: str, scale, *, seeds
         res.p95_ttft_ms = torch.empty((P,), dtype=torch.float64, device=dev)
         res.p95_e2e_ms = torch.empty((P,), dtype=torch.float64, device=dev)
     o = _outputs_struct(res.route, res.hit_blocks, res.ttft_ms, res.e2e_ms, res.p95_ttft_ms, res.p95_e2e_ms)
-    code = POLICIES[policy]
     need = workspace_bytes(trace, model, P, o, options, policy)
+    if workspace is None or workspace.numel() < need:
+        workspace = torch.empty((need,), dtype=torch.uint8, device=dev)
+    res.workspace = workspace
     s = stream if stream is not None else torch.cuda.current_stream(dev)
     m = model.c()
-
-    def call(ws):
-        return lib().gorgo_eval_policy(trace._h, C.byref(m), _opt(options), _ptr(rtt), code, _ptr(sd), _ptr(sc), P, C.byref(o),
-                                       C.c_void_p(ws.data_ptr()), ws.numel(), C.c_void_p(s.cuda_stream))
     with torch.cuda.device(dev):
-        res.workspace = _in_workspace(workspace, need, dev, call)
+        _check(lib().gorgo_eval_policy(trace._h, C.byref(m), _opt(options), _ptr(rtt), POLICIES[policy], _ptr(sd), _ptr(sc), P, C.byref(o),
+                                       C.c_void_p(workspace.data_ptr()), workspace.numel(), C.c_void_p(s.cuda_stream)))
     return res
 
 
@@ -499,15 +483,15 @@ def eval_online(trace: Trace, model: Model, rtt_ms, theta0, z, scale, *, lo, hi,
     on = _Online(window, hop, (C.c_double * 3)(*[float(x) for x in lo]), (C.c_double * 3)(*[float(x) for x in hi]),
                  float(sigma0), dp(zt), dp(res.theta_step), dp(res.fitness_step), dp(res.theta_final),
                  dp(res.sigma_final), dp(res.accepted))
-    need = workspace_bytes(trace, model, P, o, options)
+    need = workspace_bytes(trace, model, P, o, options, "cost-model")
+    if workspace is None or workspace.numel() < need:
+        workspace = torch.empty((need,), dtype=torch.uint8, device=dev)
+    res.workspace = workspace
     s = stream if stream is not None else torch.cuda.current_stream(dev)
     m = model.c()
-
-    def call(ws):
-        return lib().gorgo_eval_online(trace._h, C.byref(m), _opt(options), _ptr(rtt), _ptr(th0), _ptr(sc), P, C.byref(on), C.byref(o),
-                                       C.c_void_p(ws.data_ptr()), ws.numel(), C.c_void_p(s.cuda_stream))
     with torch.cuda.device(dev):
-        res.workspace = _in_workspace(workspace, need, dev, call)
+        _check(lib().gorgo_eval_online(trace._h, C.byref(m), _opt(options), _ptr(rtt), _ptr(th0), _ptr(sc), P, C.byref(on), C.byref(o),
+                                       C.c_void_p(workspace.data_ptr()), workspace.numel(), C.c_void_p(s.cuda_stream)))
     res._z = zt          # keep the draws alive until the stream has consumed them
     return res
 
@@ -581,17 +565,17 @@ def eval_engine(trace: Trace, model: Model, engine: Engine, rtt_ms, scale, *, pa
                      C.c_void_p(res.fitness_step.data_ptr()), C.c_void_p(res.theta_final.data_ptr()),
                      C.c_void_p(res.sigma_final.data_ptr()), C.c_void_p(res.accepted.data_ptr()))
     o = _outputs_struct(res.route, res.hit_blocks, res.ttft_ms, res.e2e_ms, res.p95_ttft_ms, res.p95_e2e_ms)
-    code = _policy_code(policy)
     need = workspace_bytes(trace, model, P, o, options, policy)
+    if workspace is None or workspace.numel() < need:
+        workspace = torch.empty((need,), dtype=torch.uint8, device=dev)
+    res.workspace = workspace
     s = stream if stream is not None else torch.cuda.current_stream(dev)
     m = model.c()
-
-    def call(ws):
-        return lib().gorgo_eval_engine(trace._h, C.byref(m), _opt(options), C.byref(eng), _ptr(rtt), code, _ptr(par), _ptr(sd),
-                                       None if on is None else C.byref(on), _ptr(sc), P, C.byref(o), C.c_void_p(ws.data_ptr()),
-                                       ws.numel(), C.c_void_p(s.cuda_stream))
+    code = _policy_code(policy)
     with torch.cuda.device(dev):
-        res.workspace = _in_workspace(workspace, need, dev, call)
+        _check(lib().gorgo_eval_engine(trace._h, C.byref(m), _opt(options), C.byref(eng), _ptr(rtt), code, _ptr(par), _ptr(sd),
+                                       None if on is None else C.byref(on), _ptr(sc), P, C.byref(o),
+                                       C.c_void_p(workspace.data_ptr()), workspace.numel(), C.c_void_p(s.cuda_stream)))
     return res
 
 
@@ -668,16 +652,16 @@ def eval_proxy(trace: Trace, model: Model, proxy: Proxy, params, scale, *, engin
                      C.c_void_p(res.fitness_step.data_ptr()), C.c_void_p(res.theta_final.data_ptr()),
                      C.c_void_p(res.sigma_final.data_ptr()), C.c_void_p(res.accepted.data_ptr()))
     o = _outputs_struct(res.route, res.hit_blocks, res.ttft_ms, res.e2e_ms, res.p95_ttft_ms, res.p95_e2e_ms)
-    need = workspace_bytes(trace, model, P, o, options)
+    need = workspace_bytes(trace, model, P, o, options, "cost-model")
+    if workspace is None or workspace.numel() < need:
+        workspace = torch.empty((need,), dtype=torch.uint8, device=dev)
+    res.workspace = workspace
     s = stream if stream is not None else torch.cuda.current_stream(dev)
     m = model.c()
-
-    def call(ws):
-        return lib().gorgo_eval_proxy(trace._h, C.byref(m), _opt(options), C.byref(px), None if eng is None else C.byref(eng), _ptr(par),
-                                      None if on is None else C.byref(on), _ptr(sc), P, C.byref(o), C.c_void_p(ws.data_ptr()),
-                                      ws.numel(), C.c_void_p(s.cuda_stream))
     with torch.cuda.device(dev):
-        res.workspace = _in_workspace(workspace, need, dev, call)
+        _check(lib().gorgo_eval_proxy(trace._h, C.byref(m), _opt(options), C.byref(px), None if eng is None else C.byref(eng), _ptr(par),
+                                      None if on is None else C.byref(on), _ptr(sc), P, C.byref(o),
+                                      C.c_void_p(workspace.data_ptr()), workspace.numel(), C.c_void_p(s.cuda_stream)))
     res._tables = tables
     return res
 
@@ -730,14 +714,14 @@ def es_step(trace: Trace, model: Model, rtt_ms, scale: float, P: int, state: EsS
     rtt = _np(rtt_ms, np.float64)
     dev = torch.device(device)
     need = es_workspace_bytes(trace, model, P, options)
+    if workspace is None or workspace.numel() < need:
+        workspace = torch.empty((need,), dtype=torch.uint8, device=dev)
     par = np.zeros((P, 3), np.float64)
     fit = np.zeros(P, np.float64)
     s = stream if stream is not None else torch.cuda.current_stream(dev)
     m = model.c()
-
-    def call(ws):
-        return lib().gorgo_es_step(trace._h, C.byref(m), _opt(options), _ptr(rtt), float(scale), P, C.byref(state), _ptr(par), _ptr(fit),
-                                   C.c_void_p(ws.data_ptr()), ws.numel(), C.c_void_p(s.cuda_stream))
     with torch.cuda.device(dev):
-        workspace = _in_workspace(workspace, need, dev, call)
+        _check(lib().gorgo_es_step(trace._h, C.byref(m), _opt(options), _ptr(rtt), float(scale), P, C.byref(state), _ptr(par),
+                                   _ptr(fit), C.c_void_p(workspace.data_ptr()), workspace.numel(),
+                                   C.c_void_p(s.cuda_stream)))
     return par, fit, workspace

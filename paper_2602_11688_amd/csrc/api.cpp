@@ -111,7 +111,7 @@ void lay_out(const gorgo_trace* t, const gorgo_outputs* o, Plan* pl) {
 bool dictates(int32_t policy) { return policy == GORGO_POLICY_SESSION_AFFINITY || policy == GORGO_POLICY_RANDOM; }
 
 // Table geometry and workspace carve-up.  `room`: bytes of workspace there are, where that is known.  `dictated`: whether the
-// evaluation's policy dictates the routes.
+// evaluation's policy dictates the routes (or may, where only the size is asked for).
 int make_plan(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* options, int32_t P, const gorgo_outputs* o,
               Plan* pl, size_t room = SIZE_MAX, bool dictated = false) {
     if (P < 1 || P > (1 << 20)) return fail(GORGO_ERR_INVALID_ARG, "P must be in 1..2^20");
@@ -230,7 +230,7 @@ int gorgo_workspace_bytes(const gorgo_trace* t, const gorgo_model* m, const gorg
     int rc = check_model(t, m);
     if (rc) return rc;
     Plan pl;
-    rc = make_plan(t, m, options, P, outputs, &pl);
+    rc = make_plan(t, m, options, P, outputs, &pl, SIZE_MAX, true);
     if (rc) return rc;
     *bytes = pl.total;
     return GORGO_OK;

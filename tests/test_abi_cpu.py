@@ -226,23 +226,23 @@ def test_options_are_per_call_and_validated():
 
 @pytest.mark.parametrize("R,N", [(1, 300), (2, 255), (2, 256), (16, 300), (64, 2000)])
 def test_room_for_dictated_routes_is_asked_for_by_their_policies_alone(R, N):
-    """What the other evaluations cannot use is not in gorgo_workspace_bytes (whose size per replay is the same for few replays,
-    which a policy's replays may be laid out by replica for, and many), and it is not needed: any evaluation is content with
-    that size."""
+    """gorgo_workspace_bytes has room for any evaluation, the policies' own size what each can use (per replay the same for few
+    replays, which may be laid out by replica, and many); that room is not needed: any policy is content with the others' size."""
     t = _trace(tg.random_forest(R + N, N, roots=3))
     model, L = g.Model(R, 4, 0, 0.05, 20.0), g.lib()
     m, n, o = model.c(), C.c_size_t(), gb._Outputs()
     few = 64
-    plain = g.workspace_bytes(t, model, few)
+    plain = g.workspace_bytes(t, model, few, policy="cost-model")
     assert g.workspace_bytes(t, model, 16 * few) > 15 * plain
     laid_out = N >= 256 and R > 1
+    assert g.workspace_bytes(t, model, few) == g.workspace_bytes(t, model, few, policy="random")
     for policy, more in (("cost-model", False), ("least-request", False), ("session-affinity", laid_out), ("random", laid_out)):
         size = g.workspace_bytes(t, model, few, policy=policy)
         assert size > plain if more else size == plain, policy
     assert L.gorgo_policy_workspace_bytes(t._h, C.byref(m), None, 4, few, None, C.byref(n)) == -1
     assert L.gorgo_policy_workspace_bytes(t._h, C.byref(m), None, 2, few, None, None) == -1
     rtt, sc, seeds = np.ones(R), np.ones(few), np.arange(few, dtype=np.uint64)
-    exact = g.workspace_bytes(t, model, few, o)
+    exact = g.workspace_bytes(t, model, few, o, policy="cost-model")
 
     def policy_call(policy, nbytes, ws):
         return L.gorgo_eval_policy(t._h, C.byref(m), None, gb._ptr(rtt), policy, gb._ptr(seeds), gb._ptr(sc), few, C.byref(o), ws, nbytes,

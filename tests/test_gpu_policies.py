@@ -92,36 +92,26 @@ def test_dictated_routes_replica_by_replica(monkeypatch, R, N):
         go()
 
 
-@pytest.mark.parametrize("ids", ["prefix", "tangled"])
-def test_a_callers_workspace_that_is_enough_is_used(ids):
-    """Of the size asked for without a policy, and (where hashed tables take less than rows of stamps) of the smallest that will do:
-    nothing is allocated beside it; a smaller one is replaced."""
+def test_a_callers_workspace_that_is_enough_is_used():
+    """Of the size asked for without a policy by every call, and without its room for dictated routes by those that have no use for
+    it; a smaller one is replaced, and the replays of a policy are laid out by replica either way."""
     import torch
-    consistent = ids == "prefix"
-    tr = tg.random_small(5, 900, 4, n_ids=400, max_blocks=12, consistent=consistent, gap_ms=5)
-    model, rtt = g.Model(4, 3, 24, 0.05, 20.0), np.linspace(5.0, 80.0, 4)
+    tr = tg.random_small(5, 900, 4, n_ids=400, max_blocks=12, consistent=True, gap_ms=5)
+    model, rtt, seeds = g.Model(4, 3, 24, 0.05, 20.0), np.linspace(5.0, 80.0, 4), np.array([1, 2], np.uint64)
     h = load(tr)
-    sizes = [g.workspace_bytes(h, model, 2)]
-    o = binding._Outputs()
-    m = model.c()
-    small = np.ones((2, 3)), np.ones(2)
-    L = g.lib()
-    assert L.gorgo_eval_population(h._h, binding.C.byref(m), None, binding._ptr(np.asarray(rtt)), binding._ptr(small[0]),
-                                   binding._ptr(small[1]), 2, binding.C.byref(o), binding.C.c_void_p(256), 0, None) == -7
-    least = int(re.search(rb"needs (\d+)", L.gorgo_last_error()).group(1)) + 2 * 2 * 8 * tr.N + 512     # (the latencies' stand-ins)
-    sizes.append(min(least, sizes[0]))
-    for size in sizes:
+    every, plain = g.workspace_bytes(h, model, 2), g.workspace_bytes(h, model, 2, policy="cost-model")
+    assert plain < every
+    ref = g.eval_policy(h, model, rtt, "random", [1.0, 2.0], seeds=seeds)
+    for size in (every, plain, 256):
         ws = torch.zeros(size, dtype=torch.uint8, device="cuda:0")
-        runs = [g.eval_population(h, model, rtt, small[0], 1.0, workspace=ws)]
-        runs += [g.eval_policy(h, model, rtt, policy, [1.0, 2.0], seeds=np.array([1, 2], np.uint64), workspace=ws)
-                 for policy in ("least-request", "session-affinity", "random")]
-        torch.cuda.synchronize()
-        assert all(res.workspace is ws for res in runs)
-        ref = g.eval_policy(h, model, rtt, "random", [1.0, 2.0], seeds=np.array([1, 2], np.uint64))
-        assert torch.equal(runs[3].route, ref.route) and torch.equal(runs[3].ttft_ms, ref.ttft_ms)
-    res = g.eval_policy(h, model, rtt, "random", [1.0, 2.0], seeds=np.array([1, 2], np.uint64), workspace=ws[:256])
-    torch.cuda.synchronize()
-    assert res.workspace.numel() > 256 and torch.equal(res.ttft_ms, ref.ttft_ms)
+        res = g.eval_population(h, model, rtt, np.ones((2, 3)), 1.0, workspace=ws)
+        assert (res.workspace is ws) == (size >= plain)
+        for policy in ("least-request", "session-affinity", "random"):
+            res = g.eval_policy(h, model, rtt, policy, [1.0, 2.0], seeds=seeds, workspace=ws)
+            assert (res.workspace is ws) == (size >= (plain if policy == "least-request" else every)), policy
+            assert res.workspace.numel() >= g.workspace_bytes(h, model, 2, binding._outputs_struct(
+                res.route, res.hit_blocks, res.ttft_ms, res.e2e_ms, res.p95_ttft_ms, res.p95_e2e_ms), policy=policy)
+        assert torch.equal(res.route, ref.route) and torch.equal(res.ttft_ms, ref.ttft_ms)
 
 
 def test_special_case_weights_are_the_other_two_baselines():
