@@ -351,10 +351,11 @@ int gorgo_eval_engine(const gorgo_trace* t, const gorgo_model* m, const gorgo_op
  *     sees the replicas' caches as they are.
  * With one epoch (or equal rows) and index_blocks = -1 or = cache_blocks the results equal
  * gorgo_eval_population's bit for bit.
- * In the block-table formulation the index lives in the replica's table (the same entries read against a second
- * eviction threshold), so a bounded cache's tables must also hold what only the index still holds: the call fails
- * with GORGO_ERR_CAPACITY, naming the options.table_factor_percent that is enough, when the tables of the
- * workspace are too small for index_blocks (or, with index_blocks = 0, for every id of the trace). */
+ * In hashed block tables the index lives in the replica's table (the same entries read against a second
+ * eviction threshold), so a bounded cache's tables must also hold what only the index still holds: block by block the call fails
+ * with GORGO_ERR_CAPACITY, naming the options.table_factor_percent that is enough, when tables of that factor
+ * are too small for index_blocks (or, with index_blocks = 0, for every id of the trace).  It does so over rows of stamps
+ * too, which could hold it: which calls are refused does not depend on how much workspace there is. */
 typedef struct gorgo_proxy {
     int32_t epochs;               /* 1..65536 probe epochs given                                              */
     int32_t probe_interval_ms;    /* >= 1                                                                     */

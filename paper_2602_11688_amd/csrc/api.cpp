@@ -332,7 +332,8 @@ int evaluate(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* op
             return fail(GORGO_ERR_NONFINITE, "scale[" + std::to_string(p) + "] must be finite and in 0..1e6");
     if (proxy && proxy->index_blocks >= 0 && pl.path == PATH_BLOCKS && pl.C > 0) {
         // the tables also hold what only the proxy's index still holds: more entries than the cache's, all the
-        // trace's when the index never forgets
+        // trace's when the index never forgets (rows of stamps could hold it, but whether a call is refused is not to depend on
+        // the workspace that it is given)
         const int64_t held = proxy->index_blocks > 0 ? std::max<int64_t>(pl.C, proxy->index_blocks) : t->unique_ids;
         const int64_t least = least_table_slots(held + t->max_distinct, t->max_distinct);
         if (pl.cap < least)
