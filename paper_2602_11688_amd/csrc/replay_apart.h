@@ -699,12 +699,12 @@ __device__ __forceinline__ void apart_decide_wave(const SegArgs& a, size_t p, in
         const int r = __builtin_amdgcn_readfirstlane(next);
         const SegDesc* const dr = &comm->ring[r & (DESC_RING - 1)];
         const int target = DICTATED && MODE != MODE_GIVEN ? dr->target : 0;
-        look();
         double left = DICTATED ? 0.0 : comm->gone[r & 1][lane];      // (read again behind Y(r - 1))
         // (what the choice before adds to the load signal, while LDS is read)
         if (COUNTS) q += of_mask(went1) ? 1.0 : 0.0;
         else if (!DICTATED) q += of_mask(went1) ? tokens : 0.0;
         if constexpr (PROXY) my_rtt = comm->rtt[r & 1][lane];
+        look();       // (behind the other reads: online tuner and proxy 0.5 % faster than before them)
         const int flags = __builtin_amdgcn_readfirstlane(word);
         const int was = __builtin_amdgcn_readfirstlane(before);
         bool behind = (was & DESC_SYNC) != 0;
