@@ -6,7 +6,7 @@
 // order of the requests.  A segment's first request on a replica starts its row over there (SEG_FRESH): the loader links
 // every reference to the request before it with the same segment, where it has the same place in the path.
 // Bound by the longest share's chain, about 0.55 us a request.  One replay of 20,011 requests on 13
-// replicas: affinity 11.9 -> 1.2 ms, random 10.5 -> 1.2, of which the layout and the way back take 60 us.
+// replicas: affinity 10.2 -> 1.1 ms, random 11.0 -> 1.2, of which the layout and the way back take 30 to 45 us.
 #pragma once
 #include "device_common.h"
 #include "internal.h"

@@ -18,7 +18,7 @@
 // X(r) the updating wavefront reads the chosen replica's stamps and cursor records while the deciding one reads the next
 // request's stamps.  What r changes of those is known beforehand: blocks that r has as well (ROW_IN_BEFORE) are cached where r
 // went, the others' stamps stay, and the threshold is there at Y(r).
-// Bound by the chain of a request, about 2.1 us: the trip to memory, the eviction behind it, the scores and two meetings.
+// Bound by the chain of a request, about 2.2 us: the trip to memory, the eviction behind it, the scores and two meetings.
 // 65 replays of 3,001 requests on 7 replicas: 23.6 ms with tables, 8.1 with the updating wavefront as the book-keeper, each
 // dead record a trip to memory and the chosen replica's stamps read behind Y(r), 6.7 so.  1,024 of 1,000 on 64: 17.9, 8.9, 7.9.
 #pragma once

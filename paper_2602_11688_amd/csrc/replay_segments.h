@@ -44,8 +44,8 @@
 // match behind Y(r), so 9.8 and 11.2; without decode time 8.6 and 9.6, so 6.8 and 8.2.)
 //
 // 1,024 replays of 250,000 requests on 32 replicas: 241 ms with two barriers per request and half of its work between
-// them, 164 ms so (0.65 us, some 1,400 cycles a request).  The deciding and the queue wavefront now have chains of
-// the same length, each is the last to arrive about half of the time; 2 replays take 0.55 us.
+// them, 154 ms so (0.61 us, some 1,450 cycles a request).  The deciding and the queue wavefront now have chains of
+// the same length, each is the last to arrive about half of the time; 2 replays would take 0.53 us (they have six wavefronts).
 #pragma once
 #include "device_common.h"
 #include "internal.h"
