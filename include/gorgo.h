@@ -391,8 +391,8 @@ int gorgo_last_eval_kernel_ms(double* fill_ms, double* replay_ms, double* select
  * advances, 10 log records dropped because they own nothing, 11 ownership walks), [p][1] the queue wavefront (0 times
  * and lengths, 1 waiting at X, 2 retiring, 5 outputs and tuner, 6 batch turnover, 9 choice and service), [p][2] the
  * front-end wavefront (0 descriptors and row cells, 1 waiting) and the book-keeping wavefront (2 stores, 3 waiting at
- * X).  Where a replay has six wavefronts (launches of up to 512 replays, 768 with up to 12 replicas, but for caches of more than 32
- * replicas that hold fewer than 15 requests), the deciding one has no sections 2 and 4 to 6, [p][1] is the serving wavefront (without 2) and the retiring one (2 retiring, 3 waiting at X), and [p][2] also has the
+ * X).  Where a replay has six wavefronts (launches of up to 512 replays, 768 with up to 12 replicas, but for caches that hold fewer than
+ * 15 requests with more than 32 replicas, fewer than 10 with 24 or more), the deciding one has no sections 2 and 4 to 6, [p][1] is the serving wavefront (without 2) and the retiring one (2 retiring, 3 waiting at X), and [p][2] also has the
  * evicting one (4 cursors, 5 waiting at X).  Needs the segment formulation without packing; everything else as gorgo_eval_population. */
 #define GORGO_SECTIONS 12
 int gorgo_eval_population_sections(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* options, const double* rtt_ms,

@@ -459,17 +459,22 @@ int prepare(const Plan& pl, double* d_small, int32_t* last, int64_t rows, hipStr
 // for a workgroup of six takes the room of two on each: three up to 80 registers, two up to 128.  (The time doubles from 768
 // replays to 769, 2 replicas 6.5 / 11.6 ms, 32 6.0 / 10.6, and not where the kernel is kept to 64 registers; proxy, engine model
 // and tuner together take 85, 3,000 requests on 8 replicas: 512 replays 3.0 ms, 640 5.9, with four wavefronts 4.8.)
-// Nor where a cache of one of more than 32 replicas holds fewer requests than the look-ahead has records, `least` with
-// fixed weights and the linear model, somewhat more with session affinity: the deciding wavefront then waits for the evicting one at
+// Nor, with fixed weights or session affinity and the linear model, where the cache of one of 24 replicas or more holds about as few
+// requests as the look-ahead has records, `least` of them: the deciding wavefront then waits for the evicting one at
 // nearly every request.  (6,000 requests of 62 blocks, 300 replays.  48 replicas of 600 blocks 4.00 / 4.17, 800 3.97 / 4.01, 1,000 3.93
 // / 3.92, 1,600 3.89 / 3.79; 64 3.99 / 4.18, -, 3.93 / 3.89, 3.90 / 3.77; of 11 blocks, 48 replicas of 60 4.17 / 4.37, 100 4.10 / 4.18, 150 4.04
-// / 3.99.  Affinity, 48 of 600 3.88 / 4.09, 1,000 3.81 / 3.85, 1,600 3.77 / 3.75.  32 replicas of 600 3.75 / 3.81, 1,000 3.67 / 3.51.
+// / 3.99.  Affinity, 48 of 600 3.88 / 4.09, 1,000 3.81 / 3.85, 1,600 3.77 / 3.75.  32 of 250 3.97 / 4.23, 450 3.85 / 3.95, 600 3.78 / 3.81,
+// 750 3.73 / 3.68, affinity 3.89 / 4.19, 3.69 / 3.87, 3.64 / 3.72, 3.59 / 3.60; 24 4.05 / 4.22, 3.90 / 3.99, 3.84 / 3.84, 3.80 / 3.73, affinity 3.96 /
+// 4.20, 3.77 / 3.91, 3.72 / 3.79, 3.67 / 3.66; 16 of 250 4.31 / 4.22, affinity 4.33 / 4.28.
 // Least-request, random, tuner, engine and proxy, 48 and 64 of 600: six are the faster by 3 to 15 %.)
 constexpr int SPREAD_UP_TO = 512, SPREAD_FEW_REPLICAS = 12, SPREAD_FEW_UP_TO = 768;
-constexpr double SPREAD_LEAST_HELD = 15.0, SPREAD_LEAST_HELD_AFFINITY = 20.0;
+constexpr int SPREAD_WAITS_FROM = 24;       // replicas
+double spread_least_held(const Plan& pl, bool affinity) {
+    return pl.R < SPREAD_WAITS_FROM ? 0.0 : pl.R <= HALF ? (affinity ? 12.0 : 10.0) : affinity ? 20.0 : 15.0;
+}
 bool spread_replays(const Plan& pl, bool proxy, size_t lds, int held, double least) {
     if (pl.P > (pl.R <= SPREAD_FEW_REPLICAS ? SPREAD_FEW_UP_TO : SPREAD_UP_TO)) return false;
-    if (pl.R > HALF && pl.requests_held < least) return false;
+    if (pl.requests_held < least) return false;
     const size_t fixed = proxy ? sizeof(ApartHandover<true>) : sizeof(ApartHandover<false>);
     const size_t per_cu = (size_t)160 * 1024 / ((fixed + lds + 1279) / 1280 * 1280);        // (given out in pieces of 1,280 bytes)
     return pl.P <= 256 * std::min((int)per_cu, held);
@@ -481,9 +486,8 @@ template <int MODE>
 void launch_segments(bool engine, bool proxy, const Plan& pl, hipStream_t s, const SegArgs& a) {
     const size_t lds = replay_queue_lds_bytes(pl.R, pl.B, engine, a.window);
     const dim3 grid((unsigned)pl.P);
-    const double least = engine || proxy ? 0.0
-                         : MODE == MODE_COST_MODEL ? SPREAD_LEAST_HELD
-                         : MODE == MODE_AFFINITY ? SPREAD_LEAST_HELD_AFFINITY : 0.0;
+    const bool waits = (MODE == MODE_COST_MODEL || MODE == MODE_AFFINITY) && !engine && !proxy;
+    const double least = waits ? spread_least_held(pl, MODE == MODE_AFFINITY) : 0.0;
     if (spread_replays(pl, proxy, lds, MODE == MODE_ONLINE && engine && proxy ? 2 : 3, least)) {
         const dim3 block(APART_WAVES * WAVE);
         if constexpr (MODE == MODE_COST_MODEL || MODE == MODE_ONLINE) {
@@ -677,7 +681,7 @@ int launch_replay(const gorgo_trace* t, const Plan& pl, const double* d_rtt, con
             } else if (mode == MODE_COST_MODEL && !engine && !proxy && !sections && pack_replays(pl, a.nseg)) {
                 hipLaunchKernelGGL((replay_segments_kernel<MODE_COST_MODEL, false, false, 2>), dim3((unsigned)(pl.P / 2)),
                                    dim3(seg_threads<2>()), 2 * replay_queue_lds_bytes(pl.R, pl.B, false, 0), s, a);
-            } else if (sections && spread_replays(pl, false, replay_queue_lds_bytes(pl.R, pl.B, false, 0), 3, SPREAD_LEAST_HELD)) {
+            } else if (sections && spread_replays(pl, false, replay_queue_lds_bytes(pl.R, pl.B, false, 0), 3, spread_least_held(pl, false))) {
                 hipLaunchKernelGGL((replay_apart_kernel<MODE_COST_MODEL, false, false, true>), dim3((unsigned)pl.P),
                                    dim3(APART_WAVES * WAVE), replay_queue_lds_bytes(pl.R, pl.B, false, 0), s, a);
             } else if (sections) {

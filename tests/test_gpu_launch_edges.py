@@ -84,7 +84,7 @@ def wavefronts(handle, model, rtt, P):
 
 
 @pytest.mark.parametrize("R,B,P,held,want", [(12, 2, 768, 0, 6), (12, 2, 769, 0, 4), (13, 2, 512, 0, 6), (13, 2, 513, 0, 4),
-                                             (32, 2, 300, 5, 6), (33, 2, 300, 14.9, 4), (33, 2, 300, 15.1, 6), (64, 2, 2, 5, 4),
+                                             (23, 2, 300, 5, 6), (24, 2, 300, 9.9, 4), (32, 2, 300, 10.1, 6), (33, 2, 300, 14.9, 4), (33, 2, 300, 15.1, 6), (64, 2, 2, 5, 4),
                                              (64, 16, 512, 0, 6), (12, 64, 768, 0, 6)])
 def test_which_launches_have_six_wavefronts(R, B, P, held, want):
     """The number of replays, of replicas, and of requests that a cache holds; many slots (fixed weights fit all the same)."""
@@ -96,7 +96,7 @@ def test_which_launches_have_six_wavefronts(R, B, P, held, want):
     assert wavefronts(load(wl.trace), g.Model(R, B, cache, 0.05, 20.0), np.linspace(5.0, 90.0, R), P) == want
 
 
-@pytest.mark.parametrize("R,held", [(32, 12), (33, 12), (64, 14), (64, 24), (40, 26)])
+@pytest.mark.parametrize("R,held", [(23, 5), (24, 8), (32, 11), (32, 13), (33, 12), (64, 14), (64, 24)])
 def test_caches_of_few_requests(R, held):
     """On both sides of the rule for caches that hold few requests, the policies it concerns and one that it does not."""
     tr = tg.random_forest(R + held, 1500, roots=5, max_blocks=30, grow=3, gap_ms=30, keep=0.8)
