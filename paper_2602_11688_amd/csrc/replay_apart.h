@@ -393,7 +393,7 @@ __device__ __forceinline__ void apart_book_wave(const SegArgs& a, size_t p, int 
     const int reset_rep = lane - 32 < R ? lane - 32 : R - 1;
     int tail_r = -1;                          // youngest request routed to replica = lane
     int o_route = 0, o_hit = 0, o_seen = 0;
-    int touched = 0;
+    Touched<1> touched;
     const bool wide = (row_bytes & 127u) != 0 || row_bytes > 128u;      // (rows that straddle a cache line, or are longer)
     const int64_t refs = a.seg_off[N];
     // (a lane per array; a group of eight requests is 32 or 64 bytes of each; one reference behind the last is there to be read)
@@ -411,7 +411,8 @@ __device__ __forceinline__ void apart_book_wave(const SegArgs& a, size_t p, int 
     static_assert(sizeof(SegRef) == 8);
     auto touch_trace = [&](int x, int64_t j0) {
         const int64_t j = j0 + (lane - 4) * 16, k = lane >= 5 && lane < 21 ? (j < refs ? j : refs) : x < N ? x : N - 1;
-        return ld(reinterpret_cast<const int32_t*>(my_array + ((uint64_t)k << log_size)));
+        // (a load from global memory: a flat one counts as an access to LDS as well, and the next meeting would wait for it)
+        return ld(reinterpret_cast<const __attribute__((address_space(1))) int32_t*>(my_array + ((uint64_t)k << log_size)));
     };
     meet(true);                               // the first descriptors are there
     meet(true);
@@ -464,12 +465,11 @@ __device__ __forceinline__ void apart_book_wave(const SegArgs& a, size_t p, int 
         tail_r = is_best ? r : tail_r;
         if ((r & (DESC_GROUP - 1)) == 3) {
             // (the rows of the eight requests from the next multiple of eight on: their descriptors are there but for the last words)
-            asm volatile("" ::"v"(touched));
+            touched.done();
             const SegDesc& x = comm->ring[((r & ~(DESC_GROUP - 1)) + DESC_AHEAD + lane / SEG_CHUNK) & (DESC_RING - 1)];
             const uint32_t off = x.rowoff[lane % SEG_CHUNK];
-            touched = ld(reinterpret_cast<const int32_t*>(rows + off));
-            if (wide) touched ^= ld(reinterpret_cast<const int32_t*>(rows + (off + row_bytes - 4u)));
-            touched ^= touch_trace(r + 5 * DESC_GROUP, d->j0);
+            touched.rows(rows, off, wide ? row_bytes - 4u : 0u, 0u);
+            touched.also = touch_trace(r + 5 * DESC_GROUP, d->j0);
         }
         const int slot = r & (WAVE - 1);
         const bool mine = lane == slot;
@@ -492,7 +492,7 @@ __device__ __forceinline__ void apart_book_wave(const SegArgs& a, size_t p, int 
         }
         if (flags & DESC_SYNC) meet(false);                          // Y(r)
     }
-    asm volatile("" ::"v"(touched));
+    touched.done();
     if (TIMED && a.sections && lane == 0) {
         a.sections[(p * 3 + 2) * SECTIONS + 2] = clk.acc[2];
         a.sections[(p * 3 + 2) * SECTIONS + 3] = clk.acc[3];
