@@ -898,6 +898,16 @@ __device__ __forceinline__ void apart_decide_wave(const SegArgs& a, size_t p, in
         for (int k = 0; k < 8; ++k) a.sections[p * 3 * SECTIONS + k] = clk.acc[k];
 }
 
+// What the wavefronts of a workgroup do.  The one with number w runs on the same SIMD as those with w + 4, so which two share one is
+// a matter of this order; the longest chains go with the shortest.  (With decide, serve, retire, book, evict, front -- deciding and
+// evicting on one SIMD -- 64 replays of 6,000 requests on 32 replicas of 4,000 blocks took 0.495 us a request, so 0.485, proxy
+// 0.656 / 0.591; 512 of them 0.547 / 0.523, proxy 0.717 / 0.679, engine model 0.681 / 0.631.)
+enum ApartRole { DECIDE, SERVE, RETIRE, BOOK, EVICT, FRONT };
+__device__ __forceinline__ int apart_role(int wave) {
+    constexpr unsigned ROLES = DECIDE | SERVE << 4 | EVICT << 8 | RETIRE << 12 | BOOK << 16 | FRONT << 20;
+    return (int)(ROLES >> (4 * wave)) & 15;
+}
+
 // Replay p by one workgroup.  Three fit a CU by their registers, two in the proxy variant with engine model and tuner; LDS may
 // allow fewer (30,592 bytes of hand-over words in the proxy variants and 53,248 of slots and window make 84 KB: one).  The launch
 // rule counts both.
@@ -905,29 +915,29 @@ template <int MODE, bool ENGINE, bool PROXY, bool TIMED>
 __device__ __forceinline__ void apart_replay(const SegArgs& a, size_t p, unsigned char* lds_raw) {
     __shared__ ApartHandover<PROXY> comm;
     const int lane = threadIdx.x & (WAVE - 1);
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+    const int role = apart_role(__builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE)));
     double* const window = reinterpret_cast<double*>(lds_raw + SlotQueues::bytes(a.R, a.B, ENGINE));
     if (a.N == 0) {           // (an empty trace still reports the tuner's initial state)
-        if (wave == 1) Tuner<MODE == MODE_ONLINE>(a, p, window, lane).results();
+        if (role == SERVE) Tuner<MODE == MODE_ONLINE>(a, p, window, lane).results();
         return;
     }
-    if (wave == 0) {
+    if (role == DECIDE) {
         __builtin_amdgcn_s_setprio(3);      // the wavefront on the chain goes first at issue
         apart_decide_wave<MODE, ENGINE, PROXY, TIMED>(a, p, lane, &comm);
-    } else if (wave == 1) {
+    } else if (role == SERVE) {
         __builtin_amdgcn_s_setprio(2);
         SlotQueues Q;
         Q.init(lds_raw, a.R, a.B, ENGINE, lane);
         apart_serve_wave<MODE, ENGINE, PROXY, TIMED>(a, p, lane, Q, window, &comm);
-    } else if (wave == 2) {
+    } else if (role == RETIRE) {
         __builtin_amdgcn_s_setprio(2);
         SlotQueues Q;
         Q.attach(lds_raw, a.R, a.B);
         apart_retire_wave<PROXY, TIMED>(a, p, lane, Q, &comm);
-    } else if (wave == 3) {
+    } else if (role == BOOK) {
         __builtin_amdgcn_s_setprio(1);
         apart_book_wave<PROXY, TIMED>(a, p, lane, &comm);
-    } else if (wave == 4) {
+    } else if (role == EVICT) {
         __builtin_amdgcn_s_setprio(2);
         apart_evict_wave<PROXY, TIMED>(a, p, lane, &comm);
     } else {
