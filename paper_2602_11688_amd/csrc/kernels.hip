@@ -513,6 +513,16 @@ void launch_segments(bool engine, bool proxy, const Plan& pl, hipStream_t s, con
     else hipLaunchKernelGGL((replay_segments_kernel<MODE, false, false>), grid, block, lds, s, a);
 }
 
+// Log records of look-ahead per replica with six wavefronts, of the fifteen there is room for.  The deciding wavefront waits for the
+// evicting one when it matches blocks of a record in the look-ahead, so a long one is waited for often where a cache holds few
+// requests, and a short one runs dry.  (us per request, 64 replays on 32 replicas, 5 / 6 / 8 / 11 / 15 records.  Caches of 700 blocks, 11
+// requests: 0.522 / 0.520 / 0.531 / 0.554 / 0.586, proxy 0.769 / 0.745 / 0.741 / 0.759 / 0.794; 1,500: 0.493 / 0.490 / 0.491 / 0.497 /
+// 0.510, proxy 0.752 / 0.730 / 0.706 / 0.706 / 0.715; 3,000, 48 requests: 0.480 / 0.484 / 0.486 / 0.483 / 0.487, proxy 0.712 / 0.685 /
+// 0.672 / 0.668 / 0.670.  Three replicas, 700: 0.583 / 0.579 / 0.580 / 0.582 / 0.587; 3,000: 0.554 / 0.547 / 0.542 / 0.539 / 0.537.)
+constexpr double LOOK_FEW_HELD = 40.0;       // requests
+int32_t apart_look(const Plan& pl, bool proxy) { return pl.requests_held < LOOK_FEW_HELD ? (proxy ? 8 : 6) : 11; }
+static_assert(APART_LOOK > 11);
+
 // Dictated routes: the shares laid out, a replay per share, the outputs back in their order.
 int launch_each(const gorgo_trace* t, const Plan& pl, int mode, bool engine, const SegArgs& a, char* ws, hipStream_t s) {
     const size_t P = (size_t)pl.P, N = (size_t)pl.N, R = (size_t)pl.R;
@@ -619,6 +629,7 @@ int launch_replay(const gorgo_trace* t, const Plan& pl, const double* d_rtt, con
     a.C = pl.C;
     a.nseg = pl.nseg + 2;             // rows of one replay: one per segment, one that no request touches, a spare
     a.block_tokens = pl.block_tokens;
+    a.look = apart_look(pl, proxy != nullptr);
     a.a_pf = pl.a_pf;
     a.a_dec = pl.a_dec;
     a.least_dec = engine ? engine->least_dec : pl.a_dec;

@@ -76,6 +76,7 @@ struct ApartCursor {
     unsigned long long raw = 0;          // the record asked for
     unsigned long long* ring = nullptr;  // records packed as r | own << 32 | n << 48, ring_cnt of them from slot ring_head on
     int ring_head = 0, ring_cnt = 0, ring_hi = -1, stock = 0;        // the youngest; blocks they own
+    int most = APART_LOOK - 1;           // records that the ring is filled up to
     unsigned long long next = ~0ull;     // the record at ring_head, read at the end of the request before
     int over = 0;                        // blocks this LRU holds beyond its capacity (below 0: room)
     int n_spot = 0, n_adv = 0, n_dead = 0;       // statistics of the timed instantiation
@@ -113,7 +114,7 @@ struct ApartCursor {
     // Asks for the next record of the log where the ring has room for it (`spare`, the record behind the log, where
     // there is nothing to fetch).  Called when nothing is pending.
     __device__ __forceinline__ void ask(const unsigned long long* log64, int spare, const LogChange& f) {
-        const bool want = fill_r >= 0 && fill_r != f.r && ring_cnt < APART_LOOK - 1;
+        const bool want = fill_r >= 0 && fill_r != f.r && ring_cnt < most;
         expect(want, f);
         raw = ld(&log64[want ? fill_r : spare]);
     }
@@ -236,6 +237,7 @@ __device__ __forceinline__ void apart_evict_wave(const SegArgs& a, size_t p, int
         c2.init(comm->look[PROXY ? 1 : 0], lane);
         c2.over = forgets ? -index_cap : -INT32_MAX;
     }
+    c1.most = c2.most = a.look;
     const int every = look_every(R);
     int n_walks = 0;
     // (the deciding wavefront may look in between: `hi` is written first and read last.  LDS performs a wavefront's accesses in their

@@ -72,6 +72,7 @@ struct SegArgs {
     int64_t C;
     int64_t nseg;
     int32_t block_tokens;
+    int32_t look;                 // six wavefronts: log records of look-ahead per replica
     double a_pf, a_dec;
     double least_dec;             // smallest decode time per output token of any replica
     const double* rtt;
