@@ -29,6 +29,15 @@ __device__ __forceinline__ void st(T* p, T v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
+// The kernel's (first) argument, as one of a workgroup's roles reads it: taken as it stands the compiler loads what any role needs
+// before it branches to them, and with that many scalars keeps some in lanes of a vector register, to be read back in the loops.
+template <class T>
+__device__ __forceinline__ const T& kernel_args() {
+    auto k = __builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(k));
+    return *(const T*)k;
+}
+
 __device__ __forceinline__ double readlane_f64(double v, int src) {
     const long long b = __double_as_longlong(v);
     const int lo = __builtin_amdgcn_readlane((int)b, src);

@@ -480,6 +480,32 @@ bool spread_replays(const Plan& pl, bool proxy, size_t lds, int held, double lea
     return pl.P <= 256 * std::min((int)per_cu, held);
 }
 
+// Whether the pairs of a launch, eight wavefronts each, are all resident: two workgroups for each of the 256 CUs, fewer where their
+// service slots' LDS, `lds` bytes of a pair, does not leave the room.  (By registers four wavefronts fit a SIMD up to 128.)
+bool pairs_resident(const Plan& pl, bool proxy, size_t lds, int64_t rows) {
+    if (pl.packing == 0 || pl.R > HALF || 2ull * (uint64_t)rows * (uint64_t)pl.R * 4u >= (1ull << 32)) return false;
+    const size_t fixed = proxy ? sizeof(ApartHandover<true, 2>) : sizeof(ApartHandover<false, 2>);
+    const size_t per_cu = (size_t)160 * 1024 / ((fixed + lds + 1279) / 1280 * 1280);
+    return (pl.P + 1) / 2 <= 256 * std::min((int)per_cu, 2);
+}
+// Whether they take the launch: it has too many replays for six wavefronts each, or more than one for each CU in the variants whose
+// serving or deciding wavefront has so much to do that it does better alone on its SIMD; and the caches hold enough requests, for two
+// replays wait twice as often for the evicting wavefront.  (us per request.  1,000 replays, four wavefronts each / pairs of eight, caches of
+// 8,000 blocks, 130 requests: 2 replicas 0.844 / 0.671, tuner 0.955 / 0.727, engine model 1.075 / 0.867, proxy 1.338 / 0.988; 16 0.676 / 0.607,
+// 0.787 / 0.676, 0.940 / 0.796, 0.862 / 0.787; 32 0.606 / 0.574, 0.709 / 0.647, 0.806 / 0.690, 0.739 / 0.684.  Caches of 400, 560, 700,
+// 900 and 1,200 blocks, 6.5, 9, 11, 14.5 and 19 requests: 16 replicas 0.738 / 0.782, 0.737 / 0.721, 0.724 / 0.691, 0.712 / 0.669, 0.713 / 0.648;
+// 32 0.677 / 0.757, 0.669 / 0.696, 0.658 / 0.664, 0.655 / 0.638, 0.652 / 0.620; tuner, 32 0.774 / 0.810, 0.760 / 0.751, 0.753 / 0.725, -, -;
+// engine model, 32 0.823 / 0.798 and, of 260 blocks, 0.831 / 0.858; proxy, 16 1.046 / 1.102, 0.995 / 1.002, 0.972 / 0.966, -, -; 32 -, 0.876 /
+// 0.956, 0.858 / 0.907, 0.845 / 0.866, 0.836 / 0.838.  401 replays, six each / pairs, 4,000 blocks: engine model, 16 replicas 0.714 / 0.700, 24 0.675 /
+// 0.657, 32 0.655 / 0.595; proxy, 16 0.763 / 0.717, 24 0.720 / 0.666, 32 0.706 / 0.642, and 12 0.822 / 0.842; the others within 1 %.)
+bool pair_replays(const Plan& pl, int mode, bool engine, bool proxy) {
+    if (pl.packing == 1) return true;
+    const bool few = pl.R <= 16;         // replicas
+    if (pl.requests_held < (proxy ? (few ? 10.0 : 20.0) : engine ? 6.0 : mode == MODE_ONLINE ? 8.0 : few ? 9.0 : 12.0)) return false;
+    if (pl.P > (pl.R <= SPREAD_FEW_REPLICAS ? SPREAD_FEW_UP_TO : SPREAD_UP_TO)) return true;
+    return (engine || proxy) && pl.R >= 16 && pl.P > 256 && pl.requests_held >= (engine ? 12.0 : 30.0);
+}
+
 // The segment-row kernels' instantiations: every mode with either replica model; imperfect proxy knowledge concerns the
 // cost model (fixed weights or tuned online) only.
 template <int MODE>
@@ -488,7 +514,9 @@ void launch_segments(bool engine, bool proxy, const Plan& pl, hipStream_t s, con
     const dim3 grid((unsigned)pl.P);
     const bool waits = (MODE == MODE_COST_MODEL || MODE == MODE_AFFINITY) && !engine && !proxy;
     const double least = waits ? spread_least_held(pl, MODE == MODE_AFFINITY) : 0.0;
-    if (spread_replays(pl, proxy, lds, MODE == MODE_ONLINE && engine && proxy ? 2 : 3, least)) {
+    constexpr bool PAIRS = MODE == MODE_COST_MODEL || MODE == MODE_ONLINE || MODE == MODE_LEAST_REQUEST;
+    const bool pairs = PAIRS && pairs_resident(pl, proxy, 2 * lds, a.nseg) && pair_replays(pl, MODE, engine, proxy);
+    if (!pairs && spread_replays(pl, proxy, lds, MODE == MODE_ONLINE && engine && proxy ? 2 : 3, least)) {
         const dim3 block(APART_WAVES * WAVE);
         if constexpr (MODE == MODE_COST_MODEL || MODE == MODE_ONLINE) {
             if (proxy) {
@@ -500,6 +528,21 @@ void launch_segments(bool engine, bool proxy, const Plan& pl, hipStream_t s, con
         if (engine) hipLaunchKernelGGL((replay_apart_kernel<MODE, true, false>), grid, block, lds, s, a);
         else hipLaunchKernelGGL((replay_apart_kernel<MODE, false, false>), grid, block, lds, s, a);
         return;
+    }
+    if constexpr (PAIRS) {
+        if (pairs) {
+            const dim3 grid2((unsigned)((pl.P + 1) / 2)), block(apart_threads<2>());
+            if constexpr (MODE != MODE_LEAST_REQUEST) {
+                if (proxy) {
+                    if (engine) hipLaunchKernelGGL((replay_apart_pairs_kernel<MODE, true, true>), grid2, block, 2 * lds, s, a);
+                    else hipLaunchKernelGGL((replay_apart_pairs_kernel<MODE, false, true>), grid2, block, 2 * lds, s, a);
+                    return;
+                }
+            }
+            if (engine) hipLaunchKernelGGL((replay_apart_pairs_kernel<MODE, true, false>), grid2, block, 2 * lds, s, a);
+            else hipLaunchKernelGGL((replay_apart_pairs_kernel<MODE, false, false>), grid2, block, 2 * lds, s, a);
+            return;
+        }
     }
     const dim3 block(seg_threads<1>());
     if constexpr (MODE == MODE_COST_MODEL || MODE == MODE_ONLINE) {
@@ -513,7 +556,7 @@ void launch_segments(bool engine, bool proxy, const Plan& pl, hipStream_t s, con
     else hipLaunchKernelGGL((replay_segments_kernel<MODE, false, false>), grid, block, lds, s, a);
 }
 
-// Log records of look-ahead per replica with six wavefronts, of the fifteen there is room for.  The deciding wavefront waits for the
+// Log records of look-ahead per replica with six and eight wavefronts, of the fifteen there is room for.  The deciding wavefront waits for the
 // evicting one when it matches blocks of a record in the look-ahead, so a long one is waited for often where a cache holds few
 // requests, and a short one runs dry.  (us per request, 64 replays on 32 replicas, 5 / 6 / 8 / 11 / 15 records.  Caches of 700 blocks, 11
 // requests: 0.522 / 0.520 / 0.531 / 0.554 / 0.586, proxy 0.769 / 0.745 / 0.741 / 0.759 / 0.794; 1,500: 0.493 / 0.490 / 0.491 / 0.497 /
@@ -624,6 +667,7 @@ int launch_replay(const gorgo_trace* t, const Plan& pl, const double* d_rtt, con
     a.seg = segments ? t->dev.seg : nullptr;
     a.blk_off = t->dev.blk_off;
     a.N = pl.N;
+    a.P = pl.P;
     a.R = pl.R;
     a.B = pl.B;
     a.C = pl.C;

@@ -35,13 +35,13 @@ struct Served {
     int32_t at;          // service slot, -1: it has completed already
     int32_t weight;      // what it takes from the load signal
 };
-template <bool PROXY>
+template <bool PROXY, int PACK = 1>
 struct ApartHandover : QueueHandover<PROXY> {
     static constexpr bool APART = true;
     int32_t cells[CELL_SETS][SEG_CHUNK][WAVE];    // [request mod 3]: row cells of the request's first eight segments per replica
     unsigned long long look[PROXY ? 2 : 1][APART_LOOK * WAVE];       // rings of the cursors (one slot is always free)
     SegDesc ring[DESC_RING];
-    Served served[2];                     // [request mod 2]
+    Served served[PACK][2];               // [replay of the workgroup][request mod 2]
     // Where the eviction cursors are, per replica.
     int32_t cur_r[PROXY ? 2 : 1][WAVE];   // request
     uint32_t k_room[WAVE];                // the cache's cursor's position | room << 16
@@ -56,6 +56,25 @@ struct ApartHandover : QueueHandover<PROXY> {
     int32_t evicted;                      // the cursors are up to date with the requests up to this one
     int32_t walked;                       // a request whose previous owners have been looked up
 };
+
+// The replays of a workgroup: one, or two neighbouring ones, lanes 0..31 and 32..63 of the wavefronts that they share.  The last
+// workgroup of an odd number has nothing for its upper half: a replay that is not there reads what belongs to the lower one,
+// writes nothing but the spare row and log record, and goes nowhere.
+template <int PACK>
+struct Pair {
+    bool upper;          // this lane's replay is the second one
+    bool there;          // ... and there is one
+    int rl;              // lane within the replay
+    size_t p0, p;        // the workgroup's first replay; this lane's
+    __device__ __forceinline__ Pair(const SegArgs& a, size_t first, int lane)
+        : upper(PACK == 2 && lane >= HALF), there(!upper || first + 1 < (size_t)a.P), rl(PACK == 2 ? lane & (HALF - 1) : lane), p0(first),
+          p(first + (upper && there ? 1 : 0)) {}
+};
+// Replay `which` of a workgroup whose first is p0, for the wavefronts that have one replay each.
+template <int PACK>
+__device__ __forceinline__ bool pair_has(const SegArgs& a, size_t p0, int which) {
+    return PACK == 1 || which == 0 || p0 + 1 < (size_t)a.P;
+}
 
 // The compiler moves no access to memory across this.
 __device__ __forceinline__ void in_order() { __atomic_signal_fence(__ATOMIC_SEQ_CST); }
@@ -218,13 +237,13 @@ struct ApartCursor {
     }
 };
 
-template <bool PROXY, bool TIMED, class Comm>
-__device__ __forceinline__ void apart_evict_wave(const SegArgs& a, size_t p, int lane, Comm* comm) {
+template <bool PROXY, int PACK, bool TIMED, class Comm>
+__device__ __forceinline__ void apart_evict_wave(const SegArgs& a, size_t p0, int lane, Comm* comm) {
     const int R = a.R, N = (int)a.N;
+    const Pair<PACK> mine(a, p0, lane);
     const unsigned row_bytes = (unsigned)R * 4u;
     const unsigned spare_row = (unsigned)(a.nseg - 1) * row_bytes;
-    const char* const rows = reinterpret_cast<const char*>(a.last + p * (size_t)a.nseg * R);
-    LogRec* const log = a.log + p * ((size_t)N + 1);
+    LogRec* const log = a.log + mine.p * ((size_t)N + 1);
     const unsigned long long* const log64 = reinterpret_cast<const unsigned long long*>(log);
     const int spare = N;                      // the log record behind the last request's
     int tail_r = -1;                          // youngest request routed to replica = lane
@@ -267,27 +286,32 @@ __device__ __forceinline__ void apart_evict_wave(const SegArgs& a, size_t p, int
         clk.tick(4);                                                 // cursors
         meet(true);                                                  // X(r)
         clk.tick(5);                                                 // waiting at X
-        const int best = __builtin_amdgcn_readfirstlane(comm->best[r & 1][0]);
+        const int best = PACK == 1 ? __builtin_amdgcn_readfirstlane(comm->best[r & 1][0]) : comm->best[r & 1][mine.upper ? 1 : 0];
         const Choice<PROXY> c = comm->choice[r & 1][lane];           // (of this lane's replica: no second trip to LDS)
-        const bool is_best = lane == best;
+        const bool is_best = lane == best && mine.there;
         int owner = is_best ? c.owner : spare;
         const int end = (int)(c.hit_end >> 16);
-        if (__builtin_expect(ballot(owner == OWN_WALK) != 0, 0)) {
+        for (unsigned long long walks = ballot(owner == OWN_WALK); __builtin_expect(walks != 0, 0); walks &= walks - 1) {
             // The segments that this request takes over on the chosen replica have several previous owners: along the path
             // these form runs; each run moves its owner's `own` to the end of the run.  Only what is held matters (what is
             // evicted belongs to requests the cursor has passed, or to the cursor's request beyond its position).  The rows are
             // read as they still are: the book-keeping wavefront waits.
             ++n_walks;
-            const int cb_r = __builtin_amdgcn_readlane(PROXY ? c2.cur_r : c1.cur_r, best);
-            const int cb_k = __builtin_amdgcn_readlane(PROXY ? c2.cur_k : c1.cur_k, best);
+            const int of_lane = __builtin_ctzll(walks);                  // (of either replay)
+            const bool second = PACK == 2 && of_lane >= HALF;
+            const size_t its_p = p0 + (second ? 1 : 0);
+            LogRec* const its_log = a.log + its_p * ((size_t)N + 1);
+            const char* const cells = reinterpret_cast<const char*>(a.last + its_p * (size_t)a.nseg * R) + (second ? of_lane - HALF : of_lane) * 4;
+            const int cb_r = __builtin_amdgcn_readlane(PROXY ? c2.cur_r : c1.cur_r, of_lane);
+            const int cb_k = __builtin_amdgcn_readlane(PROXY ? c2.cur_k : c1.cur_k, of_lane);
             int run_owner = -1, run_end = 0, vpos = 0;
             bool walking = true;
             auto changed = [&](int of, int to) {
-                st(&log[of].own, (uint16_t)to);
-                const int its = is_best ? of : spare;
-                if (ballot(c1.disowned(its, to)) != 0) c1.disowned_in_ring(best, of, to, lane);
+                st(&its_log[of].own, (uint16_t)to);
+                const int its = lane == of_lane ? of : spare;
+                if (ballot(c1.disowned(its, to)) != 0) c1.disowned_in_ring(of_lane, of, to, lane);
                 if (PROXY) {
-                    if (ballot(c2.disowned(its, to)) != 0) c2.disowned_in_ring(best, of, to, lane);
+                    if (ballot(c2.disowned(its, to)) != 0) c2.disowned_in_ring(of_lane, of, to, lane);
                 }
             };
             // (lane = segment: one load for the references, one for the cells)
@@ -295,8 +319,7 @@ __device__ __forceinline__ void apart_evict_wave(const SegArgs& a, size_t p, int
             for (int j = 0; j < s && walking; j += WAVE) {
                 const SegRef sr = a.seg[j0 + (j + lane < s ? j + lane : s - 1)];
                 const bool fresh = (sr.end & SEG_FRESH) != 0;
-                const int32_t cell = ld(reinterpret_cast<const int32_t*>(rows + (fresh ? spare_row : (uint32_t)sr.id * row_bytes) +
-                                                                         (unsigned)best * 4u));
+                const int32_t cell = ld(reinterpret_cast<const int32_t*>(cells + (fresh ? spare_row : (uint32_t)sr.id * row_bytes)));
                 const int my_at = fresh ? NEVER_CACHED : cell, my_to = sr.end & SEG_END_MASK;
                 for (int k = 0; k < WAVE && j + k < s && walking; ++k) {
                     const int at = __builtin_amdgcn_readlane(my_at, k), to = __builtin_amdgcn_readlane(my_to, k);
@@ -311,9 +334,10 @@ __device__ __forceinline__ void apart_evict_wave(const SegArgs& a, size_t p, int
                 }
             }
             if (run_owner >= 0) changed(run_owner, run_end);
-            owner = owner == OWN_WALK ? spare : owner;
+            owner = lane == of_lane ? spare : owner;
             c1.look_ahead();
             if (PROXY) c2.look_ahead();
+            if (PACK == 2 && (walks & (walks - 1)) != 0) continue;
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             st(&comm->walked, (int32_t)r);
         }
@@ -326,11 +350,15 @@ __device__ __forceinline__ void apart_evict_wave(const SegArgs& a, size_t p, int
                 c2.append(is_best, f);
                 in_ring2 = c2.disowned(owner, end);
             }
-            if (__builtin_expect(ballot(in_ring || in_ring2) != 0, 0)) {
-                const int of = __builtin_amdgcn_readlane(owner, best), to = __builtin_amdgcn_readlane(end, best);
-                if (ballot(in_ring) != 0) c1.disowned_in_ring(best, of, to, lane);
-                if (PROXY) {
-                    if (ballot(in_ring2) != 0) c2.disowned_in_ring(best, of, to, lane);
+            const unsigned long long rings = ballot(in_ring || in_ring2);
+            if (__builtin_expect(rings != 0, 0)) {
+                for (unsigned long long left = rings; left != 0; left &= left - 1) {         // (one of either replay)
+                    const int x = __builtin_ctzll(left);
+                    const int of = __builtin_amdgcn_readlane(owner, x), to = __builtin_amdgcn_readlane(end, x);
+                    if ((ballot(in_ring) >> x & 1) != 0) c1.disowned_in_ring(x, of, to, lane);
+                    if (PROXY) {
+                        if ((ballot(in_ring2) >> x & 1) != 0) c2.disowned_in_ring(x, of, to, lane);
+                    }
                 }
                 c1.look_ahead();
                 if (PROXY) c2.look_ahead();
@@ -363,7 +391,7 @@ __device__ __forceinline__ void apart_evict_wave(const SegArgs& a, size_t p, int
         const unsigned spot = wave_sum_u32((unsigned)c1.n_spot), adv = wave_sum_u32((unsigned)c1.n_adv),
                        dead = wave_sum_u32((unsigned)c1.n_dead);
         if (lane == 0) {
-            unsigned long long* const out = a.sections + p * 3 * SECTIONS;
+            unsigned long long* const out = a.sections + p0 * 3 * SECTIONS;
             out[2 * SECTIONS + 4] = clk.acc[4];
             out[2 * SECTIONS + 5] = clk.acc[5];
             out[8] = spot;
@@ -377,25 +405,29 @@ __device__ __forceinline__ void apart_evict_wave(const SegArgs& a, size_t p, int
 // ---------------------------------------------------------------------------------------------- book-keeping
 // As book_wave of replay_segments.h; also touches, eight requests at a time, the rows and the lines of the trace that the front
 // end is going to read.  (Loads whose values only keep them: this wavefront waits for none.)
-template <bool PROXY, bool TIMED, class Comm>
-__device__ __forceinline__ void apart_book_wave(const SegArgs& a, size_t p, int lane, Comm* comm) {
+template <bool PROXY, int PACK, bool TIMED, class Comm>
+__device__ __forceinline__ void apart_book_wave(const SegArgs& a, size_t p0, int lane, Comm* comm) {
     const int R = a.R, N = (int)a.N;
-    const bool in = lane < R;
+    const Pair<PACK> pair(a, p0, lane);
+    const bool in = pair.rl < R && pair.there;
     const unsigned row_bytes = (unsigned)R * 4u;
     const unsigned spare_row = (unsigned)(a.nseg - 1) * row_bytes;
-    char* const rows = reinterpret_cast<char*>(a.last + p * (size_t)a.nseg * R);
+    const unsigned other_replay = PACK == 2 && pair_has<PACK>(a, p0, 1) ? (unsigned)a.nseg * row_bytes : 0u;
+    const unsigned replay_off = pair.upper ? other_replay : 0u;
+    char* const rows = reinterpret_cast<char*>(a.last + p0 * (size_t)a.nseg * R);
     auto cell_of = [&](uint32_t rowoff, int replica) -> int32_t* {
-        return reinterpret_cast<int32_t*>(rows + (rowoff + (unsigned)replica * 4u));
+        return reinterpret_cast<int32_t*>(rows + (rowoff + replay_off + (unsigned)replica * 4u));
     };
-    auto cell_at = [&](uint32_t rowoff) -> int32_t* { return cell_of(rowoff, in ? lane : 0); };
-    LogRec* const log = a.log + p * ((size_t)N + 1);
+    auto cell_at = [&](uint32_t rowoff) -> int32_t* { return cell_of(rowoff, in ? pair.rl : 0); };
+    LogRec* const log = a.log + pair.p * ((size_t)N + 1);
     unsigned long long* const log64 = reinterpret_cast<unsigned long long*>(log);
-    // the lanes that reset the row of a fresh last segment, and the replica of each
-    const bool reset_lane = R <= 32 && lane >= 32;
+    // the lanes that reset the row of a fresh last segment, and the replica of each (two replays: a store of its own)
+    const bool reset_lane = PACK == 1 && R <= 32 && lane >= 32;
     const int reset_rep = lane - 32 < R ? lane - 32 : R - 1;
     int tail_r = -1;                          // youngest request routed to replica = lane
     int o_route = 0, o_hit = 0, o_seen = 0;
-    Touched<1> touched;
+    Touched<PACK> touched;
+    constexpr int BATCH = WAVE / PACK;
     const bool wide = (row_bytes & 127u) != 0 || row_bytes > 128u;      // (rows that straddle a cache line, or are longer)
     const int64_t refs = a.seg_off[N];
     // (a lane per array; a group of eight requests is 32 or 64 bytes of each; one reference behind the last is there to be read)
@@ -422,14 +454,15 @@ __device__ __forceinline__ void apart_book_wave(const SegArgs& a, size_t p, int 
     clk.start();
     for (int r = 0; r < N; ++r) {
         const SegDesc* const d = &comm->ring[r & (DESC_RING - 1)];
-        const uint32_t of_seg = d->slot[lane & (SEG_CHUNK - 1)], of_tail = d->tail;
+        const uint32_t of_seg = PACK == 1 || pair.there ? d->slot[lane & (SEG_CHUNK - 1)] : spare_row, of_tail = d->tail;
         const int n = d->n, s = __builtin_amdgcn_readfirstlane(d->s), flags = __builtin_amdgcn_readfirstlane(d->flags);
         clk.tick(2);                                                 // stores
         meet(true);                                                  // X(r)
         clk.tick(3);                                                 // waiting at X
-        const int best = comm->best[r & 1][0];
+        const int lane_best = comm->best[r & 1][pair.upper ? 1 : 0];
         const Choice<PROXY> c = comm->choice[r & 1][lane];           // (of this lane's replica: no second trip to LDS)
-        const bool is_best = lane == best;
+        const int best = PACK == 2 ? lane_best & (HALF - 1) : lane_best;
+        const bool is_best = lane == lane_best && pair.there;
         // (several previous owners: the evicting wavefront looks them up in the rows as they still are, and stores the changes)
         if (__builtin_expect(ballot(is_best && c.owner == OWN_WALK) != 0, 0))
             while (ld(&comm->walked) < r) __builtin_amdgcn_s_sleep(1);
@@ -440,6 +473,7 @@ __device__ __forceinline__ void apart_book_wave(const SegArgs& a, size_t p, int 
             const int32_t val = reset_lane && rep != best ? NEVER_CACHED : r;
             const uint32_t off = reset_lane ? (lane - 32 < R ? of_tail : spare_row) : of_seg;
             st(cell_of(off, rep), val);
+            if (PACK == 2) st(cell_at(in ? of_tail : spare_row), is_best ? r : NEVER_CACHED);
         }
         if (flags & (DESC_FRESH_MORE | DESC_DEEP)) {      // (one test on the usual path for the two rare cases)
             const int32_t fresh_cell = is_best ? r : NEVER_CACHED;
@@ -470,12 +504,17 @@ __device__ __forceinline__ void apart_book_wave(const SegArgs& a, size_t p, int 
             touched.done();
             const SegDesc& x = comm->ring[((r & ~(DESC_GROUP - 1)) + DESC_AHEAD + lane / SEG_CHUNK) & (DESC_RING - 1)];
             const uint32_t off = x.rowoff[lane % SEG_CHUNK];
-            touched.rows(rows, off, wide ? row_bytes - 4u : 0u, 0u);
+            touched.rows(rows, off, wide ? row_bytes - 4u : 0u, other_replay);
             touched.also = touch_trace(r + 5 * DESC_GROUP, d->j0);
         }
-        const int slot = r & (WAVE - 1);
-        const bool mine = lane == slot;
-        auto of_best = [&](int x) { return __builtin_amdgcn_readlane(x, __builtin_amdgcn_readfirstlane(best)); };
+        const int slot = r & (BATCH - 1);
+        const bool mine = pair.rl == slot;
+        auto of_best = [&](int x) {
+            const int a = __builtin_amdgcn_readlane(x, __builtin_amdgcn_readfirstlane(lane_best));
+            if (PACK == 1) return a;
+            const int b = __builtin_amdgcn_readlane(x, __builtin_amdgcn_readlane(lane_best, WAVE - 1));
+            return pair.upper ? b : a;
+        };
         const int hit = of_best((int)(c.hit_end & 0xFFFFu));          // (by all lanes together)
         o_route = mine ? best : o_route;
         o_hit = mine ? hit : o_hit;
@@ -483,10 +522,10 @@ __device__ __forceinline__ void apart_book_wave(const SegArgs& a, size_t p, int 
             const int seen = of_best(c.seen);
             o_seen = mine ? seen : o_seen;
         }
-        if (slot == WAVE - 1 || r == N - 1) {
-            const int x = r - slot + lane;
-            if (lane <= slot) {
-                const size_t o = p * N + x;
+        if (slot == BATCH - 1 || r == N - 1) {
+            const int x = r - slot + pair.rl;
+            if (pair.rl <= slot && pair.there) {
+                const size_t o = pair.p * N + x;
                 if (a.route) a.route[o] = (uint8_t)o_route;
                 if (a.hit) a.hit[o] = (uint16_t)o_hit;
                 if (PROXY && a.believed) a.believed[o] = (uint16_t)o_seen;
@@ -496,8 +535,8 @@ __device__ __forceinline__ void apart_book_wave(const SegArgs& a, size_t p, int 
     }
     touched.done();
     if (TIMED && a.sections && lane == 0) {
-        a.sections[(p * 3 + 2) * SECTIONS + 2] = clk.acc[2];
-        a.sections[(p * 3 + 2) * SECTIONS + 3] = clk.acc[3];
+        a.sections[(p0 * 3 + 2) * SECTIONS + 2] = clk.acc[2];
+        a.sections[(p0 * 3 + 2) * SECTIONS + 3] = clk.acc[3];
     }
 }
 
@@ -505,26 +544,27 @@ __device__ __forceinline__ void apart_book_wave(const SegArgs& a, size_t p, int 
 // Retiring wavefront: the lists of requests in flight (all of SlotQueues but the times the slots become free).  After X(r)
 // it enters r - 1, which has not completed by the arrival of r + 1 (else the serving wavefront has dealt with it), and retires
 // what completes by the arrival of r + 2, r itself aside.
-template <bool PROXY, bool TIMED, class Comm>
-__device__ __forceinline__ void apart_retire_wave(const SegArgs& a, size_t p, int lane, SlotQueues& Q, Comm* comm) {
+template <bool PROXY, int PACK, bool TIMED, class Comm>
+__device__ __forceinline__ void apart_retire_wave(const SegArgs& a, size_t p0, int which, int lane, SlotQueues& Q, Comm* comm) {
     const int N = (int)a.N;
+    const size_t p = p0 + (pair_has<PACK>(a, p0, which) ? which : 0);       // (one that is not there is served, but never enters)
     Rec* const rec = a.rec + p * N;
     const double sc = a.scale[p];
-    if (lane == 0) comm->served[1].at = -1;   // (there is nothing before the first request)
+    if (lane == 0) comm->served[which][1].at = -1;   // (there is nothing before the first request)
     meet(true);                               // the first descriptors are there
     double t1 = (double)a.ts[N > 1 ? 1 : 0] * sc;
     meet(true);
-    auto retire = [&](unsigned due, double t, int r) { Q.template retire<!PROXY>(due, t, rec, lane, comm->gone[r & 1]); };
+    auto retire = [&](unsigned due, double t, int r) { Q.template retire<!PROXY>(due, t, rec, lane, &comm->gone[r & 1][which * HALF]); };
     SectionClock<TIMED> clk;
     clk.start();
     for (int r = 0; r < N; ++r) {
         const SegDesc& d = comm->ring[r & (DESC_RING - 1)];
         const bool sync = (__builtin_amdgcn_readfirstlane(d.flags) & DESC_SYNC) != 0;
-        const double t2 = d.t2[0];
+        const double t2 = d.t2[which];
         clk.tick(2);                                                 // retiring
         meet(true);                                                  // X(r)
         clk.tick(3);                                                 // waiting at X
-        const Served x = comm->served[(r - 1) & 1];
+        const Served x = comm->served[which][(r - 1) & 1];
         const int at = __builtin_amdgcn_readfirstlane(x.at);
         if (at >= 0) Q.template enter<PROXY>(at, r - 1, x.done, x.weight, rec, lane);
         if (sync) {
@@ -542,13 +582,15 @@ __device__ __forceinline__ void apart_retire_wave(const SegArgs& a, size_t p, in
 // ---------------------------------------------------------------------------------------------- serving
 // Serving wavefront: after X(r) it serves r and hands it to the retiring wavefront, unless r completes by the arrival of
 // r + 2: then it takes r from the load signal itself.  The times at which the slots become free are its own.
-template <int MODE, bool ENGINE, bool PROXY, bool TIMED, class Comm>
-__device__ __forceinline__ void apart_serve_wave(const SegArgs& a, size_t p, int lane, SlotQueues& Q, double* window, Comm* comm) {
+template <int MODE, bool ENGINE, bool PROXY, int PACK, bool TIMED, class Comm>
+__device__ __forceinline__ void apart_serve_wave(const SegArgs& a, size_t p0, int which, int lane, SlotQueues& Q, double* window, Comm* comm) {
     constexpr bool COUNTS = MODE == MODE_LEAST_REQUEST;      // the load signal is the number of requests, not their tokens
     const int N = (int)a.N;
+    const bool there = pair_has<PACK>(a, p0, which);
+    const size_t p = p0 + (there ? which : 0);
     const double sc = a.scale[p];
-    Tuner<MODE == MODE_ONLINE> tuner(a, p, window, lane);
-    if (MODE == MODE_ONLINE && lane < 3) comm->w[0][lane] = a.params[3 * p + lane];
+    Tuner<MODE == MODE_ONLINE> tuner(a, p, window, lane, there);
+    if (MODE == MODE_ONLINE && lane < 3) comm->w[which][lane] = a.params[3 * p + lane];
     ProbeEpochs<PROXY> probes(a, lane);
     // proxy variants: half the round trip time of replica = lane, the request in hand's and the next two's
     double half0 = 0.0, half1 = 0.0, half2 = 0.0;
@@ -558,12 +600,13 @@ __device__ __forceinline__ void apart_serve_wave(const SegArgs& a, size_t p, int
     const double my_a_dec = ENGINE && lane < a.R ? a.eng_a_dec[lane] : 0.0;
     const double my_budget = ENGINE && lane < a.R ? a.eng_budget[lane] : 0.0;
     meet(true);                               // the first descriptors are there
-    for (int b = 0; b < 2; ++b) comm->gone[b][lane] = 0.0;
+    for (int b = 0; b < 2; ++b)
+        if (PACK == 1 || lane < HALF) comm->gone[b][which * HALF + lane] = 0.0;
     // arrival times of the request in hand and the two after it
     double t0 = (double)a.ts[0] * sc, t1 = (double)a.ts[N > 1 ? 1 : 0] * sc;
     if (PROXY) {
-        half0 = probes.at(t0, 0, comm);
-        if (N > 1) half1 = probes.at(t1, 1, comm);
+        half0 = probes.template at<PACK>(t0, 0, comm, which);
+        if (N > 1) half1 = probes.template at<PACK>(t1, 1, comm, which);
     }
     meet(true);                               // (nothing has completed yet: the first request can be decided)
     double o_ttft = 0.0, o_e2e = 0.0;
@@ -576,13 +619,14 @@ __device__ __forceinline__ void apart_serve_wave(const SegArgs& a, size_t p, int
             const SegDesc& d = comm->ring[r & (DESC_RING - 1)];
             const int4 h = *reinterpret_cast<const int4*>(&d.L);
             const int L = h.x, O = ENGINE ? d.O : 0;
-            const double t2 = d.t2[0], dec = ENGINE ? 0.0 : d.dec;
+            const double t2 = d.t2[which], dec = ENGINE ? 0.0 : d.dec;
             const bool sync = (__builtin_amdgcn_readfirstlane(h.w) & DESC_SYNC) != 0;
             clk.tick(0);
             meet(true);                                                  // X(r)
             clk.tick(1);                                                 // waiting at X
-            const int best = __builtin_amdgcn_readfirstlane(comm->best[r & 1][0]);
-            const double prefill = (double)comm->choice[r & 1][best].prefill;
+            const int lane_best = __builtin_amdgcn_readfirstlane(comm->best[r & 1][which]);
+            const double prefill = (double)comm->choice[r & 1][lane_best].prefill;
+            const int best = PACK == 2 ? lane_best & (HALF - 1) : lane_best;
             double half;
             if constexpr (PROXY) half = readlane_f64(half0, best);
             else half = comm->half[best];
@@ -599,12 +643,12 @@ __device__ __forceinline__ void apart_serve_wave(const SegArgs& a, size_t p, int
             // (the same in every lane)
             auto leave = [&](int to) {
                 if (lane == 0)
-                    __hip_atomic_fetch_add(&comm->gone[to & 1][best], -(double)weight, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    __hip_atomic_fetch_add(&comm->gone[to & 1][lane_best], -(double)weight, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             };
             if (__builtin_expect(ballot(left) != 0, 0)) leave(sync ? r + 1 : r + 2);
             o_ttft = lane == i ? ttft : o_ttft;
             o_e2e = lane == i ? e2e : o_e2e;
-            if constexpr (MODE == MODE_ONLINE) tuner.sample(ttft, comm->w[0]);
+            if constexpr (MODE == MODE_ONLINE) tuner.sample(ttft, comm->w[which]);
             clk.tick(5);                                                 // outputs, tuner
             if (sync) {
                 meet(true);                                              // Y(r)
@@ -612,9 +656,9 @@ __device__ __forceinline__ void apart_serve_wave(const SegArgs& a, size_t p, int
                 if (ballot(now) != 0) leave(r + 2);
                 left = left || now;
             }
-            comm->served[r & 1] = Served{done, left ? -1 : best * Q.B + k, weight};
+            comm->served[which][r & 1] = Served{done, left || !there ? -1 : best * Q.B + k, weight};
             if (PROXY) {
-                half2 = probes.at(t2, r + 2, comm);
+                half2 = probes.template at<PACK>(t2, r + 2, comm, which);
                 half0 = half1;
                 half1 = half2;
             }
@@ -622,7 +666,7 @@ __device__ __forceinline__ void apart_serve_wave(const SegArgs& a, size_t p, int
             t1 = t2;
         }
         // the batch is done: its outputs go out
-        if (lane < in_batch) {
+        if (lane < in_batch && there) {
             const size_t o = p * N + b0 + lane;
             if (a.ttft) a.ttft[o] = o_ttft;
             if (a.e2e) a.e2e[o] = o_e2e;
@@ -635,25 +679,28 @@ __device__ __forceinline__ void apart_serve_wave(const SegArgs& a, size_t p, int
 }
 
 // ---------------------------------------------------------------------------------------------- deciding
-template <int MODE, bool ENGINE, bool PROXY, bool TIMED, class Comm>
-__device__ __forceinline__ void apart_decide_wave(const SegArgs& a, size_t p, int lane, Comm* comm) {
+template <int MODE, bool ENGINE, bool PROXY, int PACK, bool TIMED, class Comm>
+__device__ __forceinline__ void apart_decide_wave(const SegArgs& a, size_t p0, int lane, Comm* comm) {
     constexpr bool ONLINE = MODE == MODE_ONLINE;
     constexpr bool SCORED = MODE == MODE_COST_MODEL || MODE == MODE_ONLINE;
     constexpr bool COUNTS = MODE == MODE_LEAST_REQUEST;
     constexpr bool DICTATED = MODE == MODE_AFFINITY || MODE == MODE_RANDOM || MODE == MODE_GIVEN;
     const int R = a.R, N = (int)a.N;
-    const bool in = lane < R;
+    const Pair<PACK> pair(a, p0, lane);
+    const size_t p = pair.p;
+    const int rl = pair.rl;
+    const bool in = rl < R;
     double w_rtt = a.params[3 * p + 0], w_prefill = a.params[3 * p + 1], w_queue = a.params[3 * p + 2];
-    double my_rtt = !PROXY && in ? a.rtt[lane] : 0.0;            // (proxy variants: comes from the serving wavefront)
+    double my_rtt = !PROXY && in ? a.rtt[rl] : 0.0;            // (proxy variants: comes from the serving wavefront)
     // first product of Eq. 3 (lanes without a replica: a score above any)
     double rtt_term = in ? w_rtt * my_rtt : INFINITY;
     double q = COUNTS && !in ? INFINITY : 0.0;       // load signal of replica = lane (an integer below 2^53, exact in fp64)
     double tokens = 0.0;                             // what the request before adds to it where it went
     const bool own_index = PROXY && a.index_blocks >= 0;
     unsigned long long went1 = 0, went2 = 0, went3 = 0;  // where the three requests before went
-    const char* const rows = reinterpret_cast<const char*>(a.last + p * (size_t)a.nseg * R);
+    const char* const rows = reinterpret_cast<const char*>(a.last + p0 * (size_t)a.nseg * R);
     const unsigned row_bytes = (unsigned)R * 4u;
-    const unsigned lane_off = (unsigned)(in ? lane : 0) * 4u;
+    const unsigned lane_off = (pair.upper && pair.there ? (unsigned)a.nseg * row_bytes : 0u) + (unsigned)(in ? rl : 0) * 4u;
     auto cell_at = [&](uint32_t rowoff) { return reinterpret_cast<const int32_t*>(rows + (rowoff + lane_off)); };
     const int spare = N;                      // the log record behind the last request's
     // the request before, on this lane's replica: blocks it would have added, oldest request it matched blocks of
@@ -715,9 +762,9 @@ __device__ __forceinline__ void apart_decide_wave(const SegArgs& a, size_t p, in
             behind = false;
             if (!DICTATED) left = comm->gone[r & 1][lane];
             if (ONLINE) {
-                w_rtt = comm->w[0][0];
-                w_prefill = comm->w[0][1];
-                w_queue = comm->w[0][2];
+                w_rtt = comm->w[pair.upper ? 1 : 0][0];
+                w_prefill = comm->w[pair.upper ? 1 : 0][1];
+                w_queue = comm->w[pair.upper ? 1 : 0][2];
                 rtt_term = in ? w_rtt * my_rtt : INFINITY;
             }
         };
@@ -874,7 +921,7 @@ __device__ __forceinline__ void apart_decide_wave(const SegArgs& a, size_t p, in
         } else if (COUNTS) {
             my_score = q;                       // requests in flight
         } else {
-            my_score = lane == target ? 0.0 : 1.0;      // the replica is dictated
+            my_score = rl == target ? 0.0 : 1.0;      // the replica is dictated
         }
         // ---- what every replica would mean for the request, whatever the choice
         const unsigned hit_end = (unsigned)my_m | ((unsigned)k_end << 16);
@@ -886,8 +933,9 @@ __device__ __forceinline__ void apart_decide_wave(const SegArgs& a, size_t p, in
         tokens = (double)L;
         set = set == CELL_SETS - 1 ? 0 : set + 1;
         take(r + 1, set);
-        const unsigned long long bests = argmin_mask<1>(my_score, false);
-        comm->best[r & 1][0] = __builtin_ctzll(bests);
+        const unsigned long long bests = argmin_mask<PACK>(my_score, pair.upper);
+        if (PACK == 1) comm->best[r & 1][0] = __builtin_ctzll(bests);
+        else comm->best[r & 1][pair.upper ? 1 : 0] = pair.upper ? HALF + __builtin_ctz((unsigned)(bests >> 32)) : __builtin_ctz((unsigned)bests);
         clk.tick(3);                                                 // score, minimum, announcement
         went3 = went2;
         went2 = went1;
@@ -897,60 +945,83 @@ __device__ __forceinline__ void apart_decide_wave(const SegArgs& a, size_t p, in
         before = flags;
     }
     if (TIMED && a.sections && lane == 0)            // (the evicting wavefront writes the counts)
-        for (int k = 0; k < 8; ++k) a.sections[p * 3 * SECTIONS + k] = clk.acc[k];
+        for (int k = 0; k < 8; ++k) a.sections[p0 * 3 * SECTIONS + k] = clk.acc[k];
 }
+
+// Replay p0, or replays p0 and p0 + 1, by one workgroup.  Three of a replay each fit a CU by their registers, two in the proxy
+// variant with engine model and tuner; LDS may allow fewer (30,592 bytes of hand-over words in the proxy variants and 53,248 of
+// slots and window make 84 KB: one).  The launch rule counts both.
+template <int PACK>
+constexpr int apart_threads() { return (APART_WAVES + 2 * (PACK - 1)) * WAVE; }
 
 // What the wavefronts of a workgroup do.  The one with number w runs on the same SIMD as those with w + 4, so which two share one is
-// a matter of this order; the longest chains go with the shortest.  (With decide, serve, retire, book, evict, front -- deciding and
-// evicting on one SIMD -- 64 replays of 6,000 requests on 32 replicas of 4,000 blocks took 0.495 us a request, so 0.485, proxy
-// 0.656 / 0.591; 512 of them 0.547 / 0.523, proxy 0.717 / 0.679, engine model 0.681 / 0.631.)
-enum ApartRole { DECIDE, SERVE, RETIRE, BOOK, EVICT, FRONT };
+// a matter of this order; the longest chains go with the shortest.  (4,000 blocks a cache.  One replay: with decide, serve, retire,
+// book, evict, front -- deciding and evicting on one SIMD -- 64 replays of 6,000 requests on 32 replicas took 0.495 us a
+// request, so 0.485, proxy 0.656 / 0.591; 512 of them 0.547 / 0.523, proxy 0.717 / 0.679, engine model 0.681 / 0.631.
+// Two replays, 1,023 on 32 replicas: decide, serve, serve, evict, book, retire, retire, front 0.591, tuner 0.660, proxy 0.693; so 0.582,
+// 0.657, 0.684.  With the engine model, whose serving wavefront is among the longest, 0.689, so 0.717, and in its own order 0.677.)
+enum ApartRole { DECIDE, SERVE, RETIRE, BOOK, EVICT, FRONT, SERVE_2, RETIRE_2 };       // (_2: of the workgroup's second replay)
+template <bool ENGINE, int PACK>
 __device__ __forceinline__ int apart_role(int wave) {
-    constexpr unsigned ROLES = DECIDE | SERVE << 4 | EVICT << 8 | RETIRE << 12 | BOOK << 16 | FRONT << 20;
-    return (int)(ROLES >> (4 * wave)) & 15;
+    constexpr unsigned long long ONE = DECIDE | SERVE << 4 | EVICT << 8 | RETIRE << 12 | BOOK << 16 | FRONT << 20;
+    constexpr unsigned long long TWO = ENGINE
+        ? DECIDE | SERVE << 4 | SERVE_2 << 8 | EVICT << 12 | RETIRE << 16 | RETIRE_2 << 20 | BOOK << 24 | (unsigned long long)FRONT << 28
+        : DECIDE | EVICT << 4 | RETIRE << 8 | RETIRE_2 << 12 | FRONT << 16 | BOOK << 20 | SERVE << 24 | (unsigned long long)SERVE_2 << 28;
+    return (int)((PACK == 1 ? ONE : TWO) >> (4 * wave)) & 15;
 }
 
-// Replay p by one workgroup.  Three fit a CU by their registers, two in the proxy variant with engine model and tuner; LDS may
-// allow fewer (30,592 bytes of hand-over words in the proxy variants and 53,248 of slots and window make 84 KB: one).  The launch
-// rule counts both.
-template <int MODE, bool ENGINE, bool PROXY, bool TIMED>
-__device__ __forceinline__ void apart_replay(const SegArgs& a, size_t p, unsigned char* lds_raw) {
-    __shared__ ApartHandover<PROXY> comm;
+// args: where a role gets the launch's arguments from.
+template <int MODE, bool ENGINE, bool PROXY, int PACK, bool TIMED, class Args>
+__device__ __forceinline__ void apart_replay(Args args, size_t p0, unsigned char* lds_raw) {
+    __shared__ ApartHandover<PROXY, PACK> comm;
+    const SegArgs& a = args();
     const int lane = threadIdx.x & (WAVE - 1);
-    const int role = apart_role(__builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE)));
-    double* const window = reinterpret_cast<double*>(lds_raw + SlotQueues::bytes(a.R, a.B, ENGINE));
-    if (a.N == 0) {           // (an empty trace still reports the tuner's initial state)
-        if (role == SERVE) Tuner<MODE == MODE_ONLINE>(a, p, window, lane).results();
+    const int role = apart_role<ENGINE, PACK>(__builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE)));
+    const int which = PACK == 2 && role >= SERVE_2 ? 1 : 0;
+    unsigned char* const queues = lds_raw + which * replay_queue_lds_bytes(a.R, a.B, ENGINE, MODE == MODE_ONLINE ? a.window : 0);
+    if (role == SERVE || (PACK == 2 && role == SERVE_2)) {
+        double* const window = reinterpret_cast<double*>(queues + SlotQueues::bytes(a.R, a.B, ENGINE));
+        if (a.N == 0) {       // (an empty trace still reports the tuner's initial state)
+            if (pair_has<PACK>(a, p0, which)) Tuner<MODE == MODE_ONLINE>(a, p0 + which, window, lane).results();
+            return;
+        }
+        __builtin_amdgcn_s_setprio(2);
+        SlotQueues Q;
+        Q.init(queues, a.R, a.B, ENGINE, lane);
+        apart_serve_wave<MODE, ENGINE, PROXY, PACK, TIMED>(args(), p0, which, lane, Q, window, &comm);
+    } else if (a.N == 0) {
         return;
-    }
-    if (role == DECIDE) {
+    } else if (role == DECIDE) {
         __builtin_amdgcn_s_setprio(3);      // the wavefront on the chain goes first at issue
-        apart_decide_wave<MODE, ENGINE, PROXY, TIMED>(a, p, lane, &comm);
-    } else if (role == SERVE) {
+        apart_decide_wave<MODE, ENGINE, PROXY, PACK, TIMED>(args(), p0, lane, &comm);
+    } else if (role == RETIRE || (PACK == 2 && role == RETIRE_2)) {
         __builtin_amdgcn_s_setprio(2);
         SlotQueues Q;
-        Q.init(lds_raw, a.R, a.B, ENGINE, lane);
-        apart_serve_wave<MODE, ENGINE, PROXY, TIMED>(a, p, lane, Q, window, &comm);
-    } else if (role == RETIRE) {
-        __builtin_amdgcn_s_setprio(2);
-        SlotQueues Q;
-        Q.attach(lds_raw, a.R, a.B);
-        apart_retire_wave<PROXY, TIMED>(a, p, lane, Q, &comm);
+        Q.attach(queues, a.R, a.B);
+        apart_retire_wave<PROXY, PACK, TIMED>(args(), p0, which, lane, Q, &comm);
     } else if (role == BOOK) {
         __builtin_amdgcn_s_setprio(1);
-        apart_book_wave<PROXY, TIMED>(a, p, lane, &comm);
+        apart_book_wave<PROXY, PACK, TIMED>(args(), p0, lane, &comm);
     } else if (role == EVICT) {
         __builtin_amdgcn_s_setprio(2);
-        apart_evict_wave<PROXY, TIMED>(a, p, lane, &comm);
+        apart_evict_wave<PROXY, PACK, TIMED>(args(), p0, lane, &comm);
     } else {
-        front_wave<MODE, PROXY, 1, TIMED>(a, lane, &comm);
+        front_wave<MODE, PROXY, PACK, TIMED>(args(), lane, &comm);
     }
 }
 
 template <int MODE, bool ENGINE, bool PROXY, bool TIMED = false>
-__global__ void __launch_bounds__(APART_WAVES * WAVE, 4) replay_apart_kernel(SegArgs a) {
+__global__ void __launch_bounds__(apart_threads<1>(), 4) replay_apart_kernel(SegArgs a) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    apart_replay<MODE, ENGINE, PROXY, TIMED>(a, blockIdx.x, lds_raw);
+    apart_replay<MODE, ENGINE, PROXY, 1, TIMED>([]() -> const SegArgs& { return kernel_args<SegArgs>(); }, blockIdx.x, lds_raw);
+}
+
+// Two replays per workgroup: the wavefronts that look at replicas have them in their halves, each replay has a serving and a retiring
+// wavefront of its own.
+template <int MODE, bool ENGINE, bool PROXY>
+__global__ void __launch_bounds__(apart_threads<2>(), 4) replay_apart_pairs_kernel(SegArgs a) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    apart_replay<MODE, ENGINE, PROXY, 2, false>([]() -> const SegArgs& { return kernel_args<SegArgs>(); }, 2 * (size_t)blockIdx.x, lds_raw);
 }
 
 }  // namespace gorgo

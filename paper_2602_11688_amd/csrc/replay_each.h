@@ -212,7 +212,7 @@ __global__ void __launch_bounds__(APART_WAVES * WAVE, 4) replay_each_kernel(SegA
         a.eng_a_dec += i;
         a.eng_budget += i;
     }
-    apart_replay<MODE_GIVEN, ENGINE, false, false>(a, 0, lds_raw);
+    apart_replay<MODE_GIVEN, ENGINE, false, 1, false>([&]() -> const SegArgs& { return a; }, 0, lds_raw);
 }
 
 // Outputs from the places to the requests.

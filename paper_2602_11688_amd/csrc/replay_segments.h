@@ -68,11 +68,11 @@ struct SegArgs {
     const int64_t* blk_off;       // [N+1]
     const SegRef* seg;
     int64_t N;
-    int32_t R, B;
+    int32_t P, R, B;
     int64_t C;
     int64_t nseg;
     int32_t block_tokens;
-    int32_t look;                 // six wavefronts: log records of look-ahead per replica
+    int32_t look;                 // six and eight wavefronts: log records of look-ahead per replica
     double a_pf, a_dec;
     double least_dec;             // smallest decode time per output token of any replica
     const double* rtt;
@@ -644,14 +644,15 @@ __device__ __forceinline__ void front_wave(const SegArgs& a, int lane, Comm* com
     const int R = a.R, N = (int)a.N;
     const int q = lane / SEG_CHUNK, k = lane % SEG_CHUNK;
     const size_t p = MODE == MODE_GIVEN ? 0 : (size_t)blockIdx.x * PACK;
-    const double scale0 = a.scale[p], scale1 = PACK == 2 ? a.scale[p + 1] : 0.0;
+    const bool pair = PACK == 2 && (!APART || p + 1 < (size_t)a.P);      // (four wavefronts: an even number of replays)
+    const double scale0 = a.scale[p], scale1 = PACK == 2 ? a.scale[p + (pair ? 1 : 0)] : 0.0;
     const uint64_t seed = MODE == MODE_RANDOM ? a.seeds[p] : 0;
     const uint32_t row_bytes = (uint32_t)R * 4u;
     const uint32_t never_off = (uint32_t)(a.nseg - 2) * row_bytes;      // the extra row that no request touches
     const uint32_t spare_off = (uint32_t)(a.nseg - 1) * row_bytes;      // the row that nothing reads
     const char* const rows = reinterpret_cast<const char*>(a.last + p * (size_t)a.nseg * R);
     // lane = replica, for the row cells and the log records that the deciding wavefront gets
-    const bool upper = PACK == 2 && lane >= HALF;
+    const bool upper = pair && lane >= HALF;
     const int rl = PACK == 2 ? lane & (HALF - 1) : lane;
     const uint32_t lane_off = (upper ? (uint32_t)a.nseg * row_bytes : 0u) + (uint32_t)(rl < R ? rl : 0) * 4u;
     const unsigned long long* const log64 = reinterpret_cast<const unsigned long long*>(a.log + (p + (upper ? 1 : 0)) * ((size_t)N + 1));
@@ -775,7 +776,7 @@ __device__ __forceinline__ void front_wave(const SegArgs& a, int lane, Comm* com
         const unsigned fresh8 = (unsigned)(allf >> byte) & 0xffu;
         // the last segment's row, if it is fresh: with at most 32 replicas the book-keeping wavefront's upper lanes
         // reset it in the same store
-        const bool tail_fresh = PACK == 1 && R <= 32 && now.s > 0 && now.s <= SEG_CHUNK && ((fresh8 >> ((now.s - 1) & 31)) & 1u) != 0;
+        const bool tail_fresh = (PACK == 1 || APART) && R <= 32 && now.s > 0 && now.s <= SEG_CHUNK && ((fresh8 >> ((now.s - 1) & 31)) & 1u) != 0;
         const uint32_t tail = (uint32_t)__builtin_amdgcn_ds_bpermute((byte + ((now.s - 1) & (SEG_CHUNK - 1))) << 2, (int)slot_off);
         const unsigned rest = fresh8 & ~(tail_fresh ? 1u << (now.s - 1) : 0u);
         const int flags = (now.s > 4 ? DESC_MORE4 : 0) | (now.s > SEG_CHUNK ? DESC_DEEP : 0) | (tail_fresh ? DESC_FRESH_TAIL : 0) |
@@ -902,13 +903,14 @@ struct Tuner {
     double* const ring;                 // the window (LDS)
     const int lane, W, H, kth;
     const int wk;                       // the weight of this lane
+    const bool there;                   // whether the replay reports
     int ring_pos = 0, until_step, accepted = 0;
     int64_t step = 0;
     bool have_parent = false;
     double ln_par = 0.0, ln_cur = 0.0, f_par = 0.0, sigma = 0.0;
-    __device__ __forceinline__ Tuner(const SegArgs& a_, size_t p_, double* ring_, int lane_)
+    __device__ __forceinline__ Tuner(const SegArgs& a_, size_t p_, double* ring_, int lane_, bool there_ = true)
         : a(a_), p(p_), ring(ring_), lane(lane_), W(ONLINE ? a_.window : 0), H(ONLINE ? a_.hop : 0), kth((95 * W + 99) / 100),
-          wk(lane_ < 3 ? lane_ : 2), until_step(W) {
+          wk(lane_ < 3 ? lane_ : 2), there(there_), until_step(W) {
         if (ONLINE) {
             ln_par = ln_cur = a.ln_theta0[3 * p + wk];
             sigma = a.tuner[12];
@@ -916,7 +918,7 @@ struct Tuner {
         }
     }
     __device__ __forceinline__ void results() const {
-        if (ONLINE) {
+        if (ONLINE && there) {
             const double best = clip(tuner_exp(ln_par), a.tuner[wk], a.tuner[3 + wk]);
             if (a.theta_final && lane < 3) a.theta_final[3 * p + lane] = best;
             if (a.sigma_final && lane == 0) a.sigma_final[p] = sigma;
@@ -948,9 +950,9 @@ struct Tuner {
             const double th = clip(tuner_exp(ln_cur), a.tuner[wk], a.tuner[3 + wk]);
             if (lane < 3) {
                 weights[lane] = th;
-                if (a.theta_step) a.theta_step[(p * a.steps + step) * 3 + lane] = th;
+                if (a.theta_step && there) a.theta_step[(p * a.steps + step) * 3 + lane] = th;
             }
-            if (lane == 0 && a.fitness_step) a.fitness_step[p * a.steps + step] = f;
+            if (lane == 0 && a.fitness_step && there) a.fitness_step[p * a.steps + step] = f;
             ++step;
             wave_sync();
         }
@@ -968,9 +970,10 @@ struct ProbeEpochs {
     int epoch = 0;
     double next_probe, rtt_now = 0.0, est_now = 0.0;
     __device__ __forceinline__ ProbeEpochs(const SegArgs& a_, int lane_) : a(a_), lane(lane_), next_probe(PROXY ? (double)a_.probe_ms : 0.0) {}
-    // request r arrives at t: half the round trip time of replica = lane
-    template <class Comm>
-    __device__ __forceinline__ double at(double t, int r, Comm* comm) {
+    // request r arrives at t: half the round trip time of replica = lane.  PACK, which: the estimates go to the lanes of one of two
+    // replays.
+    template <int PACK = 1, class Comm>
+    __device__ __forceinline__ double at(double t, int r, Comm* comm, int which = 0) {
         bool moved = r == 0;
         while (epoch + 1 < a.epochs && next_probe <= t) {       // (timestamps do not decrease)
             ++epoch;
@@ -982,7 +985,9 @@ struct ProbeEpochs {
             rtt_now = a.rtt_true[x];
             est_now = a.rtt_est[x];
         }
-        if constexpr (PROXY) comm->rtt[r & 1][lane] = est_now;
+        if constexpr (PROXY) {
+            if (PACK == 1 || lane < HALF) comm->rtt[r & 1][which * HALF + lane] = est_now;
+        }
         return 0.5 * rtt_now;
     }
 };

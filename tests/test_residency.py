@@ -134,3 +134,18 @@ def test_replays_over_rows_of_stamps(kernels, R, B, window, least):
         assert _resident(kernel, dynamic) >= least + (0 if all_three or R * B > 256 else 1), (name, kernel, dynamic)
         seen += 1
     assert seen == 14
+
+
+@pytest.mark.parametrize("R,B,window,pairs", [(32, 8, 128, 2), (16, 16, 128, 2), (32, 16, 128, 2), (32, 32, 128, 1)])
+def test_pairs_of_replays(kernels, R, B, window, pairs):
+    """Workgroups of eight wavefronts with two replays: two per compute unit, one with 1,024 service slots."""
+    seen = 0
+    for name, kernel in kernels.items():
+        apart = re.search(r"replay_apart_pairs_kernel<(\d), (true|false), (true|false)>", name)
+        if not apart:
+            continue
+        mode, engine, proxy = apart.groups()
+        dynamic = 2 * _queues(R, B, engine == "true", window if mode == "1" else 0)
+        assert kernel[2] == 512 and min(_resident(kernel, dynamic), 2) == pairs, (name, kernel, dynamic)
+        seen += 1
+    assert seen == 10
