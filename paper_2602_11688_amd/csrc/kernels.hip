@@ -565,6 +565,7 @@ void launch_segments(bool engine, bool proxy, const Plan& pl, hipStream_t s, con
 constexpr double LOOK_FEW_HELD = 40.0;       // requests
 int32_t apart_look(const Plan& pl, bool proxy) { return pl.requests_held < LOOK_FEW_HELD ? (proxy ? 8 : 6) : 11; }
 static_assert(APART_LOOK > 11);
+constexpr int LOOK_FROM = 4;                 // from when on: the longest requests that there is still room for
 
 // Dictated routes: the shares laid out, a replay per share, the outputs back in their order.
 int launch_each(const gorgo_trace* t, const Plan& pl, int mode, bool engine, const SegArgs& a, char* ws, hipStream_t s) {
@@ -674,6 +675,7 @@ int launch_replay(const gorgo_trace* t, const Plan& pl, const double* d_rtt, con
     a.nseg = pl.nseg + 2;             // rows of one replay: one per segment, one that no request touches, a spare
     a.block_tokens = pl.block_tokens;
     a.look = apart_look(pl, proxy != nullptr);
+    a.near = LOOK_FROM * t->max_blocks;              // (at most 2^16 of them)
     a.a_pf = pl.a_pf;
     a.a_dec = pl.a_dec;
     a.least_dec = engine ? engine->least_dec : pl.a_dec;

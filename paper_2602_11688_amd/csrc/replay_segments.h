@@ -72,7 +72,7 @@ struct SegArgs {
     int64_t C;
     int64_t nseg;
     int32_t block_tokens;
-    int32_t look;                 // six and eight wavefronts: log records of look-ahead per replica
+    int32_t look, near;           // six and eight wavefronts: log records of look-ahead per replica, from when on (blocks of room)
     double a_pf, a_dec;
     double least_dec;             // smallest decode time per output token of any replica
     const double* rtt;
