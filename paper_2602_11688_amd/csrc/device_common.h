@@ -38,6 +38,14 @@ __device__ __forceinline__ const T& kernel_args() {
     return *(const T*)k;
 }
 
+// A scalar argument that a loop keeps: the compiler otherwise reads it again each time round, where all of a wavefront's accesses
+// to LDS have to be waited for along with it.
+template <class T>
+__device__ __forceinline__ T kept(T x) {
+    asm volatile("" : "+s"(x));
+    return x;
+}
+
 __device__ __forceinline__ double readlane_f64(double v, int src) {
     const long long b = __double_as_longlong(v);
     const int lo = __builtin_amdgcn_readlane((int)b, src);

@@ -599,6 +599,7 @@ __device__ __forceinline__ void apart_serve_wave(const SegArgs& a, size_t p0, in
     Tuner<MODE == MODE_ONLINE> tuner(a, p, window, lane, there);
     if (MODE == MODE_ONLINE && lane < 3) comm->w[which][lane] = a.params[3 * p + lane];
     ProbeEpochs<PROXY> probes(a, lane);
+    const double a_pf = PROXY ? kept(a.a_pf) : 0.0, slowdown = ENGINE ? kept(a.eng_slowdown) : 0.0;
     // proxy variants: half the round trip time of replica = lane, the request in hand's and the next two's
     double half0 = 0.0, half1 = 0.0, half2 = 0.0;
     if constexpr (!PROXY) comm->half[lane] = lane < a.R ? 0.5 * a.rtt[lane] : 0.0;
@@ -641,9 +642,9 @@ __device__ __forceinline__ void apart_serve_wave(const SegArgs& a, size_t p0, in
             int k;
             if constexpr (ENGINE)
                 k = Q.start_engine(best, t0, half, readlane_f64(my_a_pf, best) * prefill, readlane_f64(my_a_dec, best) * (double)O,
-                            (unsigned)L + (unsigned)O, readlane_f64(my_budget, best), a.eng_slowdown, lane, &ttft, &e2e, &done);
+                            (unsigned)L + (unsigned)O, readlane_f64(my_budget, best), slowdown, lane, &ttft, &e2e, &done);
             else
-                k = Q.template start_linear<PROXY>(best, t0, half, PROXY ? a.a_pf * prefill : prefill, dec, lane, &ttft, &e2e, &done);
+                k = Q.template start_linear<PROXY>(best, t0, half, PROXY ? a_pf * prefill : prefill, dec, lane, &ttft, &e2e, &done);
             clk.tick(9);                                                 // service
             const int weight = COUNTS ? 1 : L;
             bool left = done <= (sync ? t1 : t2);
@@ -697,6 +698,8 @@ __device__ __forceinline__ void apart_decide_wave(const SegArgs& a, size_t p0, i
     const size_t p = pair.p;
     const int rl = pair.rl;
     const bool in = rl < R;
+    const int block_tokens = kept(a.block_tokens);
+    const double a_pf = kept(a.a_pf);
     double w_rtt = a.params[3 * p + 0], w_prefill = a.params[3 * p + 1], w_queue = a.params[3 * p + 2];
     double my_rtt = !PROXY && in ? a.rtt[rl] : 0.0;            // (proxy variants: comes from the serving wavefront)
     // first product of Eq. 3 (lanes without a replica: a score above any)
@@ -905,24 +908,24 @@ __device__ __forceinline__ void apart_decide_wave(const SegArgs& a, size_t p0, i
         clk.tick(1);                                                 // patch, match
 
         // ---- score (Eq. 3) and lowest-index minimum.  block_tokens * blocks fits: below 2^15 and 2^16.
-        int hit_tok = __mul24(a.block_tokens, my_m);
+        int hit_tok = __mul24(block_tokens, my_m);
         hit_tok = hit_tok > L ? L : hit_tok;
         const int my_u = L - hit_tok;
         int my_u_seen = my_u;       // uncached tokens as Eq. 3 sees them
         if (PROXY) {
-            int seen_tok = __mul24(a.block_tokens, own_index ? my_seen : my_m);
+            int seen_tok = __mul24(block_tokens, own_index ? my_seen : my_m);
             seen_tok = seen_tok > L ? L : seen_tok;
             my_u_seen = L - seen_tok;
         }
         q += left;
         double my_score, my_prefill = (double)my_u;
-        if (!ENGINE && !PROXY) my_prefill = a.a_pf * my_prefill;
+        if (!ENGINE && !PROXY) my_prefill = a_pf * my_prefill;
         if (SCORED) {
-            const double pf = PROXY || ENGINE ? a.a_pf * (double)my_u_seen : my_prefill;
+            const double pf = PROXY || ENGINE ? a_pf * (double)my_u_seen : my_prefill;
             const double s_rtt = PROXY ? (in ? w_rtt * my_rtt : INFINITY) : rtt_term;
             const double s_pf = w_prefill * pf;
             const double rtt_and_prefill = s_rtt + s_pf;
-            const double qd = a.a_pf * q;
+            const double qd = a_pf * q;
             const double s_q = w_queue * qd + 0.0;       // (not -0.0: nor is the score then)
             my_score = rtt_and_prefill + s_q;
         } else if (COUNTS) {

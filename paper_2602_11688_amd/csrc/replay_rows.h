@@ -635,13 +635,13 @@ __global__ void __launch_bounds__(ROW_WAVES * WAVE, 4) replay_rows_kernel(RowArg
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
     const int p = blockIdx.x;
     if (wave == 2) {
-        queue_wave<MODE, ENGINE, PROXY, 1, true, false>(b.q, 0, lane, lds_raw, &comm);
+        queue_wave<MODE, ENGINE, PROXY, 1, true, false>(kernel_args<RowArgs>().q, 0, lane, lds_raw, &comm);
     } else if (b.q.N > 0) {
         const RowState state(lds_raw + ((replay_queue_lds_bytes(b.q.R, b.q.B, ENGINE, MODE == MODE_ONLINE ? b.q.window : 0) + 15) & ~(size_t)15),
                              b.q.R);
-        if (wave == 0) rows_decide_wave<MODE, ENGINE, PROXY>(b, p, lane, state, &comm);
-        else if (wave == 1) rows_update_wave<PROXY>(b, p, lane, state, &comm);
-        else rows_book_wave<PROXY>(b, p, lane, state, &comm);
+        if (wave == 0) rows_decide_wave<MODE, ENGINE, PROXY>(kernel_args<RowArgs>(), p, lane, state, &comm);
+        else if (wave == 1) rows_update_wave<PROXY>(kernel_args<RowArgs>(), p, lane, state, &comm);
+        else rows_book_wave<PROXY>(kernel_args<RowArgs>(), p, lane, state, &comm);
     }
 }
 

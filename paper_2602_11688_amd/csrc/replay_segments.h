@@ -643,6 +643,7 @@ __device__ __forceinline__ void front_wave(const SegArgs& a, int lane, Comm* com
     constexpr bool SIGNAL = MODE == MODE_COST_MODEL || MODE == MODE_ONLINE || MODE == MODE_LEAST_REQUEST;
     const int R = a.R, N = (int)a.N;
     const int q = lane / SEG_CHUNK, k = lane % SEG_CHUNK;
+    const double least_dec = kept(a.least_dec), a_dec = kept(a.a_dec);
     const size_t p = MODE == MODE_GIVEN ? 0 : (size_t)blockIdx.x * PACK;
     const bool pair = PACK == 2 && (!APART || p + 1 < (size_t)a.P);      // (four wavefronts: an even number of replays)
     const double scale0 = a.scale[p], scale1 = PACK == 2 ? a.scale[p + (pair ? 1 : 0)] : 0.0;
@@ -710,7 +711,7 @@ __device__ __forceinline__ void front_wave(const SegArgs& a, int lane, Comm* com
         // ... if this one may have completed by its arrival -- it takes its decode time at least: every further term of its
         // completion time is added to it and none is negative, and rounding keeps the order ...
         if (SIGNAL) {
-            const double t = (double)c.ts0, t1 = (double)c.ts1, dec = a.least_dec * (double)c.O;
+            const double t = (double)c.ts0, t1 = (double)c.ts1, dec = least_dec * (double)c.O;
             sync = sync || !(t * scale0 + dec > t1 * scale0);
             if (PACK == 2) sync = sync || !(t * scale1 + dec > t1 * scale1);
         }
@@ -796,7 +797,7 @@ __device__ __forceinline__ void front_wave(const SegArgs& a, int lane, Comm* com
             d->t2[1] = now.t1;
         }
         if (k == 3) {
-            d->dec = a.a_dec * (double)now.O;
+            d->dec = a_dec * (double)now.O;
             d->O = now.O;
         }
         old_id = ref_id;
@@ -1013,6 +1014,7 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
     if (ONLINE && lane < 3) comm->w[which][lane] = a.params[3 * p + lane];
     const double sc = a.scale[p];
     ProbeEpochs<PROXY> probes(a, lane);
+    const double a_pf = PROXY ? kept(a.a_pf) : 0.0, slowdown = ENGINE ? kept(a.eng_slowdown) : 0.0;
     // proxy variants: half the round trip time of replica = lane, the request in hand's and the next two's
     double half0 = 0.0, half1 = 0.0, half2 = 0.0;
     if constexpr (!PROXY) comm->half[lane] = lane < R ? 0.5 * a.rtt[lane] : 0.0;
@@ -1129,9 +1131,9 @@ __device__ __forceinline__ void queue_wave(const SegArgs& a, int which, int lane
             if constexpr (ENGINE) {
                 Q.template serve_engine<PROXY>(r, best, t0, half, readlane_f64(my_a_pf, best) * prefill,
                                                readlane_f64(my_a_dec, best) * (double)O, weight, (unsigned)L + (unsigned)O,
-                                               readlane_f64(my_budget, best), a.eng_slowdown, rec, lane, &ttft, &e2e, until, due);
+                                               readlane_f64(my_budget, best), slowdown, rec, lane, &ttft, &e2e, until, due);
             } else {
-                Q.template serve<PROXY>(r, best, t0, half, PROXY ? a.a_pf * prefill : prefill, dec, weight, rec, lane, &ttft, &e2e, until, due);
+                Q.template serve<PROXY>(r, best, t0, half, PROXY ? a_pf * prefill : prefill, dec, weight, rec, lane, &ttft, &e2e, until, due);
             }
             clk.tick(9);                                                 // service
             if (AHEAD) read_desc(r + 1);
@@ -1309,6 +1311,8 @@ __device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Comm* co
     const int rl = PACK == 2 ? lane & (HALF - 1) : lane;
     const size_t p0 = (size_t)blockIdx.x * PACK, p = p0 + (upper ? 1 : 0);
     const bool in = rl < R;
+    const int block_tokens = kept(a.block_tokens);
+    const double a_pf = kept(a.a_pf);
     double w_rtt = a.params[3 * p + 0], w_prefill = a.params[3 * p + 1], w_queue = a.params[3 * p + 2];
     double my_rtt = !PROXY && in ? a.rtt[rl] : 0.0;              // (proxy variants: comes from the queue wavefront)
     // first product of Eq. 3 (lanes without a replica: a score above any)
@@ -1516,24 +1520,24 @@ __device__ __forceinline__ void decide_wave(const SegArgs& a, int lane, Comm* co
         clk.tick(2);                                                 // log records
 
         // ---- score (Eq. 3) and lowest-index minimum.  block_tokens * blocks fits: below 2^15 and 2^16.
-        int hit_tok = __mul24(a.block_tokens, my_m);
+        int hit_tok = __mul24(block_tokens, my_m);
         hit_tok = hit_tok > L ? L : hit_tok;
         const int my_u = L - hit_tok;
         int my_u_seen = my_u;       // uncached tokens as Eq. 3 sees them
         if (PROXY) {
-            int seen_tok = __mul24(a.block_tokens, own_index ? my_seen : my_m);
+            int seen_tok = __mul24(block_tokens, own_index ? my_seen : my_m);
             seen_tok = seen_tok > L ? L : seen_tok;
             my_u_seen = L - seen_tok;
         }
         q += left;
         double my_score, my_prefill = (double)my_u;
-        if (!ENGINE && !PROXY) my_prefill = a.a_pf * my_prefill;
+        if (!ENGINE && !PROXY) my_prefill = a_pf * my_prefill;
         if (SCORED) {
-            const double pf = PROXY || ENGINE ? a.a_pf * (double)my_u_seen : my_prefill;
+            const double pf = PROXY || ENGINE ? a_pf * (double)my_u_seen : my_prefill;
             const double s_rtt = PROXY ? (in ? w_rtt * my_rtt : INFINITY) : rtt_term;
             const double s_pf = w_prefill * pf;
             const double rtt_and_prefill = s_rtt + s_pf;
-            const double qd = a.a_pf * q;
+            const double qd = a_pf * q;
             const double s_q = w_queue * qd + 0.0;       // (not -0.0: nor is the score then)
             my_score = rtt_and_prefill + s_q;
         } else if (COUNTS) {
