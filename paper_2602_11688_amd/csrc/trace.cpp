@@ -40,10 +40,36 @@ struct KeyInfo {
     uint8_t ends = 0;                // some request ends here
 };
 
-// Open-addressed map from ids to keys: linear probing over the keys' numbers alone (0: empty), grows by doubling.
+// The block ids of a trace's requests, one after the other, as they lie in memory: in one array, or in several, each with the ids
+// of whole requests from block `from` on.
+struct IdRun {
+    int64_t from;
+    const int64_t* ids;
+};
+class Ids {
+  public:
+    explicit Ids(const std::vector<IdRun>& runs) : runs_(runs) {}
+    // those of a request whose first block is b; called with increasing b
+    const int64_t* of(int64_t b) {
+        while (at_ + 1 < runs_.size() && runs_[at_ + 1].from <= b) ++at_;
+        return runs_[at_].ids + (b - runs_[at_].from);
+    }
+
+  private:
+    const std::vector<IdRun>& runs_;
+    size_t at_ = 0;
+};
+
+// Open-addressed map from ids to keys: linear probing over the keys' numbers alone (0: empty), grows fourfold (by doubling, keys
+// are entered twice as often again).
 class IdMap {
   public:
-    explicit IdMap(std::vector<KeyInfo>& keys) : keys_(keys), slot_((size_t)1 << 12, 0) {}
+    // (a table of half the trace's blocks, up to 4 MiB, to begin with: growing costs more than clearing it)
+    IdMap(std::vector<KeyInfo>& keys, int64_t blocks) : keys_(keys) {
+        size_t n = (size_t)1 << 12;
+        while (n < ((size_t)1 << 20) && n < (size_t)blocks / 2) n *= 2;
+        slot_.assign(n, 0);
+    }
     // the key of an id, the next one on first sight
     uint32_t get_or_add(int64_t id, bool* added) {
         if (keys_.size() * 2 > slot_.size()) grow();
@@ -66,7 +92,7 @@ class IdMap {
         return x ^ (x >> 31);
     }
     void grow() {
-        slot_.assign(slot_.size() * 2, 0);
+        slot_.assign(slot_.size() * 4, 0);
         for (size_t k = 1; k < keys_.size(); ++k) {
             size_t h = mix((uint64_t)keys_[k].id) & (slot_.size() - 1);
             while (slot_[h] != 0) h = (h + 1) & (slot_.size() - 1);
@@ -116,7 +142,7 @@ int block_rows(gorgo_trace* t, const std::vector<KeyInfo>& keys) {
 }
 
 // Fills key/first/statistics from the raw ids.  Returns 0 or an error code.
-int preprocess(gorgo_trace* t, const int64_t* hash_ids) {
+int preprocess(gorgo_trace* t, const std::vector<IdRun>& runs) {
     const int64_t N = t->N;
     const int64_t total = t->blk_off[N];
     t->total_blocks = total;
@@ -125,31 +151,42 @@ int preprocess(gorgo_trace* t, const int64_t* hash_ids) {
     std::vector<KeyInfo> keys;
     keys.reserve((size_t)std::min<int64_t>(total, 1 << 20) + 1);
     keys.emplace_back();             // (key 0 stands before a request's first block)
-    IdMap map(keys);
+    IdMap map(keys, total);
+    Ids ids(runs);
     bool consistent = true;
     int32_t max_blocks = 0, max_distinct = 0;
+    uint32_t* const out = t->key.data();       // (by value: a byte that is written may be anything, also where a vector lies)
+    uint8_t* const first = t->first.data();
+    KeyInfo* info = keys.data();
     for (int64_t r = 0; r < N; ++r) {
         const int64_t b = t->blk_off[r], e = t->blk_off[r + 1];
         const int64_t n = e - b;
         if (n > max_blocks) max_blocks = (int32_t)n;
         int32_t distinct = 0;
         uint32_t prev = 0;
+        size_t known = keys.size();
+        const int64_t* const its = n > 0 ? ids.of(b) : nullptr;
         for (int64_t k = 0; k < n; ++k) {
-            // Prompts repeat each other's beginnings: an id is mostly the one that followed its predecessor the last time,
-            // whose entry is the next one in memory, and needs no look-up.
-            const int64_t id = hash_ids[b + k];
+            // Prompts repeat each other's beginnings: an id is mostly the one that first appeared behind its predecessor, or else
+            // the one that followed it the last time, and needs no look-up.
+            const int64_t id = its[k];
             bool added = false;
-            uint32_t key = prev ? keys[prev].next : 0;
-            if (key == 0 || keys[key].id != id) {
-                key = map.get_or_add(id, &added);
-                if (keys.size() > 0xFFFFFFF0ull) return fail(GORGO_ERR_INVALID_ARG, "too many distinct hash ids");
-                if (prev) keys[prev].next = key;
+            uint32_t key = prev + 1;
+            if (prev == 0 || key >= known || info[key].id != id) {
+                key = prev ? info[prev].next : 0;
+                if (key == 0 || info[key].id != id) {
+                    key = map.get_or_add(id, &added);
+                    known = keys.size();
+                    info = keys.data();
+                    if (known > 0xFFFFFFF0ull) return fail(GORGO_ERR_INVALID_ARG, "too many distinct hash ids");
+                    if (prev) info[prev].next = key;
+                }
             }
-            KeyInfo& of = keys[key];
+            KeyInfo& of = info[key];
             if (added) {
                 of.parent = prev;
                 of.pos = (uint32_t)k;
-                if (prev) ++keys[prev].nchild;
+                if (prev) ++info[prev].nchild;
             } else if (of.parent != prev || of.pos != (uint32_t)k) {
                 consistent = false;
             }
@@ -157,11 +194,11 @@ int preprocess(gorgo_trace* t, const int64_t* hash_ids) {
             if (dup) consistent = false;
             else ++distinct;
             of.seen_in = (int32_t)r;
-            t->key[(size_t)(b + k)] = key;
-            t->first[(size_t)(b + k)] = dup ? 0 : 1;
+            out[b + k] = key;
+            first[b + k] = dup ? 0 : 1;
             prev = key;
         }
-        if (prev) keys[prev].ends = 1;
+        if (prev) info[prev].ends = 1;
         if (distinct > max_distinct) max_distinct = distinct;
     }
     t->max_blocks = max_blocks;
@@ -183,11 +220,17 @@ int preprocess(gorgo_trace* t, const int64_t* hash_ids) {
     // together.  Keys are numbered in order of first appearance, so a predecessor precedes its successors.
     const size_t U = keys.size() - 1;
     std::vector<int32_t> seg_of(U + 1, 0);
+    std::vector<int32_t> seg_end;          // of each segment: blocks of a request up to and including it
     int64_t nseg = 0;
     for (size_t k = 1; k <= U; ++k) {
         const uint32_t par = keys[k].parent;
-        if (par == 0 || keys[par].nchild > 1 || keys[par].ends) seg_of[k] = (int32_t)(nseg++);
-        else seg_of[k] = seg_of[par];
+        if (par == 0 || keys[par].nchild > 1 || keys[par].ends) {
+            seg_of[k] = (int32_t)(nseg++);
+            seg_end.push_back(0);
+        } else {
+            seg_of[k] = seg_of[par];
+        }
+        seg_end[(size_t)seg_of[k]] = (int32_t)keys[k].pos + 1;       // (its last key has the highest number)
         if (nseg >= 0x7FFFFFF0) return fail(GORGO_ERR_INVALID_ARG, "too many segments");
     }
     t->n_segments = nseg;
@@ -195,9 +238,9 @@ int preprocess(gorgo_trace* t, const int64_t* hash_ids) {
     t->seg_off[0] = 0;
     for (int64_t r = 0; r < N; ++r) {
         const int64_t b = t->blk_off[r], e = t->blk_off[r + 1];
-        for (int64_t k = b; k < e; ++k) {
+        for (int64_t k = b; k < e; k = b + t->seg.back().end) {      // (whole segments)
             const int32_t sg = seg_of[t->key[(size_t)k]];
-            if (k + 1 == e || seg_of[t->key[(size_t)k + 1]] != sg) t->seg.push_back(gorgo::SegRef{sg, (int32_t)(k + 1 - b)});
+            t->seg.push_back(gorgo::SegRef{sg, seg_end[(size_t)sg]});
         }
         t->seg_off[(size_t)r + 1] = (int64_t)t->seg.size();
     }
@@ -243,7 +286,7 @@ int preprocess(gorgo_trace* t, const int64_t* hash_ids) {
     return segments_suit(t) ? GORGO_OK : block_rows(t, keys);
 }
 
-int check_and_finish(gorgo_trace* t, const int64_t* hash_ids, int32_t block_tokens) {
+int check_and_finish(gorgo_trace* t, const std::vector<IdRun>& runs, int32_t block_tokens) {
     if (block_tokens < 1) return fail(GORGO_ERR_INVALID_ARG, "block_tokens must be >= 1");
     const int64_t N = t->N;
     if (N >= 0x7FFFFFFF) return fail(GORGO_ERR_INVALID_ARG, "too many requests (limit 2^31-2)");
@@ -269,14 +312,15 @@ int check_and_finish(gorgo_trace* t, const int64_t* hash_ids, int32_t block_toke
     // session-affinity policy (Sec. 4 "Baseline policies"): hash of the request's first block, here the high word
     // of the output that a SplitMix64 generator (Steele, Lea, Flood, OOPSLA'14) in state `id` gives next
     t->first_hash.assign((size_t)N, 0u);
+    Ids ids(runs);
     for (int64_t r = 0; r < N; ++r)
         if (t->blk_off[r + 1] > t->blk_off[r]) {
-            uint64_t z = (uint64_t)hash_ids[t->blk_off[r]] + 0x9E3779B97F4A7C15ull;
+            uint64_t z = (uint64_t)*ids.of(t->blk_off[r]) + 0x9E3779B97F4A7C15ull;
             z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
             z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
             t->first_hash[(size_t)r] = (uint32_t)((z ^ (z >> 31)) >> 32);
         }
-    return preprocess(t, hash_ids);
+    return preprocess(t, runs);
 }
 
 // ---- minimal JSON scanner (enough for flat objects with numbers, strings and arrays of numbers)
@@ -405,8 +449,14 @@ bool parse_line(const char* b, const char* e, int64_t* ts, int64_t* il, int64_t*
     return c.p == c.e;
 }
 
-// Records of a piece of a file; `off` begins with the 0 of the first one.
+// Records of a piece of a file; `off` begins with the 0 of the first one.  The block ids of pieces behind the first stay where
+// they were parsed (`more`), each from where its first request's begin.
 struct Records {
+    struct More {
+        int64_t from;
+        std::vector<int64_t> ids;
+    };
+    std::vector<More> more;
     std::vector<int64_t> ts, off{0}, ids;
     std::vector<int32_t> in_len, out_len;
     int64_t lines = 0;           // read so far
@@ -470,13 +520,17 @@ struct Records {
             rc = GORGO_ERR_OOM;
         }
     }
-    void append(const Records& x) {
+    void append(Records& x) {
+        if (lines == 0) {
+            *this = std::move(x);
+            return;
+        }
         const int64_t at = off.back();
         ts.insert(ts.end(), x.ts.begin(), x.ts.end());
         in_len.insert(in_len.end(), x.in_len.begin(), x.in_len.end());
         out_len.insert(out_len.end(), x.out_len.begin(), x.out_len.end());
         for (size_t i = 1; i < x.off.size(); ++i) off.push_back(at + x.off[i]);
-        ids.insert(ids.end(), x.ids.begin(), x.ids.begin() + x.off.back());
+        if (x.off.back() > 0) more.push_back(More{at, std::move(x.ids)});
         lines += x.lines;
         rc = x.rc;
         what = x.what;
@@ -484,7 +538,8 @@ struct Records {
 };
 
 // A file of records, in blocks of whole lines, a block in as many pieces as there are threads for it.  (A file of 5,000 requests
-// and 319,000 block ids, 2.6 MB: 4.7 ms to load with one thread and a copy of every line, 3.1 so; 2.4 are what follows.)
+// and 319,000 block ids, 2.6 MB: 4.7 ms to load with one thread and a copy of every line; 3.3 with the pieces' ids put together
+// in one array, 2.4 without, and with what stands at IdMap and below about the numbering, 1.3 of it, and the segments.)
 #ifndef GORGO_READ_BYTES       // (tests read small files in blocks and pieces of a few lines)
 #define GORGO_READ_BYTES ((size_t)32 << 20)
 #define GORGO_PIECE_BYTES ((size_t)128 << 10)
@@ -512,7 +567,9 @@ int read_records(FILE* f, const char* path, Records* all) {
                 if (failed && nuls) e = nl ? nl + 1 : b;
             }
             if (nuls) {
-                if (b < e) all->parse_with_nuls(b, e);      // (nothing is not a line)
+                Records rest;
+                if (b < e) rest.parse_with_nuls(b, e);      // (nothing is not a line)
+                all->append(rest);
             } else {
                 const size_t bytes = (size_t)(e - b);
                 const size_t most = std::min(std::max(1u, std::thread::hardware_concurrency()), READ_THREADS);
@@ -541,13 +598,7 @@ int read_records(FILE* f, const char* path, Records* all) {
                     from = to;
                 }
                 for (std::thread& t : threads) t.join();
-                size_t ids = all->ids.size();
-                for (const Records& x : piece) ids += x.ids.size();
-                if (n > 1) all->ids.reserve(ids);
-                for (size_t i = 0; i < n && all->rc == GORGO_OK; ++i) {
-                    if (n == 1 && all->lines == 0) *all = std::move(piece[0]);
-                    else all->append(piece[i]);
-                }
+                for (size_t i = 0; i < n && all->rc == GORGO_OK; ++i) all->append(piece[i]);
             }
             if (all->rc == GORGO_ERR_OOM) return fail(GORGO_ERR_OOM, "out of host memory");
             if (all->rc != GORGO_OK)
@@ -597,7 +648,7 @@ int gorgo_load_trace_arrays(int64_t N, const int64_t* ts_ms, const int32_t* in_l
         t->in_len.assign(in_len, in_len + N);
         t->out_len.assign(out_len, out_len + N);
         t->blk_off.assign(blk_off, blk_off + N + 1);
-        int rc = check_and_finish(t, hash_ids, block_tokens);
+        int rc = check_and_finish(t, {IdRun{0, hash_ids}}, block_tokens);
         if (rc != GORGO_OK) { delete t; return rc; }
     } catch (const std::bad_alloc&) {
         delete t;
@@ -618,8 +669,23 @@ int gorgo_load_trace(const char* jsonl_path, int32_t block_tokens, gorgo_trace**
     int rc = read_records(f, jsonl_path, &all);
     std::fclose(f);
     if (rc != GORGO_OK) return rc;
-    return gorgo_load_trace_arrays((int64_t)all.ts.size(), all.ts.data(), all.in_len.data(), all.out_len.data(), all.off.data(),
-                                   all.ids.data(), block_tokens, out);
+    gorgo_trace* t = new (std::nothrow) gorgo_trace();
+    if (!t) return fail(GORGO_ERR_OOM, "out of host memory");
+    try {
+        std::vector<IdRun> runs{IdRun{0, all.ids.data()}};
+        for (const Records::More& x : all.more) runs.push_back(IdRun{x.from, x.ids.data()});
+        t->N = (int64_t)all.ts.size();
+        t->ts = std::move(all.ts);
+        t->in_len = std::move(all.in_len);
+        t->out_len = std::move(all.out_len);
+        t->blk_off = std::move(all.off);
+        rc = check_and_finish(t, runs, block_tokens);
+    } catch (const std::bad_alloc&) {
+        rc = fail(GORGO_ERR_OOM, "out of host memory");
+    }
+    if (rc != GORGO_OK) { delete t; return rc; }
+    *out = t;
+    return GORGO_OK;
 }
 
 int gorgo_trace_info(const gorgo_trace* t, int64_t* N, int64_t* total_blocks, int32_t* max_blocks,
