@@ -83,15 +83,16 @@ template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ unsigned dpp_add_u32(unsigned x) {
     return x + (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROW_MASK, 0xf, false);
 }
-__device__ __forceinline__ unsigned wave_sum_u32(unsigned x) {
+// wave_scan_u32: of the lanes up to this one.
+__device__ __forceinline__ unsigned wave_scan_u32(unsigned x) {
     x = dpp_add_u32<0x111, 0xf>(x);   // row_shr:1
     x = dpp_add_u32<0x112, 0xf>(x);   // row_shr:2
     x = dpp_add_u32<0x114, 0xf>(x);   // row_shr:4
     x = dpp_add_u32<0x118, 0xf>(x);   // row_shr:8: lane 15 of each row holds the row's sum
     x = dpp_add_u32<0x142, 0xa>(x);   // row_bcast:15 into rows 1, 3
-    x = dpp_add_u32<0x143, 0xc>(x);   // row_bcast:31 into rows 2, 3
-    return (unsigned)__builtin_amdgcn_readlane((int)x, 63);
+    return dpp_add_u32<0x143, 0xc>(x);   // row_bcast:31 into rows 2, 3
 }
+__device__ __forceinline__ unsigned wave_sum_u32(unsigned x) { return (unsigned)__builtin_amdgcn_readlane((int)wave_scan_u32(x), 63); }
 
 // Lowest-index minimum over the lanes below `count` (count >= 1; values must not be NaN).  The values are
 // compared through the usual order-preserving map of an IEEE double to an unsigned 64-bit key (zeros of

@@ -18,9 +18,10 @@
 // X(r) the updating wavefront reads the chosen replica's stamps and cursor records while the deciding one reads the next
 // request's stamps.  What r changes of those is known beforehand: blocks that r has as well (ROW_IN_BEFORE) are cached where r
 // went, the others' stamps stay, and the threshold is there at Y(r).
-// Bound by the chain of a request, about 2.2 us: the trip to memory, the eviction behind it, the scores and two meetings.
+// Bound by the chain of a request, about 1.8 us: the trip to memory, the eviction behind it, the scores and two meetings.
 // 65 replays of 3,001 requests on 7 replicas: 23.6 ms with tables, 8.1 with the updating wavefront as the book-keeper, each
-// dead record a trip to memory and the chosen replica's stamps read behind Y(r), 6.7 so.  1,024 of 1,000 on 64: 17.9, 8.9, 7.9.
+// dead record a trip to memory and the chosen replica's stamps read behind Y(r), 6.4 with the eviction record by record and word by
+// word and loads waited for between Y(r) and X(r + 1), 5.4 so.  1,024 of 1,000 on 8: 3.2, so 2.7; on 64: 17.9 with tables, 7.5 now.
 #pragma once
 #include "device_common.h"
 #include "internal.h"
@@ -74,25 +75,41 @@ struct RowHandover : QueueHandover<PROXY> {
     int32_t first_on[WAVE];               // first request on each replica (-1: none yet)
 };
 
-// Where a request's blocks are, how many, input tokens, and its first 128 references (lane = block).  Read ahead.
+// Where a request's blocks are, how many, input tokens, and its first 128 references (lane = block).  Read ahead, the numbers as
+// vector loads of the same word by every lane: a scalar load is waited for at the next meeting, as LDS accesses are, and there
+// took some 400 cycles of each of the wavefronts' chains.  (Every word that is loaded is used, and no load is under a condition: for
+// the register of an unused word, or to merge what is loaded with what is there otherwise, the compiler waits on the spot.)
 struct RowRequest {
     int64_t off;
     int n, L;
     uint32_t ref[2];
-    __device__ __forceinline__ void read_scalars(const RowArgs& b, int64_t r) {
-        const int64_t x = r < b.q.N ? r : b.q.N - 1;
-        off = b.blk_off[x];
-        n = (int)(b.blk_off[x + 1] - off);
-        L = b.q.in_len[x];
+    int64_t from;                         // as they come from memory
+    int to, tokens;                       // (to: its low word)
+    __device__ __forceinline__ void ask(const RowArgs& b, int64_t r) {
+        uint64_t x = (uint64_t)(r < b.q.N ? r : b.q.N - 1);
+        asm("" : "+v"(x));
+        from = b.blk_off[x];
+        to = reinterpret_cast<const int32_t*>(b.blk_off)[2 * (x + 1)];
+        tokens = b.q.in_len[x];
     }
+    __device__ __forceinline__ void arrive() {
+        off = readlane_i64(from, 0);
+        n = __builtin_amdgcn_readfirstlane(to) - (int)off;
+        L = __builtin_amdgcn_readfirstlane(tokens);
+    }
+    __device__ __forceinline__ void read_scalars(const RowArgs& b, int64_t r) {
+        ask(b, r);
+        arrive();
+    }
+    // (beyond the request's blocks: the trace's first reference, whose row there is)
     __device__ __forceinline__ void read_refs(const RowArgs& b, int lane) {
 #pragma unroll
         for (int g = 0; g < 2; ++g) {
             const int k = g * WAVE + lane;
-            ref[g] = k < n ? b.ref[off + k] : 0u;
+            ref[g] = b.ref[k < n ? off + k : 0];
         }
     }
-    // reference k = base + lane
+    // reference k = base + lane (any one for k >= n)
     __device__ __forceinline__ uint32_t at(const RowArgs& b, int base, int lane) const {
         if (base == 0) return ref[0];
         if (base == WAVE) return ref[1];
@@ -129,7 +146,7 @@ __device__ __forceinline__ void rows_decide_wave(const RowArgs& b, int p, int la
     now.read_refs(b, lane);
     next.read_scalars(b, 1);
     next.read_refs(b, lane);
-    after.read_scalars(b, 2);
+    after.ask(b, 2);
 
     // ---- prefix match of a request on the replicas in `holders`, four at a time.  unread: marks of blocks whose stamps are not
     // there to be read, which are not cached.
@@ -210,18 +227,13 @@ __device__ __forceinline__ void rows_decide_wave(const RowArgs& b, int p, int la
     int64_t before[2] = {-1, -1};        // stamps of the first 128 blocks there, from before it was updated
     for (int64_t r = 0; r < N; ++r) {
         const int n = now.n, L = now.L;
-        // the next request's first block on every replica, for those that this request does not go to
-        const uint32_t ref0 = (uint32_t)__builtin_amdgcn_readlane((int)next.ref[0], 0);
-        const int64_t stamp0 = ld_cell(cells, ref0, R, in ? lane : 0);
         // the replica that the previous request went to was still being updated: its turn now.  The stamps of before serve:
         // what that request touched is cached.
         if (previous >= 0 && n > 0) {
             const int64_t t1 = tau1[previous], t2 = two ? tau2[previous] : t1;
             int m1 = 0, m2 = 0;
             bool open1 = true, open2 = two;
-            for (int base = 0; base < n && (open1 || open2); base += WAVE) {
-                const uint32_t ref = now.at(b, base, lane);
-                const int64_t stamp = base == 0 ? before[0] : base == WAVE ? before[1] : ld_cell(cells, ref, R, previous);
+            auto compare = [&](int base, uint32_t ref, int64_t stamp) {
                 const bool there = base + lane < n && (ref & ROW_FRESH) == 0, touched = (ref & ROW_IN_BEFORE) != 0;
                 const unsigned long long got1 = ballot(there && (touched || stamp >= t1));
                 const unsigned long long got2 = ballot(there && (touched || stamp >= t2));
@@ -231,10 +243,20 @@ __device__ __forceinline__ void rows_decide_wave(const RowArgs& b, int p, int la
                 if (open2) m2 += got2 == want ? width : __builtin_ctzll(~got2);
                 open1 = open1 && got1 == want;
                 open2 = open2 && got2 == want;
+            };
+            compare(0, now.ref[0], before[0]);
+            if (n > WAVE) compare(WAVE, now.ref[1], before[1]);
+            for (int base = 2 * WAVE; base < n && (open1 || open2); base += WAVE) {
+                const uint32_t ref = now.at(b, base, lane);
+                compare(base, ref, ld_cell(cells, ref, R, previous));
             }
             my_m = lane == previous ? m1 : my_m;
             my_seen = lane == previous ? m2 : my_seen;
         }
+        // the next request's first block on every replica, for those that this request does not go to (asked for here: what a path of
+        // more than 128 blocks reads above would be waited for together with it)
+        const uint32_t ref0 = (uint32_t)__builtin_amdgcn_readlane((int)next.ref[0], 0);
+        const int64_t stamp0 = ld_cell(cells, ref0, R, in ? lane : 0);
         // uncached tokens, really and as Eq. 3 sees them (block_tokens * blocks fits: below 2^15 and 2^16)
         int hit_tok = a.block_tokens * my_m;
         hit_tok = hit_tok > L ? L : hit_tok;
@@ -282,6 +304,7 @@ __device__ __forceinline__ void rows_decide_wave(const RowArgs& b, int p, int la
         // ---- the next request, on the replicas that this one does not change
 #pragma unroll
         for (int h = 0; h < 2; ++h) before[h] = h * WAVE < next.n ? ld_cell(cells, next.ref[h], R, best) : -1;
+        after.arrive();
         after.read_refs(b, lane);
         my_m = my_seen = 0;
         if (r + 1 < N && next.n > 0 && (ref0 & (ROW_FRESH | ROW_NEW_BEFORE)) == 0) {
@@ -291,7 +314,7 @@ __device__ __forceinline__ void rows_decide_wave(const RowArgs& b, int p, int la
         }
         now = next;
         next = after;
-        after.read_scalars(b, r + 3);
+        after.ask(b, r + 3);
         previous = best;
         meet(true);                                                  // Y(r): what completes by the next arrival is known
         if (ONLINE) {
@@ -312,11 +335,12 @@ __device__ __forceinline__ void rows_update_wave(const RowArgs& b, int p, int la
     const int C1 = (int)a.C, C2 = two ? (int)a.index_blocks : 0;          // (0: it never forgets)
     int64_t* const cells = b.cells + (size_t)p * (size_t)b.slots * R;
     uint32_t* const log = b.log + (size_t)p * (size_t)N * words;
-    auto record = [&](int x) { return log + (size_t)x * words; };
-    // Records' words, a lane each, two loads of as many records as fit a wavefront (8, 4 or 2).  Past the CU's own cache:
-    // bits are cleared by atomics, which are performed behind it.
-    const int shift = words <= 16 ? 4 : words <= 32 ? 5 : 6, each = WAVE >> shift;
-    const int word = (lane & ((1 << shift) - 1)) < words ? lane & ((1 << shift) - 1) : words - 1;
+    auto record = [&](int x) { return log + (size_t)((uint64_t)(uint32_t)x * (uint32_t)words); };
+    // Records' words, a lane each, the last one first, two loads of as many records as fit a wavefront (8, 4 or 2): blocks are
+    // evicted in the order of the lanes.  Past the CU's own cache: bits are cleared by atomics, which are performed behind it.
+    const int shift = words <= 16 ? 4 : words <= 32 ? 5 : 6, each = WAVE >> shift, group = (1 << shift) - 1;
+    const int place_of = group - (lane & group);      // (beyond the record: reads its last word, which then counts for nothing)
+    const int word = place_of < words ? place_of : words - 1;
     auto load_record = [&](int x) { return __hip_atomic_load(record(x >= 0 ? x : 0) + word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
     RowRequest now, next;
     now.read_scalars(b, 0);
@@ -327,7 +351,7 @@ __device__ __forceinline__ void rows_update_wave(const RowArgs& b, int p, int la
         const int r = __builtin_amdgcn_readfirstlane((int)r64), n = now.n;
         next.read_refs(b, lane);
         RowRequest after;
-        after.read_scalars(b, r64 + 2);
+        after.ask(b, r64 + 2);
         meet(true);                                                  // X(r): the choice is there
         const int best = __builtin_amdgcn_readfirstlane(comm->best[r & 1][0]);
         auto cell = [&](uint32_t ref) {
@@ -396,7 +420,7 @@ __device__ __forceinline__ void rows_update_wave(const RowArgs& b, int p, int la
                 while (__builtin_expect(lost != 0, 0)) {
                     const int lead = __builtin_ctzll(lost), of = __builtin_amdgcn_readlane(x, lead);
                     const unsigned long long its = lost & ballot(x == of), even = its & ballot(k == base + lane);
-                    const int w = 2 + base / 32, at = lane & ((1 << shift) - 1);
+                    const int w = 2 + base / 32, at = place_of;
 #pragma unroll
                     for (int l = 0; l < 2; ++l)
                         if (c[i].id[l] == of) c[i].rec[l] &= at == w ? ~(uint32_t)even : at == w + 1 ? ~(uint32_t)(even >> 32) : ~0u;
@@ -416,6 +440,7 @@ __device__ __forceinline__ void rows_update_wave(const RowArgs& b, int p, int la
             old[h] = was(now.ref[h], k, old[h]);
             count(old[h], mine(now.ref[h], k), h * WAVE);
         }
+        after.arrive();
         // Blocks that change hands, in the records of their owners: a bit each, and their number.  Mostly the turn of the
         // conversation before owned them, at the same places of its prompt.
         auto disown = [&](int64_t stamp, int base) {
@@ -460,39 +485,44 @@ __device__ __forceinline__ void rows_update_wave(const RowArgs& b, int p, int la
             int E = C > 0 && held > C ? held - C : 0;
             if (lane == 0) *state.word(best, i, LRU_LIVE) = held - E;
             if (E == 0) return;
-            int x = u.r, k = u.k, to = -1;
-            // takes set bits below position k of the record whose words are in the lanes from `from` on, the last ones first
-            auto take = [&](uint32_t rec, int from) {
-                for (int w = (k + 31) / 32 - 1; w >= 0 && E > 0; --w) {
-                    uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)rec, from + 2 + w);
-                    if (k < 32 * w + 32) bits &= (1u << (k - 32 * w)) - 1;
-                    const int have = __builtin_popcount(bits);
-                    if (have <= E) {
-                        E -= have;
-                        k = 32 * w;
-                    } else {
-                        // the position from which on E of them are left
-                        int at = 0;
-#pragma unroll
-                        for (int step = 16; step > 0; step >>= 1)
-                            if (__builtin_popcount(bits >> (at + step)) >= E) at += step;
-                        k = 32 * w + at;
-                        E = 0;
-                    }
+            // Blocks are taken lane by lane: a sum over the lanes before says in which the last one is, and lane = bit which bit of that
+            // it is.  (Record after record and word after word, on scalars, took 1,700 of the 5,000 cycles of a request.)
+            int x = u.r, k = u.k, to = -1, used = 0;       // used: records read ahead that the cursor has come to
+            // from the records in `there`; lane of the last block taken, -1: they do not hold E
+            auto take = [&](uint32_t rec, int id, bool there, int below) {
+                const int have = below < 0 ? 0 : below > 32 ? 32 : below;
+                uint32_t bits = there && place_of >= 2 && place_of < words ? rec : 0u;
+                bits = have < 32 ? bits & ((1u << have) - 1) : bits;
+                const unsigned sum = wave_scan_u32((unsigned)__builtin_popcount(bits));
+                const unsigned long long enough = ballot((int)sum >= E), any = ballot(there);
+                if (enough != 0) {
+                    const int lead = __builtin_ctzll(enough);
+                    const uint32_t its = (uint32_t)__builtin_amdgcn_readlane((int)bits, lead);
+                    const int left = E - (__builtin_amdgcn_readlane((int)sum, lead) - __builtin_popcount(its));
+                    const unsigned long long bit = ballot(lane < 32 && __builtin_popcount(its >> (lane & 31)) >= left);
+                    x = __builtin_amdgcn_readlane(id, lead);
+                    k = 32 * (group - (lead & group) - 2) + (63 - __builtin_clzll(bit));
+                    E = 0;
+                    return lead;
                 }
-                to = __builtin_amdgcn_readlane((int)rec, from);
+                E -= __builtin_amdgcn_readlane((int)sum, WAVE - 1);
+                if (any != 0) {
+                    const int lead = 63 - __builtin_clzll(any);
+                    x = __builtin_amdgcn_readlane(id, lead);
+                    k = 0;
+                    to = __builtin_amdgcn_readlane((int)rec, lead | group);
+                }
+                return -1;
             };
-            int used = 0;                     // records read ahead that the cursor has come to
-            for (int j = 0; j < 2 * each && j <= u.count && E > 0; ++j) {
-                const uint32_t rec = j < each ? u.rec[0] : u.rec[1];
-                const int from = (j & (each - 1)) << shift, id = __builtin_amdgcn_readlane(j < each ? u.id[0] : u.id[1], from);
-                used = j;
-                if (j > 0) {
-                    if (id <= x) continue;    // (the cursor has passed it while it was being read)
-                    x = id;
-                    k = (int)((uint32_t)__builtin_amdgcn_readlane((int)rec, from + 1) & 0xFFFFu);
-                }
-                if (x >= 0) take(rec, from);
+#pragma unroll
+            for (int l = 0; l < 2; ++l) {
+                if (l > 0 && (E == 0 || u.count < each)) break;
+                const int j = l * each + (lane >> shift);
+                // (the cursor may have passed a record while it was being read)
+                const bool there = u.id[l] >= 0 && (j == 0 || u.id[l] > u.r);
+                const int lead = take(u.rec[l], u.id[l], there, j == 0 ? u.k - 32 * (place_of - 2) : 32);
+                const int last = (l + 1) * each - 1;
+                used = lead >= 0 ? l * each + (lead >> shift) : u.count < last ? u.count : last;
             }
             if (__builtin_expect(E > 0, 0)) {
                 // further records, one after the other
@@ -507,10 +537,7 @@ __device__ __forceinline__ void rows_update_wave(const RowArgs& b, int p, int la
                         to = __builtin_amdgcn_readfirstlane(comm->first_on[best]);
                     }
                     if (to < 0 || to >= r) break;             // cannot happen while E > 0; bounds the loop
-                    const uint32_t rec = load_record(to);
-                    x = to;
-                    k = (int)((uint32_t)__builtin_amdgcn_readlane((int)rec, 1) & 0xFFFFu);
-                    take(rec, 0);
+                    take(load_record(to), to, lane <= group, 32);
                 }
             }
             if (used > 0) {
@@ -563,7 +590,7 @@ __device__ __forceinline__ void rows_book_wave(const RowArgs& b, int p, int lane
         const int r = __builtin_amdgcn_readfirstlane((int)r64), n = now.n;
         next.read_refs(b, lane);
         RowRequest after;
-        after.read_scalars(b, r64 + 2);
+        after.ask(b, r64 + 2);
         meet(true);                                                  // X(r)
         const int best = __builtin_amdgcn_readfirstlane(comm->best[r & 1][0]);
         int owned = 0;
@@ -588,11 +615,14 @@ __device__ __forceinline__ void rows_book_wave(const RowArgs& b, int p, int lane
                 }
             }
         }
-        if (lane < 2) st(record(r) + lane, lane == 0 ? ~0u : (uint32_t)n | (uint32_t)owned << 16);
+        // (with zeros for what is beyond its blocks: the eviction reads whole records)
+        if (lane < 2 || (lane >= 2 + (n + WAVE - 1) / WAVE * 2 && lane < words))
+            st(record(r) + lane, lane == 0 ? ~0u : lane == 1 ? (uint32_t)n | (uint32_t)owned << 16 : 0u);
         if (lane == best) {
             if (tail >= 0) st(record(tail), (uint32_t)r);
             else comm->first_on[lane] = r;
         }
+        after.arrive();
         meet(true);                                                  // Y(r)
 #pragma unroll
         for (int i = 0; i < (PROXY ? 2 : 1); ++i) {
