@@ -62,7 +62,7 @@ def kernel_source_digest():
     import hashlib
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2602_11688_amd", "csrc")
-    for name in ("device_common.h", "replay_segments.h", "kernels.hip"):
+    for name in ("device_common.h", "replay_segments.h", "replay_apart.h", "kernels.hip"):
         with open(os.path.join(csrc, name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
@@ -365,7 +365,8 @@ def main():
     segs_mean = rp["segment_refs"] / max(N, 1)
     if rp["path"] == 2:
         bpr = algorithmic_bytes_per_routing_segments(wl.R, segs_mean, outputs_bytes=8)   # ttft f64
-        kernel = "replay_segments_kernel"
+        # (a workgroup of six wavefronts per replay, of eight per two replays, or of four)
+        kernel = "replay_apart_kernel" if P <= 512 else "replay_apart_pairs_kernel" if P <= 1024 and wl.R <= 32 else "replay_segments_kernel"
     else:
         bpr = algorithmic_bytes_per_routing(wl.R, n_mean, hit_mean, outputs_bytes=9)
         kernel = "replay_blocks_kernel"
