@@ -153,10 +153,11 @@ def cpu_baseline(wl, params, n_req, threads, online=None, engine=None, proxy=Non
     return threads * tr.N / dt, dt, tr.N
 
 
-def section_table(sec, N, P, R):
+def section_table(sec, N, P, waves):
     """The timed instantiation's per-wavefront section budget as text: shader-clock cycles per request of each
     of the wavefronts of a replay (mean over replays), between the marks the kernel sets, and the deciding wavefront's
-    event counts.  sec = the [P, 3, 12] array of gorgo_eval_population_sections."""
+    event counts.  sec = the [P, 3, 12] array of gorgo_eval_population_sections; waves = wavefronts of a workgroup (six per
+    replay, eight per two, of which the serving and the retiring one are each replay's own, or four)."""
     m = (sec.astype(np.float64) / max(N, 1)).mean(axis=0)
     lines = []
     decide = {0: "waiting at the meeting X", 1: "patching, prefix match", 2: "log records asked for and taken", 3: "score, minimum, announcement",
@@ -167,7 +168,7 @@ def section_table(sec, N, P, R):
     book = {2: "stores", 3: "waiting at the meeting X"}
     wavefronts = [("deciding wavefront (lane = replica):", 0, decide), ("queue wavefront (lane = service slot):", 1, queue),
                   ("front-end wavefront:", 2, front), ("book-keeping wavefront:", 2, book)]
-    if P <= (768 if R <= 12 else 512):                       # (six wavefronts per replay)
+    if waves >= 6:
         wavefronts = [("deciding wavefront (lane = replica):", 0, {k: decide[k] for k in (0, 1, 3)}),
                       ("serving wavefront (lane = service slot):", 1, {k: queue[k] for k in (0, 1, 9, 5)}),
                       ("retiring wavefront:", 1, {2: "requests in flight", 3: "waiting at the meeting X"}),
@@ -405,7 +406,7 @@ def main():
         t_ms = g.last_eval_kernel_ms()["replay_ms"]
         print(f"[bench] timed instantiation: replay kernel {t_ms:.1f} ms = {t_ms * 1e3 / max(N, 1):.3f} us per request step "
               f"(plain kernel: {k_ms * 1e3 / max(N, 1):.3f})", file=sys.stderr)
-        print(section_table(res.sections.cpu().numpy(), N, P, wl.R), file=sys.stderr, flush=True)
+        print(section_table(res.sections.cpu().numpy(), N, P, g.replay_workgroups(tr, model, P)[1]), file=sys.stderr, flush=True)
         del res
 
     mode = "P online tuners (window 128, hop 32) over the trace per step" if args.online else \

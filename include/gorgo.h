@@ -98,12 +98,14 @@ typedef struct gorgo_model {
  *     results; they differ in workspace size and speed.  Automatic picks segment rows when the trace is
  *     chain-consistent and its requests average at most 16 segments.  Size the workspace with the same options
  *     as the evaluation.
- *   replay_packing: with at most 32 replicas, at most 16 slots per replica and an even number of replays,
- *     gorgo_eval_population and gorgo_es_step can run two replays per workgroup of the segment-row kernel
- *     (a replay keeps one lane per replica, so half of a 64-lane wavefront idles otherwise).  A replay is a serial
- *     chain, so this pays when the replays would not all be resident on the GPU at once (with up to 256 service
- *     slots more than 1,280 of them): 2 (default) packs then, up to twice as many, 1 whenever the shape allows,
- *     0 never.
+ *   replay_packing: a replay keeps one lane per replica, so with at most 32 replicas two replays can share a workgroup of a
+ *     segment-row kernel.  There are two such kernels.  Packed (gorgo_eval_population, gorgo_es_step; an even number of replays, at
+ *     most 16 slots per replica): five wavefronts, four of them as one replay has and a second queue wavefront.  Pairs (these two, online
+ *     tuners, the engine model, imperfect proxy knowledge and least-request; any number of replays): eight wavefronts.  Values: 2
+ *     (default) packs when the replays would not all be resident on the GPU at once, up to twice as many, and takes pairs for up
+ *     to 1,024 replays, as many as are resident, where they are the faster; 1 packs whenever the shape allows and else takes
+ *     pairs wherever they are resident, down to a single replay; 0 never lets replays share a workgroup.
+ *     gorgo_query_replay_workgroups tells what a launch gets.
  *   handover_poll_limit: how many times wavefronts that hand over through polled words poll before a replay is
  *     given up (default 2^24; must be >= 0).  The value has no effect and no replay is given up: the wavefronts of a replay
  *     meet at workgroup barriers, and where one looks at a word until another has written it (replays of six wavefronts), the
@@ -391,19 +393,31 @@ int gorgo_last_eval_kernel_ms(double* fill_ms, double* replay_ms, double* select
  * advances, 10 log records dropped because they own nothing, 11 ownership walks), [p][1] the queue wavefront (0 times
  * and lengths, 1 waiting at X, 2 retiring, 5 outputs and tuner, 6 batch turnover, 9 choice and service), [p][2] the
  * front-end wavefront (0 descriptors and row cells, 1 waiting) and the book-keeping wavefront (2 stores, 3 waiting at
- * X).  Where a replay has six wavefronts (launches of up to 512 replays, 768 with up to 12 replicas, but for caches that hold fewer than
- * 15 requests with more than 32 replicas, fewer than 10 with 24 or more), the deciding one has no sections 2 and 4 to 6, [p][1] is the serving wavefront (without 2) and the retiring one (2 retiring, 3 waiting at X), and [p][2] also has the
- * evicting one (4 cursors, 5 waiting at X).  Needs the segment formulation without packing; everything else as gorgo_eval_population. */
+ * X).  The kernel is the one that gorgo_eval_population would run (gorgo_query_replay_workgroups), except that a launch that
+ * would be packed has four wavefronts per replay.  Where they are six or eight, the deciding one has no sections 2 and 4 to 6,
+ * [p][1] is the serving wavefront (without 2) and the retiring one (2 retiring, 3 waiting at X), and [p][2] also has the evicting one
+ * (4 cursors, 5 waiting at X).  Of eight, the wavefronts that two replays share write the same cycles for both, the counts each
+ * replay's own.  Needs the segment formulation; everything else as gorgo_eval_population. */
 #define GORGO_SECTIONS 12
 int gorgo_eval_population_sections(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* options, const double* rtt_ms,
                                    const double* params, const double* scale, int32_t P,
                                    const gorgo_outputs* outputs, void* workspace, size_t workspace_bytes,
                                    void* hip_stream, uint64_t* sections);
 
-/* Whether gorgo_eval_population with P replays of this trace and model would pack them under these options
- * (*packed = 1) or not (0).  Asks the current device how many workgroups it holds at once. */
+/* Whether gorgo_eval_population with P replays of this trace and model would run the packed kernel under these options
+ * (*packed = 1) or not (0, also where it runs pairs of eight wavefronts: see gorgo_options and the next query).  Asks the current
+ * device how many workgroups it holds at once. */
 int gorgo_query_replay_packing(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* options, int32_t P,
                                int32_t* packed);
+
+/* How an evaluation of P replays is spread over workgroups, given the workspace it asks for: *replays per workgroup and
+ * the *wavefronts of one (each pointer may be NULL).  online, engine and proxy are NULL where the evaluation has none; of their
+ * contents only online->window counts, which LDS depends on.  In the segment formulation 1 replay and 4 or 6 wavefronts, 2 and 5
+ * (packed) or 8 (pairs), or 0 and 6: the policy dictates the routes and each replica of a replay has a workgroup.  Block by block 1
+ * replay.  Which one it is makes no difference to results. */
+int gorgo_query_replay_workgroups(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* options, int32_t policy,
+                                  const gorgo_online* online, const gorgo_engine* engine, const gorgo_proxy* proxy, int32_t P,
+                                  int32_t* replays, int32_t* wavefronts);
 
 /* Rows of cells that a replay of this trace keeps in the segment formulation (0 for a trace that is not
  * chain-consistent).  A segment only needs a row from the first to the last request that references it, which the

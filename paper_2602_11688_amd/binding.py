@@ -50,8 +50,8 @@ class _Proxy(C.Structure):
 
 class Options(C.Structure):
     """gorgo_options: how an evaluation is carried out (no result depends on it), passed to the library with every
-    call.  replay_path 0 automatic / 1 hashed block tables / 2 dense segment rows; replay_packing 0 never / 1 whenever
-    the shape allows / 2 automatic; handover_poll_limit has no effect (no kernel polls);
+    call.  replay_path 0 automatic / 1 hashed block tables / 2 dense segment rows; replay_packing (two replays in a workgroup)
+    0 never / 1 whenever the shape allows / 2 automatic; handover_poll_limit has no effect (no kernel polls);
     table_factor_percent 110..1600."""
     _fields_ = [("replay_path", C.c_int32), ("replay_packing", C.c_int32), ("handover_poll_limit", C.c_int32),
                 ("table_factor_percent", C.c_int32)]
@@ -109,6 +109,8 @@ def lib():
         L.gorgo_es_workspace_bytes.argtypes = [vp, C.POINTER(_Model), C.POINTER(Options), i32, C.POINTER(C.c_size_t)]
         L.gorgo_es_step.argtypes = [vp, C.POINTER(_Model), C.POINTER(Options), vp, dbl, i32, C.POINTER(EsState), vp, vp, vp, C.c_size_t, vp]
         L.gorgo_query_replay_packing.argtypes = [vp, C.POINTER(_Model), C.POINTER(Options), i32, C.POINTER(i32)]
+        L.gorgo_query_replay_workgroups.argtypes = [vp, C.POINTER(_Model), C.POINTER(Options), i32, C.POINTER(_Online), C.POINTER(_Engine),
+                                                    C.POINTER(_Proxy), i32, C.POINTER(i32), C.POINTER(i32)]
         L.gorgo_query_replay_path.argtypes = [vp, C.POINTER(Options), C.POINTER(i32), C.POINTER(i64), C.POINTER(i64)]
         L.gorgo_query_row_slots.argtypes = [vp, C.POINTER(i64)]
         L.gorgo_query_row_slots.restype = C.c_int
@@ -118,7 +120,7 @@ def lib():
         for name in ("gorgo_load_trace", "gorgo_load_trace_arrays", "gorgo_trace_info", "gorgo_workspace_bytes", "gorgo_policy_workspace_bytes",
                      "gorgo_eval_population", "gorgo_eval_population_sections", "gorgo_trace_to_device", "gorgo_eval_population_static", "gorgo_eval_online", "gorgo_eval_policy", "gorgo_eval_engine", "gorgo_eval_proxy", "gorgo_es_init", "gorgo_es_sample", "gorgo_es_propose",
                      "gorgo_es_update", "gorgo_es_workspace_bytes", "gorgo_es_step",
-                     "gorgo_last_eval_kernel_ms", "gorgo_query_replay_packing", "gorgo_query_replay_path"):
+                     "gorgo_last_eval_kernel_ms", "gorgo_query_replay_packing", "gorgo_query_replay_workgroups", "gorgo_query_replay_path"):
             getattr(L, name).restype = C.c_int
         _lib = L
     return _lib
@@ -241,17 +243,30 @@ def set_table_factor_percent(pct: int):
 
 
 def set_replay_packing(mode: int) -> None:
-    """Two replays per wavefront pair: 0 never, 1 whenever the shape allows it, 2 (default) when the replays would not
-    all be resident at once otherwise; results do not depend on it."""
+    """Two replays in a workgroup, with at most 32 replicas, whatever the entry point: 0 never, 1 whenever the shape allows it, 2
+    (default) where it is the faster; results do not depend on it.  replay_workgroups() tells what a launch gets."""
     _set_default("replay_packing", mode, 0, 2, "replay_packing")
 
 
 def replay_packing(trace: "Trace", model: "Model", P: int, options: Optional[Options] = None) -> bool:
-    """Whether eval_population with P replays would run two replays per wavefront pair under the options."""
+    """Whether eval_population with P replays would run the packed kernel (two replays on five wavefronts) under the options."""
     out = C.c_int32()
     m = model.c()
     _check(lib().gorgo_query_replay_packing(trace._h, C.byref(m), _opt(options), P, C.byref(out)))
     return bool(out.value)
+
+
+def replay_workgroups(trace: "Trace", model: "Model", P: int, policy: str = "cost-model", window: int = 0, engine: bool = False,
+                      proxy: bool = False, options: Optional[Options] = None) -> tuple:
+    """(replays, wavefronts) of a workgroup of an evaluation of P replays under the options: (1, 4), (1, 6), (2, 5), (2, 8), or
+    (0, 6) where each replica of a replay has a workgroup; block by block (1, 3 or 4).  window: the online tuner's, 0 for none."""
+    replays, wavefronts = C.c_int32(), C.c_int32()
+    m, online, eng, px = model.c(), _Online(), _Engine(), _Proxy()
+    online.window = window
+    _check(lib().gorgo_query_replay_workgroups(trace._h, C.byref(m), _opt(options), _policy_code(policy), C.byref(online) if window else None,
+                                               C.byref(eng) if engine else None, C.byref(px) if proxy else None, P,
+                                               C.byref(replays), C.byref(wavefronts)))
+    return replays.value, wavefronts.value
 
 
 def set_handover_poll_limit(polls: int):

@@ -201,6 +201,26 @@ int gorgo_query_replay_packing(const gorgo_trace* t, const gorgo_model* m, const
     return GORGO_OK;
 }
 
+int gorgo_query_replay_workgroups(const gorgo_trace* t, const gorgo_model* m, const gorgo_options* options, int32_t policy,
+                                  const gorgo_online* online, const gorgo_engine* engine, const gorgo_proxy* proxy, int32_t P,
+                                  int32_t* replays, int32_t* wavefronts) {
+    clear_error();
+    if (policy < GORGO_POLICY_COST_MODEL || policy > GORGO_POLICY_RANDOM)
+        return fail(GORGO_ERR_INVALID_ARG, "policy must be 0 (cost model) .. 3 (random)");
+    if ((online || proxy) && policy != GORGO_POLICY_COST_MODEL)
+        return fail(GORGO_ERR_INVALID_ARG, "a tuner and imperfect proxy knowledge concern the cost model, not the baseline policies");
+    if (online && (online->window < 1 || online->window > 1024)) return fail(GORGO_ERR_INVALID_ARG, "window must be in 1..1024");
+    int rc = check_model(t, m);
+    if (rc) return rc;
+    Plan pl;
+    rc = make_plan(t, m, options, P, nullptr, &pl, SIZE_MAX, dictates(policy));
+    if (rc) return rc;
+    const Workgroups w = replay_workgroups(pl, policy, online ? online->window : 0, engine != nullptr, proxy != nullptr);
+    if (replays) *replays = w.replays;
+    if (wavefronts) *wavefronts = w.wavefronts;
+    return GORGO_OK;
+}
+
 int gorgo_query_row_slots(const gorgo_trace* t, int64_t* slots) {
     clear_error();
     if (!t) return fail(GORGO_ERR_INVALID_ARG, "trace is NULL");

@@ -178,6 +178,10 @@ struct ProxyLaunch {
 
 // kernels.hip
 bool pack_replays(const Plan& pl, int64_t rows);     // rows of one replay: its segments + 2
+struct Workgroups {
+    int32_t replays, wavefronts;         // of a workgroup (0 replays: a workgroup for each replica of a replay)
+};
+Workgroups replay_workgroups(const Plan& pl, int32_t policy, int32_t window, bool engine, bool proxy);      // window 0: no tuner
 int launch_replay(const gorgo_trace* t, const Plan& pl, const double* d_rtt, const double* d_params,
                   const double* d_scale, uint8_t* route, uint16_t* hit, double* ttft, double* e2e,
                   void* workspace, void* stream, const OnlineLaunch* online = nullptr,

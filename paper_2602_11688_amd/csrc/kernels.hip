@@ -506,17 +506,33 @@ bool pair_replays(const Plan& pl, int mode, bool engine, bool proxy) {
     return (engine || proxy) && pl.R >= 16 && pl.P > 256 && pl.requests_held >= (engine ? 12.0 : 30.0);
 }
 
+// Which of the segment-row kernels takes a launch, `window` the tuner's.  (The answer is the launch's, gorgo_query_replay_workgroups'
+// and, for want of a timed instantiation of the packed one, nearly the section timing's.)
+enum SegmentKernel { FOUR_WAVEFRONTS, SIX_WAVEFRONTS, PAIRS, PACKED };
+SegmentKernel segment_kernel(const Plan& pl, int mode, bool engine, bool proxy, int32_t window) {
+    const int64_t rows = pl.nseg + 2;
+    const size_t lds = replay_queue_lds_bytes(pl.R, pl.B, engine, mode == MODE_ONLINE ? window : 0);
+    if (mode == MODE_COST_MODEL && !engine && !proxy && pack_replays(pl, rows)) return PACKED;
+    if ((mode == MODE_COST_MODEL || mode == MODE_ONLINE || mode == MODE_LEAST_REQUEST) && pairs_resident(pl, proxy, 2 * lds, rows) &&
+        pair_replays(pl, mode, engine, proxy))
+        return PAIRS;
+    const bool waits = (mode == MODE_COST_MODEL || mode == MODE_AFFINITY) && !engine && !proxy;
+    const double least = waits ? spread_least_held(pl, mode == MODE_AFFINITY) : 0.0;
+    return spread_replays(pl, proxy, lds, mode == MODE_ONLINE && engine && proxy ? 2 : 3, least) ? SIX_WAVEFRONTS : FOUR_WAVEFRONTS;
+}
+
+int mode_of(int32_t policy, bool online) {
+    return online ? MODE_ONLINE
+                  : policy == 0 ? MODE_COST_MODEL : policy == 1 ? MODE_LEAST_REQUEST : policy == 2 ? MODE_AFFINITY : MODE_RANDOM;
+}
+
 // The segment-row kernels' instantiations: every mode with either replica model; imperfect proxy knowledge concerns the
 // cost model (fixed weights or tuned online) only.
 template <int MODE>
-void launch_segments(bool engine, bool proxy, const Plan& pl, hipStream_t s, const SegArgs& a) {
+void launch_segments(SegmentKernel kernel, bool engine, bool proxy, const Plan& pl, hipStream_t s, const SegArgs& a) {
     const size_t lds = replay_queue_lds_bytes(pl.R, pl.B, engine, a.window);
     const dim3 grid((unsigned)pl.P);
-    const bool waits = (MODE == MODE_COST_MODEL || MODE == MODE_AFFINITY) && !engine && !proxy;
-    const double least = waits ? spread_least_held(pl, MODE == MODE_AFFINITY) : 0.0;
-    constexpr bool PAIRS = MODE == MODE_COST_MODEL || MODE == MODE_ONLINE || MODE == MODE_LEAST_REQUEST;
-    const bool pairs = PAIRS && pairs_resident(pl, proxy, 2 * lds, a.nseg) && pair_replays(pl, MODE, engine, proxy);
-    if (!pairs && spread_replays(pl, proxy, lds, MODE == MODE_ONLINE && engine && proxy ? 2 : 3, least)) {
+    if (kernel == SIX_WAVEFRONTS) {
         const dim3 block(APART_WAVES * WAVE);
         if constexpr (MODE == MODE_COST_MODEL || MODE == MODE_ONLINE) {
             if (proxy) {
@@ -529,8 +545,8 @@ void launch_segments(bool engine, bool proxy, const Plan& pl, hipStream_t s, con
         else hipLaunchKernelGGL((replay_apart_kernel<MODE, false, false>), grid, block, lds, s, a);
         return;
     }
-    if constexpr (PAIRS) {
-        if (pairs) {
+    if constexpr (MODE == MODE_COST_MODEL || MODE == MODE_ONLINE || MODE == MODE_LEAST_REQUEST) {
+        if (kernel == PAIRS) {
             const dim3 grid2((unsigned)((pl.P + 1) / 2)), block(apart_threads<2>());
             if constexpr (MODE != MODE_LEAST_REQUEST) {
                 if (proxy) {
@@ -646,6 +662,17 @@ void launch_blocks(bool engine, bool proxy, dim3 grid, size_t lds, hipStream_t s
 
 }  // namespace
 
+Workgroups replay_workgroups(const Plan& pl, int32_t policy, int32_t window, bool engine, bool proxy) {
+    if (pl.path != PATH_SEGMENTS) return {1, pl.row_slots > 0 ? ROW_WAVES : BLOCK_THREADS / WAVE};
+    if (pl.each) return {0, APART_WAVES};
+    switch (segment_kernel(pl, mode_of(policy, window > 0), engine, proxy, window)) {
+        case SIX_WAVEFRONTS: return {1, apart_threads<1>() / WAVE};
+        case PAIRS: return {2, apart_threads<2>() / WAVE};
+        case PACKED: return {2, seg_threads<2>() / WAVE};
+        default: return {1, seg_threads<1>() / WAVE};
+    }
+}
+
 int launch_replay(const gorgo_trace* t, const Plan& pl, const double* d_rtt, const double* d_params,
                   const double* d_scale, uint8_t* route, uint16_t* hit, double* ttft, double* e2e,
                   void* workspace, void* stream, const OnlineLaunch* online, const PolicyLaunch* policy,
@@ -723,35 +750,37 @@ int launch_replay(const gorgo_trace* t, const Plan& pl, const double* d_rtt, con
                            proxy->alpha);
         if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "launch smooth_rtt");
     }
-    const int mode = online ? MODE_ONLINE
-                            : !policy || policy->policy == 0 ? MODE_COST_MODEL
-                            : policy->policy == 1 ? MODE_LEAST_REQUEST
-                            : policy->policy == 2 ? MODE_AFFINITY : MODE_RANDOM;
+    const int mode = mode_of(policy ? policy->policy : 0, online != nullptr);
     // (a row is written through before it is first read -- the request that brings a segment into a row slot resets the
     // row -- so only the never-cached row needs a value beforehand)
     if ((rc = prepare(pl, const_cast<double*>(d_rtt), segments ? a.last : nullptr, a.nseg, s))) return rc;
     if (segments) {
         mark(1, s);
         if (pl.N > 0 || online) {      // (an empty trace still reports the tuner's initial state)
+            const SegmentKernel kernel = pl.each ? SIX_WAVEFRONTS : segment_kernel(pl, mode, engine != nullptr, proxy != nullptr, a.window);
+            const size_t lds = replay_queue_lds_bytes(pl.R, pl.B, false, 0);
             if (pl.each) {
                 if ((rc = launch_each(t, pl, mode, engine != nullptr, a, ws, s))) return rc;
-            } else if (mode == MODE_COST_MODEL && !engine && !proxy && !sections && pack_replays(pl, a.nseg)) {
-                hipLaunchKernelGGL((replay_segments_kernel<MODE_COST_MODEL, false, false, 2>), dim3((unsigned)(pl.P / 2)),
-                                   dim3(seg_threads<2>()), 2 * replay_queue_lds_bytes(pl.R, pl.B, false, 0), s, a);
-            } else if (sections && spread_replays(pl, false, replay_queue_lds_bytes(pl.R, pl.B, false, 0), 3, spread_least_held(pl, false))) {
-                hipLaunchKernelGGL((replay_apart_kernel<MODE_COST_MODEL, false, false, true>), dim3((unsigned)pl.P),
-                                   dim3(APART_WAVES * WAVE), replay_queue_lds_bytes(pl.R, pl.B, false, 0), s, a);
+            } else if (sections && kernel == SIX_WAVEFRONTS) {
+                hipLaunchKernelGGL((replay_apart_kernel<MODE_COST_MODEL, false, false, true>), dim3((unsigned)pl.P), dim3(apart_threads<1>()),
+                                   lds, s, a);
+            } else if (sections && kernel == PAIRS) {
+                hipLaunchKernelGGL((replay_apart_pairs_timed_kernel<MODE_COST_MODEL, false, false>), dim3((unsigned)((pl.P + 1) / 2)),
+                                   dim3(apart_threads<2>()), 2 * lds, s, a);
             } else if (sections) {
-                const dim3 grid((unsigned)pl.P), block(seg_threads<1>());
-                hipLaunchKernelGGL((replay_segments_kernel<MODE_COST_MODEL, false, false, 1, true>), grid, block,
-                                   replay_queue_lds_bytes(pl.R, pl.B, false, 0), s, a);
+                hipLaunchKernelGGL((replay_segments_kernel<MODE_COST_MODEL, false, false, 1, true>), dim3((unsigned)pl.P), dim3(seg_threads<1>()),
+                                   lds, s, a);
+            } else if (kernel == PACKED) {
+                hipLaunchKernelGGL((replay_segments_kernel<MODE_COST_MODEL, false, false, 2>), dim3((unsigned)(pl.P / 2)),
+                                   dim3(seg_threads<2>()), 2 * lds, s, a);
             } else {
+                const bool eng = engine != nullptr;
                 switch (mode) {
-                    case MODE_COST_MODEL: launch_segments<MODE_COST_MODEL>(engine != nullptr, proxy != nullptr, pl, s, a); break;
-                    case MODE_ONLINE: launch_segments<MODE_ONLINE>(engine != nullptr, proxy != nullptr, pl, s, a); break;
-                    case MODE_LEAST_REQUEST: launch_segments<MODE_LEAST_REQUEST>(engine != nullptr, false, pl, s, a); break;
-                    case MODE_AFFINITY: launch_segments<MODE_AFFINITY>(engine != nullptr, false, pl, s, a); break;
-                    default: launch_segments<MODE_RANDOM>(engine != nullptr, false, pl, s, a); break;
+                    case MODE_COST_MODEL: launch_segments<MODE_COST_MODEL>(kernel, eng, proxy != nullptr, pl, s, a); break;
+                    case MODE_ONLINE: launch_segments<MODE_ONLINE>(kernel, eng, proxy != nullptr, pl, s, a); break;
+                    case MODE_LEAST_REQUEST: launch_segments<MODE_LEAST_REQUEST>(kernel, eng, false, pl, s, a); break;
+                    case MODE_AFFINITY: launch_segments<MODE_AFFINITY>(kernel, eng, false, pl, s, a); break;
+                    default: launch_segments<MODE_RANDOM>(kernel, eng, false, pl, s, a); break;
                 }
             }
             if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "launch replay_segments_kernel");

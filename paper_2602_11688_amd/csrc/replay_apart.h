@@ -75,6 +75,20 @@ template <int PACK>
 __device__ __forceinline__ bool pair_has(const SegArgs& a, size_t p0, int which) {
     return PACK == 1 || which == 0 || p0 + 1 < (size_t)a.P;
 }
+// The sum over the lanes of replay `which` of a workgroup.
+template <int PACK>
+__device__ __forceinline__ unsigned replay_sum_u32(unsigned x, int which) {
+    const int scan = (int)wave_scan_u32(x), lower = __builtin_amdgcn_readlane(scan, HALF - 1), all = __builtin_amdgcn_readlane(scan, WAVE - 1);
+    return (unsigned)(PACK == 1 ? all : which == 0 ? lower : all - lower);
+}
+// What a wavefront of a timed instantiation writes: sections first .. last of `row` for each of the workgroup's replays (a wavefront
+// that has both takes its time for both).
+template <int PACK, class Clock>
+__device__ __forceinline__ void write_sections(const SegArgs& a, size_t p0, int row, int first, int last, const Clock& clk, int lane) {
+    if (!a.sections || lane != 0) return;
+    for (int which = 0; which < PACK && pair_has<PACK>(a, p0, which); ++which)
+        for (int k = first; k <= last; ++k) a.sections[((p0 + which) * 3 + row) * SECTIONS + k] = clk.acc[k];
+}
 
 // The compiler moves no access to memory across this.
 __device__ __forceinline__ void in_order() { __atomic_signal_fence(__ATOMIC_SEQ_CST); }
@@ -265,7 +279,7 @@ __device__ __forceinline__ void apart_evict_wave(const SegArgs& a, size_t p0, in
     c1.most = c2.most = a.look;
     c1.near = c2.near = a.near;
     const int every = look_every(R);
-    int n_walks = 0;
+    int n_walks[PACK] = {};
     // (the deciding wavefront may look in between: `hi` is written first and read last.  LDS performs a wavefront's accesses in their
     // order, so relaxed ones that the compiler keeps in order will do)
     auto publish = [&]() {
@@ -303,9 +317,10 @@ __device__ __forceinline__ void apart_evict_wave(const SegArgs& a, size_t p0, in
             // these form runs; each run moves its owner's `own` to the end of the run.  Only what is held matters (what is
             // evicted belongs to requests the cursor has passed, or to the cursor's request beyond its position).  The rows are
             // read as they still are: the book-keeping wavefront waits.
-            ++n_walks;
             const int of_lane = __builtin_ctzll(walks);                  // (of either replay)
             const bool second = PACK == 2 && of_lane >= HALF;
+            n_walks[0] += second ? 0 : 1;
+            n_walks[PACK - 1] += second ? 1 : 0;
             const size_t its_p = p0 + (second ? 1 : 0);
             LogRec* const its_log = a.log + its_p * ((size_t)N + 1);
             const char* const cells = reinterpret_cast<const char*>(a.last + its_p * (size_t)a.nseg * R) + (second ? of_lane - HALF : of_lane) * 4;
@@ -393,18 +408,19 @@ __device__ __forceinline__ void apart_evict_wave(const SegArgs& a, size_t p0, in
         }
         if (flags & DESC_SYNC) meet(true);                           // Y(r)
     }
-    if (TIMED && a.sections) {
-        // (with statistics of the eviction walk, summed over the replicas)
-        const unsigned spot = wave_sum_u32((unsigned)c1.n_spot), adv = wave_sum_u32((unsigned)c1.n_adv),
-                       dead = wave_sum_u32((unsigned)c1.n_dead);
-        if (lane == 0) {
-            unsigned long long* const out = a.sections + p0 * 3 * SECTIONS;
-            out[2 * SECTIONS + 4] = clk.acc[4];
-            out[2 * SECTIONS + 5] = clk.acc[5];
-            out[8] = spot;
-            out[9] = adv;
-            out[10] = dead;
-            out[11] = (unsigned)n_walks;
+    if (TIMED) {
+        write_sections<PACK>(a, p0, 2, 4, 5, clk, lane);
+        // statistics of the eviction walk, summed over the replicas
+        for (int which = 0; which < PACK; ++which) {
+            const unsigned spot = replay_sum_u32<PACK>((unsigned)c1.n_spot, which), adv = replay_sum_u32<PACK>((unsigned)c1.n_adv, which),
+                           dead = replay_sum_u32<PACK>((unsigned)c1.n_dead, which);
+            if (a.sections && lane == 0 && pair_has<PACK>(a, p0, which)) {
+                unsigned long long* const out = a.sections + (p0 + which) * 3 * SECTIONS;
+                out[8] = spot;
+                out[9] = adv;
+                out[10] = dead;
+                out[11] = (unsigned)n_walks[which];
+            }
         }
     }
 }
@@ -541,10 +557,7 @@ __device__ __forceinline__ void apart_book_wave(const SegArgs& a, size_t p0, int
         if (flags & DESC_SYNC) meet(false);                          // Y(r)
     }
     touched.done();
-    if (TIMED && a.sections && lane == 0) {
-        a.sections[(p0 * 3 + 2) * SECTIONS + 2] = clk.acc[2];
-        a.sections[(p0 * 3 + 2) * SECTIONS + 3] = clk.acc[3];
-    }
+    if (TIMED) write_sections<PACK>(a, p0, 2, 2, 3, clk, lane);
 }
 
 // ---------------------------------------------------------------------------------------------- retiring
@@ -581,9 +594,7 @@ __device__ __forceinline__ void apart_retire_wave(const SegArgs& a, size_t p0, i
         retire(Q.due(t2, lane), t2, r + 2);
         t1 = t2;
     }
-    if (TIMED && a.sections && lane == 0) {
-        for (int k = 2; k < 4; ++k) a.sections[(p * 3 + 1) * SECTIONS + k] = clk.acc[k];
-    }
+    if (TIMED && pair_has<PACK>(a, p0, which)) write_sections<1>(a, p, 1, 2, 3, clk, lane);
 }
 
 // ---------------------------------------------------------------------------------------------- serving
@@ -680,9 +691,10 @@ __device__ __forceinline__ void apart_serve_wave(const SegArgs& a, size_t p0, in
             if (a.e2e) a.e2e[o] = o_e2e;
         }
     }
-    if (TIMED && a.sections && lane == 0)
-        for (int k = 0; k < SECTIONS; ++k)
-            if (k != 2 && k != 3) a.sections[(p * 3 + 1) * SECTIONS + k] = clk.acc[k];
+    if (TIMED && there) {
+        write_sections<1>(a, p, 1, 0, 1, clk, lane);
+        write_sections<1>(a, p, 1, 4, SECTIONS - 1, clk, lane);
+    }
     tuner.results();
 }
 
@@ -954,8 +966,7 @@ __device__ __forceinline__ void apart_decide_wave(const SegArgs& a, size_t p0, i
         clk.tick(0);                                                 // waiting at X
         before = flags;
     }
-    if (TIMED && a.sections && lane == 0)            // (the evicting wavefront writes the counts)
-        for (int k = 0; k < 8; ++k) a.sections[p0 * 3 * SECTIONS + k] = clk.acc[k];
+    if (TIMED) write_sections<PACK>(a, p0, 0, 0, 7, clk, lane);     // (the evicting wavefront writes the counts)
 }
 
 // Replay p0, or replays p0 and p0 + 1, by one workgroup.  Three of a replay each fit a CU by their registers, two in the proxy
@@ -1032,6 +1043,13 @@ template <int MODE, bool ENGINE, bool PROXY>
 __global__ void __launch_bounds__(apart_threads<2>(), 4) replay_apart_pairs_kernel(SegArgs a) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     apart_replay<MODE, ENGINE, PROXY, 2, false>([]() -> const SegArgs& { return kernel_args<SegArgs>(); }, 2 * (size_t)blockIdx.x, lds_raw);
+}
+
+// The timed instantiation.
+template <int MODE, bool ENGINE, bool PROXY>
+__global__ void __launch_bounds__(apart_threads<2>(), 4) replay_apart_pairs_timed_kernel(SegArgs a) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    apart_replay<MODE, ENGINE, PROXY, 2, true>([]() -> const SegArgs& { return kernel_args<SegArgs>(); }, 2 * (size_t)blockIdx.x, lds_raw);
 }
 
 }  // namespace gorgo

@@ -889,7 +889,8 @@ __device__ __forceinline__ void front_wave(const SegArgs& a, int lane, Comm* com
     }
     touched.done();
     if (TIMED && a.sections && lane == 0)            // (the book-keeping wavefront writes the next two)
-        for (int i = 0; i < 2; ++i) a.sections[(p * 3 + 2) * SECTIONS + i] = clk.acc[i];
+        for (int which = 0; which < (pair ? 2 : 1); ++which)
+            for (int i = 0; i < 2; ++i) a.sections[((p + which) * 3 + 2) * SECTIONS + i] = clk.acc[i];
 }
 
 // ---------------------------------------------------------------------------------------------- tuner, probe epochs

@@ -31,6 +31,7 @@ void perform() {
 namespace gorgo {
 
 bool pack_replays(const Plan&, int64_t) { return false; }
+Workgroups replay_workgroups(const Plan&, int32_t, int32_t, bool, bool) { return {1, 4}; }
 int launch_replay(const gorgo_trace*, const Plan&, const double*, const double*, const double*, uint8_t*, uint16_t*, double*,
                   double*, void*, void*, const OnlineLaunch*, const PolicyLaunch* policy, const EngineLaunch*, const ProxyLaunch*,
                   unsigned long long*) {

@@ -8,6 +8,7 @@ namespace gorgo {
 static int no_device(const char* what) { return fail(GORGO_ERR_DEVICE, std::string(what) + ": no device in this build"); }
 
 bool pack_replays(const Plan&, int64_t) { return false; }
+Workgroups replay_workgroups(const Plan&, int32_t, int32_t, bool, bool) { return {1, 4}; }
 int launch_replay(const gorgo_trace*, const Plan&, const double*, const double*, const double*, uint8_t*, uint16_t*, double*,
                   double*, void*, void*, const OnlineLaunch*, const PolicyLaunch*, const EngineLaunch*, const ProxyLaunch*,
                   unsigned long long*) {

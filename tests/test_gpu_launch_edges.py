@@ -77,23 +77,39 @@ def test_requests_that_are_waited_for(gap_ms, decode):
 
 
 def wavefronts(handle, model, rtt, P):
-    """Of each replay in a launch of P with fixed weights, by the sections of its time: the evicting wavefront's is one of six."""
-    res = g.eval_population(handle, model, rtt, np.tile([[0.5, 1.0, 0.1]], (P, 1)), np.ones(P), per_request=False, sections=True)
-    kinds = {(bool(x[0][2] > 0), bool(x[2][4] > 0)) for x in res.sections.cpu().numpy()}
-    return {frozenset([(True, False)]): 4, frozenset([(False, True)]): 6}[frozenset(kinds)]
+    """Of a workgroup in a launch of P replays with fixed weights, by the sections of its time: the evicting wavefront's is one of six
+    or eight, and of eight two replays share it.  Timed or not, the results are the same."""
+    call = lambda **kw: g.eval_population(handle, model, rtt, np.tile([[0.5, 1.0, 0.1]], (P, 1)), np.linspace(0.5, 2.0, P), per_request=False, **kw)
+    res, plain = call(sections=True), call()
+    assert torch.equal(res.p95_ttft_ms, plain.p95_ttft_ms) and torch.equal(res.p95_e2e_ms, plain.p95_e2e_ms)
+    sec = res.sections.cpu().numpy()
+    (kind,) = {(bool(x[0][2] > 0), bool(x[2][4] > 0)) for x in sec}
+    assert (sec[:, 0, [1, 3]] > 0).all() and (sec[:, 1, [1, 9]] > 0).all() and (sec[:, 2, :4] > 0).all()
+    if kind == (True, False):
+        return 4
+    assert kind == (False, True) and (sec[:, 1, [2, 3]] > 0).all() and (sec[:, 2, 5] > 0).all()
+    own = [(1, 1), (1, 2), (1, 9)]                           # the serving and the retiring wavefront
+    pairs = sec[:P // 2 * 2].reshape(P // 2, 2, 3, -1)
+    assert all((pairs[:, 0, i, j] != pairs[:, 1, i, j]).any() for i, j in own)
+    shared = [(pairs[:, 0, i, j] == pairs[:, 1, i, j]).all() for i, j in [(0, 1), (2, 0), (2, 2), (2, 4)]]
+    assert len(set(shared)) == 1
+    return 8 if shared[0] else 6
 
 
-@pytest.mark.parametrize("R,B,P,held,want", [(12, 2, 768, 0, 6), (12, 2, 769, 0, 4), (13, 2, 512, 0, 6), (13, 2, 513, 0, 4),
+@pytest.mark.parametrize("R,B,P,held,want", [(12, 2, 768, 0, 6), (12, 2, 769, 0, 8), (13, 2, 512, 0, 6), (13, 2, 513, 0, 8),
                                              (23, 2, 300, 5, 6), (24, 2, 300, 9.9, 4), (32, 2, 300, 10.1, 6), (33, 2, 300, 14.9, 4), (33, 2, 300, 15.1, 6), (64, 2, 2, 5, 4),
-                                             (64, 16, 512, 0, 6), (12, 64, 768, 0, 6)])
+                                             (64, 16, 512, 0, 6), (12, 64, 768, 0, 6), (33, 2, 513, 0, 4), (32, 8, 1024, 0, 8), (32, 8, 1025, 0, 4)])
 def test_which_launches_have_six_wavefronts(R, B, P, held, want):
-    """The number of replays, of replicas, and of requests that a cache holds; many slots (fixed weights fit all the same)."""
+    """The number of replays, of replicas, and of requests that a cache holds; many slots (fixed weights fit all the same).  What times a
+    launch is the kernel that it runs otherwise."""
     wl = tg.config(2, 400)
     blocks = int(np.diff(wl.trace.blk_off).max())
     mean = wl.trace.blk_off[-1] / wl.trace.N
     cache = int(held * mean)
     assert cache == 0 or cache >= blocks
-    assert wavefronts(load(wl.trace), g.Model(R, B, cache, 0.05, 20.0), np.linspace(5.0, 90.0, R), P) == want
+    handle, model = load(wl.trace), g.Model(R, B, cache, 0.05, 20.0)
+    assert g.replay_workgroups(handle, model, P) == (2 if want == 8 else 1, want)
+    assert wavefronts(handle, model, np.linspace(5.0, 90.0, R), P) == want
 
 
 @pytest.mark.parametrize("R,held", [(23, 5), (24, 8), (32, 11), (32, 13), (33, 12), (64, 14), (64, 24)])
