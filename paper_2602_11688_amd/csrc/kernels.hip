@@ -472,12 +472,12 @@ constexpr int SPREAD_WAITS_FROM = 24;       // replicas
 double spread_least_held(const Plan& pl, bool affinity) {
     return pl.R < SPREAD_WAITS_FROM ? 0.0 : pl.R <= HALF ? (affinity ? 12.0 : 10.0) : affinity ? 20.0 : 15.0;
 }
+int spread_up_to(const Plan& pl, int held) { return std::min(pl.R <= SPREAD_FEW_REPLICAS ? SPREAD_FEW_UP_TO : SPREAD_UP_TO, 256 * held); }
 bool spread_replays(const Plan& pl, bool proxy, size_t lds, int held, double least) {
-    if (pl.P > (pl.R <= SPREAD_FEW_REPLICAS ? SPREAD_FEW_UP_TO : SPREAD_UP_TO)) return false;
-    if (pl.requests_held < least) return false;
+    if (pl.P > spread_up_to(pl, held) || pl.requests_held < least) return false;
     const size_t fixed = proxy ? sizeof(ApartHandover<true>) : sizeof(ApartHandover<false>);
     const size_t per_cu = (size_t)160 * 1024 / ((fixed + lds + 1279) / 1280 * 1280);        // (given out in pieces of 1,280 bytes)
-    return pl.P <= 256 * std::min((int)per_cu, held);
+    return pl.P <= 256 * (int)per_cu;
 }
 
 // Whether the pairs of a launch, eight wavefronts each, are all resident: two workgroups for each of the 256 CUs, fewer where their
@@ -497,12 +497,14 @@ bool pairs_resident(const Plan& pl, bool proxy, size_t lds, int64_t rows) {
 // 32 0.677 / 0.757, 0.669 / 0.696, 0.658 / 0.664, 0.655 / 0.638, 0.652 / 0.620; tuner, 32 0.774 / 0.810, 0.760 / 0.751, 0.753 / 0.725, -, -;
 // engine model, 32 0.823 / 0.798 and, of 260 blocks, 0.831 / 0.858; proxy, 16 1.046 / 1.102, 0.995 / 1.002, 0.972 / 0.966, -, -; 32 -, 0.876 /
 // 0.956, 0.858 / 0.907, 0.845 / 0.866, 0.836 / 0.838.  401 replays, six each / pairs, 4,000 blocks: engine model, 16 replicas 0.714 / 0.700, 24 0.675 /
-// 0.657, 32 0.655 / 0.595; proxy, 16 0.763 / 0.717, 24 0.720 / 0.666, 32 0.706 / 0.642, and 12 0.822 / 0.842; the others within 1 %.)
-bool pair_replays(const Plan& pl, int mode, bool engine, bool proxy) {
+// 0.657, 32 0.655 / 0.595; proxy, 16 0.763 / 0.717, 24 0.720 / 0.666, 32 0.706 / 0.642, and 12 0.822 / 0.842; the others within 1 %.
+// Proxy, engine model and tuner together, of which 512 are resident with six wavefronts each; four each / pairs, 513 and 768 replays on 4
+// replicas of 8,000 blocks 1.507 / 1.010 and 1.521 / 1.050, on 12 1.449 / 1.002 and 1.442 / 1.028; 768 on 12 of 800 blocks 1.535 / 1.147.)
+bool pair_replays(const Plan& pl, int mode, bool engine, bool proxy, int held) {
     if (pl.packing == 1) return true;
     const bool few = pl.R <= 16;         // replicas
     if (pl.requests_held < (proxy ? (few ? 10.0 : 20.0) : engine ? 6.0 : mode == MODE_ONLINE ? 8.0 : few ? 9.0 : 12.0)) return false;
-    if (pl.P > (pl.R <= SPREAD_FEW_REPLICAS ? SPREAD_FEW_UP_TO : SPREAD_UP_TO)) return true;
+    if (pl.P > spread_up_to(pl, held)) return true;
     return (engine || proxy) && pl.R >= 16 && pl.P > 256 && pl.requests_held >= (engine ? 12.0 : 30.0);
 }
 
@@ -513,12 +515,13 @@ SegmentKernel segment_kernel(const Plan& pl, int mode, bool engine, bool proxy, 
     const int64_t rows = pl.nseg + 2;
     const size_t lds = replay_queue_lds_bytes(pl.R, pl.B, engine, mode == MODE_ONLINE ? window : 0);
     if (mode == MODE_COST_MODEL && !engine && !proxy && pack_replays(pl, rows)) return PACKED;
+    const int held = mode == MODE_ONLINE && engine && proxy ? 2 : 3;         // workgroups of six wavefronts, of a CU's registers
     if ((mode == MODE_COST_MODEL || mode == MODE_ONLINE || mode == MODE_LEAST_REQUEST) && pairs_resident(pl, proxy, 2 * lds, rows) &&
-        pair_replays(pl, mode, engine, proxy))
+        pair_replays(pl, mode, engine, proxy, held))
         return PAIRS;
     const bool waits = (mode == MODE_COST_MODEL || mode == MODE_AFFINITY) && !engine && !proxy;
     const double least = waits ? spread_least_held(pl, mode == MODE_AFFINITY) : 0.0;
-    return spread_replays(pl, proxy, lds, mode == MODE_ONLINE && engine && proxy ? 2 : 3, least) ? SIX_WAVEFRONTS : FOUR_WAVEFRONTS;
+    return spread_replays(pl, proxy, lds, held, least) ? SIX_WAVEFRONTS : FOUR_WAVEFRONTS;
 }
 
 int mode_of(int32_t policy, bool online) {

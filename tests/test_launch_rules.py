@@ -44,6 +44,15 @@ def test_by_the_number_of_replays(trace, kw):
     assert ask(trace, 32, 511, B=32, packing=1, **kw) == PAIRS and ask(trace, 32, 513, B=32, packing=1, **kw) == FOUR
 
 
+def test_proxy_engine_model_and_tuner(trace):
+    """Together they leave registers for two workgroups of six wavefronts on a compute unit, whatever the number of replicas."""
+    for R in (4, 12, 13):
+        for held in (0.0, 12.5):
+            assert ask(trace, R, 512, held, engine=True, proxy=True, **TUNER) == SIX
+            for P in (513, 600, 768, 769, 1024):
+                assert ask(trace, R, P, held, engine=True, proxy=True, **TUNER) == PAIRS
+
+
 def test_dictated_routes(trace):
     for policy in ("session-affinity", "random"):
         assert ask(trace, 13, 256, policy=policy) == EACH
