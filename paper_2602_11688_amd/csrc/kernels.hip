@@ -488,24 +488,49 @@ bool pairs_resident(const Plan& pl, bool proxy, size_t lds, int64_t rows) {
     const size_t per_cu = (size_t)160 * 1024 / ((fixed + lds + 1279) / 1280 * 1280);
     return (pl.P + 1) / 2 <= 256 * std::min((int)per_cu, 2);
 }
-// Whether they take the launch: it has too many replays for six wavefronts each, or more than one for each CU in the variants whose
-// serving or deciding wavefront has so much to do that it does better alone on its SIMD; and the caches hold enough requests, for two
-// replays wait twice as often for the evicting wavefront.  (us per request.  1,000 replays, four wavefronts each / pairs of eight, caches of
-// 8,000 blocks, 130 requests: 2 replicas 0.844 / 0.671, tuner 0.955 / 0.727, engine model 1.075 / 0.867, proxy 1.338 / 0.988; 16 0.676 / 0.607,
-// 0.787 / 0.676, 0.940 / 0.796, 0.862 / 0.787; 32 0.606 / 0.574, 0.709 / 0.647, 0.806 / 0.690, 0.739 / 0.684.  Caches of 400, 560, 700,
-// 900 and 1,200 blocks, 6.5, 9, 11, 14.5 and 19 requests: 16 replicas 0.738 / 0.782, 0.737 / 0.721, 0.724 / 0.691, 0.712 / 0.669, 0.713 / 0.648;
-// 32 0.677 / 0.757, 0.669 / 0.696, 0.658 / 0.664, 0.655 / 0.638, 0.652 / 0.620; tuner, 32 0.774 / 0.810, 0.760 / 0.751, 0.753 / 0.725, -, -;
-// engine model, 32 0.823 / 0.798 and, of 260 blocks, 0.831 / 0.858; proxy, 16 1.046 / 1.102, 0.995 / 1.002, 0.972 / 0.966, -, -; 32 -, 0.876 /
-// 0.956, 0.858 / 0.907, 0.845 / 0.866, 0.836 / 0.838.  401 replays, six each / pairs, 4,000 blocks: engine model, 16 replicas 0.714 / 0.700, 24 0.675 /
-// 0.657, 32 0.655 / 0.595; proxy, 16 0.763 / 0.717, 24 0.720 / 0.666, 32 0.706 / 0.642, and 12 0.822 / 0.842; the others within 1 %.
+// Whether they take the launch: it has too many replays for six wavefronts each, and the caches hold enough requests, for two replays
+// wait twice as often for the evicting wavefront (PAIR_HELD); or it has more than one for each CU in the variants whose serving or
+// deciding wavefront has so much to do that it does better alone on its SIMD, and the caches hold more still.  How often that
+// wait comes depends on the trace: the lines are where pairs gain on the mean and lose a few per cent on no kind of trace.
+// (us per request.  1,000 replays, four wavefronts each / pairs of eight, users by Zipf's law, caches of 8,000 blocks, 130 requests: 2 replicas 0.844 / 0.671,
+// tuner 0.955 / 0.727, engine model 1.075 / 0.867, proxy 1.338 / 0.988; 16 0.676 / 0.607, 0.787 / 0.676, 0.940 / 0.796, 0.862 / 0.787; 32
+// 0.606 / 0.574, 0.709 / 0.647, 0.806 / 0.690, 0.739 / 0.684; 513, 600, 768 and 900 replays on 32 0.577 / 0.502, 0.579 / 0.516, 0.574 / 0.516, 0.584 / 0.515.
+// How many times as long four wavefronts take as pairs, by requests held, least / mean / most of five traces of 4,000 requests, four of
+// them with users drawn evenly, 767 replays (1,023 on 12 replicas).  Fixed weights, 12 replicas: 9 0.98 / 1.00 / 1.02, 12 1.00 / 1.02 / 1.06; 16: 9 0.92 / 0.98 / 1.03,
+// 15 0.96 / 1.02 / 1.08, 18 1.00 / 1.05 / 1.09; 32: 12 0.90 / 0.92 / 1.00, 18 0.98 / 1.00 / 1.04, 22 1.01 / 1.03 / 1.05.  Tuner, 16: 9 0.95 / 0.97 / 1.02, 15 1.00 / 1.02 /
+// 1.10; 32: 9 0.87 / 0.90 / 0.98, 18 1.00 / 1.02 / 1.07.  Engine model, 24 and 28: 6 0.98 / 1.07 / 1.16 and 0.98 / 1.07 / 1.14; 32: 6 0.91 / 0.96 / 1.01, 12 0.99 / 1.04 / 1.09; with a tuner, 32: 6 0.98 / 1.01 /
+// 1.06.  Proxy, 12: 9 0.97 / 0.99 / 1.04, 12 0.97 / 1.02 / 1.09; 16: 12 0.95 / 0.99 / 1.04, 15 0.97 / 1.03 / 1.07; 24: 15 0.93 / 0.99 / 1.05, 22 0.98 / 1.04 / 1.11; with a
+// tuner, 16: 9 0.95 / 0.99 / 1.09, 12 1.00 / 1.03 / 1.12; with the engine model, 16: 9 1.03 / 1.09 / 1.13, 32: 9 0.94 / 0.98 / 1.03, 18 1.06 / 1.10 / 1.13.
+// Least-request, 32: 6 1.09 / 1.09 / 1.10.
+// Six wavefronts and pairs, the same.  Engine model, 24 replicas: 257 replays, 40 held 0.94 / 0.99 / 1.05; 288, 30 0.96 / 1.00 / 1.03; 320, 20 0.99 / 1.02 / 1.04, 30 1.02 /
+// 1.04 / 1.07.  Proxy, 16: 257, 60 0.95 / 0.96 / 0.97; 288, 40 1.00 / 1.02 / 1.04; 401, 30 0.95 / 0.98 / 1.02, 40 0.96 / 1.00 / 1.04, 60 1.00 / 1.03 / 1.05; 32: 288, 20 0.94 / 0.98 / 1.02,
+// 40 1.03 / 1.06 / 1.08.  Tuner and engine model, 16 and 32, unbounded: 320 0.97 / 0.98 / 0.99, 0.98 / 1.00 / 1.02, 511 0.96 / 0.97 / 0.98, 0.98 / 0.99 / 1.01.  Proxy and engine
+// model, 16: 511, 60 0.97 / 0.98 / 0.99; 24: 320, 60 1.00 / 1.03 / 1.04 and on other traces from 0.96, 401, 40 0.98 / 0.99 / 1.01, 60 0.99 / 1.02 / 1.03; with a tuner, 24: 320, 20 0.96 /
+// 0.98 / 1.01, 40 1.01 / 1.03 / 1.06.  Least-request and engine model, 24: 257 0.97 / 1.00 / 1.02, 288 1.06 / 1.07 / 1.08.
 // Proxy, engine model and tuner together, of which 512 are resident with six wavefronts each; four each / pairs, 513 and 768 replays on 4
 // replicas of 8,000 blocks 1.507 / 1.010 and 1.521 / 1.050, on 12 1.449 / 1.002 and 1.442 / 1.028; 768 on 12 of 800 blocks 1.535 / 1.147.)
+constexpr double PAIR_HELD[][6] = {       // requests; up to 8, 12, 16, 24, 28 and 32 replicas
+    {9, 12, 16, 18, 18, 20},              // fixed weights
+    {8, 8, 14, 17, 18, 18},               // tuner
+    {6, 6, 6, 6, 6, 10},                  // engine model
+    {6, 6, 6, 6, 6, 6},                   // ... and tuner
+    {10, 12, 15, 20, 18, 21},             // proxy
+    {10, 10, 11, 20, 20, 20},             // ... and tuner
+    {10, 10, 10, 20, 20, 20},             // ... and engine model
+    {10, 10, 10, 20, 20, 20},             // all three
+    {9, 9, 9, 12, 12, 12},                // least-request
+    {6, 6, 6, 6, 6, 6}};                  // ... and engine model
 bool pair_replays(const Plan& pl, int mode, bool engine, bool proxy, int held) {
     if (pl.packing == 1) return true;
-    const bool few = pl.R <= 16;         // replicas
-    if (pl.requests_held < (proxy ? (few ? 10.0 : 20.0) : engine ? 6.0 : mode == MODE_ONLINE ? 8.0 : few ? 9.0 : 12.0)) return false;
-    if (pl.P > spread_up_to(pl, held)) return true;
-    return (engine || proxy) && pl.R >= 16 && pl.P > 256 && pl.requests_held >= (engine ? 12.0 : 30.0);
+    const bool tuner = mode == MODE_ONLINE, least_request = mode == MODE_LEAST_REQUEST, few = pl.R < 24;       // replicas
+    if (pl.P > spread_up_to(pl, held)) {
+        const int row = least_request ? (engine ? 9 : 8) : (proxy ? 4 : 0) + (engine ? 2 : 0) + (tuner ? 1 : 0);
+        return pl.requests_held >= PAIR_HELD[row][pl.R <= 8 ? 0 : pl.R <= 12 ? 1 : pl.R <= 16 ? 2 : pl.R <= 24 ? 3 : pl.R <= 28 ? 4 : 5];
+    }
+    if (pl.P < 288 || pl.R < 16) return false;
+    if (proxy && engine && !tuner) return pl.P >= 400 && !few && pl.requests_held >= 60.0;
+    if (proxy) return pl.requests_held >= (few && !engine ? 45.0 : 35.0);
+    return engine && !tuner && pl.requests_held >= (least_request ? 12.0 : 30.0);
 }
 
 // Which of the segment-row kernels takes a launch, `window` the tuner's.  (The answer is the launch's, gorgo_query_replay_workgroups'

@@ -89,3 +89,40 @@ def test_what_the_question_refuses(trace):
     assert call(online=C.byref(on)) < 0
     assert L.gorgo_query_replay_workgroups(None, C.byref(m), None, 0, None, None, None, 4, None, None) < 0
     assert L.gorgo_query_replay_workgroups(handle._h, C.byref(m), None, 0, None, None, None, 4, None, None) == 0
+
+
+# requests that a cache holds from which on pairs take a launch of too many replays for six wavefronts each: up to 8, 12, 16, 24, 28
+# and 32 replicas
+@pytest.mark.parametrize("kw,held", [({}, (9, 12, 16, 18, 18, 20)), (TUNER, (8, 8, 14, 17, 18, 18)), (dict(engine=True), (6, 6, 6, 6, 6, 10)),
+                                     (dict(engine=True, **TUNER), (6,) * 6), (dict(proxy=True), (10, 12, 15, 20, 18, 21)),
+                                     (dict(proxy=True, **TUNER), (10, 10, 11, 20, 20, 20)), (dict(proxy=True, engine=True), (10, 10, 10, 20, 20, 20)),
+                                     (dict(proxy=True, engine=True, **TUNER), (10, 10, 10, 20, 20, 20)),
+                                     (dict(policy="least-request"), (9, 9, 9, 12, 12, 12)), (dict(policy="least-request", engine=True), (6,) * 6)], ids=str)
+def test_caches_of_few_requests(trace, kw, held):
+    for replicas, least in zip([(1, 8), (9, 12), (13, 16), (17, 24), (25, 28), (29, 32)], held):
+        for R in replicas:
+            for P in (769, 1023):
+                assert ask(trace, R, P, least - 0.1, **kw) == FOUR, (R, P)
+                assert ask(trace, R, P, least + 0.01, **kw) == PAIRS, (R, P)
+                assert ask(trace, R, P, least - 0.1, packing=1, **kw) == PAIRS and ask(trace, R, P, packing=0, **kw) == FOUR
+
+
+# ... from how many replays and requests held on they take a launch that six wavefronts would, with 16 and with 24 replicas
+@pytest.mark.parametrize("kw,P,held", [({}, 0, None), (TUNER, 0, None), (dict(engine=True, **TUNER), 0, None), (dict(policy="least-request"), 0, None),
+                                       (dict(engine=True), 288, (30, 30)), (dict(policy="least-request", engine=True), 288, (12, 12)),
+                                       (dict(proxy=True), 288, (45, 35)), (dict(proxy=True, **TUNER), 288, (45, 35)),
+                                       (dict(proxy=True, engine=True), 400, (None, 60)),
+                                       (dict(proxy=True, engine=True, **TUNER), 288, (35, 35))], ids=str)
+def test_pairs_before_six_wavefronts_are_too_many(trace, kw, P, held):
+    if not held:
+        assert ask(trace, 16, 511, **kw) == ask(trace, 32, 512, **kw) == SIX
+        return
+    for replicas, least in zip([(16, 23), (24, 32)], held):
+        for R in replicas:
+            if least is None:
+                assert ask(trace, R, 512, **kw) == SIX
+                continue
+            for n in (P, 511):
+                assert ask(trace, R, n, least - 0.1, **kw) == SIX and ask(trace, R, n, least + 0.01, **kw) == PAIRS
+            assert ask(trace, R, P - 1, **kw) == SIX and ask(trace, 15, n, **kw) == SIX
+            assert ask(trace, R, 511, packing=0, **kw) == SIX
