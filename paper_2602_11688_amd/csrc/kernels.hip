@@ -498,7 +498,7 @@ bool pairs_resident(const Plan& pl, bool proxy, size_t lds, int64_t rows) {
 // How many times as long four wavefronts take as pairs, by requests held, least / mean / most of five traces of 4,000 requests, four of
 // them with users drawn evenly, 767 replays (1,023 on 12 replicas).  Fixed weights, 12 replicas: 9 0.98 / 1.00 / 1.02, 12 1.00 / 1.02 / 1.06; 16: 9 0.92 / 0.98 / 1.03,
 // 15 0.96 / 1.02 / 1.08, 18 1.00 / 1.05 / 1.09; 32: 12 0.90 / 0.92 / 1.00, 18 0.98 / 1.00 / 1.04, 22 1.01 / 1.03 / 1.05.  Tuner, 16: 9 0.95 / 0.97 / 1.02, 15 1.00 / 1.02 /
-// 1.10; 32: 9 0.87 / 0.90 / 0.98, 18 1.00 / 1.02 / 1.07.  Engine model, 24 and 28: 6 0.98 / 1.07 / 1.16 and 0.98 / 1.07 / 1.14; 32: 6 0.91 / 0.96 / 1.01, 12 0.99 / 1.04 / 1.09; with a tuner, 32: 6 0.98 / 1.01 /
+// 1.10; 32: 9 0.87 / 0.90 / 0.98, 18 1.00 / 1.02 / 1.07.  Engine model, 24: 6 0.98 / 1.07 / 1.16; 28: 6 0.98 / 1.07 / 1.14 and on other traces from 0.95, 9 1.02 / 1.11 / 1.17; 32: 6 0.91 / 0.96 / 1.01, 12 0.99 / 1.04 / 1.09; with a tuner, 32: 6 0.98 / 1.01 /
 // 1.06.  Proxy, 12: 9 0.97 / 0.99 / 1.04, 12 0.97 / 1.02 / 1.09; 16: 12 0.95 / 0.99 / 1.04, 15 0.97 / 1.03 / 1.07; 24: 15 0.93 / 0.99 / 1.05, 22 0.98 / 1.04 / 1.11; with a
 // tuner, 16: 9 0.95 / 0.99 / 1.09, 12 1.00 / 1.03 / 1.12; with the engine model, 16: 9 1.03 / 1.09 / 1.13, 32: 9 0.94 / 0.98 / 1.03, 18 1.06 / 1.10 / 1.13.
 // Least-request, 32: 6 1.09 / 1.09 / 1.10.
@@ -512,7 +512,7 @@ bool pairs_resident(const Plan& pl, bool proxy, size_t lds, int64_t rows) {
 constexpr double PAIR_HELD[][6] = {       // requests; up to 8, 12, 16, 24, 28 and 32 replicas
     {9, 12, 16, 18, 18, 20},              // fixed weights
     {8, 8, 14, 17, 18, 18},               // tuner
-    {6, 6, 6, 6, 6, 10},                  // engine model
+    {6, 6, 6, 6, 9, 10},                  // engine model
     {6, 6, 6, 6, 6, 6},                   // ... and tuner
     {10, 12, 15, 20, 18, 21},             // proxy
     {10, 10, 11, 20, 20, 20},             // ... and tuner

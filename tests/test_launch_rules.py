@@ -93,7 +93,7 @@ def test_what_the_question_refuses(trace):
 
 # requests that a cache holds from which on pairs take a launch of too many replays for six wavefronts each: up to 8, 12, 16, 24, 28
 # and 32 replicas
-@pytest.mark.parametrize("kw,held", [({}, (9, 12, 16, 18, 18, 20)), (TUNER, (8, 8, 14, 17, 18, 18)), (dict(engine=True), (6, 6, 6, 6, 6, 10)),
+@pytest.mark.parametrize("kw,held", [({}, (9, 12, 16, 18, 18, 20)), (TUNER, (8, 8, 14, 17, 18, 18)), (dict(engine=True), (6, 6, 6, 6, 9, 10)),
                                      (dict(engine=True, **TUNER), (6,) * 6), (dict(proxy=True), (10, 12, 15, 20, 18, 21)),
                                      (dict(proxy=True, **TUNER), (10, 10, 11, 20, 20, 20)), (dict(proxy=True, engine=True), (10, 10, 10, 20, 20, 20)),
                                      (dict(proxy=True, engine=True, **TUNER), (10, 10, 10, 20, 20, 20)),
