@@ -1,11 +1,11 @@
 """Rows of stamps: eviction by records of one to a wavefront's worth of words, few and many of them at a time, against the CPU
-oracle, on memory that held something else before."""
+oracle, in a workspace that held something else before."""
 import numpy as np
 import pytest
 import torch
 
 import paper_2602_11688_amd as g
-from tests.gpu_helpers import check_population
+from tests.gpu_helpers import assert_replay_equal, load, oracle_eval
 from tests.test_gpu_general_path import _tangled
 
 pytestmark = pytest.mark.gpu
@@ -16,7 +16,19 @@ pytestmark = pytest.mark.gpu
                                               (960, 90, 2, 1100), (961, 90, 3, 1000), (1984, 40, 2, 2100)])
 def test_eviction_over_records_of_every_size(blocks, N, R, cache):
     tr = _tangled(blocks, N=N, R=R, n_ids=4 * blocks + 20, max_blocks=blocks, gap_ms=20)
-    for byte in (0xFF, 0x55):
-        held = torch.full((256 << 20,), byte, dtype=torch.uint8, device="cuda")      # (what the allocator hands out next)
-        del held
-        check_population(tr, g.Model(R, 4, cache, 0.05, 20.0), np.linspace(10.0, 30.0, R), [[0.5, 1.0, 0.1], [0.0, 1.0, 0.0]], [1.0, 0.5])
+    assert int(np.diff(tr.blk_off).max()) <= blocks and (np.diff(tr.blk_off) < blocks - 32).any() == (blocks > 33)
+    model, rtt = g.Model(R, 4, cache, 0.05, 20.0), np.linspace(10.0, 30.0, R)
+    params, scale = np.array([[0.5, 1.0, 0.1], [0.0, 1.0, 0.0]]), np.array([1.0, 0.5])
+    refs = [oracle_eval(tr, model, rtt, w, float(s)) for w, s in zip(params, scale)]
+    handle = load(tr)
+    assert g.replay_workgroups(handle, model, 2) == (1, 4)
+    for byte in (0x00, 0xFF, 0x55):
+        workspace = torch.full((g.workspace_bytes(handle, model, 2),), byte, dtype=torch.uint8, device="cuda:0")
+        res = g.eval_population(handle, model, rtt, params, scale, workspace=workspace)
+        torch.cuda.synchronize()
+        assert res.workspace is workspace
+        got = dict(route=res.route, hit=res.hit_blocks, ttft=res.ttft_ms, e2e=res.e2e_ms, p95_ttft=res.p95_ttft_ms, p95_e2e=res.p95_e2e_ms)
+        got = {k: v.cpu().numpy() for k, v in got.items()}
+        for p in range(2):
+            assert_replay_equal(got, p, refs[p], f"{byte:#x}")
+    handle.close()
