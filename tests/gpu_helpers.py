@@ -40,14 +40,20 @@ def formulation(path, table_factor_percent=None):
 
 @contextlib.contextmanager
 def four_wavefronts():
-    """Calls inside have their replays repeated until a launch has too many of them for six wavefronts each; what they
-    return is one of the repetitions, neither the first nor the last."""
+    """Calls inside have their replays repeated until a launch has too many of them for six wavefronts each and for pairs on eight;
+    what they return is one of the repetitions, neither the first nor the last."""
     def over(call, first):
         def evaluate(*args, **kw):
             args = list(args)
             policy = kw.get("policy", args[3] if call.__name__ == "eval_policy" else "cost-model")
             P = len(np.atleast_1d(args[4])) if policy != "cost-model" else len(kw["params"] if "params" in kw else args[first])
-            n = 768 // P + 1
+            n = 1024 // P + 1
+            if args[0].replay_path()["path"] == 2:
+                online = kw if call.__name__ == "eval_online" else kw.get("online") or {}
+                got = g.replay_workgroups(args[0], args[1], n * P, policy, online.get("window", 128) if online else 0,
+                                          call.__name__ == "eval_engine" or kw.get("engine") is not None, call.__name__ == "eval_proxy")
+                # (or, where a test asks for it, the packed kernel: five, two replays of four that share three)
+                assert got == (1, 4) or got == (2, 5) and g.default_options().replay_packing == 1, (call.__name__, got)
 
             def many(x):
                 x = np.asarray(x.cpu() if hasattr(x, "cpu") else x)
@@ -60,7 +66,7 @@ def four_wavefronts():
             if kw.get("online"):
                 kw["online"] = dict(kw["online"], z=many(kw["online"]["z"]))
             res = call(*args, **kw)
-            assert len(res.p95_ttft_ms) == n * P > 768
+            assert len(res.p95_ttft_ms) == n * P > 1024
             one = slice(n // 2 * P, (n // 2 + 1) * P)
             whole = ("workspace", "rtt_est_ms", "_z", "_tables")
             return dataclasses.replace(res, **{f.name: getattr(res, f.name)[one] for f in dataclasses.fields(res)

@@ -1,6 +1,7 @@
 """GPU parity of replays of four wavefronts with the CPU oracle.  Launches of up to 512 replays (768 with up to 12 replicas) have
-six per replay, so the other tests' few replays nearly all run those; here the same tests run with their replays repeated in
-launches of more than 768, which have four, and what one of the repetitions gives is compared."""
+six per replay and launches of up to 1,024 on up to 32 replicas eight per two, so the other tests' few replays nearly all run
+those; here the same tests run with their replays repeated in launches of more than 1,024, which have four, and what one of
+the repetitions gives is compared."""
 import pytest
 
 from tests import test_gpu_engine, test_gpu_fuzz, test_gpu_launch_edges, test_gpu_online, test_gpu_parity, test_gpu_policies, test_gpu_proxy

@@ -125,7 +125,7 @@ def test_caches_of_few_requests(R, held):
 
 @pytest.mark.parametrize("R,B,cache", [(3, 8, 1), (5, 3, 3), (16, 2, 2), (33, 8, 1), (64, 16, 4), (7, 9, 0), (32, 4, 9), (12, 8, 14)])
 def test_six_wavefronts_or_four(R, B, cache):
-    """The same replays in a launch of 12 and repeated in one of 780: paths of many segments and owners, caches that hold one to
+    """The same replays in a launch of 12 and repeated in one of 1,032: paths of many segments and owners, caches that hold one to
     four of the longest requests (cursors that run into their look-ahead's end), about as many as the look-ahead has records
     (owners are found in it), or everything, requests that complete at
     once, every entry point; bit for bit."""
@@ -134,7 +134,7 @@ def test_six_wavefronts_or_four(R, B, cache):
     rng = np.random.default_rng(R * B)
     model = g.Model(R, B, cache * nmax, 0.05, 2.0)
     rtt = rng.uniform(0.0, 400.0, R)
-    few, times = 12, 65
+    few, times = 12, 86
     params = np.concatenate([rng.uniform(0.05, 2.0, (few - 2, 3)), [[1.0, 0.0, 0.0], [0.0, 1.0, 0.0]]])
     scale = rng.choice([0.02, 0.5, 1.0, 4.0, 100.0], few)
     most = int((tr.in_len.astype(np.int64) + tr.out_len).max())
@@ -162,6 +162,11 @@ def test_six_wavefronts_or_four(R, B, cache):
     names = ("route", "hit_blocks", "believed_hit_blocks", "ttft_ms", "e2e_ms", "p95_ttft_ms", "p95_e2e_ms", "theta_final", "accepted")
     with formulation(2):
         few_of, many_of = list(everything(1)), list(everything(times))
+        for kw in ({}, dict(policy="least-request"), dict(window=16), dict(engine=True), dict(proxy=True), dict(proxy=True, engine=True, window=16),
+                   dict(policy="session-affinity"), dict(policy="random")):
+            dictated = kw.get("policy") in ("session-affinity", "random")
+            one, other = (g.replay_workgroups(handle, model, n, **kw) for n in (few, few * times))
+            assert other == (1, 4) and (one == ((0, 6) if dictated else (1, 6)) or one == (1, 4) and R >= 24 and not kw), kw
     for (label, one), (_, other) in zip(few_of, many_of):
         for name in names:
             a, b = getattr(one, name, None), getattr(other, name, None)
