@@ -235,7 +235,7 @@ def main():
     ap.add_argument("--path", type=int, default=0, help="0 auto, 1 hashed block tables, 2 segment rows (experiments only)")
     ap.add_argument("--sections", action="store_true",
                     help="after the timed region, launch the kernel's timed instantiation once (it reads the clock at marks "
-                         "in each of its four wavefronts) and print the per-section cycle budget to stderr")
+                         "in each of its wavefronts) and print the per-section cycle budget to stderr")
     ap.add_argument("--policies", action="store_true",
                     help="also replay the trace once under each routing policy of the paper's comparison (cost model with "
                          "the tuner's weights, its special cases, least-request, session affinity, random) and report "
@@ -364,10 +364,11 @@ def main():
     n_mean = float(np.diff(wl.trace.blk_off).mean())
     rp = tr.replay_path()
     segs_mean = rp["segment_refs"] / max(N, 1)
+    waves = g.replay_workgroups(tr, model, P, window=128 if args.online else 0, engine=args.engine, proxy=args.proxy)[1]
     if rp["path"] == 2:
         bpr = algorithmic_bytes_per_routing_segments(wl.R, segs_mean, outputs_bytes=8)   # ttft f64
-        # (a workgroup of six wavefronts per replay, of eight per two replays, or of four)
-        kernel = "replay_apart_kernel" if P <= 512 else "replay_apart_pairs_kernel" if P <= 1024 and wl.R <= 32 else "replay_segments_kernel"
+        # (a workgroup of six wavefronts per replay, of eight per two replays, or of four or five)
+        kernel = {6: "replay_apart_kernel", 8: "replay_apart_pairs_kernel"}.get(waves, "replay_segments_kernel")
     else:
         bpr = algorithmic_bytes_per_routing(wl.R, n_mean, hit_mean, outputs_bytes=9)
         kernel = "replay_blocks_kernel"
@@ -406,7 +407,7 @@ def main():
         t_ms = g.last_eval_kernel_ms()["replay_ms"]
         print(f"[bench] timed instantiation: replay kernel {t_ms:.1f} ms = {t_ms * 1e3 / max(N, 1):.3f} us per request step "
               f"(plain kernel: {k_ms * 1e3 / max(N, 1):.3f})", file=sys.stderr)
-        print(section_table(res.sections.cpu().numpy(), N, P, g.replay_workgroups(tr, model, P)[1]), file=sys.stderr, flush=True)
+        print(section_table(res.sections.cpu().numpy(), N, P, waves), file=sys.stderr, flush=True)
         del res
 
     mode = "P online tuners (window 128, hop 32) over the trace per step" if args.online else \

@@ -605,11 +605,16 @@ void launch_segments(SegmentKernel kernel, bool engine, bool proxy, const Plan& 
 // requests, and a short one runs dry.  (us per request, 64 replays on 32 replicas, 5 / 6 / 8 / 11 / 15 records.  Caches of 700 blocks, 11
 // requests: 0.522 / 0.520 / 0.531 / 0.554 / 0.586, proxy 0.769 / 0.745 / 0.741 / 0.759 / 0.794; 1,500: 0.493 / 0.490 / 0.491 / 0.497 /
 // 0.510, proxy 0.752 / 0.730 / 0.706 / 0.706 / 0.715; 3,000, 48 requests: 0.480 / 0.484 / 0.486 / 0.483 / 0.487, proxy 0.712 / 0.685 /
-// 0.672 / 0.668 / 0.670.  Three replicas, 700: 0.583 / 0.579 / 0.580 / 0.582 / 0.587; 3,000: 0.554 / 0.547 / 0.542 / 0.539 / 0.537.)
+// 0.672 / 0.668 / 0.670.  Three replicas, 700: 0.583 / 0.579 / 0.580 / 0.582 / 0.587; 3,000: 0.554 / 0.547 / 0.542 / 0.539 / 0.537.
+// Pairs wait for two replays and have the same line.  1,000 replays of 4,000 requests on 3 to 32 replicas, means of three traces, 64 alike: eleven records from
+// 15 requests held on instead of 40, 16 held up to 6 % slower, 25 up to 3 %, 35 from 1.4 % slower (tuner, 16 replicas) to 1.4 % faster (fixed weights, 32); from
+// 100 on, 60 and 90 held up to 2 % slower.)
 constexpr double LOOK_FEW_HELD = 40.0;       // requests
 int32_t apart_look(const Plan& pl, bool proxy) { return pl.requests_held < LOOK_FEW_HELD ? (proxy ? 8 : 6) : 11; }
 static_assert(APART_LOOK > 11);
-constexpr int LOOK_FROM = 4;                 // from when on: the longest requests that there is still room for
+// From when on: the longest requests that there is still room for.  (The same launches.  One request instead of four: 16 held up to 4 %
+// faster, 100 held up to 1.5 % slower, else within 1.3 %.  Sixteen: 1,000 requests into caches of 25 up to 19 % slower, 4,000 into caches of 60 up to 6 %.)
+constexpr int LOOK_FROM = 4;
 
 // Dictated routes: the shares laid out, a replay per share, the outputs back in their order.
 int launch_each(const gorgo_trace* t, const Plan& pl, int mode, bool engine, const SegArgs& a, char* ws, hipStream_t s) {

@@ -1,9 +1,11 @@
-// Replay kernel, segment formulation, for launches that leave most of the chip idle: six wavefronts per replay.
+// Replay kernels, segment formulation, for launches that leave most of the chip idle: six wavefronts per replay, or eight for two.
 //
 // A replay is one dependent chain of requests, so a launch of few replays takes as long as one of them.  What
 // replay_segments.h does in four wavefronts is here spread over six, which costs a quarter more vector instructions per
 // request (the wavefronts read the announcement and the descriptors each for themselves) and shortens the longest of
-// the chains: with a replay per SIMD the instructions are what counts, with two per CU or fewer the chain is.  The state, the
+// the chains: with a replay per SIMD the instructions are what counts, with two per CU or fewer the chain is.  With up to 32 replicas
+// half of a wavefront's lanes idle where a lane is a replica: two replays share such wavefronts, in halves, and have a
+// serving and a retiring one each (PACK = 2), so that four per CU are resident with the chain little longer.  The state, the
 // descriptors and the results are the same.
 //   The deciding wavefront only matches, scores, takes the minimum and announces.  Meeting X(r).
 //   The evicting wavefront holds the eviction cursors.  After X(r) it moves the one of the replica that r went to, while r + 1
