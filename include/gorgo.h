@@ -108,7 +108,7 @@ typedef struct gorgo_model {
  *     gorgo_query_replay_workgroups tells what a launch gets.
  *   handover_poll_limit: how many times wavefronts that hand over through polled words poll before a replay is
  *     given up (default 2^24; must be >= 0).  The value has no effect and no replay is given up: the wavefronts of a replay
- *     meet at workgroup barriers, and where one looks at a word until another has written it (replays of six wavefronts), the
+ *     meet at workgroup barriers, and where one looks at a word until another has written it (six and eight wavefronts), the
  *     writer waits for nothing but barriers that it has passed.
  *   table_factor_percent: the open-addressed cache tables of the block-table formulation get at least
  *     ceil(factor/100 * (cache_blocks + max blocks of a request)) slots, rounded up to a power of two
