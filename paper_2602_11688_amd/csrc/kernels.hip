@@ -491,7 +491,8 @@ bool pairs_resident(const Plan& pl, bool proxy, size_t lds, int64_t rows) {
 // Whether they take the launch: it has too many replays for six wavefronts each, and the caches hold enough requests, for two replays
 // wait twice as often for the evicting wavefront (PAIR_HELD); or it has more than one for each CU in the variants whose serving or
 // deciding wavefront has so much to do that it does better alone on its SIMD, and the caches hold more still.  How often that
-// wait comes depends on the trace: the lines are where pairs gain on the mean and lose a few per cent on no kind of trace.
+// wait comes depends on the trace: the lines are where pairs gain on the mean and lose no more than some five per cent on any
+// one (proxy of any index, 16 replicas, 288 replays, 45 held 0.94 to 1.06; 2 replicas, an index that never forgets, 10 held 0.96 to 1.06).
 // (us per request.  1,000 replays, four wavefronts each / pairs of eight, users by Zipf's law, caches of 8,000 blocks, 130 requests: 2 replicas 0.844 / 0.671,
 // tuner 0.955 / 0.727, engine model 1.075 / 0.867, proxy 1.338 / 0.988; 16 0.676 / 0.607, 0.787 / 0.676, 0.940 / 0.796, 0.862 / 0.787; 32
 // 0.606 / 0.574, 0.709 / 0.647, 0.806 / 0.690, 0.739 / 0.684; 513, 600, 768 and 900 replays on 32 0.577 / 0.502, 0.579 / 0.516, 0.574 / 0.516, 0.584 / 0.515.
